@@ -16,5 +16,6 @@ __all__ = list(_BINDING_NAMES)
 def __getattr__(name):
     if name in _BINDING_NAMES:
         from . import binding
-        return getattr(binding, name)
+        globals().update({n: getattr(binding, n) for n in _BINDING_NAMES})     # the next access finds the name itself
+        return globals()[name]
     raise AttributeError(name)

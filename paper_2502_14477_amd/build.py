@@ -1,4 +1,4 @@
-"""Build libesa.so (HIP, gfx950 only) in-tree.  `python -m paper_2502_14477_amd.build`."""
+"""Build libesa.so (HIP, gfx950 only) and the Python binding's native half, _native.so, in-tree.  `python -m paper_2502_14477_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -11,6 +11,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libesa.so")
+NATIVE = os.path.join(PKG, "_native.so")
 
 SOURCES = ["esa_api.hip", "compress.hip", "score.hip", "topk.hip", "gather.hip", "attend.hip", "attend_mfma.hip", "attend_decode.hip", "rope.hip"]
 
@@ -45,6 +46,19 @@ def _run(cmd):
     return out
 
 
+def _native_flags():
+    """Compiler and linker flags of the binding: host code against torch's and Python's headers."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    includes = cpp_extension.include_paths("cuda") + [sysconfig.get_paths()["include"]]
+    libs = cpp_extension.library_paths("cuda")
+    compile_flags = ["-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+                     "-I", os.path.join(ROOT, "include")] + [f for i in includes for f in ("-isystem", i)]
+    link_flags = ["-shared", "-L" + PKG, "-lesa", "-Wl,-rpath,$ORIGIN"] + ["-L" + d for d in libs] + \
+        ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-lamdhip64"]
+    return compile_flags, link_flags
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     hipcc = _hipcc()
@@ -56,9 +70,15 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
             print(out)
         return obj
 
+    native_compile, native_link = _native_flags()
+    native_obj = os.path.join(OBJ, "binding.o")
+
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        native = pool.submit(_run, ["g++", *native_compile, "-c", os.path.join(CSRC, "binding.cpp"), "-o", native_obj])
         objs = list(pool.map(compile_one, SOURCES))
+        native.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB])
+    _run(["g++", native_obj, *native_link, "-o", NATIVE])
     return LIB
 
 
