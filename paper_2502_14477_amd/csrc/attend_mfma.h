@@ -1,4 +1,4 @@
-// Matrix-core attention kernel for bf16 storage, head size 128 (declared here, defined in attend_mfma.hip).
+// Matrix-core attention kernel for bf16 storage, head sizes 64 and 128 (declared here, defined in attend_mfma.hip).
 #pragma once
 #include "esa_common.h"
 

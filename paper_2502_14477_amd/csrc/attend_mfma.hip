@@ -1,9 +1,11 @@
-// Selected attention (Eq. 1) on the matrix cores: bf16 storage, head size 128.
+// Selected attention (Eq. 1) on the matrix cores: bf16 storage, head sizes 128 and 64.
 //
 // Work decomposition.  The query heads of one KV group share keys and values, so a workgroup
-// owns 256 "rows" = (heads of one KV group) x (256/G consecutive current tokens) and one slice of
-// the virtual key sequence [I | M_k | L | C]; slices of one row tile are merged afterwards with
-// the log-sum-exp rule of Algorithm 1 (esa_attend_merge).  Eight waves of 32 rows each, two waves
+// owns up to 256 "rows" = (up to 256/G consecutive current tokens) x (heads of one KV group), numbered
+// token by token, and one slice of the virtual key sequence [I | M_k | L | C]; slices of one row tile
+// are merged afterwards with the log-sum-exp rule of Algorithm 1 (esa_attend_merge).  The chunk's tokens are
+// shared out evenly over the row tiles, in units of a wave's 32 rows, and a wave without rows, or whose rows see
+// no key of a tile, leaves the tile's arithmetic out.  Eight waves of 32 rows each, two waves
 // per SIMD, so that one wave's softmax arithmetic overlaps the other's matrix instructions; the
 // kernel stays under 256 registers per lane for that.  Workgroups are numbered so that all
 // workgroups of one (batch element, KV head) land on the same XCD and share its L2.
@@ -22,7 +24,8 @@
 // global_load_lds_dwordx4 deposits 16 bytes per lane at consecutive LDS addresses, so one wave
 // instruction brings four 256-byte rows, and which 16 bytes of its row a lane fetches is chosen
 // such that the rows land XOR-swizzled (K: 16-byte pieces by row % 16, V: 64-byte chunks by
-// row % 4), which makes the fragment reads below free of bank conflicts without padding.  K
+// row % 4; with head size 64, where two rows share the 256 bytes that the banks cover, by the same bits of
+// row / 2), which makes the fragment reads below free of bank conflicts without padding.  K
 // fragments are plain 16-byte reads.  V stays row-major [key][dim]; its transposed fragments (eight
 // keys of one head dimension per lane) come from ds_read_b64_tr_b16, which hands lane i of a 16-lane
 // group element i%4 of the 8 bytes addressed by lanes 4e + i/4 (e = 0..3): sixteen lanes that point
@@ -45,14 +48,13 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void global_void;
 
-constexpr int kD = 128;             // head size
 constexpr int kKT = 64;             // virtual keys per tile
 constexpr int kRows = 256;          // query rows per workgroup
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kTileElems = kKT * kD;    // one K or V tile in LDS: 64 rows of 256 bytes, unpadded, swizzled
-constexpr int kMaxSplits = 8;
-constexpr int kMaxSlots = 2 * kMaxSplits;   // two-call form: local slices, then selected slices
+constexpr int kMaxSlots = 16;           // partial results per row
+constexpr int kMaxSplits = 16;          // slices of the key sequence, one-call form
+constexpr int kMaxSelSplits = 8;        // two-call form: at most half as many local slices, then the selected ones
 constexpr int kMinLc = 16;          // shorter chunks go to the plain kernel
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.f;        // the softmax reference lags the running maximum by at most 2^8
@@ -83,12 +85,14 @@ struct AttendArgs {
   KeyView view[2];
   bf16_t* out;
   float* lse;
-  uint16_t* part_o;   // [batch][n_slot][l_c][h][128] fp16 partial outputs, un-normalised, scaled by 2^-E per row
+  uint16_t* part_o;   // [batch][n_slot][l_c][h][D] fp16 partial outputs, un-normalised, scaled by 2^-E per row
   float* part_ml;     // [batch][n_slot][l_c][h][2]   softmax reference (log2 domain) + E, and sum * 2^-E
   const char* k_sel;
   const char* v_sel;
   uint32_t sel_bytes;               // row stride of the gathered buffers
-  int l_c, h, h_kv, group, qpt, n_qt, batch;
+  int l_c, h, h_kv, group, group_log2;
+  int qpt, n_qt;                    // tokens per row tile (a whole number of waves' rows, at most 256 rows), row tiles
+  int batch;
   int xcd_mapping;                  // 1: (batch, KV head) pairs are a multiple of 8
   int n_slot;         // slots per row in the partial-result arrays
   int to_slots;       // 1: write partial results even when the launch has a single slice
@@ -139,7 +143,21 @@ __device__ __forceinline__ RowRef row_ref(const KeyView& V, const int32_t* sidx,
   return r;
 }
 
+// Swizzles of the LDS tiles: the 16-byte slot of piece p of K row R is p ^ k_swizzle(R), the 64-byte slot of chunk c
+// of V row R is c ^ v_swizzle(R).
+template <int D> __device__ __forceinline__ uint32_t k_swizzle(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+template <int D> __device__ __forceinline__ uint32_t v_swizzle(uint32_t row) { return D == 128 ? row & 3 : (row >> 1) & 1; }
+
+template <int D>
 __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
+  static_assert(D == 64 || D == 128, "swizzles and store patterns");
+  constexpr int kTileElems = kKT * D;     // one K or V tile in LDS: 64 unpadded rows, swizzled
+  constexpr int kPieces = D / 8;          // 16-byte pieces of a row
+  constexpr int kLoadRows = 64 / kPieces; // rows that one wave instruction brings
+  constexpr int kMyRows = kKT / (kLoadRows * kWaves);   // rows of a tile that a lane fetches a piece of (2 or 1)
+  constexpr int kRowStep = kLoadRows * kWaves;          // distance between them
+  constexpr int kKS = D / 16;             // reduction steps of the first product
+  constexpr int kMD = D / 32;             // 32-dim tiles of the second product
   // Two stages of a K tile and a V tile.  Separate arrays, so that the compiler can tell a load into one
   // stage from a fragment read of the other and does not wait for the load first.
   __shared__ __attribute__((aligned(1024))) bf16_t k_st0[kTileElems];
@@ -189,10 +207,10 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   }
   const int split = slice - (vw ? a.view[0].n_split : 0);        // slice number inside the view
 
-  const char* kc = V.k_cache + (int64_t)b * V.cache_bs_bytes + (int64_t)g * kD * 2;
-  const char* vc = V.v_cache + (int64_t)b * V.cache_bs_bytes + (int64_t)g * kD * 2;
-  const char* ksl = a.k_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * kD * 2 : 0);
-  const char* vsl = a.v_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * kD * 2 : 0);
+  const char* kc = V.k_cache + (int64_t)b * V.cache_bs_bytes + (int64_t)g * D * 2;
+  const char* vc = V.v_cache + (int64_t)b * V.cache_bs_bytes + (int64_t)g * D * 2;
+  const char* ksl = a.k_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
+  const char* vsl = a.v_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
 
   // ---- this workgroup's rows and key slice
   const int q0 = qt * a.qpt;
@@ -203,48 +221,51 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const uint32_t tile_end = (uint32_t)((uint64_t)n_tiles * (split + 1) / V.n_split);
   const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
 
-  // ---- this wave's 32 rows: one head, 32 consecutive current tokens, one per lane (both half-waves)
-  const int tph = a.qpt / 32;                                      // 32-row tiles per head
-  const int head = g * a.group + wave / tph;
-  const int c = q0 + (wave % tph) * 32 + r;
-  const bool c_ok = c < a.l_c;
-  const int cc = c_ok ? c : a.l_c - 1;                             // rows past the chunk repeat its last token
+  // ---- this wave's 32 rows (32/G consecutive current tokens, the group's heads of each), one per lane (both half-waves)
+  const int row_in_tile = wave * 32 + r;
+  const int head = g * a.group + (row_in_tile & (a.group - 1));
+  const int c = q0 + (row_in_tile >> a.group_log2);
+  const bool c_ok = c <= c_last;
+  const int cc = c_ok ? c : c_last;                                // rows past the tile repeat its last token
   const uint32_t vis = V.n_fixed + (V.with_chunk ? cc + 1 : 0);
   const uint32_t lim = vis < k_end ? vis : k_end;                  // first virtual key this lane's query may NOT see
-  const uint32_t lim_lo = __shfl(lim, 0, 64);                      // smallest limit in the wave (r = 0)
-  bf16x8 qf[kD / 16];                                              // loaded below, behind the first tile's loads
+  const uint32_t lim_lo = __builtin_amdgcn_readlane(lim, 0);       // smallest limit in the wave (r = 0)
+  // largest limit in the wave; 0 for a wave without rows
+  const bool wave_has_rows = q0 + ((wave * 32) >> a.group_log2) <= c_last;
+  const uint32_t lim_hi = wave_has_rows ? __builtin_amdgcn_readlane(lim, 31) : 0;
+  bf16x8 qf[kKS];                                                  // loaded below, behind the first tile's loads
 
-  f32x16 o[4];
+  f32x16 o[kMD];
 #pragma unroll
-  for (int md = 0; md < 4; ++md)
+  for (int md = 0; md < kMD; ++md)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[md][v] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
   // ---- staging of one tile: global -> LDS directly, 16 bytes per lane.  A wave instruction fills 1 KB =
-  // four rows; wave w brings row groups w and w + 8 of K and of V.  Lane l fills 16-byte slot l%16 of row
-  // l/16 of its group; the piece of the global row it fetches for that slot undoes the swizzle:
-  // K slot s of row R holds piece s ^ (R%16); V slot s of row R holds piece s%4 of chunk (s/4) ^ (R%4).
-  const uint32_t st_row = 4 * wave + (lane >> 4);                  // first of this lane's two rows (second: + 32)
-  const uint32_t st_slot = lane & 15;
-  const uint32_t kcol = (st_slot ^ (st_row & 15)) * 16;            // byte column of the piece fetched for K
-  const uint32_t vcol = ((((st_slot >> 2) ^ (st_row & 3)) << 2) | (st_slot & 3)) * 16;   // ... for V
+  // four rows of 256 bytes or eight of 128; wave w brings row groups w and (head size 128) w + 8 of K and of V.
+  // Lane l fills one 16-byte slot of a row of its group; the piece of the global row it fetches for that slot undoes
+  // the swizzle.
+  const uint32_t st_row = kLoadRows * wave + lane / kPieces;       // first of this lane's rows (second: + 32)
+  const uint32_t st_slot = lane % kPieces;
+  const uint32_t kcol = (st_slot ^ k_swizzle<D>(st_row)) * 16;     // byte column of the piece fetched for K
+  const uint32_t vcol = ((((st_slot >> 2) ^ v_swizzle<D>(st_row)) << 2) | (st_slot & 3)) * 16;   // ... for V
   auto dma16 = [&](const char* src, bf16_t* dst_wave_uniform) {
     __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)dst_wave_uniform, 16, 0, 0);
   };
-  // Index-driven selected rows (the gather folded into this kernel): the two cache rows this lane fetches
+  // Index-driven selected rows (the gather folded into this kernel): the cache rows this lane fetches
   // for a tile that lies inside the selected segment are looked up one tile ahead of the tile's loads,
   // so that the look-up is not a dependent round trip in front of them.
   const int32_t* sidx = V.sel_idx ? V.sel_idx + (int64_t)b * V.idx_bs : nullptr;
   // The entries are kept as loaded and clamped where tile_load uses them, a whole tile later: clamping here
   // would be a use, and the wait in front of it would also wait for the tile loads issued just before, which
   // are meant to land during the tile's arithmetic.
-  int32_t idx_a = 0, idx_b = 0;
+  int32_t picked[kMyRows] = {};
   auto idx_prefetch = [&](uint32_t t) {
     const uint32_t j0 = t * kKT;
     if (sidx && t < tile_end && j0 >= V.i_end && j0 + kKT <= V.i_end + V.n_sel) {
-      idx_a = sidx[j0 - V.i_end + st_row];
-      idx_b = sidx[j0 - V.i_end + st_row + 32];
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) picked[u] = sidx[j0 - V.i_end + st_row + kRowStep * u];
     }
   };
   // a middle token's position, clamped so that a bad index cannot leave the cache
@@ -266,33 +287,36 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
       seg = 0;
       row0 = j0 - sel_end + V.l_start;
     }
-    bf16_t* kd0 = kt + wave * 512;                                 // 1 KB per row group
-    bf16_t* kd1 = kt + (wave + 8) * 512;
-    bf16_t* vd0 = vt + wave * 512;
-    bf16_t* vd1 = vt + (wave + 8) * 512;
-    if (seg == 1 && sidx) {             // rows idx_a / idx_b of the cache, looked up by idx_prefetch for this tile
-      const uint32_t row_a = cache_row(idx_a), row_b = cache_row(idx_b);
-      dma16(kc + ((uint64_t)row_a * V.tok_bytes + kcol), kd0);
-      dma16(kc + ((uint64_t)row_b * V.tok_bytes + kcol), kd1);
-      dma16(vc + ((uint64_t)row_a * V.tok_bytes + vcol), vd0);
-      dma16(vc + ((uint64_t)row_b * V.tok_bytes + vcol), vd1);
+    bf16_t* kd = kt + wave * 512;                                  // 1 KB per row group
+    bf16_t* vd = vt + wave * 512;
+    constexpr int kGroupStep = kWaves * 512;
+    if (seg == 1 && sidx) {             // cache rows looked up by idx_prefetch for this tile
+      uint64_t off[kMyRows];
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) off[u] = (uint64_t)cache_row(picked[u]) * V.tok_bytes;
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) dma16(kc + (off[u] + kcol), kd + kGroupStep * u);
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) dma16(vc + (off[u] + vcol), vd + kGroupStep * u);
     } else if (seg >= 0) {
       const uint32_t stride = seg ? a.sel_bytes : V.tok_bytes;
       const char* kb = (seg ? ksl : kc) + (uint64_t)row0 * stride;
       const char* vbase = (seg ? vsl : vc) + (uint64_t)row0 * stride;
-      dma16(kb + (st_row * stride + kcol), kd0);
-      dma16(kb + ((st_row + 32) * stride + kcol), kd1);
-      dma16(vbase + (st_row * stride + vcol), vd0);
-      dma16(vbase + ((st_row + 32) * stride + vcol), vd1);
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) dma16(kb + ((st_row + kRowStep * u) * stride + kcol), kd + kGroupStep * u);
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) dma16(vbase + ((st_row + kRowStep * u) * stride + vcol), vd + kGroupStep * u);
     } else {
-      uint32_t ja = j0 + st_row, jb = j0 + st_row + 32;
-      ja = ja < k_end ? ja : k_end - 1;                            // the tail repeats a key; masked below
-      jb = jb < k_end ? jb : k_end - 1;
-      const RowRef ra = row_ref(V, sidx, a.sel_bytes, ja), rb = row_ref(V, sidx, a.sel_bytes, jb);
-      dma16((ra.in_sel ? ksl : kc) + ra.off + kcol, kd0);
-      dma16((rb.in_sel ? ksl : kc) + rb.off + kcol, kd1);
-      dma16((ra.in_sel ? vsl : vc) + ra.off + vcol, vd0);
-      dma16((rb.in_sel ? vsl : vc) + rb.off + vcol, vd1);
+      RowRef ref[kMyRows];
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) {
+        const uint32_t j = j0 + st_row + kRowStep * u;
+        ref[u] = row_ref(V, sidx, a.sel_bytes, j < k_end ? j : k_end - 1);      // the tail repeats a key; masked below
+      }
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) dma16((ref[u].in_sel ? ksl : kc) + ref[u].off + kcol, kd + kGroupStep * u);
+#pragma unroll
+      for (int u = 0; u < kMyRows; ++u) dma16((ref[u].in_sel ? vsl : vc) + ref[u].off + vcol, vd + kGroupStep * u);
     }
   };
   // Every load of this wave has landed in LDS (vmcnt = 0; the other counters are left alone).
@@ -306,31 +330,32 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   // ---- one tile: S^T = K Q^T, online softmax, O^T += V^T P^T
   auto tile_math = [&](uint32_t t, const bf16_t* kt, const bf16_t* vt) {
     const uint32_t j0 = t * kKT;
+    if (j0 >= lim_hi) return;           // no row of this wave sees any of the tile's keys
     f32x16 s[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) s[mt][v] = 0.f;
-    // The sixteen K fragments of the tile are requested eight ahead of the matrix instructions that use
+    // The K fragments of the tile are requested half of them ahead of the matrix instructions that use
     // them (the order is pinned below): LDS latency is paid once per tile, not once per reduction step.
-    bf16x8 kf[kD / 16][2];
+    bf16x8 kf[kKS][2];
 #pragma unroll
-    for (int ks16 = 0; ks16 < kD / 16; ++ks16)
+    for (int ks16 = 0; ks16 < kKS; ++ks16)
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
-        kf[ks16][mt] = *(const bf16x8*)&kt[(32 * mt + r) * kD + (((2 * ks16 + hi) ^ (r & 15)) << 3)];
+        kf[ks16][mt] = *(const bf16x8*)&kt[(32 * mt + r) * D + (((2 * ks16 + hi) ^ k_swizzle<D>(r)) << 3)];
 #pragma unroll
-    for (int ks16 = 0; ks16 < kD / 16; ++ks16)
+    for (int ks16 = 0; ks16 < kKS; ++ks16)
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
         s[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks16][mt], qf[ks16], s[mt], 0, 0, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, kKS, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kKS / 2; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, kKS, 0);
 
     // ---- mask keys beyond each query's limit (causal diagonal, end of the slice)
     if (j0 + kKT > lim_lo) {
@@ -370,7 +395,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     l_run = l_run * corr + psum;
     if (__ballot(corr != 1.f) != 0ull) {
 #pragma unroll
-      for (int md = 0; md < 4; ++md)
+      for (int md = 0; md < kMD; ++md)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[md][v] *= corr;
     }
@@ -388,25 +413,26 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
       pf[kp] = *(bf16x8*)&w;
     }
 
-    // ---- O^T += V^T P^T.  Row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot c ^ (key%4).
+    // ---- O^T += V^T P^T.  Row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot
+    // c ^ v_swizzle(key), which keys 4 apart share.
 #pragma unroll
     for (int kp = 0; kp < 4; ++kp)
 #pragma unroll
-      for (int md = 0; md < 4; ++md) {
-        const bf16_t* vp = vt + (16 * kp + 4 * hi + tr_key) * kD + ((md ^ tr_key) << 5) + tr_dim;
+      for (int md = 0; md < kMD; ++md) {
+        const bf16_t* vp = vt + (16 * kp + 4 * hi + tr_key) * D + ((md ^ v_swizzle<D>(tr_key)) << 5) + tr_dim;
         const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);             // keys 16kp + 4hi + 0..3
-        const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * kD));  // keys 16kp + 8 + 4hi + 0..3
+        const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D));  // keys 16kp + 8 + 4hi + 0..3
         const i16x8 both = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
         o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[kp], o[md], 0, 0, 0);
       }
-    // the V fragments of sixteen keys (eight reads) are requested ahead of the four matrix instructions that use them
-    __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);
+    // the V fragments of sixteen keys (2 kMD reads) are requested ahead of the kMD matrix instructions that use them
+    __builtin_amdgcn_sched_group_barrier(0x100, 4 * kMD, 0);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, kMD, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2 * kMD, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kMD, 0);
   };
 
   // The first tile's loads go out before the query fragments' so that the two round trips overlap.
@@ -414,13 +440,13 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   if (tile_begin < tile_end) tile_load(tile_begin * kKT, k_st0, v_st0);
   idx_prefetch(tile_begin + 1);
   {
-    const bf16_t* qp = V.q + (int64_t)b * V.q_bs + ((int64_t)cc * a.h + head) * kD + hi * 8;
+    const bf16_t* qp = V.q + (int64_t)b * V.q_bs + ((int64_t)cc * a.h + head) * D + hi * 8;
 #pragma unroll
-    for (int ks16 = 0; ks16 < kD / 16; ++ks16) qf[ks16] = *(const bf16x8*)(qp + ks16 * 16);
+    for (int ks16 = 0; ks16 < kKS; ++ks16) qf[ks16] = *(const bf16x8*)(qp + ks16 * 16);
     // Pin the fragments as arrived values here: otherwise every use inside the tile loop carries a
     // wait on the vector-memory counter.
 #pragma unroll
-    for (int ks16 = 0; ks16 < kD / 16; ++ks16) asm volatile("" : "+v"(qf[ks16]));
+    for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(qf[ks16]));
   }
   // Two tiles per trip so that every stage is named statically.  At each barrier tile t is in LDS and
   // every wave is done with tile t-1, whose stage the loads issued right after the barrier overwrite.
@@ -441,7 +467,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
 
   // ---- results.  Accumulator register v of tile md is head-dim 32*md + 8*(v/4) + 4*hi + v%4 of this
   // lane's query, so a lane holds its whole output row in 8-byte pieces.  The rows are narrowed to 16
-  // bits and turned into whole 256-byte rows in LDS (free by now), from where each wave writes its own
+  // bits and turned into whole rows in LDS (free by now), from where each wave writes its own
   // 32 rows with fully coalesced 16-byte stores.  Final outputs are normalised and rounded to bf16.
   // Partial results of a key slice stay un-normalised and are stored as fp16 with a per-row power-of-two
   // scale 2^-E that brings the row's largest magnitude to about 2^13 (fp16's 11-bit significand keeps the
@@ -455,7 +481,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   if (!final_out) {
     float amax = 0.f;
 #pragma unroll
-    for (int md = 0; md < 4; ++md)
+    for (int md = 0; md < kMD; ++md)
 #pragma unroll
       for (int v = 0; v < 16; ++v) amax = fmaxf(amax, __builtin_fabsf(o[md][v]));
     amax = halves_max(amax);
@@ -467,10 +493,10 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   }
   __syncthreads();                       // every wave is done with the last tile
   {
-    // wave w's 32 rows of 256 bytes go to half (w%2) of stage array w/2, 16-byte slots swizzled by row % 16
-    uint16_t* ot = (uint16_t*)(wave < 2 ? k_st0 : wave < 4 ? k_st1 : wave < 6 ? v_st0 : v_st1) + ((wave & 1) * 32 + r) * kD;
+    // wave w's 32 rows go to half (w%2) of stage array w/2, 16-byte slots swizzled as in a K tile
+    uint16_t* ot = (uint16_t*)(wave < 2 ? k_st0 : wave < 4 ? k_st1 : wave < 6 ? v_st0 : v_st1) + ((wave & 1) * 32 + r) * D;
 #pragma unroll
-    for (int md = 0; md < 4; ++md)
+    for (int md = 0; md < kMD; ++md)
 #pragma unroll
       for (int vg = 0; vg < 4; ++vg) {
         uint2 w;
@@ -481,29 +507,29 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
           w.x = pack_f16x2(o[md][4 * vg + 0] * inv, o[md][4 * vg + 1] * inv);
           w.y = pack_f16x2(o[md][4 * vg + 2] * inv, o[md][4 * vg + 3] * inv);
         }
-        *(uint2*)(ot + (((4 * md + vg) ^ (r & 15)) << 3) + 4 * hi) = w;
+        *(uint2*)(ot + (((4 * md + vg) ^ k_swizzle<D>(r)) << 3) + 4 * hi) = w;
       }
   }
   __syncthreads();
-  const int c_wave = q0 + (wave % tph) * 32;                        // first current token of this wave's rows
   uint16_t* dst;
   if (final_out) {
-    dst = (uint16_t*)a.out + (int64_t)b * a.out_bs + ((int64_t)c_wave * a.h + head) * kD;
+    dst = (uint16_t*)a.out + (int64_t)b * a.out_bs;
   } else {
     const int64_t prow0 = ((int64_t)(b * a.n_slot + V.slot0 + split) * a.l_c) * a.h;
-    dst = a.part_o + (prow0 + (int64_t)c_wave * a.h + head) * kD;
+    dst = a.part_o + prow0 * D;
     if (hi == 0 && c_ok) {
       float2 ml = {m_store, l_store};
       *(float2*)(a.part_ml + (prow0 + (int64_t)c * a.h + head) * 2) = ml;
     }
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int rw = 4 * i + (lane >> 4), piece = lane & 15;
-    if (c_wave + rw < a.l_c) {
+  for (int i = 0; i < kPieces / 2; ++i) {
+    const int rw = kLoadRows * i + lane / kPieces, piece = lane % kPieces;
+    const int row = wave * 32 + rw, tok = q0 + (row >> a.group_log2), hd = g * a.group + (row & (a.group - 1));
+    if (tok <= c_last) {
       const uint16_t* ob = (const uint16_t*)(wave < 2 ? k_st0 : wave < 4 ? k_st1 : wave < 6 ? v_st0 : v_st1);
-      const uint4 w = *(const uint4*)(ob + ((wave & 1) * 32 + rw) * kD + ((piece ^ (rw & 15)) << 3));
-      *(uint4*)(dst + (int64_t)rw * a.h * kD + piece * 8) = w;
+      const uint4 w = *(const uint4*)(ob + ((wave & 1) * 32 + rw) * D + ((piece ^ k_swizzle<D>(rw)) << 3));
+      *(uint4*)(dst + ((int64_t)tok * a.h + hd) * D + piece * 8) = w;
     }
   }
   if (final_out && a.lse && hi == 0 && c_ok)
@@ -512,14 +538,16 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
 
 // Algorithm 1's merge over partial results (un-normalised outputs and sums, both relative to the slice's
 // reference m_s): weights 2^(m_s - M) with the maximum subtracted first.
-// The slots in use are [0, ns_a) and [slot_b, slot_b + ns_b) of n_slot.  16 lanes per row (eight
-// head-dims, 16 bytes of fp16 partials, each), sixteen rows per workgroup.
+// The slots in use are [0, ns_a) and [slot_b, slot_b + ns_b) of n_slot.  D / 8 lanes per row (eight
+// head-dims, 16 bytes of fp16 partials, each), sixteen or thirty-two rows per workgroup.
+template <int D>
 __global__ __launch_bounds__(256) void esa_attend_merge(const uint16_t* __restrict__ part_o,
                                                         const float* __restrict__ part_ml, int n_slot, int ns_a,
                                                         int slot_b, int ns_b, int64_t rows, bf16_t* __restrict__ out,
                                                         float* __restrict__ lse, int64_t out_bs, int64_t lse_bs) {
-  const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int d8 = (threadIdx.x & 15) * 8;
+  constexpr int kLanes = D / 8;
+  const int64_t row = (int64_t)blockIdx.x * (256 / kLanes) + threadIdx.x / kLanes;
+  const int d8 = (threadIdx.x % kLanes) * 8;
   const int b = blockIdx.y;
   if (row >= rows) return;
   // Every load of the row goes out before the first use (one round trip): the slices' (maximum, sum)
@@ -536,7 +564,7 @@ __global__ __launch_bounds__(256) void esa_attend_merge(const uint16_t* __restri
       const float2 ml = *(const float2*)(part_ml + prow * 2);
       m[s] = ml.x;
       l[s] = ml.y;
-      po[s] = *(const uint4*)(part_o + prow * kD + d8);
+      po[s] = *(const uint4*)(part_o + prow * D + d8);
     }
   }
   float M = -INFINITY;
@@ -564,21 +592,40 @@ __global__ __launch_bounds__(256) void esa_attend_merge(const uint16_t* __restri
   w4.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
   w4.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
   w4.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
-  *(uint4*)(out + (int64_t)b * out_bs + row * kD + d8) = w4;
+  *(uint4*)(out + (int64_t)b * out_bs + row * D + d8) = w4;
   if (lse && d8 == 0) lse[(int64_t)b * lse_bs + row] = (M + __builtin_amdgcn_logf(L)) * kLn2;
 }
 
+// Row tiles: as few as hold the chunk at 256 rows each, the tokens shared out evenly in units of a wave's 32 rows.
+struct RowTiles {
+  int n_qt, qpt;
+};
+RowTiles row_tiles(int l_c, int group) {
+  const int most = kRows / group, unit = 32 / group;
+  RowTiles t;
+  t.n_qt = (l_c + most - 1) / most;
+  t.qpt = ((l_c + t.n_qt - 1) / t.n_qt + unit - 1) / unit * unit;
+  return t;
+}
+
 int choose_splits(int l_c, int group, int h_kv, int batch) {
-  const int qpt = kRows / group;
-  const int64_t row_tiles = (int64_t)((l_c + qpt - 1) / qpt) * h_kv * batch;
-  int64_t ns = (256 + row_tiles - 1) / row_tiles;
+  const int64_t tiles = (int64_t)row_tiles(l_c, group).n_qt * h_kv * batch;
+  int64_t ns = (256 + tiles - 1) / tiles;
   return (int)(ns < 1 ? 1 : (ns > kMaxSplits ? kMaxSplits : ns));
+}
+
+template <int D>
+void launch_merge(const AttendArgs& a, int ns_a, int slot_b, int ns_b, hipStream_t st) {
+  const int64_t rows = (int64_t)a.l_c * a.h;
+  constexpr int kRowsPerWg = 256 / (D / 8);
+  esa_attend_merge<D><<<dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg), a.batch), 256, 0, st>>>(
+      a.part_o, a.part_ml, a.n_slot, ns_a, slot_b, ns_b, rows, a.out, a.lse, a.out_bs, rows);
 }
 
 }  // namespace
 
 bool attend_mfma_supported(int l_c, int h, int h_kv, int d, int dtype) {
-  if (dtype != ESA_BF16 || d != kD || l_c < kMinLc || h % h_kv != 0) return false;
+  if (dtype != ESA_BF16 || (d != 128 && d != 64) || l_c < kMinLc || h % h_kv != 0) return false;
   const int group = h / h_kv;
   return group == 1 || group == 2 || group == 4 || group == 8;
 }
@@ -603,14 +650,14 @@ struct SplitPlan {
 SplitPlan plan_splits(int l_c, int group, int h_kv, int batch) {
   SplitPlan p;
   p.all = choose_splits(l_c, group, h_kv, batch);
-  p.sel = p.all;
-  p.local = p.all > 1 ? p.all / 2 : 1;
+  p.sel = p.all < kMaxSelSplits ? p.all : kMaxSelSplits;
+  p.local = p.sel > 1 ? p.sel / 2 : 1;
   return p;
 }
 
-size_t slots_bytes(int n_slot, int l_c, int h, int batch) {
+size_t slots_bytes(int n_slot, int l_c, int h, int d, int batch) {
   const size_t rows = (size_t)batch * n_slot * l_c * h;
-  return align_up(rows * kD * sizeof(uint16_t), 256) + align_up(rows * 2 * sizeof(float), 256);
+  return align_up(rows * d * sizeof(uint16_t), 256) + align_up(rows * 2 * sizeof(float), 256);
 }
 
 }  // namespace
@@ -618,7 +665,7 @@ size_t slots_bytes(int n_slot, int l_c, int h, int batch) {
 size_t attend_mfma_workspace_bytes(int l_c, int h, int h_kv, int d, int batch) {
   const SplitPlan p = plan_splits(l_c, h / h_kv, h_kv, batch);
   const int n_slot = p.local + p.sel > p.all ? p.local + p.sel : p.all;
-  return slots_bytes(n_slot, l_c, h, batch);
+  return slots_bytes(n_slot, l_c, h, d, batch);
 }
 
 namespace {
@@ -671,8 +718,10 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.h = h;
   a.h_kv = h_kv;
   a.group = h / h_kv;
-  a.qpt = kRows / a.group;
-  a.n_qt = (l_c + a.qpt - 1) / a.qpt;
+  a.group_log2 = __builtin_ctz(a.group);
+  const RowTiles tiles = row_tiles(l_c, a.group);
+  a.qpt = tiles.qpt;
+  a.n_qt = tiles.n_qt;
   a.batch = batch;
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
@@ -692,25 +741,28 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.part_o = nullptr;
   a.part_ml = nullptr;
   if (part != kAttendAll || ns_all > 1) {
-    const size_t need = slots_bytes(n_slot, l_c, h, batch);
+    const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
     if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend: workspace needs %zu bytes", need);
     const size_t rows = (size_t)batch * n_slot * l_c * h;
     a.part_o = (uint16_t*)ws;
-    a.part_ml = (float*)((char*)ws + align_up(rows * kD * sizeof(uint16_t), 256));
+    a.part_ml = (float*)((char*)ws + align_up(rows * d * sizeof(uint16_t), 256));
   }
   a.n_slot = n_slot;
   a.view[1] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, 0, 0, 0, 0, 0, 0, 0);   // unused
-  auto launch = [&](int64_t n_wg) { attend_mfma_bf16<<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a); };
-  const int64_t rows = (int64_t)l_c * h;
-  const dim3 merge_grid((unsigned)((rows + 15) / 16), batch);
+  auto launch = [&](int64_t n_wg) {
+    if (d == 128) attend_mfma_bf16<128><<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a);
+    else attend_mfma_bf16<64><<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a);
+  };
+  auto merge = [&](int ns_a, int slot_b, int ns_b) {
+    if (d == 128) launch_merge<128>(a, ns_a, slot_b, ns_b, st);
+    else launch_merge<64>(a, ns_a, slot_b, ns_b, st);
+  };
   if (part == kAttendAll) {
     a.view[0] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, i_end, n_sel, l_start,
                           i_end + n_sel + (t0 - l_start), 1, ns_all, 0, sel_idx, idx_bs, l_start);
     a.to_slots = 0;
     launch((int64_t)batch * h_kv * a.n_qt * ns_all);
-    if (ns_all > 1)
-      esa_attend_merge<<<merge_grid, 256, 0, st>>>(a.part_o, a.part_ml, n_slot, ns_all, 0, 0, rows, (bf16_t*)out, lse,
-                                                   out_bs, rows);
+    if (ns_all > 1) merge(ns_all, 0, 0);
   } else if (part == kAttendLocal) {
     a.view[0] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, i_early, 0, l_start,
                           i_early + (t0 - l_start), 1, ns_local, 0);
@@ -723,8 +775,7 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
       a.to_slots = 1;
       launch((int64_t)batch * h_kv * a.n_qt * ns_sel);
     }
-    esa_attend_merge<<<merge_grid, 256, 0, st>>>(a.part_o, a.part_ml, n_slot, ns_local, plan.local, ns_sel, rows,
-                                                 (bf16_t*)out, lse, out_bs, rows);
+    merge(ns_local, plan.local, ns_sel);
   }
   ESA_LAUNCH_CHECK("attend_mfma");
   return ESA_OK;
@@ -752,8 +803,10 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.h = h;
   a.h_kv = h_kv;
   a.group = h / h_kv;
-  a.qpt = kRows / a.group;
-  a.n_qt = (l_c + a.qpt - 1) / a.qpt;
+  a.group_log2 = __builtin_ctz(a.group);
+  const RowTiles tiles = row_tiles(l_c, a.group);
+  a.qpt = tiles.qpt;
+  a.n_qt = tiles.n_qt;
   a.batch = batch;
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
@@ -769,25 +822,25 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   ns_a = clamp_splits(ns_a, n_loc + first_rows);
   if (ns_b > 0) ns_b = clamp_splits(ns_b, keys_b);
   const int n_slot = ns_a + ns_b;
-  const size_t need = slots_bytes(n_slot, l_c, h, batch);
+  const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
   a.part_o = nullptr;
   a.part_ml = nullptr;
   if (n_slot > 1) {
     if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend: workspace needs %zu bytes", need);
     const size_t rows = (size_t)batch * n_slot * l_c * h;
     a.part_o = (uint16_t*)ws;
-    a.part_ml = (float*)((char*)ws + align_up(rows * kD * sizeof(uint16_t), 256));
+    a.part_ml = (float*)((char*)ws + align_up(rows * d * sizeof(uint16_t), 256));
   }
   a.n_slot = n_slot;
   a.to_slots = 0;
   a.view[0] = make_view(q_loc, qw_bs, k_loc, v_loc, (int64_t)h_kv * d, loc_bs, 0, 0, 0, n_loc, 1, ns_a, 0);
   a.view[1] = make_view(q_glob, qw_bs, k_cache, v_cache, tok_stride, cache_bs, i_end, n_sel, 0, keys_b, 0, ns_b, ns_a);
-  attend_mfma_bf16<<<dim3((unsigned)((int64_t)batch * h_kv * a.n_qt * n_slot)), kThreads, 0, st>>>(a);
-  const int64_t rows = (int64_t)l_c * h;
+  const dim3 grid((unsigned)((int64_t)batch * h_kv * a.n_qt * n_slot));
+  if (d == 128) attend_mfma_bf16<128><<<grid, kThreads, 0, st>>>(a);
+  else attend_mfma_bf16<64><<<grid, kThreads, 0, st>>>(a);
   if (n_slot > 1) {
-    const dim3 merge_grid((unsigned)((rows + 15) / 16), batch);
-    esa_attend_merge<<<merge_grid, 256, 0, st>>>(a.part_o, a.part_ml, n_slot, n_slot, 0, 0, rows, (bf16_t*)out, lse, out_bs,
-                                                 rows);
+    if (d == 128) launch_merge<128>(a, n_slot, 0, 0, st);
+    else launch_merge<64>(a, n_slot, 0, 0, st);
   }
   ESA_LAUNCH_CHECK("attend_mfma (two views)");
   return ESA_OK;

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void score_fma(const T* __restrict__ qc, int l
 }
 
 
-// ------------------------------------------------------------------------------------------ MFMA (bf16, d_c = 128)
+// ------------------------------------------------------------------------------------------ MFMA (bf16, d_c = 128 or 64)
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -101,14 +101,15 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 //
 // Here A rows are current tokens (queries), B columns are middle tokens.  A workgroup of eight
 // waves (two per SIMD) owns up to 512 consecutive middle tokens.  Its whole share of K' (at most
-// 128 KB) goes from memory straight into LDS, without passing through registers: sixteen
-// global_load_lds_dwordx4 per thread, issued back to back at the start of the kernel, each wave
-// instruction bringing four 256-byte rows.  Which 16 bytes of its row a lane fetches is chosen such
-// that the rows land XOR-swizzled (piece p of row R in slot p ^ R%16), which makes the fragment
+// 128 KB) goes from memory straight into LDS, without passing through registers: sixteen (d_c = 64:
+// eight) global_load_lds_dwordx4 per thread, issued back to back at the start of the kernel, each wave
+// instruction bringing four 256-byte (eight 128-byte) rows.  Which 16 bytes of its row a lane fetches is
+// chosen such that the rows land XOR-swizzled (piece p of row R in slot p ^ R%16; d_c = 64, where two rows
+// share the 256 bytes that the banks cover: p ^ (R/2)%8), which makes the fragment
 // reads free of bank conflicts without padding.  Loads complete in order, so tile t (32 tokens,
-// instruction t of every wave) is usable once every wave has waited for its own instruction t and
+// instruction t, or t/2, of every wave) is usable once every wave has waited for its own instruction and
 // a barrier has passed; the tiles are consumed as they land, two per barrier.  Queries are the
-// register-resident operand (64 per wave as A fragments for the whole d_c = 128; chunks longer than
+// register-resident operand (64 per wave as A fragments for the whole d_c; chunks longer than
 // 512 loop over query blocks against the same LDS tile), so K' is read from memory once per sweep.
 //
 // Inside a wave the tiles are software-pipelined: right after the matrix instructions of reduction
@@ -125,22 +126,19 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // own with its own counter waits: an LDS access the compiler generates is preceded by a wait for ALL
 // outstanding loads into LDS (it cannot tell which rows they fill), which would turn the stream into
 // one round trip followed by the arithmetic.  LDS operations complete in order, which the waits
-// below rely on: "at most 7 outstanding" before the use of fragment ks means that fragment has
-// arrived, because exactly seven fragment reads were issued after it (the rest of this tile's and the
+// below rely on: "at most 7 (d_c = 64: 3) outstanding" before the use of fragment ks means that fragment
+// has arrived, because exactly so many fragment reads were issued after it (the rest of this tile's and the
 // first ks of the next tile's).  Operations the compiler adds on the same counter are newer still
 // and only make these waits stricter.
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 typedef __attribute__((address_space(1))) const void global_void;
-constexpr int kDc = 128;
-constexpr int kKSteps = kDc / 16;        // MFMA reduction steps per tile
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kMT = 2;                   // 32-query tiles per wave
 constexpr int kQPerWave = 32 * kMT;
 constexpr int kQPerBlock = kWaves * kQPerWave;
-constexpr int kMaxTilesPerBlock = 16;    // 512 tokens: 128 KB of LDS; one load instruction per thread and tile
-constexpr int kTileBytes = 32 * kDc * 2; // one tile of K' in LDS
+constexpr int kMaxTilesPerBlock = 16;    // 512 tokens: 128 KB of LDS (d_c = 128); one load instruction per thread and 8 KB
 
 __host__ __device__ inline int64_t mfma_tiles_per_block(int64_t n) {
   const int64_t n_tiles = (n + 31) / 32;
@@ -152,29 +150,26 @@ __host__ __device__ inline int64_t mfma_blocks(int64_t n) {
   return ((n + 31) / 32 + per - 1) / per;
 }
 // K' share, column maxima, digit histogram
-__host__ __device__ inline size_t mfma_lds_bytes(int64_t per) {
-  return (size_t)per * kTileBytes + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t);
+__host__ __device__ inline size_t mfma_lds_bytes(int64_t per, int d_c) {
+  return (size_t)per * 32 * d_c * sizeof(bf16_t) + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t);
 }
 // Row maxima of the matrix-core path: one row of mfma_mu_stride(l_c) floats per batch entry, so that groups
 // of four are 16-byte aligned and in bounds for every query tile that holds a query.
 __host__ __device__ inline int mfma_mu_stride(int l_c) { return (l_c + 63) / 64 * 64; }
 
-// Wait until at most `left` (14, 12, 8 or 0) vector-memory loads of this wave are outstanding, then the
-// workgroup barrier.  Only the first one (14) also waits for the LDS operations issued before it, the
-// initialising writes; in the tile loop the fragment reads in flight stay in flight across the barrier.
-__device__ __forceinline__ void wait_loads_then_barrier(int left) {
-  switch (left) {
-    case 0: asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); break;
-    case 8: asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory"); break;
-    case 12: asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory"); break;
-    default: asm volatile("s_waitcnt vmcnt(14) lgkmcnt(0)\n\ts_barrier" ::: "memory"); break;
-  }
+// Wait until at most LEFT vector-memory loads of this wave are outstanding, then the workgroup barrier.  Only the
+// first one also waits for the LDS operations issued before it, the initialising writes; in the tile loop the
+// fragment reads in flight stay in flight across the barrier.
+template <int LEFT, bool LDS_TOO = false>
+__device__ __forceinline__ void wait_loads_then_barrier() {
+  if (LDS_TOO) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+  else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LEFT) : "memory");
 }
 
 // PASS 0: partial row maxima into part_max[l_c][blocks].  PASS 1: F into score, using mu; with
 // first_hist given, also the histogram of the scores' leading 11 key bits (the first digit of the radix
 // selection that follows: the scores are in LDS here, so the selection need not read them for it).
-template <int PASS>
+template <int PASS, int DC>
 __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __restrict__ qc, int l_c,
                                                             const bf16_t* __restrict__ kc, int64_t m_lo, int64_t n,
                                                             float* __restrict__ part_max,
@@ -183,6 +178,13 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
                                                             int64_t score_bs, int tiles_per_block,
                                                             uint32_t* __restrict__ first_hist, int64_t first_hist_bs,
                                                             bf16_t* __restrict__ qfrag, int64_t qfrag_bs, int n_wg) {
+  static_assert(DC == 64 || DC == 128, "swizzle and load pattern");
+  constexpr int kDc = DC;
+  constexpr int kKSteps = kDc / 16;        // MFMA reduction steps per tile
+  constexpr int kTileBytes = 32 * kDc * 2; // one tile of K' in LDS
+  constexpr int kPieces = kDc / 8;         // 16-byte pieces of a row
+  constexpr int kTilesPerLoad = kWaves * 1024 / kTileBytes;           // tiles that one load instruction per wave brings
+  constexpr int kLoads = kMaxTilesPerBlock / kTilesPerLoad;           // load instructions of a full share
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];   // n_wg: workgroups per batch entry
   const int tpb = tiles_per_block;
   const int span = tpb * 32;                                           // tokens of this workgroup
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
 #pragma unroll
         for (int ks = 0; ks < kKSteps; ++ks) {
           if (ks < 4) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p), "n"(ks * 1024));
-          else asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p + 2048), "n"((ks - 4) * 1024));
+          else asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p + 2048), "n"((ks & 3) * 1024));
         }
       } else {
         int row = q0 + 32 * mt + r;
@@ -263,18 +265,31 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     }
   };
 #define ESA_QUERY_REGS(mt)                                                                                     \
-  "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3]), "+v"(a[mt][4]), "+v"(a[mt][5]), "+v"(a[mt][6]), \
-      "+v"(a[mt][7])
+  "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3]), "+v"(a[mt][kKSteps - 4]), "+v"(a[mt][kKSteps - 3]), \
+      "+v"(a[mt][kKSteps - 2]), "+v"(a[mt][kKSteps - 1])
+#define ESA_QUERY_REGS_SHORT(mt) "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3])
 #define ESA_MU_REGS(mt) "+v"(mu4[mt][0]), "+v"(mu4[mt][1]), "+v"(mu4[mt][2]), "+v"(mu4[mt][3])
-  // Everything requested before the share has arrived once at most fourteen of the share's sixteen requests
-  // are outstanding (first block; tiles 0 and 1 are in LDS then as well), or nothing at all (later blocks).
+  // Everything requested before the share has arrived once at most all but (16 / d_c-dependent) two tiles' worth of
+  // the share's requests are outstanding (first block; tiles 0 and 1 are in LDS then as well), or nothing at all
+  // (later blocks).
+  constexpr int kLeftFirst = kLoads - 2 / kTilesPerLoad;
   auto queries_arrived = [&](bool first) {
-    if (PASS == 0) {
-      if (first) asm volatile("s_waitcnt vmcnt(14)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1));
-      else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1));
+    if constexpr (kKSteps == 8) {
+      if (PASS == 0) {
+        if (first) asm volatile("s_waitcnt vmcnt(%c16)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1) : "n"(kLeftFirst));
+        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1));
+      } else {
+        if (first) asm volatile("s_waitcnt vmcnt(%c24)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1), ESA_MU_REGS(0), ESA_MU_REGS(1) : "n"(kLeftFirst));
+        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1), ESA_MU_REGS(0), ESA_MU_REGS(1));
+      }
     } else {
-      if (first) asm volatile("s_waitcnt vmcnt(14)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1), ESA_MU_REGS(0), ESA_MU_REGS(1));
-      else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1), ESA_MU_REGS(0), ESA_MU_REGS(1));
+      if (PASS == 0) {
+        if (first) asm volatile("s_waitcnt vmcnt(%c8)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1) : "n"(kLeftFirst));
+        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1));
+      } else {
+        if (first) asm volatile("s_waitcnt vmcnt(%c16)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1), ESA_MU_REGS(0), ESA_MU_REGS(1) : "n"(kLeftFirst));
+        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1), ESA_MU_REGS(0), ESA_MU_REGS(1));
+      }
     }
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt)
@@ -294,22 +309,25 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
       }
   };
 #undef ESA_QUERY_REGS
+#undef ESA_QUERY_REGS_SHORT
 #undef ESA_MU_REGS
 
   // ---- the pipeline over this workgroup's tiles
   bf16x8 bfr[kKSteps];
   f32x16 acc0[kMT], acc1[kMT];
-  // LDS byte address of this lane's fragment ks of tile nt: row r, slot (2 ks + hi) ^ (r % 16).  The share
+  // LDS byte address of this lane's fragment ks of tile nt: row r, slot (2 ks + hi) ^ swizzle(r).  The share
   // starts at a multiple of 256 bytes, so the slot's ks bits can be XORed into the address of fragment 0.
-  const uint32_t frag0_at = lds_tiles + (uint32_t)r * (kDc * 2) + (uint32_t)((hi ^ (r & 15)) * 16);
+  auto swizzle = [](uint32_t row) { return kDc == 128 ? row & 15 : (row >> 1) & 7; };
+  const uint32_t frag0_at = lds_tiles + (uint32_t)r * (kDc * 2) + (uint32_t)((hi ^ swizzle(r)) * 16);
   auto read_fragment = [&](int nt, int ks) {
     asm volatile("ds_read_b128 %0, %1" : "=v"(bfr[ks]) : "v"((frag0_at ^ (uint32_t)(ks * 32)) + (uint32_t)nt * kTileBytes));
   };
   float best = -INFINITY;
-  // One eighth of the maximum / subtract work on a finished tile's accumulators.
+  // One reduction step's share of the maximum / subtract work on a finished tile's accumulators.
   auto epilogue_part = [&](f32x16 (&P)[kMT], int part) {
+    constexpr int kShare = 16 * kMT / kKSteps;
 #pragma unroll
-    for (int e = 4 * part; e < 4 * part + 4; ++e) {
+    for (int e = kShare * part; e < kShare * (part + 1); ++e) {
       const int mt = e / 16, v = e % 16;
       if (PASS == 0) aux[mt][v] = fmaxf(aux[mt][v], P[mt][v]);
       else best = fmaxf(best, P[mt][v] - aux[mt][v]);
@@ -334,7 +352,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < kKSteps; ++ks) {
-      asm volatile("s_waitcnt lgkmcnt(7)" : "+v"(bfr[ks]));
+      asm volatile("s_waitcnt lgkmcnt(%c1)" : "+v"(bfr[ks]) : "n"(kKSteps - 1));
 #pragma unroll
       for (int mt = 0; mt < kMT; ++mt)
         C[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][ks], bfr[ks], ks == 0 ? zero : C[mt], 0, 0, 0);
@@ -350,11 +368,15 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   // ahead of the arithmetic, the waves run free of each other (a barrier per pair of tiles costs more than
   // it hides: of the two waves of a SIMD one gets ahead, waits, and the other cannot fill the matrix pipe
   // alone).  The number of tiles is even.
+  auto next_group = [&](int nt) {                            // the wait and barrier behind step nt (0, 2 or 6)
+    if (nt == 0) wait_loads_then_barrier<kLoads - 4 / kTilesPerLoad>();
+    else if (nt == 2) wait_loads_then_barrier<kLoads - 8 / kTilesPerLoad>();
+    else wait_loads_then_barrier<0>();
+  };
   auto run_tiles = [&](bool streaming, bool active) {
     if (!active) {
       if (streaming)
-        for (int nt = 0; nt + 2 < tpb && nt <= 6; nt += nt + 2)       // nt = 0, 2, 6: the barriers below
-          wait_loads_then_barrier(nt == 0 ? 12 : (nt == 2 ? 8 : 0));
+        for (int nt = 0; nt + 2 < tpb && nt <= 6; nt += nt + 2) next_group(nt);
       return;
     }
 #pragma unroll
@@ -367,7 +389,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     for (int nt = 0; nt < tpb; nt += 2) {
       step(nt, acc0, acc1);
       if (streaming && nt + 2 < tpb && (nt == 0 || nt == 2 || nt == 6))
-        wait_loads_then_barrier(nt == 0 ? 12 : (nt == 2 ? 8 : 0));
+        next_group(nt);
       step(nt + 1, acc1, acc0);
     }
 #pragma unroll
@@ -413,8 +435,8 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   };
 
   // ---- requests, in the order their results are needed (loads complete in order): query fragments and row
-  // maxima, then the K' share.  Instruction i of wave w fills row group 8*i + w (four rows, 1 KB of
-  // LDS); lane l fetches, for slot l%16 of row l/16 of the group, the piece that undoes the swizzle.
+  // maxima, then the K' share.  Instruction i of wave w fills row group 8*i + w (four or eight rows, 1 KB of
+  // LDS); a lane fetches, for its slot of its row of the group, the piece that undoes the swizzle.
   // Rows past the end of the middle segment repeat its last token (no maximum changes, nothing of theirs
   // is stored); shares shorter than sixteen tiles repeat their last instruction, identical data to an
   // identical place, so that the count of outstanding loads means the same in every workgroup.
@@ -426,12 +448,13 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   request_query_block(0);
   __builtin_amdgcn_sched_barrier(0);
   {
-    const uint32_t row_in_tile = 4 * wave + (lane >> 4);
-    const uint32_t piece = (lane & 15) ^ (row_in_tile & 15);
+    const uint32_t row_in_load = (64 / kPieces) * wave + lane / kPieces;
+    const uint32_t piece = (lane % kPieces) ^ swizzle(row_in_load);
+    const int n_loads = tpb / kTilesPerLoad;                 // tpb is even
 #pragma unroll
-    for (int i = 0; i < kMaxTilesPerBlock; ++i) {
-      const int t = i < tpb ? i : tpb - 1;
-      uint32_t row = 32 * t + row_in_tile;
+    for (int i = 0; i < kLoads; ++i) {
+      const int t = i < n_loads ? i : n_loads - 1;
+      uint32_t row = 32 * kTilesPerLoad * t + row_in_load;
       row = row < last_row ? row : last_row;
       __builtin_amdgcn_global_load_lds((global_void*)(kshare + (size_t)row * (kDc * sizeof(bf16_t)) + piece * 16),
                                        (lds_void*)(lds_raw + (size_t)(8 * t + wave) * 1024), 16, 0, 0);
@@ -439,7 +462,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   }
   __builtin_amdgcn_sched_barrier(0);
   queries_arrived(true);
-  wait_loads_then_barrier(14);                               // tiles 0 and 1 (and this wave's LDS writes above)
+  wait_loads_then_barrier<kLeftFirst, true>();               // tiles 0 and 1 (and this wave's LDS writes above)
 
   // ---- query blocks (chunks longer than 512 tokens take several); from the second on, the share is in LDS
   for (int qb = 0; qb * kQPerBlock < l_c; ++qb) {
@@ -697,7 +720,32 @@ __host__ inline size_t part_bytes(int l_c, int64_t n_mid, int batch) {
 
 // fragment-ordered copy of Q' (matrix-core path): whole blocks of 512 queries, 256 bytes each
 __host__ inline size_t qfrag_bytes_per_batch(int l_c) {
-  return l_c > 1 ? (size_t)((l_c + kQPerBlock - 1) / kQPerBlock) * kQPerBlock * kDc * sizeof(bf16_t) : 0;
+  return l_c > 1 ? (size_t)((l_c + kQPerBlock - 1) / kQPerBlock) * kQPerBlock * 128 * sizeof(bf16_t) : 0;
+}
+
+// The two sweeps of the matrix-core path and the reduction between them.
+template <int DC>
+int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int64_t n, float* part, float* mu, float* score,
+                  int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, uint32_t* hists, bool fill_first, int64_t hists_bs,
+                  bf16_t* qfrag, int64_t qfrag_bs, hipStream_t st) {
+  const int per = (int)mfma_tiles_per_block(n), nblk = (int)mfma_blocks(n);
+  const dim3 grid(nblk, batch);
+  const size_t lds = mfma_lds_bytes(per, DC);
+  static bool lds_limit_raised = false;        // idempotent; a race only repeats the call
+  if (!lds_limit_raised) {
+    const int most = (int)mfma_lds_bytes(kMaxTilesPerBlock, DC);
+    hipError_t e = hipFuncSetAttribute((const void*)score_mfma_bf16<0, DC>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)score_mfma_bf16<1, DC>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e != hipSuccess) return hip_failed(e, "hipFuncSetAttribute(score_mfma_bf16)");
+    lds_limit_raised = true;
+  }
+  score_mfma_bf16<0, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per, nullptr,
+                                                      0, qfrag, qfrag_bs, nblk);
+  score_rowmax_reduce<<<dim3((l_c + 3) / 4, batch), 256, 0, st>>>(part, nblk, l_c, mu, mfma_mu_stride(l_c), hists, hists_bs);
+  score_mfma_bf16<1, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per,
+                                                      fill_first ? hists : nullptr, hists_bs, qfrag, qfrag_bs, nblk);
+  return ESA_OK;
 }
 
 size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
@@ -742,34 +790,16 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     const int blocks = sub_mu_blocks(n);
     score_sub_mu<<<dim3(blocks, batch), 256, 0, st>>>(raw, n, part, nblk, raw_bs, pool_hist ? nullptr : fh, fbs);
     if (fh && !pool_hist && first_hist_done) *first_hist_done = true;
-  } else if (vec_ok && d_c == kDc) {
-    const int per = (int)mfma_tiles_per_block(n);
-    const int nblk = (int)mfma_blocks(n);
-    const dim3 grid(nblk, batch);
+  } else if (vec_ok && (d_c == 128 || d_c == 64)) {
     float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
-    float* muf = (float*)ws;
-    const size_t lds0 = mfma_lds_bytes(per), lds1 = lds0;
-    static bool lds_limit_raised = false;      // idempotent; a race only repeats the call
-    if (!lds_limit_raised) {
-      const int most = (int)mfma_lds_bytes(kMaxTilesPerBlock);
-      hipError_t e = hipFuncSetAttribute((const void*)score_mfma_bf16<0>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         most);
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void*)score_mfma_bf16<1>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-      if (e != hipSuccess) return hip_failed(e, "hipFuncSetAttribute(score_mfma_bf16)");
-      lds_limit_raised = true;
-    }
     size_t qfrag_at = mu_bytes(l_c, batch) + part_bytes(l_c, n, batch);
     if (eps > 0) qfrag_at += align_up((size_t)n * 4, 256) * (size_t)batch;
     bf16_t* qfrag = (bf16_t*)((char*)ws + qfrag_at);
     const int64_t qfrag_bs = (int64_t)(qfrag_bytes_per_batch(l_c) / sizeof(bf16_t));
-    score_mfma_bf16<0><<<grid, kThreads, lds0, st>>>((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, muf,
-                                                raw, q_bs, kc_bs, raw_bs, per, nullptr, 0, qfrag, qfrag_bs, nblk);
-    score_rowmax_reduce<<<dim3((l_c + 3) / 4, batch), 256, 0, st>>>(part, nblk, l_c, muf, mfma_mu_stride(l_c), first_hist,
-                                                                  first_hist_bs);
-    score_mfma_bf16<1><<<grid, kThreads, lds1, st>>>((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, muf,
-                                                raw, q_bs, kc_bs, raw_bs, per, pool_hist ? nullptr : first_hist,
-                                                first_hist_bs, qfrag, qfrag_bs, nblk);
+    const auto sweeps = d_c == 128 ? launch_sweeps<128> : launch_sweeps<64>;
+    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, raw, batch, q_bs, kc_bs,
+                          raw_bs, first_hist, !pool_hist, first_hist_bs, qfrag, qfrag_bs, st);
+    if (rc != ESA_OK) return rc;
     zeroed = first_hist != nullptr;
     if (first_hist && !pool_hist && first_hist_done) *first_hist_done = true;
   } else {

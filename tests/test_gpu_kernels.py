@@ -1,0 +1,66 @@
+"""GPU kernels at the sizes where they can go wrong (tile edges, remainders, smallest and largest of a dispatch
+range), against the float64 oracle.  Tolerances as in test_gpu_parity.py: derived there from the storage type."""
+import numpy as np
+import pytest
+import torch
+
+from esa_inputs import segment_bounds
+from oracle import esa_oracle as orc
+from support import f64_to_dev, to_f64
+from test_gpu_parity import F_TOL, O_TOL, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def esa():
+    import paper_2502_14477_amd as lib
+    return lib
+
+
+def attend_inputs(seed, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
+    rng = np.random.default_rng(seed)
+    S = t0 + l_C
+    q = orc.round_to_storage(rng.standard_normal((B, l_C, H, d)), dtype)
+    K = orc.round_to_storage(rng.standard_normal((B, S, H_kv, d)), dtype)
+    V = orc.round_to_storage(rng.standard_normal((B, S, H_kv, d)), dtype)
+    i_end, l_start = segment_bounds(t0, l_I, l_L)
+    sel = np.stack([np.sort(rng.choice(np.arange(i_end, l_start), n_sel, replace=False)) for _ in range(B)]).astype(np.int32) \
+        if n_sel else np.empty((B, 0), np.int32)
+    return q, K, V, sel
+
+
+# one token of a 32-row wave tile more or less, row tiles of unequal filling, one slice and many, every group size
+@pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
+    (1, 4, 4, 64, 900, 16, 8, 64, 31), (1, 8, 4, 64, 700, 17, 8, 100, 64), (2, 8, 2, 64, 1000, 65, 0, 130, 129),
+    (1, 16, 2, 64, 1100, 33, 16, 64, 200), (1, 8, 2, 64, 0, 63, 16, 64, 0), (1, 32, 8, 64, 3000, 257, 128, 512, 700),
+    (1, 16, 2, 128, 1100, 33, 16, 64, 200), (2, 8, 2, 128, 1000, 65, 0, 130, 129), (1, 8, 8, 128, 700, 259, 8, 100, 64)])
+def test_matrix_core_attention_head_sizes_and_row_tiles(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
+    say(f"attend B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16"), torch.from_numpy(sel).cuda()
+    O, lse = esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx, return_lse=True)
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx) if n_sel else (None, None)
+    O_re = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5)
+    for b in range(B):
+        want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"]
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3
+        want, _ = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
+        assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL["bf16"]
+
+
+# the shortest shares, shares with every number of load groups in flight, two blocks of queries
+@pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 40, 1, 64, 0), (1, 64, 8193, 64, 0), (2, 512, 33000, 64, 0), (1, 530, 66000, 64, 1),
+                                             (1, 20, 131072, 64, 0), (1, 96, 40000, 128, 0)])
+def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
+    say(f"score B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
+    rng = np.random.default_rng(n + l_c)
+    qc = orc.round_to_storage(rng.standard_normal((B, l_c, d_c)) * 1.5, "bf16")
+    kc = orc.round_to_storage(rng.standard_normal((B, n + 8, d_c)), "bf16")
+    got = to_f64(esa.esa_score(f64_to_dev(qc, "bf16"), f64_to_dev(kc, "bf16"), 3, n + 3, eps=eps))
+    for b in range(B):
+        want = orc.importance(qc[b], kc[b, 3:n + 3])
+        want = orc.proximity(want, eps) if eps else want
+        assert np.max(np.abs(got[b] - want)) <= F_TOL["bf16"]
+        assert got[b].max() == 0.0
