@@ -177,15 +177,23 @@ int esa_score_select_gather(const void* qc, int l_c, const void* kc_cache, int64
   const int k_eff = (int)(k < n ? k : n);
   const size_t score_ws = align_up(score_workspace_bytes(l_c, n, eps, batch), 256);
   char* topk_ws = (char*)workspace + score_ws;
-  bool hist_done = false;
-  int rc = ESA_OK;
-  if (k < n) {     // otherwise every middle token is taken and no score is needed
-    uint32_t* hists = (uint32_t*)topk_ws + TopkLayout::hist;
+  int rc;
+  if (k < n && n <= kSelectSmallMax) {
+    ScoreTail tail;
     rc = launch_score(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, score_ws,
-                      st, hists, topk_row_stride_words(n, batch), &hist_done);
+                      st, nullptr, 0, nullptr, &tail);
     if (rc != ESA_OK) return rc;
+    rc = launch_select_small(tail, tail.part || tail.eps > 0 ? score : nullptr, score_bs, n, k, m_lo, idx, idx_bs, batch, st);
+  } else {
+    bool hist_done = false;
+    if (k < n) {     // otherwise every middle token is taken and no score is needed
+      uint32_t* hists = (uint32_t*)topk_ws + TopkLayout::hist;
+      rc = launch_score(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, score_ws,
+                        st, hists, topk_row_stride_words(n, batch), &hist_done);
+      if (rc != ESA_OK) return rc;
+    }
+    rc = launch_topk(score, n, k, m_lo, idx, batch, score_bs, idx_bs, topk_ws, ws_bytes - score_ws, st, hist_done);
   }
-  rc = launch_topk(score, n, k, m_lo, idx, batch, score_bs, idx_bs, topk_ws, ws_bytes - score_ws, st, hist_done);
   if (rc != ESA_OK) return rc;
   if (gathers)
     rc = launch_gather(k_cache, v_cache, tok_stride, idx, k_eff, h_kv, d, k_sel, v_sel, dtype, batch, cache_bs, idx_bs, sel_bs, st);

@@ -107,17 +107,30 @@ int launch_compress_pair(const void* x0, int64_t d_in0, int64_t ldx0, const void
                          int64_t n_tok, int d_c, int w_layout, int dtype, int batch, hipStream_t st);
 
 size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch);
-// first_hist: null, or [batch] rows (stride first_hist_bs words) holding the three digit histograms of the
-// selection that follows; when the kernels in use can, they zero all three and fill the first with the
-// leading digits of the scores they write, and *first_hist_done is set.
+// What a selection that keeps a whole row in one workgroup finishes of the scores before it selects from them: the
+// row maximum mu over n_part partial maxima (null part: already subtracted), pooling over +-eps (0: none or done).
+struct ScoreTail {
+  const float* in;
+  int64_t in_bs;
+  const float* part;      // [batch][n_part]
+  int n_part, eps;
+};
+constexpr int kTailMaxEps = 16;     // wider windows keep their own pass
+// first_hist: null, or [batch] rows (stride first_hist_bs words) holding the histogram of the selection that
+// follows; the kernels zero it and fill it with the scores they write when they can, and *first_hist_done is set.
+// tail: null, or the selection that follows is launch_select_small: the scores are left as *tail says.
 int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
                  float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs,
                  void* ws, size_t ws_bytes, hipStream_t st, uint32_t* first_hist = nullptr, int64_t first_hist_bs = 0,
-                 bool* first_hist_done = nullptr);
+                 bool* first_hist_done = nullptr, ScoreTail* tail = nullptr);
+
+// Rows of at most kSelectSmallMax scores (radix_hist.h), k < n.  score: where the finished scores go (null: they are
+// finished, or nothing is to be written).
+int launch_select_small(const ScoreTail& tail, float* score, int64_t score_bs, int64_t n, int k, int64_t base, int32_t* idx,
+                        int64_t idx_bs, int batch, hipStream_t st);
 
 size_t topk_workspace_bytes(int64_t n, int k, int batch);
-// first_hist_ready: the workspace's histograms are zeroed and the first one already holds the scores'
-// leading digits (left there by launch_score).
+// first_hist_ready: the workspace's histogram already holds the scores (left there by launch_score).
 int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx, int batch, int64_t score_bs,
                 int64_t idx_bs, void* ws, size_t ws_bytes, hipStream_t st, bool first_hist_ready = false);
 

@@ -167,8 +167,8 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 }
 
 // PASS 0: partial row maxima into part_max[l_c][blocks].  PASS 1: F into score, using mu; with
-// first_hist given, also the histogram of the scores' leading 11 key bits (the first digit of the radix
-// selection that follows: the scores are in LDS here, so the selection need not read them for it).
+// first_hist given, also the histogram of the scores' bins (radix_hist.h; the scores are in LDS here, so the
+// selection need not read them for it).
 template <int PASS, int DC>
 __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __restrict__ qc, int l_c,
                                                             const bf16_t* __restrict__ kc, int64_t m_lo, int64_t n,
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
       const bool ok = i < span && m < n;
       const uint32_t key = ok ? colmax[32 + i] : 0u;
       if (ok) score[(int64_t)b * score_bs + m] = ordered_key_to_f32(key);
-      if (first_hist) hist_add(digit_hist, ok, key >> 21);
+      if (first_hist) hist_add(digit_hist, ok, score_bin(key));
     }
     if (first_hist) {
       __syncthreads();
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
 }
 
 // mu[c] = max over workgroups of their partial row maxima ([l_c][blocks] layout): one wave per query.
-// Running between the two sweeps, it also zeroes the selection's three digit histograms when given them.
+// Running between the two sweeps, it also zeroes the selection's histogram when given it.
 __global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restrict__ part_max, int nblk, int l_c,
                                                            float* __restrict__ mu, int mu_stride,
                                                            uint32_t* __restrict__ hists, int64_t hists_bs) {
@@ -570,7 +570,7 @@ __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict_
   const int n_wg = (int)((n + kGemvRows - 1) / kGemvRows);           // workgroups per batch entry (the launch's grid)
   __shared__ float red[4];
   const int b = __builtin_amdgcn_workgroup_id_y();
-  if (hists)       // the selection's digit histograms, zeroed here for the pass that follows
+  if (hists)       // the selection's histogram, zeroed here for the pass that follows
     for (int i = __builtin_amdgcn_workgroup_id_x() * 256 + __builtin_amdgcn_workitem_id_x(); i < kHistWords; i += n_wg * 256)
       hists[(int64_t)b * hists_bs + i] = 0u;
   const bf16_t* kmid = kc + (int64_t)b * kc_bs + m_lo * (int64_t)kDcv;
@@ -651,7 +651,7 @@ __global__ __launch_bounds__(256) void score_sub_mu(float* __restrict__ raw, int
     const int64_t i = first + u * stride;
     const float f = x[u] - mu;
     if (i < n) p[i] = f;
-    if (first_hist) hist_add(digit_hist, i < n, ordered_key(f) >> 21);
+    if (first_hist) hist_add(digit_hist, i < n, score_bin(ordered_key(f)));
   }
   // whole waves stay in the loop together (hist_add is a wave-wide operation); four scores in flight per lane
   for (int64_t c0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * 1024 + chunk_stride; c0 < n; c0 += chunk_stride) {
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256) void score_sub_mu(float* __restrict__ raw, int
       const int64_t i = c0 + u * stride + __builtin_amdgcn_workitem_id_x();
       const float f = y[u] - mu;
       if (i < n) p[i] = f;
-      if (first_hist) hist_add(digit_hist, i < n, ordered_key(f) >> 21);
+      if (first_hist) hist_add(digit_hist, i < n, score_bin(ordered_key(f)));
     }
   }
   if (first_hist) {
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(256) void score_sub_mu(float* __restrict__ raw, int
 }
 
 // Eq. 8: out[j] = max(in[max(j-eps,0) .. min(j+eps,n-1)]).  With first_hist given, also the histogram of the
-// pooled scores' leading 11 key bits (this is the kernel that writes the scores the selection reads).
+// pooled scores' bins (this is the kernel that writes the scores the selection reads).
 __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict__ in, float* __restrict__ out, int64_t n,
                                                          int eps, int64_t in_bs, int64_t out_bs,
                                                          uint32_t* __restrict__ first_hist, int64_t first_hist_bs) {
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict
       for (int64_t w = lo + 1; w <= hi; ++w) m = fmaxf(m, src[w]);
       dst[j] = m;
     }
-    if (first_hist) hist_add(digit_hist, j < n, ordered_key(m) >> 21);
+    if (first_hist) hist_add(digit_hist, j < n, score_bin(ordered_key(m)));
   }
   if (first_hist) {
     __syncthreads();
@@ -758,7 +758,8 @@ size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
 
 int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
                  float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* ws,
-                 size_t ws_bytes, hipStream_t st, uint32_t* first_hist, int64_t first_hist_bs, bool* first_hist_done) {
+                 size_t ws_bytes, hipStream_t st, uint32_t* first_hist, int64_t first_hist_bs, bool* first_hist_done,
+                 ScoreTail* tail) {
   const int64_t n = m_hi - m_lo;
   // With pooling the kernel that writes the final scores is the pooling pass: the kernels before it only zero
   // the histograms (pool_hist), it fills the first one.
@@ -772,6 +773,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     raw = (float*)((char*)ws + mu_bytes(l_c, batch) + part_bytes(l_c, n, batch));
     raw_bs = (int64_t)(align_up((size_t)n * 4, 256) / 4);
   }
+  if (tail) *tail = ScoreTail{raw, raw_bs, nullptr, 0, eps <= kTailMaxEps ? eps : 0};
   const bool vec_ok = dtype == ESA_BF16 && (((uintptr_t)qc | (uintptr_t)kc_cache) % 16 == 0) && q_bs % 8 == 0 &&
                       kc_bs % 8 == 0;
   if (vec_ok && l_c == 1 && (d_c == 64 || d_c == 128 || d_c == 256)) {
@@ -788,7 +790,12 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     else if (lpr == 16) score_gemv_bf16<16><<<grid, 256, 0, st>>>(q, k, m_lo, n, part, raw, q_bs, kc_bs, raw_bs, fh, fbs);
     else score_gemv_bf16<32><<<grid, 256, 0, st>>>(q, k, m_lo, n, part, raw, q_bs, kc_bs, raw_bs, fh, fbs);
     const int blocks = sub_mu_blocks(n);
-    score_sub_mu<<<dim3(blocks, batch), 256, 0, st>>>(raw, n, part, nblk, raw_bs, pool_hist ? nullptr : fh, fbs);
+    if (tail && eps <= kTailMaxEps) {
+      tail->part = part;
+      tail->n_part = nblk;
+    } else {
+      score_sub_mu<<<dim3(blocks, batch), 256, 0, st>>>(raw, n, part, nblk, raw_bs, pool_hist ? nullptr : fh, fbs);
+    }
     if (fh && !pool_hist && first_hist_done) *first_hist_done = true;
   } else if (vec_ok && (d_c == 128 || d_c == 64)) {
     float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
@@ -826,7 +833,8 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                                                    raw, q_bs, kc_bs, raw_bs);
     }
   }
-  if (eps > 0) {
+  if (tail && eps > kTailMaxEps) *tail = ScoreTail{score, score_bs, nullptr, 0, 0};
+  if (eps > 0 && !(tail && eps <= kTailMaxEps)) {
     const int blocks = maxpool_blocks(n);
     uint32_t* ph = zeroed ? pool_hist : nullptr;       // only behind kernels that have zeroed the histograms
     proximity_maxpool<<<dim3(blocks, batch), 256, 0, st>>>(raw, score, n, eps, raw_bs, score_bs, ph, first_hist_bs);

@@ -1,19 +1,21 @@
-// Token-level top-k over the middle-token scores (Eq. 2): exact radix select on
-// order-preserving 32-bit keys, then an ordered compaction.
+// Token-level top-k over the middle-token scores (Eq. 2): exact selection on order-preserving 32-bit keys, then an
+// ordered compaction (ascending positions; equal scores: the lower position wins).
 //
-// Three histogram passes (11 + 11 + 10 bits, most significant first) pin down the key T of the
-// k-th largest score and how many scores equal to T are still needed; a writing pass then emits
-// the positions of every score above T plus the first `need` scores equal to T, in ascending
-// position order (equal scores: the lower position wins).  For its output offsets a workgroup of
-// the writing pass needs the number of selected scores in the workgroups before it; the third
-// histogram pass leaves that per workgroup in two pieces: the count of scores above the 22-bit
-// prefix fixed so far (selected whatever the last digit of T turns out to be), and the list of the
-// last digits of the scores that share the prefix (usually a handful), which the writing pass
-// compares with T's last digit once it knows it.
+// Rows of up to kSelectSmallMax scores: one workgroup per row keeps the row's keys in registers and does everything
+// in one launch (select_small), including what the score call would otherwise need a pass of its own for (mu of a
+// single current token, Eq. 8's pooling).
+//
+// Longer rows: a histogram over 2048 fine bins (radix_hist.h) is built by the kernel that writes the scores; then
+//   topk_compact  every workgroup picks the bin that holds the k-th score, counts its scores above it and lists
+//                 its keys inside it (a few per thousand scores);
+//   topk_write    every workgroup collects all lists (a few hundred keys) in LDS, finds the exact threshold T among
+//                 them and how many keys equal to T are still needed, and from the counts and lists of the
+//                 workgroups before it its own output offset, and writes its selected positions.
+// Rows whose k-th score shares its bin with more keys than the lists hold (massive ties) take a slower path inside
+// topk_write that finds T and the offset from the scores themselves.
 // All cross-block traffic is integer atomics and plain stores, so the result is deterministic.
-// No workgroup ever waits for another: what one pass leaves in global memory (a 2048-bin
-// histogram, or the per-block counts) is re-read and scanned by EVERY workgroup of the next
-// launch, redundantly, instead of being finished by a last-arriving workgroup — a launch is then
+// No workgroup ever waits for another: what one pass leaves in global memory is re-read and scanned by EVERY
+// workgroup of the next launch, redundantly, instead of being finished by a last-arriving workgroup: a launch is then
 // one round trip to memory plus a little LDS work, which is what bounds this latency-bound call.
 #include <atomic>
 
@@ -27,6 +29,9 @@ constexpr int kThreads = 512;
 constexpr int kItems = 2;                       // consecutive scores per thread
 constexpr int kTile = kThreads * kItems;        // scores per block
 constexpr int kBins = kRadixBins;
+constexpr int kCandPerTile = 64;                // list slots of a workgroup per tile of scores
+constexpr int kPeek = 8;                        // of them read ahead of their count
+constexpr uint32_t kListMax = 2048;             // keys topk_write can hold
 
 struct TopkPlan {
   int64_t sub;      // tiles of kTile scores per workgroup
@@ -34,7 +39,7 @@ struct TopkPlan {
 };
 // One tile of kTile scores per workgroup while that keeps the chip busy (a call is latency-bound
 // then); with many rows a workgroup takes several tiles, so that the fixed work per workgroup
-// (prefix resolution, histogram flush) is paid by fewer of them.
+// (bin and list resolution) is paid by fewer of them.
 __host__ inline TopkPlan topk_plan(int64_t n, int batch) {
   const int64_t tiles = (n + kTile - 1) / kTile;
   int64_t sub = (tiles * batch + 767) / 768;
@@ -44,9 +49,10 @@ __host__ inline TopkPlan topk_plan(int64_t n, int batch) {
   p.nblk = (tiles + sub - 1) / sub;
   return p;
 }
+// counts of a kind, per row: a multiple of four words, so that the lists behind them are 16-byte aligned
+__host__ __device__ inline int64_t count_words(int64_t nblk) { return (nblk + 3) / 4 * 4; }
 __host__ inline int64_t topk_row_words(const TopkPlan& p) {
-  const int64_t cand_words = (p.nblk * p.sub * kTile + 1) / 2;
-  return TopkLayout::blk + 2 * p.nblk + cand_words;
+  return TopkLayout::blk + 2 * count_words(p.nblk) + p.nblk * p.sub * kCandPerTile;
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave in the vector unit: shifts inside the 16-lane rows, then the
@@ -62,11 +68,12 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
-// Exclusive prefix sums of two values per thread over the block (one pair of barriers for both); *total_a and
-// *total_b get the block sums.  wave_sums: 2 * kThreads / 64 words.
+// Exclusive prefix sums of two values per thread over a block of NT threads (one pair of barriers for both);
+// *total_a and *total_b get the block sums.  wave_sums: 2 * NT / 64 words.
+template <int NT>
 __device__ __forceinline__ void block_excl_scan2(uint32_t a, uint32_t b, uint32_t* before_a, uint32_t* before_b,
                                                  uint32_t* total_a, uint32_t* total_b, uint32_t* wave_sums) {
-  constexpr int kWavesPerBlock = kThreads / 64;
+  constexpr int kWavesPerBlock = NT / 64;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
   __syncthreads();                       // wave_sums may still be read from a previous call
@@ -92,21 +99,17 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t a, uint32_t b, uint32_
   *before_b = base_b + ib - b;
 }
 
-// Exclusive prefix sum of one value per thread over the block; *total gets the block sum.
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* total, uint32_t* wave_sums) {
+// Exclusive prefix sum of one value per thread over the block.
+template <int NT>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_sums) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t incl = wave_incl_scan(v);
   __syncthreads();                       // wave_sums may still be read from a previous call
   if (lane == 63) wave_sums[w] = incl;
   __syncthreads();
-  uint32_t base = 0, tot = 0;
+  uint32_t base = 0;
 #pragma unroll
-  for (int i = 0; i < kThreads / 64; ++i) {
-    uint32_t s = wave_sums[i];
-    if (i < w) base += s;
-    tot += s;
-  }
-  *total = tot;
+  for (int i = 0; i < NT / 64; ++i) base += i < w ? wave_sums[i] : 0u;
   return base + incl - v;
 }
 
@@ -125,108 +128,72 @@ __device__ __forceinline__ void load_keys(const float* row, int64_t n, int64_t f
   for (int e = 0; e < kItems; ++e) key[e] = ok[e] ? ordered_key(v[e]) : 0u;
 }
 
-// One thread's share of a finished 2048-bin histogram; thread 0 owns the highest bins.
-constexpr int kBinsPerThread = kBins / kThreads;
-struct BinSlice {
-  uint32_t c[kBinsPerThread];
-};
-__device__ __forceinline__ BinSlice load_slice(const uint32_t* __restrict__ gh) {   // gh: [kHistReplicas][kBins]
-  static_assert(kBinsPerThread == 4, "one 16-byte load per copy");
-  BinSlice s;
-  const uint4* lowest = (const uint4*)gh + (kThreads - 1 - threadIdx.x);      // bins top-3 .. top of this thread
-  uint4 c[kHistReplicas];
-#pragma unroll
-  for (int r = 0; r < kHistReplicas; ++r) c[r] = lowest[r * (kBins / 4)];
-  uint4 t = c[0];
-#pragma unroll
-  for (int r = 1; r < kHistReplicas; ++r) {
-    t.x += c[r].x; t.y += c[r].y; t.z += c[r].z; t.w += c[r].w;
-  }
-  s.c[0] = t.w; s.c[1] = t.z; s.c[2] = t.y; s.c[3] = t.x;
-  return s;
-}
-
-// Where rank k_rem falls in a histogram, walking from the top bin down: the bin, and the rank
-// inside that bin.  Every thread of the block gets the result.
+// Where rank k_rem falls in a histogram of 2048 bins, walking from the top bin down: the bin, its population, and
+// the rank inside it.  Thread t owns bins kBins - 1 - t * PER .. downwards, c[0] the highest.  Every thread of the
+// block gets the result.
 struct BinPick {
-  uint32_t bin, k_rem;
+  uint32_t bin, count, k_rem;
 };
-__device__ __forceinline__ BinPick pick_bin(const BinSlice& sl, uint32_t k_rem, uint32_t* wave_sums,
+template <int NT>
+__device__ __forceinline__ BinPick pick_bin(const uint32_t (&c)[kBins / NT], uint32_t k_rem, uint32_t* wave_sums,
                                             uint32_t* result) {
-  const int top = kBins - 1 - threadIdx.x * kBinsPerThread;
+  constexpr int kPer = kBins / NT;
+  const int top = kBins - 1 - threadIdx.x * kPer;
   uint32_t mine = 0;
 #pragma unroll
-  for (int e = 0; e < kBinsPerThread; ++e) mine += sl.c[e];
-  uint32_t total;
-  const uint32_t above = block_excl_scan(mine, &total, wave_sums);
+  for (int e = 0; e < kPer; ++e) mine += c[e];
+  const uint32_t above = block_excl_scan<NT>(mine, wave_sums);
   if (above < k_rem && k_rem <= above + mine) {          // exactly one thread
     uint32_t cum = above;
     bool done = false;
 #pragma unroll
-    for (int e = 0; e < kBinsPerThread; ++e) {
-      if (!done && cum + sl.c[e] >= k_rem) {
+    for (int e = 0; e < kPer; ++e) {
+      if (!done && cum + c[e] >= k_rem) {
         result[0] = (uint32_t)(top - e);
-        result[1] = k_rem - cum;
+        result[1] = c[e];
+        result[2] = k_rem - cum;
         done = true;
       }
-      cum += sl.c[e];
+      cum += c[e];
     }
   }
   __syncthreads();
-  BinPick r;
-  r.bin = result[0];
-  r.k_rem = result[1];
+  const BinPick r = {result[0], result[1], result[2]};
   __syncthreads();                       // result[] is free for the next pick
   return r;
 }
+// This thread's bins of a histogram in LDS.
+template <int NT>
+__device__ __forceinline__ void lds_bins(const uint32_t* h, uint32_t (&c)[kBins / NT]) {
+#pragma unroll
+  for (int e = 0; e < kBins / NT; ++e) c[e] = h[kBins - 1 - (int)threadIdx.x * (kBins / NT) - e];
+}
 
-// Key bits fixed by the passes before PASS, and the rank still to find below them.  All
-// histogram loads are issued before the first scan, so they cost one round trip together.
-// A pass picks one histogram itself (the one the pass before it filled) and reads what the earlier passes
-// picked from the workspace, where the pass that made the pick left it (every workgroup writes the same
-// two words).
-template <int PASS>
-__device__ __forceinline__ void resolve_prefix(uint32_t* __restrict__ w, uint32_t k, uint32_t* wave_sums,
-                                               uint32_t* result, uint32_t* prefix, uint32_t* k_rem) {
-  uint32_t p = 0, kr = k;
-  if (PASS == 0) {
-    *prefix = 0;
-    *k_rem = k;
-    return;
+// Keys in [lo, hi] of which the k_rem largest are wanted, narrowed until they all are or only one value is left:
+// the caller then takes every key above hi and the first k_rem keys (by position) in [lo, hi].
+// add(lo, hi, shift) adds the digits ((key - lo) >> shift) of the keys in [lo, hi] to the histogram.
+struct Narrowed {
+  uint32_t lo, hi, k_rem;
+};
+template <int NT, typename Add>
+__device__ __forceinline__ Narrowed narrow(Narrowed r, uint32_t count, uint32_t* h, uint32_t* wave_sums, uint32_t* result,
+                                           Add&& add) {
+  while (r.lo != r.hi && count != r.k_rem) {             // the same in every thread
+    const int bits = 32 - __clz(r.hi - r.lo), shift = bits > 11 ? bits - 11 : 0;
+    for (int i = threadIdx.x; i < kBins; i += NT) h[i] = 0u;
+    __syncthreads();
+    add(r.lo, r.hi, shift);
+    __syncthreads();
+    uint32_t c[kBins / NT];
+    lds_bins<NT>(h, c);
+    const BinPick p = pick_bin<NT>(c, r.k_rem, wave_sums, result);
+    const uint32_t lo = r.lo + (p.bin << shift), last = lo + ((1u << shift) - 1u);
+    r.hi = last < r.hi ? last : r.hi;
+    r.lo = lo;
+    r.k_rem = p.k_rem;
+    count = p.count;
   }
-  const BinSlice sl = load_slice(w + TopkLayout::hist + (PASS - 1) * kHistReplicas * kBins);
-  uint32_t b0 = 0, k0 = 0, b1 = 0, k1 = 0;
-  if (PASS >= 2) {
-    b0 = w[TopkLayout::pick + 0];
-    k0 = w[TopkLayout::pick + 1];
-  }
-  if (PASS >= 3) {
-    b1 = w[TopkLayout::pick + 2];
-    k1 = w[TopkLayout::pick + 3];
-  }
-  if (PASS == 1) {
-    const BinPick b = pick_bin(sl, k, wave_sums, result);
-    if (threadIdx.x == 0) {
-      w[TopkLayout::pick + 0] = b.bin;
-      w[TopkLayout::pick + 1] = b.k_rem;
-    }
-    p = b.bin << 21;
-    kr = b.k_rem;
-  } else if (PASS == 2) {
-    const BinPick b = pick_bin(sl, k0, wave_sums, result);
-    if (threadIdx.x == 0) {
-      w[TopkLayout::pick + 2] = b.bin;
-      w[TopkLayout::pick + 3] = b.k_rem;
-    }
-    p = (b0 << 21) | (b.bin << 10);
-    kr = b.k_rem;
-  } else {
-    const BinPick b = pick_bin(sl, k1, wave_sums, result);
-    p = (b0 << 21) | (b1 << 10) | b.bin;
-    kr = b.k_rem;
-  }
-  *prefix = p;
-  *k_rem = kr;
+  return r;
 }
 
 __global__ void topk_init(uint32_t* ws, int64_t row_words) {
@@ -234,56 +201,84 @@ __global__ void topk_init(uint32_t* ws, int64_t row_words) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kHistWords; i += gridDim.x * blockDim.x) w[i] = 0u;
 }
 
-// PASS 0: bits 31..21, PASS 1: bits 20..10, PASS 2: bits 9..0.
-template <int PASS>
+// The histogram, for callers whose scores were written by something else.
 __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ score, int64_t n, int64_t score_bs,
-                                                      uint32_t* __restrict__ ws, int64_t row_words, int nblk,
-                                                      uint32_t k, int sub) {
+                                                      uint32_t* __restrict__ ws, int64_t row_words, int sub) {
   __shared__ uint32_t h[kBins];
+  const float* row = score + (int64_t)blockIdx.y * score_bs;
+  const int64_t first = (int64_t)blockIdx.x * kTile * sub + (int64_t)threadIdx.x * kItems;
+  uint32_t key[kItems];
+  bool ok[kItems];
+  load_keys(row, n, first, key, ok);
+  for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
+  __syncthreads();
+  for (int st = 0; st < sub; ++st) {
+    if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
+#pragma unroll
+    for (int e = 0; e < kItems; ++e) hist_add(h, ok[e], score_bin(key[e]));
+  }
+  __syncthreads();
+  hist_flush(ws + (int64_t)blockIdx.y * row_words + TopkLayout::hist, h, blockIdx.x, threadIdx.x, kThreads);
+}
+
+__global__ __launch_bounds__(kThreads) void topk_compact(const float* __restrict__ score, int64_t n, int64_t score_bs,
+                                                         uint32_t* __restrict__ ws, int64_t row_words, int nblk,
+                                                         uint32_t k, int sub) {
   __shared__ uint32_t wave_sums[kThreads / 64];
-  __shared__ uint32_t result[2];
-  __shared__ uint32_t n_above, n_cand;             // PASS 2: this workgroup's scores above / sharing the prefix
+  __shared__ uint32_t result[3];
+  __shared__ uint32_t n_above, n_cand;
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
   const int64_t first = (int64_t)blockIdx.x * kTile * sub + (int64_t)threadIdx.x * kItems;
   uint32_t key[kItems];
   bool ok[kItems];
   load_keys(row, n, first, key, ok);
-  for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
+  uint32_t c[kBins / kThreads];
+  {
+    static_assert(kBins / kThreads == 4, "one 16-byte load per copy");
+    const uint4* lowest = (const uint4*)(w + TopkLayout::hist) + (kThreads - 1 - threadIdx.x);      // bins top-3 .. top of this thread
+    uint4 copy[kHistReplicas];
+#pragma unroll
+    for (int r = 0; r < kHistReplicas; ++r) copy[r] = lowest[r * (kBins / 4)];
+    uint4 t = copy[0];
+#pragma unroll
+    for (int r = 1; r < kHistReplicas; ++r) {
+      t.x += copy[r].x; t.y += copy[r].y; t.z += copy[r].z; t.w += copy[r].w;
+    }
+    c[0] = t.w; c[1] = t.z; c[2] = t.y; c[3] = t.x;
+  }
   if (threadIdx.x == 0) {
     n_above = 0u;
     n_cand = 0u;
   }
-  uint32_t prefix, k_rem;
-  resolve_prefix<PASS>(w, k, wave_sums, result, &prefix, &k_rem);
-  __syncthreads();
-  uint16_t* cand = (uint16_t*)(w + TopkLayout::blk + 2 * nblk) + (int64_t)blockIdx.x * kTile * sub;
+  const BinPick p = pick_bin<kThreads>(c, k, wave_sums, result);       // (its barriers also publish the zeros)
+  if (threadIdx.x == 0) {                                              // every workgroup writes the same words
+    w[TopkLayout::pick + 0] = p.bin;
+    w[TopkLayout::pick + 1] = p.count;
+    w[TopkLayout::pick + 2] = p.k_rem;
+  }
+  uint32_t lo, hi;
+  bin_keys(p.bin, &lo, &hi);
+  const uint32_t cap = (uint32_t)(kCandPerTile * sub);
+  uint32_t* cand = w + TopkLayout::blk + 2 * count_words(nblk) + (int64_t)blockIdx.x * cap;
   uint32_t above = 0;
-  for (int st = 0; st < sub; ++st) {               // `sub` tiles of kTile scores, one histogram
+  for (int st = 0; st < sub; ++st) {
     if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
-      if (PASS == 0) {
-        hist_add(h, ok[e], key[e] >> 21);
-      } else if (PASS == 1) {
-        hist_add(h, ok[e] && (key[e] >> 21) == (prefix >> 21), (key[e] >> 10) & 2047u);
-      } else {
-        const bool shares = ok[e] && (key[e] >> 10) == (prefix >> 10);
-        hist_add(h, shares, key[e] & 1023u);
-        above += (ok[e] && (key[e] >> 10) > (prefix >> 10)) ? 1u : 0u;
-        if (shares) cand[atomicAdd(&n_cand, 1u)] = (uint16_t)(key[e] & 1023u);   // order does not matter: they are counted
+      above += ok[e] && key[e] > hi ? 1u : 0u;
+      if (ok[e] && key[e] >= lo && key[e] <= hi) {
+        const uint32_t at = atomicAdd(&n_cand, 1u);                    // order does not matter: they are counted
+        if (at < cap) cand[at] = key[e];
       }
     }
   }
-  if (PASS == 2) {
-    above = wave_incl_scan(above);                 // lane 63 holds the wave's total
-    if ((threadIdx.x & 63) == 63) atomicAdd(&n_above, above);
-  }
+  above = wave_incl_scan(above);                                       // lane 63 holds the wave's total
+  if ((threadIdx.x & 63) == 63) atomicAdd(&n_above, above);
   __syncthreads();
-  hist_flush(w + TopkLayout::hist + PASS * kHistReplicas * kBins, h, blockIdx.x, threadIdx.x, kThreads);
-  if (PASS == 2 && threadIdx.x == 0) {
+  if (threadIdx.x == 0) {
     w[TopkLayout::blk + blockIdx.x] = n_above;
-    w[TopkLayout::blk + nblk + blockIdx.x] = n_cand;
+    w[TopkLayout::blk + count_words(nblk) + blockIdx.x] = n_cand;
   }
 }
 
@@ -291,8 +286,11 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
                                                        uint32_t* __restrict__ ws, int64_t row_words, int nblk,
                                                        int64_t base, int32_t* __restrict__ idx, int64_t idx_bs,
                                                        uint32_t k, int sub) {
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t list_key[kListMax], list_owner[kListMax];
   __shared__ uint32_t wave_sums[2 * kThreads / 64];
-  __shared__ uint32_t result[2];
+  __shared__ uint32_t result[3];
+  __shared__ uint32_t n_list, too_many;
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
   int32_t* out = idx + (int64_t)blockIdx.y * idx_bs;
@@ -300,68 +298,94 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
   uint32_t key[kItems];
   bool ok[kItems];
   load_keys(row, n, first0, key, ok);
-  // What the third histogram pass left about the first workgroup this thread looks at: requested
-  // before T is resolved, so that the two round trips overlap.
-  constexpr int kPeek = 4;
-  const uint16_t* cand_all = (const uint16_t*)(w + TopkLayout::blk + 2 * nblk);
-  const int64_t cap = (int64_t)kTile * sub;
-  uint32_t c0 = 0, above0 = 0, peek[kPeek];
-#pragma unroll
-  for (int j = 0; j < kPeek; ++j) peek[j] = 0u;
-  if ((int)threadIdx.x < (int)blockIdx.x) {
-    above0 = w[TopkLayout::blk + threadIdx.x];
-    c0 = w[TopkLayout::blk + nblk + threadIdx.x];
-    // read whether or not that workgroup left so many (its slots exist either way; the count decides below what
-    // is used): asking for the count first would put a second round trip in front of them
-    static_assert(kPeek <= kTile, "a workgroup's candidate slots");
-#pragma unroll
-    for (int j = 0; j < kPeek; ++j) peek[j] = cand_all[threadIdx.x * cap + j];
+  const uint32_t cap = (uint32_t)(kCandPerTile * sub);
+  const uint32_t* n_above = w + TopkLayout::blk;
+  const uint32_t* n_cand = n_above + count_words(nblk);
+  const uint32_t* cand = n_cand + count_words(nblk);
+  const uint32_t bin = w[TopkLayout::pick + 0], in_bin = w[TopkLayout::pick + 1];
+  Narrowed r;
+  r.k_rem = w[TopkLayout::pick + 2];
+  if (threadIdx.x == 0) {
+    n_list = 0u;
+    too_many = in_bin > kListMax ? 1u : 0u;
   }
-  uint32_t T, need;                                      // need: equal-to-T scores to take, lowest positions first
-  resolve_prefix<3>(w, k, wave_sums, result, &T, &need);
-  // scores above / equal to T in the workgroups before this one: those above the 22-bit prefix, plus
-  // those sharing it whose last digit is above / equal to T's
-  const uint32_t t_digit = T & 1023u;
+  __syncthreads();
   uint32_t my_gt = 0, my_eq = 0;
-  for (int i = threadIdx.x; i < (int)blockIdx.x; i += kThreads) {
-    const bool head = i == (int)threadIdx.x;
-    uint32_t c = head ? c0 : w[TopkLayout::blk + nblk + i];
-    c = c < (uint32_t)cap ? c : (uint32_t)cap;           // a workgroup cannot have left more than its scores: the reads below stay inside its slots
-    my_gt += head ? above0 : w[TopkLayout::blk + i];
-    uint32_t j0 = 0;
-    if (head) {
+  if (in_bin <= kListMax) {
+    for (int i = threadIdx.x; i < nblk; i += kThreads) {
+      // the first slots are read whether or not that workgroup filled them: asking for the count first would put a
+      // second round trip in front of them
+      const uint32_t cnt = n_cand[i], above = n_above[i];
+      const uint4 a = *(const uint4*)(cand + (int64_t)i * cap), b = *(const uint4*)(cand + (int64_t)i * cap + 4);
+      my_gt += i < (int)blockIdx.x ? above : 0u;
+      if (cnt > 0) {
+        if (cnt > cap) too_many = 1u;
+        const uint32_t at = atomicAdd(&n_list, cnt);
+        const uint32_t peek[kPeek] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-      for (int j = 0; j < kPeek; ++j) {
-        my_gt += ((uint32_t)j < c && peek[j] > t_digit) ? 1u : 0u;
-        my_eq += ((uint32_t)j < c && peek[j] == t_digit) ? 1u : 0u;
+        for (uint32_t j = 0; j < (uint32_t)kPeek; ++j)
+          if (j < cnt && at + j < kListMax) {
+            list_key[at + j] = peek[j];
+            list_owner[at + j] = (uint32_t)i;
+          }
+        for (uint32_t j = kPeek; j < cnt && j < cap && at + j < kListMax; ++j) {
+          list_key[at + j] = cand[(int64_t)i * cap + j];
+          list_owner[at + j] = (uint32_t)i;
+        }
       }
-      j0 = kPeek;
-    }
-    for (uint32_t j = j0; j < c; ++j) {
-      const uint32_t dgt = cand_all[i * cap + j];
-      my_gt += dgt > t_digit ? 1u : 0u;
-      my_eq += dgt == t_digit ? 1u : 0u;
     }
   }
+  bin_keys(bin, &r.lo, &r.hi);
+  __syncthreads();
+  if (!too_many) {
+    const uint32_t listed = n_list;
+    r = narrow<kThreads>(r, in_bin, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
+      for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
+        const uint32_t v = list_key[e];
+        if (v >= lo && v <= hi) atomicAdd(&h[(v - lo) >> shift], 1u);
+      }
+    });
+    for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
+      const bool before = list_owner[e] < blockIdx.x;
+      my_gt += before && list_key[e] > r.hi ? 1u : 0u;
+      my_eq += before && list_key[e] >= r.lo && list_key[e] <= r.hi ? 1u : 0u;
+    }
+  } else {
+    // more keys in the bin than the lists hold: the same from the scores themselves
+    r = narrow<kThreads>(r, in_bin, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
+      for (int64_t i0 = threadIdx.x & ~63; i0 < n; i0 += kThreads) {     // whole waves stay in step for hist_add
+        const int64_t i = i0 + (threadIdx.x & 63);
+        const uint32_t v = ordered_key(row[i < n ? i : 0]);
+        hist_add(h, i < n && v >= lo && v <= hi, (v - lo) >> shift);
+      }
+    });
+    my_gt = 0;
+    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x * kTile * sub; i += kThreads) {
+      const uint32_t v = ordered_key(row[i]);
+      my_gt += v > r.hi ? 1u : 0u;
+      my_eq += v >= r.lo && v <= r.hi ? 1u : 0u;
+    }
+  }
+  const uint32_t need = r.k_rem;
   uint32_t off_gt, off_eq, unused_a, unused_b;
-  block_excl_scan2(my_gt, my_eq, &unused_a, &unused_b, &off_gt, &off_eq, wave_sums);
+  block_excl_scan2<kThreads>(my_gt, my_eq, &unused_a, &unused_b, &off_gt, &off_eq, wave_sums);
   for (int st = 0; st < sub; ++st) {                     // tiles in position order; the offsets run on
     const int64_t first = first0 + (int64_t)st * kTile;
     if (st > 0) load_keys(row, n, first, key, ok);
     uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
-      gt += (ok[e] && key[e] > T) ? 1u : 0u;
-      eq += (ok[e] && key[e] == T) ? 1u : 0u;
+      gt += (ok[e] && key[e] > r.hi) ? 1u : 0u;
+      eq += (ok[e] && key[e] >= r.lo && key[e] <= r.hi) ? 1u : 0u;
     }
     uint32_t tot_g, tot_e, g_before, e_before;
-    block_excl_scan2(gt, eq, &g_before, &e_before, &tot_g, &tot_e, wave_sums);
+    block_excl_scan2<kThreads>(gt, eq, &g_before, &e_before, &tot_g, &tot_e, wave_sums);
     g_before += off_gt;
     e_before += off_eq;
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
       if (!ok[e]) continue;
-      const bool is_gt = key[e] > T, is_eq = key[e] == T;
+      const bool is_gt = key[e] > r.hi, is_eq = !is_gt && key[e] >= r.lo;
       if (is_gt || (is_eq && e_before < need)) {
         const uint32_t slot = g_before + (e_before < need ? e_before : need);
         if (slot < k) out[slot] = (int32_t)(base + first + e);
@@ -371,6 +395,108 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
     }
     off_gt += tot_g;
     off_eq += tot_e;
+  }
+}
+
+// A whole row in one workgroup: wave w holds scores [64 * ITEMS * w, ...), lane l of it every 64th, so that loads are
+// coalesced and (item, lane) is position order inside the wave.  Before the selection it finishes the scores where
+// that is left to do (see ScoreTail): pooling over +-eps, minus mu = the largest of n_part partial maxima.
+// What bounds it: round trips and barriers (two loads deep, a histogram or two, one scan): 5.5 us at 3.8k scores
+// where the four launches it replaces (subtract mu, two histogram passes, write) took 13.7 us.
+template <int ITEMS>
+__global__ __launch_bounds__(kSelectSmallThreads) void select_small(ScoreTail t, float* __restrict__ score, int64_t score_bs,
+                                                                    int n, int64_t base, int32_t* __restrict__ idx,
+                                                                    int64_t idx_bs, uint32_t k) {
+  constexpr int NT = kSelectSmallThreads, kW = NT / 64;
+  extern __shared__ float staged[];              // [n] unpooled scores when pooling
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t wave_sums[2 * kW];
+  __shared__ uint32_t result[3];
+  const float* in = t.in + (int64_t)blockIdx.x * t.in_bs;
+  int32_t* out = idx + (int64_t)blockIdx.x * idx_bs;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int first = wave * 64 * ITEMS + lane;
+  float x[ITEMS];
+#pragma unroll
+  for (int e = 0; e < ITEMS; ++e) x[e] = in[first + 64 * e < n ? first + 64 * e : 0];
+  float mu = 0.f;
+  if (t.part) {
+    const float* part = t.part + (int64_t)blockIdx.x * t.n_part;
+    float m = -INFINITY;
+    for (int i = tid; i < t.n_part; i += NT) m = fmaxf(m, part[i]);
+    m = wave_max(m);
+    if (lane == 0) wave_sums[wave] = __float_as_uint(m);
+  }
+  for (int i = tid; i < kBins; i += NT) h[i] = 0u;
+  if (t.eps > 0) {
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e)
+      if (first + 64 * e < n) staged[first + 64 * e] = x[e];
+  }
+  __syncthreads();
+  if (t.part) {
+    mu = __uint_as_float(wave_sums[0]);
+#pragma unroll
+    for (int i = 1; i < kW; ++i) mu = fmaxf(mu, __uint_as_float(wave_sums[i]));
+  }
+  uint32_t key[ITEMS];
+#pragma unroll
+  for (int e = 0; e < ITEMS; ++e) {
+    const int i = first + 64 * e;
+    const bool ok = i < n;
+    float f = x[e];
+    if (t.eps > 0 && ok) {                       // max - mu rounds as the max over the rounded differences does
+      const int a = i - t.eps > 0 ? i - t.eps : 0, b = i + t.eps < n - 1 ? i + t.eps : n - 1;
+      for (int j = a; j <= b; ++j) f = fmaxf(f, staged[j]);
+    }
+    if (t.part) f -= mu;
+    if (ok && score) score[(int64_t)blockIdx.x * score_bs + i] = f;
+    key[e] = ordered_key(f);
+    hist_add(h, ok, score_bin(key[e]));
+  }
+  __syncthreads();
+  uint32_t c[kBins / NT];
+  lds_bins<NT>(h, c);
+  const BinPick p = pick_bin<NT>(c, k, wave_sums, result);
+  Narrowed r;
+  bin_keys(p.bin, &r.lo, &r.hi);
+  r.k_rem = p.k_rem;
+  r = narrow<NT>(r, p.count, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e)
+      hist_add(h, first + 64 * e < n && key[e] >= lo && key[e] <= hi, (key[e] - lo) >> shift);
+  });
+  uint32_t gt = 0, eq = 0;                       // of the wave
+#pragma unroll
+  for (int e = 0; e < ITEMS; ++e) {
+    const bool ok = first + 64 * e < n;
+    gt += (uint32_t)__popcll(__ballot(ok && key[e] > r.hi));
+    eq += (uint32_t)__popcll(__ballot(ok && key[e] >= r.lo && key[e] <= r.hi));
+  }
+  if (lane == 0) {
+    wave_sums[wave] = gt;
+    wave_sums[kW + wave] = eq;
+  }
+  __syncthreads();
+  uint32_t g0 = 0, e0 = 0;
+#pragma unroll
+  for (int i = 0; i < kW; ++i) {
+    g0 += i < wave ? wave_sums[i] : 0u;
+    e0 += i < wave ? wave_sums[kW + i] : 0u;
+  }
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int e = 0; e < ITEMS; ++e) {
+    const bool ok = first + 64 * e < n;
+    const bool is_gt = ok && key[e] > r.hi, is_eq = ok && !is_gt && key[e] >= r.lo;
+    const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
+    const uint32_t gb = g0 + (uint32_t)__popcll(mg & below), eb = e0 + (uint32_t)__popcll(me & below);
+    if (is_gt || (is_eq && eb < r.k_rem)) {
+      const uint32_t slot = gb + (eb < r.k_rem ? eb : r.k_rem);
+      if (slot < k) out[slot] = (int32_t)(base + first + 64 * e);
+    }
+    g0 += (uint32_t)__popcll(mg);
+    e0 += (uint32_t)__popcll(me);
   }
 }
 
@@ -438,6 +564,17 @@ int64_t topk_row_stride_words(int64_t n, int batch) {
   return (int64_t)(align_up((size_t)topk_row_words(topk_plan(n, batch)) * sizeof(uint32_t), 256) / sizeof(uint32_t));
 }
 
+int launch_select_small(const ScoreTail& tail, float* score, int64_t score_bs, int64_t n, int k, int64_t base, int32_t* idx,
+                        int64_t idx_bs, int batch, hipStream_t st) {
+  const size_t lds = tail.eps > 0 ? (size_t)n * sizeof(float) : 0;
+  const auto kernel = n <= kSelectSmallThreads * 2   ? select_small<2>
+                      : n <= kSelectSmallThreads * 4 ? select_small<4>
+                                                     : select_small<kSelectSmallItems>;
+  kernel<<<batch, kSelectSmallThreads, lds, st>>>(tail, score, score_bs, (int)n, base, idx, idx_bs, (uint32_t)k);
+  ESA_LAUNCH_CHECK("select_small");
+  return ESA_OK;
+}
+
 int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx, int batch, int64_t score_bs,
                 int64_t idx_bs, void* ws, size_t ws_bytes, hipStream_t st, bool first_hist_ready) {
   if (k >= n) {
@@ -446,17 +583,20 @@ int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx
     ESA_LAUNCH_CHECK("topk_all");
     return ESA_OK;
   }
+  if (n <= kSelectSmallMax) {
+    ScoreTail whole = {score, score_bs, nullptr, 0, 0};
+    return launch_select_small(whole, nullptr, 0, n, k, base, idx, idx_bs, batch, st);
+  }
   const TopkPlan plan = topk_plan(n, batch);
   const int sub = (int)plan.sub, nblk = (int)plan.nblk;
   const int64_t row_words = topk_row_stride_words(n, batch);
   uint32_t* w = (uint32_t*)ws;
   const dim3 grid(nblk, batch);
-  if (!first_hist_ready) {     // otherwise the score call has zeroed the histograms and filled the first one
-    topk_init<<<dim3(3 * kHistReplicas, batch), 1024, 0, st>>>(w, row_words);
-    topk_hist<0><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
+  if (!first_hist_ready) {     // otherwise the score call has zeroed and filled the histogram
+    topk_init<<<dim3(kHistReplicas, batch), 1024, 0, st>>>(w, row_words);
+    topk_hist<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, sub);
   }
-  topk_hist<1><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
-  topk_hist<2><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
+  topk_compact<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
   topk_write<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, base, idx, idx_bs, (uint32_t)k, sub);
   ESA_LAUNCH_CHECK("topk");
   return ESA_OK;

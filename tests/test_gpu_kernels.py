@@ -64,3 +64,39 @@ def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
         want = orc.proximity(want, eps) if eps else want
         assert np.max(np.abs(got[b] - want)) <= F_TOL["bf16"]
         assert got[b].max() == 0.0
+
+
+def _bin_crowd(rng, n, crowd, kind):
+    """Scores of which `crowd` lie so close below -1 that they share one bin of the first histogram."""
+    s = (-2.0 - rng.random(n) * 60.0).astype(np.float32)
+    at = rng.choice(n, crowd, replace=False) if kind != "run" else np.arange(n // 3, n // 3 + crowd)
+    s[at] = np.float32(-1.0) - (np.float32(0.0) if kind == "equal" else rng.random(crowd).astype(np.float32) * np.float32(2 ** -7))
+    s[rng.choice(n, 40, replace=False)] = np.linspace(-0.9, 40.0, 40).astype(np.float32)        # both signs above it
+    return s
+
+
+# around the longest row one workgroup takes; lists that just fit, overflow one workgroup's slots, or exceed the whole list
+@pytest.mark.parametrize("n,k,crowd,kind", [
+    (1024, 1023, 900, "spread"), (8192, 2048, 5000, "spread"), (8193, 2048, 2040, "spread"), (8192, 700, 3000, "equal"),
+    (40000, 500, 1900, "run"), (100000, 2048, 2100, "spread"), (100000, 900, 2000, "equal"), (100000, 60000, 90000, "equal")])
+def test_select_topk_where_the_threshold_bin_is_crowded(esa, n, k, crowd, kind):
+    say(f"select n={n} k={k} crowd={crowd} {kind}")
+    rng = np.random.default_rng(n + crowd)
+    s = np.stack([_bin_crowd(rng, n, crowd, kind) for _ in range(2)])
+    got = esa.esa_select_topk(torch.from_numpy(s).cuda(), k, base=5).cpu().numpy()
+    for b in range(2):
+        order = np.lexsort((np.arange(n), -s[b].astype(np.float64)))[:k]
+        assert np.array_equal(got[b], np.sort(order) + 5)
+
+
+@pytest.mark.parametrize("B,l_c,n,d_c,k,eps", [(2, 1, 8192, 128, 2048, 0), (3, 1, 8192, 128, 100, 3), (1, 1, 8193, 128, 2048, 3),
+                                               (1, 33, 8192, 64, 1, 16), (2, 40, 2050, 128, 2048, 17), (2, 1, 1025, 128, 1024, 1)])
+def test_scores_finished_by_the_selection_equal_the_separate_calls(esa, B, l_c, n, d_c, k, eps):
+    say(f"fused score+select B={B} l_c={l_c} n={n} d_c={d_c} k={k} eps={eps}")
+    g = torch.Generator(device="cuda").manual_seed(n + l_c)
+    qc = torch.randn((B, l_c, d_c), generator=g, device="cuda").to(torch.bfloat16)
+    kc = torch.randn((B, n + 20, d_c), generator=g, device="cuda").to(torch.bfloat16)
+    score, idx, _, _ = esa.esa_score_select_gather(qc, kc, 7, n + 7, k, eps=eps)
+    want = esa.esa_score(qc, kc, 7, n + 7, eps=eps)
+    assert torch.equal(score, want)
+    assert torch.equal(idx, esa.esa_select_topk(want, k, base=7))
