@@ -4,7 +4,7 @@
 // (t0 - l_start): everything before the chunk plus the chunk up to itself (Algorithm 1).
 #include "esa_common.h"
 #include "attend_mfma.h"
-#include "attend_decode.h"
+#include "attend_split.h"
 #include "keyspace.h"
 
 namespace esa {
@@ -26,7 +26,7 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 }
 
 // One workgroup per (current token, query head, batch element); fp32 arithmetic with full-precision
-// expf/logf.  Serves fp32 storage and every shape the matrix-core kernel does not cover.
+// expf/logf.  Serves every shape and alignment that the tiled kernels do not cover.
 template <typename T>
 __global__ __launch_bounds__(256) void attend_fma(const T* __restrict__ q, int l_c, int h, int h_kv, int d, KeySpace ks,
                                                   int64_t n_fixed, int with_chunk, float scale, T* __restrict__ out,
@@ -107,6 +107,17 @@ __global__ void attend_merge_two(const float* __restrict__ o_a, const float* __r
   if (lse && threadIdx.x == 0) lse[r] = m + logf(wa + wb);
 }
 
+// 16-byte accesses to every row the tiled kernels touch
+bool attend_aligned(const void* q, const void* k_cache, const void* v_cache, const void* k_sel, const void* v_sel,
+                    const void* out, int64_t tok_stride, int64_t q_bs, int64_t cache_bs, int64_t sel_bs, int64_t out_bs,
+                    int64_t esz) {
+  const uintptr_t p = (uintptr_t)q | (uintptr_t)k_cache | (uintptr_t)v_cache | (uintptr_t)k_sel | (uintptr_t)v_sel | (uintptr_t)out;
+  const int64_t s = (tok_stride | q_bs | cache_bs | sel_bs | out_bs) * esz;
+  return p % 16 == 0 && s % 16 == 0;
+}
+
+constexpr int64_t kTwoCallMaxLocal = 65536;      // longer local parts of a two-call attention go to the plain kernel
+
 size_t generic_parts_bytes(int l_c, int h, int d, int batch) {
   const size_t rows = (size_t)batch * l_c * h;
   return 2 * (align_up(rows * d * sizeof(float), 256) + align_up(rows * sizeof(float), 256));
@@ -124,9 +135,9 @@ size_t attend_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int ba
   if (attend_mfma_supported(l_c, h, h_kv, d, dtype)) return attend_mfma_workspace_bytes(l_c, h, h_kv, d, batch);
   // shapes outside the matrix-core kernel: room for the two parts of a two-call attention
   const size_t parts = generic_parts_bytes(l_c, h, d, batch);
-  if (attend_decode_supported(l_c, h, h_kv, d, dtype)) {
-    const size_t dec = attend_decode_workspace_bytes(l_c, h, batch);
-    return dec > parts ? dec : parts;
+  if (attend_split_supported(l_c, h, h_kv, d, dtype, batch)) {
+    const size_t split = attend_split_workspace_bytes(l_c, h, h_kv, d, dtype, batch);
+    return split > parts ? split : parts;
   }
   return parts;
 }
@@ -140,8 +151,9 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
   if (n_sel == 0) sel_idx = nullptr;
   const int64_t n_fixed = sg.i_end + n_sel + (t0 - sg.l_start);
   const bool mfma_shape = attend_mfma_supported(l_c, h, h_kv, d, dtype);
+  const int64_t esz = (dtype == ESA_F32) ? 4 : 2;
   const bool mfma_aligned =
-      attend_mfma_aligned(q, k_cache, v_cache, k_sel, v_sel, out, tok_stride, q_bs, cache_bs, sel_bs, out_bs);
+      attend_aligned(q, k_cache, v_cache, k_sel, v_sel, out, tok_stride, q_bs, cache_bs, sel_bs, out_bs, esz);
   // The two calls of a separately encoded attention must take the same kernel: no fallback between them.
   if (mfma_shape && !mfma_aligned && part != kAttendAll && split == ESA_SPLIT_ALGORITHM1)
     ESA_FAIL(ESA_EINVAL, "esa_attend (two calls, Algorithm 1 grouping): pointers and strides must be 16-byte aligned");
@@ -156,23 +168,26 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
   // per part and merges.
   const bool two_parts = part != kAttendAll && split == ESA_SPLIT_ALGORITHM1;
   if (part == kAttendLocal && !two_parts) return ESA_OK;
-  if (two_parts && attend_decode_supported(l_c, h, h_kv, d, dtype) && (int64_t)batch * l_c <= 65535 &&
-      attend_decode_covers_parts(t0 - sg.l_start + l_c, l_c, h_kv, batch)) {
-    // decode-sized chunk in Algorithm 1's two parts: both calls must agree on this kernel, so nothing
-    // that only one of them knows (the number of selected tokens, its pointers' alignment) may veto it
-    if (!attend_mfma_aligned(q, k_cache, v_cache, k_sel, v_sel, out, tok_stride, q_bs, cache_bs, sel_bs, out_bs))
+  // Few current tokens, or fp32.  (The kernel keeps row numbers in 31 bits and row strides in 32.)  The two calls of a
+  // separately encoded attention must agree on the kernel, so nothing that only one of them knows (the number of selected
+  // tokens, its pointers' alignment) may decide: they take it for bf16 rows of head size 128 and insist on alignment.
+  const bool split_shape = attend_split_supported(l_c, h, h_kv, d, dtype, batch) && t0 + l_c <= (int64_t)INT32_MAX &&
+                           tok_stride * esz < ((int64_t)1 << 32);
+  const bool split_two = dtype == ESA_BF16 && d == 128 && 8 % (h / h_kv) == 0 && t0 - sg.l_start + l_c <= kTwoCallMaxLocal;
+  if (split_shape && (two_parts ? split_two : mfma_aligned)) {
+    if (!mfma_aligned)
       ESA_FAIL(ESA_EINVAL, "esa_attend (two calls, Algorithm 1 grouping): pointers and strides must be 16-byte aligned");
-    return launch_attend_decode(part == kAttendLocal ? 1 : 2, q, l_c, h, h_kv, k_cache, v_cache, tok_stride, t0, sg.i_end,
-                                sg.l_start, k_sel, v_sel, n_sel, sel_idx, idx_bs, scale, out, lse, batch, q_bs, cache_bs,
-                                sel_bs, out_bs, ws, ws_bytes, st);
+    const SplitCall call = {l_c, h, h_kv, d, dtype, batch, scale, k_sel, v_sel, sel_bs, out, out_bs, lse, ws, ws_bytes};
+    const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
+    const int64_t n_local = t0 - sg.l_start, n_global = sg.i_end + n_sel;
+    if (!two_parts)
+      return launch_attend_split(call, make_view(q, q_bs, cache, esz, sg.i_end, n_sel, sg.l_start, n_fixed, 1, 0, 0, sel_idx,
+                                                 idx_bs, sg.l_start), nullptr, st);
+    if (part == kAttendLocal)
+      return launch_attend_split_early(call, make_view(q, q_bs, cache, esz, 0, 0, sg.l_start, n_local, 1, 0, 0), n_local + l_c, st);
+    return launch_attend_split_late(call, make_view(q, q_bs, cache, esz, sg.i_end, n_sel, sg.l_start, n_global, 0, 0, 0, sel_idx,
+                                                    idx_bs, sg.l_start), n_global, n_local + l_c, st);
   }
-  if (!two_parts && attend_decode_supported(l_c, h, h_kv, d, dtype) && (int64_t)batch * l_c <= 65535 &&
-      attend_decode_covers(n_fixed + l_c, l_c, h_kv, batch) &&
-      attend_mfma_aligned(q, k_cache, v_cache, k_sel, v_sel, out, tok_stride, q_bs, cache_bs, sel_bs, out_bs)) {
-    return launch_attend_decode(0, q, l_c, h, h_kv, k_cache, v_cache, tok_stride, t0, sg.i_end, sg.l_start, k_sel, v_sel,
-                                n_sel, sel_idx, idx_bs, scale, out, lse, batch, q_bs, cache_bs, sel_bs, out_bs, ws, ws_bytes, st);
-  }
-  const int64_t esz = (dtype == ESA_F32) ? 4 : 2;
   KeySpace ks;
   ks.k_cache = (const char*)k_cache;
   ks.v_cache = (const char*)v_cache;
@@ -243,9 +258,11 @@ size_t attend_reencoded_workspace_bytes(int l_c, int h, int h_kv, int d, int dty
 
 // Section 3.2 on un-encoded queries and keys.  The workspace holds, behind the attention workspace
 // proper, the chunk's queries in their two encodings and a dense re-encoded copy of the local rows
-// [l_start, t0 + l_c) of the key cache with the matching value rows; the local part then runs on
+// [l_start, t0 + l_c) of the key cache; the local part then runs on
 // that copy as a sequence of its own (no initial tokens, window = all of it), the global part on
-// the caller's un-encoded caches (position 0 is the identity), merged by Algorithm 1's rule.
+// the caller's un-encoded caches (position 0 is the identity), merged by Algorithm 1's rule.  The tiled kernels take
+// both parts in one launch and read the local values where they are; only the plain kernel, which takes keys and
+// values of one layout, gets a copy of these too.
 int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, const void* k_cache, const void* v_cache,
                             int64_t tok_stride, int64_t t0, int64_t l_i, int64_t l_l, const void* k_sel,
                             const void* v_sel, int n_sel, float scale, double w, double base, void* out, float* lse,
@@ -265,16 +282,12 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   char* v_loc = k_loc + kv_bytes;
   const int64_t q_row = (int64_t)h * d, kv_row = (int64_t)h_kv * d;
   const int64_t qw_bs = (int64_t)l_c * q_row, kvw_bs = rows * kv_row;
-  if (attend_mfma_supported(l_c, h, h_kv, d, dtype) &&
-      !attend_mfma_aligned(q_loc, k_cache, v_cache, k_sel, v_sel, out, tok_stride, qw_bs, cache_bs, sel_bs, out_bs))
+  const bool ok16 = attend_aligned(q_loc, k_cache, v_cache, k_sel, v_sel, out, tok_stride, qw_bs, cache_bs, sel_bs, out_bs, (int64_t)esz);
+  const bool mfma = attend_mfma_supported(l_c, h, h_kv, d, dtype);
+  const bool split = !mfma && attend_split_supported(l_c, h, h_kv, d, dtype, batch) && ok16 &&
+                     t0 + l_c <= (int64_t)INT32_MAX && tok_stride * (int64_t)esz < ((int64_t)1 << 32);
+  if (mfma && !ok16)
     ESA_FAIL(ESA_EINVAL, "esa_attend_reencoded: pointers and strides must be 16-byte aligned for this shape");
-  // decode-sized chunks on the split-key kernel: the global part must fit its half of the slices too
-  // (checked here so that nothing is enqueued when it does not)
-  if (attend_decode_supported(l_c, h, h_kv, d, dtype) && (int64_t)batch * l_c <= 65535 &&
-      attend_decode_covers_parts(n_loc + l_c, l_c, h_kv, batch) && sg.i_end + n_sel > 0 &&
-      !attend_decode_covers_parts(sg.i_end + n_sel, l_c, h_kv, batch))
-    ESA_FAIL(ESA_EUNSUPPORTED, "esa_attend_reencoded: %lld initial and selected keys exceed the decode kernel's range",
-             (long long)(sg.i_end + n_sel));
 
   RopeJob jobs[4];
   jobs[0] = RopeJob{q, q_loc, l_c, q_row, q_row, q_bs, qw_bs, (double)n_loc, 1.0, h, 1};     // local queries, in order
@@ -283,12 +296,20 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   const char* v_rows = (const char*)v_cache + (size_t)sg.l_start * tok_stride * esz;
   jobs[2] = RopeJob{k_rows, k_loc, rows, tok_stride, kv_row, cache_bs, kvw_bs, 0.0, 1.0, h_kv, 1};   // local keys from 0
   jobs[3] = RopeJob{v_rows, v_loc, rows, tok_stride, kv_row, cache_bs, kvw_bs, 0.0, 0.0, h_kv, 0};   // their values
-  int rc = launch_rope_jobs(jobs, 4, d, base, dtype, batch, st);
+  const bool tiled = mfma || split;
+  int rc = launch_rope_jobs(jobs, tiled ? 3 : 4, d, base, dtype, batch, st);
   if (rc != ESA_OK) return rc;
-  if (attend_mfma_supported(l_c, h, h_kv, d, dtype))     // both parts in one launch of the matrix-core kernel
-    return launch_attend_mfma_two_views(q_loc, q_glob, qw_bs, l_c, h, h_kv, d, k_loc, v_loc, n_loc, kvw_bs, k_cache, v_cache,
-                                        tok_stride, cache_bs, sg.i_end, k_sel, v_sel, n_sel, sel_bs, scale, out, lse, batch,
-                                        out_bs, ws, own, st);
+  const CacheRef local = {k_loc, v_rows, kv_row, tok_stride, kvw_bs, cache_bs};
+  const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
+  if (mfma)
+    return launch_attend_mfma_two_views(q_loc, q_glob, qw_bs, l_c, h, h_kv, d, local, n_loc, cache, sg.i_end, k_sel, v_sel, n_sel,
+                                        sel_bs, scale, out, lse, batch, out_bs, ws, own, st);
+  if (split) {
+    const SplitCall call = {l_c, h, h_kv, d, dtype, batch, scale, k_sel, v_sel, sel_bs, out, out_bs, lse, ws, own};
+    const KeyView a = make_view(q_loc, qw_bs, local, (int64_t)esz, 0, 0, 0, n_loc, 1, 0, 0);
+    const KeyView b = make_view(q_glob, qw_bs, cache, (int64_t)esz, sg.i_end, n_sel, 0, sg.i_end + n_sel, 0, 0, 0);
+    return launch_attend_split(call, a, &b, st);
+  }
   rc = launch_attend(kAttendLocal, ESA_SPLIT_ALGORITHM1, q_loc, l_c, h, h_kv, d, k_loc, v_loc, kv_row, n_loc, 0, n_loc,
                      nullptr, nullptr, 0, nullptr, 0, scale, nullptr, nullptr, dtype, batch, qw_bs, kvw_bs, 0, 0, ws, own, st);
   if (rc != ESA_OK) return rc;

@@ -60,27 +60,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.f;        // the softmax reference lags the running maximum by at most 2^8
 constexpr float kLn2 = 0.6931471805599453f;
 
-// What one slice of a launch attends to: a query tensor and a virtual key sequence
-// [ cache rows [0, i_end) | n_sel gathered rows | cache rows [l_start, ..) ].  A launch carries two views;
-// the usual one uses view 0 only, the re-encoded attention of Section 3.2 gives the local keys (their own
-// encoding of queries and keys, causal) to view 0 and the initial and selected keys (queries at the fixed
-// position, every key visible) to view 1, so that both parts run in one launch.
-struct KeyView {
-  const bf16_t* q;
-  const char* k_cache;
-  const char* v_cache;
-  int64_t q_bs, cache_bs_bytes;
-  uint32_t tok_bytes;               // row stride of the cache
-  uint32_t i_end, n_sel, l_start;
-  uint32_t n_fixed;                 // keys every row sees
-  const int32_t* sel_idx;           // not null: the n_sel selected rows are cache rows sel_idx[0..n_sel), not a gathered buffer
-  int64_t idx_bs;                   // batch stride of the index list
-  uint32_t idx_limit;               // indices are clamped into [0, idx_limit)
-  int with_chunk;     // 1: the virtual sequence ends with the current chunk (causal); 0: every key is visible to every row
-  int n_split;        // slices of this view (view 0's slices come first)
-  int slot0;          // partial results of slice s go to slot slot0 + s
-};
-
 struct AttendArgs {
   KeyView view[2];
   bf16_t* out;
@@ -122,24 +101,23 @@ __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
   return *(uint32_t*)&h;
 }
 
-// Row of virtual key j: which buffer, and the byte offset inside it (branch-free).
+// Row of virtual key j: which buffer, and its number there (branch-free).
 struct RowRef {
   bool in_sel;
-  uint64_t off;
+  uint32_t row;
 };
 __device__ __forceinline__ uint32_t clamped_index(const KeyView& V, const int32_t* sidx, uint32_t pos) {
   const int32_t v = sidx[pos];      // a middle token's position; clamped so that a bad index cannot leave the cache
   return v < 0 ? 0u : ((uint32_t)v < V.idx_limit ? (uint32_t)v : V.idx_limit - 1);
 }
 // sidx: this batch element's index list, or null when the selected rows come from the gathered buffer
-__device__ __forceinline__ RowRef row_ref(const KeyView& V, const int32_t* sidx, uint32_t sel_bytes, uint32_t j) {
+__device__ __forceinline__ RowRef row_ref(const KeyView& V, const int32_t* sidx, uint32_t j) {
   const bool in_i = j < V.i_end;
   const bool in_s = !in_i && (j < V.i_end + V.n_sel);
-  uint32_t row = in_i ? j : (in_s ? j - V.i_end : j - V.i_end - V.n_sel + V.l_start);
   RowRef r;
+  r.row = in_i ? j : (in_s ? j - V.i_end : j - V.i_end - V.n_sel + V.l_start);
   r.in_sel = in_s && !sidx;
-  if (in_s && sidx) row = clamped_index(V, sidx, row);
-  r.off = (uint64_t)row * (r.in_sel ? sel_bytes : V.tok_bytes);
+  if (in_s && sidx) r.row = clamped_index(V, sidx, r.row);
   return r;
 }
 
@@ -184,31 +162,11 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const int b = pair / a.h_kv, g = pair % a.h_kv;
   const int qt = inner % a.n_qt, slice = inner / a.n_qt;
   const int vw = slice >= a.view[0].n_split ? 1 : 0;             // which view this slice belongs to
-  // field-wise select (not an indexed load): every kernel argument is then fetched in the first round trip
-  KeyView V;
-  {
-    const KeyView &v0 = a.view[0], &v1 = a.view[1];
-    V.q = vw ? v1.q : v0.q;
-    V.k_cache = vw ? v1.k_cache : v0.k_cache;
-    V.v_cache = vw ? v1.v_cache : v0.v_cache;
-    V.q_bs = vw ? v1.q_bs : v0.q_bs;
-    V.cache_bs_bytes = vw ? v1.cache_bs_bytes : v0.cache_bs_bytes;
-    V.tok_bytes = vw ? v1.tok_bytes : v0.tok_bytes;
-    V.i_end = vw ? v1.i_end : v0.i_end;
-    V.n_sel = vw ? v1.n_sel : v0.n_sel;
-    V.l_start = vw ? v1.l_start : v0.l_start;
-    V.n_fixed = vw ? v1.n_fixed : v0.n_fixed;
-    V.sel_idx = vw ? v1.sel_idx : v0.sel_idx;
-    V.idx_bs = vw ? v1.idx_bs : v0.idx_bs;
-    V.idx_limit = vw ? v1.idx_limit : v0.idx_limit;
-    V.with_chunk = vw ? v1.with_chunk : v0.with_chunk;
-    V.n_split = vw ? v1.n_split : v0.n_split;
-    V.slot0 = vw ? v1.slot0 : v0.slot0;
-  }
+  const KeyView V = pick_view(a.view, vw);
   const int split = slice - (vw ? a.view[0].n_split : 0);        // slice number inside the view
 
-  const char* kc = V.k_cache + (int64_t)b * V.cache_bs_bytes + (int64_t)g * D * 2;
-  const char* vc = V.v_cache + (int64_t)b * V.cache_bs_bytes + (int64_t)g * D * 2;
+  const char* kc = V.k_cache + (int64_t)b * V.k_bs_bytes + (int64_t)g * D * 2;
+  const char* vc = V.v_cache + (int64_t)b * V.v_bs_bytes + (int64_t)g * D * 2;
   const char* ksl = a.k_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
   const char* vsl = a.v_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
 
@@ -291,32 +249,34 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     bf16_t* vd = vt + wave * 512;
     constexpr int kGroupStep = kWaves * 512;
     if (seg == 1 && sidx) {             // cache rows looked up by idx_prefetch for this tile
-      uint64_t off[kMyRows];
+      uint32_t row[kMyRows];
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) off[u] = (uint64_t)cache_row(picked[u]) * V.tok_bytes;
+      for (int u = 0; u < kMyRows; ++u) row[u] = cache_row(picked[u]);
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(kc + (off[u] + kcol), kd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u) dma16(kc + ((uint64_t)row[u] * V.k_bytes + kcol), kd + kGroupStep * u);
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(vc + (off[u] + vcol), vd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u) dma16(vc + ((uint64_t)row[u] * V.v_bytes + vcol), vd + kGroupStep * u);
     } else if (seg >= 0) {
-      const uint32_t stride = seg ? a.sel_bytes : V.tok_bytes;
-      const char* kb = (seg ? ksl : kc) + (uint64_t)row0 * stride;
-      const char* vbase = (seg ? vsl : vc) + (uint64_t)row0 * stride;
+      const uint32_t ks = seg ? a.sel_bytes : V.k_bytes, vs = seg ? a.sel_bytes : V.v_bytes;
+      const char* kb = (seg ? ksl : kc) + (uint64_t)row0 * ks;
+      const char* vbase = (seg ? vsl : vc) + (uint64_t)row0 * vs;
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(kb + ((st_row + kRowStep * u) * stride + kcol), kd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u) dma16(kb + ((st_row + kRowStep * u) * ks + kcol), kd + kGroupStep * u);
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(vbase + ((st_row + kRowStep * u) * stride + vcol), vd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u) dma16(vbase + ((st_row + kRowStep * u) * vs + vcol), vd + kGroupStep * u);
     } else {
       RowRef ref[kMyRows];
 #pragma unroll
       for (int u = 0; u < kMyRows; ++u) {
         const uint32_t j = j0 + st_row + kRowStep * u;
-        ref[u] = row_ref(V, sidx, a.sel_bytes, j < k_end ? j : k_end - 1);      // the tail repeats a key; masked below
+        ref[u] = row_ref(V, sidx, j < k_end ? j : k_end - 1);                   // the tail repeats a key; masked below
       }
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16((ref[u].in_sel ? ksl : kc) + ref[u].off + kcol, kd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u)
+        dma16((ref[u].in_sel ? ksl : kc) + (uint64_t)ref[u].row * (ref[u].in_sel ? a.sel_bytes : V.k_bytes) + kcol, kd + kGroupStep * u);
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16((ref[u].in_sel ? vsl : vc) + ref[u].off + vcol, vd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u)
+        dma16((ref[u].in_sel ? vsl : vc) + (uint64_t)ref[u].row * (ref[u].in_sel ? a.sel_bytes : V.v_bytes) + vcol, vd + kGroupStep * u);
     }
   };
   // Every load of this wave has landed in LDS (vmcnt = 0; the other counters are left alone).
@@ -440,7 +400,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   if (tile_begin < tile_end) tile_load(tile_begin * kKT, k_st0, v_st0);
   idx_prefetch(tile_begin + 1);
   {
-    const bf16_t* qp = V.q + (int64_t)b * V.q_bs + ((int64_t)cc * a.h + head) * D + hi * 8;
+    const bf16_t* qp = (const bf16_t*)V.q + (int64_t)b * V.q_bs + ((int64_t)cc * a.h + head) * D + hi * 8;
 #pragma unroll
     for (int ks16 = 0; ks16 < kKS; ++ks16) qf[ks16] = *(const bf16x8*)(qp + ks16 * 16);
     // Pin the fragments as arrived values here: otherwise every use inside the tile loop carries a
@@ -630,15 +590,6 @@ bool attend_mfma_supported(int l_c, int h, int h_kv, int d, int dtype) {
   return group == 1 || group == 2 || group == 4 || group == 8;
 }
 
-bool attend_mfma_aligned(const void* q, const void* k_cache, const void* v_cache, const void* k_sel,
-                         const void* v_sel, const void* out, int64_t tok_stride, int64_t q_bs, int64_t cache_bs,
-                         int64_t sel_bs, int64_t out_bs) {
-  const uintptr_t p = (uintptr_t)q | (uintptr_t)k_cache | (uintptr_t)v_cache | (uintptr_t)k_sel | (uintptr_t)v_sel |
-                      (uintptr_t)out;
-  const int64_t s = tok_stride | q_bs | cache_bs | sel_bs | out_bs;
-  return (p % 16 == 0) && (s % 8 == 0);
-}
-
 namespace {
 
 // Planned slice counts.  One call: `all` slices of the whole virtual sequence.  Two calls: the local
@@ -669,29 +620,6 @@ size_t attend_mfma_workspace_bytes(int l_c, int h, int h_kv, int d, int batch) {
 }
 
 namespace {
-
-KeyView make_view(const void* q, int64_t q_bs, const void* k_cache, const void* v_cache, int64_t tok_stride,
-                  int64_t cache_bs, int64_t i_end, int n_sel, int64_t l_start, int64_t n_fixed, int with_chunk,
-                  int n_split, int slot0, const int32_t* sel_idx = nullptr, int64_t idx_bs = 0, int64_t idx_limit = 1) {
-  KeyView v;
-  v.sel_idx = n_sel > 0 ? sel_idx : nullptr;
-  v.idx_bs = idx_bs;
-  v.idx_limit = (uint32_t)(idx_limit > 0 ? idx_limit : 1);
-  v.q = (const bf16_t*)q;
-  v.k_cache = (const char*)k_cache;
-  v.v_cache = (const char*)v_cache;
-  v.q_bs = q_bs;
-  v.cache_bs_bytes = cache_bs * 2;
-  v.tok_bytes = (uint32_t)(tok_stride * 2);
-  v.i_end = (uint32_t)i_end;
-  v.n_sel = (uint32_t)n_sel;
-  v.l_start = (uint32_t)l_start;
-  v.n_fixed = (uint32_t)n_fixed;
-  v.with_chunk = with_chunk;
-  v.n_split = n_split;
-  v.slot0 = slot0;
-  return v;
-}
 
 int clamp_splits(int ns, int64_t keys_of_first_tile) {
   const int64_t tiles = (keys_of_first_tile + kKT - 1) / kKT;
@@ -748,7 +676,8 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
     a.part_ml = (float*)((char*)ws + align_up(rows * d * sizeof(uint16_t), 256));
   }
   a.n_slot = n_slot;
-  a.view[1] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, 0, 0, 0, 0, 0, 0, 0);   // unused
+  const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
+  a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0, 0, 0);   // unused
   auto launch = [&](int64_t n_wg) {
     if (d == 128) attend_mfma_bf16<128><<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a);
     else attend_mfma_bf16<64><<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a);
@@ -758,20 +687,18 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
     else launch_merge<64>(a, ns_a, slot_b, ns_b, st);
   };
   if (part == kAttendAll) {
-    a.view[0] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, i_end, n_sel, l_start,
-                          i_end + n_sel + (t0 - l_start), 1, ns_all, 0, sel_idx, idx_bs, l_start);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, ns_all, 0, sel_idx, idx_bs,
+                          l_start);
     a.to_slots = 0;
     launch((int64_t)batch * h_kv * a.n_qt * ns_all);
     if (ns_all > 1) merge(ns_all, 0, 0);
   } else if (part == kAttendLocal) {
-    a.view[0] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, i_early, 0, l_start,
-                          i_early + (t0 - l_start), 1, ns_local, 0);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1, ns_local, 0);
     a.to_slots = 1;
     launch((int64_t)batch * h_kv * a.n_qt * ns_local);
   } else {
     if (ns_sel > 0) {
-      a.view[0] = make_view(q, q_bs, k_cache, v_cache, tok_stride, cache_bs, i_late, n_sel, 0, i_late + n_sel, 0, ns_sel,
-                            plan.local, sel_idx, idx_bs, l_start);
+      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, ns_sel, plan.local, sel_idx, idx_bs, l_start);
       a.to_slots = 1;
       launch((int64_t)batch * h_kv * a.n_qt * ns_sel);
     }
@@ -781,17 +708,15 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   return ESA_OK;
 }
 
-// Section 3.2 in one launch: the local keys (dense re-encoded copy, rows [0, n_loc + l_c), causal) with the
-// queries q_loc, and the initial and selected keys (caller's un-encoded cache and gathered rows, every key
-// visible) with the queries q_glob; the slices of both share the launch and the merge.
+// Section 3.2 in one launch: the local keys (dense re-encoded copy, rows [0, n_loc + l_c), causal; their values where
+// they are in the caller's cache) with the queries q_loc, and the initial and selected keys (caller's un-encoded cache
+// and gathered rows, every key visible) with the queries q_glob; the slices of both share the launch and the merge.
 int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t qw_bs, int l_c, int h, int h_kv, int d,
-                                 const void* k_loc, const void* v_loc, int64_t n_loc, int64_t loc_bs,
-                                 const void* k_cache, const void* v_cache, int64_t tok_stride, int64_t cache_bs,
-                                 int64_t i_end, const void* k_sel, const void* v_sel, int n_sel, int64_t sel_bs,
-                                 float scale, void* out, float* lse, int batch, int64_t out_bs, void* ws, size_t ws_bytes,
-                                 hipStream_t st) {
+                                 const CacheRef& local, int64_t n_loc, const CacheRef& cache, int64_t i_end,
+                                 const void* k_sel, const void* v_sel, int n_sel, int64_t sel_bs, float scale, void* out,
+                                 float* lse, int batch, int64_t out_bs, void* ws, size_t ws_bytes, hipStream_t st) {
   if (!(scale > 0.f)) ESA_FAIL(ESA_EINVAL, "esa_attend: scale must be positive");
-  if (n_loc + l_c >= ((int64_t)1 << 31) || tok_stride * 2 >= ((int64_t)1 << 32))
+  if (n_loc + l_c >= ((int64_t)1 << 31) || cache.k_stride * 2 >= ((int64_t)1 << 32))
     ESA_FAIL(ESA_EUNSUPPORTED, "esa_attend: positions beyond 2^31 are not supported by the matrix-core kernel");
   AttendArgs a;
   a.out = (bf16_t*)out;
@@ -833,8 +758,8 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   }
   a.n_slot = n_slot;
   a.to_slots = 0;
-  a.view[0] = make_view(q_loc, qw_bs, k_loc, v_loc, (int64_t)h_kv * d, loc_bs, 0, 0, 0, n_loc, 1, ns_a, 0);
-  a.view[1] = make_view(q_glob, qw_bs, k_cache, v_cache, tok_stride, cache_bs, i_end, n_sel, 0, keys_b, 0, ns_b, ns_a);
+  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1, ns_a, 0);
+  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0, ns_b, ns_a);
   const dim3 grid((unsigned)((int64_t)batch * h_kv * a.n_qt * n_slot));
   if (d == 128) attend_mfma_bf16<128><<<grid, kThreads, 0, st>>>(a);
   else attend_mfma_bf16<64><<<grid, kThreads, 0, st>>>(a);

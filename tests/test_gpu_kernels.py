@@ -100,3 +100,25 @@ def test_scores_finished_by_the_selection_equal_the_separate_calls(esa, B, l_c, 
     want = esa.esa_score(qc, kc, 7, n + 7, eps=eps)
     assert torch.equal(score, want)
     assert torch.equal(idx, esa.esa_select_topk(want, k, base=7))
+
+
+# one key, fewer keys than waves, rows that fill a 32-row tile or run one over, group sizes that divide nothing, a single
+# slice and many, every head size and storage type of the kernel
+@pytest.mark.parametrize("dtype,B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
+    ("bf16", 1, 8, 2, 64, 0, 1, 16, 64, 0), ("bf16", 2, 8, 2, 128, 700, 8, 16, 64, 33), ("bf16", 1, 8, 1, 128, 900, 5, 7, 129, 300),
+    ("bf16", 40, 16, 8, 64, 300, 15, 3, 70, 90), ("bf16", 3, 6, 2, 128, 500, 11, 0, 31, 1), ("bf16", 1, 32, 8, 128, 9000, 2, 128, 2048, 2048),
+    ("f32", 1, 4, 2, 32, 700, 130, 16, 64, 100), ("f32", 2, 6, 2, 64, 400, 11, 0, 31, 1), ("f32", 1, 8, 1, 128, 600, 33, 7, 129, 300),
+    ("f32", 1, 4, 2, 128, 0, 3, 7, 129, 0), ("f32", 1, 4, 2, 64, 5000, 1, 32, 2500, 1000)])
+def test_split_key_attention(esa, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
+    say(f"split attend {dtype} B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
+    q, K, V, sel = attend_inputs(d + l_C, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    qd, Kd, Vd, idx = f64_to_dev(q, dtype), f64_to_dev(K, dtype), f64_to_dev(V, dtype), torch.from_numpy(sel).cuda()
+    O, lse = esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx, return_lse=True)
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx) if n_sel else (None, None)
+    O_re = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5)
+    for b in range(B):
+        want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL[dtype]
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= (1e-5 if dtype == "f32" else 1e-3)
+        want, _ = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
+        assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL[dtype]
