@@ -55,17 +55,11 @@ struct TopkLayout {
   // then [nblk][cap]: keys inside the bin
 };
 
-// One LDS-histogram increment per lane, with the lanes of a wave that hit the leader's bin
-// folded into a single atomic (equal scores come in runs: pooled windows, a row's best tokens).
-// Every lane of the wave must call it.
+// One LDS-histogram increment per lane.  With bins this fine a wave's 64 scores fall into dozens of them; folding the
+// lanes that share the first lane's bin into one atomic, which paid when four fifths of a row shared a bin, cost more
+// than the few lanes served one after the other.
 __device__ __forceinline__ void hist_add(uint32_t* h, bool active, uint32_t bin) {
-  const uint64_t act = __ballot(active);
-  if (act == 0ull) return;
-  const int leader = __ffsll((long long)act) - 1;
-  const uint32_t lead_bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);     // leader is the same in every lane
-  const uint64_t same = __ballot(active && bin == lead_bin);
-  if ((int)(__builtin_amdgcn_workitem_id_x() & 63) == leader) atomicAdd(&h[lead_bin], (uint32_t)__popcll(same));
-  if (active && bin != lead_bin) atomicAdd(&h[bin], 1u);
+  if (active) atomicAdd(&h[bin], 1u);
 }
 
 // A workgroup's finished LDS histogram h, added to its copy of the global histogram gh ([kHistReplicas][kRadixBins]).
@@ -77,5 +71,7 @@ __device__ __forceinline__ void hist_flush(uint32_t* __restrict__ gh, const uint
 
 // Words of one batch row's selection workspace and the stride between rows (host side).
 int64_t topk_row_stride_words(int64_t n, int batch);
+// Tiles of 1024 scores that a workgroup of the selection takes (host side).
+int topk_tiles_per_wg(int64_t n, int batch);
 
 }  // namespace esa

@@ -2,12 +2,12 @@
 //   S[c,m] = q'_c . k'_m,  mu[c] = max_m S[c,m],  F[m] = max_c (S[c,m] - mu[c]),
 // optionally followed by the proximity max-pool of Eq. 8.
 //
-// F needs every row maximum before any column maximum, so K' is swept twice and S is
-// recomputed instead of being stored (S would be l_C x N fp32; K' is only N x d_c storage
-// elements).  Both sweeps compute S[c,m] with the same instruction sequence, so the second one
-// reproduces the first bit for bit: the row arg-max token gets F = 0 exactly and F <= 0 everywhere.
-// Row maxima are combined across workgroups with integer atomicMax on order-preserving keys
-// (exact and order-independent).
+// F needs every row maximum before any column maximum.  A chunk of more than a few queries sweeps K' twice and
+// recomputes S instead of storing it (S would be l_C x N fp32; K' is only N x d_c storage elements).  Both sweeps compute
+// S[c,m] with the same instruction sequence, so the second one reproduces the first bit for bit: the row arg-max token
+// gets F = 0 exactly and F <= 0 everywhere.  With up to sixteen queries a row of S is a fraction of a row of K' (4 bytes
+// per query against 128 or 256 per token), and a small problem's S is small whatever its shape: there S is stored by one
+// sweep, with per-workgroup row maxima beside it, and score_finish subtracts and takes the column maximum.
 //
 // This file is compiled with the IEEE mode bit off and NaNs declared absent (see build.py): with the bit
 // on, every fmaxf() on a matrix-core result costs three instructions, because the compiler first
@@ -541,11 +541,10 @@ __global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restri
 // One current token: S is a matrix-vector product over the whole compressed-key cache, pure HBM
 // streaming.  LPR lanes share a K' row (16 bytes each), so a wave reads 64*16 contiguous bytes per
 // step; a workgroup covers 256 rows with all its steps' loads in flight.  Writes S and the workgroup's maximum of it (no atomics: thousands of
-// workgroups folding into one word serialise in L2); score_sub_mu then reduces those maxima to mu,
+// workgroups folding into one word serialise in L2); score_finish then reduces those maxima to mu,
 // every workgroup for itself, and forms F = S - mu.
 constexpr int kGemvRows = 256;           // rows per workgroup
 // grids of the passes over the scores (host and device agree on them; the kernels do not ask the dispatch packet)
-__host__ __device__ inline int sub_mu_blocks(int64_t n) { return (int)((n + 1023) / 1024 < 2048 ? (n + 1023) / 1024 : 2048); }
 __host__ __device__ inline int maxpool_blocks(int64_t n) { return (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096); }
 
 // Sum over groups of LPR consecutive lanes (LPR = 8, 16, 32) with DPP moves; every lane gets the total.
@@ -557,6 +556,14 @@ __device__ __forceinline__ float lanes_sum(float v) {
   if (LPR >= 16) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true));   // row_mirror
   if (LPR >= 32) v += __shfl_xor(v, 16, 64);
   return v;
+}
+
+// Maximum over the 16 lanes of a DPP row; every lane receives it.
+__device__ __forceinline__ float lanes_max16(float v) {
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true)));
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true)));
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true)));
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true)));
 }
 
 template <int LPR>
@@ -611,68 +618,279 @@ __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict_
     part[(int64_t)b * n_wg + __builtin_amdgcn_workgroup_id_x()] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-__global__ __launch_bounds__(256) void score_sub_mu(float* __restrict__ raw, int64_t n, const float* __restrict__ part,
-                                                    int n_part, int64_t raw_bs, uint32_t* __restrict__ first_hist,
-                                                    int64_t first_hist_bs) {
-  __shared__ float red[4];
-  __shared__ uint32_t digit_hist[kRadixBins];
-  const int n_wg = sub_mu_blocks(n);                          // workgroups per batch entry (the launch's grid)
-  if (first_hist)
-    for (int i = __builtin_amdgcn_workitem_id_x(); i < kRadixBins; i += 256) digit_hist[i] = 0u;
-  float* p = raw + (int64_t)__builtin_amdgcn_workgroup_id_y() * raw_bs;
-  // A workgroup owns chunks of 1024 consecutive scores (the first one is the chunk the selection's workgroup of
-  // the same number reads next: written and read on the same XCD), a thread four scores 256 apart.
-  const int64_t first = (int64_t)__builtin_amdgcn_workgroup_id_x() * 1024 + __builtin_amdgcn_workitem_id_x(), stride = 256;
-  const int64_t chunk_stride = (int64_t)n_wg * 1024;
-  // this thread's first four scores are requested together with the partial maxima: one round trip
-  float x[4];
+// Two to sixteen current tokens: one pass over K' on the matrix cores, S stored.  v_mfma_f32_16x16x32_bf16, A rows are
+// tokens, B columns queries (rows past the chunk repeat its last one): a lane owns four consecutive tokens of one query,
+// a 16-byte store.  K' is the stream to keep moving: a wave has its 64 tokens' fragments in flight at once (16 or 8
+// loads of 16 bytes per lane, sixteen rows of 64 bytes per instruction).  Four sequences of 100k tokens, five queries:
+// 102 MB, where each of the two sweeps took 35 us.
+constexpr int kFewQueries = 16;
+constexpr int kFewTok = 256;             // tokens per workgroup
+template <int DC>
+__global__ __launch_bounds__(256) void score_few_bf16(const bf16_t* __restrict__ qc, int l_c, const bf16_t* __restrict__ kc,
+                                                      int64_t m_lo, int64_t n, float* __restrict__ part, float* __restrict__ S,
+                                                      int64_t s_ld, int64_t s_bs, int64_t q_bs, int64_t kc_bs, int n_wg,
+                                                      uint32_t* __restrict__ hists, int64_t hists_bs) {
+  constexpr int kKS = DC / 32, kTiles = kFewTok / 64;
+  __shared__ float red[4][kFewQueries];
+  const int b = __builtin_amdgcn_workgroup_id_y(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
+  const int lane = tid & 63, wave = tid >> 6, r = lane & 15, q4 = lane >> 4;
+  const bf16_t* k = kc + (int64_t)b * kc_bs + m_lo * (int64_t)DC + q4 * 8;
+  const bf16_t* qp = qc + (int64_t)b * q_bs + (int64_t)(r < l_c ? r : l_c - 1) * DC + q4 * 8;
+  bf16x8 kf[kTiles][kKS], qf[kKS];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int64_t i = first + u * stride;
-    x[u] = i < n ? p[i] : 0.f;
-  }
-  float mu = -INFINITY;
-  for (int i0 = __builtin_amdgcn_workitem_id_x(); i0 < n_part; i0 += 4 * 256) {
-    float v[4];
+  for (int ks = 0; ks < kKS; ++ks) qf[ks] = *(const bf16x8*)(qp + 32 * ks);
+  const int64_t tok0 = (int64_t)blk * kFewTok + wave * (16 * kTiles);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + 256 * u;
-      v[u] = part[(int64_t)__builtin_amdgcn_workgroup_id_y() * n_part + (i < n_part ? i : 0)];
-      if (i >= n_part) v[u] = -INFINITY;
-    }
-    mu = fmaxf(fmaxf(mu, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
+  for (int t = 0; t < kTiles; ++t) {
+    int64_t tok = tok0 + 16 * t + r;
+    tok = tok < n ? tok : n - 1;                            // repeats the last token: no maximum changes
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) kf[t][ks] = *(const bf16x8*)(k + tok * DC + 32 * ks);
   }
-  mu = wave_max(mu);
-  if ((__builtin_amdgcn_workitem_id_x() & 63) == 0) red[__builtin_amdgcn_workitem_id_x() >> 6] = mu;
+  if (hists)       // the selection's histogram, zeroed here for the pass that follows
+    for (int i = blk * 256 + tid; i < kHistWords; i += n_wg * 256) hists[(int64_t)b * hists_bs + i] = 0u;
+  float best = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qf[ks], acc, 0, 0, 0);
+    best = fmaxf(fmaxf(best, acc[0]), fmaxf(fmaxf(acc[1], acc[2]), acc[3]));
+    const int64_t tok = tok0 + 16 * t + 4 * q4;
+    if (r < l_c && tok < s_ld) *(f32x4*)(S + (int64_t)b * s_bs + (int64_t)r * s_ld + tok) = acc;      // s_ld: n rounded up to whole tiles
+  }
+  best = fmaxf(best, __shfl_xor(best, 16, 64));
+  best = fmaxf(best, __shfl_xor(best, 32, 64));
+  if (lane < kFewQueries) red[wave][lane] = best;
   __syncthreads();
-  mu = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  if (tid < l_c) part[((int64_t)b * n_wg + blk) * l_c + tid] = fmaxf(fmaxf(red[0][tid], red[1][tid]), fmaxf(red[2][tid], red[3][tid]));
+}
+
+// The same for every storage type and d_c: a workgroup computes S for 64 tokens (one per lane) and 32 queries (eight per
+// wave), both in LDS as fp32 rows (the queries' reads are broadcasts), fp32 FMAs in ascending order.
+constexpr int kStoreQ = 32;
+__host__ __device__ inline int store_ld(int d_c) { return d_c + 4; }       // d_c is a multiple of 16: rows 16-byte aligned, spread over the banks
+template <typename T>
+__global__ __launch_bounds__(256) void score_store_fma(const T* __restrict__ qc, int l_c, const T* __restrict__ kc, int64_t m_lo,
+                                                       int64_t n, int d_c, float* __restrict__ part, float* __restrict__ S,
+                                                       int64_t s_ld, int64_t s_bs, int64_t q_bs, int64_t kc_bs, int n_wg,
+                                                       uint32_t* __restrict__ hists, int64_t hists_bs) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];               // [kGTok][ld] tokens, [kStoreQ][ld] queries
+  const int ld = store_ld(d_c);
+  float* qs = smem + kGTok * ld;
+  const int b = __builtin_amdgcn_workgroup_id_z(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m0 = (int64_t)blk * kGTok;
+  const int cg0 = (int)__builtin_amdgcn_workgroup_id_y() * kStoreQ, c0 = cg0 + wave * (kStoreQ / 4);
+  const T* k = kc + (int64_t)b * kc_bs + m_lo * (int64_t)d_c;
+  const T* q = qc + (int64_t)b * q_bs;
+  constexpr int kAtOnce = 12;                          // loads in flight per thread: all of them at d_c = 32
+  for (int e0 = tid; e0 < (kGTok + kStoreQ) * d_c; e0 += 256 * kAtOnce) {
+    float v[kAtOnce];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int64_t i = first + u * stride;
-    const float f = x[u] - mu;
-    if (i < n) p[i] = f;
-    if (first_hist) hist_add(digit_hist, i < n, score_bin(ordered_key(f)));
-  }
-  // whole waves stay in the loop together (hist_add is a wave-wide operation); four scores in flight per lane
-  for (int64_t c0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * 1024 + chunk_stride; c0 < n; c0 += chunk_stride) {
-    float y[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = c0 + u * stride + __builtin_amdgcn_workitem_id_x();
-      y[u] = i < n ? p[i] : 0.f;
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int e = e0 + 256 * u, t = e / d_c, i = e % d_c;
+      // past the end: the last token, the last query again
+      const T* from = t < kGTok ? k + (m0 + t < n ? m0 + t : n - 1) * (int64_t)d_c
+                                : q + (int64_t)(cg0 + t - kGTok < l_c ? cg0 + t - kGTok : l_c - 1) * d_c;
+      v[u] = load_f32(from + i);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = c0 + u * stride + __builtin_amdgcn_workitem_id_x();
-      const float f = y[u] - mu;
-      if (i < n) p[i] = f;
-      if (first_hist) hist_add(digit_hist, i < n, score_bin(ordered_key(f)));
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int e = e0 + 256 * u;
+      if (e < (kGTok + kStoreQ) * d_c) smem[e / d_c * ld + e % d_c] = v[u];
+    }
+  }
+  if (hists && __builtin_amdgcn_workgroup_id_y() == 0)
+    for (int i = blk * 256 + tid; i < kHistWords; i += n_wg * 256) hists[(int64_t)b * hists_bs + i] = 0u;
+  __syncthreads();
+  float acc[kStoreQ / 4] = {};
+  const float* qrow = qs + wave * (kStoreQ / 4) * ld;
+  for (int i = 0; i < d_c; i += 4) {
+    const float4 kv = *(const float4*)&smem[lane * ld + i];
+#pragma unroll
+    for (int j = 0; j < kStoreQ / 4; ++j) {
+      const float4 qv = *(const float4*)&qrow[j * ld + i];
+      acc[j] = __fmaf_rn(qv.x, kv.x, acc[j]);
+      acc[j] = __fmaf_rn(qv.y, kv.y, acc[j]);
+      acc[j] = __fmaf_rn(qv.z, kv.z, acc[j]);
+      acc[j] = __fmaf_rn(qv.w, kv.w, acc[j]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kStoreQ / 4; ++j) {
+    if (c0 + j >= l_c) break;
+    if (m0 + lane < s_ld) S[(int64_t)b * s_bs + (int64_t)(c0 + j) * s_ld + m0 + lane] = acc[j];
+    const float mx = wave_max(acc[j]);
+    if (lane == 0) part[((int64_t)b * n_wg + blk) * l_c + c0 + j] = mx;
+  }
+}
+
+// F[m] = max_c (S[c][m] - mu_c), mu_c = the largest of the n_part partial maxima of query c ([n_part][l_c]), found by
+// every workgroup for itself; pooled over +-eps (<= kTailMaxEps) when asked; with first_hist given also the histogram
+// of the results' bins.  SPLIT = 1 (up to sixteen queries): a workgroup owns `sub` tiles of 1024 tokens, four per
+// thread, the ones that the selection's workgroup of the same number reads next (written and read on the same XCD; with
+// many rows several tiles, so that fewer workgroups reduce the partial maxima and flush a histogram).
+// SPLIT = 4: 64 tokens (pooled ones at the ends only feed their neighbours), the queries shared out over the waves.
+constexpr int kFinishMaxQueries = 4096;
+template <int SPLIT, bool POOL, bool ONE = false>
+__global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S, int64_t s_ld, int64_t s_bs, int64_t n,
+                                                    const float* __restrict__ part, int n_part, int l_c, int eps_arg, int sub,
+                                                    float* __restrict__ score, int64_t score_bs,
+                                                    uint32_t* __restrict__ first_hist, int64_t first_hist_bs) {
+  const int eps = POOL ? eps_arg : 0;
+  constexpr int kPer = POOL ? 5 : 4;                        // SPLIT = 1: tokens of a thread, the last one of the pooling margin
+  constexpr int kAhead = ONE ? 1 : 4;                       // queries whose scores are in flight together
+  constexpr int kTok = SPLIT == 1 ? 1024 : 64;
+  __shared__ float mu[SPLIT == 1 ? kFewQueries : kFinishMaxQueries];
+  __shared__ float red[256];
+  __shared__ float tile[SPLIT == 1 ? kTok + 2 * kTailMaxEps : kTok];
+  __shared__ uint32_t bin_hist[kRadixBins];
+  const int b = __builtin_amdgcn_workgroup_id_y(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
+  const int lane = tid & 63, wave = tid >> 6;
+  const float* s = S + (int64_t)b * s_bs;
+  const float* pt = part + (int64_t)b * n_part * l_c;
+  int64_t first = SPLIT == 1 ? (int64_t)blk * sub * kTok - eps : (int64_t)blk * (kTok - 2 * eps) - eps;   // of the tokens read
+  auto clamped = [&](int64_t m) { return m < 0 ? (int64_t)0 : (m < n ? m : n - 1); };
+  // SPLIT = 1: the first queries' scores are requested in front of the partial maxima (one round trip together)
+  float x[kAhead][kPer];
+  auto request = [&](int64_t from, int c0) {
+    int64_t mine_at[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) mine_at[u] = clamped(from + 256 * u + tid);
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        if ((a == 0 || (!ONE && c0 + a < l_c)) && (u < 4 || tid < 2 * eps)) x[a][u] = s[(int64_t)(c0 + a) * s_ld + mine_at[u]];
+  };
+  if (SPLIT == 1) request(first, 0);
+  // The 256 threads are shared out over lc2 >= l_c queries (a power of two): thread t reduces every (256 / lc2)-th partial
+  // maximum of one of them.
+  float mu_one = 0.f;
+  if (ONE) {
+    float m = -INFINITY;
+    for (int j0 = tid; j0 < n_part; j0 += 4 * 256) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = pt[j0 + u * 256 < n_part ? j0 + u * 256 : j0];
+      m = fmaxf(fmaxf(m, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
+    }
+    if (first_hist)
+      for (int i = tid; i < kRadixBins; i += 256) bin_hist[i] = 0u;
+    m = wave_max(m);
+    if (lane == 0) red[wave] = m;
+    __syncthreads();
+    mu_one = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  } else if (SPLIT == 1) {
+    int lc2 = 1;
+    while (lc2 < l_c) lc2 *= 2;                             // at most sixteen: whole 16-lane rows per query
+    const int per = 256 / lc2, c = tid / per < l_c ? tid / per : l_c - 1;
+    float m = -INFINITY;
+    for (int j0 = tid % per; j0 < n_part; j0 += 4 * per) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = pt[(int64_t)(j0 + u * per < n_part ? j0 + u * per : j0) * l_c + c];
+      m = fmaxf(fmaxf(m, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
+    }
+    m = lanes_max16(m);
+    if ((tid & 15) == 0) red[tid >> 4] = m;
+    if (first_hist)
+      for (int i = tid; i < kRadixBins; i += 256) bin_hist[i] = 0u;
+    __syncthreads();
+    if (tid < l_c) {
+      const int rows = 16 / lc2;
+      m = red[tid * rows];
+      for (int i = 1; i < rows; ++i) m = fmaxf(m, red[tid * rows + i]);
+      mu[tid] = m;
+    }
+    __syncthreads();
+  } else {
+    if (first_hist)
+      for (int i = tid; i < kRadixBins; i += 256) bin_hist[i] = 0u;
+    int lc2 = 1;
+    while (lc2 < l_c && lc2 < 256) lc2 *= 2;
+    const int groups = 256 / lc2, jg = tid / lc2;
+    for (int c0 = 0; c0 < l_c; c0 += lc2) {
+      const int c = c0 + tid % lc2 < l_c ? c0 + tid % lc2 : l_c - 1;
+      float m = -INFINITY;
+      for (int j0 = jg; j0 < n_part; j0 += 8 * groups) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = pt[(int64_t)(j0 + u * groups < n_part ? j0 + u * groups : j0) * l_c + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
+      }
+      red[tid] = m;
+      __syncthreads();
+      if (tid < lc2 && c0 + tid < l_c) {
+        for (int g = 1; g < groups; ++g) m = fmaxf(m, red[g * lc2 + tid]);
+        mu[c0 + tid] = m;
+      }
+      __syncthreads();
+    }
+  }
+  auto pooled = [&](int64_t at_token, int at, float f) {    // tile[at] is token at_token
+    for (int d = -eps; d <= eps; ++d)
+      if (at_token + d >= 0 && at_token + d < n) f = fmaxf(f, tile[at + d]);
+    return f;
+  };
+  if (SPLIT == 1) {
+    for (int st = 0; st < sub && first + eps < n; ++st, first += kTok) {
+      float f[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) f[u] = ONE ? x[0][u] - mu_one : -INFINITY;
+      for (int c0 = 0; !ONE && c0 < l_c; c0 += kAhead) {
+        if (c0 > 0) request(first, c0);
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+          if (c0 + a < l_c) {
+            const float muc = mu[c0 + a];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) f[u] = fmaxf(f[u], x[a][u] - muc);
+          }
+        }
+      }
+      if (st + 1 < sub) request(first + kTok, 0);           // the next tile's, during this one's histogram
+      if (POOL) {
+        if (st > 0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+          if (u < 4 || tid < 2 * eps) tile[256 * u + tid] = f[u];
+        __syncthreads();
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t m = first + eps + 256 * u + tid;
+        float v = f[u];
+        if (POOL) v = m < n ? pooled(m, 256 * u + tid + eps, tile[256 * u + tid + eps]) : 0.f;
+        if (m < n) score[(int64_t)b * score_bs + m] = v;
+        if (first_hist) hist_add(bin_hist, m < n, score_bin(ordered_key(v)));
+      }
+    }
+  } else {
+    const int64_t m = first + lane;
+    const float* col = s + clamped(m);
+    float f = -INFINITY;
+#pragma unroll 8
+    for (int c = wave; c < l_c; c += 4) f = fmaxf(f, col[(int64_t)c * s_ld] - mu[c]);
+    red[tid] = f;
+    __syncthreads();
+    if (wave == 0) {
+      f = fmaxf(fmaxf(red[lane], red[64 + lane]), fmaxf(red[128 + lane], red[192 + lane]));
+      tile[lane] = f;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const bool mine = m >= 0 && m < n && lane >= eps && lane < kTok - eps;
+      if (POOL && mine) f = pooled(m, lane, f);
+      if (mine) score[(int64_t)b * score_bs + m] = f;
+      if (first_hist) hist_add(bin_hist, mine, score_bin(ordered_key(f)));
     }
   }
   if (first_hist) {
     __syncthreads();
-    uint32_t* gh = first_hist + (int64_t)__builtin_amdgcn_workgroup_id_y() * first_hist_bs;
-    hist_flush(gh, digit_hist, __builtin_amdgcn_workgroup_id_x(), __builtin_amdgcn_workitem_id_x(), 256);
+    hist_flush(first_hist + (int64_t)b * first_hist_bs, bin_hist, blk, tid, 256);
   }
 }
 
@@ -709,11 +927,20 @@ __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict
 
 }  // namespace
 
+// S is stored (one pass over K') instead of recomputed: few queries, or a small S.
+__host__ inline bool stores_scores(int l_c, int64_t n, int batch) {
+  return l_c <= kFewQueries || (l_c <= kFinishMaxQueries && (int64_t)l_c * n * batch * 4 <= ((int64_t)16 << 20));
+}
+__host__ inline int64_t stored_ld(int64_t n) { return (n + 63) / 64 * 64; }
+__host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {        // one current token: S is kept where F goes
+  return l_c > 1 && stores_scores(l_c, n, batch) ? (size_t)l_c * stored_ld(n) * 4 * batch : 0;
+}
+
 __host__ inline size_t part_bytes(int l_c, int64_t n_mid, int batch) {
   size_t blocks = (size_t)mfma_blocks(n_mid) * l_c;
-  if (l_c == 1) {   // the one-token kernel: a partial maximum per workgroup of at least 256 rows
-    const size_t gemv_blocks = (size_t)((n_mid + 255) / 256);
-    blocks = gemv_blocks > blocks ? gemv_blocks : blocks;
+  if (stores_scores(l_c, n_mid, batch)) {   // a partial maximum per query and workgroup of at least 64 tokens
+    const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c;
+    blocks = stored > blocks ? stored : blocks;
   }
   return align_up(blocks * batch * 4, 256);
 }
@@ -753,6 +980,7 @@ size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
   size_t b = mu_bytes(l_c, batch) + part_bytes(l_c, n_mid, batch);
   if (eps > 0) b += align_up((size_t)n_mid * 4, 256) * (size_t)batch;
   b += qfrag_bytes_per_batch(l_c) * (size_t)batch;
+  b += stored_bytes(l_c, n_mid, batch);
   return b;
 }
 
@@ -761,55 +989,92 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                  size_t ws_bytes, hipStream_t st, uint32_t* first_hist, int64_t first_hist_bs, bool* first_hist_done,
                  ScoreTail* tail) {
   const int64_t n = m_hi - m_lo;
-  // With pooling the kernel that writes the final scores is the pooling pass: the kernels before it only zero
-  // the histograms (pool_hist), it fills the first one.
-  uint32_t* pool_hist = eps > 0 ? first_hist : nullptr;
-  bool zeroed = false;
-  if (first_hist_done) *first_hist_done = false;
-  uint32_t* mu = (uint32_t*)ws;
+  // eps > 0: windows of up to kTailMaxEps on either side are pooled by whatever finishes the scores (score_finish, or
+  // the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
+  const bool narrow = eps <= kTailMaxEps;
+  bool zeroed = false;                  // the selection's histogram has been zeroed ...
+  if (first_hist_done) *first_hist_done = false;        // ... and filled
+  float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
+  char* at = (char*)part + part_bytes(l_c, n, batch);
   float* raw = score;
   int64_t raw_bs = score_bs;
   if (eps > 0) {
-    raw = (float*)((char*)ws + mu_bytes(l_c, batch) + part_bytes(l_c, n, batch));
+    raw = (float*)at;
     raw_bs = (int64_t)(align_up((size_t)n * 4, 256) / 4);
+    at += align_up((size_t)n * 4, 256) * (size_t)batch;
   }
-  if (tail) *tail = ScoreTail{raw, raw_bs, nullptr, 0, eps <= kTailMaxEps ? eps : 0};
+  bf16_t* qfrag = (bf16_t*)at;
+  at += qfrag_bytes_per_batch(l_c) * (size_t)batch;
+  if (tail) *tail = ScoreTail{score, score_bs, nullptr, 0, 0};
+  bool pool_left = eps > 0;
   const bool vec_ok = dtype == ESA_BF16 && (((uintptr_t)qc | (uintptr_t)kc_cache) % 16 == 0) && q_bs % 8 == 0 &&
                       kc_bs % 8 == 0;
+  // S of one current token: where F goes (pooling reads neighbours: the unpooled buffer); of several: in the workspace
+  float* S = l_c == 1 ? raw : (float*)at;
+  const int64_t s_ld = l_c == 1 ? n : stored_ld(n), s_bs = l_c == 1 ? raw_bs : (int64_t)l_c * s_ld;
+  auto finish = [&](int n_part) {
+    float* out = narrow ? score : raw;
+    const int64_t out_bs = narrow ? score_bs : raw_bs;
+    const int e = narrow ? eps : 0;
+    uint32_t* hist = narrow ? first_hist : nullptr;
+    const bool few = l_c <= kFewQueries;
+    const auto kernel = l_c == 1 ? (e > 0 ? score_finish<1, true, true> : score_finish<1, false, true>)
+                        : few    ? (e > 0 ? score_finish<1, true> : score_finish<1, false>)
+                                 : (e > 0 ? score_finish<4, true> : score_finish<4, false>);
+    const int sub = topk_tiles_per_wg(n, batch);
+    const unsigned wgs = few ? (unsigned)((n + 1024 * (int64_t)sub - 1) / (1024 * (int64_t)sub)) : (unsigned)((n + 63 - 2 * e) / (64 - 2 * e));
+    kernel<<<dim3(wgs, batch), 256, 0, st>>>(S, s_ld, s_bs, n, part, n_part, l_c, e, sub, out, out_bs, hist, first_hist_bs);
+    if (hist && first_hist_done) *first_hist_done = true;
+    zeroed = first_hist != nullptr;
+    pool_left = eps > 0 && !narrow;
+  };
   if (vec_ok && l_c == 1 && (d_c == 64 || d_c == 128 || d_c == 256)) {
-    const int lpr = d_c / 8;
     const int nblk = (int)((n + kGemvRows - 1) / kGemvRows);
-    const dim3 grid((unsigned)nblk, batch);
-    const bf16_t* q = (const bf16_t*)qc;
-    const bf16_t* k = (const bf16_t*)kc_cache;
-    float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
-    uint32_t* fh = first_hist;
-    const int64_t fbs = first_hist_bs;
-    zeroed = fh != nullptr;
-    if (lpr == 8) score_gemv_bf16<8><<<grid, 256, 0, st>>>(q, k, m_lo, n, part, raw, q_bs, kc_bs, raw_bs, fh, fbs);
-    else if (lpr == 16) score_gemv_bf16<16><<<grid, 256, 0, st>>>(q, k, m_lo, n, part, raw, q_bs, kc_bs, raw_bs, fh, fbs);
-    else score_gemv_bf16<32><<<grid, 256, 0, st>>>(q, k, m_lo, n, part, raw, q_bs, kc_bs, raw_bs, fh, fbs);
-    const int blocks = sub_mu_blocks(n);
-    if (tail && eps <= kTailMaxEps) {
-      tail->part = part;
-      tail->n_part = nblk;
+    const auto gemv = d_c == 64 ? score_gemv_bf16<8> : d_c == 128 ? score_gemv_bf16<16> : score_gemv_bf16<32>;
+    gemv<<<dim3((unsigned)nblk, batch), 256, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
+                                                      first_hist, first_hist_bs);
+    if (tail && narrow) {
+      *tail = ScoreTail{raw, raw_bs, part, nblk, eps};
+      pool_left = false;
     } else {
-      score_sub_mu<<<dim3(blocks, batch), 256, 0, st>>>(raw, n, part, nblk, raw_bs, pool_hist ? nullptr : fh, fbs);
+      finish(nblk);
     }
-    if (fh && !pool_hist && first_hist_done) *first_hist_done = true;
+  } else if (vec_ok && l_c <= kFewQueries && (d_c == 128 || d_c == 64)) {
+    const int nblk = (int)((n + kFewTok - 1) / kFewTok);
+    const auto few = d_c == 128 ? score_few_bf16<128> : score_few_bf16<64>;
+    few<<<dim3((unsigned)nblk, batch), 256, 0, st>>>((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, S, s_ld, s_bs, q_bs,
+                                                     kc_bs, nblk, first_hist, first_hist_bs);
+    finish(nblk);
   } else if (vec_ok && (d_c == 128 || d_c == 64)) {
-    float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
-    size_t qfrag_at = mu_bytes(l_c, batch) + part_bytes(l_c, n, batch);
-    if (eps > 0) qfrag_at += align_up((size_t)n * 4, 256) * (size_t)batch;
-    bf16_t* qfrag = (bf16_t*)((char*)ws + qfrag_at);
     const int64_t qfrag_bs = (int64_t)(qfrag_bytes_per_batch(l_c) / sizeof(bf16_t));
     const auto sweeps = d_c == 128 ? launch_sweeps<128> : launch_sweeps<64>;
     const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, raw, batch, q_bs, kc_bs,
-                          raw_bs, first_hist, !pool_hist, first_hist_bs, qfrag, qfrag_bs, st);
+                          raw_bs, first_hist, eps == 0, first_hist_bs, qfrag, qfrag_bs, st);
     if (rc != ESA_OK) return rc;
     zeroed = first_hist != nullptr;
-    if (first_hist && !pool_hist && first_hist_done) *first_hist_done = true;
+    if (first_hist && eps == 0 && first_hist_done) *first_hist_done = true;
+    if (tail && narrow && eps > 0) {
+      *tail = ScoreTail{raw, raw_bs, nullptr, 0, eps};
+      pool_left = false;
+    }
+  } else if (stores_scores(l_c, n, batch)) {
+    const int nblk = (int)((n + kGTok - 1) / kGTok);
+    const dim3 grid((unsigned)nblk, (unsigned)((l_c + kStoreQ - 1) / kStoreQ), batch);
+    const size_t smem = (size_t)(kGTok + kStoreQ) * store_ld(d_c) * sizeof(float);
+    const auto go = [&](auto kernel, auto* q, auto* k) -> int {
+      if (smem > 65536) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return hip_failed(e, "hipFuncSetAttribute(score_store_fma)");
+      }
+      kernel<<<grid, 256, smem, st>>>(q, l_c, k, m_lo, n, d_c, part, S, s_ld, s_bs, q_bs, kc_bs, nblk, first_hist, first_hist_bs);
+      return ESA_OK;
+    };
+    const int rc = dtype == ESA_BF16 ? go(score_store_fma<bf16_t>, (const bf16_t*)qc, (const bf16_t*)kc_cache)
+                                     : go(score_store_fma<float>, (const float*)qc, (const float*)kc_cache);
+    if (rc != ESA_OK) return rc;
+    finish(nblk);
   } else {
+    uint32_t* mu = (uint32_t*)ws;
     fill_u32<<<(l_c * batch + 255) / 256, 256, 0, st>>>(mu, (int64_t)l_c * batch, kOrderedKeyOfMinusInf);
     const dim3 grid((unsigned)((n + kGTok - 1) / kGTok), batch);
     const size_t smem = (size_t)(kGTok * (d_c + 1) + 4 * kGTok) * sizeof(float);
@@ -833,11 +1098,9 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                                                    raw, q_bs, kc_bs, raw_bs);
     }
   }
-  if (tail && eps > kTailMaxEps) *tail = ScoreTail{score, score_bs, nullptr, 0, 0};
-  if (eps > 0 && !(tail && eps <= kTailMaxEps)) {
-    const int blocks = maxpool_blocks(n);
-    uint32_t* ph = zeroed ? pool_hist : nullptr;       // only behind kernels that have zeroed the histograms
-    proximity_maxpool<<<dim3(blocks, batch), 256, 0, st>>>(raw, score, n, eps, raw_bs, score_bs, ph, first_hist_bs);
+  if (pool_left) {
+    uint32_t* ph = zeroed ? first_hist : nullptr;      // only behind kernels that have zeroed the histogram
+    proximity_maxpool<<<dim3(maxpool_blocks(n), batch), 256, 0, st>>>(raw, score, n, eps, raw_bs, score_bs, ph, first_hist_bs);
     if (ph && first_hist_done) *first_hist_done = true;
   }
   ESA_LAUNCH_CHECK("score");

@@ -564,6 +564,11 @@ int64_t topk_row_stride_words(int64_t n, int batch) {
   return (int64_t)(align_up((size_t)topk_row_words(topk_plan(n, batch)) * sizeof(uint32_t), 256) / sizeof(uint32_t));
 }
 
+int topk_tiles_per_wg(int64_t n, int batch) {
+  static_assert(kTile == 1024, "tiles of the kernels that write the scores");
+  return (int)topk_plan(n, batch).sub;
+}
+
 int launch_select_small(const ScoreTail& tail, float* score, int64_t score_bs, int64_t n, int k, int64_t base, int32_t* idx,
                         int64_t idx_bs, int batch, hipStream_t st) {
   const size_t lds = tail.eps > 0 ? (size_t)n * sizeof(float) : 0;
