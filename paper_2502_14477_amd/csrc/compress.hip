@@ -11,71 +11,100 @@
 //   * compress_few_packed_bf16 — the same inputs for one to four tokens (a decode step): one workgroup per
 //     output, a dot product per token.
 //   * compress_mfma_bf16 — bf16 storage, weights as given ([d_in, d_c]); W is transposed through LDS.
-//   * compress_fma — any storage type, shape and weight layout, plain fp32 FMAs in ascending
-//     reduction order.
+//   * compress_fma — any storage type, shape and weight layout, plain fp32 FMAs.
 //   * pack_weights — the one-time transposition [d_in, d_c] -> [d_c, d_in].
 #include "esa_common.h"
 
 namespace esa {
 namespace {
 
+// One launch serves up to two inputs ("jobs") that share the token count, d_c and the batch: the chunk's
+// queries and keys are compressed side by side (Eq. 5 has both).  The job is the slow index of the grid
+// (blockIdx.y = job * col_tiles + column tile), so that all workgroups of job 0 are dispatched before
+// those of job 1 and a compute unit gets one of each rather than two of the long ones.
+template <typename T>
+struct CompressJob {
+  const T* x;
+  const T* Wt;
+  const T* bias;
+  T* out;
+  int64_t d_in, ldx, ldo, x_bs, out_bs;
+};
+// field-wise select: every kernel argument is fetched in the first round trip
+template <typename T>
+__device__ __forceinline__ CompressJob<T> pick_job(const CompressJob<T>& j0, const CompressJob<T>& j1, bool second) {
+  CompressJob<T> j;
+  j.x = second ? j1.x : j0.x;
+  j.Wt = second ? j1.Wt : j0.Wt;
+  j.bias = second ? j1.bias : j0.bias;
+  j.out = second ? j1.out : j0.out;
+  j.d_in = second ? j1.d_in : j0.d_in;
+  j.ldx = second ? j1.ldx : j0.ldx;
+  j.ldo = second ? j1.ldo : j0.ldo;
+  j.x_bs = second ? j1.x_bs : j0.x_bs;
+  j.out_bs = second ? j1.out_bs : j0.out_bs;
+  return j;
+}
+
 // ------------------------------------------------------------------------------------------ generic
-constexpr int kTok = 16;       // tokens per block
-constexpr int kChunk = 64;     // reduction elements staged per step
-constexpr int kMaxColsPerLane = 4;
+// A workgroup owns 16 tokens x 16 outputs, one per thread of 256; four groups of 256 threads take a quarter of every
+// 256 staged reduction elements each, and their sums are added in a fixed order.  What bounds a small layer is the
+// number of round trips (a chunk of 128 tokens of an fp32 layer with d_in = 256: one; 28 us per input for one workgroup
+// per 16 tokens that walked the reduction 64 elements at a time).
+constexpr int kTok = 16;
+constexpr int kCols = 16;
+constexpr int kStage = 256;    // reduction elements staged per step
 
 template <typename T, bool PACKED>
-__global__ __launch_bounds__(256) void compress_fma(const T* __restrict__ x, int64_t n_tok, int64_t d_in, int64_t ldx,
-                                                    const T* __restrict__ W, const T* __restrict__ bias, int d_c,
-                                                    T* __restrict__ out, int64_t ldo, int64_t x_bs, int64_t out_bs) {
-  __shared__ float xs[kTok][kChunk + 1];
-  const T* xb = x + (int64_t)blockIdx.y * x_bs;
-  T* ob = out + (int64_t)blockIdx.y * out_bs;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(1024) void compress_fma(CompressJob<T> j0, CompressJob<T> j1, int64_t n_tok, int d_c, int col_tiles) {
+  constexpr int kLd = kStage + 4;                // rows 16 bytes apart in the banks
+  __shared__ __attribute__((aligned(16))) float xs[kTok][kLd], ws[kCols][kLd];
+  __shared__ float red[4][kTok * kCols];
+  const bool second = (int)blockIdx.y >= col_tiles;
+  const CompressJob<T> j = pick_job(j0, j1, second);
+  const T* xb = j.x + (int64_t)blockIdx.z * j.x_bs;
+  const int tid = threadIdx.x, kg = tid >> 8, o = tid & 255, t = o >> 4, c = o & 15;
   const int64_t tok0 = (int64_t)blockIdx.x * kTok;
-  float acc[4][kMaxColsPerLane];
+  const int col0 = ((int)blockIdx.y - (second ? col_tiles : 0)) * kCols;      // d_c is a multiple of 16
+  float acc = 0.f;
+  for (int64_t i0 = 0; i0 < j.d_in; i0 += kStage) {
+    float xv[4], wv[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + 1024 * u, row = e >> 8;
+      const int64_t i = i0 + (e & 255), tok = tok0 + row;
+      xv[u] = i < j.d_in && tok < n_tok ? load_f32(xb + tok * j.ldx + i) : 0.f;
+      if (PACKED) {
+        wv[u] = i < j.d_in ? load_f32(j.Wt + (int64_t)(col0 + row) * j.d_in + i) : 0.f;
+      } else {
+        const int64_t iw = i0 + (e >> 4);
+        wv[u] = iw < j.d_in ? load_f32(j.Wt + iw * (int64_t)d_c + col0 + (e & 15)) : 0.f;
+      }
+    }
+    __syncthreads();                             // the previous step's reads are done
 #pragma unroll
-    for (int c = 0; c < kMaxColsPerLane; ++c) acc[t][c] = 0.f;
-
-  for (int64_t i0 = 0; i0 < d_in; i0 += kChunk) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < kTok * kChunk; e += 256) {
-      const int t = e / kChunk, c = e % kChunk;
-      const int64_t tok = tok0 + t, i = i0 + c;
-      xs[t][c] = (tok < n_tok && i < d_in) ? load_f32(xb + tok * ldx + i) : 0.f;
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + 1024 * u;
+      xs[e >> 8][e & 255] = xv[u];
+      if (PACKED) ws[e >> 8][e & 255] = wv[u];
+      else ws[e & 15][e >> 4] = wv[u];
     }
     __syncthreads();
-    const int lim = (d_in - i0) < kChunk ? (int)(d_in - i0) : kChunk;
-    for (int ii = 0; ii < lim; ++ii) {
-      float wv[kMaxColsPerLane];
 #pragma unroll
-      for (int c = 0; c < kMaxColsPerLane; ++c) {
-        const int j = lane + 64 * c;
-        wv[c] = (j < d_c) ? load_f32(PACKED ? W + (int64_t)j * d_in + (i0 + ii) : W + (i0 + ii) * (int64_t)d_c + j) : 0.f;
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const float xv = xs[wave * 4 + t][ii];
-#pragma unroll
-        for (int c = 0; c < kMaxColsPerLane; ++c) acc[t][c] = __fmaf_rn(xv, wv[c], acc[t][c]);
-      }
+    for (int k = 0; k < kStage / 4; k += 4) {
+      const float4 a = *(const float4*)&xs[t][kg * (kStage / 4) + k], b = *(const float4*)&ws[c][kg * (kStage / 4) + k];
+      acc = __fmaf_rn(a.x, b.x, acc);
+      acc = __fmaf_rn(a.y, b.y, acc);
+      acc = __fmaf_rn(a.z, b.z, acc);
+      acc = __fmaf_rn(a.w, b.w, acc);
     }
   }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int64_t tok = tok0 + wave * 4 + t;
-    if (tok >= n_tok) continue;
-#pragma unroll
-    for (int c = 0; c < kMaxColsPerLane; ++c) {
-      const int j = lane + 64 * c;
-      if (j < d_c) {
-        float v = acc[t][c];
-        if (bias) v += load_f32(bias + j);
-        store_f32(ob + tok * ldo + j, v);
-      }
-    }
+  red[kg][o] = acc;
+  __syncthreads();
+  if (kg == 0 && tok0 + t < n_tok) {
+    float v = (red[0][o] + red[1][o]) + (red[2][o] + red[3][o]);
+    if (j.bias) v += load_f32(j.bias + col0 + c);
+    store_f32(j.out + (int64_t)blockIdx.z * j.out_bs + (tok0 + t) * j.ldo + col0 + c, v);
   }
 }
 
@@ -144,30 +173,15 @@ __global__ __launch_bounds__(256) void compress_mfma_bf16(const bf16_t* __restri
 // v_mfma_f32_16x16x32_bf16: lane l supplies A[l%16][8*(l/16) .. +7] and B[8*(l/16) .. +7][l%16] and owns
 // C[4*(l/16) .. +3][l%16].  A rows are tokens, B columns are outputs, so a lane reads eight consecutive
 // reduction elements of one token row of x and of one output row of the packed weights.
-// One launch serves up to two inputs ("jobs") that share the token count, d_c and the batch: the chunk's
-// queries and keys are compressed side by side (Eq. 5 has both).  The job is the slow index of the grid
-// (blockIdx.y = job * col_tiles + column tile), so that all workgroups of job 0 are dispatched before
-// those of job 1 and a compute unit gets one of each rather than two of the long ones.
-struct CompressJob {
-  const bf16_t* x;
-  const bf16_t* Wt;
-  const bf16_t* bias;
-  bf16_t* out;
-  int64_t d_in, ldx, ldo, x_bs, out_bs;
-};
-
 template <int NW>
-__global__ __launch_bounds__(64 * NW) void compress_mfma_packed_bf16(CompressJob j0, CompressJob j1, int64_t n_tok,
+__global__ __launch_bounds__(64 * NW) void compress_mfma_packed_bf16(CompressJob<bf16_t> j0, CompressJob<bf16_t> j1, int64_t n_tok,
                                                                  int col_tiles) {
   __shared__ float red[NW][256];
   const bool second = (int)blockIdx.y >= col_tiles;
-  // field-wise select: every kernel argument is fetched in the first round trip
-  const bf16_t* x = second ? j1.x : j0.x;
-  const bf16_t* Wt = second ? j1.Wt : j0.Wt;
-  const bf16_t* bias = second ? j1.bias : j0.bias;
-  bf16_t* out = second ? j1.out : j0.out;
-  const int64_t d_in = second ? j1.d_in : j0.d_in, ldx = second ? j1.ldx : j0.ldx, ldo = second ? j1.ldo : j0.ldo;
-  const int64_t x_bs = second ? j1.x_bs : j0.x_bs, out_bs = second ? j1.out_bs : j0.out_bs;
+  const CompressJob<bf16_t> jb = pick_job(j0, j1, second);
+  const bf16_t *x = jb.x, *Wt = jb.Wt, *bias = jb.bias;
+  bf16_t* out = jb.out;
+  const int64_t d_in = jb.d_in, ldx = jb.ldx, ldo = jb.ldo, x_bs = jb.x_bs, out_bs = jb.out_bs;
   const bf16_t* xb = x + (int64_t)blockIdx.z * x_bs;
   bf16_t* ob = out + (int64_t)blockIdx.z * out_bs;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -212,15 +226,13 @@ __global__ __launch_bounds__(64 * NW) void compress_mfma_packed_bf16(CompressJob
 // LDS): deterministic, no atomics.  blockIdx.x = output, blockIdx.y = input (job), blockIdx.z = batch entry.
 constexpr int kFewTok = 4;
 constexpr int kFewBatch = 4;     // larger batches re-read the weights once per entry here: the matrix-core kernel wins
-__global__ __launch_bounds__(256) void compress_few_packed_bf16(CompressJob j0, CompressJob j1, int n_tok) {
+__global__ __launch_bounds__(256) void compress_few_packed_bf16(CompressJob<bf16_t> j0, CompressJob<bf16_t> j1, int n_tok) {
   __shared__ float red[4][kFewTok];
   const bool second = blockIdx.y != 0;
-  const bf16_t* x = second ? j1.x : j0.x;
-  const bf16_t* Wt = second ? j1.Wt : j0.Wt;
-  const bf16_t* bias = second ? j1.bias : j0.bias;
-  bf16_t* out = second ? j1.out : j0.out;
-  const int64_t d_in = second ? j1.d_in : j0.d_in, ldx = second ? j1.ldx : j0.ldx, ldo = second ? j1.ldo : j0.ldo;
-  const int64_t x_bs = second ? j1.x_bs : j0.x_bs, out_bs = second ? j1.out_bs : j0.out_bs;
+  const CompressJob<bf16_t> jb = pick_job(j0, j1, second);
+  const bf16_t *x = jb.x, *Wt = jb.Wt, *bias = jb.bias;
+  bf16_t* out = jb.out;
+  const int64_t d_in = jb.d_in, ldx = jb.ldx, ldo = jb.ldo, x_bs = jb.x_bs, out_bs = jb.out_bs;
   const bf16_t* xb = x + (int64_t)blockIdx.z * x_bs;
   const int col = blockIdx.x;
   const bf16_t* wrow = Wt + (int64_t)col * d_in;
@@ -291,18 +303,30 @@ int launch_pack_weights(const void* W, int64_t d_in, int d_c, int dtype, void* W
   return ESA_OK;
 }
 
+namespace {
+
+// The kernel for every storage type, shape and alignment; job 1 may repeat job 0 (n_jobs = 1).
+template <typename T>
+void run_compress_fma(const CompressJob<T>& j0, const CompressJob<T>& j1, int n_jobs, int64_t n_tok, int d_c, bool packed, int batch,
+                      hipStream_t st) {
+  const dim3 grid((unsigned)((n_tok + kTok - 1) / kTok), n_jobs * (d_c / kCols), batch);
+  if (packed) compress_fma<T, true><<<grid, 1024, 0, st>>>(j0, j1, n_tok, d_c, d_c / kCols);
+  else compress_fma<T, false><<<grid, 1024, 0, st>>>(j0, j1, n_tok, d_c, d_c / kCols);
+}
+
+}  // namespace
+
 int launch_compress(const void* x, int64_t n_tok, int64_t d_in, int64_t ldx, const void* W, int w_layout,
                     const void* bias, int d_c, void* out, int64_t ldo, int dtype, int batch, int64_t x_bs,
                     int64_t out_bs, hipStream_t st) {
-  const int64_t nblk = (n_tok + kTok - 1) / kTok;
   const bool packed = (w_layout == ESA_W_PACKED);
   if (dtype == ESA_BF16) {
     const bool vec_ok = (ldx % 8 == 0) && (x_bs % 8 == 0) && (((uintptr_t)x | (uintptr_t)W) % 16 == 0);
+    const CompressJob<bf16_t> job{(const bf16_t*)x, (const bf16_t*)W, (const bf16_t*)bias, (bf16_t*)out, d_in, ldx, ldo, x_bs, out_bs};
     if (packed && vec_ok && d_c % 16 == 0 && d_in % 128 == 0) {
       // few tokens: the reduction is cut sixteen ways so that every lane's loads are all in flight at once
       const int tiles = (int)((n_tok + 15) / 16);
       const dim3 grid((unsigned)tiles, d_c / 16, batch);
-      const CompressJob job{(const bf16_t*)x, (const bf16_t*)W, (const bf16_t*)bias, (bf16_t*)out, d_in, ldx, ldo, x_bs, out_bs};
       if (n_tok <= kFewTok && batch <= kFewBatch)
         compress_few_packed_bf16<<<dim3(d_c, 1, batch), 256, 0, st>>>(job, job, (int)n_tok);
       else if (d_in % 512 == 0 && n_tok <= 4096)
@@ -310,30 +334,22 @@ int launch_compress(const void* x, int64_t n_tok, int64_t d_in, int64_t ldx, con
       else
         compress_mfma_packed_bf16<4><<<grid, 256, 0, st>>>(job, job, n_tok, d_c / 16);
     } else if (!packed && vec_ok && (d_c % kMCols == 0) && (d_in % kMStep == 0)) {
-      compress_mfma_bf16<<<dim3((unsigned)nblk, d_c / kMCols, batch), 256, 0, st>>>(
-          (const bf16_t*)x, n_tok, d_in, ldx, (const bf16_t*)W, (const bf16_t*)bias, d_c, (bf16_t*)out, ldo, x_bs,
-          out_bs);
-    } else if (packed) {
-      compress_fma<bf16_t, true><<<dim3((unsigned)nblk, batch), 256, 0, st>>>(
+      compress_mfma_bf16<<<dim3((unsigned)((n_tok + kMTok - 1) / kMTok), d_c / kMCols, batch), 256, 0, st>>>(
           (const bf16_t*)x, n_tok, d_in, ldx, (const bf16_t*)W, (const bf16_t*)bias, d_c, (bf16_t*)out, ldo, x_bs,
           out_bs);
     } else {
-      compress_fma<bf16_t, false><<<dim3((unsigned)nblk, batch), 256, 0, st>>>(
-          (const bf16_t*)x, n_tok, d_in, ldx, (const bf16_t*)W, (const bf16_t*)bias, d_c, (bf16_t*)out, ldo, x_bs,
-          out_bs);
+      run_compress_fma<bf16_t>(job, job, 1, n_tok, d_c, packed, batch, st);
     }
-  } else if (packed) {
-    compress_fma<float, true><<<dim3((unsigned)nblk, batch), 256, 0, st>>>(
-        (const float*)x, n_tok, d_in, ldx, (const float*)W, (const float*)bias, d_c, (float*)out, ldo, x_bs, out_bs);
   } else {
-    compress_fma<float, false><<<dim3((unsigned)nblk, batch), 256, 0, st>>>(
-        (const float*)x, n_tok, d_in, ldx, (const float*)W, (const float*)bias, d_c, (float*)out, ldo, x_bs, out_bs);
+    const CompressJob<float> job{(const float*)x, (const float*)W, (const float*)bias, (float*)out, d_in, ldx, ldo, x_bs, out_bs};
+    run_compress_fma<float>(job, job, 1, n_tok, d_c, packed, batch, st);
   }
   ESA_LAUNCH_CHECK("compress");
   return ESA_OK;
 }
 
-// Two inputs in one launch when both take the short-reduction matrix-core kernel; otherwise one launch each.
+// Two inputs in one launch when both take the same kernel (the short-reduction matrix-core kernel, or fp32); otherwise
+// one launch each.
 int launch_compress_pair(const void* x0, int64_t d_in0, int64_t ldx0, const void* W0, const void* bias0, void* out0,
                          int64_t ldo0, int64_t x0_bs, int64_t out0_bs, const void* x1, int64_t d_in1, int64_t ldx1,
                          const void* W1, const void* bias1, void* out1, int64_t ldo1, int64_t x1_bs, int64_t out1_bs,
@@ -344,13 +360,20 @@ int launch_compress_pair(const void* x0, int64_t d_in0, int64_t ldx0, const void
   if (dtype == ESA_BF16 && w_layout == ESA_W_PACKED && d_c % 16 == 0 && n_tok <= 4096 && n_tok > 0 &&
       fast(x0, d_in0, ldx0, W0, x0_bs) && fast(x1, d_in1, ldx1, W1, x1_bs)) {
     const int tiles = (int)((n_tok + 15) / 16);
-    const CompressJob j0{(const bf16_t*)x0, (const bf16_t*)W0, (const bf16_t*)bias0, (bf16_t*)out0, d_in0, ldx0, ldo0, x0_bs, out0_bs};
-    const CompressJob j1{(const bf16_t*)x1, (const bf16_t*)W1, (const bf16_t*)bias1, (bf16_t*)out1, d_in1, ldx1, ldo1, x1_bs, out1_bs};
+    const CompressJob<bf16_t> j0{(const bf16_t*)x0, (const bf16_t*)W0, (const bf16_t*)bias0, (bf16_t*)out0, d_in0, ldx0, ldo0, x0_bs, out0_bs};
+    const CompressJob<bf16_t> j1{(const bf16_t*)x1, (const bf16_t*)W1, (const bf16_t*)bias1, (bf16_t*)out1, d_in1, ldx1, ldo1, x1_bs, out1_bs};
     if (n_tok <= kFewTok && batch <= kFewBatch)
       compress_few_packed_bf16<<<dim3(d_c, 2, batch), 256, 0, st>>>(j0, j1, (int)n_tok);
     else
       compress_mfma_packed_bf16<16><<<dim3(tiles, 2 * (d_c / 16), batch), 1024, 0, st>>>(j0, j1, n_tok, d_c / 16);
     ESA_LAUNCH_CHECK("compress (pair)");
+    return ESA_OK;
+  }
+  if (dtype == ESA_F32) {
+    const CompressJob<float> j0{(const float*)x0, (const float*)W0, (const float*)bias0, (float*)out0, d_in0, ldx0, ldo0, x0_bs, out0_bs};
+    const CompressJob<float> j1{(const float*)x1, (const float*)W1, (const float*)bias1, (float*)out1, d_in1, ldx1, ldo1, x1_bs, out1_bs};
+    run_compress_fma<float>(j0, j1, 2, n_tok, d_c, w_layout == ESA_W_PACKED, batch, st);
+    ESA_LAUNCH_CHECK("compress (fp32 pair)");
     return ESA_OK;
   }
   const int rc = launch_compress(x0, n_tok, d_in0, ldx0, W0, w_layout, bias0, d_c, out0, ldo0, dtype, batch, x0_bs, out0_bs, st);
