@@ -4,84 +4,175 @@
 // element i of its second half turn by the angle pos * base^(-2i/d).
 //
 // The arithmetic is fp64 end to end and rounds once into the storage type, so a row encoded here
-// equals the fp64 definition rounded to storage.  The volume is small (the chunk's queries and the
-// local window's keys, a few MB per step); one workgroup per row, one frequency per thread.
+// equals the fp64 definition rounded to storage.  What bounds it is that arithmetic as much as the memory traffic
+// (re-encoded decode, batch 8: 16392 key rows of 2 KB, 67 MB): with a power, a sine and a cosine per row and frequency,
+// their table read again for every head, and a rounding from fp64 to bf16 in 64-bit integer steps it took 31.5 us.  Now
+// the frequencies and the turn from one row to the next come from the host (fp64 too, kept per thread for a base and
+// head size), a thread evaluates sine and cosine for the first of its few consecutive rows and turns the others by complex
+// multiplication (a handful of errors of 2^-53), and the heads of a row share the pairs held in registers.
+#include <cmath>
+
 #include "esa_common.h"
 
 namespace esa {
 namespace {
 
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+
+constexpr int kMaxHalf = 128;
+// Angle per position of every frequency, and its cosine and sine for one turn of `step` positions.
+struct Turns {
+  double freq[kMaxHalf], c[kMaxHalf], s[kMaxHalf];
+};
 struct RopeJobs {
   RopeJob j[kMaxRopeJobs];
 };
 
-// fp64 -> bf16, round to nearest even in one step (through fp32 first would round twice).
-__device__ __forceinline__ bf16_t f64_to_bf16(double v) {
+// fp64 -> fp32, such that rounding the result to bf16 rounds the fp64 value: where the nearest fp32 number is the midpoint
+// of two bf16 numbers and not the value itself, the side the value lies on is kept.
+__device__ __forceinline__ float narrow_for_bf16(double v) {
   const float f = (float)v;
-  const float a = fabsf(f);
-  if (!(a >= 1.1754944e-38f && a < 3.0e38f)) return f32_to_bf16(f);   // zero, subnormal, huge, NaN: via fp32
-  uint64_t u = (uint64_t)__double_as_longlong(v);
-  u += ((1ull << 44) - 1) + ((u >> 45) & 1ull);      // 52 - 7 = 45 fraction bits go
-  u &= ~((1ull << 45) - 1);
-  return (bf16_t)(__float_as_uint((float)__longlong_as_double((long long)u)) >> 16);   // exact conversions
+  const uint32_t u = __float_as_uint(f);
+  if ((u & 0xFFFFu) == 0x8000u) {
+    const double left = v - (double)f;      // exact
+    if (left != 0.0) return __uint_as_float((left > 0.0) == (f > 0.f) ? u + 1u : u - 1u);
+  }
+  return f;
 }
 
-template <typename T> __device__ __forceinline__ double load_f64(const T* p);
-template <> __device__ __forceinline__ double load_f64<float>(const float* p) { return (double)*p; }
-template <> __device__ __forceinline__ double load_f64<bf16_t>(const bf16_t* p) { return (double)bf16_to_f32(*p); }
-template <typename T> __device__ __forceinline__ void store_f64(T* p, double v);
-template <> __device__ __forceinline__ void store_f64<float>(float* p, double v) { *p = (float)v; }
-template <> __device__ __forceinline__ void store_f64<bf16_t>(bf16_t* p, double v) { *p = f64_to_bf16(v); }
+template <typename T> __device__ __forceinline__ double load_f64(T v);
+template <> __device__ __forceinline__ double load_f64<float>(float v) { return (double)v; }
+template <> __device__ __forceinline__ double load_f64<bf16_t>(bf16_t v) { return (double)bf16_to_f32(v); }
 
-// grid (rows, jobs, batch); 256 threads.  The row's d/2 angles are computed once (fp64) and shared
-// through LDS; every thread then turns VEC consecutive pairs per step (VEC elements = 16 bytes per
-// access when VEC > 1; VEC == 1 serves unaligned rows).
+// Two results rounded into storage.
+template <typename T> __device__ __forceinline__ void store_f64(T* p, double a, double b);
+template <> __device__ __forceinline__ void store_f64<float>(float* p, double a, double b) {
+  p[0] = (float)a;
+  p[1] = (float)b;
+}
+template <> __device__ __forceinline__ void store_f64<bf16_t>(bf16_t* p, double a, double b) {
+  const f32x2 f = {narrow_for_bf16(a), narrow_for_bf16(b)};
+  *(uint32_t*)p = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+}
+
+constexpr int kRopeRows = 16;     // most rows of a workgroup
+constexpr int kAhead = 4;         // heads whose loads a thread has in flight
+// Rows of a workgroup, of at most `budget` rows x heads: fewer of the wide ones, so that a thread has one or two rounds
+// of kAhead heads to turn (every round is a round trip to memory, and a chunk's queries are few rows of many heads).
+__host__ __device__ inline int rows_of(int heads, int budget) {
+  int r = kRopeRows;
+  while (r > 1 && r * heads > budget) r /= 2;
+  return r;
+}
+
+// grid (groups of rows, jobs, batch); 256 threads.  The rows' angles go through LDS once; then a thread owns VEC
+// consecutive pairs of a row (VEC elements = 16 bytes per access when VEC > 1; VEC == 1 serves unaligned rows) for all of
+// the row's heads, or for every hs-th of them where there are too few rows to go round.
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, int d, double base) {
-  __shared__ double cs[2][128];
+__global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int d, int budget) {
+  extern __shared__ double cs[];                       // [kRopeRows][d/2] cosines, then sines
   const RopeJob jb = jobs.j[blockIdx.y];
-  const int64_t row = blockIdx.x;
-  if (row >= jb.n_tok) return;
-  const int half = d >> 1;
-  const T* x = (const T*)jb.x + (int64_t)blockIdx.z * jb.x_bs + row * jb.ldx;
-  T* o = (T*)jb.out + (int64_t)blockIdx.z * jb.out_bs + row * jb.ldo;
+  const int wg_rows = rows_of(jb.heads, budget);
+  const int64_t row0 = (int64_t)blockIdx.x * wg_rows;
+  if (row0 >= jb.n_tok) return;
+  const int n_rows = jb.n_tok - row0 < wg_rows ? (int)(jb.n_tok - row0) : wg_rows;
+  const int half = d >> 1, tid = threadIdx.x;
+  const T* x = (const T*)jb.x + (int64_t)blockIdx.z * jb.x_bs + row0 * jb.ldx;
+  T* o = (T*)jb.out + (int64_t)blockIdx.z * jb.out_bs + row0 * jb.ldo;
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
-  if (!jb.rotate) {                       // plain copy of the row
-    const int n = jb.heads * d;
-    for (int e = threadIdx.x * VEC; e < n; e += 256 * VEC) *(vec_t*)(o + e) = *(const vec_t*)(x + e);
+  if (!jb.rotate) {                       // plain copy of the rows
+    const int n = jb.heads * d / VEC;     // d is a multiple of VEC
+    for (int e = tid; e < n_rows * n; e += 256)
+      *(vec_t*)(o + (int64_t)(e / n) * jb.ldo + e % n * VEC) = *(const vec_t*)(x + (int64_t)(e / n) * jb.ldx + e % n * VEC);
     return;
   }
-  const double pos = jb.pos0 + (double)row * jb.pos_step;
-  if ((int)threadIdx.x < half) {
-    double c = 1.0, s = 0.0;
-    if (pos != 0.0) {
-      const double ang = pos * pow(base, -2.0 * (double)threadIdx.x / (double)d);
-      s = sin(ang);
-      c = cos(ang);
+  double* sn = cs + kRopeRows * half;
+  {
+    const int groups = 256 / half, i = tid % half, g = tid / half;        // half is a power of two, at most kMaxHalf
+    const int per = groups < wg_rows ? wg_rows / groups : 1;              // consecutive rows of a thread
+    const int first = g * per;
+    if (first < n_rows) {
+      const double pos = jb.pos0 + (double)(row0 + first) * jb.pos_step;
+      double c = 1.0, s = 0.0;
+      if (pos != 0.0) sincos(pos * turns.freq[i], &s, &c);
+      const bool turning = jb.pos_step != 0.0;
+      const double dc = turning ? turns.c[i] : 1.0, ds = turning ? turns.s[i] : 0.0;
+      for (int r = first; r < first + per && r < n_rows; ++r) {
+        cs[r * half + i] = c;
+        sn[r * half + i] = s;
+        const double c2 = c * dc - s * ds;
+        s = s * dc + c * ds;
+        c = c2;
+      }
     }
-    cs[0][threadIdx.x] = c;
-    cs[1][threadIdx.x] = s;
   }
   __syncthreads();
-  const int n_pairs = jb.heads * half;    // half is a multiple of VEC
-  for (int p = threadIdx.x * VEC; p < n_pairs; p += 256 * VEC) {
-    const int h = p / half, i = p % half;
-    const vec_t a = *(const vec_t*)(x + h * d + i), b = *(const vec_t*)(x + h * d + half + i);
-    vec_t ra, rb;
+  const int n_vecs = half / VEC;                       // half is a multiple of VEC
+  int hs = 1;
+  while (hs < jb.heads && n_rows * n_vecs * hs < 256) hs *= 2;
+  for (int e = tid; e < n_rows * n_vecs * hs; e += 256) {
+    const int i = e % n_vecs * VEC, r = e / n_vecs % n_rows, h0 = e / (n_vecs * n_rows);
+    double c[VEC], s[VEC];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      T ae = a[e], be = b[e];
-      const double x1 = load_f64<T>(&ae), x2 = load_f64<T>(&be);
-      const double c = cs[0][i + e], sn = cs[1][i + e];
-      T r1, r2;
-      store_f64<T>(&r1, x1 * c - x2 * sn);
-      store_f64<T>(&r2, x2 * c + x1 * sn);
-      ra[e] = r1;
-      rb[e] = r2;
+    for (int k = 0; k < VEC; ++k) {
+      c[k] = cs[r * half + i + k];
+      s[k] = sn[r * half + i + k];
     }
-    *(vec_t*)(o + h * d + i) = ra;
-    *(vec_t*)(o + h * d + half + i) = rb;
+    const T* xr = x + (int64_t)r * jb.ldx + i;
+    T* orow = o + (int64_t)r * jb.ldo + i;
+    for (int hb = h0; hb < jb.heads; hb += hs * kAhead) {
+      vec_t a[kAhead], b[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int h = hb + u * hs < jb.heads ? hb + u * hs : hb;
+        a[u] = *(const vec_t*)(xr + h * d);
+        b[u] = *(const vec_t*)(xr + h * d + half);
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int h = hb + u * hs;
+        if (h >= jb.heads) break;
+        if constexpr (VEC > 1) {
+          vec_t ra, rb;
+#pragma unroll
+          for (int k = 0; k < VEC; k += 2) {
+            const double a0 = load_f64<T>(a[u][k]), a1 = load_f64<T>(a[u][k + 1]), b0 = load_f64<T>(b[u][k]), b1 = load_f64<T>(b[u][k + 1]);
+            store_f64<T>((T*)&ra + k, a0 * c[k] - b0 * s[k], a1 * c[k + 1] - b1 * s[k + 1]);
+            store_f64<T>((T*)&rb + k, b0 * c[k] + a0 * s[k], b1 * c[k + 1] + a1 * s[k + 1]);
+          }
+          *(vec_t*)(orow + h * d) = ra;
+          *(vec_t*)(orow + h * d + half) = rb;
+        } else {
+          const double a0 = load_f64<T>(a[u][0]), b0 = load_f64<T>(b[u][0]);
+          __attribute__((aligned(8))) T both[2];
+          store_f64<T>(both, a0 * c[0] - b0 * s[0], b0 * c[0] + a0 * s[0]);
+          orow[h * d] = both[0];
+          orow[h * d + half] = both[1];
+        }
+      }
+    }
   }
+}
+
+const Turns& turns_for(double base, int d, double step) {
+  struct Kept {
+    double base = 0.0, step = 0.0;
+    int d = 0;
+    Turns t;
+  };
+  static thread_local Kept k;
+  if (k.base != base || k.d != d || k.step != step) {
+    k.base = base;
+    k.d = d;
+    k.step = step;
+    for (int i = 0; i < d / 2; ++i) {
+      k.t.freq[i] = std::pow(base, -2.0 * (double)i / (double)d);
+      k.t.c[i] = std::cos(step * k.t.freq[i]);
+      k.t.s[i] = std::sin(step * k.t.freq[i]);
+    }
+  }
+  return k.t;
 }
 
 }  // namespace
@@ -90,14 +181,34 @@ bool rope_head_size_ok(int d) { return d >= 2 && d <= 256 && (d & (d - 1)) == 0;
 
 int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dtype, int batch, hipStream_t st) {
   RopeJobs js;
+  double step = 0.0;      // the jobs' common step (a job may also stand still)
   int64_t rows = 0;
   for (int k = 0; k < kMaxRopeJobs; ++k) {
     js.j[k] = jobs[k < n_jobs ? k : 0];
     if (k >= n_jobs) js.j[k].n_tok = 0;
     if (js.j[k].n_tok > rows) rows = js.j[k].n_tok;
+    if (k < n_jobs && js.j[k].rotate && js.j[k].pos_step != 0.0) {
+      if (step != 0.0 && step != js.j[k].pos_step) ESA_FAIL(ESA_EINVAL, "rope: jobs of one launch share their step");
+      step = js.j[k].pos_step;
+    }
   }
   if (rows == 0) return ESA_OK;
-  const dim3 grid((unsigned)rows, n_jobs, batch);
+  const Turns& turns = turns_for(base, d, step);
+  // Sixteen rows of eight heads share their sines and cosines best; eight where that would leave compute units without
+  // work (batch 8: 18.6 against 20.0 us; a chunk of 512 behind a window of 4096: 14.2 against 12.6 us).
+  auto most_groups = [&](int budget) {
+    int64_t most = 0;
+    for (int k = 0; k < n_jobs; ++k) {
+      const int r = rows_of(jobs[k].heads, budget);
+      const int64_t g = (jobs[k].n_tok + r - 1) / r;
+      most = g > most ? g : most;
+    }
+    return most;
+  };
+  const int budget = most_groups(128) * batch >= 512 ? 128 : 64;
+  const int64_t groups = most_groups(budget);
+  const dim3 grid((unsigned)groups, n_jobs, batch);
+  const size_t lds = (size_t)kRopeRows * d * sizeof(double);
   // 16-byte accesses when every row of every job starts on a 16-byte boundary
   const int vec = dtype == ESA_BF16 ? 8 : 4;
   bool wide = (d / 2) % vec == 0;
@@ -108,14 +219,14 @@ int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dt
   }
   if (dtype == ESA_BF16) {
     if (wide)
-      rope_rows<bf16_t, 8><<<grid, 256, 0, st>>>(js, d, base);
+      rope_rows<bf16_t, 8><<<grid, 256, lds, st>>>(js, turns, d, budget);
     else
-      rope_rows<bf16_t, 1><<<grid, 256, 0, st>>>(js, d, base);
+      rope_rows<bf16_t, 1><<<grid, 256, lds, st>>>(js, turns, d, budget);
   } else {
     if (wide)
-      rope_rows<float, 4><<<grid, 256, 0, st>>>(js, d, base);
+      rope_rows<float, 4><<<grid, 256, lds, st>>>(js, turns, d, budget);
     else
-      rope_rows<float, 1><<<grid, 256, 0, st>>>(js, d, base);
+      rope_rows<float, 1><<<grid, 256, lds, st>>>(js, turns, d, budget);
   }
   ESA_LAUNCH_CHECK("rope_rows");
   return ESA_OK;

@@ -122,3 +122,59 @@ def test_split_key_attention(esa, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel
         assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= (1e-5 if dtype == "f32" else 1e-3)
         want, _ = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
         assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL[dtype]
+
+
+# S stored: a few queries on the matrix cores (one token, tile and workgroup remainders), every other shape in fp32 FMAs;
+# pooled by the finishing pass (windows up to 16) or by the pass of its own
+@pytest.mark.parametrize("dtype,B,l_c,n,d_c,eps", [
+    ("bf16", 2, 2, 1, 128, 0), ("bf16", 1, 16, 1025, 128, 16), ("bf16", 3, 5, 9999, 64, 1), ("bf16", 17, 3, 60000, 128, 0),
+    ("bf16", 1, 7, 30001, 128, 17), ("bf16", 1, 6, 2500, 256, 2), ("f32", 2, 17, 64, 32, 16), ("f32", 1, 130, 1633, 32, 3),
+    ("f32", 1, 1, 20001, 48, 0), ("f32", 2, 16, 4097, 16, 1), ("bf16", 1, 40, 12000, 32, 5), ("bf16", 2, 1, 30000, 128, 5)])
+def test_score_with_s_stored(esa, dtype, B, l_c, n, d_c, eps):
+    say(f"score {dtype} B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
+    rng = np.random.default_rng(n + l_c)
+    qc = orc.round_to_storage(rng.standard_normal((B, l_c, d_c)) * 1.5, dtype)
+    kc = orc.round_to_storage(rng.standard_normal((B, n + 8, d_c)), dtype)
+    qd, kd, k = f64_to_dev(qc, dtype), f64_to_dev(kc, dtype), min(n, 700)
+    got = esa.esa_score(qd, kd, 3, n + 3, eps=eps)
+    for b in range(B):
+        want = orc.importance(qc[b], kc[b, 3:n + 3])
+        want = orc.proximity(want, eps) if eps else want
+        assert np.max(np.abs(to_f64(got[b]) - want)) <= F_TOL[dtype]
+        assert float(got[b].max()) == 0.0
+    score, idx, _, _ = esa.esa_score_select_gather(qd, kd, 3, n + 3, k, eps=eps)
+    assert score is None or torch.equal(score, got)
+    assert torch.equal(idx, esa.esa_select_topk(got, k, base=3))
+
+
+@pytest.mark.parametrize("dtype,B,n_tok,d_in,d_c,packed", [("f32", 2, 1, 1, 16, True), ("f32", 1, 17, 257, 48, False),
+                                                           ("f32", 3, 15, 1030, 256, True), ("bf16", 2, 33, 130, 16, True)])
+def test_compress_with_plain_fmas(esa, dtype, B, n_tok, d_in, d_c, packed):
+    """Any shape, both inputs in one launch; d_in products of rounded unit-scale numbers added in fp32."""
+    say(f"compress {dtype} B={B} n_tok={n_tok} d_in={d_in} d_c={d_c} packed={packed}")
+    rng = np.random.default_rng(n_tok + d_in)
+    x = orc.round_to_storage(rng.standard_normal((B, n_tok, d_in)), dtype)
+    W = orc.round_to_storage(rng.standard_normal((d_in, d_c)) / np.sqrt(d_in), dtype)
+    xd, Wd = f64_to_dev(x, dtype), f64_to_dev(W, dtype)
+    Wd = esa.esa_pack_weights(Wd) if packed else Wd
+    q, k = esa.esa_compress_qk(xd, Wd, xd[:, :, :].clone(), Wd)
+    ulp = 2.0 ** -7 if dtype == "bf16" else 0.0
+    for b in range(B):
+        want = x[b] @ W
+        for got in (to_f64(q[b]), to_f64(k[b])):
+            assert np.all(np.abs(got - want) <= 1e-5 + ulp * np.abs(want))
+
+
+# a row or two of many heads, sixteen rows and one more, a step that is not one, positions on both sides of zero
+@pytest.mark.parametrize("dtype,B,n_tok,heads,d,pos0,step", [("bf16", 1, 1, 32, 128, 70000.0, 1.0), ("bf16", 40, 33, 8, 64, -16.0, 1.0),
+                                                              ("f32", 1, 17, 5, 256, 3.0, 2.5), ("bf16", 1, 19, 200, 128, 9.0, 1.0),
+                                                              ("f32", 2, 16, 1, 2, 100.0, 1.0)])
+def test_rope_rows(esa, dtype, B, n_tok, heads, d, pos0, step):
+    say(f"rope {dtype} B={B} n_tok={n_tok} heads={heads} d={d} pos0={pos0} step={step}")
+    rng = np.random.default_rng(n_tok + heads)
+    x = orc.round_to_storage(rng.standard_normal((B, n_tok, heads, d)), dtype)
+    want = np.stack([orc.round_to_storage(orc.rope(x[b], pos0 + step * np.arange(n_tok), 5e5), dtype) for b in range(B)])
+    got = to_f64(esa.esa_rope(f64_to_dev(x, dtype), pos0, step, 5e5))
+    # one rounding on each side of fp64 values that differ in their last bits
+    assert np.all(np.abs(got - want) <= np.abs(want) * (2.0 ** -7 if dtype == "bf16" else 2.0 ** -23))
+    assert np.count_nonzero(got != want) <= max(2, 1e-5 * want.size)
