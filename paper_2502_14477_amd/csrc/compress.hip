@@ -4,10 +4,9 @@
 // Kernels:
 //   * compress_mfma_packed_bf16 — bf16 storage, weights in the packed (output-major) layout written by
 //     esa_pack_weights.  Both MFMA operands then have their reduction elements contiguous in memory
-//     and are loaded straight from global memory, 16 bytes per lane, with no LDS staging.  A
-//     workgroup owns a 16-token x 16-output tile; its four (many tokens) or sixteen (few tokens:
-//     latency-bound) waves each reduce an equal share of d_in and the partial tiles are added in a
-//     fixed order (deterministic, no atomics).
+//     and reach LDS in whole cache lines without passing through registers.  A workgroup owns 16 or 32
+//     token rows x 16 outputs; its eight waves share d_in and the partial tiles are added in a fixed
+//     order (deterministic, no atomics).
 //   * compress_few_packed_bf16 — the same inputs for one to four tokens (a decode step): one workgroup per
 //     output, a dot product per token.
 //   * compress_mfma_bf16 — bf16 storage, weights as given ([d_in, d_c]); W is transposed through LDS.
@@ -171,51 +170,179 @@ __global__ __launch_bounds__(256) void compress_mfma_bf16(const bf16_t* __restri
 
 // ------------------------------------------------------------------------------------------ MFMA, packed weights
 // v_mfma_f32_16x16x32_bf16: lane l supplies A[l%16][8*(l/16) .. +7] and B[8*(l/16) .. +7][l%16] and owns
-// C[4*(l/16) .. +3][l%16].  A rows are tokens, B columns are outputs, so a lane reads eight consecutive
-// reduction elements of one token row of x and of one output row of the packed weights.
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void compress_mfma_packed_bf16(CompressJob<bf16_t> j0, CompressJob<bf16_t> j1, int64_t n_tok,
-                                                                 int col_tiles) {
-  __shared__ float red[NW][256];
-  const bool second = (int)blockIdx.y >= col_tiles;
-  const CompressJob<bf16_t> jb = pick_job(j0, j1, second);
-  const bf16_t *x = jb.x, *Wt = jb.Wt, *bias = jb.bias;
-  bf16_t* out = jb.out;
-  const int64_t d_in = jb.d_in, ldx = jb.ldx, ldo = jb.ldo, x_bs = jb.x_bs, out_bs = jb.out_bs;
-  const bf16_t* xb = x + (int64_t)blockIdx.z * x_bs;
-  bf16_t* ob = out + (int64_t)blockIdx.z * out_bs;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 15, q = lane >> 4;
-  const int64_t tok0 = (int64_t)blockIdx.x * 16;
-  const int col0 = ((int)blockIdx.y - (second ? col_tiles : 0)) * 16;
-  int64_t tok = tok0 + r;
-  tok = tok < n_tok ? tok : n_tok - 1;               // keep the address valid; the row is discarded
-  const int64_t kq = d_in / NW;                      // this wave's share of the reduction (multiple of 32)
-  const bf16_t* xp = xb + tok * ldx + wave * kq + q * 8;
-  const bf16_t* wp = Wt + (int64_t)(col0 + r) * d_in + wave * kq + q * 8;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // One pair of loads in flight per wave is enough here: sixteen waves per workgroup and two workgroups
-  // per compute unit hide the latency.  Putting eight steps' loads in flight at once changed nothing
-  // (11.8 us for the chunk's queries and keys either way), and was slower when the short job had to issue
-  // surplus loads to fit the same unrolled loop (17.5 us).
-  for (int64_t ks = 0; ks < kq; ks += 32) {
-    const bf16x8 a = *(const bf16x8*)(xp + ks);
-    const bf16x8 b = *(const bf16x8*)(wp + ks);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+// C[4*(l/16) .. +3][l%16].  A rows are tokens (of all batch entries, numbered through), B columns are outputs.
+//
+// A workgroup owns TT x 16 rows x 16 outputs of both inputs, its eight waves take every eighth piece of 64 reduction
+// elements.  What bounds it is the rate at which a compute unit takes rows in (75 GB/s from L2): each reads (16 TT + 16)
+// rows of d_in.  Read as fragments, sixteen half cache lines per instruction, a line's second half had left the first-
+// level cache before it was asked for and the 80 MB of a chunk of 512 tokens became 160 MB of L2 traffic: 11.1 us
+// (7.3 now; 1024 tokens 22.4 -> 11.0, 77 tokens 9.8 -> 6.4).  So whole lines go to LDS without passing through registers, eight 128-byte rows per instruction, RING
+// pieces ahead in a ring of the wave's own: no barrier until the waves' sums meet, in a fixed order (deterministic).
+// 16-byte slots of a row are swizzled by row / 2 (two rows share the 256 bytes that the banks cover), which keeps the
+// fragment reads free of conflicts.
+constexpr int kPWaves = 8;
+constexpr int kPiece = 64;                       // reduction elements of a piece: a cache line per row
+constexpr int kPieceRows = 16 * kPiece * 2;      // bytes of sixteen rows of a piece
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) const void global_void;
+
+template <int TT, int RING>
+constexpr int packed_lds_bytes() { return kPWaves * RING * (TT + 1) * kPieceRows; }
+
+// Every load but the LEFT newest of this wave is in LDS.
+template <int LEFT>
+__device__ __forceinline__ void loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory"); }
+
+// split_jobs: a workgroup takes one of the two inputs (column tiles numbered job by job) instead of both.
+template <int TT, int RING>
+__global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(CompressJob<bf16_t> j0, CompressJob<bf16_t> j1, int n_jobs,
+                                                                          int split_jobs, uint32_t n_tok, uint32_t n_rows,
+                                                                          int row_tiles, int col_tiles) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char ring_lds[];
+  constexpr int kLoads = 2 * TT + 2;             // load instructions of a piece
+  constexpr int kBytes = (TT + 1) * kPieceRows;  // a piece in LDS: the token rows, then the weight rows
+  static_assert((RING - 1) * kLoads < 64 && RING >= 2 && RING <= 4, "wait counter, waits below");
+  // Column tiles of one row tile on one XCD where there are enough row tiles (workgroup w runs on XCD w % 8): its rows
+  // are then fetched into one L2.  Fewer row tiles spread over the XCDs.
+  const int n_col = split_jobs ? n_jobs * col_tiles : col_tiles;
+  int rt, ct;
+  if (row_tiles >= 8) {
+    const int k = blockIdx.x >> 3;
+    rt = (blockIdx.x & 7) + 8 * (k / n_col);
+    ct = k % n_col;
+    if (rt >= row_tiles) return;
+  } else {
+    rt = blockIdx.x / n_col;
+    ct = blockIdx.x % n_col;
   }
+  const int only = split_jobs && ct >= col_tiles ? 1 : 0;
+  const int job_first = only, job_last = split_jobs ? only : n_jobs - 1;
+  const int col0 = (ct - only * col_tiles) * 16;
+  const uint32_t row0 = (uint32_t)rt * (16 * TT);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, q = lane >> 4;
+
+  // ---- pieces of this wave, input after input: wave, wave + 8, ... of each
+  const int n0 = (int)(j0.d_in / kPiece), n1 = (int)(j1.d_in / kPiece);
+  const int c0 = job_first == 0 ? (n0 - wave + kPWaves - 1) / kPWaves : 0;        // of job 0 (never negative: n0 >= 1)
+  const int c1 = job_last == 1 ? (n1 - wave + kPWaves - 1) / kPWaves : 0;
+  const int count = c0 + c1;
+
+  // ---- loads: a lane brings 16 bytes of row lane / 8 of every group of eight rows
+  const uint32_t lr = lane >> 3, slot = lane & 7;
+  uint32_t xb[2 * TT], xt[2 * TT];               // batch entry and token of this lane's rows
 #pragma unroll
-  for (int v = 0; v < 4; ++v) red[wave][(4 * q + v) * 16 + r] = acc[v];
+  for (int i = 0; i < 2 * TT; ++i) {
+    uint32_t row = row0 + 8 * i + lr;
+    row = row < n_rows ? row : n_rows - 1;       // keep the address valid; the row is discarded
+    xb[i] = n_rows == n_tok ? 0u : row / n_tok;
+    xt[i] = row - xb[i] * n_tok;
+  }
+  const char *px[2 * TT], *pw[2];
+  auto point_at = [&](bool second) {
+    const CompressJob<bf16_t> j = pick_job(j0, j1, second);
+#pragma unroll
+    for (int i = 0; i < 2 * TT; ++i)
+      px[i] = (const char*)(j.x + (int64_t)xb[i] * j.x_bs + (int64_t)xt[i] * j.ldx + wave * kPiece + (slot ^ (((8 * i + lr) >> 1) & 7)) * 8);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      pw[i] = (const char*)(j.Wt + (int64_t)(col0 + 8 * i + lr) * j.d_in + wave * kPiece + (slot ^ (((8 * i + lr) >> 1) & 7)) * 8);
+  };
+  unsigned char* mine = ring_lds + wave * (RING * kBytes);
+  int issued = 0, in_slot = 0;
+  auto issue = [&]() {                           // the next piece into the next slot of the ring
+    if (issued == 0 || issued == c0) point_at(issued >= c0);
+    unsigned char* dst = mine + in_slot * kBytes;
+#pragma unroll
+    for (int i = 0; i < 2 * TT; ++i) {
+      __builtin_amdgcn_global_load_lds((global_void*)px[i], (lds_void*)(dst + 1024 * i), 16, 0, 0);
+      px[i] += kPWaves * kPiece * 2;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      __builtin_amdgcn_global_load_lds((global_void*)pw[i], (lds_void*)(dst + TT * kPieceRows + 1024 * i), 16, 0, 0);
+      pw[i] += kPWaves * kPiece * 2;
+    }
+    ++issued;
+    in_slot = in_slot + 1 == RING ? 0 : in_slot + 1;
+  };
+#pragma unroll
+  for (int i = 0; i < RING; ++i)
+    if (i < count) issue();
+
+  // Two chains per tile (even and odd halves of the pieces) for each input.
+  f32x4 acc[2][TT][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[j][t][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint32_t frag = (uint32_t)(uintptr_t)(lds_void*)mine + r * 128 + ((q ^ ((r >> 1) & 7)) << 4);
+  int out_slot = 0;
+  for (int i = 0; i < count; ++i) {
+    const int behind = issued - i - 1;           // pieces requested after this one
+    if (behind >= 3) loads_but<RING >= 4 ? 3 * kLoads : 0>();
+    else if (behind == 2) loads_but<RING >= 3 ? 2 * kLoads : 0>();
+    else if (behind == 1) loads_but<kLoads>();
+    else loads_but<0>();
+    // The fragment reads and their wait are one block: reads that the compiler sees would wait for every load in flight.
+    const uint32_t at0 = frag + (uint32_t)(out_slot * kBytes), at1 = at0 ^ 64u;
+    bf16x8 x0[TT], x1[TT], w0, w1;
+    if constexpr (TT == 1) {
+      asm volatile(
+          "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %4 offset:2048\n\tds_read_b128 %3, %5 offset:2048\n\t"
+          "s_waitcnt lgkmcnt(0)"
+          : "=&v"(x0[0]), "=&v"(x1[0]), "=&v"(w0), "=&v"(w1)
+          : "v"(at0), "v"(at1)
+          : "memory");
+    } else {
+      asm volatile(
+          "ds_read_b128 %0, %6\n\tds_read_b128 %1, %7\n\tds_read_b128 %4, %6 offset:4096\n\tds_read_b128 %5, %7 offset:4096\n\t"
+          "ds_read_b128 %2, %6 offset:2048\n\tds_read_b128 %3, %7 offset:2048\n\ts_waitcnt lgkmcnt(0)"
+          : "=&v"(x0[0]), "=&v"(x1[0]), "=&v"(x0[TT - 1]), "=&v"(x1[TT - 1]), "=&v"(w0), "=&v"(w1)
+          : "v"(at0), "v"(at1)
+          : "memory");
+    }
+    if (issued < count) issue();                 // the slot is free: its fragments are in registers
+    out_slot = out_slot + 1 == RING ? 0 : out_slot + 1;
+    auto multiply = [&](f32x4 (&c)[TT][2]) {
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {
+        c[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0[t], w0, c[t][0], 0, 0, 0);
+        c[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1[t], w1, c[t][1], 0, 0, 0);
+      }
+    };
+    if (i < c0) multiply(acc[0]);
+    else multiply(acc[1]);
+  }
+
+  // ---- the waves' sums meet in LDS: red[input][wave][row][output]
   __syncthreads();
-  const int t = threadIdx.x;
-  if (t >= 256) return;
-  const int64_t row = tok0 + (t >> 4);
-  const int col = col0 + (t & 15);
-  if (row < n_tok) {
-    float v = red[0][t];
+  float* red = (float*)ring_lds;
+  constexpr int kTile = TT * 256;
+  static_assert(2 * kPWaves * kTile * 4 <= packed_lds_bytes<TT, RING>(), "the sums of both inputs fit the ring");
 #pragma unroll
-    for (int w = 1; w < NW; ++w) v += red[w][t];     // fixed order: deterministic
-    if (bias) v += bf16_to_f32(bias[col]);
-    ob[row * ldo + col] = f32_to_bf16(v);
+  for (int j = 0; j < 2; ++j)
+    if (j >= job_first && j <= job_last)
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[(j * kPWaves + wave) * kTile + (16 * t + 4 * q + v) * 16 + r] = acc[j][t][0][v] + acc[j][t][1][v];
+  __syncthreads();
+  for (int e = tid + job_first * kTile; e < (job_last + 1) * kTile; e += 64 * kPWaves) {
+    const int job = e / kTile, at = e % kTile;
+    const uint32_t row = row0 + (at >> 4);
+    const int col = col0 + (at & 15);
+    if (row >= n_rows) continue;
+    const CompressJob<bf16_t> j = pick_job(j0, j1, job == 1);
+    float v = red[job * kPWaves * kTile + at];
+#pragma unroll
+    for (int w = 1; w < kPWaves; ++w) v += red[(job * kPWaves + w) * kTile + at];
+    if (j.bias) v += bf16_to_f32(j.bias[col]);
+    const uint32_t b = n_rows == n_tok ? 0u : row / n_tok, t = row - b * n_tok;
+    j.out[(int64_t)b * j.out_bs + (int64_t)t * j.ldo + col] = f32_to_bf16(v);
   }
 }
 
@@ -305,6 +432,46 @@ int launch_pack_weights(const void* W, int64_t d_in, int d_c, int dtype, void* W
 
 namespace {
 
+// Inputs that the packed kernels read 16 bytes at a time.
+bool packed_ok(const void* x, int64_t d_in, int64_t ldx, const void* W, int64_t x_bs) {
+  return d_in % kPiece == 0 && ldx % 8 == 0 && x_bs % 8 == 0 && (((uintptr_t)x | (uintptr_t)W) % 16 == 0);
+}
+
+template <int TT, int RING>
+int run_packed_tiles(const CompressJob<bf16_t>& j0, const CompressJob<bf16_t>& j1, int n_jobs, int split_jobs, uint32_t n_tok,
+                     uint32_t n_rows, int d_c, hipStream_t st) {
+  constexpr int kLds = packed_lds_bytes<TT, RING>();
+  static bool lds_limit_raised = false;        // idempotent; a race only repeats the call
+  if (!lds_limit_raised) {
+    const hipError_t e = hipFuncSetAttribute((const void*)compress_mfma_packed_bf16<TT, RING>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess) ESA_FAIL(ESA_EHIP, "esa_compress: %s", hipGetErrorString(e));
+    lds_limit_raised = true;
+  }
+  const int row_tiles = (int)((n_rows + 16 * TT - 1) / (16 * TT)), col_tiles = d_c / 16;
+  const int64_t padded = row_tiles >= 8 ? (row_tiles + 7) / 8 * 8 : row_tiles;
+  const int64_t n_wg = padded * col_tiles * (split_jobs ? n_jobs : 1);
+  compress_mfma_packed_bf16<TT, RING><<<dim3((unsigned)n_wg), 64 * kPWaves, kLds, st>>>(j0, j1, n_jobs, split_jobs, n_tok, n_rows,
+                                                                                      row_tiles, col_tiles);
+  ESA_LAUNCH_CHECK("compress");
+  return ESA_OK;
+}
+
+// bf16 with packed weights, one input or two.
+int run_packed(const CompressJob<bf16_t>& j0, const CompressJob<bf16_t>& j1, int n_jobs, int64_t n_tok, int d_c, int batch, hipStream_t st) {
+  if (n_tok <= kFewTok && batch <= kFewBatch) {
+    compress_few_packed_bf16<<<dim3(d_c, n_jobs, batch), 256, 0, st>>>(j0, j1, (int)n_tok);
+    ESA_LAUNCH_CHECK("compress");
+    return ESA_OK;
+  }
+  const uint32_t n_rows = (uint32_t)(n_tok * batch);
+  const int64_t tiles = ((int64_t)n_rows + 15) / 16 * (d_c / 16);
+  // Sixteen rows per workgroup while those fit the chip at one workgroup per compute unit (each brings 32 rows of d_in
+  // in); beyond, thirty-two rows (48 rows for twice the work).  Both inputs in one workgroup, unless compute units
+  // would stay idle.
+  if (tiles > 256) return run_packed_tiles<2, 3>(j0, j1, n_jobs, 0, (uint32_t)n_tok, n_rows, d_c, st);
+  return run_packed_tiles<1, 4>(j0, j1, n_jobs, n_jobs == 2 && 2 * tiles <= 256, (uint32_t)n_tok, n_rows, d_c, st);
+}
+
 // The kernel for every storage type, shape and alignment; job 1 may repeat job 0 (n_jobs = 1).
 template <typename T>
 void run_compress_fma(const CompressJob<T>& j0, const CompressJob<T>& j1, int n_jobs, int64_t n_tok, int d_c, bool packed, int batch,
@@ -323,16 +490,8 @@ int launch_compress(const void* x, int64_t n_tok, int64_t d_in, int64_t ldx, con
   if (dtype == ESA_BF16) {
     const bool vec_ok = (ldx % 8 == 0) && (x_bs % 8 == 0) && (((uintptr_t)x | (uintptr_t)W) % 16 == 0);
     const CompressJob<bf16_t> job{(const bf16_t*)x, (const bf16_t*)W, (const bf16_t*)bias, (bf16_t*)out, d_in, ldx, ldo, x_bs, out_bs};
-    if (packed && vec_ok && d_c % 16 == 0 && d_in % 128 == 0) {
-      // few tokens: the reduction is cut sixteen ways so that every lane's loads are all in flight at once
-      const int tiles = (int)((n_tok + 15) / 16);
-      const dim3 grid((unsigned)tiles, d_c / 16, batch);
-      if (n_tok <= kFewTok && batch <= kFewBatch)
-        compress_few_packed_bf16<<<dim3(d_c, 1, batch), 256, 0, st>>>(job, job, (int)n_tok);
-      else if (d_in % 512 == 0 && n_tok <= 4096)
-        compress_mfma_packed_bf16<16><<<grid, 1024, 0, st>>>(job, job, n_tok, d_c / 16);
-      else
-        compress_mfma_packed_bf16<4><<<grid, 256, 0, st>>>(job, job, n_tok, d_c / 16);
+    if (packed && d_c % 16 == 0 && packed_ok(x, d_in, ldx, W, x_bs) && n_tok * batch < ((int64_t)1 << 31)) {
+      return run_packed(job, job, 1, n_tok, d_c, batch, st);
     } else if (!packed && vec_ok && (d_c % kMCols == 0) && (d_in % kMStep == 0)) {
       compress_mfma_bf16<<<dim3((unsigned)((n_tok + kMTok - 1) / kMTok), d_c / kMCols, batch), 256, 0, st>>>(
           (const bf16_t*)x, n_tok, d_in, ldx, (const bf16_t*)W, (const bf16_t*)bias, d_c, (bf16_t*)out, ldo, x_bs,
@@ -348,26 +507,16 @@ int launch_compress(const void* x, int64_t n_tok, int64_t d_in, int64_t ldx, con
   return ESA_OK;
 }
 
-// Two inputs in one launch when both take the same kernel (the short-reduction matrix-core kernel, or fp32); otherwise
-// one launch each.
+// Two inputs in one launch when both take the same kernel (packed bf16, or fp32); otherwise one launch each.
 int launch_compress_pair(const void* x0, int64_t d_in0, int64_t ldx0, const void* W0, const void* bias0, void* out0,
                          int64_t ldo0, int64_t x0_bs, int64_t out0_bs, const void* x1, int64_t d_in1, int64_t ldx1,
                          const void* W1, const void* bias1, void* out1, int64_t ldo1, int64_t x1_bs, int64_t out1_bs,
                          int64_t n_tok, int d_c, int w_layout, int dtype, int batch, hipStream_t st) {
-  auto fast = [&](const void* x, int64_t d_in, int64_t ldx, const void* W, int64_t x_bs) {
-    return (ldx % 8 == 0) && (x_bs % 8 == 0) && (((uintptr_t)x | (uintptr_t)W) % 16 == 0) && d_in % 512 == 0;
-  };
-  if (dtype == ESA_BF16 && w_layout == ESA_W_PACKED && d_c % 16 == 0 && n_tok <= 4096 && n_tok > 0 &&
-      fast(x0, d_in0, ldx0, W0, x0_bs) && fast(x1, d_in1, ldx1, W1, x1_bs)) {
-    const int tiles = (int)((n_tok + 15) / 16);
+  if (dtype == ESA_BF16 && w_layout == ESA_W_PACKED && d_c % 16 == 0 && n_tok * batch < ((int64_t)1 << 31) &&
+      packed_ok(x0, d_in0, ldx0, W0, x0_bs) && packed_ok(x1, d_in1, ldx1, W1, x1_bs)) {
     const CompressJob<bf16_t> j0{(const bf16_t*)x0, (const bf16_t*)W0, (const bf16_t*)bias0, (bf16_t*)out0, d_in0, ldx0, ldo0, x0_bs, out0_bs};
     const CompressJob<bf16_t> j1{(const bf16_t*)x1, (const bf16_t*)W1, (const bf16_t*)bias1, (bf16_t*)out1, d_in1, ldx1, ldo1, x1_bs, out1_bs};
-    if (n_tok <= kFewTok && batch <= kFewBatch)
-      compress_few_packed_bf16<<<dim3(d_c, 2, batch), 256, 0, st>>>(j0, j1, (int)n_tok);
-    else
-      compress_mfma_packed_bf16<16><<<dim3(tiles, 2 * (d_c / 16), batch), 1024, 0, st>>>(j0, j1, n_tok, d_c / 16);
-    ESA_LAUNCH_CHECK("compress (pair)");
-    return ESA_OK;
+    return run_packed(j0, j1, 2, n_tok, d_c, batch, st);
   }
   if (dtype == ESA_F32) {
     const CompressJob<float> j0{(const float*)x0, (const float*)W0, (const float*)bias0, (float*)out0, d_in0, ldx0, ldo0, x0_bs, out0_bs};

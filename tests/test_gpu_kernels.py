@@ -7,7 +7,7 @@ import torch
 from esa_inputs import segment_bounds
 from oracle import esa_oracle as orc
 from support import f64_to_dev, to_f64
-from test_gpu_parity import F_TOL, O_TOL, say
+from test_gpu_parity import F_TOL, O_TOL, bf16_ulp, say
 
 pytestmark = pytest.mark.gpu
 
@@ -163,6 +163,27 @@ def test_compress_with_plain_fmas(esa, dtype, B, n_tok, d_in, d_c, packed):
         want = x[b] @ W
         for got in (to_f64(q[b]), to_f64(k[b])):
             assert np.all(np.abs(got - want) <= 1e-5 + ulp * np.abs(want))
+
+
+# one piece of the reduction for one wave, pieces that do not share out evenly, row tiles of 16 and of 32 with and without
+# remainders, rows numbered through the batch, both inputs in a workgroup and one in each
+@pytest.mark.parametrize("B,n_tok,d_q,d_k,d_c", [(1, 5, 64, 64, 16), (1, 16, 192, 64, 48), (3, 11, 1088, 576, 128), (16, 1, 4096, 1024, 128),
+                                                 (1, 257, 1024, 256, 128), (1, 513, 576, 192, 128), (2, 300, 4096, 1024, 64), (1, 4097, 128, 64, 16)])
+def test_compress_packed_row_tiles(esa, B, n_tok, d_q, d_k, d_c):
+    say(f"compress_qk B={B} n_tok={n_tok} d_q={d_q} d_k={d_k} d_c={d_c}")
+    rng = np.random.default_rng(d_q + n_tok)
+    xs = [orc.round_to_storage(rng.standard_normal((B, n_tok, d)), "bf16") for d in (d_q, d_k)]
+    Ws = [orc.round_to_storage(rng.standard_normal((d, d_c)) / np.sqrt(d), "bf16") for d in (d_q, d_k)]
+    bias = orc.round_to_storage(rng.standard_normal(d_c) * 0.1, "bf16")
+    xd, Wd = [f64_to_dev(x, "bf16") for x in xs], [esa.esa_pack_weights(f64_to_dev(W, "bf16")) for W in Ws]
+    cache = torch.full((B, n_tok + 6, d_c), 3.0, dtype=torch.bfloat16, device="cuda")
+    got_q, _ = esa.esa_compress_qk(xd[0], Wd[0], xd[1], Wd[1], bias_q=f64_to_dev(bias, "bf16"), out_k=cache[:, 2:2 + n_tok])
+    assert torch.all(cache[:, :2] == 3.0) and torch.all(cache[:, 2 + n_tok:] == 3.0)
+    assert torch.equal(cache[:, 2:2 + n_tok], esa.esa_compress(xd[1], Wd[1]))        # the same arithmetic, bit for bit
+    for got, x, W, b in ((got_q, xs[0], Ws[0], bias), (cache[:, 2:2 + n_tok], xs[1], Ws[1], None)):
+        for e in range(B):
+            want = orc.compress(x[e], W, b, "bf16")
+            assert np.all(np.abs(to_f64(got[e]) - want) <= bf16_ulp(want) * 1.001)
 
 
 # a row or two of many heads, sixteen rows and one more, a step that is not one, positions on both sides of zero
