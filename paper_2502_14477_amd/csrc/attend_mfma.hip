@@ -737,11 +737,13 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.out_bs = out_bs;
   a.sel_bs_bytes = sel_bs * 2;
   a.xcd_mapping = ((batch * h_kv) % 8 == 0) ? 1 : 0;
-  // the planned number of slices is shared out in proportion to the two parts' lengths, at least one each
+  // the planned number of slices (two where one is planned) is shared out in proportion to the two parts' lengths, at
+  // least one each: never more than kMaxSlots, nor more than the workspace holds
   const SplitPlan plan = plan_splits(l_c, a.group, h_kv, batch);
   const int first_rows = l_c < a.qpt ? l_c : a.qpt;
   const int64_t keys_a = n_loc + (l_c + 1) / 2, keys_b = i_end + n_sel;
   int ns_b = keys_b > 0 ? (int)((plan.all * keys_b + (keys_a + keys_b) / 2) / (keys_a + keys_b)) : 0;
+  if (ns_b > plan.all - 1) ns_b = plan.all - 1;
   if (keys_b > 0 && ns_b < 1) ns_b = 1;
   int ns_a = plan.all - ns_b < 1 ? 1 : plan.all - ns_b;
   ns_a = clamp_splits(ns_a, n_loc + first_rows);

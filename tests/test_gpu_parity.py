@@ -650,6 +650,7 @@ def test_rope_matches_the_fp64_definition_rounded_once(esa, dtype, B, n_tok, hea
     ("bf16", 2, 8, 2, 128, 1400, 80, 16, 300, 150),     # batched
     ("bf16", 1, 8, 2, 128, 40, 32, 16, 300, 0),         # early chunk: no middle tokens, I and L touch
     ("bf16", 1, 8, 2, 128, 0, 64, 16, 300, 0),          # first chunk: nothing but C
+    ("bf16", 1, 32, 8, 128, 5000, 20, 128, 8, 2048),    # short chunk, hardly any local keys: sixteen slices in all
     ("f32", 1, 4, 2, 64, 900, 100, 8, 64, 31),          # plain kernel, one launch per part
     ("f32", 2, 4, 2, 64, 900, 7, 8, 64, 31),
     ("bf16", 1, 8, 2, 128, 2999, 1, 16, 256, 128),      # decode shape: split-key kernel, one launch per part
