@@ -19,27 +19,30 @@ constexpr int kSelectSmallThreads = 1024;
 constexpr int kSelectSmallItems = 8;                         // keys per thread
 constexpr int64_t kSelectSmallMax = kSelectSmallThreads * kSelectSmallItems;
 
-// Bin of a score, given its order-preserving key: monotone, and much finer than the key's leading bits where the
-// scores of Eq. 4 are (F = S - mu <= 0, most of it within a few powers of two): sixty-four bins per power of two for
-// negative scores from 2^-12 to 2^12, sixteen per power of two for positive ones from 2^-16 to 2^16, the bins at the
-// ends take what lies beyond.  A bin of the leading eleven key bits (four per power of two) held up to four fifths of a
-// row; the bin of the k-th score now holds well under one per cent of it (a few hundred of 128k), so that the keys inside
-// it can be listed and the exact threshold picked from the list.
-constexpr uint32_t kNegBins = 1536, kNegFirst = (127 - 12) << 6;         // magnitude >> 17 of the finest negative bin
-constexpr uint32_t kPosBins = kRadixBins - kNegBins, kPosFirst = (127 - 16) << 4;     // magnitude >> 19
+// Bin of a value, given its order-preserving key: thirty-two bins per power of two and sign from 2^-16 to 2^16, the bins at
+// the ends take what lies beyond.  The value is the score plus a shift of its row (TopkLayout::shift) that brings the bulk
+// of the row near zero, where bins are narrow: a row's scores F = S - mu lie together far below zero when one token stands
+// out (mu = 500 and a spread of 11 in a decode step on a long document), and binned as they are a bin there held several
+// thousand of 260k keys, more than the lists of topk_compact: 264 us for that step against 39 us.  Any shift gives the same
+// selection: adding a number and rounding keeps the order.
+constexpr uint32_t kNegBins = 1024, kNegFirst = (127 - 16) << 5;         // magnitude >> 18 of the finest negative bin
+constexpr uint32_t kPosBins = kRadixBins - kNegBins, kPosFirst = (127 - 16) << 5;
 __device__ __forceinline__ uint32_t score_bin(uint32_t key) {
   const bool pos = key >= 0x80000000u;
-  const int32_t unit = (int32_t)(pos ? (key - 0x80000000u) >> 19 : (0x7FFFFFFFu - key) >> 17);
+  const int32_t unit = (int32_t)(pos ? (key - 0x80000000u) >> 18 : (0x7FFFFFFFu - key) >> 18);
   int32_t b = unit - (int32_t)(pos ? kPosFirst : kNegFirst);
   const int32_t most = (int32_t)(pos ? kPosBins : kNegBins) - 1;
   b = b < 0 ? 0 : (b > most ? most : b);
   return pos ? kNegBins + (uint32_t)b : kNegBins - 1 - (uint32_t)b;
 }
-// Smallest and largest key of a bin.
+__device__ __forceinline__ uint32_t shifted_bin(float score, float shift) { return score_bin(ordered_key(score + shift)); }
+// The shift from a row maximum of S (none where that is not a number to add).
+__device__ __forceinline__ float shift_of(float mu) { return fabsf(mu) < 1e30f ? mu : 0.f; }
+// Smallest and largest key of an unshifted bin.
 __device__ __forceinline__ void bin_keys(uint32_t bin, uint32_t* lo, uint32_t* hi) {
   const bool pos = bin >= kNegBins;
   const uint32_t b = pos ? bin - kNegBins : kNegBins - 1 - bin, last = (pos ? kPosBins : kNegBins) - 1;
-  const int shift = pos ? 19 : 17;
+  const int shift = 18;
   const uint32_t first = pos ? kPosFirst : kNegFirst;
   const uint32_t m_lo = b == 0 ? 0u : (first + b) << shift;
   const uint32_t m_hi = b == last ? 0x7FFFFFFFu : ((first + b + 1) << shift) - 1;
@@ -50,7 +53,8 @@ __device__ __forceinline__ void bin_keys(uint32_t bin, uint32_t* lo, uint32_t* h
 // Workspace of one batch row of the selection, in uint32 words.
 struct TopkLayout {
   static constexpr int hist = 0;                              // [kHistReplicas][kRadixBins]
-  static constexpr int pick = kHistWords;                     // [4]: bin of the k-th score, its rank inside the bin
+  static constexpr int pick = kHistWords;                     // [3]: bin of the k-th score, keys in it, its rank inside the bin
+  static constexpr int shift = kHistWords + 3;                // fp32: written with the histogram
   static constexpr int blk = kHistWords + 4;                  // [2][nblk]: per workgroup, scores above the bin / inside it
   // then [nblk][cap]: keys inside the bin
 };

@@ -493,13 +493,14 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   if (PASS == 1) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // this wave's column maxima are in LDS
     __syncthreads();
+    const float shift = first_hist ? __uint_as_float(first_hist[(int64_t)b * first_hist_bs + TopkLayout::shift]) : 0.f;
     for (int i0 = 0; i0 < span; i0 += kThreads) {          // whole waves stay in step for hist_add
       const int i = i0 + tid;
       const int64_t m = tok_base + i;
       const bool ok = i < span && m < n;
       const uint32_t key = ok ? colmax[32 + i] : 0u;
       if (ok) score[(int64_t)b * score_bs + m] = ordered_key_to_f32(key);
-      if (first_hist) hist_add(digit_hist, ok, score_bin(key));
+      if (first_hist) hist_add(digit_hist, ok, shifted_bin(ordered_key_to_f32(key), shift));
     }
     if (first_hist) {
       __syncthreads();
@@ -535,6 +536,7 @@ __global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restri
   }
   m = wave_max(m);
   if (lane == 0) mu[(int64_t)b * mu_stride + c] = m;
+  if (hists && c == 0 && lane == 0) hists[(int64_t)b * hists_bs + TopkLayout::shift] = __float_as_uint(shift_of(m));
 }
 
 // ------------------------------------------------------------------------------------------ decode (l_c = 1)
@@ -737,7 +739,8 @@ template <int SPLIT, bool POOL, bool ONE = false>
 __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S, int64_t s_ld, int64_t s_bs, int64_t n,
                                                     const float* __restrict__ part, int n_part, int l_c, int eps_arg, int sub,
                                                     float* __restrict__ score, int64_t score_bs,
-                                                    uint32_t* __restrict__ first_hist, int64_t first_hist_bs) {
+                                                    uint32_t* __restrict__ first_hist, uint32_t* __restrict__ select_ws,
+                                                    int64_t first_hist_bs) {
   const int eps = POOL ? eps_arg : 0;
   constexpr int kPer = POOL ? 5 : 4;                        // SPLIT = 1: tokens of a thread, the last one of the pooling margin
   constexpr int kAhead = ONE ? 1 : 4;                       // queries whose scores are in flight together
@@ -830,6 +833,9 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
       __syncthreads();
     }
   }
+  // the row's shift, for this histogram and for whatever bins these scores later
+  const float shift = shift_of(ONE ? mu_one : mu[0]);
+  if (select_ws && blk == 0 && tid == 0) select_ws[(int64_t)b * first_hist_bs + TopkLayout::shift] = __float_as_uint(shift);
   auto pooled = [&](int64_t at_token, int at, float f) {    // tile[at] is token at_token
     for (int d = -eps; d <= eps; ++d)
       if (at_token + d >= 0 && at_token + d < n) f = fmaxf(f, tile[at + d]);
@@ -865,7 +871,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
         float v = f[u];
         if (POOL) v = m < n ? pooled(m, 256 * u + tid + eps, tile[256 * u + tid + eps]) : 0.f;
         if (m < n) score[(int64_t)b * score_bs + m] = v;
-        if (first_hist) hist_add(bin_hist, m < n, score_bin(ordered_key(v)));
+        if (first_hist) hist_add(bin_hist, m < n, shifted_bin(v, shift));
       }
     }
   } else {
@@ -885,7 +891,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
       const bool mine = m >= 0 && m < n && lane >= eps && lane < kTok - eps;
       if (POOL && mine) f = pooled(m, lane, f);
       if (mine) score[(int64_t)b * score_bs + m] = f;
-      if (first_hist) hist_add(bin_hist, mine, score_bin(ordered_key(f)));
+      if (first_hist) hist_add(bin_hist, mine, shifted_bin(f, shift));
     }
   }
   if (first_hist) {
@@ -906,6 +912,7 @@ __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict
   __syncthreads();
   const float* src = in + (int64_t)__builtin_amdgcn_workgroup_id_y() * in_bs;
   float* dst = out + (int64_t)__builtin_amdgcn_workgroup_id_y() * out_bs;
+  const float shift = first_hist ? __uint_as_float(first_hist[(int64_t)__builtin_amdgcn_workgroup_id_y() * first_hist_bs + TopkLayout::shift]) : 0.f;
   // whole waves stay in the loop together (hist_add is a wave-wide operation)
   for (int64_t j0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * 256 + (__builtin_amdgcn_workitem_id_x() & ~63); j0 < n; j0 += (int64_t)n_wg * 256) {
     const int64_t j = j0 + (__builtin_amdgcn_workitem_id_x() & 63);
@@ -916,7 +923,7 @@ __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict
       for (int64_t w = lo + 1; w <= hi; ++w) m = fmaxf(m, src[w]);
       dst[j] = m;
     }
-    if (first_hist) hist_add(digit_hist, j < n, score_bin(ordered_key(m)));
+    if (first_hist) hist_add(digit_hist, j < n, shifted_bin(m, shift));
   }
   if (first_hist) {
     __syncthreads();
@@ -1023,7 +1030,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                                  : (e > 0 ? score_finish<4, true> : score_finish<4, false>);
     const int sub = topk_tiles_per_wg(n, batch);
     const unsigned wgs = few ? (unsigned)((n + 1024 * (int64_t)sub - 1) / (1024 * (int64_t)sub)) : (unsigned)((n + 63 - 2 * e) / (64 - 2 * e));
-    kernel<<<dim3(wgs, batch), 256, 0, st>>>(S, s_ld, s_bs, n, part, n_part, l_c, e, sub, out, out_bs, hist, first_hist_bs);
+    kernel<<<dim3(wgs, batch), 256, 0, st>>>(S, s_ld, s_bs, n, part, n_part, l_c, e, sub, out, out_bs, hist, first_hist, first_hist_bs);
     if (hist && first_hist_done) *first_hist_done = true;
     zeroed = first_hist != nullptr;
     pool_left = eps > 0 && !narrow;

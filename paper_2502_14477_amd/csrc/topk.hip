@@ -31,7 +31,7 @@ constexpr int kTile = kThreads * kItems;        // scores per block
 constexpr int kBins = kRadixBins;
 constexpr int kCandPerTile = 64;                // list slots of a workgroup per tile of scores
 constexpr int kPeek = 8;                        // of them read ahead of their count
-constexpr uint32_t kListMax = 2048;             // keys topk_write can hold
+constexpr uint32_t kListMax = 8192;             // keys topk_write can hold
 
 struct TopkPlan {
   int64_t sub;      // tiles of kTile scores per workgroup
@@ -196,9 +196,22 @@ __device__ __forceinline__ Narrowed narrow(Narrowed r, uint32_t count, uint32_t*
   return r;
 }
 
-__global__ void topk_init(uint32_t* ws, int64_t row_words) {
+// Zeroes the histogram and takes the row's shift from its scores: minus the median of 256 of them.
+__global__ __launch_bounds__(1024) void topk_init(const float* __restrict__ score, int64_t n, int64_t score_bs, uint32_t* ws,
+                                                  int64_t row_words) {
+  __shared__ uint32_t sample[256];
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kHistWords; i += gridDim.x * blockDim.x) w[i] = 0u;
+  const int tid = threadIdx.x;
+  const uint32_t mine = ordered_key(score[(int64_t)blockIdx.y * score_bs + n * (tid & 255) / 256]);
+  for (int i = blockIdx.x * blockDim.x + tid; i < kHistWords; i += gridDim.x * blockDim.x) w[i] = 0u;
+  if (blockIdx.x != 0) return;
+  if (tid < 256) sample[tid] = mine;
+  __syncthreads();
+  if (tid >= 256) return;
+  int below = 0;
+#pragma unroll 16
+  for (int i = 0; i < 256; ++i) below += sample[i] < mine || (sample[i] == mine && i < tid) ? 1 : 0;
+  if (below == 128) w[TopkLayout::shift] = __float_as_uint(-shift_of(ordered_key_to_f32(mine)));
 }
 
 // The histogram, for callers whose scores were written by something else.
@@ -210,12 +223,13 @@ __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ 
   uint32_t key[kItems];
   bool ok[kItems];
   load_keys(row, n, first, key, ok);
+  const float shift = __uint_as_float(ws[(int64_t)blockIdx.y * row_words + TopkLayout::shift]);
   for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
   __syncthreads();
   for (int st = 0; st < sub; ++st) {
     if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
 #pragma unroll
-    for (int e = 0; e < kItems; ++e) hist_add(h, ok[e], score_bin(key[e]));
+    for (int e = 0; e < kItems; ++e) hist_add(h, ok[e], shifted_bin(ordered_key_to_f32(key[e]), shift));
   }
   __syncthreads();
   hist_flush(ws + (int64_t)blockIdx.y * row_words + TopkLayout::hist, h, blockIdx.x, threadIdx.x, kThreads);
@@ -233,6 +247,7 @@ __global__ __launch_bounds__(kThreads) void topk_compact(const float* __restrict
   uint32_t key[kItems];
   bool ok[kItems];
   load_keys(row, n, first, key, ok);
+  const float shift = __uint_as_float(w[TopkLayout::shift]);
   uint32_t c[kBins / kThreads];
   {
     static_assert(kBins / kThreads == 4, "one 16-byte load per copy");
@@ -257,8 +272,6 @@ __global__ __launch_bounds__(kThreads) void topk_compact(const float* __restrict
     w[TopkLayout::pick + 1] = p.count;
     w[TopkLayout::pick + 2] = p.k_rem;
   }
-  uint32_t lo, hi;
-  bin_keys(p.bin, &lo, &hi);
   const uint32_t cap = (uint32_t)(kCandPerTile * sub);
   uint32_t* cand = w + TopkLayout::blk + 2 * count_words(nblk) + (int64_t)blockIdx.x * cap;
   uint32_t above = 0;
@@ -266,8 +279,9 @@ __global__ __launch_bounds__(kThreads) void topk_compact(const float* __restrict
     if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
-      above += ok[e] && key[e] > hi ? 1u : 0u;
-      if (ok[e] && key[e] >= lo && key[e] <= hi) {
+      const uint32_t bin = shifted_bin(ordered_key_to_f32(key[e]), shift);
+      above += ok[e] && bin > p.bin ? 1u : 0u;
+      if (ok[e] && bin == p.bin) {
         const uint32_t at = atomicAdd(&n_cand, 1u);                    // order does not matter: they are counted
         if (at < cap) cand[at] = key[e];
       }
@@ -287,7 +301,9 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
                                                        int64_t base, int32_t* __restrict__ idx, int64_t idx_bs,
                                                        uint32_t k, int sub) {
   __shared__ uint32_t h[kBins];
-  __shared__ uint32_t list_key[kListMax], list_owner[kListMax];
+  __shared__ uint32_t list_key[kListMax];
+  __shared__ uint8_t list_before[kListMax];              // listed by a workgroup before this one
+  __shared__ uint32_t list_lo, list_hi;
   __shared__ uint32_t wave_sums[2 * kThreads / 64];
   __shared__ uint32_t result[3];
   __shared__ uint32_t n_list, too_many;
@@ -302,11 +318,14 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
   const uint32_t* n_above = w + TopkLayout::blk;
   const uint32_t* n_cand = n_above + count_words(nblk);
   const uint32_t* cand = n_cand + count_words(nblk);
+  const float shift = __uint_as_float(w[TopkLayout::shift]);
   const uint32_t bin = w[TopkLayout::pick + 0], in_bin = w[TopkLayout::pick + 1];
   Narrowed r;
   r.k_rem = w[TopkLayout::pick + 2];
   if (threadIdx.x == 0) {
     n_list = 0u;
+    list_lo = 0xFFFFFFFFu;
+    list_hi = 0u;
     too_many = in_bin > kListMax ? 1u : 0u;
   }
   __syncthreads();
@@ -326,19 +345,30 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
         for (uint32_t j = 0; j < (uint32_t)kPeek; ++j)
           if (j < cnt && at + j < kListMax) {
             list_key[at + j] = peek[j];
-            list_owner[at + j] = (uint32_t)i;
+            list_before[at + j] = i < (int)blockIdx.x;
           }
         for (uint32_t j = kPeek; j < cnt && j < cap && at + j < kListMax; ++j) {
           list_key[at + j] = cand[(int64_t)i * cap + j];
-          list_owner[at + j] = (uint32_t)i;
+          list_before[at + j] = i < (int)blockIdx.x;
         }
       }
     }
   }
-  bin_keys(bin, &r.lo, &r.hi);
   __syncthreads();
   if (!too_many) {
     const uint32_t listed = n_list;
+    uint32_t least = 0xFFFFFFFFu, most = 0u;             // the range of the bin's keys
+    for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
+      least = list_key[e] < least ? list_key[e] : least;
+      most = list_key[e] > most ? list_key[e] : most;
+    }
+    if (least <= most) {
+      atomicMin(&list_lo, least);
+      atomicMax(&list_hi, most);
+    }
+    __syncthreads();
+    r.lo = list_lo;
+    r.hi = list_hi;
     r = narrow<kThreads>(r, in_bin, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
       for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
         const uint32_t v = list_key[e];
@@ -346,12 +376,21 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
       }
     });
     for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
-      const bool before = list_owner[e] < blockIdx.x;
+      const bool before = list_before[e];
       my_gt += before && list_key[e] > r.hi ? 1u : 0u;
       my_eq += before && list_key[e] >= r.lo && list_key[e] <= r.hi ? 1u : 0u;
     }
   } else {
-    // more keys in the bin than the lists hold: the same from the scores themselves
+    // more keys in the bin than the lists hold: the same from the scores themselves.  The bin's range is found bit by bit:
+    // the most keys that lie below it, and below its end
+    r.lo = 0u;
+    uint32_t end = 0u;
+    for (uint32_t bit = 0x80000000u; bit; bit >>= 1) {
+      if (shifted_bin(ordered_key_to_f32((r.lo | bit) - 1), shift) < bin) r.lo |= bit;
+      if (shifted_bin(ordered_key_to_f32((end | bit) - 1), shift) <= bin) end |= bit;
+    }
+    const uint32_t top = shifted_bin(ordered_key_to_f32(0xFFFFFFFFu), shift);
+    r.hi = bin >= top ? 0xFFFFFFFFu : end - 1;
     r = narrow<kThreads>(r, in_bin, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
       for (int64_t i0 = threadIdx.x & ~63; i0 < n; i0 += kThreads) {     // whole waves stay in step for hist_add
         const int64_t i = i0 + (threadIdx.x & 63);
@@ -598,7 +637,7 @@ int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx
   uint32_t* w = (uint32_t*)ws;
   const dim3 grid(nblk, batch);
   if (!first_hist_ready) {     // otherwise the score call has zeroed and filled the histogram
-    topk_init<<<dim3(kHistReplicas, batch), 1024, 0, st>>>(w, row_words);
+    topk_init<<<dim3(kHistReplicas, batch), 1024, 0, st>>>(score, n, score_bs, w, row_words);
     topk_hist<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, sub);
   }
   topk_compact<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);

@@ -89,6 +89,23 @@ def test_select_topk_where_the_threshold_bin_is_crowded(esa, n, k, crowd, kind):
         assert np.array_equal(got[b], np.sort(order) + 5)
 
 
+# rows whose scores lie together far from zero (one token stands out of a decode step), of any scale, with infinities and
+# masked entries; crowds within the lists' capacity and beyond it
+@pytest.mark.parametrize("n,k,centre,spread", [(260000, 2048, -500.0, 11.0), (9001, 700, 3e4, 5.0), (100000, 8192, 0.0, 1e-6),
+                                               (8193, 8192, -1e6, 0.01), (20000, 1, 1e31, 1e28), (50000, 25000, 40.0, 1e-5)])
+def test_selection_from_scores_far_from_zero(esa, n, k, centre, spread):
+    say(f"select n={n} k={k} centre={centre} spread={spread}")
+    rng = np.random.default_rng(n + k)
+    s = (centre + spread * rng.standard_normal((2, n))).astype(np.float32)
+    s[1, rng.choice(n, n // 3, replace=False)] = np.float32(-3e38)
+    s[1, rng.choice(n, 5, replace=False)] = -np.inf
+    s[1, 17] = np.inf
+    got = esa.esa_select_topk(torch.from_numpy(s).cuda(), k, base=3).cpu().numpy()
+    for b in range(2):
+        order = np.lexsort((np.arange(n), -s[b].astype(np.float64)))[:k]
+        assert np.array_equal(got[b], np.sort(order) + 3)
+
+
 @pytest.mark.parametrize("B,l_c,n,d_c,k,eps", [(2, 1, 8192, 128, 2048, 0), (3, 1, 8192, 128, 100, 3), (1, 1, 8193, 128, 2048, 3),
                                                (1, 33, 8192, 64, 1, 16), (2, 40, 2050, 128, 2048, 17), (2, 1, 1025, 128, 1024, 1)])
 def test_scores_finished_by_the_selection_equal_the_separate_calls(esa, B, l_c, n, d_c, k, eps):
