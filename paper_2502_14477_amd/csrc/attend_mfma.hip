@@ -41,6 +41,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
@@ -55,7 +56,7 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxSlots = 16;           // partial results per row
 constexpr int kMaxSplits = 16;          // slices of the key sequence, one-call form
 constexpr int kMaxSelSplits = 8;        // two-call form: at most half as many local slices, then the selected ones
-constexpr int kMinLc = 16;          // shorter chunks go to the plain kernel
+constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.f;        // the softmax reference lags the running maximum by at most 2^8
 constexpr float kLn2 = 0.6931471805599453f;
@@ -64,8 +65,8 @@ struct AttendArgs {
   KeyView view[2];
   bf16_t* out;
   float* lse;
-  uint16_t* part_o;   // [batch][n_slot][l_c][h][D] fp16 partial outputs, un-normalised, scaled by 2^-E per row
-  float* part_ml;     // [batch][n_slot][l_c][h][2]   softmax reference (log2 domain) + E, and sum * 2^-E
+  void* part_o;       // [batch][n_slot][l_c][h][D] partial outputs, un-normalised: fp16, scaled by 2^-E per row (D = 128), or fp32
+  float* part_ml;     // [batch][n_slot][l_c][h][2]   softmax reference (log2 domain) + E, and sum * 2^-E (fp32 partials: E = 0)
   const char* k_sel;
   const char* v_sel;
   uint32_t sel_bytes;               // row stride of the gathered buffers
@@ -125,6 +126,16 @@ __device__ __forceinline__ RowRef row_ref(const KeyView& V, const int32_t* sidx,
 // of V row R is c ^ v_swizzle(R).
 template <int D> __device__ __forceinline__ uint32_t k_swizzle(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
 template <int D> __device__ __forceinline__ uint32_t v_swizzle(uint32_t row) { return D == 128 ? row & 3 : (row >> 1) & 1; }
+
+// Head size 64 keeps what it computes in fp32: a probability goes into the second product as three bf16 terms, which
+// together are its fp32 value, and the results of a slice are stored as they were accumulated.  (One term and fp16 slices,
+// as for head size 128, put the outputs 2.3e-3 from the 64-bit result where rounding them to bf16 alone makes 1.66e-3.)
+template <int D> constexpr bool kFp32Probs = D == 64;
+// Natural-log normaliser from a reference in the log2 domain and the sum of exponentials relative to it.  The fp32 form
+// adds the logarithm in its own domain, one rounding of the sum instead of two.
+template <int D> __device__ __forceinline__ float lse_of(float m, float l) {
+  return kFp32Probs<D> ? __builtin_fmaf(m, kLn2, logf(l)) : (m + __builtin_amdgcn_logf(l)) * kLn2;
+}
 
 template <int D>
 __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
@@ -337,9 +348,10 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     mx = halves_max(mx);
     // The reference m_run of the exponentials follows the running maximum lazily: it moves only when
     // a tile's maximum exceeds it by more than 2^kLazy, so probabilities stay below 2^kLazy (harmless
-    // in bf16 and fp32) and the accumulators are rescaled once or twice per row instead of per tile.
+    // in bf16 and fp32) and the accumulators are rescaled once or twice per row instead of per tile.  (Head size 64
+    // follows it at once: the sum stays small, and its logarithm as exact as the normaliser can hold.)
     const float cand = mx * a.c2;
-    const float m_new = cand > m_run + kLazy ? cand : m_run;
+    const float m_new = cand > m_run + (kFp32Probs<D> ? 0.f : kLazy) ? cand : m_run;
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
     m_run = m_new;
@@ -361,17 +373,26 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     }
     // Accumulator register v = 8*(e/4) + e%4 (+ 4*hi in the key number): fragment kp of P^T is S^T's
     // registers 8*(kp%2) .. + 7 of key tile kp/2, i.e. keys 16*kp + 4*hi + {0..3} and 16*kp + 8 + 4*hi + {0..3}.
-    bf16x8 pf[4];
+    constexpr int kTerms = kFp32Probs<D> ? 3 : 1;
+    bf16x8 pf[kTerms][4];
 #pragma unroll
-    for (int kp = 0; kp < 4; ++kp) {
-      const int mt = kp >> 1, e0 = (kp & 1) * 8;
-      uint4 w;
-      w.x = pack_bf16x2(s[mt][e0 + 0], s[mt][e0 + 1]);
-      w.y = pack_bf16x2(s[mt][e0 + 2], s[mt][e0 + 3]);
-      w.z = pack_bf16x2(s[mt][e0 + 4], s[mt][e0 + 5]);
-      w.w = pack_bf16x2(s[mt][e0 + 6], s[mt][e0 + 7]);
-      pf[kp] = *(bf16x8*)&w;
-    }
+    for (int term = 0; term < kTerms; ++term)
+#pragma unroll
+      for (int kp = 0; kp < 4; ++kp) {
+        const int mt = kp >> 1, e0 = (kp & 1) * 8;
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int v = e0 + 2 * e;
+          w[e] = pack_bf16x2(s[mt][v], s[mt][v + 1]);
+          if (term + 1 < kTerms) {          // what the term leaves, exactly
+            s[mt][v] -= __uint_as_float(w[e] << 16);
+            s[mt][v + 1] -= __uint_as_float(w[e] & 0xFFFF0000u);
+          }
+        }
+        const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
+        pf[term][kp] = *(const bf16x8*)&v;
+      }
 
     // ---- O^T += V^T P^T.  Row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot
     // c ^ v_swizzle(key), which keys 4 apart share.
@@ -383,16 +404,18 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
         const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);             // keys 16kp + 4hi + 0..3
         const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D));  // keys 16kp + 8 + 4hi + 0..3
         const i16x8 both = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
-        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[kp], o[md], 0, 0, 0);
+#pragma unroll
+        for (int term = 0; term < kTerms; ++term)
+          o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[term][kp], o[md], 0, 0, 0);
       }
-    // the V fragments of sixteen keys (2 kMD reads) are requested ahead of the kMD matrix instructions that use them
+    // the V fragments of sixteen keys (2 kMD reads) are requested ahead of the matrix instructions that use them
     __builtin_amdgcn_sched_group_barrier(0x100, 4 * kMD, 0);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, kMD, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, kTerms * kMD, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 2 * kMD, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kMD, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kTerms * kMD, 0);
   };
 
   // The first tile's loads go out before the query fragments' so that the two round trips overlap.
@@ -433,11 +456,29 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   // scale 2^-E that brings the row's largest magnitude to about 2^13 (fp16's 11-bit significand keeps the
   // rounding well below that of the bf16 output, and any magnitude bf16 inputs can produce fits); beside
   // them go m + E and l * 2^-E, so that the merge's sums of 2^(m+E-M) * (O 2^-E) and 2^(m+E-M) * (l 2^-E)
-  // are the plain log-sum-exp combination of Algorithm 1 with no trace of E.
+  // are the plain log-sum-exp combination of Algorithm 1 with no trace of E.  Head size 64 stores its slices in fp32, each
+  // lane its own row.
   const float l_tot = halves_sum(l_run);
   const bool final_out = n_slices == 1 && !a.to_slots;
   float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   float m_store = m_run, l_store = l_tot;
+  if constexpr (kFp32Probs<D>) {
+    if (!final_out) {
+      const int64_t prow = ((int64_t)(b * a.n_slot + V.slot0 + split) * a.l_c + c) * a.h + head;
+      if (c_ok) {
+        float* dst = (float*)a.part_o + prow * D + 4 * hi;
+#pragma unroll
+        for (int md = 0; md < kMD; ++md)
+#pragma unroll
+          for (int vg = 0; vg < 4; ++vg) {
+            const f32x4 w = {o[md][4 * vg], o[md][4 * vg + 1], o[md][4 * vg + 2], o[md][4 * vg + 3]};
+            *(f32x4*)(dst + 32 * md + 8 * vg) = w;
+          }
+        if (hi == 0) *(float2*)(a.part_ml + prow * 2) = make_float2(m_run, l_tot);
+      }
+      return;
+    }
+  }
   if (!final_out) {
     float amax = 0.f;
 #pragma unroll
@@ -476,7 +517,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     dst = (uint16_t*)a.out + (int64_t)b * a.out_bs;
   } else {
     const int64_t prow0 = ((int64_t)(b * a.n_slot + V.slot0 + split) * a.l_c) * a.h;
-    dst = a.part_o + prow0 * D;
+    dst = (uint16_t*)a.part_o + prow0 * D;
     if (hi == 0 && c_ok) {
       float2 ml = {m_store, l_store};
       *(float2*)(a.part_ml + (prow0 + (int64_t)c * a.h + head) * 2) = ml;
@@ -493,24 +534,25 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     }
   }
   if (final_out && a.lse && hi == 0 && c_ok)
-    a.lse[(int64_t)b * a.l_c * a.h + (int64_t)c * a.h + head] = (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2;
+    a.lse[(int64_t)b * a.l_c * a.h + (int64_t)c * a.h + head] = lse_of<D>(m_run, l_tot);
 }
 
 // Algorithm 1's merge over partial results (un-normalised outputs and sums, both relative to the slice's
 // reference m_s): weights 2^(m_s - M) with the maximum subtracted first.
-// The slots in use are [0, ns_a) and [slot_b, slot_b + ns_b) of n_slot.  D / 8 lanes per row (eight
-// head-dims, 16 bytes of fp16 partials, each), sixteen or thirty-two rows per workgroup.
+// The slots in use are [0, ns_a) and [slot_b, slot_b + ns_b) of n_slot.  Sixteen lanes per row (16 bytes of partials
+// each: eight head-dims in fp16, four in fp32), sixteen rows per workgroup.
 // NS: slots in use, a constant: with a run-time number every slot's loads stood behind a branch, which made each a round
 // trip of its own, and vector instructions were issued for sixteen slots whatever their number.  Steps with
 // four slices (16.9 MB of partials for 512 tokens): 128k chunk 105.0 -> 103.75 us, 20k prompt 2885 -> 2848, outputs the same.
 template <int D, int NS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NS > 8 ? 4 : 8)))   // registers for all loads
-void esa_attend_merge(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml, int n_slot, int ns_a,
+void esa_attend_merge(const void* __restrict__ part_o, const float* __restrict__ part_ml, int n_slot, int ns_a,
                       int slot_b, int64_t rows, bf16_t* __restrict__ out, float* __restrict__ lse, int64_t out_bs,
                       int64_t lse_bs) {
-  constexpr int kLanes = D / 8;
+  constexpr int kPer = kFp32Probs<D> ? 4 : 8;     // head-dims of a lane
+  constexpr int kLanes = D / kPer;
   const int64_t row = (int64_t)blockIdx.x * (256 / kLanes) + threadIdx.x / kLanes;
-  const int d8 = (threadIdx.x % kLanes) * 8;
+  const int dim = (threadIdx.x % kLanes) * kPer;
   const int b = blockIdx.y;
   if (row >= rows) return;
   // Every load of the row goes out before the first use (one round trip): the slices' (maximum, sum)
@@ -521,15 +563,15 @@ void esa_attend_merge(const uint16_t* __restrict__ part_o, const float* __restri
   for (int i = 0; i < NS; ++i) {
     const int64_t prow = ((int64_t)b * n_slot + (i < ns_a ? i : slot_b + i - ns_a)) * rows + row;
     ml[i] = *(const float2*)(part_ml + prow * 2);
-    po[i] = *(const uint4*)(part_o + prow * D + d8);
+    po[i] = *(const uint4*)((const char*)part_o + (prow * D + dim) * (16 / kPer));
   }
   float M = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NS; ++i) M = fmaxf(M, ml[i].x);
   float L = 0.f;
-  float acc[8];
+  float acc[kPer];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+  for (int i = 0; i < kPer; ++i) acc[i] = 0.f;
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     const float w = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - M);
@@ -537,19 +579,23 @@ void esa_attend_merge(const uint16_t* __restrict__ part_o, const float* __restri
     L += w * ml[i].y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const f16x2 p = *(const f16x2*)&u[e];
-      acc[2 * e] += w * (float)p[0];
-      acc[2 * e + 1] += w * (float)p[1];
+      if constexpr (kFp32Probs<D>) {
+        acc[e] += w * __uint_as_float(u[e]);
+      } else {
+        const f16x2 p = *(const f16x2*)&u[e];
+        acc[2 * e] += w * (float)p[0];
+        acc[2 * e + 1] += w * (float)p[1];
+      }
     }
   }
   const float inv = 1.f / L;
-  uint4 w4;
-  w4.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-  w4.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-  w4.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
-  w4.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
-  *(uint4*)(out + (int64_t)b * out_bs + row * D + d8) = w4;
-  if (lse && d8 == 0) lse[(int64_t)b * lse_bs + row] = (M + __builtin_amdgcn_logf(L)) * kLn2;
+  uint32_t w[kPer / 2];
+#pragma unroll
+  for (int e = 0; e < kPer / 2; ++e) w[e] = pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv);
+  bf16_t* dst = out + (int64_t)b * out_bs + row * D + dim;
+  if constexpr (kPer == 8) *(uint4*)dst = make_uint4(w[0], w[1], w[2], w[3]);
+  else *(uint2*)dst = make_uint2(w[0], w[1]);
+  if (lse && dim == 0) lse[(int64_t)b * lse_bs + row] = lse_of<D>(M, L);
 }
 
 // Row tiles: as few as hold the chunk at 256 rows each, the tokens shared out evenly in units of a wave's 32 rows.
@@ -577,7 +623,7 @@ void launch_merge(const AttendArgs& a, int ns_a, int slot_b, int ns_b, hipStream
     return;
   }
   const int64_t rows = (int64_t)a.l_c * a.h;
-  constexpr int kRowsPerWg = 256 / (D / 8);
+  constexpr int kRowsPerWg = 256 / (D / (kFp32Probs<D> ? 4 : 8));
   esa_attend_merge<D, NS><<<dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg), a.batch), 256, 0, st>>>(
       a.part_o, a.part_ml, a.n_slot, ns_a, slot_b, rows, a.out, a.lse, a.out_bs, rows);
 }
@@ -606,9 +652,10 @@ SplitPlan plan_splits(int l_c, int group, int h_kv, int batch) {
   return p;
 }
 
+size_t part_o_bytes(size_t rows, int d) { return align_up(rows * d * (d == 64 ? sizeof(float) : sizeof(uint16_t)), 256); }
 size_t slots_bytes(int n_slot, int l_c, int h, int d, int batch) {
   const size_t rows = (size_t)batch * n_slot * l_c * h;
-  return align_up(rows * d * sizeof(uint16_t), 256) + align_up(rows * 2 * sizeof(float), 256);
+  return part_o_bytes(rows, d) + align_up(rows * 2 * sizeof(float), 256);
 }
 
 }  // namespace
@@ -672,8 +719,8 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
     const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
     if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend: workspace needs %zu bytes", need);
     const size_t rows = (size_t)batch * n_slot * l_c * h;
-    a.part_o = (uint16_t*)ws;
-    a.part_ml = (float*)((char*)ws + align_up(rows * d * sizeof(uint16_t), 256));
+    a.part_o = ws;
+    a.part_ml = (float*)((char*)ws + part_o_bytes(rows, d));
   }
   a.n_slot = n_slot;
   const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
@@ -755,8 +802,8 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   if (n_slot > 1) {
     if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend: workspace needs %zu bytes", need);
     const size_t rows = (size_t)batch * n_slot * l_c * h;
-    a.part_o = (uint16_t*)ws;
-    a.part_ml = (float*)((char*)ws + align_up(rows * d * sizeof(uint16_t), 256));
+    a.part_o = ws;
+    a.part_ml = (float*)((char*)ws + part_o_bytes(rows, d));
   }
   a.n_slot = n_slot;
   a.to_slots = 0;

@@ -45,7 +45,8 @@ constexpr float kLn2 = 0.6931471805599453f;
 // Exponentials of the softmax: base 2 on the hardware instruction for bf16 storage, full-precision base e for fp32.
 template <typename T> __device__ __forceinline__ float exp_of(float x) { return __builtin_amdgcn_exp2f(x); }
 template <> __device__ __forceinline__ float exp_of<float>(float x) { return expf(x); }
-template <typename T> __device__ __forceinline__ float lse_of(float m, float l) { return (m + __builtin_amdgcn_logf(l)) * kLn2; }
+// (the normaliser of the base-2 form adds the logarithm in its own domain: one rounding of the sum instead of two)
+template <typename T> __device__ __forceinline__ float lse_of(float m, float l) { return __builtin_fmaf(m, kLn2, logf(l)); }
 template <> __device__ __forceinline__ float lse_of<float>(float m, float l) { return m + logf(l); }
 
 __device__ __forceinline__ float halves_max(float v) {
@@ -245,9 +246,10 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
       const bool more = t + kWaves < tile_end;
       const uint32_t j0 = t * kKT;
       wait_loads<kLoads>();                                                 // the keys; the values may still be on their way
-      f32x16 s;
+      // bf16: two chains (even and odd fragments), each of half the sum: a logit is rounded at its full size once
+      f32x16 s, s_odd;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) s[v] = 0.f;
+      for (int v = 0; v < 16; ++v) s[v] = s_odd[v] = 0.f;
       u32x4 kf[kKS];
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) kf[ks] = lds_read16(k_at ^ (ks << 5));
@@ -263,7 +265,8 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
 #pragma unroll
         for (int ks = g4; ks < g4 + 4; ++ks) {
           if constexpr (kBf16) {
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, qf[ks]), s, 0, 0, 0);
+            f32x16& chain = ks & 1 ? s_odd : s;
+            chain = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, qf[ks]), chain, 0, 0, 0);
           } else {
             const f32x4 k4 = __builtin_bit_cast(f32x4, kf[ks]), q4 = __builtin_bit_cast(f32x4, qf[ks]);
 #pragma unroll
@@ -271,6 +274,7 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
           }
         }
       }
+      if constexpr (kBf16) s += s_odd;
       __builtin_amdgcn_sched_barrier(0);
       if (more) {
         spread(place_of(t + kWaves, next), mine);
@@ -320,19 +324,23 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
           constexpr int kNewer = kp == 0 ? 2 * kMD : 0;
 #pragma unroll
           for (int md = 0; md < kMD; md += 2) arrived4<kNewer>(vf[kp][md][0], vf[kp][md][1], vf[kp][md + 1][0], vf[kp][md + 1][1]);
-          // A probability goes in as its bf16 value and, in a second instruction, the bf16 value of what that leaves:
-          // sixteen significant bits, at a price in matrix instructions that a kernel waiting for memory does not notice.
-          bf16x8 pf, rest;
+          // A probability goes in as three bf16 terms, each the rounded value of what the ones before it leave: together
+          // they are its fp32 value, at a price in matrix instructions that a kernel waiting for memory does not notice.
+          // (Two terms, sixteen bits, left ten times as many outputs off the nearest bf16 number: 2.3e-3 of them.)
+          bf16x8 pf, rest, last;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             pf[e] = (__bf16)s[8 * kp + e];
-            rest[e] = (__bf16)(s[8 * kp + e] - (float)pf[e]);
+            const float left = s[8 * kp + e] - (float)pf[e];
+            rest[e] = (__bf16)left;
+            last[e] = (__bf16)(left - (float)rest[e]);
           }
 #pragma unroll
           for (int md = 0; md < kMD; ++md) {
             const i16x8 both = __builtin_shufflevector(vf[kp][md][0], vf[kp][md][1], 0, 1, 2, 3, 4, 5, 6, 7);
             o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf, o[md], 0, 0, 0);
             o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), rest, o[md], 0, 0, 0);
+            o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), last, o[md], 0, 0, 0);
           }
         };
         request(std::integral_constant<int, 0>());
