@@ -152,7 +152,8 @@ def esa_compress(x: torch.Tensor, W, bias: Optional[torch.Tensor] = None,
     PackedWeights.  `out` may be a row-strided view (e.g. rows t0.. of the compressed-key cache)."""
     if isinstance(W, PackedWeights):
         return _native.compress(x, W.data, ESA_W_PACKED, W.d_in, W.d_c, bias, out)
-    return _native.compress(x, W, ESA_W_ROWMAJOR, W.shape[0], W.shape[1], bias, out)
+    d_in, d_c = W.shape
+    return _native.compress(x, W, ESA_W_ROWMAJOR, d_in, d_c, bias, out)
 
 
 def esa_compress_qk(xq: torch.Tensor, Wq, xk: torch.Tensor, Wk, bias_q: Optional[torch.Tensor] = None,
@@ -165,8 +166,9 @@ def esa_compress_qk(xq: torch.Tensor, Wq, xk: torch.Tensor, Wk, bias_q: Optional
         assert Wq.d_c == Wk.d_c
         return _native.compress_qk(xq, Wq.data, Wq.d_in, xk, Wk.data, Wk.d_in, ESA_W_PACKED, Wq.d_c, bias_q, bias_k, out_q, out_k)
     assert not isinstance(Wk, PackedWeights), "both weight matrices in the same layout"
-    assert Wq.shape[1] == Wk.shape[1]
-    return _native.compress_qk(xq, Wq, Wq.shape[0], xk, Wk, Wk.shape[0], ESA_W_ROWMAJOR, Wq.shape[1], bias_q, bias_k, out_q, out_k)
+    (dq, dc), (dk, dck) = Wq.shape, Wk.shape
+    assert dc == dck
+    return _native.compress_qk(xq, Wq, dq, xk, Wk, dk, ESA_W_ROWMAJOR, dc, bias_q, bias_k, out_q, out_k)
 
 
 def esa_score(qc: torch.Tensor, kc_cache: torch.Tensor, m_lo: int, m_hi: int, eps: int = 0,

@@ -240,7 +240,7 @@ ESA_ENTRY(compress, 7) {
   const int layout = int32_of(a[2]);
   const int64_t d_in = int_of(a[3]), d_c = int_of(a[4]);
   const at::Tensor *bias = tensor_or_none(a[5]), *out = tensor_or_none(a[6]);
-  ESA_ASSERT(W.is_contiguous());
+  ESA_ASSERT(W.is_contiguous() && W.scalar_type() == x.scalar_type());
   const int dt = dtype_of(x);
   const CompressIo io = compress_io(x, d_in, d_c, out);
   void *st = stream(), *wp = ptr(W), *bp = ptr(bias);
@@ -257,7 +257,7 @@ ESA_ENTRY(compress_qk, 12) {
   const int64_t dq = int_of(a[2]), dk = int_of(a[5]), d_c = int_of(a[7]);
   const int layout = int32_of(a[6]);
   const at::Tensor *bq = tensor_or_none(a[8]), *bk = tensor_or_none(a[9]), *oq = tensor_or_none(a[10]), *ok = tensor_or_none(a[11]);
-  ESA_ASSERT(Wq.is_contiguous() && Wk.is_contiguous());
+  ESA_ASSERT(Wq.is_contiguous() && Wk.is_contiguous() && Wq.scalar_type() == xq.scalar_type() && Wk.scalar_type() == xk.scalar_type());
   const CompressIo q = compress_io(xq, dq, d_c, oq), k = compress_io(xk, dk, d_c, ok);
   ESA_ASSERT(q.x.B == k.x.B && q.x.n[0] == k.x.n[0] && xq.scalar_type() == xk.scalar_type());
   const int dt = dtype_of(xq);
@@ -354,10 +354,10 @@ ESA_ENTRY(select_topk_static, 4) {
   return wrap(s.batched ? out->unsqueeze(0) : out->select(0, 0));
 }
 
-// The key and value caches: [B?, S, h_kv, d], heads contiguous, same strides.
+// The key and value caches: [B?, S, h_kv, d], heads contiguous, same strides and type.
 View caches_of(const at::Tensor& k, const at::Tensor& v, bool same_shape) {
   const View kv = view_of(k, 3), vv = view_of(v, 3);
-  ESA_ASSERT(kv.s[2] == 1 && kv.s[1] == kv.n[2]);
+  ESA_ASSERT(kv.s[2] == 1 && kv.s[1] == kv.n[2] && v.scalar_type() == k.scalar_type());
   ESA_ASSERT(vv.s[0] == kv.s[0] && vv.s[1] == kv.s[1] && vv.s[2] == kv.s[2] && vv.bs == kv.bs);
   ESA_ASSERT(!same_shape || (vv.B == kv.B && vv.n[0] == kv.n[0] && vv.n[1] == kv.n[1] && vv.n[2] == kv.n[2]));
   return kv;
@@ -381,7 +381,7 @@ ESA_ENTRY(score_select_gather, 8) {
   if (kcache) {
     ESA_ASSERT(vcache != nullptr);
     c = caches_of(*kcache, *vcache, true);
-    ESA_ASSERT(c.B == q.B && kcache->is_cuda());
+    ESA_ASSERT(c.B == q.B && kcache->scalar_type() == qc.scalar_type() && kcache->is_cuda());
     ks = new_tensor(Shape(q.batched, q.B, {k_eff, c.n[1], c.n[2]}), kcache->scalar_type(), dev);
     vs = new_tensor(Shape(q.batched, q.B, {k_eff, c.n[1], c.n[2]}), kcache->scalar_type(), dev);
   }
@@ -446,7 +446,11 @@ AttendIo attend_io(PyObject* q_obj, PyObject* k_obj, PyObject* v_obj, int64_t t0
   io.h = (int)io.q.n[1];
   io.d = (int)io.q.n[2];
   io.h_kv = (int)io.c.n[1];
-  if (io.c.n[0] < t0 + io.l_c) fail(PyExc_AssertionError, "the cache must already hold the current tokens");
+  // what the kernels address with the queries' sizes: both caches have their batch, head size and type
+  ESA_ASSERT(io.c.n[2] == io.q.n[2] && io.c.B == io.q.B && k.scalar_type() == q.scalar_type());
+  const View vv = view_of(v, 3);
+  ESA_ASSERT(vv.B == io.c.B && vv.n[1] == io.c.n[1] && vv.n[2] == io.c.n[2]);
+  if (io.c.n[0] < t0 + io.l_c || vv.n[0] < t0 + io.l_c) fail(PyExc_AssertionError, "the cache must already hold the current tokens");
   io.dt = dtype_of(q);
   io.scale = scale == Py_None ? (float)(1.0 / std::sqrt((double)io.d)) : (float)float_of(scale);
   if (want_lse) {       // null: the call has no outputs
@@ -471,7 +475,7 @@ struct Gathered {
   int n_sel = 0;
   int64_t bs = 0;
 };
-Gathered gathered_of(PyObject* k_obj, PyObject* v_obj) {
+Gathered gathered_of(PyObject* k_obj, PyObject* v_obj, const AttendIo& io) {
   Gathered g;
   const at::Tensor* k = tensor_or_none(k_obj);
   if (!k || k->numel() == 0) return g;
@@ -479,6 +483,7 @@ Gathered gathered_of(PyObject* k_obj, PyObject* v_obj) {
   const View kv = view_of(*k, 3), vv = view_of(v, 3);
   ESA_ASSERT(k->is_contiguous() && v.is_contiguous());
   ESA_ASSERT(kv.B == vv.B && kv.n[0] == vv.n[0] && kv.n[1] == vv.n[1] && kv.n[2] == vv.n[2]);
+  ESA_ASSERT(kv.B == io.B && kv.n[1] == io.h_kv && kv.n[2] == io.d && dtype_of(*k) == io.dt && dtype_of(v) == io.dt);
   g.k = ptr(*k);
   g.v = ptr(v);
   g.n_sel = (int)kv.n[0];
@@ -515,7 +520,7 @@ ESA_ENTRY(attend_indexed, 9) {
 ESA_ENTRY(attend_reencoded, 12) {
   const int64_t t0 = int_of(a[3]), l_i = int_of(a[4]), l_l = int_of(a[5]);
   AttendIo io = attend_io(a[0], a[1], a[2], t0, a[10], a[11]);
-  const Gathered g = gathered_of(a[6], a[7]);
+  const Gathered g = gathered_of(a[6], a[7], io);
   const double w = float_of(a[8]), base = float_of(a[9]);
   at::Tensor ws = workspace(esa_attend_reencoded_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B, l_l), io.out.device(), kWsAttend);
   void *st = stream(), *wp = ptr(ws), *op = ptr(io.out);
@@ -531,7 +536,7 @@ ESA_ENTRY(attend_reencoded, 12) {
 ESA_ENTRY(attend, 11) {
   const int64_t t0 = int_of(a[3]), l_i = int_of(a[4]), l_l = int_of(a[5]);
   AttendIo io = attend_io(a[0], a[1], a[2], t0, a[8], a[9]);
-  const Gathered g = gathered_of(a[6], a[7]);
+  const Gathered g = gathered_of(a[6], a[7], io);
   const bool one_call = a[10] == Py_None;
   const int split = one_call ? 0 : int32_of(a[10]);
   at::Tensor ws = workspace(esa_attend_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B), io.out.device(), kWsAttend);
