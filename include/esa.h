@@ -235,9 +235,10 @@ ESA_API int esa_attend(const void* q, int l_c, int h, int h_kv, int d,
  *                      partial results in `workspace`
  *   esa_attend_finish  arguments exactly as esa_attend, same `workspace`; writes out / lse
  * Both calls must be given identical sizes, strides, split and workspace.  With ESA_SPLIT_I_EARLY,
- * shapes outside the matrix-core kernel (fp32, head sizes other than 128, chunks shorter than 16
+ * shapes outside the matrix-core kernel (fp32, head sizes other than 64 and 128, chunks shorter than 16
  * tokens) are served whole by esa_attend_finish and esa_attend_local enqueues nothing; with
- * ESA_SPLIT_ALGORITHM1 they run the plain kernel once per part.
+ * ESA_SPLIT_ALGORITHM1 they, and head size 64, run the plain kernel once per part (bf16, head size 128 and fewer than
+ * 16 tokens: the split-key kernel).  bf16 rows of head size 128 must then be 16-byte aligned (ESA_EINVAL otherwise).
  */
 #define ESA_SPLIT_I_EARLY 0
 #define ESA_SPLIT_ALGORITHM1 1

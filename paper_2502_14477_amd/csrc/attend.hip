@@ -116,6 +116,11 @@ bool attend_aligned(const void* q, const void* k_cache, const void* v_cache, con
   return p % 16 == 0 && s % 16 == 0;
 }
 
+// Row numbers in 31 bits, row strides (bytes) in 32: what the tiled kernels keep.
+bool attend_in_range(int64_t rows, int64_t tok_stride, int64_t esz) {
+  return rows <= (int64_t)INT32_MAX && tok_stride * esz < ((int64_t)1 << 32);
+}
+
 constexpr int64_t kTwoCallMaxLocal = 65536;      // longer local parts of a two-call attention go to the plain kernel
 
 size_t generic_parts_bytes(int l_c, int h, int d, int batch) {
@@ -132,30 +137,34 @@ size_t attend_indexed_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype
 
 size_t attend_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int batch) {
   if (l_c <= 0 || h <= 0 || h_kv <= 0 || d <= 0 || batch <= 0) return 256;
-  if (attend_mfma_supported(l_c, h, h_kv, d, dtype)) return attend_mfma_workspace_bytes(l_c, h, h_kv, d, batch);
-  // shapes outside the matrix-core kernel: room for the two parts of a two-call attention
+  const bool mfma = attend_mfma_supported(l_c, h, h_kv, d, dtype);
+  if (mfma && d == 128) return attend_mfma_workspace_bytes(l_c, h, h_kv, d, batch);
+  // shapes that the plain kernel may serve as well: room for the two parts of a two-call attention
   const size_t parts = generic_parts_bytes(l_c, h, d, batch);
-  if (attend_split_supported(l_c, h, h_kv, d, dtype, batch)) {
-    const size_t split = attend_split_workspace_bytes(l_c, h, h_kv, d, dtype, batch);
-    return split > parts ? split : parts;
-  }
-  return parts;
+  const size_t tiled = mfma ? attend_mfma_workspace_bytes(l_c, h, h_kv, d, batch)
+                       : attend_split_supported(l_c, h, h_kv, d, dtype, batch) ? attend_split_workspace_bytes(l_c, h, h_kv, d, dtype, batch)
+                                                                               : 0;
+  return tiled > parts ? tiled : parts;
 }
 
 int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, int d, const void* k_cache, const void* v_cache,
                   int64_t tok_stride, int64_t t0, int64_t l_i, int64_t l_l, const void* k_sel, const void* v_sel,
                   int n_sel, const int32_t* sel_idx, int64_t idx_bs, float scale, void* out, float* lse, int dtype,
                   int batch, int64_t q_bs, int64_t cache_bs, int64_t sel_bs, int64_t out_bs, void* ws, size_t ws_bytes,
-                  hipStream_t st) {
+                  hipStream_t st, bool plain) {
   const Segments sg = segments(t0, l_i, l_l);
   if (n_sel == 0) sel_idx = nullptr;
   const int64_t n_fixed = sg.i_end + n_sel + (t0 - sg.l_start);
-  const bool mfma_shape = attend_mfma_supported(l_c, h, h_kv, d, dtype);
   const int64_t esz = (dtype == ESA_F32) ? 4 : 2;
+  const bool two_parts = part != kAttendAll && split == ESA_SPLIT_ALGORITHM1;
+  const bool in_range = !plain && attend_in_range(t0 + l_c, tok_stride, esz);
+  // The two calls of a separately encoded attention must take the same kernel: no fallback between them, so nothing that
+  // only one of them knows (the number of selected tokens, its pointers' alignment) may decide.  Rows of head size 128
+  // are required to be aligned and take the tiled kernels; every other head size takes any alignment, on the plain kernel.
+  const bool mfma_shape = attend_mfma_supported(l_c, h, h_kv, d, dtype) && (d == 128 || (in_range && !two_parts));
   const bool mfma_aligned =
       attend_aligned(q, k_cache, v_cache, k_sel, v_sel, out, tok_stride, q_bs, cache_bs, sel_bs, out_bs, esz);
-  // The two calls of a separately encoded attention must take the same kernel: no fallback between them.
-  if (mfma_shape && !mfma_aligned && part != kAttendAll && split == ESA_SPLIT_ALGORITHM1)
+  if (mfma_shape && !mfma_aligned && two_parts)
     ESA_FAIL(ESA_EINVAL, "esa_attend (two calls, Algorithm 1 grouping): pointers and strides must be 16-byte aligned");
   if (mfma_shape && mfma_aligned) {
     // an index list is followed by the kernel itself (index-driven tile loads): no gathered copy
@@ -166,13 +175,9 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
   // Every other shape.  With the initial tokens in the early part the finishing (or the only) call
   // computes everything; Algorithm 1's grouping (separately encoded parts) runs the plain kernel once
   // per part and merges.
-  const bool two_parts = part != kAttendAll && split == ESA_SPLIT_ALGORITHM1;
   if (part == kAttendLocal && !two_parts) return ESA_OK;
-  // Few current tokens, or fp32.  (The kernel keeps row numbers in 31 bits and row strides in 32.)  The two calls of a
-  // separately encoded attention must agree on the kernel, so nothing that only one of them knows (the number of selected
-  // tokens, its pointers' alignment) may decide: they take it for bf16 rows of head size 128 and insist on alignment.
-  const bool split_shape = attend_split_supported(l_c, h, h_kv, d, dtype, batch) && t0 + l_c <= (int64_t)INT32_MAX &&
-                           tok_stride * esz < ((int64_t)1 << 32);
+  // Few current tokens, or fp32.
+  const bool split_shape = attend_split_supported(l_c, h, h_kv, d, dtype, batch) && in_range;
   const bool split_two = dtype == ESA_BF16 && d == 128 && 8 % (h / h_kv) == 0 && t0 - sg.l_start + l_c <= kTwoCallMaxLocal;
   if (split_shape && (two_parts ? split_two : mfma_aligned)) {
     if (!mfma_aligned)
@@ -283,11 +288,12 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   const int64_t q_row = (int64_t)h * d, kv_row = (int64_t)h_kv * d;
   const int64_t qw_bs = (int64_t)l_c * q_row, kvw_bs = rows * kv_row;
   const bool ok16 = attend_aligned(q_loc, k_cache, v_cache, k_sel, v_sel, out, tok_stride, qw_bs, cache_bs, sel_bs, out_bs, (int64_t)esz);
-  const bool mfma = attend_mfma_supported(l_c, h, h_kv, d, dtype);
-  const bool split = !mfma && attend_split_supported(l_c, h, h_kv, d, dtype, batch) && ok16 &&
-                     t0 + l_c <= (int64_t)INT32_MAX && tok_stride * (int64_t)esz < ((int64_t)1 << 32);
-  if (mfma && !ok16)
+  const bool in_range = attend_in_range(t0 + l_c, tok_stride, (int64_t)esz);
+  const bool mfma_shape = attend_mfma_supported(l_c, h, h_kv, d, dtype);
+  if (mfma_shape && d == 128 && !ok16)
     ESA_FAIL(ESA_EINVAL, "esa_attend_reencoded: pointers and strides must be 16-byte aligned for this shape");
+  const bool mfma = mfma_shape && (d == 128 || (ok16 && in_range));
+  const bool split = !mfma && attend_split_supported(l_c, h, h_kv, d, dtype, batch) && ok16 && in_range;
 
   RopeJob jobs[4];
   jobs[0] = RopeJob{q, q_loc, l_c, q_row, q_row, q_bs, qw_bs, (double)n_loc, 1.0, h, 1};     // local queries, in order
@@ -311,11 +317,11 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
     return launch_attend_split(call, a, &b, st);
   }
   rc = launch_attend(kAttendLocal, ESA_SPLIT_ALGORITHM1, q_loc, l_c, h, h_kv, d, k_loc, v_loc, kv_row, n_loc, 0, n_loc,
-                     nullptr, nullptr, 0, nullptr, 0, scale, nullptr, nullptr, dtype, batch, qw_bs, kvw_bs, 0, 0, ws, own, st);
+                     nullptr, nullptr, 0, nullptr, 0, scale, nullptr, nullptr, dtype, batch, qw_bs, kvw_bs, 0, 0, ws, own, st, !in_range);
   if (rc != ESA_OK) return rc;
   return launch_attend(kAttendFinish, ESA_SPLIT_ALGORITHM1, q_glob, l_c, h, h_kv, d, k_cache, v_cache, tok_stride, t0, l_i,
                        l_l, k_sel, v_sel, n_sel, nullptr, 0, scale, out, lse, dtype, batch, qw_bs, cache_bs, sel_bs, out_bs,
-                       ws, own, st);
+                       ws, own, st, !in_range);
 }
 
 }  // namespace esa

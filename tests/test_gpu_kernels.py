@@ -50,6 +50,37 @@ def test_matrix_core_attention_head_sizes_and_row_tiles(esa, B, H, H_kv, d, t0, 
         assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL["bf16"]
 
 
+# Rows and pointers that are not 16-byte aligned: every head size but 128 takes them, in one call, in two and re-encoded
+@pytest.mark.parametrize("dtype,d,l_C,pad,shift", [("bf16", 64, 40, 4, 0), ("bf16", 64, 16, 0, 1), ("bf16", 64, 3, 4, 1), ("f32", 32, 20, 1, 0)])
+def test_head_sizes_that_take_unaligned_rows(esa, dtype, d, l_C, pad, shift):
+    say(f"unaligned rows {dtype} d={d} l_C={l_C} pad={pad} shift={shift}")
+    H, H_kv, t0, l_I, l_L, n_sel = 8, 2, 700, 16, 130, 90
+    q, K, V, sel = attend_inputs(d + l_C, dtype, 1, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    q, K, V, sel = q[0], K[0], V[0], sel[0]
+
+    def rows(x):                    # token rows `pad` elements apart, the first one `shift` elements into its buffer
+        x = f64_to_dev(x, dtype)
+        n, width = x.shape[0], x.shape[1] * d
+        buf = torch.zeros(n * (width + pad) + shift, dtype=x.dtype, device="cuda")
+        view = buf[shift:].as_strided((n, x.shape[1], d), (width + pad, d, 1), shift)
+        view.copy_(x)
+        return view
+
+    qd, Kd, Vd, idx = f64_to_dev(q, dtype), rows(K), rows(V), torch.from_numpy(sel).cuda()
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx)
+    want, _ = orc.attend(q, K, V, t0, l_I, l_L, sel, 1.0 / np.sqrt(d))
+    got = [esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx), esa.esa_attend(qd, Kd, Vd, t0, l_I, l_L, ks, vs)]
+    for split in (esa.ESA_SPLIT_I_EARLY, esa.ESA_SPLIT_ALGORITHM1):
+        for k_cache, v_cache, k_sel in ((Kd, Vd, ks), (f64_to_dev(K, dtype), f64_to_dev(V, dtype), ks), (Kd, Vd, rows(to_f64(ks)) if pad == 0 else ks)):
+            esa.esa_attend_local(qd, k_cache, v_cache, t0, l_I, l_L, split=split)
+            got.append(esa.esa_attend_finish(qd, k_cache, v_cache, t0, l_I, l_L, k_sel, vs, split=split))
+    for O in got:
+        assert np.max(np.abs(to_f64(O) - want)) <= O_TOL[dtype]
+    want, _ = orc.attend_reencoded(q, K, V, t0, l_I, l_L, sel, 1.0 / np.sqrt(d), 4096.0, 5e5)
+    O = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5)
+    assert np.max(np.abs(to_f64(O) - want)) <= O_TOL[dtype]
+
+
 # Probabilities and partial sums in fp32: a few tokens, and head size 64 at any length.  Outputs are then off by about
 # 2^-22 of their rms, so that one in a thousand or two is not the bf16 number nearest to the exact result (an output's
 # last place is 2^-8 of itself or less; small outputs count most).  Probabilities of 16 bits, 2^-17.8 of the rms, leave
