@@ -116,8 +116,9 @@ struct ScoreTail {
   int n_part, eps;
 };
 constexpr int kTailMaxEps = 16;     // wider windows keep their own pass
-// first_hist: null, or [batch] rows (stride first_hist_bs words) holding the histogram of the selection that
-// follows; the kernels zero it and fill it with the scores they write when they can, and *first_hist_done is set.
+// first_hist: null, or [batch] rows (stride first_hist_bs words) holding the three digit histograms of the selection that
+// follows; the kernels zero all three and fill the first with the leading digits of the scores they write when they can,
+// and *first_hist_done is set.
 // tail: null, or the selection that follows is launch_select_small: the scores are left as *tail says.
 int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
                  float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs,
@@ -130,7 +131,8 @@ int launch_select_small(const ScoreTail& tail, float* score, int64_t score_bs, i
                         int64_t idx_bs, int batch, hipStream_t st);
 
 size_t topk_workspace_bytes(int64_t n, int k, int batch);
-// first_hist_ready: the workspace's histogram already holds the scores (left there by launch_score).
+// first_hist_ready: the workspace's histograms are zeroed and the first one already holds the scores' leading digits (left
+// there by launch_score).
 int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx, int batch, int64_t score_bs,
                 int64_t idx_bs, void* ws, size_t ws_bytes, hipStream_t st, bool first_hist_ready = false);
 

@@ -1,30 +1,29 @@
-// First-level histogram of the selection (Eq. 2), shared by the selection kernels and by the
-// score kernels that build it while the scores are still on chip.
+// Histograms of the selection (Eq. 2): the first digit's, shared by the selection kernels of long rows and by the score
+// kernels that build it while the scores are still on chip, and the finer bins of the rows that one workgroup takes.
 #pragma once
 #include "esa_common.h"
 
 namespace esa {
 
-constexpr int kRadixBins = 2048;
+constexpr int kRadixBins = 2048;        // 11-bit digits (the last pass uses 10 bits of them)
 // Copies of the global histogram; workgroup w adds into copy w % kHistReplicas and a reader sums the copies.
 // Adds to one address are served one after the other (about 30 ns each, measured), and where most scores share
-// a bin every workgroup adds to the same few: 250 workgroups on one copy cost 5 us, on four copies 0.4 us.
+// a digit every workgroup adds to the same few: 250 workgroups on one copy cost 5 us, on four copies 0.4 us.
 constexpr int kHistReplicas = 4;
-constexpr int kHistWords = kHistReplicas * kRadixBins;       // of one batch row
+constexpr int kHistWords = 3 * kHistReplicas * kRadixBins;   // the three passes' histograms of one batch row
 
 // Rows up to this long are selected from by one workgroup that keeps the row's keys in registers (no global
-// histogram).  Measured: 4.8 / 5.5 / 7.2 / 13.2 us for up to 2 / 4 / 8 / 16 thousand scores (its LDS histogram is one
-// compute unit's work), the two passes of longer rows 8 us and a launch boundary at any of these lengths.
+// histogram).  Measured: 6.0 / 7.8 us for 3.8 / 8.2 thousand N(0,1) scores, 5 to 12 us for crowded ones and 28 where all
+// are equal (its LDS histogram is one compute unit's work); the passes of longer rows take 15 us at any of these lengths.
 constexpr int kSelectSmallThreads = 1024;
 constexpr int kSelectSmallItems = 8;                         // keys per thread
 constexpr int64_t kSelectSmallMax = kSelectSmallThreads * kSelectSmallItems;
 
-// Bin of a value, given its order-preserving key: thirty-two bins per power of two and sign from 2^-16 to 2^16, the bins at
-// the ends take what lies beyond.  The value is the score plus a shift of its row (TopkLayout::shift) that brings the bulk
-// of the row near zero, where bins are narrow: a row's scores F = S - mu lie together far below zero when one token stands
-// out (mu = 500 and a spread of 11 in a decode step on a long document), and binned as they are a bin there held several
-// thousand of 260k keys, more than the lists of topk_compact: 264 us for that step against 39 us.  Any shift gives the same
-// selection: adding a number and rounding keeps the order.
+// Digit of the first histogram of a long row, given a score's order-preserving key.
+__device__ __forceinline__ uint32_t score_digit(uint32_t key) { return key >> 21; }
+
+// Bin of a score in a short row's first histogram, given its key: thirty-two bins per power of two and sign from 2^-16 to
+// 2^16, the bins at the ends take what lies beyond.
 constexpr uint32_t kNegBins = 1024, kNegFirst = (127 - 16) << 5;         // magnitude >> 18 of the finest negative bin
 constexpr uint32_t kPosBins = kRadixBins - kNegBins, kPosFirst = (127 - 16) << 5;
 __device__ __forceinline__ uint32_t score_bin(uint32_t key) {
@@ -35,10 +34,7 @@ __device__ __forceinline__ uint32_t score_bin(uint32_t key) {
   b = b < 0 ? 0 : (b > most ? most : b);
   return pos ? kNegBins + (uint32_t)b : kNegBins - 1 - (uint32_t)b;
 }
-__device__ __forceinline__ uint32_t shifted_bin(float score, float shift) { return score_bin(ordered_key(score + shift)); }
-// The shift from a row maximum of S (none where that is not a number to add).
-__device__ __forceinline__ float shift_of(float mu) { return fabsf(mu) < 1e30f ? mu : 0.f; }
-// Smallest and largest key of an unshifted bin.
+// Smallest and largest key of a bin.
 __device__ __forceinline__ void bin_keys(uint32_t bin, uint32_t* lo, uint32_t* hi) {
   const bool pos = bin >= kNegBins;
   const uint32_t b = pos ? bin - kNegBins : kNegBins - 1 - bin, last = (pos ? kPosBins : kNegBins) - 1;
@@ -52,21 +48,31 @@ __device__ __forceinline__ void bin_keys(uint32_t bin, uint32_t* lo, uint32_t* h
 
 // Workspace of one batch row of the selection, in uint32 words.
 struct TopkLayout {
-  static constexpr int hist = 0;                              // [kHistReplicas][kRadixBins]
-  static constexpr int pick = kHistWords;                     // [3]: bin of the k-th score, keys in it, its rank inside the bin
-  static constexpr int shift = kHistWords + 3;                // fp32: written with the histogram
-  static constexpr int blk = kHistWords + 4;                  // [2][nblk]: per workgroup, scores above the bin / inside it
-  // then [nblk][cap]: keys inside the bin
+  static constexpr int hist = 0;                              // [3][kHistReplicas][kRadixBins]
+  static constexpr int pick = kHistWords;                     // [2][2]: (bin, remaining rank) chosen in the first / second histogram
+  static constexpr int blk = kHistWords + 4;                  // [2][nblk]: per workgroup, scores above the 22-bit prefix / sharing it
+  // then [nblk][cap] uint16: last digits of the scores sharing the prefix, cap = scores per workgroup
 };
 
-// One LDS-histogram increment per lane.  With bins this fine a wave's 64 scores fall into dozens of them; folding the
-// lanes that share the first lane's bin into one atomic, which paid when four fifths of a row shared a bin, cost more
-// than the few lanes served one after the other.
+// One LDS-histogram increment per lane, with the lanes of a wave that hit the leader's bin folded into a single atomic
+// (scores of one row share their exponent, so in the first pass almost every lane hits the same bin).  Every lane of the
+// wave must call it.
 __device__ __forceinline__ void hist_add(uint32_t* h, bool active, uint32_t bin) {
+  const uint64_t act = __ballot(active);
+  if (act == 0ull) return;
+  const int leader = __ffsll((long long)act) - 1;
+  const uint32_t lead_bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);     // leader is the same in every lane
+  const uint64_t same = __ballot(active && bin == lead_bin);
+  if ((int)(__builtin_amdgcn_workitem_id_x() & 63) == leader) atomicAdd(&h[lead_bin], (uint32_t)__popcll(same));
+  if (active && bin != lead_bin) atomicAdd(&h[bin], 1u);
+}
+// The same without folding, for a short row's finer bins: a wave's 64 scores fall into dozens of them, and folding cost more
+// than the few lanes served one after the other (8192 scores: 7.2 against 6.0 us).
+__device__ __forceinline__ void bin_add(uint32_t* h, bool active, uint32_t bin) {
   if (active) atomicAdd(&h[bin], 1u);
 }
 
-// A workgroup's finished LDS histogram h, added to its copy of the global histogram gh ([kHistReplicas][kRadixBins]).
+// A workgroup's finished LDS histogram h, added to its copy of one pass's global histogram gh ([kHistReplicas][kRadixBins]).
 __device__ __forceinline__ void hist_flush(uint32_t* __restrict__ gh, const uint32_t* h, int wg, int tid, int n_threads) {
   uint32_t* g = gh + (wg % kHistReplicas) * kRadixBins;
   for (int i = tid; i < kRadixBins; i += n_threads)

@@ -167,7 +167,7 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 }
 
 // PASS 0: partial row maxima into part_max[l_c][blocks].  PASS 1: F into score, using mu; with
-// first_hist given, also the histogram of the scores' bins (radix_hist.h; the scores are in LDS here, so the
+// first_hist given, also the histogram of the scores' first digits (radix_hist.h; the scores are in LDS here, so the
 // selection need not read them for it).
 template <int PASS, int DC>
 __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __restrict__ qc, int l_c,
@@ -493,14 +493,13 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   if (PASS == 1) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // this wave's column maxima are in LDS
     __syncthreads();
-    const float shift = first_hist ? __uint_as_float(first_hist[(int64_t)b * first_hist_bs + TopkLayout::shift]) : 0.f;
     for (int i0 = 0; i0 < span; i0 += kThreads) {          // whole waves stay in step for hist_add
       const int i = i0 + tid;
       const int64_t m = tok_base + i;
       const bool ok = i < span && m < n;
       const uint32_t key = ok ? colmax[32 + i] : 0u;
       if (ok) score[(int64_t)b * score_bs + m] = ordered_key_to_f32(key);
-      if (first_hist) hist_add(digit_hist, ok, shifted_bin(ordered_key_to_f32(key), shift));
+      if (first_hist) hist_add(digit_hist, ok, score_digit(key));
     }
     if (first_hist) {
       __syncthreads();
@@ -511,7 +510,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
 }
 
 // mu[c] = max over workgroups of their partial row maxima ([l_c][blocks] layout): one wave per query.
-// Running between the two sweeps, it also zeroes the selection's histogram when given it.
+// Running between the two sweeps, it also zeroes the selection's histograms when given them.
 __global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restrict__ part_max, int nblk, int l_c,
                                                            float* __restrict__ mu, int mu_stride,
                                                            uint32_t* __restrict__ hists, int64_t hists_bs) {
@@ -536,7 +535,6 @@ __global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restri
   }
   m = wave_max(m);
   if (lane == 0) mu[(int64_t)b * mu_stride + c] = m;
-  if (hists && c == 0 && lane == 0) hists[(int64_t)b * hists_bs + TopkLayout::shift] = __float_as_uint(shift_of(m));
 }
 
 // ------------------------------------------------------------------------------------------ decode (l_c = 1)
@@ -579,7 +577,7 @@ __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict_
   const int n_wg = (int)((n + kGemvRows - 1) / kGemvRows);           // workgroups per batch entry (the launch's grid)
   __shared__ float red[4];
   const int b = __builtin_amdgcn_workgroup_id_y();
-  if (hists)       // the selection's histogram, zeroed here for the pass that follows
+  if (hists)       // the selection's histograms, zeroed here for the pass that follows
     for (int i = __builtin_amdgcn_workgroup_id_x() * 256 + __builtin_amdgcn_workitem_id_x(); i < kHistWords; i += n_wg * 256)
       hists[(int64_t)b * hists_bs + i] = 0u;
   const bf16_t* kmid = kc + (int64_t)b * kc_bs + m_lo * (int64_t)kDcv;
@@ -649,7 +647,7 @@ __global__ __launch_bounds__(256) void score_few_bf16(const bf16_t* __restrict__
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) kf[t][ks] = *(const bf16x8*)(k + tok * DC + 32 * ks);
   }
-  if (hists)       // the selection's histogram, zeroed here for the pass that follows
+  if (hists)       // the selection's histograms, zeroed here for the pass that follows
     for (int i = blk * 256 + tid; i < kHistWords; i += n_wg * 256) hists[(int64_t)b * hists_bs + i] = 0u;
   float best = -INFINITY;
 #pragma unroll
@@ -730,7 +728,7 @@ __global__ __launch_bounds__(256) void score_store_fma(const T* __restrict__ qc,
 
 // F[m] = max_c (S[c][m] - mu_c), mu_c = the largest of the n_part partial maxima of query c ([n_part][l_c]), found by
 // every workgroup for itself; pooled over +-eps (<= kTailMaxEps) when asked; with first_hist given also the histogram
-// of the results' bins.  SPLIT = 1 (up to sixteen queries): a workgroup owns `sub` tiles of 1024 tokens, four per
+// of the results' first digits.  SPLIT = 1 (up to sixteen queries): a workgroup owns `sub` tiles of 1024 tokens, four per
 // thread, the ones that the selection's workgroup of the same number reads next (written and read on the same XCD; with
 // many rows several tiles, so that fewer workgroups reduce the partial maxima and flush a histogram).
 // SPLIT = 4: 64 tokens (pooled ones at the ends only feed their neighbours), the queries shared out over the waves.
@@ -739,8 +737,7 @@ template <int SPLIT, bool POOL, bool ONE = false>
 __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S, int64_t s_ld, int64_t s_bs, int64_t n,
                                                     const float* __restrict__ part, int n_part, int l_c, int eps_arg, int sub,
                                                     float* __restrict__ score, int64_t score_bs,
-                                                    uint32_t* __restrict__ first_hist, uint32_t* __restrict__ select_ws,
-                                                    int64_t first_hist_bs) {
+                                                    uint32_t* __restrict__ first_hist, int64_t first_hist_bs) {
   const int eps = POOL ? eps_arg : 0;
   constexpr int kPer = POOL ? 5 : 4;                        // SPLIT = 1: tokens of a thread, the last one of the pooling margin
   constexpr int kAhead = ONE ? 1 : 4;                       // queries whose scores are in flight together
@@ -748,7 +745,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
   __shared__ float mu[SPLIT == 1 ? kFewQueries : kFinishMaxQueries];
   __shared__ float red[256];
   __shared__ float tile[SPLIT == 1 ? kTok + 2 * kTailMaxEps : kTok];
-  __shared__ uint32_t bin_hist[kRadixBins];
+  __shared__ uint32_t digit_hist[kRadixBins];
   const int b = __builtin_amdgcn_workgroup_id_y(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
   const int lane = tid & 63, wave = tid >> 6;
   const float* s = S + (int64_t)b * s_bs;
@@ -780,7 +777,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
       m = fmaxf(fmaxf(m, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
     }
     if (first_hist)
-      for (int i = tid; i < kRadixBins; i += 256) bin_hist[i] = 0u;
+      for (int i = tid; i < kRadixBins; i += 256) digit_hist[i] = 0u;
     m = wave_max(m);
     if (lane == 0) red[wave] = m;
     __syncthreads();
@@ -799,7 +796,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
     m = lanes_max16(m);
     if ((tid & 15) == 0) red[tid >> 4] = m;
     if (first_hist)
-      for (int i = tid; i < kRadixBins; i += 256) bin_hist[i] = 0u;
+      for (int i = tid; i < kRadixBins; i += 256) digit_hist[i] = 0u;
     __syncthreads();
     if (tid < l_c) {
       const int rows = 16 / lc2;
@@ -810,7 +807,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
     __syncthreads();
   } else {
     if (first_hist)
-      for (int i = tid; i < kRadixBins; i += 256) bin_hist[i] = 0u;
+      for (int i = tid; i < kRadixBins; i += 256) digit_hist[i] = 0u;
     int lc2 = 1;
     while (lc2 < l_c && lc2 < 256) lc2 *= 2;
     const int groups = 256 / lc2, jg = tid / lc2;
@@ -833,9 +830,6 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
       __syncthreads();
     }
   }
-  // the row's shift, for this histogram and for whatever bins these scores later
-  const float shift = shift_of(ONE ? mu_one : mu[0]);
-  if (select_ws && blk == 0 && tid == 0) select_ws[(int64_t)b * first_hist_bs + TopkLayout::shift] = __float_as_uint(shift);
   auto pooled = [&](int64_t at_token, int at, float f) {    // tile[at] is token at_token
     for (int d = -eps; d <= eps; ++d)
       if (at_token + d >= 0 && at_token + d < n) f = fmaxf(f, tile[at + d]);
@@ -871,7 +865,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
         float v = f[u];
         if (POOL) v = m < n ? pooled(m, 256 * u + tid + eps, tile[256 * u + tid + eps]) : 0.f;
         if (m < n) score[(int64_t)b * score_bs + m] = v;
-        if (first_hist) hist_add(bin_hist, m < n, shifted_bin(v, shift));
+        if (first_hist) hist_add(digit_hist, m < n, score_digit(ordered_key(v)));
       }
     }
   } else {
@@ -891,17 +885,17 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
       const bool mine = m >= 0 && m < n && lane >= eps && lane < kTok - eps;
       if (POOL && mine) f = pooled(m, lane, f);
       if (mine) score[(int64_t)b * score_bs + m] = f;
-      if (first_hist) hist_add(bin_hist, mine, shifted_bin(f, shift));
+      if (first_hist) hist_add(digit_hist, mine, score_digit(ordered_key(f)));
     }
   }
   if (first_hist) {
     __syncthreads();
-    hist_flush(first_hist + (int64_t)b * first_hist_bs, bin_hist, blk, tid, 256);
+    hist_flush(first_hist + (int64_t)b * first_hist_bs, digit_hist, blk, tid, 256);
   }
 }
 
 // Eq. 8: out[j] = max(in[max(j-eps,0) .. min(j+eps,n-1)]).  With first_hist given, also the histogram of the
-// pooled scores' bins (this is the kernel that writes the scores the selection reads).
+// pooled scores' first digits (this is the kernel that writes the scores the selection reads).
 __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict__ in, float* __restrict__ out, int64_t n,
                                                          int eps, int64_t in_bs, int64_t out_bs,
                                                          uint32_t* __restrict__ first_hist, int64_t first_hist_bs) {
@@ -912,7 +906,6 @@ __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict
   __syncthreads();
   const float* src = in + (int64_t)__builtin_amdgcn_workgroup_id_y() * in_bs;
   float* dst = out + (int64_t)__builtin_amdgcn_workgroup_id_y() * out_bs;
-  const float shift = first_hist ? __uint_as_float(first_hist[(int64_t)__builtin_amdgcn_workgroup_id_y() * first_hist_bs + TopkLayout::shift]) : 0.f;
   // whole waves stay in the loop together (hist_add is a wave-wide operation)
   for (int64_t j0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * 256 + (__builtin_amdgcn_workitem_id_x() & ~63); j0 < n; j0 += (int64_t)n_wg * 256) {
     const int64_t j = j0 + (__builtin_amdgcn_workitem_id_x() & 63);
@@ -923,7 +916,7 @@ __global__ __launch_bounds__(256) void proximity_maxpool(const float* __restrict
       for (int64_t w = lo + 1; w <= hi; ++w) m = fmaxf(m, src[w]);
       dst[j] = m;
     }
-    if (first_hist) hist_add(digit_hist, j < n, shifted_bin(m, shift));
+    if (first_hist) hist_add(digit_hist, j < n, score_digit(ordered_key(m)));
   }
   if (first_hist) {
     __syncthreads();
@@ -999,8 +992,8 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
   // eps > 0: windows of up to kTailMaxEps on either side are pooled by whatever finishes the scores (score_finish, or
   // the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
   const bool narrow = eps <= kTailMaxEps;
-  bool zeroed = false;                  // the selection's histogram has been zeroed ...
-  if (first_hist_done) *first_hist_done = false;        // ... and filled
+  bool zeroed = false;                  // the selection's histograms have been zeroed ...
+  if (first_hist_done) *first_hist_done = false;        // ... and the first one filled
   float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
   char* at = (char*)part + part_bytes(l_c, n, batch);
   float* raw = score;
@@ -1030,7 +1023,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                                  : (e > 0 ? score_finish<4, true> : score_finish<4, false>);
     const int sub = topk_tiles_per_wg(n, batch);
     const unsigned wgs = few ? (unsigned)((n + 1024 * (int64_t)sub - 1) / (1024 * (int64_t)sub)) : (unsigned)((n + 63 - 2 * e) / (64 - 2 * e));
-    kernel<<<dim3(wgs, batch), 256, 0, st>>>(S, s_ld, s_bs, n, part, n_part, l_c, e, sub, out, out_bs, hist, first_hist, first_hist_bs);
+    kernel<<<dim3(wgs, batch), 256, 0, st>>>(S, s_ld, s_bs, n, part, n_part, l_c, e, sub, out, out_bs, hist, first_hist_bs);
     if (hist && first_hist_done) *first_hist_done = true;
     zeroed = first_hist != nullptr;
     pool_left = eps > 0 && !narrow;
@@ -1106,7 +1099,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     }
   }
   if (pool_left) {
-    uint32_t* ph = zeroed ? first_hist : nullptr;      // only behind kernels that have zeroed the histogram
+    uint32_t* ph = zeroed ? first_hist : nullptr;      // only behind kernels that have zeroed the histograms
     proximity_maxpool<<<dim3(maxpool_blocks(n), batch), 256, 0, st>>>(raw, score, n, eps, raw_bs, score_bs, ph, first_hist_bs);
     if (ph && first_hist_done) *first_hist_done = true;
   }

@@ -5,18 +5,23 @@
 // in one launch (select_small), including what the score call would otherwise need a pass of its own for (mu of a
 // single current token, Eq. 8's pooling).
 //
-// Longer rows: a histogram over 2048 fine bins (radix_hist.h) is built by the kernel that writes the scores; then
-//   topk_compact  every workgroup picks the bin that holds the k-th score, counts its scores above it and lists
-//                 its keys inside it (a few per thousand scores);
-//   topk_write    every workgroup collects all lists (a few hundred keys) in LDS, finds the exact threshold T among
-//                 them and how many keys equal to T are still needed, and from the counts and lists of the
-//                 workgroups before it its own output offset, and writes its selected positions.
-// Rows whose k-th score shares its bin with more keys than the lists hold (massive ties) take a slower path inside
-// topk_write that finds T and the offset from the scores themselves.
+// Longer rows: three histogram passes (11 + 11 + 10 bits, most significant first) pin down the key T of the k-th
+// largest score and how many scores equal to T are still needed; the first histogram is built by the kernel that writes
+// the scores where that can.  A writing pass then emits the positions.  For its output offsets a workgroup of it needs
+// the number of selected scores in the workgroups before it; the third histogram pass leaves that per workgroup in two
+// pieces: the count of scores above the 22-bit prefix fixed so far (selected whatever the last digit of T turns out to
+// be), and the list of the last digits of the scores that share the prefix (usually a handful), which the writing pass
+// compares with T's last digit once it knows it.
+// Why digits of the key and not finer bins: no bin that is fixed before the scores are known is fine enough for every
+// row.  One histogram of 32 bins per power of two around an estimate of the row's bulk, and lists of the keys in the
+// threshold's bin, save a pass where the selected tokens stand clear of all others (260k scores: 25.0 against 27.3 us for
+// a decode step's score and selection) and lose wherever they do not: N(0,1) scores 30.9 against 27.7 us, a passage of
+// 3000 tokens of similar score 275 against 15, a chunk whose first query is fifty times the others 446 against 139.
 // All cross-block traffic is integer atomics and plain stores, so the result is deterministic.
-// No workgroup ever waits for another: what one pass leaves in global memory is re-read and scanned by EVERY
-// workgroup of the next launch, redundantly, instead of being finished by a last-arriving workgroup: a launch is then
-// one round trip to memory plus a little LDS work, which is what bounds this latency-bound call.
+// No workgroup ever waits for another: what one pass leaves in global memory (a 2048-bin histogram, or the per-workgroup
+// counts) is re-read and scanned by EVERY workgroup of the next launch, redundantly, instead of being finished by a
+// last-arriving workgroup: a launch is then one round trip to memory plus a little LDS work, which is what bounds this
+// latency-bound call.
 #include <atomic>
 
 #include "esa_common.h"
@@ -29,9 +34,7 @@ constexpr int kThreads = 512;
 constexpr int kItems = 2;                       // consecutive scores per thread
 constexpr int kTile = kThreads * kItems;        // scores per block
 constexpr int kBins = kRadixBins;
-constexpr int kCandPerTile = 64;                // list slots of a workgroup per tile of scores
-constexpr int kPeek = 8;                        // of them read ahead of their count
-constexpr uint32_t kListMax = 8192;             // keys topk_write can hold
+constexpr int kBinsPerThread = kBins / kThreads;
 
 struct TopkPlan {
   int64_t sub;      // tiles of kTile scores per workgroup
@@ -39,7 +42,7 @@ struct TopkPlan {
 };
 // One tile of kTile scores per workgroup while that keeps the chip busy (a call is latency-bound
 // then); with many rows a workgroup takes several tiles, so that the fixed work per workgroup
-// (bin and list resolution) is paid by fewer of them.
+// (prefix resolution, histogram flush) is paid by fewer of them.
 __host__ inline TopkPlan topk_plan(int64_t n, int batch) {
   const int64_t tiles = (n + kTile - 1) / kTile;
   int64_t sub = (tiles * batch + 767) / 768;
@@ -49,10 +52,9 @@ __host__ inline TopkPlan topk_plan(int64_t n, int batch) {
   p.nblk = (tiles + sub - 1) / sub;
   return p;
 }
-// counts of a kind, per row: a multiple of four words, so that the lists behind them are 16-byte aligned
-__host__ __device__ inline int64_t count_words(int64_t nblk) { return (nblk + 3) / 4 * 4; }
 __host__ inline int64_t topk_row_words(const TopkPlan& p) {
-  return TopkLayout::blk + 2 * count_words(p.nblk) + p.nblk * p.sub * kCandPerTile;
+  const int64_t cand_words = (p.nblk * p.sub * kTile + 1) / 2;
+  return TopkLayout::blk + 2 * p.nblk + cand_words;
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave in the vector unit: shifts inside the 16-lane rows, then the
@@ -196,103 +198,104 @@ __device__ __forceinline__ Narrowed narrow(Narrowed r, uint32_t count, uint32_t*
   return r;
 }
 
-// Zeroes the histogram and takes the row's shift from its scores: minus the median of 256 of them.
-__global__ __launch_bounds__(1024) void topk_init(const float* __restrict__ score, int64_t n, int64_t score_bs, uint32_t* ws,
-                                                  int64_t row_words) {
-  __shared__ uint32_t sample[256];
-  uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
-  const int tid = threadIdx.x;
-  const uint32_t mine = ordered_key(score[(int64_t)blockIdx.y * score_bs + n * (tid & 255) / 256]);
-  for (int i = blockIdx.x * blockDim.x + tid; i < kHistWords; i += gridDim.x * blockDim.x) w[i] = 0u;
-  if (blockIdx.x != 0) return;
-  if (tid < 256) sample[tid] = mine;
-  __syncthreads();
-  if (tid >= 256) return;
-  int below = 0;
-#pragma unroll 16
-  for (int i = 0; i < 256; ++i) below += sample[i] < mine || (sample[i] == mine && i < tid) ? 1 : 0;
-  if (below == 128) w[TopkLayout::shift] = __float_as_uint(-shift_of(ordered_key_to_f32(mine)));
-}
-
-// The histogram, for callers whose scores were written by something else.
-__global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ score, int64_t n, int64_t score_bs,
-                                                      uint32_t* __restrict__ ws, int64_t row_words, int sub) {
-  __shared__ uint32_t h[kBins];
-  const float* row = score + (int64_t)blockIdx.y * score_bs;
-  const int64_t first = (int64_t)blockIdx.x * kTile * sub + (int64_t)threadIdx.x * kItems;
-  uint32_t key[kItems];
-  bool ok[kItems];
-  load_keys(row, n, first, key, ok);
-  const float shift = __uint_as_float(ws[(int64_t)blockIdx.y * row_words + TopkLayout::shift]);
-  for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
-  __syncthreads();
-  for (int st = 0; st < sub; ++st) {
-    if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
+// This thread's share of a finished histogram in global memory ([kHistReplicas][kBins]); thread 0 owns the highest bins.
+__device__ __forceinline__ void load_slice(const uint32_t* __restrict__ gh, uint32_t (&c)[kBinsPerThread]) {
+  static_assert(kBinsPerThread == 4, "one 16-byte load per copy");
+  const uint4* lowest = (const uint4*)gh + (kThreads - 1 - threadIdx.x);      // bins top-3 .. top of this thread
+  uint4 copy[kHistReplicas];
 #pragma unroll
-    for (int e = 0; e < kItems; ++e) hist_add(h, ok[e], shifted_bin(ordered_key_to_f32(key[e]), shift));
+  for (int r = 0; r < kHistReplicas; ++r) copy[r] = lowest[r * (kBins / 4)];
+  uint4 t = copy[0];
+#pragma unroll
+  for (int r = 1; r < kHistReplicas; ++r) {
+    t.x += copy[r].x; t.y += copy[r].y; t.z += copy[r].z; t.w += copy[r].w;
   }
-  __syncthreads();
-  hist_flush(ws + (int64_t)blockIdx.y * row_words + TopkLayout::hist, h, blockIdx.x, threadIdx.x, kThreads);
+  c[0] = t.w; c[1] = t.z; c[2] = t.y; c[3] = t.x;
 }
 
-__global__ __launch_bounds__(kThreads) void topk_compact(const float* __restrict__ score, int64_t n, int64_t score_bs,
-                                                         uint32_t* __restrict__ ws, int64_t row_words, int nblk,
-                                                         uint32_t k, int sub) {
+// Key bits fixed by the passes before PASS, and the rank still to find below them.  A pass picks one histogram itself
+// (the one the pass before it filled) and reads what the earlier passes picked from the workspace, where the pass that
+// made the pick left it (every workgroup writes the same two words); all of it is one round trip.
+template <int PASS>
+__device__ __forceinline__ void resolve_prefix(uint32_t* __restrict__ w, uint32_t k, uint32_t* wave_sums,
+                                               uint32_t* result, uint32_t* prefix, uint32_t* k_rem) {
+  *prefix = 0;
+  *k_rem = k;
+  if constexpr (PASS > 0) {
+    uint32_t c[kBinsPerThread];
+    load_slice(w + TopkLayout::hist + (PASS - 1) * kHistReplicas * kBins, c);
+    uint32_t bin[3] = {0, 0, 0}, rank = k;
+#pragma unroll
+    for (int p = 0; p < PASS - 1; ++p) {
+      bin[p] = w[TopkLayout::pick + 2 * p];
+      rank = w[TopkLayout::pick + 2 * p + 1];
+    }
+    const BinPick b = pick_bin<kThreads>(c, rank, wave_sums, result);
+    bin[PASS - 1] = b.bin;
+    if (PASS < 3 && threadIdx.x == 0) {
+      w[TopkLayout::pick + 2 * (PASS - 1)] = b.bin;
+      w[TopkLayout::pick + 2 * (PASS - 1) + 1] = b.k_rem;
+    }
+    *prefix = (bin[0] << 21) | (bin[1] << 10) | bin[2];
+    *k_rem = b.k_rem;
+  }
+}
+
+__global__ void topk_init(uint32_t* ws, int64_t row_words) {
+  uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kHistWords; i += gridDim.x * blockDim.x) w[i] = 0u;
+}
+
+// PASS 0: bits 31..21, PASS 1: bits 20..10, PASS 2: bits 9..0.
+template <int PASS>
+__global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ score, int64_t n, int64_t score_bs,
+                                                      uint32_t* __restrict__ ws, int64_t row_words, int nblk,
+                                                      uint32_t k, int sub) {
+  __shared__ uint32_t h[kBins];
   __shared__ uint32_t wave_sums[kThreads / 64];
   __shared__ uint32_t result[3];
-  __shared__ uint32_t n_above, n_cand;
+  __shared__ uint32_t n_above, n_cand;             // PASS 2: this workgroup's scores above / sharing the prefix
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
   const int64_t first = (int64_t)blockIdx.x * kTile * sub + (int64_t)threadIdx.x * kItems;
   uint32_t key[kItems];
   bool ok[kItems];
   load_keys(row, n, first, key, ok);
-  const float shift = __uint_as_float(w[TopkLayout::shift]);
-  uint32_t c[kBins / kThreads];
-  {
-    static_assert(kBins / kThreads == 4, "one 16-byte load per copy");
-    const uint4* lowest = (const uint4*)(w + TopkLayout::hist) + (kThreads - 1 - threadIdx.x);      // bins top-3 .. top of this thread
-    uint4 copy[kHistReplicas];
-#pragma unroll
-    for (int r = 0; r < kHistReplicas; ++r) copy[r] = lowest[r * (kBins / 4)];
-    uint4 t = copy[0];
-#pragma unroll
-    for (int r = 1; r < kHistReplicas; ++r) {
-      t.x += copy[r].x; t.y += copy[r].y; t.z += copy[r].z; t.w += copy[r].w;
-    }
-    c[0] = t.w; c[1] = t.z; c[2] = t.y; c[3] = t.x;
-  }
+  for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
   if (threadIdx.x == 0) {
     n_above = 0u;
     n_cand = 0u;
   }
-  const BinPick p = pick_bin<kThreads>(c, k, wave_sums, result);       // (its barriers also publish the zeros)
-  if (threadIdx.x == 0) {                                              // every workgroup writes the same words
-    w[TopkLayout::pick + 0] = p.bin;
-    w[TopkLayout::pick + 1] = p.count;
-    w[TopkLayout::pick + 2] = p.k_rem;
-  }
-  const uint32_t cap = (uint32_t)(kCandPerTile * sub);
-  uint32_t* cand = w + TopkLayout::blk + 2 * count_words(nblk) + (int64_t)blockIdx.x * cap;
+  uint32_t prefix, k_rem;
+  resolve_prefix<PASS>(w, k, wave_sums, result, &prefix, &k_rem);
+  __syncthreads();
+  uint16_t* cand = (uint16_t*)(w + TopkLayout::blk + 2 * nblk) + (int64_t)blockIdx.x * kTile * sub;
   uint32_t above = 0;
-  for (int st = 0; st < sub; ++st) {
+  for (int st = 0; st < sub; ++st) {               // `sub` tiles of kTile scores, one histogram
     if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
-      const uint32_t bin = shifted_bin(ordered_key_to_f32(key[e]), shift);
-      above += ok[e] && bin > p.bin ? 1u : 0u;
-      if (ok[e] && bin == p.bin) {
-        const uint32_t at = atomicAdd(&n_cand, 1u);                    // order does not matter: they are counted
-        if (at < cap) cand[at] = key[e];
+      if (PASS == 0) {
+        hist_add(h, ok[e], score_digit(key[e]));
+      } else if (PASS == 1) {
+        hist_add(h, ok[e] && (key[e] >> 21) == (prefix >> 21), (key[e] >> 10) & 2047u);
+      } else {
+        const bool shares = ok[e] && (key[e] >> 10) == (prefix >> 10);
+        hist_add(h, shares, key[e] & 1023u);
+        above += (ok[e] && (key[e] >> 10) > (prefix >> 10)) ? 1u : 0u;
+        if (shares) cand[atomicAdd(&n_cand, 1u)] = (uint16_t)(key[e] & 1023u);   // order does not matter: they are counted
       }
     }
   }
-  above = wave_incl_scan(above);                                       // lane 63 holds the wave's total
-  if ((threadIdx.x & 63) == 63) atomicAdd(&n_above, above);
+  if (PASS == 2) {
+    above = wave_incl_scan(above);                 // lane 63 holds the wave's total
+    if ((threadIdx.x & 63) == 63) atomicAdd(&n_above, above);
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  hist_flush(w + TopkLayout::hist + PASS * kHistReplicas * kBins, h, blockIdx.x, threadIdx.x, kThreads);
+  if (PASS == 2 && threadIdx.x == 0) {
     w[TopkLayout::blk + blockIdx.x] = n_above;
-    w[TopkLayout::blk + count_words(nblk) + blockIdx.x] = n_cand;
+    w[TopkLayout::blk + nblk + blockIdx.x] = n_cand;
   }
 }
 
@@ -300,13 +303,8 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
                                                        uint32_t* __restrict__ ws, int64_t row_words, int nblk,
                                                        int64_t base, int32_t* __restrict__ idx, int64_t idx_bs,
                                                        uint32_t k, int sub) {
-  __shared__ uint32_t h[kBins];
-  __shared__ uint32_t list_key[kListMax];
-  __shared__ uint8_t list_before[kListMax];              // listed by a workgroup before this one
-  __shared__ uint32_t list_lo, list_hi;
   __shared__ uint32_t wave_sums[2 * kThreads / 64];
   __shared__ uint32_t result[3];
-  __shared__ uint32_t n_list, too_many;
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
   int32_t* out = idx + (int64_t)blockIdx.y * idx_bs;
@@ -314,98 +312,49 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
   uint32_t key[kItems];
   bool ok[kItems];
   load_keys(row, n, first0, key, ok);
-  const uint32_t cap = (uint32_t)(kCandPerTile * sub);
-  const uint32_t* n_above = w + TopkLayout::blk;
-  const uint32_t* n_cand = n_above + count_words(nblk);
-  const uint32_t* cand = n_cand + count_words(nblk);
-  const float shift = __uint_as_float(w[TopkLayout::shift]);
-  const uint32_t bin = w[TopkLayout::pick + 0], in_bin = w[TopkLayout::pick + 1];
-  Narrowed r;
-  r.k_rem = w[TopkLayout::pick + 2];
-  if (threadIdx.x == 0) {
-    n_list = 0u;
-    list_lo = 0xFFFFFFFFu;
-    list_hi = 0u;
-    too_many = in_bin > kListMax ? 1u : 0u;
-  }
-  __syncthreads();
-  uint32_t my_gt = 0, my_eq = 0;
-  if (in_bin <= kListMax) {
-    for (int i = threadIdx.x; i < nblk; i += kThreads) {
-      // the first slots are read whether or not that workgroup filled them: asking for the count first would put a
-      // second round trip in front of them
-      const uint32_t cnt = n_cand[i], above = n_above[i];
-      const uint4 a = *(const uint4*)(cand + (int64_t)i * cap), b = *(const uint4*)(cand + (int64_t)i * cap + 4);
-      my_gt += i < (int)blockIdx.x ? above : 0u;
-      if (cnt > 0) {
-        if (cnt > cap) too_many = 1u;
-        const uint32_t at = atomicAdd(&n_list, cnt);
-        const uint32_t peek[kPeek] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  // What the third histogram pass left about the first workgroup this thread looks at: requested
+  // before T is resolved, so that the two round trips overlap.
+  constexpr int kPeek = 4;
+  const uint16_t* cand_all = (const uint16_t*)(w + TopkLayout::blk + 2 * nblk);
+  const int64_t cap = (int64_t)kTile * sub;
+  uint32_t c0 = 0, above0 = 0, peek[kPeek];
 #pragma unroll
-        for (uint32_t j = 0; j < (uint32_t)kPeek; ++j)
-          if (j < cnt && at + j < kListMax) {
-            list_key[at + j] = peek[j];
-            list_before[at + j] = i < (int)blockIdx.x;
-          }
-        for (uint32_t j = kPeek; j < cnt && j < cap && at + j < kListMax; ++j) {
-          list_key[at + j] = cand[(int64_t)i * cap + j];
-          list_before[at + j] = i < (int)blockIdx.x;
-        }
+  for (int j = 0; j < kPeek; ++j) peek[j] = 0u;
+  if ((int)threadIdx.x < (int)blockIdx.x) {
+    above0 = w[TopkLayout::blk + threadIdx.x];
+    c0 = w[TopkLayout::blk + nblk + threadIdx.x];
+    // read whether or not that workgroup left so many (its slots exist either way; the count decides below what
+    // is used): asking for the count first would put a second round trip in front of them
+    static_assert(kPeek <= kTile, "a workgroup's candidate slots");
+#pragma unroll
+    for (int j = 0; j < kPeek; ++j) peek[j] = cand_all[threadIdx.x * cap + j];
+  }
+  uint32_t T, need;                                      // need: equal-to-T scores to take, lowest positions first
+  resolve_prefix<3>(w, k, wave_sums, result, &T, &need);
+  // scores above / equal to T in the workgroups before this one: those above the 22-bit prefix, plus
+  // those sharing it whose last digit is above / equal to T's
+  const uint32_t t_digit = T & 1023u;
+  uint32_t my_gt = 0, my_eq = 0;
+  for (int i = threadIdx.x; i < (int)blockIdx.x; i += kThreads) {
+    const bool head = i == (int)threadIdx.x;
+    uint32_t c = head ? c0 : w[TopkLayout::blk + nblk + i];
+    c = c < (uint32_t)cap ? c : (uint32_t)cap;           // a workgroup cannot have left more than its scores: the reads below stay inside its slots
+    my_gt += head ? above0 : w[TopkLayout::blk + i];
+    uint32_t j0 = 0;
+    if (head) {
+#pragma unroll
+      for (int j = 0; j < kPeek; ++j) {
+        my_gt += ((uint32_t)j < c && peek[j] > t_digit) ? 1u : 0u;
+        my_eq += ((uint32_t)j < c && peek[j] == t_digit) ? 1u : 0u;
       }
+      j0 = kPeek;
+    }
+    for (uint32_t j = j0; j < c; ++j) {
+      const uint32_t dgt = cand_all[i * cap + j];
+      my_gt += dgt > t_digit ? 1u : 0u;
+      my_eq += dgt == t_digit ? 1u : 0u;
     }
   }
-  __syncthreads();
-  if (!too_many) {
-    const uint32_t listed = n_list;
-    uint32_t least = 0xFFFFFFFFu, most = 0u;             // the range of the bin's keys
-    for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
-      least = list_key[e] < least ? list_key[e] : least;
-      most = list_key[e] > most ? list_key[e] : most;
-    }
-    if (least <= most) {
-      atomicMin(&list_lo, least);
-      atomicMax(&list_hi, most);
-    }
-    __syncthreads();
-    r.lo = list_lo;
-    r.hi = list_hi;
-    r = narrow<kThreads>(r, in_bin, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
-      for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
-        const uint32_t v = list_key[e];
-        if (v >= lo && v <= hi) atomicAdd(&h[(v - lo) >> shift], 1u);
-      }
-    });
-    for (uint32_t e = threadIdx.x; e < listed; e += kThreads) {
-      const bool before = list_before[e];
-      my_gt += before && list_key[e] > r.hi ? 1u : 0u;
-      my_eq += before && list_key[e] >= r.lo && list_key[e] <= r.hi ? 1u : 0u;
-    }
-  } else {
-    // more keys in the bin than the lists hold: the same from the scores themselves.  The bin's range is found bit by bit:
-    // the most keys that lie below it, and below its end
-    r.lo = 0u;
-    uint32_t end = 0u;
-    for (uint32_t bit = 0x80000000u; bit; bit >>= 1) {
-      if (shifted_bin(ordered_key_to_f32((r.lo | bit) - 1), shift) < bin) r.lo |= bit;
-      if (shifted_bin(ordered_key_to_f32((end | bit) - 1), shift) <= bin) end |= bit;
-    }
-    const uint32_t top = shifted_bin(ordered_key_to_f32(0xFFFFFFFFu), shift);
-    r.hi = bin >= top ? 0xFFFFFFFFu : end - 1;
-    r = narrow<kThreads>(r, in_bin, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
-      for (int64_t i0 = threadIdx.x & ~63; i0 < n; i0 += kThreads) {     // whole waves stay in step for hist_add
-        const int64_t i = i0 + (threadIdx.x & 63);
-        const uint32_t v = ordered_key(row[i < n ? i : 0]);
-        hist_add(h, i < n && v >= lo && v <= hi, (v - lo) >> shift);
-      }
-    });
-    my_gt = 0;
-    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x * kTile * sub; i += kThreads) {
-      const uint32_t v = ordered_key(row[i]);
-      my_gt += v > r.hi ? 1u : 0u;
-      my_eq += v >= r.lo && v <= r.hi ? 1u : 0u;
-    }
-  }
-  const uint32_t need = r.k_rem;
   uint32_t off_gt, off_eq, unused_a, unused_b;
   block_excl_scan2<kThreads>(my_gt, my_eq, &unused_a, &unused_b, &off_gt, &off_eq, wave_sums);
   for (int st = 0; st < sub; ++st) {                     // tiles in position order; the offsets run on
@@ -414,8 +363,8 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
     uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
-      gt += (ok[e] && key[e] > r.hi) ? 1u : 0u;
-      eq += (ok[e] && key[e] >= r.lo && key[e] <= r.hi) ? 1u : 0u;
+      gt += (ok[e] && key[e] > T) ? 1u : 0u;
+      eq += (ok[e] && key[e] == T) ? 1u : 0u;
     }
     uint32_t tot_g, tot_e, g_before, e_before;
     block_excl_scan2<kThreads>(gt, eq, &g_before, &e_before, &tot_g, &tot_e, wave_sums);
@@ -424,7 +373,7 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
       if (!ok[e]) continue;
-      const bool is_gt = key[e] > r.hi, is_eq = !is_gt && key[e] >= r.lo;
+      const bool is_gt = key[e] > T, is_eq = key[e] == T;
       if (is_gt || (is_eq && e_before < need)) {
         const uint32_t slot = g_before + (e_before < need ? e_before : need);
         if (slot < k) out[slot] = (int32_t)(base + first + e);
@@ -491,7 +440,7 @@ __global__ __launch_bounds__(kSelectSmallThreads) void select_small(ScoreTail t,
     if (t.part) f -= mu;
     if (ok && score) score[(int64_t)blockIdx.x * score_bs + i] = f;
     key[e] = ordered_key(f);
-    hist_add(h, ok, score_bin(key[e]));
+    bin_add(h, ok, score_bin(key[e]));
   }
   __syncthreads();
   uint32_t c[kBins / NT];
@@ -503,7 +452,7 @@ __global__ __launch_bounds__(kSelectSmallThreads) void select_small(ScoreTail t,
   r = narrow<NT>(r, p.count, h, wave_sums, result, [&](uint32_t lo, uint32_t hi, int shift) {
 #pragma unroll
     for (int e = 0; e < ITEMS; ++e)
-      hist_add(h, first + 64 * e < n && key[e] >= lo && key[e] <= hi, (key[e] - lo) >> shift);
+      bin_add(h, first + 64 * e < n && key[e] >= lo && key[e] <= hi, (key[e] - lo) >> shift);
   });
   uint32_t gt = 0, eq = 0;                       // of the wave
 #pragma unroll
@@ -636,11 +585,12 @@ int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx
   const int64_t row_words = topk_row_stride_words(n, batch);
   uint32_t* w = (uint32_t*)ws;
   const dim3 grid(nblk, batch);
-  if (!first_hist_ready) {     // otherwise the score call has zeroed and filled the histogram
-    topk_init<<<dim3(kHistReplicas, batch), 1024, 0, st>>>(score, n, score_bs, w, row_words);
-    topk_hist<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, sub);
+  if (!first_hist_ready) {     // otherwise the score call has zeroed the histograms and filled the first one
+    topk_init<<<dim3(3 * kHistReplicas, batch), 1024, 0, st>>>(w, row_words);
+    topk_hist<0><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
   }
-  topk_compact<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
+  topk_hist<1><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
+  topk_hist<2><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
   topk_write<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, base, idx, idx_bs, (uint32_t)k, sub);
   ESA_LAUNCH_CHECK("topk");
   return ESA_OK;

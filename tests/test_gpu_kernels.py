@@ -123,7 +123,7 @@ def _bin_crowd(rng, n, crowd, kind):
     return s
 
 
-# around the longest row one workgroup takes; lists that just fit, overflow one workgroup's slots, or exceed the whole list
+# around the longest row one workgroup takes; scores that share many leading bits, or all of them
 @pytest.mark.parametrize("n,k,crowd,kind", [
     (1024, 1023, 900, "spread"), (8192, 2048, 5000, "spread"), (8193, 2048, 2040, "spread"), (8192, 700, 3000, "equal"),
     (40000, 500, 1900, "run"), (100000, 2048, 2100, "spread"), (100000, 900, 2000, "equal"), (100000, 60000, 90000, "equal")])
@@ -138,7 +138,7 @@ def test_select_topk_where_the_threshold_bin_is_crowded(esa, n, k, crowd, kind):
 
 
 # rows whose scores lie together far from zero (one token stands out of a decode step), of any scale, with infinities and
-# masked entries; crowds within the lists' capacity and beyond it
+# masked entries
 @pytest.mark.parametrize("n,k,centre,spread", [(260000, 2048, -500.0, 11.0), (9001, 700, 3e4, 5.0), (100000, 8192, 0.0, 1e-6),
                                                (8193, 8192, -1e6, 0.01), (20000, 1, 1e31, 1e28), (50000, 25000, 40.0, 1e-5)])
 def test_selection_from_scores_far_from_zero(esa, n, k, centre, spread):
@@ -152,6 +152,64 @@ def test_selection_from_scores_far_from_zero(esa, n, k, centre, spread):
     for b in range(2):
         order = np.lexsort((np.arange(n), -s[b].astype(np.float64)))[:k]
         assert np.array_equal(got[b], np.sort(order) + 3)
+
+
+def _time_us(call, passes=20):
+    """Median device time of a call, in microseconds."""
+    call()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(passes):
+            call()
+    times = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / passes)
+    return sorted(times)[3]
+
+
+# The selection's time does not depend on how the scores lie: tokens of a passage score alike, a row lies far from zero, one
+# query of a chunk is much larger than the others (its row maximum, too).  Twice the time of N(0, 1) scores leaves room for
+# noise; a selection whose lists overflowed took 5 to 11 times as long.
+@pytest.mark.parametrize("kind", ["passage", "far", "pooled"])
+def test_selection_time_does_not_depend_on_the_scores(esa, kind):
+    say(f"select, {kind} scores against N(0, 1)")
+    n, k = 200000, 2048
+    g = torch.Generator(device="cuda").manual_seed(11)
+    plain = torch.randn(n, generator=g, device="cuda")
+    s = 3.0 * plain - 100.0
+    if kind == "passage":
+        s[1000:4000] = -30.0 + 0.3 * plain[1000:4000]
+    elif kind == "far":
+        s = plain - 700.0
+    else:
+        s = torch.nn.functional.max_pool1d(s[None], 33, 1, 16)[0].contiguous()
+    a, b = _time_us(lambda: esa.esa_select_topk(plain, k)), _time_us(lambda: esa.esa_select_topk(s, k))
+    print(f"{a:.1f} us, {kind} {b:.1f} us", flush=True)
+    assert b <= 2.0 * a
+    order = np.lexsort((np.arange(n), -s.cpu().numpy().astype(np.float64)))[:k]
+    assert np.array_equal(esa.esa_select_topk(s, k).cpu().numpy(), np.sort(order))
+
+
+@pytest.mark.parametrize("l_c", [5, 64])
+def test_selection_time_does_not_depend_on_one_large_query(esa, l_c):
+    say(f"score and select, {l_c} queries of which the first is large")
+    n, k = 100000, 2048
+    g = torch.Generator(device="cuda").manual_seed(l_c)
+    q = torch.randn((l_c, 128), generator=g, device="cuda").to(torch.bfloat16)
+    kc = torch.randn((n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    large = q.clone()
+    large[0] *= 50.0
+    a, b = _time_us(lambda: esa.esa_score_select_gather(q, kc, 0, n, k)), _time_us(lambda: esa.esa_score_select_gather(large, kc, 0, n, k))
+    print(f"{a:.1f} us, one large query {b:.1f} us", flush=True)
+    assert b <= 2.0 * a
+    score, idx, _, _ = esa.esa_score_select_gather(large, kc, 0, n, k)
+    order = np.lexsort((np.arange(n), -score.cpu().numpy().astype(np.float64)))[:k]
+    assert np.array_equal(idx.cpu().numpy(), np.sort(order))
 
 
 @pytest.mark.parametrize("B,l_c,n,d_c,k,eps", [(2, 1, 8192, 128, 2048, 0), (3, 1, 8192, 128, 100, 3), (1, 1, 8193, 128, 2048, 3),
