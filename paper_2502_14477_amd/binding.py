@@ -234,8 +234,9 @@ def esa_attend_reencoded(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
 def esa_attend_local(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor, t0: int, l_i: int, l_l: int,
                      scale: Optional[float] = None, split: int = ESA_SPLIT_I_EARLY) -> None:
     """First half of the two-call form of esa_attend: the keys that do not depend on the selection
-    ([I, L, C], or [L, C] with split = ESA_SPLIT_ALGORITHM1).  Leaves partial results in the attend
-    workspace for esa_attend_finish (same sizes and split, ordered after it)."""
+    ([I, L, C], or [L, C] with split = ESA_SPLIT_ALGORITHM1).  Leaves partial results in a buffer that the device's
+    two-call attentions share, for esa_attend_finish (same sizes and split, ordered after it, with no other
+    esa_attend_local of the device between the two)."""
     _native.attend_local(q, k_cache, v_cache, t0, l_i, l_l, scale, split)
 
 

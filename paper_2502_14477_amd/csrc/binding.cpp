@@ -9,8 +9,10 @@
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
+#include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
+#include <c10/core/Allocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -136,17 +138,36 @@ struct Shape {
   operator at::IntArrayRef() const { return at::IntArrayRef(dim, (size_t)len); }
 };
 
-// A reusable 256-byte aligned scratch tensor per (device, purpose), grown on demand and kept.  Guarded by the
-// interpreter lock; never destroyed (the allocator may be gone by the time statics are).
-enum Purpose { kWsScore = 0, kWsTopk = 1, kWsScoreSelect = 2, kWsAttend = 3 };
-at::Tensor workspace(size_t nbytes, const at::Device& dev, Purpose purpose) {
-  static auto& kept = *new std::map<std::pair<int, int>, at::Tensor>();
-  at::Tensor& t = kept[{dev.index(), (int)purpose}];
-  if (!t.defined() || (size_t)t.numel() < nbytes) {
-    t = new_tensor({(int64_t)(nbytes < 256 ? 256 : nbytes)}, at::kByte, dev);
-    ESA_ASSERT((uintptr_t)t.data_ptr() % 256 == 0);
-  }
-  return t;
+// A call's scratch (256-byte aligned): a block of torch's allocator that the call gives back when its kernels are
+// enqueued.  The allocator hands it out again in the order of the stream it was taken on, so calls on other streams, of
+// other threads or in a graph under capture never share it with this one.
+struct Scratch {
+  c10::DataPtr block;
+  void* p;
+  size_t n;
+};
+Scratch scratch(size_t nbytes) {
+  static c10::Allocator* const allocator = c10::GetAllocator(c10::DeviceType::CUDA);      // torch's name for the device type
+  Scratch s;
+  s.n = nbytes < 256 ? 256 : nbytes;
+  s.block = allocator->allocate(s.n);
+  s.p = s.block.get();
+  ESA_ASSERT((uintptr_t)s.p % 256 == 0);
+  return s;
+}
+// The scratch that attend_local hands over to attend_finish, one per device, grown on demand and kept (never destroyed: the
+// allocator may be gone by the time statics are).  The two calls may run on different streams; a block given up for a
+// larger one is reused only behind both.
+Scratch handed_over(size_t nbytes, const at::Device& dev) {
+  static auto& kept = *new std::map<int, at::Tensor>();
+  at::Tensor& t = kept[dev.index()];
+  if (!t.defined() || (size_t)t.numel() < nbytes) t = new_tensor({(int64_t)nbytes}, at::kByte, dev);
+  t.record_stream(c10::hip::getCurrentHIPStreamMasqueradingAsCUDA().unwrap());
+  ESA_ASSERT((uintptr_t)t.data_ptr() % 256 == 0);
+  Scratch s;
+  s.p = t.data_ptr();
+  s.n = (size_t)t.numel();
+  return s;
 }
 
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
@@ -291,9 +312,9 @@ ESA_ENTRY(score, 6) {
     sv = view_of(fresh, 1);
   }
   const int dt = dtype_of(qc), l_c = (int)q.n[0], B = (int)q.B;
-  at::Tensor ws = workspace(esa_score_workspace_bytes(l_c, n, eps, B), qc.device(), kWsScore);
-  void *st = stream(), *qp = ptr(qc), *kp = ptr(kc), *sp = out ? ptr(*out) : ptr(fresh), *wp = ptr(ws);
-  const size_t wn = (size_t)ws.numel();
+  const Scratch ws = scratch(esa_score_workspace_bytes(l_c, n, eps, B));
+  void *st = stream(), *qp = ptr(qc), *kp = ptr(kc), *sp = out ? ptr(*out) : ptr(fresh), *wp = ws.p;
+  const size_t wn = ws.n;
   launch([&] {
     return esa_score(qp, l_c, kp, m_lo, m_hi, (int)q.n[1], eps, (float*)sp, dt, B, q.bs, k.bs, B > 1 ? sv.bs : (n > 1 ? n : 1), wp, wn, st);
   });
@@ -314,9 +335,9 @@ ESA_ENTRY(select_topk, 3) {
   const int64_t n = s.n[0], k_eff = k < n ? k : n;
   ESA_ASSERT(score.scalar_type() == at::kFloat && (n == 0 || s.s[0] == 1));
   at::Tensor idx = new_tensor(Shape(s.batched, s.B, {k_eff}), at::kInt, score.device());
-  at::Tensor ws = workspace(esa_select_topk_workspace_bytes(n, k, (int)s.B), score.device(), kWsTopk);
-  void *st = stream(), *sp = ptr(score), *ip = ptr(idx), *wp = ptr(ws);
-  const size_t wn = (size_t)ws.numel();
+  const Scratch ws = scratch(esa_select_topk_workspace_bytes(n, k, (int)s.B));
+  void *st = stream(), *sp = ptr(score), *ip = ptr(idx), *wp = ws.p;
+  const size_t wn = ws.n;
   launch([&] {
     return esa_select_topk((const float*)sp, n, k, base, (int32_t*)ip, (int)s.B, s.B > 1 ? s.bs : (n > 1 ? n : 1),
                            k_eff > 1 ? k_eff : 1, wp, wn, st);
@@ -385,10 +406,10 @@ ESA_ENTRY(score_select_gather, 8) {
     ks = new_tensor(Shape(q.batched, q.B, {k_eff, c.n[1], c.n[2]}), kcache->scalar_type(), dev);
     vs = new_tensor(Shape(q.batched, q.B, {k_eff, c.n[1], c.n[2]}), kcache->scalar_type(), dev);
   }
-  at::Tensor ws = workspace(esa_score_select_gather_workspace_bytes(l_c, n, eps, k, B), dev, kWsScoreSelect);
-  void *st = stream(), *qp = ptr(qc), *kp = ptr(kc), *sp = score.defined() ? ptr(score) : nullptr, *ip = ptr(idx), *wp = ptr(ws);
+  const Scratch ws = scratch(esa_score_select_gather_workspace_bytes(l_c, n, eps, k, B));
+  void *st = stream(), *qp = ptr(qc), *kp = ptr(kc), *sp = score.defined() ? ptr(score) : nullptr, *ip = ptr(idx), *wp = ws.p;
   void *kcp = ptr(kcache), *vcp = kcache ? ptr(*vcache) : nullptr, *ksp = kcache ? ptr(ks) : nullptr, *vsp = kcache ? ptr(vs) : nullptr;
-  const size_t wn = (size_t)ws.numel();
+  const size_t wn = ws.n;
   launch([&] {
     return esa_score_select_gather(qp, l_c, kp, m_lo, m_hi, (int)q.n[1], eps, k, (float*)sp, (int32_t*)ip, kcp, vcp, c.s[0],
                                    (int)c.n[1], (int)c.n[2], ksp, vsp, dt, B, q.bs, kv.bs, n > 1 ? n : 1, k_eff > 1 ? k_eff : 1,
@@ -506,9 +527,9 @@ ESA_ENTRY(attend_indexed, 9) {
     idx_bs = i.bs;
     ip = ptr(*idx);
   }
-  at::Tensor ws = workspace(esa_attend_indexed_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B, n_sel), io.out.device(), kWsAttend);
-  void *st = stream(), *wp = ptr(ws), *op = ptr(io.out);
-  const size_t wn = (size_t)ws.numel();
+  const Scratch ws = scratch(esa_attend_indexed_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B, n_sel));
+  void *st = stream(), *wp = ws.p, *op = ptr(io.out);
+  const size_t wn = ws.n;
   launch([&] {
     return esa_attend_indexed(io.qp, io.l_c, io.h, io.h_kv, io.d, io.kp, io.vp, io.c.s[0], t0, l_i, l_l, (const int32_t*)ip, n_sel,
                               idx_bs, io.scale, op, lse_ptr(io), io.dt, io.B, io.q.bs, io.c.bs, row_elems(io), wp, wn, st);
@@ -522,9 +543,9 @@ ESA_ENTRY(attend_reencoded, 12) {
   AttendIo io = attend_io(a[0], a[1], a[2], t0, a[10], a[11]);
   const Gathered g = gathered_of(a[6], a[7], io);
   const double w = float_of(a[8]), base = float_of(a[9]);
-  at::Tensor ws = workspace(esa_attend_reencoded_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B, l_l), io.out.device(), kWsAttend);
-  void *st = stream(), *wp = ptr(ws), *op = ptr(io.out);
-  const size_t wn = (size_t)ws.numel();
+  const Scratch ws = scratch(esa_attend_reencoded_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B, l_l));
+  void *st = stream(), *wp = ws.p, *op = ptr(io.out);
+  const size_t wn = ws.n;
   launch([&] {
     return esa_attend_reencoded(io.qp, io.l_c, io.h, io.h_kv, io.d, io.kp, io.vp, io.c.s[0], t0, l_i, l_l, g.k, g.v, g.n_sel, io.scale,
                                 w, base, op, lse_ptr(io), io.dt, io.B, io.q.bs, io.c.bs, g.bs, row_elems(io), wp, wn, st);
@@ -539,9 +560,10 @@ ESA_ENTRY(attend, 11) {
   const Gathered g = gathered_of(a[6], a[7], io);
   const bool one_call = a[10] == Py_None;
   const int split = one_call ? 0 : int32_of(a[10]);
-  at::Tensor ws = workspace(esa_attend_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B), io.out.device(), kWsAttend);
-  void *st = stream(), *wp = ptr(ws), *op = ptr(io.out);
-  const size_t wn = (size_t)ws.numel();
+  const size_t need = esa_attend_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B);
+  const Scratch ws = one_call ? scratch(need) : handed_over(need, io.out.device());
+  void *st = stream(), *wp = ws.p, *op = ptr(io.out);
+  const size_t wn = ws.n;
   launch([&] {
     if (one_call)
       return esa_attend(io.qp, io.l_c, io.h, io.h_kv, io.d, io.kp, io.vp, io.c.s[0], t0, l_i, l_l, g.k, g.v, g.n_sel, io.scale, op,
@@ -557,9 +579,9 @@ ESA_ENTRY(attend_local, 8) {
   const int64_t t0 = int_of(a[3]), l_i = int_of(a[4]), l_l = int_of(a[5]);
   const AttendIo io = attend_io(a[0], a[1], a[2], t0, a[6], nullptr);
   const int split = int32_of(a[7]);
-  at::Tensor ws = workspace(esa_attend_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B), tensor_of(a[0]).device(), kWsAttend);
-  void *st = stream(), *wp = ptr(ws);
-  const size_t wn = (size_t)ws.numel();
+  const Scratch ws = handed_over(esa_attend_workspace_bytes(io.l_c, io.h, io.h_kv, io.d, io.dt, io.B), tensor_of(a[0]).device());
+  void *st = stream(), *wp = ws.p;
+  const size_t wn = ws.n;
   launch([&] {
     return esa_attend_local(io.qp, io.l_c, io.h, io.h_kv, io.d, io.kp, io.vp, io.c.s[0], t0, l_i, l_l, io.scale, split, io.dt, io.B,
                             io.q.bs, io.c.bs, wp, wn, st);

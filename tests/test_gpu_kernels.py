@@ -322,3 +322,43 @@ def test_rope_rows(esa, dtype, B, n_tok, heads, d, pos0, step):
     # one rounding on each side of fp64 values that differ in their last bits
     assert np.all(np.abs(got - want) <= np.abs(want) * (2.0 ** -7 if dtype == "bf16" else 2.0 ** -23))
     assert np.count_nonzero(got != want) <= max(2, 1e-5 * want.size)
+
+
+def test_calls_on_two_streams_and_threads_do_not_share_scratch(esa):
+    """Each thread runs steps of its own on a stream of its own; their results are those of the same steps run alone."""
+    say("two threads, two streams, different steps")
+    import threading
+    l_I, l_L, k, passes = 128, 1024, 512, 12
+
+    def step(t0, l_C, seed):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        mk = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+        q, K, V, qc, kc = mk(l_C, 8, 128), mk(t0 + l_C, 2, 128), mk(t0 + l_C, 2, 128), mk(l_C, 128), mk(t0 + l_C, 128)
+
+        def run():
+            score, idx, ks, vs = esa.esa_score_select_gather(qc, kc, l_I, t0 - l_L, k, K, V)
+            return (score, idx, esa.esa_select_topk(score, 64), esa.esa_attend_indexed(q, K, V, t0, l_I, l_L, idx),
+                    esa.esa_attend_reencoded(q, K, V, t0, l_I, l_L, ks, vs, 4096.0, 5e5))
+        return run
+
+    steps = [step(60000, 1, 1), step(45000, 40, 2)]
+    want = [run() for run in steps]
+    torch.cuda.synchronize()
+    got = [[], []]
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(passes):
+                got[i].append(steps[i]())
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert len(got[i]) == passes
+        for results in got[i]:
+            for a, b in zip(results, want[i]):
+                assert torch.equal(a, b)
