@@ -441,12 +441,9 @@ template <int TT, int RING>
 int run_packed_tiles(const CompressJob<bf16_t>& j0, const CompressJob<bf16_t>& j1, int n_jobs, int split_jobs, uint32_t n_tok,
                      uint32_t n_rows, int d_c, hipStream_t st) {
   constexpr int kLds = packed_lds_bytes<TT, RING>();
-  static bool lds_limit_raised = false;        // idempotent; a race only repeats the call
-  if (!lds_limit_raised) {
-    const hipError_t e = hipFuncSetAttribute((const void*)compress_mfma_packed_bf16<TT, RING>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    if (e != hipSuccess) ESA_FAIL(ESA_EHIP, "esa_compress: %s", hipGetErrorString(e));
-    lds_limit_raised = true;
-  }
+  static OncePerDevice raised;
+  const int rc = raise_lds_limit(raised, {(const void*)compress_mfma_packed_bf16<TT, RING>}, kLds, "esa_compress");
+  if (rc != ESA_OK) return rc;
   const int row_tiles = (int)((n_rows + 16 * TT - 1) / (16 * TT)), col_tiles = d_c / 16;
   const int64_t padded = row_tiles >= 8 ? (row_tiles + 7) / 8 * 8 : row_tiles;
   const int64_t n_wg = padded * col_tiles * (split_jobs ? n_jobs : 1);

@@ -22,6 +22,16 @@ int hip_failed(hipError_t e, const char* what) {
   set_error("%s: %s", what, hipGetErrorString(e));
   return ESA_EHIP;
 }
+int raise_lds_limit(OncePerDevice& raised, std::initializer_list<const void*> kernels, size_t bytes, const char* what) {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess && raised.done(dev)) return ESA_OK;
+  for (const void* k : kernels)
+    if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) return hip_failed(e, what);
+  raised.mark(dev);
+  return ESA_OK;
+}
 
 static bool dtype_ok(int dtype) { return dtype == ESA_F32 || dtype == ESA_BF16; }
 static size_t elem_size(int dtype) { return dtype == ESA_F32 ? 4 : 2; }

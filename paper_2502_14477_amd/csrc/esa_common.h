@@ -5,13 +5,20 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <initializer_list>
+
 #include "esa.h"
+#include "per_device.h"
 
 namespace esa {
 
 // ---------------------------------------------------------------- errors (host)
 void set_error(const char* fmt, ...);
 int hip_failed(hipError_t e, const char* what);   // records the text, returns ESA_EHIP
+
+// Lets the kernels use `bytes` of dynamic LDS on the current device (a limit belongs to a kernel on a device), the first
+// time that `raised` sees the device.
+int raise_lds_limit(OncePerDevice& raised, std::initializer_list<const void*> kernels, size_t bytes, const char* what);
 
 #define ESA_FAIL(code, ...)          \
   do {                               \

@@ -958,15 +958,10 @@ int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int
   const int per = (int)mfma_tiles_per_block(n), nblk = (int)mfma_blocks(n);
   const dim3 grid(nblk, batch);
   const size_t lds = mfma_lds_bytes(per, DC);
-  static bool lds_limit_raised = false;        // idempotent; a race only repeats the call
-  if (!lds_limit_raised) {
-    const int most = (int)mfma_lds_bytes(kMaxTilesPerBlock, DC);
-    hipError_t e = hipFuncSetAttribute((const void*)score_mfma_bf16<0, DC>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)score_mfma_bf16<1, DC>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (e != hipSuccess) return hip_failed(e, "hipFuncSetAttribute(score_mfma_bf16)");
-    lds_limit_raised = true;
-  }
+  static OncePerDevice raised;
+  const int rc = raise_lds_limit(raised, {(const void*)score_mfma_bf16<0, DC>, (const void*)score_mfma_bf16<1, DC>},
+                                 mfma_lds_bytes(kMaxTilesPerBlock, DC), "score_mfma_bf16");
+  if (rc != ESA_OK) return rc;
   score_mfma_bf16<0, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per, nullptr,
                                                       0, qfrag, qfrag_bs, nblk);
   score_rowmax_reduce<<<dim3((l_c + 3) / 4, batch), 256, 0, st>>>(part, nblk, l_c, mu, mfma_mu_stride(l_c), hists, hists_bs);

@@ -148,3 +148,31 @@ def test_header_is_plain_c_and_the_library_serves_a_c_client(tmp_path):
     assert version == esa.esa_version() and (i_end, l_start) == (128, 128512)
     assert ws_bytes == esa.lib.esa_select_topk_workspace_bytes(128384, 2048, 1)
     assert split == esa.ESA_SPLIT_ALGORITHM1 and bf16 == esa.ESA_BF16
+
+
+ONCE_PER_DEVICE = """
+#include "per_device.h"
+static esa::OncePerDevice raised;          /* as the launches hold it: one per kernel, zero-initialised */
+int main(void) {
+  if (raised.done(0) || raised.done(1)) return 1;
+  raised.mark(1);
+  if (raised.done(0) || !raised.done(1) || raised.done(2)) return 2;      /* of this device only */
+  raised.mark(63); raised.mark(0);
+  if (!raised.done(0) || !raised.done(63) || raised.done(62)) return 3;
+  raised.mark(64); raised.mark(-1);
+  if (raised.done(64) || raised.done(-1)) return 4;                       /* beyond the bookkeeping: repeated */
+  return 0;
+}
+"""
+
+
+def test_what_is_done_once_is_done_once_on_every_device(tmp_path):
+    """The dynamic-LDS limit is a property of a kernel on a device: raised on one GPU, it is not taken for raised on another."""
+    src, exe = tmp_path / "once.cpp", tmp_path / "once"
+    src.write_text(ONCE_PER_DEVICE)
+    csrc = os.path.join(ROOT, "paper_2502_14477_amd", "csrc")
+    r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(src), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert subprocess.run([str(exe)], timeout=60).returncode == 0
+    for name in os.listdir(csrc):          # no launch keeps a flag of its own for all devices
+        assert not re.search(r"static bool \w+ *=", open(os.path.join(csrc, name)).read()), name
