@@ -194,19 +194,27 @@ int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dt
   }
   if (rows == 0) return ESA_OK;
   const Turns& turns = turns_for(base, d, step);
-  // Sixteen rows of eight heads share their sines and cosines best; eight where that would leave compute units without
-  // work (batch 8: 18.6 against 20.0 us; a chunk of 512 behind a window of 4096: 14.2 against 12.6 us).
-  auto most_groups = [&](int budget) {
-    int64_t most = 0;
+  // Groups of rows: of the longest job, and of all.
+  struct Groups {
+    int64_t most, all;
+  };
+  auto groups_of = [&](int budget) {
+    Groups g = {0, 0};
     for (int k = 0; k < n_jobs; ++k) {
       const int r = rows_of(jobs[k].heads, budget);
-      const int64_t g = (jobs[k].n_tok + r - 1) / r;
-      most = g > most ? g : most;
+      const int64_t n = (jobs[k].n_tok + r - 1) / r;
+      g.most = n > g.most ? n : g.most;
+      g.all += n;
     }
-    return most;
+    return g;
   };
-  const int budget = most_groups(128) * batch >= 512 ? 128 : 64;
-  const int64_t groups = most_groups(budget);
+  // Sixteen bf16 rows of eight heads share their sines and cosines best; eight where that would leave compute units without
+  // work (batch 8: 18.6 against 20.0 us; a chunk of 512 behind a window of 4096: 14.2 against 12.6 us), four where even
+  // those are fewer than two groups per compute unit (64 rows of 32 heads 5.1 -> 4.2, 512 of them 5.8 -> 5.2).  fp32 rows are
+  // twice as long: always eight (20000 rows 33.2 -> 26.7).
+  int budget = 64;
+  if (dtype == ESA_BF16) budget = groups_of(64).all * batch < 512 ? 32 : groups_of(128).most * batch >= 512 ? 128 : 64;
+  const int64_t groups = groups_of(budget).most;
   const dim3 grid((unsigned)groups, n_jobs, batch);
   const size_t lds = (size_t)kRopeRows * d * sizeof(double);
   // 16-byte accesses when every row of every job starts on a 16-byte boundary

@@ -309,10 +309,12 @@ def test_compress_packed_row_tiles(esa, B, n_tok, d_q, d_k, d_c):
             assert np.all(np.abs(to_f64(got[e]) - want) <= bf16_ulp(want) * 1.001)
 
 
-# a row or two of many heads, sixteen rows and one more, a step that is not one, positions on both sides of zero
+# a row or two of many heads, sixteen rows and one more, a step that is not one, positions on both sides of zero; one, eight and
+# sixteen rows to a workgroup
 @pytest.mark.parametrize("dtype,B,n_tok,heads,d,pos0,step", [("bf16", 1, 1, 32, 128, 70000.0, 1.0), ("bf16", 40, 33, 8, 64, -16.0, 1.0),
                                                               ("f32", 1, 17, 5, 256, 3.0, 2.5), ("bf16", 1, 19, 200, 128, 9.0, 1.0),
-                                                              ("f32", 2, 16, 1, 2, 100.0, 1.0)])
+                                                              ("f32", 2, 16, 1, 2, 100.0, 1.0), ("bf16", 1, 97, 32, 64, 5.0, 1.0),
+                                                              ("f32", 1, 4500, 8, 32, 0.0, 1.0), ("bf16", 2, 5001, 8, 32, 7.0, 1.0)])
 def test_rope_rows(esa, dtype, B, n_tok, heads, d, pos0, step):
     say(f"rope {dtype} B={B} n_tok={n_tok} heads={heads} d={d} pos0={pos0} step={step}")
     rng = np.random.default_rng(n_tok + heads)
