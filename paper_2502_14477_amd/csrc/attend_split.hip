@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      if (ml[w][q][1] > 0.f) {             // a wave that saw no key of this row left no output
+      if (ml[w][q][1] != 0.f) {            // a wave that saw no key of this row left no output (a sum that is no number counts)
         const float wt = exp_of<T>(ml[w][q][0] - M);
         L += wt * ml[w][q][1];
         const unsigned char* ot = (q < 16 ? k_st[w] : v_st[w]) + (q & 15) * (D * 4);
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(WPR == 1 ? 256 : 64 * WPR) void attend_split_merge(
   };
   request(w0);
   const float m = wave_max(fmaxf(a0.x, a1.x));
-  const float f0 = a0.y > 0.f ? exp_of<T>(a0.x - m) : 0.f, f1 = a1.y > 0.f ? exp_of<T>(a1.x - m) : 0.f;
+  const float f0 = a0.y != 0.f ? exp_of<T>(a0.x - m) : 0.f, f1 = a1.y != 0.f ? exp_of<T>(a1.x - m) : 0.f;
   const float l = wave_sum(__fmaf_rn(f0, a0.y, f1 * a1.y));
   float acc[kPer] = {};
   for (int s0 = w0; s0 < splits; s0 += 8 * WPR) {

@@ -247,6 +247,20 @@ def test_split_key_attention(esa, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel
         assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,d,l_C", [("bf16", 128, 1), ("bf16", 64, 5), ("f32", 64, 1), ("f32", 128, 40), ("bf16", 64, 40), ("bf16", 128, 40)])
+def test_a_key_that_is_no_number_is_not_left_out(esa, dtype, d, l_C):
+    """A NaN in one selected key reaches every output of its KV head's queries, and no other."""
+    say(f"NaN key {dtype} d={d} l_C={l_C}")
+    H, H_kv, t0, l_I, l_L, n_sel = 8, 2, 3000, 16, 130, 900
+    q, K, V, sel = attend_inputs(d + l_C, dtype, 1, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    K[0, sel[0, 17], 0, 3] = np.nan
+    Kd = torch.from_numpy(K[0]).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    O, lse = esa.esa_attend_indexed(f64_to_dev(q[0], dtype), Kd, f64_to_dev(V[0], dtype), t0, l_I, l_L, torch.from_numpy(sel[0]).cuda(),
+                                    return_lse=True)
+    assert torch.isnan(O[:, :H // H_kv]).all() and torch.isnan(lse[:, :H // H_kv]).all()
+    assert torch.isfinite(O[:, H // H_kv:]).all() and torch.isfinite(lse[:, H // H_kv:]).all()
+
+
 # S stored: a few queries on the matrix cores (one token, tile and workgroup remainders), every other shape in fp32 FMAs;
 # pooled by the finishing pass (windows up to 16) or by the pass of its own
 @pytest.mark.parametrize("dtype,B,l_c,n,d_c,eps", [
