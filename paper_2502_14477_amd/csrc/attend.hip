@@ -121,6 +121,11 @@ bool attend_in_range(int64_t rows, int64_t tok_stride, int64_t esz) {
   return rows <= (int64_t)INT32_MAX && tok_stride * esz < ((int64_t)1 << 32);
 }
 
+// Few keys of few fp32 rows: the plain kernel, one workgroup per token and head, is a single short launch (one key 4.0 to 4.9
+// us, 49 keys 4.6 to 8.9) where the split-key kernel stages tiles of 32 keys and merges its waves (5.2 to 10.0 us); from 97
+// keys, or 1024 workgroups, the split-key kernel is ahead (97 keys: 10.3 against 12.6 us with head size 128).
+bool attend_plain_is_enough(int dtype, int64_t keys, int64_t rows) { return dtype == ESA_F32 && keys <= 64 && rows <= 512; }
+
 constexpr int64_t kTwoCallMaxLocal = 65536;      // longer local parts of a two-call attention go to the plain kernel
 
 size_t generic_parts_bytes(int l_c, int h, int d, int batch) {
@@ -177,7 +182,8 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
   // per part and merges.
   if (part == kAttendLocal && !two_parts) return ESA_OK;
   // Few current tokens, or fp32.
-  const bool split_shape = attend_split_supported(l_c, h, h_kv, d, dtype, batch) && in_range;
+  const bool split_shape = attend_split_supported(l_c, h, h_kv, d, dtype, batch) && in_range &&
+                           (two_parts || !attend_plain_is_enough(dtype, n_fixed + l_c, (int64_t)l_c * h * batch));
   const bool split_two = dtype == ESA_BF16 && d == 128 && 8 % (h / h_kv) == 0 && t0 - sg.l_start + l_c <= kTwoCallMaxLocal;
   if (split_shape && (two_parts ? split_two : mfma_aligned)) {
     if (!mfma_aligned)

@@ -231,7 +231,9 @@ def test_scores_finished_by_the_selection_equal_the_separate_calls(esa, B, l_c, 
     ("bf16", 1, 8, 2, 64, 0, 1, 16, 64, 0), ("bf16", 2, 8, 2, 128, 700, 8, 16, 64, 33), ("bf16", 1, 8, 1, 128, 900, 5, 7, 129, 300),
     ("bf16", 40, 16, 8, 64, 300, 15, 3, 70, 90), ("bf16", 3, 6, 2, 128, 500, 11, 0, 31, 1), ("bf16", 1, 32, 8, 128, 9000, 2, 128, 2048, 2048),
     ("f32", 1, 4, 2, 32, 700, 130, 16, 64, 100), ("f32", 2, 6, 2, 64, 400, 11, 0, 31, 1), ("f32", 1, 8, 1, 128, 600, 33, 7, 129, 300),
-    ("f32", 1, 4, 2, 128, 0, 3, 7, 129, 0), ("f32", 1, 4, 2, 64, 5000, 1, 32, 2500, 1000)])
+    ("f32", 1, 4, 2, 128, 0, 3, 7, 129, 0), ("f32", 1, 4, 2, 64, 5000, 1, 32, 2500, 1000),
+    ("f32", 1, 4, 2, 64, 60, 4, 7, 129, 0), ("f32", 1, 4, 2, 64, 60, 5, 7, 129, 0), ("f32", 2, 32, 8, 32, 100, 8, 3, 20, 30),
+    ("f32", 2, 32, 8, 32, 100, 9, 3, 20, 30)])
 def test_split_key_attention(esa, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
     say(f"split attend {dtype} B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
     q, K, V, sel = attend_inputs(d + l_C, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
