@@ -132,7 +132,8 @@ ESA_API int esa_select_topk(const float* score, int64_t n, int k, int64_t base,
  * kernels fewer than the three calls: the kernel that writes the scores (Eq. 4, or Eq. 8's pooling
  * pass when eps > 0) also leaves the first digit histogram of the radix selection (Eq. 2) while the
  * scores are still on chip, and the zero-fill of the histograms rides on an earlier kernel of the
- * score call.
+ * score call.  Up to 8192 middle tokens are selected from by one kernel, which also finishes the scores
+ * where the score call would need a kernel of its own for that.
  * Results are those of the separate calls, bit for bit.
  *   score    [batch][m_hi-m_lo] fp32, written as by esa_score; if k >= m_hi-m_lo every middle token is
  *            selected, nothing is scored and `score` is left untouched (it may then be NULL)
@@ -140,8 +141,9 @@ ESA_API int esa_select_topk(const float* score, int64_t n, int k, int64_t base,
  *   k_cache, v_cache, k_sel, v_sel, tok_stride, h_kv, d, cache_bs, sel_bs as in esa_gather_kv; pass all
  *            four pointers as NULL to skip the gather
  *   workspace esa_score_select_gather_workspace_bytes(l_c, m_hi-m_lo, eps, k, batch) bytes, 256-byte aligned
- * Shapes outside the fused kernels (fp32, d_c other than 64/128/256) run the kernels of the three
- * calls in sequence.  m_hi == m_lo or k == 0 is a no-op.
+ * Shapes that neither a fused kernel nor stored scores serve (d_c other than 64/128/256 or fp32, with more than
+ * 16 tokens and more than 16 MiB of scores) run the kernels of the three calls in sequence.  m_hi == m_lo or
+ * k == 0 is a no-op.
  */
 ESA_API size_t esa_score_select_gather_workspace_bytes(int l_c, int64_t n_mid, int eps, int k, int batch);
 ESA_API int esa_score_select_gather(const void* qc, int l_c,

@@ -54,7 +54,9 @@ constexpr int kRows = 256;          // query rows per workgroup
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxSlots = 16;           // partial results per row
-constexpr int kMaxSplits = 16;          // slices of the key sequence, one-call form
+// Slices of the key sequence, one-call form.  Short chunks need sixteen to fill the chip (77 tokens at 50k: 61 -> 55.6 us a
+// step against eight); their fp16 results err independently (outputs 2.27e-3 from the 64-bit result, 2.31e-3 with eight).
+constexpr int kMaxSplits = 16;
 constexpr int kMaxSelSplits = 8;        // two-call form: at most half as many local slices, then the selected ones
 constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
 constexpr float kLog2e = 1.4426950408889634f;
@@ -129,7 +131,8 @@ template <int D> __device__ __forceinline__ uint32_t v_swizzle(uint32_t row) { r
 
 // Head size 64 keeps what it computes in fp32: a probability goes into the second product as three bf16 terms, which
 // together are its fp32 value, and the results of a slice are stored as they were accumulated.  (One term and fp16 slices,
-// as for head size 128, put the outputs 2.3e-3 from the 64-bit result where rounding them to bf16 alone makes 1.66e-3.)
+// as for head size 128, put the outputs 2.3e-3 from the 64-bit result where rounding them to bf16 alone makes 1.66e-3; a
+// step of 512 tokens at 32k takes 81 us for it, 63 with the narrow formats.)
 template <int D> constexpr bool kFp32Probs = D == 64;
 // Natural-log normaliser from a reference in the log2 domain and the sum of exponentials relative to it.  The fp32 form
 // adds the logarithm in its own domain, one rounding of the sum instead of two.
