@@ -115,7 +115,7 @@ def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
 
 
 def _bin_crowd(rng, n, crowd, kind):
-    """Scores of which `crowd` lie so close below -1 that they share one bin of the first histogram."""
+    """Scores of which `crowd` lie so close below -1 that they share a bin of a short row's histogram and the first digits of a long row's."""
     s = (-2.0 - rng.random(n) * 60.0).astype(np.float32)
     at = rng.choice(n, crowd, replace=False) if kind != "run" else np.arange(n // 3, n // 3 + crowd)
     s[at] = np.float32(-1.0) - (np.float32(0.0) if kind == "equal" else rng.random(crowd).astype(np.float32) * np.float32(2 ** -7))

@@ -335,7 +335,7 @@ def test_score_batched_with_two_blocks_of_queries(esa):
     ("bf16", 4, 1, 9000, 128, 0, 500, 2, 64, 0),            # decode, batched
     ("bf16", 1, 700, 70000, 128, 3, 2048, 2, 128, 0),       # more than one block of queries
     ("bf16", 1, 33, 4097, 64, 0, 64, 2, 64, 4),             # plain score kernel; cache rows not 16-byte aligned
-    ("f32", 2, 16, 3000, 32, 10, 256, 2, 64, 0),            # fp32: plain kernels throughout
+    ("f32", 2, 16, 3000, 32, 10, 256, 2, 64, 0),            # fp32: stored scores, one selection launch
     ("bf16", 1, 64, 900, 128, 5, 2048, 2, 128, 0),          # k covers the middle: nothing is scored
     ("bf16", 1, 512, 2049, 128, 128, 2048, 8, 128, 0)])     # all but one selected
 def test_score_select_gather_equals_the_three_calls(esa, dtype, B, l_c, n, d_c, m_lo, k, h_kv, d, pad):
@@ -427,9 +427,9 @@ def test_score_select_gather_with_massive_ties(esa):
     ("bf16", 32, 8, 128, 6000, 5999, 1, 128, 2048, 2048),
     ("bf16", 32, 8, 128, 40, 39, 1, 128, 2048, 0),       # decode, fewer keys than one slice
     ("bf16", 8, 8, 128, 3000, 2990, 3, 16, 500, 200),    # three current tokens (causal inside C), G = 1
-    ("bf16", 16, 2, 128, 2500, 2485, 15, 8, 300, 1000),  # G = 8, largest chunk of the decode kernel
+    ("bf16", 16, 2, 128, 2500, 2485, 15, 8, 300, 1000),  # G = 8, largest chunk of the split-key kernel
     ("bf16", 4, 2, 128, 150000, 149999, 1, 128, 120000, 0),  # slices near their maximum length
-    ("bf16", 4, 2, 128, 150000, 149999, 1, 128, 140000, 0),  # more keys than the decode kernel covers
+    ("bf16", 4, 2, 128, 150000, 149999, 1, 128, 140000, 0),  # many keys for one token
     ("bf16", 8, 2, 128, 1500, 1203, 77, 16, 100, 55),    # ragged sizes
     ("bf16", 4, 4, 128, 2300, 2000, 300, 16, 700, 333),  # matrix-core kernel, one query head per KV head
     ("bf16", 4, 2, 128, 1900, 1700, 200, 16, 500, 100),  # two query heads per KV head
@@ -651,9 +651,9 @@ def test_rope_matches_the_fp64_definition_rounded_once(esa, dtype, B, n_tok, hea
     ("bf16", 1, 8, 2, 128, 40, 32, 16, 300, 0),         # early chunk: no middle tokens, I and L touch
     ("bf16", 1, 8, 2, 128, 0, 64, 16, 300, 0),          # first chunk: nothing but C
     ("bf16", 1, 32, 8, 128, 5000, 20, 128, 8, 2048),    # short chunk, hardly any local keys: sixteen slices in all
-    ("f32", 1, 4, 2, 64, 900, 100, 8, 64, 31),          # plain kernel, one launch per part
+    ("f32", 1, 4, 2, 64, 900, 100, 8, 64, 31),          # split-key kernel, both parts in one launch
     ("f32", 2, 4, 2, 64, 900, 7, 8, 64, 31),
-    ("bf16", 1, 8, 2, 128, 2999, 1, 16, 256, 128),      # decode shape: split-key kernel, one launch per part
+    ("bf16", 1, 8, 2, 128, 2999, 1, 16, 256, 128),      # decode shape: split-key kernel
     ("bf16", 3, 32, 8, 128, 6000, 2, 128, 2048, 2048),  # decode, batched, Llama shape
     ("bf16", 2, 8, 2, 128, 40, 3, 16, 300, 0),          # decode in an early chunk: the global part is I alone
     ("bf16", 1, 8, 8, 128, 0, 5, 16, 300, 0)])          # decode at the very start: no global keys at all
@@ -686,8 +686,8 @@ def test_attend_reencoded_from_unencoded_queries_and_caches(esa, dtype, B, H, H_
 @pytest.mark.parametrize("dtype,B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
     ("bf16", 1, 32, 8, 128, 5999, 1, 128, 2048, 2048),   # decode: indices followed inside the kernel
     ("bf16", 3, 8, 2, 128, 2999, 2, 16, 256, 128),
-    ("bf16", 2, 8, 2, 128, 1400, 96, 16, 300, 200),      # matrix-core kernel: gathers into its workspace first
-    ("f32", 1, 4, 2, 64, 900, 100, 8, 64, 31),           # plain kernel
+    ("bf16", 2, 8, 2, 128, 1400, 96, 16, 300, 200),      # matrix-core kernel
+    ("f32", 1, 4, 2, 64, 900, 100, 8, 64, 31),           # split-key kernel
     ("bf16", 1, 8, 2, 128, 300, 1, 16, 400, 0)])         # nothing selected
 def test_attend_indexed_equals_gather_then_attend(esa, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
     say(f"attend_indexed dtype={dtype} B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} n_sel={n_sel}")
@@ -718,7 +718,7 @@ def test_attend_indexed_equals_gather_then_attend(esa, dtype, B, H, H_kv, d, t0,
 @pytest.mark.parametrize("l_C", [1, 3, 96])
 def test_attend_indexed_clamps_indices_that_leave_the_cache(esa, l_C):
     """Entries below 0 or at or beyond the local window's start cannot be selected tokens; the kernels
-    clamp them into [0, l_start) instead of following them (decode kernel and matrix-core kernel alike)."""
+    clamp them into [0, l_start) instead of following them (split-key kernel and matrix-core kernel alike)."""
     say(f"attend_indexed with out-of-range entries, l_C={l_C}")
     rng = np.random.default_rng(31 + l_C)
     H, H_kv, d, t0, l_I, l_L, n_sel = 8, 2, 128, 1500, 16, 300, 200
@@ -1026,7 +1026,7 @@ def test_variant_calls_captured_as_a_graph_replay_identically(esa):
 
 @pytest.mark.parametrize("l_C,pad,n_sel", [(64, 64, 100),      # matrix-core kernel, token rows wider than h_kv*d
                                            (64, 4, 100),       # rows not 16-byte aligned: the plain kernel
-                                           (1, 64, 100),       # decode kernel
+                                           (1, 64, 100),       # split-key kernel
                                            (48, 64, 0)])
 def test_attend_reads_caches_with_padded_token_rows(esa, l_C, pad, n_sel):
     """The caches as strided views (tok_stride > h_kv*d), for every attention form; the padding holds
