@@ -540,10 +540,15 @@ __global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restri
 // ------------------------------------------------------------------------------------------ decode (l_c = 1)
 // One current token: S is a matrix-vector product over the whole compressed-key cache, pure HBM
 // streaming.  LPR lanes share a K' row (16 bytes each), so a wave reads 64*16 contiguous bytes per
-// step; a workgroup covers 256 rows with all its steps' loads in flight.  Writes S and the workgroup's maximum of it (no atomics: thousands of
+// step; a workgroup covers 64 or 256 rows.  Writes S and the workgroup's maximum of it (no atomics: thousands of
 // workgroups folding into one word serialise in L2); score_finish then reduces those maxima to mu,
 // every workgroup for itself, and forms F = S - mu.
-constexpr int kGemvRows = 256;           // rows per workgroup
+// ROWS per workgroup.  256: the loads stand behind their bounds checks, each step a round trip of its own, which the
+// sixteen waves of a compute unit hide from one another.  Few rows in all do not give a compute unit so many waves: 64,
+// all requested before the first use.  Score and selection of one token, us, 256 against 64 rows: 3 thousand rows 11.2
+// against 8.3, 12 thousand 19.5 / 16.6, 100 thousand 22.2 / 18.6, 4 x 20 thousand 22.1 / 18.4; 200 thousand 25.1 / 25.4,
+// 8 x 63 thousand 37.4 / 37.1, where the longer list of partial maxima takes back what is left to gain.
+constexpr int64_t kGemvFewRows = 131072;
 // grids of the passes over the scores (host and device agree on them; the kernels do not ask the dispatch packet)
 __host__ __device__ inline int maxpool_blocks(int64_t n) { return (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096); }
 
@@ -566,15 +571,15 @@ __device__ __forceinline__ float lanes_max16(float v) {
   return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true)));
 }
 
-template <int LPR>
+template <int LPR, int ROWS>
 __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict__ qc, const bf16_t* __restrict__ kc,
                                                        int64_t m_lo, int64_t n, float* __restrict__ part,
                                                        float* __restrict__ raw, int64_t q_bs, int64_t kc_bs,
                                                        int64_t raw_bs, uint32_t* __restrict__ hists, int64_t hists_bs) {
   constexpr int kDcv = LPR * 8;
   constexpr int kRowsPerStep = 256 / LPR;
-  constexpr int kGemvSteps = kGemvRows / kRowsPerStep;
-  const int n_wg = (int)((n + kGemvRows - 1) / kGemvRows);           // workgroups per batch entry (the launch's grid)
+  constexpr int kSteps = ROWS / kRowsPerStep;
+  const int n_wg = (int)((n + ROWS - 1) / ROWS);           // workgroups per batch entry (the launch's grid)
   __shared__ float red[4];
   const int b = __builtin_amdgcn_workgroup_id_y();
   if (hists)       // the selection's histograms, zeroed here for the pass that follows
@@ -591,12 +596,8 @@ __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict_
     qv[6] = __uint_as_float(u.w << 16); qv[7] = __uint_as_float(u.w & 0xFFFF0000u);
   }
   float best = -INFINITY;
-  const int64_t row0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * kGemvRows;
-#pragma unroll
-  for (int it = 0; it < kGemvSteps; ++it) {
-    const int64_t row = row0 + it * kRowsPerStep + grp;
-    uint4 u = make_uint4(0u, 0u, 0u, 0u);
-    if (row < n) u = *(const uint4*)(kmid + row * kDcv + sub * 8);
+  const int64_t row0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * ROWS + grp;
+  auto finish = [&](const uint4& u, int64_t row) {
     float s = qv[0] * __uint_as_float(u.x << 16);
     s = __fmaf_rn(qv[1], __uint_as_float(u.x & 0xFFFF0000u), s);
     s = __fmaf_rn(qv[2], __uint_as_float(u.y << 16), s);
@@ -609,6 +610,24 @@ __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict_
     if (row < n) {
       if (sub == 0) raw[(int64_t)b * raw_bs + row] = s;
       best = fmaxf(best, s);
+    }
+  };
+  if constexpr (ROWS == 64) {              // every row requested before the first is used: with few workgroups nothing else hides a round trip
+    uint4 u[kSteps];
+#pragma unroll
+    for (int it = 0; it < kSteps; ++it) {
+      const int64_t row = row0 + it * kRowsPerStep;
+      u[it] = *(const uint4*)(kmid + (row < n ? row : n - 1) * kDcv + sub * 8);
+    }
+#pragma unroll
+    for (int it = 0; it < kSteps; ++it) finish(u[it], row0 + it * kRowsPerStep);
+  } else {
+#pragma unroll
+    for (int it = 0; it < kSteps; ++it) {
+      const int64_t row = row0 + it * kRowsPerStep;
+      uint4 u = make_uint4(0u, 0u, 0u, 0u);
+      if (row < n) u = *(const uint4*)(kmid + row * kDcv + sub * 8);
+      finish(u, row);
     }
   }
   best = wave_max(best);
@@ -1024,8 +1043,10 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     pool_left = eps > 0 && !narrow;
   };
   if (vec_ok && l_c == 1 && (d_c == 64 || d_c == 128 || d_c == 256)) {
-    const int nblk = (int)((n + kGemvRows - 1) / kGemvRows);
-    const auto gemv = d_c == 64 ? score_gemv_bf16<8> : d_c == 128 ? score_gemv_bf16<16> : score_gemv_bf16<32>;
+    const bool few_rows = n * batch <= kGemvFewRows;
+    const int rows = few_rows ? 64 : 256, nblk = (int)((n + rows - 1) / rows);
+    const auto gemv = few_rows ? (d_c == 64 ? score_gemv_bf16<8, 64> : d_c == 128 ? score_gemv_bf16<16, 64> : score_gemv_bf16<32, 64>)
+                               : (d_c == 64 ? score_gemv_bf16<8, 256> : d_c == 128 ? score_gemv_bf16<16, 256> : score_gemv_bf16<32, 256>);
     gemv<<<dim3((unsigned)nblk, batch), 256, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
                                                       first_hist, first_hist_bs);
     if (tail && narrow) {

@@ -212,6 +212,19 @@ def test_selection_time_does_not_depend_on_one_large_query(esa, l_c):
     assert np.array_equal(idx.cpu().numpy(), np.sort(order))
 
 
+# a workgroup's 64 rows, one less, one more, a single row; the most rows in all of that kernel and one more
+@pytest.mark.parametrize("B,n,d_c", [(1, 1, 128), (3, 63, 64), (2, 64, 256), (5, 65, 128), (1, 131072, 64), (1, 131073, 64)])
+def test_score_of_one_token_in_workgroups_of_64_rows_and_of_256(esa, B, n, d_c):
+    say(f"score l_c=1 B={B} n={n} d_c={d_c}")
+    rng = np.random.default_rng(n + d_c)
+    qc = orc.round_to_storage(rng.standard_normal((B, 1, d_c)), "bf16")
+    kc = orc.round_to_storage(rng.standard_normal((B, n + 3, d_c)), "bf16")
+    got = to_f64(esa.esa_score(f64_to_dev(qc, "bf16"), f64_to_dev(kc, "bf16"), 2, 2 + n))
+    for b in range(B):
+        assert np.max(np.abs(got[b] - orc.importance(qc[b], kc[b, 2:2 + n]))) <= F_TOL["bf16"], b
+        assert got[b].max() == 0.0
+
+
 @pytest.mark.parametrize("B,l_c,n,d_c,k,eps", [(2, 1, 8192, 128, 2048, 0), (3, 1, 8192, 128, 100, 3), (1, 1, 8193, 128, 2048, 3),
                                                (1, 33, 8192, 64, 1, 16), (2, 40, 2050, 128, 2048, 17), (2, 1, 1025, 128, 1024, 1)])
 def test_scores_finished_by_the_selection_equal_the_separate_calls(esa, B, l_c, n, d_c, k, eps):
