@@ -75,7 +75,7 @@ struct AttendArgs {
   int l_c, h, h_kv, group, group_log2;
   int qpt, n_qt;                    // tokens per row tile (a whole number of waves' rows, at most 256 rows), row tiles
   int batch;
-  int xcd_mapping;                  // 1: (batch, KV head) pairs are a multiple of 8
+  PairGrid grid;
   int n_slot;         // slots per row in the partial-result arrays
   int to_slots;       // 1: write partial results even when the launch has a single slice
   float c2;           // scale * log2(e)
@@ -163,18 +163,8 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
 
   // ---- which (batch element, KV head, row tile, key slice) is this workgroup
   const int n_slices = a.view[0].n_split + a.view[1].n_split;
-  const int per_pair = a.n_qt * n_slices;
-  int pair, inner;
-  if (a.xcd_mapping) {                 // consecutive workgroup ids go to consecutive XCDs
-    const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-    pair = xcd + 8 * (k / per_pair);
-    inner = k % per_pair;
-  } else {
-    pair = blockIdx.x / per_pair;
-    inner = blockIdx.x % per_pair;
-  }
-  const int b = pair / a.h_kv, g = pair % a.h_kv;
-  const int qt = inner % a.n_qt, slice = inner / a.n_qt;
+  const Placed at = place_in(a.grid);
+  const int b = at.pair / a.h_kv, g = at.pair - b * a.h_kv, qt = at.row_tile, slice = at.slice;
   const int vw = slice >= a.view[0].n_split ? 1 : 0;             // which view this slice belongs to
   const KeyView V = pick_view(a.view, vw);
   const int split = slice - (vw ? a.view[0].n_split : 0);        // slice number inside the view
@@ -189,8 +179,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const int c_last = (q0 + a.qpt < a.l_c ? q0 + a.qpt : a.l_c) - 1;
   const uint32_t n_vis = V.n_fixed + (V.with_chunk ? c_last + 1 : 0);   // keys the tile's last token sees
   const uint32_t n_tiles = (n_vis + kKT - 1) / kKT;
-  const uint32_t tile_begin = (uint32_t)((uint64_t)n_tiles * split / V.n_split);
-  const uint32_t tile_end = (uint32_t)((uint64_t)n_tiles * (split + 1) / V.n_split);
+  const uint32_t tile_begin = slice_tile(V, n_tiles, split), tile_end = slice_tile(V, n_tiles, split + 1);
   const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
 
   // ---- this wave's 32 rows (32/G consecutive current tokens, the group's heads of each), one per lane (both half-waves)
@@ -619,6 +608,14 @@ int choose_splits(int l_c, int group, int h_kv, int batch) {
   return (int)(ns < 1 ? 1 : (ns > kMaxSplits ? kMaxSplits : ns));
 }
 
+void launch_tiles(AttendArgs& a, int d, int n_slices, hipStream_t st) {
+  for_pair_grids((int64_t)a.batch * a.h_kv, a.n_qt, n_slices, [&](dim3 grid, PairGrid placed) {
+    a.grid = placed;
+    if (d == 128) attend_mfma_bf16<128><<<grid, kThreads, 0, st>>>(a);
+    else attend_mfma_bf16<64><<<grid, kThreads, 0, st>>>(a);
+  });
+}
+
 template <int D, int NS = 1>
 void launch_merge(const AttendArgs& a, int ns_a, int slot_b, int ns_b, hipStream_t st) {
   if (ns_a + ns_b != NS) {                       // 1 ... kMaxSlots slots in all
@@ -704,7 +701,6 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
   a.sel_bs_bytes = sel_bs * 2;
-  a.xcd_mapping = ((batch * h_kv) % 8 == 0) ? 1 : 0;
 
   const SplitPlan plan = plan_splits(l_c, a.group, h_kv, batch);
   const int first_rows = l_c < a.qpt ? l_c : a.qpt;
@@ -728,10 +724,7 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.n_slot = n_slot;
   const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
   a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0, 0, 0);   // unused
-  auto launch = [&](int64_t n_wg) {
-    if (d == 128) attend_mfma_bf16<128><<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a);
-    else attend_mfma_bf16<64><<<dim3((unsigned)n_wg), kThreads, 0, st>>>(a);
-  };
+  auto launch = [&](int n_slices) { launch_tiles(a, d, n_slices, st); };
   auto merge = [&](int ns_a, int slot_b, int ns_b) {
     if (d == 128) launch_merge<128>(a, ns_a, slot_b, ns_b, st);
     else launch_merge<64>(a, ns_a, slot_b, ns_b, st);
@@ -740,17 +733,17 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
     a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, ns_all, 0, sel_idx, idx_bs,
                           l_start);
     a.to_slots = 0;
-    launch((int64_t)batch * h_kv * a.n_qt * ns_all);
+    launch(ns_all);
     if (ns_all > 1) merge(ns_all, 0, 0);
   } else if (part == kAttendLocal) {
     a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1, ns_local, 0);
     a.to_slots = 1;
-    launch((int64_t)batch * h_kv * a.n_qt * ns_local);
+    launch(ns_local);
   } else {
     if (ns_sel > 0) {
       a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, ns_sel, plan.local, sel_idx, idx_bs, l_start);
       a.to_slots = 1;
-      launch((int64_t)batch * h_kv * a.n_qt * ns_sel);
+      launch(ns_sel);
     }
     merge(ns_local, plan.local, ns_sel);
   }
@@ -786,7 +779,6 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
   a.sel_bs_bytes = sel_bs * 2;
-  a.xcd_mapping = ((batch * h_kv) % 8 == 0) ? 1 : 0;
   // the planned number of slices (two where one is planned) is shared out in proportion to the two parts' lengths, at
   // least one each: never more than kMaxSlots, nor more than the workspace holds
   const SplitPlan plan = plan_splits(l_c, a.group, h_kv, batch);
@@ -812,9 +804,7 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.to_slots = 0;
   a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1, ns_a, 0);
   a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0, ns_b, ns_a);
-  const dim3 grid((unsigned)((int64_t)batch * h_kv * a.n_qt * n_slot));
-  if (d == 128) attend_mfma_bf16<128><<<grid, kThreads, 0, st>>>(a);
-  else attend_mfma_bf16<64><<<grid, kThreads, 0, st>>>(a);
+  launch_tiles(a, d, n_slot, st);
   if (n_slot > 1) {
     if (d == 128) launch_merge<128>(a, n_slot, 0, 0, st);
     else launch_merge<64>(a, n_slot, 0, 0, st);

@@ -72,9 +72,10 @@ struct SplitArgs {
   const char* k_sel;
   const char* v_sel;
   uint32_t sel_bytes;
-  int l_c, h, h_kv, group, n_rt;      // n_rt: row tiles of a KV head
+  int l_c, h, h_kv, n_rt;             // n_rt: row tiles of a KV head
+  int group, group_log2;              // query heads of a KV head, their logarithm (-1: no power of two)
   int n_slot, to_slots;
-  int xcd_mapping;
+  PairGrid grid;
   float scale;                        // includes log2(e) for bf16
   int64_t out_bs, sel_bs_bytes;
 };
@@ -126,20 +127,10 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // ---- which (batch element, KV head, row tile, slice); row tiles of one KV head share its keys: same XCD
+  // ---- which (batch element, KV head, row tile, slice)
   const int n_slices = a.view[0].n_split + a.view[1].n_split;
-  const int per_pair = a.n_rt * n_slices;
-  int pair, inner;
-  if (a.xcd_mapping) {
-    const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-    pair = xcd + 8 * (k / per_pair);
-    inner = k % per_pair;
-  } else {
-    pair = blockIdx.x / per_pair;
-    inner = blockIdx.x % per_pair;
-  }
-  const int b = pair / a.h_kv, g = pair % a.h_kv;
-  const int rt = inner % a.n_rt, slice = inner / a.n_rt;
+  const Placed at = place_in(a.grid);
+  const int b = at.pair / a.h_kv, g = at.pair - b * a.h_kv, rt = at.row_tile, slice = at.slice;
   const bool second = slice >= a.view[0].n_split;
   const KeyView V = pick_view(a.view, second);
   const int split = slice - (second ? a.view[0].n_split : 0);
@@ -153,12 +144,11 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   // ---- rows: one per lane (both half-waves)
   const int n_rows = a.l_c * a.group;
   const int row = rt * kRows + r, rr = row < n_rows ? row : n_rows - 1;     // rows past the end repeat the last one
-  const int c = rr / a.group, head = g * a.group + rr % a.group;
+  const int c = a.group_log2 >= 0 ? rr >> a.group_log2 : rr / a.group, head = g * a.group + rr - c * a.group;
   const int row_last = rt * kRows + kRows - 1 < n_rows ? rt * kRows + kRows - 1 : n_rows - 1;
-  const uint32_t n_vis = V.n_fixed + (V.with_chunk ? row_last / a.group + 1 : 0);     // keys the tile's last row sees
+  const uint32_t n_vis = V.n_fixed + (V.with_chunk ? (a.group_log2 >= 0 ? row_last >> a.group_log2 : row_last / a.group) + 1 : 0);     // keys the tile's last row sees
   const uint32_t n_tiles = (n_vis + kKT - 1) / kKT;
-  const uint32_t tile_begin = (uint32_t)((uint64_t)n_tiles * split / V.n_split);
-  const uint32_t tile_end = (uint32_t)((uint64_t)n_tiles * (split + 1) / V.n_split);
+  const uint32_t tile_begin = slice_tile(V, n_tiles, split), tile_end = slice_tile(V, n_tiles, split + 1);
   const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
   const uint32_t vis = V.n_fixed + (V.with_chunk ? c + 1 : 0);
   const uint32_t lim = vis < k_end ? vis : k_end;                           // first virtual key this lane's row may NOT see
@@ -543,7 +533,7 @@ SplitArgs make_args(const SplitCall& c) {
   a.h_kv = c.h_kv;
   a.group = c.h / c.h_kv;
   a.n_rt = row_tiles(c.l_c, c.h, c.h_kv);
-  a.xcd_mapping = (c.batch * c.h_kv) % 8 == 0 ? 1 : 0;
+  a.group_log2 = (a.group & (a.group - 1)) == 0 ? __builtin_ctz(a.group) : -1;
   a.scale = c.dtype == ESA_F32 ? c.scale : c.scale * kLog2e;
   a.out_bs = c.out_bs;
   a.sel_bs_bytes = c.sel_bs * esz;
@@ -559,9 +549,12 @@ int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
 }
 
 template <typename T, int D>
-void run(const SplitCall& c, const SplitArgs& a, hipStream_t st) {
-  const int64_t wgs = (int64_t)c.batch * c.h_kv * a.n_rt * (a.view[0].n_split + a.view[1].n_split);
-  attend_split<T, D><<<dim3((unsigned)wgs), 64 * kWaves, 0, st>>>(a);
+void run(const SplitCall& c, const SplitArgs& args, hipStream_t st) {
+  SplitArgs a = args;
+  for_pair_grids((int64_t)c.batch * c.h_kv, a.n_rt, a.view[0].n_split + a.view[1].n_split, [&](dim3 grid, PairGrid placed) {
+    a.grid = placed;
+    attend_split<T, D><<<grid, 64 * kWaves, 0, st>>>(a);
+  });
 }
 template <typename T, int D>
 void merge(const SplitCall& c, const SplitArgs& a, int splits, hipStream_t st) {
@@ -628,11 +621,9 @@ int launch_attend_split(const SplitCall& c, KeyView v0, const KeyView* v1, hipSt
   }
   n0 = split_count(n0, k0);
   a.view[0] = v0;
-  a.view[0].n_split = n0;
-  a.view[0].slot0 = 0;
+  set_splits(&a.view[0], n0, 0);
   a.view[1] = k1 > 0 ? *v1 : v0;
-  a.view[1].n_split = n1;
-  a.view[1].slot0 = n0;
+  set_splits(&a.view[1], n1, n0);
   if (n0 + n1 > 1) {
     const int rc = with_slots(&a, c, n0 + n1);
     if (rc != ESA_OK) return rc;
@@ -650,10 +641,9 @@ int launch_attend_split_early(const SplitCall& c, KeyView early, int64_t early_k
   if (rc != ESA_OK) return rc;
   a.to_slots = 1;
   a.view[0] = early;
-  a.view[0].n_split = split_count(limit, early_keys);
-  a.view[0].slot0 = 0;
+  set_splits(&a.view[0], split_count(limit, early_keys), 0);
   a.view[1] = early;
-  a.view[1].n_split = 0;
+  set_splits(&a.view[1], 0, 0);
   dispatch(c, RunIt{c, a, st});
   ESA_LAUNCH_CHECK("attend_split (early part)");
   return ESA_OK;
@@ -666,10 +656,9 @@ int launch_attend_split_late(const SplitCall& c, KeyView late, int64_t late_keys
   if (rc != ESA_OK) return rc;
   a.to_slots = 1;
   a.view[0] = late;
-  a.view[0].n_split = late_keys > 0 ? split_count(limit, late_keys) : 0;
-  a.view[0].slot0 = n_early;
+  set_splits(&a.view[0], late_keys > 0 ? split_count(limit, late_keys) : 0, n_early);
   a.view[1] = late;
-  a.view[1].n_split = 0;
+  set_splits(&a.view[1], 0, 0);
   if (late_keys > 0) dispatch(c, RunIt{c, a, st});
   dispatch(c, MergeIt{c, a, n_early + a.view[0].n_split, st});
   ESA_LAUNCH_CHECK("attend_split (late part)");

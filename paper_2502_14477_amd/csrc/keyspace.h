@@ -52,8 +52,43 @@ struct KeyView {
   uint32_t idx_limit;                     // indices are clamped into [0, idx_limit)
   int with_chunk;                         // 1: the virtual sequence ends with the current chunk (causal); 0: every key is visible to every row
   int n_split;                            // slices of this view (view 0's slices come first)
+  uint32_t split_step;                    // 2^32 / n_split, rounded up (set_splits)
   int slot0;                              // partial results of slice s go to slot slot0 + s
 };
+
+static inline void set_splits(KeyView* v, int n_split, int slot0) {
+  v->n_split = n_split;
+  v->split_step = n_split > 1 ? (uint32_t)((((uint64_t)1 << 32) + n_split - 1) / n_split) : 0u;
+  v->slot0 = slot0;
+}
+// First of n_tiles tiles of slice s (s = n_split: behind the last): n_tiles s / n_split without a division, which as a 64-bit
+// one was a third of the instructions in front of a kernel's first load.
+__device__ __forceinline__ uint32_t slice_tile(const KeyView& v, uint32_t n_tiles, uint32_t s) {
+  return s >= (uint32_t)v.n_split ? n_tiles : __umulhi(n_tiles, s * v.split_step);
+}
+
+// The grid of the tiled kernels: workgroups of one (batch entry, KV head) pair on one XCD (workgroup w runs on XCD w % 8) where
+// the pairs are a multiple of eight, decoded without a division.  x: 8 row tiles' worth of XCDs, or the row tiles; y: slices;
+// z: pairs / 8, or the pairs.
+struct PairGrid {
+  int xcd_log2;                           // 3, or 0
+  int pair0;                              // first pair of this launch
+};
+template <typename Launch>                // launch(grid, PairGrid)
+static inline void for_pair_grids(int64_t pairs, int64_t row_tiles, int n_slices, Launch&& launch) {
+  PairGrid g = {pairs % 8 == 0 ? 3 : 0, 0};
+  const int64_t z = pairs >> g.xcd_log2;
+  for (int64_t z0 = 0; z0 < z; z0 += 65535) {         // (65535: the most that a grid takes in z)
+    g.pair0 = (int)(z0 << g.xcd_log2);
+    launch(dim3((unsigned)(row_tiles << g.xcd_log2), (unsigned)n_slices, (unsigned)(z - z0 < 65535 ? z - z0 : 65535)), g);
+  }
+}
+struct Placed {
+  int pair, row_tile, slice;
+};
+__device__ __forceinline__ Placed place_in(const PairGrid& g) {
+  return {g.pair0 + (int)((blockIdx.z << g.xcd_log2) | (blockIdx.x & ((1u << g.xcd_log2) - 1))), (int)(blockIdx.x >> g.xcd_log2), (int)blockIdx.y};
+}
 
 struct CacheRef {               // cache rows as a launch function gets them (strides in elements)
   const void *k, *v;
@@ -79,8 +114,7 @@ static inline KeyView make_view(const void* q, int64_t q_bs, const CacheRef& c, 
   v.idx_bs = idx_bs;
   v.idx_limit = (uint32_t)(idx_limit > 0 ? idx_limit : 1);
   v.with_chunk = with_chunk;
-  v.n_split = n_split;
-  v.slot0 = slot0;
+  set_splits(&v, n_split, slot0);
   return v;
 }
 // Field-wise select of the view a workgroup works on (not an indexed load): every kernel argument is then fetched in
@@ -105,6 +139,7 @@ __device__ __forceinline__ KeyView pick_view(const KeyView (&view)[2], bool seco
   V.idx_limit = second ? v1.idx_limit : v0.idx_limit;
   V.with_chunk = second ? v1.with_chunk : v0.with_chunk;
   V.n_split = second ? v1.n_split : v0.n_split;
+  V.split_step = second ? v1.split_step : v0.split_step;
   V.slot0 = second ? v1.slot0 : v0.slot0;
   return V;
 }

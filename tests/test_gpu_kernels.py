@@ -212,6 +212,19 @@ def test_selection_time_does_not_depend_on_one_large_query(esa, l_c):
     assert np.array_equal(idx.cpu().numpy(), np.sort(order))
 
 
+# more pairs of batch entry and KV head than a grid takes in z (65535): few tokens and a chunk
+@pytest.mark.parametrize("l_C", [1, 16])
+def test_attention_over_more_pairs_than_one_grid(esa, l_C):
+    say(f"attend 8193 x 9 pairs l_C={l_C}")
+    B, H, d, t0 = 8193, 9, 64, 5
+    g = torch.Generator(device="cuda").manual_seed(l_C)
+    q, K, V = (torch.randn((B, n, H, d), generator=g, device="cuda", dtype=torch.bfloat16) for n in (l_C, t0 + l_C, t0 + l_C))
+    O = esa.esa_attend(q, K, V, t0, 2, 3, None, None)
+    for b in (0, 1, 4096, 7281, 7282, 8192):        # pair 65535 is entry 7281's
+        want, _ = orc.attend(to_f64(q[b]), to_f64(K[b]), to_f64(V[b]), t0, 2, 3, np.empty(0, np.int32), 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
+
+
 # a workgroup's 64 rows, one less, one more, a single row; the most rows in all of that kernel and one more
 @pytest.mark.parametrize("B,n,d_c", [(1, 1, 128), (3, 63, 64), (2, 64, 256), (5, 65, 128), (1, 131072, 64), (1, 131073, 64)])
 def test_score_of_one_token_in_workgroups_of_64_rows_and_of_256(esa, B, n, d_c):
