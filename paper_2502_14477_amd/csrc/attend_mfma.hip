@@ -20,7 +20,7 @@
 // between the two half-waves, and S^T's accumulator layout is directly P^T's B-operand layout once
 // the reduction slots of the second product are assigned to keys accordingly.
 //
-// Tiles of 64 keys are double buffered in LDS and arrive there without passing through registers:
+// Tiles of 64 keys stand three deep in LDS and arrive there without passing through registers:
 // global_load_lds_dwordx4 deposits 16 bytes per lane at consecutive LDS addresses, so one wave
 // instruction brings four 256-byte rows, and which 16 bytes of its row a lane fetches is chosen
 // such that the rows land XOR-swizzled (K: 16-byte pieces by row % 16, V: 64-byte chunks by
@@ -30,9 +30,19 @@
 // keys of one head dimension per lane) come from ds_read_b64_tr_b16, which hands lane i of a 16-lane
 // group element i%4 of the 8 bytes addressed by lanes 4e + i/4 (e = 0..3): sixteen lanes that point
 // at a 4-key x 16-dim block receive one dimension each, four consecutive keys of it.
-// One barrier per tile; the next tile's loads are in flight during the current tile's math.
+// One barrier per tile; the next two tiles' loads are in flight during the current tile's math, counted by hand.
+//
+// What bounds it: with all compute units busy the clock falls (matrix instructions alone go from 1.00 to 1.30 us per tile and
+// workgroup between one and 256 workgroups, a synthetic loop with the kernel's mix of matrix, vector and LDS instructions on
+// random data from 1.05 to 1.59), so the loop's instructions count more than their order: 1.57 us a tile on 16 workgroups,
+// 2.05 on 256, where working out each tile's segment, base and stride between two tiles took 1.68 and 2.10.  Beside the loop
+// (17 to 19 tiles, 31 to 38 us, for 512 tokens at 128k): 2.7 us from entry to the first tile, 2.6 from the last tile to the
+// stores.  Chunk of 512 at 128k 109.9 -> 108.1 us a step, 1024 at 256k 456 -> 436, 20k prompt 2918 -> 2862, tail of 77 51.9 -> 50.9,
+// head size 64 at 32k 82.6 -> 81.1.
 #include "attend_mfma.h"
 #include "keyspace.h"
+
+#include <type_traits>
 
 namespace esa {
 namespace {
@@ -46,8 +56,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void global_void;
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 constexpr int kKT = 64;             // virtual keys per tile
 constexpr int kRows = 256;          // query rows per workgroup
@@ -58,6 +67,7 @@ constexpr int kMaxSlots = 16;           // partial results per row
 // step against eight); their fp16 results err independently (outputs 2.27e-3 from the 64-bit result, 2.31e-3 with eight).
 constexpr int kMaxSplits = 16;
 constexpr int kMaxSelSplits = 8;        // two-call form: at most half as many local slices, then the selected ones
+constexpr int kStages = 3;
 constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.f;        // the softmax reference lags the running maximum by at most 2^8
@@ -150,16 +160,14 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   constexpr int kRowStep = kLoadRows * kWaves;          // distance between them
   constexpr int kKS = D / 16;             // reduction steps of the first product
   constexpr int kMD = D / 32;             // 32-dim tiles of the second product
-  // Two stages of a K tile and a V tile.  Separate arrays, so that the compiler can tell a load into one
-  // stage from a fragment read of the other and does not wait for the load first.
-  __shared__ __attribute__((aligned(1024))) bf16_t k_st0[kTileElems];
-  __shared__ __attribute__((aligned(1024))) bf16_t k_st1[kTileElems];
-  __shared__ __attribute__((aligned(1024))) bf16_t v_st0[kTileElems];
-  __shared__ __attribute__((aligned(1024))) bf16_t v_st1[kTileElems];
+  // Three stages of a K tile, then three of a V tile, then room for the query rows, which come in through the last V stage and
+  // what is behind it.  Three stages of each wave's copy of a tile's index entries.
+  __shared__ __attribute__((aligned(1024))) bf16_t st[(2 * kStages + 3) * kTileElems];
+  __shared__ __attribute__((aligned(1024))) int32_t idx_st[kStages][kWaves][kKT];
+  constexpr int kQPlace = (2 * kStages - 1) * kTileElems * 2;       // byte offset of the query rows
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);        // uniform: scalar address arithmetic
-
 
   // ---- which (batch element, KV head, row tile, key slice) is this workgroup
   const int n_slices = a.view[0].n_split + a.view[1].n_split;
@@ -211,87 +219,105 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const uint32_t st_slot = lane % kPieces;
   const uint32_t kcol = (st_slot ^ k_swizzle<D>(st_row)) * 16;     // byte column of the piece fetched for K
   const uint32_t vcol = ((((st_slot >> 2) ^ v_swizzle<D>(st_row)) << 2) | (st_slot & 3)) * 16;   // ... for V
-  auto dma16 = [&](const char* src, bf16_t* dst_wave_uniform) {
-    __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)dst_wave_uniform, 16, 0, 0);
+  const uint32_t st_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte*)st) + wave * 1024;    // 1 KB per row group
+  const uint32_t idx_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte*)&idx_st[0][wave][0]);
+  // Loads into LDS are written out: the compiler, which cannot tell the stages apart, would put a wait for all of them in
+  // front of every LDS read.  (They have no result registers that it could reuse under way.)  Every wave issues the same
+  // number per turn and waits by count.
+  auto dma16 = [&](const char* src, uint32_t dst) __attribute__((always_inline)) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory");
   };
-  // Index-driven selected rows (the gather folded into this kernel): the cache rows this lane fetches
-  // for a tile that lies inside the selected segment are looked up one tile ahead of the tile's loads,
-  // so that the look-up is not a dependent round trip in front of them.
+  // Which row a virtual key is.  Index-driven selected rows (the gather folded into this kernel): the entries of a tile's
+  // selected keys go to LDS a turn ahead of the tile's keys, lane l's being that of key l.  No branch on where in the
+  // virtual sequence a tile lies: this code stands between two tiles' matrix instructions, where nothing hides it.
   const int32_t* sidx = V.sel_idx ? V.sel_idx + (int64_t)b * V.idx_bs : nullptr;
-  // The entries are kept as loaded and clamped where tile_load uses them, a whole tile later: clamping here
-  // would be a use, and the wait in front of it would also wait for the tile loads issued just before, which
-  // are meant to land during the tile's arithmetic.
-  int32_t picked[kMyRows] = {};
-  auto idx_prefetch = [&](uint32_t t) {
-    const uint32_t j0 = t * kKT;
-    if (sidx && t < tile_end && j0 >= V.i_end && j0 + kKT <= V.i_end + V.n_sel) {
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) picked[u] = sidx[j0 - V.i_end + st_row + kRowStep * u];
-    }
+  const bool gathered = V.n_sel && !sidx;
+  const int32_t* list = sidx ? sidx : (const int32_t*)kc;                 // (nothing to look up: the cache's first word)
+  const uint32_t list_last = sidx && V.n_sel ? V.n_sel - 1 : 0;
+  auto idx_load = [&](uint32_t t, int stage) __attribute__((always_inline)) {
+    const int32_t js = (int32_t)(t * kKT + lane - V.i_end);
+    const uint32_t at = js < 0 ? 0u : (uint32_t)js < list_last ? (uint32_t)js : list_last;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(idx_lds + stage * (kWaves * kKT * 4)), "v"(list + at) : "memory");
   };
-  // a middle token's position, clamped so that a bad index cannot leave the cache
-  auto cache_row = [&](int32_t v) -> uint32_t { return v < 0 ? 0u : ((uint32_t)v < V.idx_limit ? (uint32_t)v : V.idx_limit - 1); };
-  auto tile_load = [&](uint32_t j0, bf16_t* kt, bf16_t* vt) {
-    const uint32_t sel_end = V.i_end + V.n_sel;
-    int seg = -1;                                                  // 0: cache rows, 1: gathered rows
-    uint32_t row0 = 0;
-    // A tile whose 64 keys lie inside one segment of the virtual sequence (the usual case) is addressed
-    // as uniform base + row * stride + column; tiles that straddle a segment boundary or the end of the
-    // slice take the general per-row path.
-    if (j0 + kKT <= V.i_end) {
-      seg = 0;
-      row0 = j0;
-    } else if (j0 >= V.i_end && j0 + kKT <= sel_end) {
-      seg = 1;
-      row0 = j0 - V.i_end;
-    } else if (j0 >= sel_end && j0 + kKT <= k_end) {
-      seg = 0;
-      row0 = j0 - sel_end + V.l_start;
+  // The rows of a tile that this lane fetches a piece of: numbers in the cache, or complements of numbers in the gathered buffers.
+  struct Rows {
+    int32_t at[kMyRows];
+  };
+  const uint32_t past_sel = V.l_start - V.i_end - V.n_sel;                // from a virtual key behind the selected ones to its row
+  auto rows_of = [&](uint32_t t, int stage) __attribute__((always_inline)) {
+    Rows p;
+#pragma unroll
+    for (int u = 0; u < kMyRows; ++u) {
+      const int32_t entry = idx_st[stage][wave][st_row + kRowStep * u];
+      uint32_t j = t * kKT + st_row + kRowStep * u;
+      j = j < k_end ? j : k_end - 1;                                      // the tail repeats a key; masked below
+      const uint32_t js = j - V.i_end;
+      // a middle token's position, clamped so that a bad index cannot leave the cache
+      const int32_t most = (int32_t)V.idx_limit - 1;
+      const int32_t selected = gathered ? ~(int32_t)js : entry < 0 ? 0 : entry < most ? entry : most;
+      const int32_t plain = (int32_t)(j < V.i_end ? j : j + past_sel);
+      p.at[u] = js < V.n_sel ? selected : plain;
     }
-    bf16_t* kd = kt + wave * 512;                                  // 1 KB per row group
-    bf16_t* vd = vt + wave * 512;
-    constexpr int kGroupStep = kWaves * 512;
-    if (seg == 1 && sidx) {             // cache rows looked up by idx_prefetch for this tile
-      uint32_t row[kMyRows];
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) row[u] = cache_row(picked[u]);
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(kc + ((uint64_t)row[u] * V.k_bytes + kcol), kd + kGroupStep * u);
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(vc + ((uint64_t)row[u] * V.v_bytes + vcol), vd + kGroupStep * u);
-    } else if (seg >= 0) {
-      const uint32_t ks = seg ? a.sel_bytes : V.k_bytes, vs = seg ? a.sel_bytes : V.v_bytes;
-      const char* kb = (seg ? ksl : kc) + (uint64_t)row0 * ks;
-      const char* vbase = (seg ? vsl : vc) + (uint64_t)row0 * vs;
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(kb + ((st_row + kRowStep * u) * ks + kcol), kd + kGroupStep * u);
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(vbase + ((st_row + kRowStep * u) * vs + vcol), vd + kGroupStep * u);
-    } else {
-      RowRef ref[kMyRows];
+    return p;
+  };
+  // one tile of keys or of values
+  auto tile_load = [&](const Rows& rows, int stage, auto values_c) __attribute__((always_inline)) {
+    constexpr bool kValues = decltype(values_c)::value;
+    const uint32_t dst = st_lds + ((kValues ? kStages : 0) + stage) * (kTileElems * 2);
+    const char* cache = (kValues ? vc + vcol : kc + kcol);
+    const uint32_t stride = kValues ? V.v_bytes : V.k_bytes;
+    if (gathered) {
+      const char* sel = (kValues ? vsl + vcol : ksl + kcol);
 #pragma unroll
       for (int u = 0; u < kMyRows; ++u) {
-        const uint32_t j = j0 + st_row + kRowStep * u;
-        ref[u] = row_ref(V, sidx, j < k_end ? j : k_end - 1);                   // the tail repeats a key; masked below
+        const int32_t row = rows.at[u];
+        dma16(row < 0 ? sel + (uint64_t)(uint32_t)~row * a.sel_bytes : cache + (uint64_t)(uint32_t)row * stride, dst + kWaves * 1024 * u);
       }
+    } else {
 #pragma unroll
-      for (int u = 0; u < kMyRows; ++u)
-        dma16((ref[u].in_sel ? ksl : kc) + (uint64_t)ref[u].row * (ref[u].in_sel ? a.sel_bytes : V.k_bytes) + kcol, kd + kGroupStep * u);
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u)
-        dma16((ref[u].in_sel ? vsl : vc) + (uint64_t)ref[u].row * (ref[u].in_sel ? a.sel_bytes : V.v_bytes) + vcol, vd + kGroupStep * u);
+      for (int u = 0; u < kMyRows; ++u) dma16(cache + (uint64_t)(uint32_t)rows.at[u] * stride, dst + kWaves * 1024 * u);
     }
   };
-  // Every load of this wave has landed in LDS (vmcnt = 0; the other counters are left alone).
-  auto loads_landed = [&]() { __builtin_amdgcn_s_waitcnt(0x0F70); };
+  const std::false_type keys_c = {};
+  const std::true_type values_c = {};
+  // At most LEFT vector-memory operations of this wave are outstanding (they complete in order; the other counters are
+  // left alone).
+  auto loads_landed = [&](auto left_c) __attribute__((always_inline)) {
+    constexpr int kLeft = decltype(left_c)::value;
+    static_assert(kLeft < 16, "the counter's low bits");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | kLeft);
+  };
+  // A barrier without the fences of __syncthreads(), which wait for every load in flight.  The wave's LDS reads are
+  // complete: their results have been used.
+  auto all_waves = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
 
   // Lane constants of the transposed V reads: inside its 16-lane group lane i points at key i/4 of a
   // four-key block and at four consecutive dims 4*(i%4).. of the group's sixteen.
   const int tr_key = (lane & 15) >> 2;
   const int tr_dim = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
 
+  // Byte offsets of the fragments in a stage; what comes on top, which stage and which keys, is constant and goes into the read
+  // instruction.
+  uint32_t k_at[kKS], v_at[kMD];
+#pragma unroll
+  for (int ks16 = 0; ks16 < kKS; ++ks16) k_at[ks16] = (r * D + (((2 * ks16 + hi) ^ k_swizzle<D>(r)) << 3)) * 2;
+  // row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot c ^ v_swizzle(key), which keys 4 apart share
+#pragma unroll
+  for (int md = 0; md < kMD; ++md) v_at[md] = (kStages * kTileElems + (4 * hi + tr_key) * D + ((md ^ v_swizzle<D>(tr_key)) << 5) + tr_dim) * 2;
+  // Keeps the compiler from folding a stage's place into the offsets outside the loop: twelve registers, not thirty-six.
+  auto pin_offsets = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(k_at[ks16]));
+#pragma unroll
+    for (int md = 0; md < kMD; ++md) asm volatile("" : "+v"(v_at[md]));
+  };
+
   // ---- one tile: S^T = K Q^T, online softmax, O^T += V^T P^T
-  auto tile_math = [&](uint32_t t, const bf16_t* kt, const bf16_t* vt) {
+  auto tile_math = [&](uint32_t t, int stage) __attribute__((always_inline)) {
     const uint32_t j0 = t * kKT;
     if (j0 >= lim_hi) return;           // no row of this wave sees any of the tile's keys
     f32x16 s[2];
@@ -306,7 +332,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     for (int ks16 = 0; ks16 < kKS; ++ks16)
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
-        kf[ks16][mt] = *(const bf16x8*)&kt[(32 * mt + r) * D + (((2 * ks16 + hi) ^ k_swizzle<D>(r)) << 3)];
+        kf[ks16][mt] = *(const bf16x8*)((const char*)st + k_at[ks16] + (stage * kKT + 32 * mt) * D * 2);
 #pragma unroll
     for (int ks16 = 0; ks16 < kKS; ++ks16)
 #pragma unroll
@@ -386,15 +412,14 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
         pf[term][kp] = *(const bf16x8*)&v;
       }
 
-    // ---- O^T += V^T P^T.  Row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot
-    // c ^ v_swizzle(key), which keys 4 apart share.
+    // ---- O^T += V^T P^T
 #pragma unroll
     for (int kp = 0; kp < 4; ++kp)
 #pragma unroll
       for (int md = 0; md < kMD; ++md) {
-        const bf16_t* vp = vt + (16 * kp + 4 * hi + tr_key) * D + ((md ^ v_swizzle<D>(tr_key)) << 5) + tr_dim;
+        const char* vp = (const char*)st + v_at[md] + (stage * kKT + 16 * kp) * D * 2;
         const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);             // keys 16kp + 4hi + 0..3
-        const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D));  // keys 16kp + 8 + 4hi + 0..3
+        const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D * 2));  // keys 16kp + 8 + 4hi + 0..3
         const i16x8 both = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
         for (int term = 0; term < kTerms; ++term)
@@ -410,35 +435,52 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     __builtin_amdgcn_sched_group_barrier(0x008, 2 * kTerms * kMD, 0);
   };
 
-  // The first tile's loads go out before the query fragments' so that the two round trips overlap.
-  idx_prefetch(tile_begin);
-  if (tile_begin < tile_end) tile_load(tile_begin * kKT, k_st0, v_st0);
-  idx_prefetch(tile_begin + 1);
-  {
-    const bf16_t* qp = (const bf16_t*)V.q + (int64_t)b * V.q_bs + ((int64_t)cc * a.h + head) * D + hi * 8;
+  // Turn t: tile t, requested two turns before (a turn takes 2 us, a tile that comes from HBM sometimes longer).  Its own requests
+  // are tile t + 2 and the index entries of tile t + 3; tile n is in stage (n - tile_begin) % 3.  At its barrier every wave is
+  // done with the stage that these overwrite.
 #pragma unroll
-    for (int ks16 = 0; ks16 < kKS; ++ks16) qf[ks16] = *(const bf16x8*)(qp + ks16 * 16);
-    // Pin the fragments as arrived values here: otherwise every use inside the tile loop carries a
-    // wait on the vector-memory counter.
+  for (int i = 0; i < kStages; ++i) idx_load(tile_begin + i, i);
+  // The wave's 32 query rows, through LDS like a K tile: whole rows, four or eight to an instruction.  (Fetched as
+  // fragments, 16 bytes of 32 rows to an instruction, they were 32 cache lines each.)
+  constexpr int kQLoads = 32 / kLoadRows;
 #pragma unroll
-    for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(qf[ks16]));
+  for (int i = 0; i < kQLoads; ++i) {
+    const uint32_t qr = kLoadRows * i + lane / kPieces, in_tile = wave * 32 + qr;
+    const int qc = q0 + (int)(in_tile >> a.group_log2);
+    const int64_t at = (int64_t)b * V.q_bs + ((int64_t)(qc < c_last ? qc : c_last) * a.h + g * a.group + (in_tile & (a.group - 1))) * D;
+    dma16(V.q + (at + ((lane % kPieces) ^ k_swizzle<D>(qr)) * 8) * 2, st_lds - wave * 1024 + kQPlace + wave * (32 * D * 2) + 1024 * i);
   }
-  // Two tiles per trip so that every stage is named statically.  At each barrier tile t is in LDS and
-  // every wave is done with tile t-1, whose stage the loads issued right after the barrier overwrite.
-  for (uint32_t t = tile_begin; t < tile_end; t += 2) {
-    loads_landed();
-    __syncthreads();
-    if (t + 1 < tile_end) tile_load((t + 1) * kKT, k_st1, v_st1);
-    idx_prefetch(t + 2);
-    tile_math(t, k_st0, v_st0);
+  if (sidx) loads_landed(std::integral_constant<int, kQLoads>());
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const Rows rows = rows_of(tile_begin + i, i);
+    tile_load(rows, i, keys_c);
+    tile_load(rows, i, values_c);
+  }
+  loads_landed(std::integral_constant<int, 4 * kMyRows>());
+#pragma unroll
+  for (int ks16 = 0; ks16 < kKS; ++ks16) qf[ks16] = *(const bf16x8*)((const char*)st + kQPlace + wave * (32 * D * 2) + k_at[ks16]);
+  // arrived before the barrier of the first turn, behind which other waves overwrite the rows
+#pragma unroll
+  for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(qf[ks16]));
+  auto turn = [&](uint32_t t, int s0, int s2) __attribute__((always_inline)) {        // stages of tiles t and t + 2
+    loads_landed(std::integral_constant<int, 2 * kMyRows>());
+    const Rows rows = rows_of(t + 2, s2);
+    all_waves();
+    idx_load(t + 3, s0);
+    tile_load(rows, s2, keys_c);
+    tile_load(rows, s2, values_c);
+    pin_offsets();
+    tile_math(t, s0);
+  };
+  for (uint32_t t = tile_begin; t < tile_end; t += 3) {
+    turn(t, 0, 2);
     if (t + 1 < tile_end) {
-      loads_landed();
-      __syncthreads();
-      if (t + 2 < tile_end) tile_load((t + 2) * kKT, k_st0, v_st0);
-      idx_prefetch(t + 3);
-      tile_math(t + 1, k_st1, v_st1);
+      turn(t + 1, 1, 0);
+      if (t + 2 < tile_end) turn(t + 2, 2, 1);
     }
   }
+  loads_landed(std::integral_constant<int, 0>());
 
   // ---- results.  Accumulator register v of tile md is head-dim 32*md + 8*(v/4) + 4*hi + v%4 of this
   // lane's query, so a lane holds its whole output row in 8-byte pieces.  The rows are narrowed to 16
@@ -486,8 +528,8 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   }
   __syncthreads();                       // every wave is done with the last tile
   {
-    // wave w's 32 rows go to half (w%2) of stage array w/2, 16-byte slots swizzled as in a K tile
-    uint16_t* ot = (uint16_t*)(wave < 2 ? k_st0 : wave < 4 ? k_st1 : wave < 6 ? v_st0 : v_st1) + ((wave & 1) * 32 + r) * D;
+    // 16-byte slots swizzled as in a K tile
+    uint16_t* ot = (uint16_t*)st + (wave * 32 + r) * D;
 #pragma unroll
     for (int md = 0; md < kMD; ++md)
 #pragma unroll
@@ -520,8 +562,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     const int rw = kLoadRows * i + lane / kPieces, piece = lane % kPieces;
     const int row = wave * 32 + rw, tok = q0 + (row >> a.group_log2), hd = g * a.group + (row & (a.group - 1));
     if (tok <= c_last) {
-      const uint16_t* ob = (const uint16_t*)(wave < 2 ? k_st0 : wave < 4 ? k_st1 : wave < 6 ? v_st0 : v_st1);
-      const uint4 w = *(const uint4*)(ob + ((wave & 1) * 32 + rw) * D + ((piece ^ k_swizzle<D>(rw)) << 3));
+      const uint4 w = *(const uint4*)((const uint16_t*)st + (wave * 32 + rw) * D + ((piece ^ k_swizzle<D>(rw)) << 3));
       *(uint4*)(dst + ((int64_t)tok * a.h + hd) * D + piece * 8) = w;
     }
   }
