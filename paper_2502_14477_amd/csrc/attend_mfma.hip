@@ -34,14 +34,16 @@
 //
 // What bounds it: with all compute units busy the clock falls (matrix instructions alone go from 1.00 to 1.30 us per tile and
 // workgroup between one and 256 workgroups, a synthetic loop with the kernel's mix of matrix, vector and LDS instructions on
-// random data from 1.05 to 1.59), so the loop's instructions count more than their order: 1.57 us a tile on 16 workgroups,
-// 2.05 on 256, where working out each tile's segment, base and stride between two tiles took 1.68 and 2.10.  Beside the loop
+// random data from 1.05 to 1.59), so the loop's instructions count more than their order: 1.58 us a tile on 16 workgroups,
+// 2.02 to 2.06 on 256, where working out each tile's segment, base and stride between two tiles took 1.68 and 2.10.  Beside the loop
 // (17 to 19 tiles, 31 to 38 us, for 512 tokens at 128k): 2.7 us from entry to the first tile, 2.6 from the last tile to the
 // stores.  Chunk of 512 at 128k 109.9 -> 108.1 us a step, 1024 at 256k 456 -> 436, 20k prompt 2918 -> 2862, tail of 77 51.9 -> 50.9,
 // head size 64 at 32k 82.6 -> 81.1.
 #include "attend_mfma.h"
 #include "keyspace.h"
 
+#include <float.h>
+#include <stddef.h>
 #include <type_traits>
 
 namespace esa {
@@ -71,6 +73,7 @@ constexpr int kStages = 3;
 constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.f;        // the softmax reference lags the running maximum by at most 2^8
+constexpr float kNoKey = -FLT_MAX;  // reference of a row that has seen no key: finite, so that differences stay numbers
 constexpr float kLn2 = 0.6931471805599453f;
 
 struct AttendArgs {
@@ -86,7 +89,10 @@ struct AttendArgs {
   int qpt, n_qt;                    // tokens per row tile (a whole number of waves' rows, at most 256 rows), row tiles
   int batch;
   PairGrid grid;
-  int n_slot;         // slots per row in the partial-result arrays
+  int n_split;        // slices of the launch's views, laid end to end
+  uint32_t split_step;
+  int slot0;          // slice s leaves its partial results in slot slot0 + s ...
+  int n_slot;         // ... of so many per row
   int to_slots;       // 1: write partial results even when the launch has a single slice
   float c2;           // scale * log2(e)
   int64_t out_bs, sel_bs_bytes;
@@ -150,8 +156,33 @@ template <int D> __device__ __forceinline__ float lse_of(float m, float l) {
   return kFp32Probs<D> ? __builtin_fmaf(m, kLn2, logf(l)) : (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
+// View `part` of the kernel's arguments, read where they lie: by a select of every field, the loop over the views kept both in
+// scalar registers, half of them spilled (1.3 us in front of the first load).
+__device__ __forceinline__ KeyView view_argument(int part) {
+  typedef __attribute__((address_space(4))) const KeyView argument;
+  argument& v = ((argument*)((__attribute__((address_space(4))) const char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttendArgs, view)))[part];
+  KeyView V;
+  V.q = v.q;
+  V.k_cache = v.k_cache;
+  V.v_cache = v.v_cache;
+  V.q_bs = v.q_bs;
+  V.k_bs_bytes = v.k_bs_bytes;
+  V.v_bs_bytes = v.v_bs_bytes;
+  V.k_bytes = v.k_bytes;
+  V.v_bytes = v.v_bytes;
+  V.i_end = v.i_end;
+  V.n_sel = v.n_sel;
+  V.l_start = v.l_start;
+  V.n_fixed = v.n_fixed;
+  V.sel_idx = v.sel_idx;
+  V.idx_bs = v.idx_bs;
+  V.idx_limit = v.idx_limit;
+  V.with_chunk = v.with_chunk;
+  return V;
+}
+
 template <int D>
-__global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
+__global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {       // (the only argument: view_argument)
   static_assert(D == 64 || D == 128, "swizzles and store patterns");
   constexpr int kTileElems = kKT * D;     // one K or V tile in LDS: 64 unpadded rows, swizzled
   constexpr int kPieces = D / 8;          // 16-byte pieces of a row
@@ -170,25 +201,17 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);        // uniform: scalar address arithmetic
 
   // ---- which (batch element, KV head, row tile, key slice) is this workgroup
-  const int n_slices = a.view[0].n_split + a.view[1].n_split;
   const Placed at = place_in(a.grid);
-  const int b = at.pair / a.h_kv, g = at.pair - b * a.h_kv, qt = at.row_tile, slice = at.slice;
-  const int vw = slice >= a.view[0].n_split ? 1 : 0;             // which view this slice belongs to
-  const KeyView V = pick_view(a.view, vw);
-  const int split = slice - (vw ? a.view[0].n_split : 0);        // slice number inside the view
+  const int b = at.pair / a.h_kv, g = at.pair - b * a.h_kv, qt = at.row_tile, split = at.slice;
 
-  const char* kc = V.k_cache + (int64_t)b * V.k_bs_bytes + (int64_t)g * D * 2;
-  const char* vc = V.v_cache + (int64_t)b * V.v_bs_bytes + (int64_t)g * D * 2;
-  const char* ksl = a.k_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
-  const char* vsl = a.v_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
-
-  // ---- this workgroup's rows and key slice
+  // ---- this workgroup's rows, and its slice of the tiles of both views
   const int q0 = qt * a.qpt;
   const int c_last = (q0 + a.qpt < a.l_c ? q0 + a.qpt : a.l_c) - 1;
-  const uint32_t n_vis = V.n_fixed + (V.with_chunk ? c_last + 1 : 0);   // keys the tile's last token sees
-  const uint32_t n_tiles = (n_vis + kKT - 1) / kKT;
-  const uint32_t tile_begin = slice_tile(V, n_tiles, split), tile_end = slice_tile(V, n_tiles, split + 1);
-  const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
+  auto keys_of_last_row = [&](const KeyView& V) { return V.n_fixed + (V.with_chunk ? c_last + 1 : 0); };
+  const uint32_t tiles_0 = (keys_of_last_row(a.view[0]) + kKT - 1) / kKT;
+  const uint32_t tiles_all = tiles_0 + (keys_of_last_row(a.view[1]) + kKT - 1) / kKT;
+  const uint32_t slice_begin = slice_tile(tiles_all, split, a.n_split, a.split_step);
+  const uint32_t slice_end = slice_tile(tiles_all, split + 1, a.n_split, a.split_step);
 
   // ---- this wave's 32 rows (32/G consecutive current tokens, the group's heads of each), one per lane (both half-waves)
   const int row_in_tile = wave * 32 + r;
@@ -196,20 +219,15 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const int c = q0 + (row_in_tile >> a.group_log2);
   const bool c_ok = c <= c_last;
   const int cc = c_ok ? c : c_last;                                // rows past the tile repeat its last token
-  const uint32_t vis = V.n_fixed + (V.with_chunk ? cc + 1 : 0);
-  const uint32_t lim = vis < k_end ? vis : k_end;                  // first virtual key this lane's query may NOT see
-  const uint32_t lim_lo = __builtin_amdgcn_readlane(lim, 0);       // smallest limit in the wave (r = 0)
-  // largest limit in the wave; 0 for a wave without rows
   const bool wave_has_rows = q0 + ((wave * 32) >> a.group_log2) <= c_last;
-  const uint32_t lim_hi = wave_has_rows ? __builtin_amdgcn_readlane(lim, 31) : 0;
-  bf16x8 qf[kKS];                                                  // loaded below, behind the first tile's loads
+  bf16x8 qf[kKS];
 
   f32x16 o[kMD];
 #pragma unroll
   for (int md = 0; md < kMD; ++md)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[md][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoKey, l_run = 0.f;
 
   // ---- staging of one tile: global -> LDS directly, 16 bytes per lane.  A wave instruction fills 1 KB =
   // four rows of 256 bytes or eight of 128; wave w brings row groups w and (head size 128) w + 8 of K and of V.
@@ -221,6 +239,63 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   const uint32_t vcol = ((((st_slot >> 2) ^ v_swizzle<D>(st_row)) << 2) | (st_slot & 3)) * 16;   // ... for V
   const uint32_t st_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte*)st) + wave * 1024;    // 1 KB per row group
   const uint32_t idx_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte*)&idx_st[0][wave][0]);
+  // At most LEFT vector-memory operations of this wave are outstanding (they complete in order; the other counters are
+  // left alone).
+  auto loads_landed = [&](auto left_c) __attribute__((always_inline)) {
+    constexpr int kLeft = decltype(left_c)::value;
+    static_assert(kLeft < 16, "the counter's low bits");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | kLeft);
+  };
+  // A barrier without the fences of __syncthreads(), which wait for every load in flight.  The wave's LDS reads are
+  // complete: their results have been used.
+  auto all_waves = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  // Lane constants of the transposed V reads: inside its 16-lane group lane i points at key i/4 of a
+  // four-key block and at four consecutive dims 4*(i%4).. of the group's sixteen.
+  const int tr_key = (lane & 15) >> 2;
+  const int tr_dim = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
+
+  // Byte offsets of the fragments in a stage; what comes on top, which stage and which keys, is constant and goes into the read
+  // instruction.
+  uint32_t k_at[kKS], v_at[kMD];
+#pragma unroll
+  for (int ks16 = 0; ks16 < kKS; ++ks16) k_at[ks16] = (r * D + (((2 * ks16 + hi) ^ k_swizzle<D>(r)) << 3)) * 2;
+  // row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot c ^ v_swizzle(key), which keys 4 apart share
+#pragma unroll
+  for (int md = 0; md < kMD; ++md) v_at[md] = (kStages * kTileElems + (4 * hi + tr_key) * D + ((md ^ v_swizzle<D>(tr_key)) << 5) + tr_dim) * 2;
+  // Keeps the compiler from folding a stage's place into the offsets outside the loop: twelve registers, not thirty-six.
+  auto pin_offsets = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(k_at[ks16]));
+#pragma unroll
+    for (int md = 0; md < kMD; ++md) asm volatile("" : "+v"(v_at[md]));
+  };
+
+  // ---- the slice's tiles of one view after those of the other.  Sums and reference run on: a softmax does not mind in which
+  // order, or with which encoding of the query, its logits were made.  (With slices of their own, Section 3.2's two parts were
+  // three of 24 tiles and one of 34 where four of 26.5 are possible: 512 tokens behind a window of 4096.)
+#pragma unroll 1
+  for (int part = 0; part < 2; ++part) {
+  const KeyView V = view_argument(part);
+  const uint32_t before = part ? tiles_0 : 0, up_to = part ? tiles_all : tiles_0;
+  if (slice_end <= before || slice_begin >= up_to) continue;
+  const uint32_t tile_begin = (slice_begin > before ? slice_begin : before) - before;
+  const uint32_t tile_end = (slice_end < up_to ? slice_end : up_to) - before;
+  const uint32_t n_vis = keys_of_last_row(V);                      // keys the tile's last token sees
+  const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
+  const char* kc = V.k_cache + (int64_t)b * V.k_bs_bytes + (int64_t)g * D * 2;
+  const char* vc = V.v_cache + (int64_t)b * V.v_bs_bytes + (int64_t)g * D * 2;
+  const char* ksl = a.k_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
+  const char* vsl = a.v_sel + (V.n_sel ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * D * 2 : 0);
+  const uint32_t vis = V.n_fixed + (V.with_chunk ? cc + 1 : 0);
+  const uint32_t lim = vis < k_end ? vis : k_end;                  // first virtual key this lane's query may NOT see
+  const uint32_t lim_lo = __builtin_amdgcn_readlane(lim, 0);       // smallest limit in the wave (r = 0)
+  const uint32_t lim_hi = wave_has_rows ? __builtin_amdgcn_readlane(lim, 31) : 0;      // largest; 0 for a wave without rows
+  if (part && slice_begin < tiles_0) all_waves();                  // every wave is done with the other view's last tile
   // Loads into LDS are written out: the compiler, which cannot tell the stages apart, would put a wait for all of them in
   // front of every LDS read.  (They have no result registers that it could reuse under way.)  Every wave issues the same
   // number per turn and waits by count.
@@ -280,42 +355,6 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   };
   const std::false_type keys_c = {};
   const std::true_type values_c = {};
-  // At most LEFT vector-memory operations of this wave are outstanding (they complete in order; the other counters are
-  // left alone).
-  auto loads_landed = [&](auto left_c) __attribute__((always_inline)) {
-    constexpr int kLeft = decltype(left_c)::value;
-    static_assert(kLeft < 16, "the counter's low bits");
-    __builtin_amdgcn_s_waitcnt(0x0F70 | kLeft);
-  };
-  // A barrier without the fences of __syncthreads(), which wait for every load in flight.  The wave's LDS reads are
-  // complete: their results have been used.
-  auto all_waves = [&]() __attribute__((always_inline)) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-
-  // Lane constants of the transposed V reads: inside its 16-lane group lane i points at key i/4 of a
-  // four-key block and at four consecutive dims 4*(i%4).. of the group's sixteen.
-  const int tr_key = (lane & 15) >> 2;
-  const int tr_dim = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
-
-  // Byte offsets of the fragments in a stage; what comes on top, which stage and which keys, is constant and goes into the read
-  // instruction.
-  uint32_t k_at[kKS], v_at[kMD];
-#pragma unroll
-  for (int ks16 = 0; ks16 < kKS; ++ks16) k_at[ks16] = (r * D + (((2 * ks16 + hi) ^ k_swizzle<D>(r)) << 3)) * 2;
-  // row key of the V tile holds chunk c (dims 32c .. 32c+31) at chunk slot c ^ v_swizzle(key), which keys 4 apart share
-#pragma unroll
-  for (int md = 0; md < kMD; ++md) v_at[md] = (kStages * kTileElems + (4 * hi + tr_key) * D + ((md ^ v_swizzle<D>(tr_key)) << 5) + tr_dim) * 2;
-  // Keeps the compiler from folding a stage's place into the offsets outside the loop: twelve registers, not thirty-six.
-  auto pin_offsets = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(k_at[ks16]));
-#pragma unroll
-    for (int md = 0; md < kMD; ++md) asm volatile("" : "+v"(v_at[md]));
-  };
-
   // ---- one tile: S^T = K Q^T, online softmax, O^T += V^T P^T
   auto tile_math = [&](uint32_t t, int stage) __attribute__((always_inline)) {
     const uint32_t j0 = t * kKT;
@@ -357,82 +396,93 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
         }
     }
 
+    // The V fragments of sixteen keys (two reads for each 32 dims) are requested two such groups ahead of their use.
+    bf16x8 vf[4][kMD];
+    auto request_values = [&](int kp, int md) __attribute__((always_inline)) {
+      const char* vp = (const char*)st + v_at[md] + (stage * kKT + 16 * kp) * D * 2;
+      const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);                 // keys 16kp + 4hi + 0..3
+      const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D * 2));  // keys 16kp + 8 + 4hi + 0..3
+      vf[kp][md] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+#pragma unroll
+    for (int kp = 0; kp < 2; ++kp)
+#pragma unroll
+      for (int md = 0; md < kMD; ++md) request_values(kp, md);
+    __builtin_amdgcn_sched_barrier(0);
+
     // ---- online softmax, one query per lane
     float mx = s[0][0];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[mt][v]);
-    mx = halves_max(mx);
     // The reference m_run of the exponentials follows the running maximum lazily: it moves only when
     // a tile's maximum exceeds it by more than 2^kLazy, so probabilities stay below 2^kLazy (harmless
     // in bf16 and fp32) and the accumulators are rescaled once or twice per row instead of per tile.  (Head size 64
     // follows it at once: the sum stays small, and its logarithm as exact as the normaliser can hold.)
-    const float cand = mx * a.c2;
-    const float m_new = cand > m_run + (kFp32Probs<D> ? 0.f : kLazy) ? cand : m_run;
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
-    m_run = m_new;
-    float psum = 0.f;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mt][v], a.c2, -m_use));
-        s[mt][v] = p;
-        psum += p;
-      }
-    l_run = l_run * corr + psum;
-    if (__ballot(corr != 1.f) != 0ull) {
+    const float cand = halves_max(mx) * a.c2, m_old = m_run;
+    const bool moved = cand > m_run + (kFp32Probs<D> ? 0.f : kLazy);
+    m_run = moved ? cand : m_run;
+    if (__ballot(moved) != 0ull) {
+      const float corr = __builtin_amdgcn_exp2f(m_old - m_run);
+      l_run *= corr;
 #pragma unroll
       for (int md = 0; md < kMD; ++md)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[md][v] *= corr;
     }
+    float psum = 0.f;
     // Accumulator register v = 8*(e/4) + e%4 (+ 4*hi in the key number): fragment kp of P^T is S^T's
     // registers 8*(kp%2) .. + 7 of key tile kp/2, i.e. keys 16*kp + 4*hi + {0..3} and 16*kp + 8 + 4*hi + {0..3}.
     constexpr int kTerms = kFp32Probs<D> ? 3 : 1;
-    bf16x8 pf[kTerms][4];
+    uint32_t pf[4][kTerms][4];
+    // The eight keys of a lane in group kp, pair by pair in pieces: exponentials (E), then operands of the second product (O), in
+    // the order E0 E1 O0 E2 O1 E3 O2 O3.
+    auto piece = [&](int kp, int at) __attribute__((always_inline)) {
+      const bool exps = at == 0 || at == 1 || at == 3 || at == 5;
+      const int e = at < 2 ? at : at == 7 ? 3 : at / 2 + (exps ? 1 : -1);
+      f32x16& sx = s[kp >> 1];
+      const int v = (kp & 1) * 8 + 2 * e;
+      if (exps) {
+        sx[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(sx[v], a.c2, -m_run));
+        sx[v + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sx[v + 1], a.c2, -m_run));
+      } else {
+        float x = sx[v], y = sx[v + 1];
+        psum += x;
+        psum += y;
 #pragma unroll
-    for (int term = 0; term < kTerms; ++term)
-#pragma unroll
-      for (int kp = 0; kp < 4; ++kp) {
-        const int mt = kp >> 1, e0 = (kp & 1) * 8;
-        uint32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v = e0 + 2 * e;
-          w[e] = pack_bf16x2(s[mt][v], s[mt][v + 1]);
+        for (int term = 0; term < kTerms; ++term) {
+          const uint32_t w = pack_bf16x2(x, y);
+          pf[kp][term][e] = w;
           if (term + 1 < kTerms) {          // what the term leaves, exactly
-            s[mt][v] -= __uint_as_float(w[e] << 16);
-            s[mt][v + 1] -= __uint_as_float(w[e] & 0xFFFF0000u);
+            x -= __uint_as_float(w << 16);
+            y -= __uint_as_float(w & 0xFFFF0000u);
           }
         }
-        const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
-        pf[term][kp] = *(const bf16x8*)&v;
       }
+    };
+#pragma unroll
+    for (int at = 0; at < 8; ++at) piece(0, at);
+    __builtin_amdgcn_sched_barrier(0);
 
-    // ---- O^T += V^T P^T
+    // ---- O^T += V^T P^T, sixteen keys at a time; beside each matrix instruction a share of the next sixteen's exponentials and
+    // of the fragment reads for the sixteen after them.  (The order is pinned: left to itself, or with groups of instruction
+    // kinds to follow, the scheduler puts the fragment reads next to their use: 1.57 to 1.81 us a tile.)
+    constexpr int kMat = kTerms * kMD;
 #pragma unroll
     for (int kp = 0; kp < 4; ++kp)
 #pragma unroll
-      for (int md = 0; md < kMD; ++md) {
-        const char* vp = (const char*)st + v_at[md] + (stage * kKT + 16 * kp) * D * 2;
-        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);             // keys 16kp + 4hi + 0..3
-        const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D * 2));  // keys 16kp + 8 + 4hi + 0..3
-        const i16x8 both = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
+      for (int j = 0; j < kMat; ++j) {
+        const int term = j / kMD, md = j % kMD;
+        const uint4 w = make_uint4(pf[kp][term][0], pf[kp][term][1], pf[kp][term][2], pf[kp][term][3]);
+        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kp][md], *(const bf16x8*)&w, o[md], 0, 0, 0);
+        if (kp + 2 < 4 && j < kMD) request_values(kp + 2, j);
 #pragma unroll
-        for (int term = 0; term < kTerms; ++term)
-          o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[term][kp], o[md], 0, 0, 0);
+        for (int at = 0; at < 8; ++at)
+          if (kp + 1 < 4 && at * kMat / 8 == j) piece(kp + 1, at);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    // the V fragments of sixteen keys (2 kMD reads) are requested ahead of the matrix instructions that use them
-    __builtin_amdgcn_sched_group_barrier(0x100, 4 * kMD, 0);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, kTerms * kMD, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2 * kMD, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kTerms * kMD, 0);
+    l_run += psum;
   };
 
   // Turn t: tile t, requested two turns before (a turn takes 2 us, a tile that comes from HBM sometimes longer).  Its own requests
@@ -443,12 +493,14 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   // The wave's 32 query rows, through LDS like a K tile: whole rows, four or eight to an instruction.  (Fetched as
   // fragments, 16 bytes of 32 rows to an instruction, they were 32 cache lines each.)
   constexpr int kQLoads = 32 / kLoadRows;
+  uint32_t lane_now = lane;                      // hidden from the compiler: the rows' addresses would be kept across both views' loops
+  asm volatile("" : "+v"(lane_now));
 #pragma unroll
   for (int i = 0; i < kQLoads; ++i) {
-    const uint32_t qr = kLoadRows * i + lane / kPieces, in_tile = wave * 32 + qr;
+    const uint32_t qr = kLoadRows * i + lane_now / kPieces, in_tile = wave * 32 + qr;
     const int qc = q0 + (int)(in_tile >> a.group_log2);
     const int64_t at = (int64_t)b * V.q_bs + ((int64_t)(qc < c_last ? qc : c_last) * a.h + g * a.group + (in_tile & (a.group - 1))) * D;
-    dma16(V.q + (at + ((lane % kPieces) ^ k_swizzle<D>(qr)) * 8) * 2, st_lds - wave * 1024 + kQPlace + wave * (32 * D * 2) + 1024 * i);
+    dma16(V.q + (at + ((lane_now % kPieces) ^ k_swizzle<D>(qr)) * 8) * 2, st_lds - wave * 1024 + kQPlace + wave * (32 * D * 2) + 1024 * i);
   }
   if (sidx) loads_landed(std::integral_constant<int, kQLoads>());
 #pragma unroll
@@ -481,6 +533,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
     }
   }
   loads_landed(std::integral_constant<int, 0>());
+  }
 
   // ---- results.  Accumulator register v of tile md is head-dim 32*md + 8*(v/4) + 4*hi + v%4 of this
   // lane's query, so a lane holds its whole output row in 8-byte pieces.  The rows are narrowed to 16
@@ -493,12 +546,12 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   // are the plain log-sum-exp combination of Algorithm 1 with no trace of E.  Head size 64 stores its slices in fp32, each
   // lane its own row.
   const float l_tot = halves_sum(l_run);
-  const bool final_out = n_slices == 1 && !a.to_slots;
+  const bool final_out = a.n_split == 1 && !a.to_slots;
   float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   float m_store = m_run, l_store = l_tot;
   if constexpr (kFp32Probs<D>) {
     if (!final_out) {
-      const int64_t prow = ((int64_t)(b * a.n_slot + V.slot0 + split) * a.l_c + c) * a.h + head;
+      const int64_t prow = ((int64_t)(b * a.n_slot + a.slot0 + split) * a.l_c + c) * a.h + head;
       if (c_ok) {
         float* dst = (float*)a.part_o + prow * D + 4 * hi;
 #pragma unroll
@@ -550,7 +603,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {
   if (final_out) {
     dst = (uint16_t*)a.out + (int64_t)b * a.out_bs;
   } else {
-    const int64_t prow0 = ((int64_t)(b * a.n_slot + V.slot0 + split) * a.l_c) * a.h;
+    const int64_t prow0 = ((int64_t)(b * a.n_slot + a.slot0 + split) * a.l_c) * a.h;
     dst = (uint16_t*)a.part_o + prow0 * D;
     if (hi == 0 && c_ok) {
       float2 ml = {m_store, l_store};
@@ -649,8 +702,11 @@ int choose_splits(int l_c, int group, int h_kv, int batch) {
   return (int)(ns < 1 ? 1 : (ns > kMaxSplits ? kMaxSplits : ns));
 }
 
-void launch_tiles(AttendArgs& a, int d, int n_slices, hipStream_t st) {
-  for_pair_grids((int64_t)a.batch * a.h_kv, a.n_qt, n_slices, [&](dim3 grid, PairGrid placed) {
+void launch_tiles(AttendArgs& a, int d, int n_split, int slot0, hipStream_t st) {
+  a.n_split = n_split;
+  a.split_step = split_step(n_split);
+  a.slot0 = slot0;
+  for_pair_grids((int64_t)a.batch * a.h_kv, a.n_qt, n_split, [&](dim3 grid, PairGrid placed) {
     a.grid = placed;
     if (d == 128) attend_mfma_bf16<128><<<grid, kThreads, 0, st>>>(a);
     else attend_mfma_bf16<64><<<grid, kThreads, 0, st>>>(a);
@@ -765,26 +821,26 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.n_slot = n_slot;
   const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
   a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0, 0, 0);   // unused
-  auto launch = [&](int n_slices) { launch_tiles(a, d, n_slices, st); };
+  auto launch = [&](int n_split, int slot0) { launch_tiles(a, d, n_split, slot0, st); };
   auto merge = [&](int ns_a, int slot_b, int ns_b) {
     if (d == 128) launch_merge<128>(a, ns_a, slot_b, ns_b, st);
     else launch_merge<64>(a, ns_a, slot_b, ns_b, st);
   };
   if (part == kAttendAll) {
-    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, ns_all, 0, sel_idx, idx_bs,
+    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, 0, 0, sel_idx, idx_bs,
                           l_start);
     a.to_slots = 0;
-    launch(ns_all);
+    launch(ns_all, 0);
     if (ns_all > 1) merge(ns_all, 0, 0);
   } else if (part == kAttendLocal) {
-    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1, ns_local, 0);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1, 0, 0);
     a.to_slots = 1;
-    launch(ns_local);
+    launch(ns_local, 0);
   } else {
     if (ns_sel > 0) {
-      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, ns_sel, plan.local, sel_idx, idx_bs, l_start);
+      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, 0, 0, sel_idx, idx_bs, l_start);
       a.to_slots = 1;
-      launch(ns_sel);
+      launch(ns_sel, plan.local);
     }
     merge(ns_local, plan.local, ns_sel);
   }
@@ -820,18 +876,11 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
   a.sel_bs_bytes = sel_bs * 2;
-  // the planned number of slices (two where one is planned) is shared out in proportion to the two parts' lengths, at
-  // least one each: never more than kMaxSlots, nor more than the workspace holds
+  // the planned slices of the two parts' tiles laid end to end
   const SplitPlan plan = plan_splits(l_c, a.group, h_kv, batch);
   const int first_rows = l_c < a.qpt ? l_c : a.qpt;
-  const int64_t keys_a = n_loc + (l_c + 1) / 2, keys_b = i_end + n_sel;
-  int ns_b = keys_b > 0 ? (int)((plan.all * keys_b + (keys_a + keys_b) / 2) / (keys_a + keys_b)) : 0;
-  if (ns_b > plan.all - 1) ns_b = plan.all - 1;
-  if (keys_b > 0 && ns_b < 1) ns_b = 1;
-  int ns_a = plan.all - ns_b < 1 ? 1 : plan.all - ns_b;
-  ns_a = clamp_splits(ns_a, n_loc + first_rows);
-  if (ns_b > 0) ns_b = clamp_splits(ns_b, keys_b);
-  const int n_slot = ns_a + ns_b;
+  const int64_t keys_b = i_end + n_sel;
+  const int n_slot = clamp_splits(plan.all, align_up(n_loc + first_rows, kKT) + keys_b);
   const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
   a.part_o = nullptr;
   a.part_ml = nullptr;
@@ -843,9 +892,9 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   }
   a.n_slot = n_slot;
   a.to_slots = 0;
-  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1, ns_a, 0);
-  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0, ns_b, ns_a);
-  launch_tiles(a, d, n_slot, st);
+  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1, 0, 0);
+  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0, 0, 0);
+  launch_tiles(a, d, n_slot, 0, st);
   if (n_slot > 1) {
     if (d == 128) launch_merge<128>(a, n_slot, 0, 0, st);
     else launch_merge<64>(a, n_slot, 0, 0, st);

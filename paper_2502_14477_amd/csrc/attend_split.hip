@@ -148,7 +148,8 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   const int row_last = rt * kRows + kRows - 1 < n_rows ? rt * kRows + kRows - 1 : n_rows - 1;
   const uint32_t n_vis = V.n_fixed + (V.with_chunk ? (a.group_log2 >= 0 ? row_last >> a.group_log2 : row_last / a.group) + 1 : 0);     // keys the tile's last row sees
   const uint32_t n_tiles = (n_vis + kKT - 1) / kKT;
-  const uint32_t tile_begin = slice_tile(V, n_tiles, split), tile_end = slice_tile(V, n_tiles, split + 1);
+  const uint32_t tile_begin = slice_tile(n_tiles, split, V.n_split, V.split_step);
+  const uint32_t tile_end = slice_tile(n_tiles, split + 1, V.n_split, V.split_step);
   const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
   const uint32_t vis = V.n_fixed + (V.with_chunk ? c + 1 : 0);
   const uint32_t lim = vis < k_end ? vis : k_end;                           // first virtual key this lane's row may NOT see

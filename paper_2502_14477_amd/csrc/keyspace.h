@@ -52,19 +52,22 @@ struct KeyView {
   uint32_t idx_limit;                     // indices are clamped into [0, idx_limit)
   int with_chunk;                         // 1: the virtual sequence ends with the current chunk (causal); 0: every key is visible to every row
   int n_split;                            // slices of this view (view 0's slices come first)
-  uint32_t split_step;                    // 2^32 / n_split, rounded up (set_splits)
+  uint32_t split_step;                    // 2^32 / n_split, rounded up
   int slot0;                              // partial results of slice s go to slot slot0 + s
 };
 
+static inline uint32_t split_step(int n_split) {
+  return n_split > 1 ? (uint32_t)((((uint64_t)1 << 32) + n_split - 1) / n_split) : 0u;
+}
 static inline void set_splits(KeyView* v, int n_split, int slot0) {
   v->n_split = n_split;
-  v->split_step = n_split > 1 ? (uint32_t)((((uint64_t)1 << 32) + n_split - 1) / n_split) : 0u;
+  v->split_step = split_step(n_split);
   v->slot0 = slot0;
 }
 // First of n_tiles tiles of slice s (s = n_split: behind the last): n_tiles s / n_split without a division, which as a 64-bit
 // one was a third of the instructions in front of a kernel's first load.
-__device__ __forceinline__ uint32_t slice_tile(const KeyView& v, uint32_t n_tiles, uint32_t s) {
-  return s >= (uint32_t)v.n_split ? n_tiles : __umulhi(n_tiles, s * v.split_step);
+__device__ __forceinline__ uint32_t slice_tile(uint32_t n_tiles, uint32_t s, int n_split, uint32_t step) {
+  return s >= (uint32_t)n_split ? n_tiles : __umulhi(n_tiles, s * step);
 }
 
 // The grid of the tiled kernels: workgroups of one (batch entry, KV head) pair on one XCD (workgroup w runs on XCD w % 8) where

@@ -212,6 +212,22 @@ def test_selection_time_does_not_depend_on_one_large_query(esa, l_c):
     assert np.array_equal(idx.cpu().numpy(), np.sort(order))
 
 
+# local and global part of a re-encoded attention laid end to end: one slice of both, the seam inside a slice and between two,
+# a part of one tile, parts that end inside a tile
+@pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
+    (33, 8, 8, 128, 700, 40, 16, 100, 130), (40, 8, 8, 64, 300, 17, 3, 70, 90), (1, 8, 2, 64, 1200, 70, 5, 63, 300),
+    (1, 8, 8, 128, 900, 16, 64, 48, 64), (2, 16, 2, 128, 1500, 33, 1, 700, 1), (1, 32, 8, 128, 3000, 65, 128, 1000, 130)])
+def test_reencoded_attention_over_slices_of_both_parts(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
+    say(f"attend_reencoded B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    Kd, Vd = f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16")
+    ks, vs = esa.esa_gather_kv(Kd, Vd, torch.from_numpy(sel).cuda())
+    O = esa.esa_attend_reencoded(f64_to_dev(q, "bf16"), Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5)
+    for b in range(B):
+        want, _ = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
+
+
 # more pairs of batch entry and KV head than a grid takes in z (65535): few tokens and a chunk
 @pytest.mark.parametrize("l_C", [1, 16])
 def test_attention_over_more_pairs_than_one_grid(esa, l_C):
