@@ -153,6 +153,18 @@ __host__ __device__ inline int64_t mfma_blocks(int64_t n) {
 __host__ __device__ inline size_t mfma_lds_bytes(int64_t per, int d_c) {
   return (size_t)per * 32 * d_c * sizeof(bf16_t) + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t);
 }
+// Sweep 0 of a chunk of more than kStageFrom queries brings the first block of them in through LDS, behind the share where
+// they fit beside it.  Fewer waves with queries hold the address unit for less time than the further trip takes.  The score
+// call, us, fragments from memory against LDS: 512 queries 37.3 / 34.8 (128 thousand tokens), 22.7 / 20.8 (48), 17.4 / 15.5 (12);
+// 256 24.3 / 24.1, 16.6 / 16.2, 13.6 / 13.3; 192 22.3 / 22.6, 15.6 / 15.7, 12.8 / 13.0; 77 20.7 / 21.5, 14.2 / 15.0, 11.7 / 12.6.
+constexpr int kStageFrom = 192;
+__host__ __device__ inline bool query_stage_fits(int64_t per, int d_c) { return d_c == 64 || per <= 4; }
+__host__ __device__ inline size_t mfma_sweep0_lds_bytes(int64_t per, int d_c, int l_c) {
+  if (l_c <= kStageFrom) return mfma_lds_bytes(per, d_c);
+  const size_t tile = 32 * d_c * sizeof(bf16_t), share = per * tile, rows = 16 * tile;
+  if (query_stage_fits(per, d_c)) return share + rows;
+  return share + tile > rows ? share + tile : rows;         // (the last tile's step fetches one tile more)
+}
 // Row maxima of the matrix-core path: one row of mfma_mu_stride(l_c) floats per batch entry, so that groups
 // of four are 16-byte aligned and in bounds for every query tile that holds a query.
 __host__ __device__ inline int mfma_mu_stride(int l_c) { return (l_c + 63) / 64 * 64; }
@@ -445,24 +457,85 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     if (first_hist)
       for (int i = tid; i < kRadixBins; i += kThreads) digit_hist[i] = 0u;
   }
-  request_query_block(0);
-  __builtin_amdgcn_sched_barrier(0);
-  {
-    const uint32_t row_in_load = (64 / kPieces) * wave + lane / kPieces;
-    const uint32_t piece = (lane % kPieces) ^ swizzle(row_in_load);
+  const uint32_t row_in_load = (64 / kPieces) * wave + lane / kPieces;
+  const uint32_t piece = (lane % kPieces) ^ swizzle(row_in_load);
+  auto request_share = [&](int from, int to) {
     const int n_loads = tpb / kTilesPerLoad;                 // tpb is even
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
+    for (int i = from; i < to; ++i) {
       const int t = i < n_loads ? i : n_loads - 1;
       uint32_t row = 32 * kTilesPerLoad * t + row_in_load;
       row = row < last_row ? row : last_row;
       __builtin_amdgcn_global_load_lds((global_void*)(kshare + (size_t)row * (kDc * sizeof(bf16_t)) + piece * 16),
                                        (lds_void*)(lds_raw + (size_t)(8 * t + wave) * 1024), 16, 0, 0);
     }
+  };
+  const bool room = query_stage_fits(tpb, kDc);
+  if (PASS == 0 && l_c > kStageFrom) {
+    // The first query block comes in through LDS, whole rows of 256 (128) bytes, four (eight) to an instruction, into a place
+    // of each wave's own; read as fragments, 16 bytes of 32 rows to an instruction, it held the address unit for 2 us before
+    // the share's first request got through.  Behind a short share there is room for all of it; beside a long one half the
+    // rows at a time take the place of tiles 8 to 15, which are requested when every wave is done with it.
+    constexpr int kRowsPerLoad = 64 / kPieces, kTileLoads = 32 / kRowsPerLoad;
+    const uint32_t stage = room ? (uint32_t)(tpb * kTileBytes + wave * kMT * kTileBytes) : (uint32_t)(kWaves * kTileBytes + wave * kTileBytes);
+    auto request_rows = [&](int mt, uint32_t to) {
+#pragma unroll
+      for (int i = 0; i < kTileLoads; ++i) {
+        const uint32_t in_tile = kRowsPerLoad * i + lane / kPieces;
+        int row = wave * kQPerWave + 32 * mt + (int)in_tile;
+        row = row < l_c ? row : l_c - 1;
+        __builtin_amdgcn_global_load_lds((global_void*)(q + (int64_t)row * kDc + ((lane % kPieces) ^ swizzle(in_tile)) * 8),
+                                         (lds_void*)(lds_raw + to + 1024 * i), 16, 0, 0);
+      }
+    };
+    auto read_rows = [&](int mt, uint32_t from) {             // requests and wait in one block: the registers are complete behind it
+      const uint32_t at = frag0_at + from;
+      if constexpr (kKSteps == 8)
+        asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                     "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3]), "=&v"(a[mt][kKSteps - 4]),
+                       "=&v"(a[mt][kKSteps - 3]), "=&v"(a[mt][kKSteps - 2]), "=&v"(a[mt][kKSteps - 1])
+                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u), "v"(at ^ 224u)
+                     : "memory");
+      else
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3])
+                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u)
+                     : "memory");
+    };
+    auto landed = [&](auto left) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(left)::value) : "memory"); };
+    static_assert(kMT == 2, "two tiles of queries");
+    if (room) {
+      request_rows(0, stage);
+      request_rows(1, stage + kTileBytes);
+      request_share(0, kLoads);
+      landed(std::integral_constant<int, kLoads>());
+      read_rows(0, stage);
+      read_rows(1, stage + kTileBytes);
+      wait_loads_then_barrier<kLeftFirst>();                 // tiles 0 and 1
+    } else {
+      request_rows(0, stage);
+      request_share(0, kLoads / 2);
+      landed(std::integral_constant<int, kLoads / 2>());
+      read_rows(0, stage);
+      request_rows(1, stage);
+      landed(std::integral_constant<int, 0>());              // the first half of the share, too
+      read_rows(1, stage);
+      wait_loads_then_barrier<0>();
+      request_share(kLoads / 2, kLoads);
+    }
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) aux[mt][v] = -INFINITY;
+  } else {
+    request_query_block(0);
+    __builtin_amdgcn_sched_barrier(0);
+    request_share(0, kLoads);
+    __builtin_amdgcn_sched_barrier(0);
+    queries_arrived(true);
+    wait_loads_then_barrier<kLeftFirst, true>();               // tiles 0 and 1 (and this wave's LDS writes above)
   }
-  __builtin_amdgcn_sched_barrier(0);
-  queries_arrived(true);
-  wait_loads_then_barrier<kLeftFirst, true>();               // tiles 0 and 1 (and this wave's LDS writes above)
 
   // ---- query blocks (chunks longer than 512 tokens take several); from the second on, the share is in LDS
   for (int qb = 0; qb * kQPerBlock < l_c; ++qb) {
@@ -976,12 +1049,14 @@ int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int
                   bf16_t* qfrag, int64_t qfrag_bs, hipStream_t st) {
   const int per = (int)mfma_tiles_per_block(n), nblk = (int)mfma_blocks(n);
   const dim3 grid(nblk, batch);
-  const size_t lds = mfma_lds_bytes(per, DC);
+  const size_t lds = mfma_lds_bytes(per, DC), most = mfma_lds_bytes(kMaxTilesPerBlock, DC);
+  const size_t most0 = mfma_sweep0_lds_bytes(DC == 64 ? kMaxTilesPerBlock : 4, DC, kQPerBlock);          // 128 and 160 KB
+  static_assert(kQPerBlock == 512, "mfma_sweep0_lds_bytes");
   static OncePerDevice raised;
   const int rc = raise_lds_limit(raised, {(const void*)score_mfma_bf16<0, DC>, (const void*)score_mfma_bf16<1, DC>},
-                                 mfma_lds_bytes(kMaxTilesPerBlock, DC), "score_mfma_bf16");
+                                 most > most0 ? most : most0, "score_mfma_bf16");
   if (rc != ESA_OK) return rc;
-  score_mfma_bf16<0, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per, nullptr,
+  score_mfma_bf16<0, DC><<<grid, kThreads, mfma_sweep0_lds_bytes(per, DC, l_c), st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per, nullptr,
                                                       0, qfrag, qfrag_bs, nblk);
   score_rowmax_reduce<<<dim3((l_c + 3) / 4, batch), 256, 0, st>>>(part, nblk, l_c, mu, mfma_mu_stride(l_c), hists, hists_bs);
   score_mfma_bf16<1, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per,

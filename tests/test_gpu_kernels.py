@@ -98,9 +98,11 @@ def test_attention_outputs_are_the_exact_ones_rounded(esa, H, H_kv, d, l_C):
     assert elsewhere <= 1.5e-3
 
 
-# the shortest shares, shares with every number of load groups in flight, two blocks of queries
+# the shortest shares, shares with every number of load groups in flight, two blocks of queries; the first block through LDS
+# (more than 192 queries): behind a short share, in the place of the last tiles of a long one, a block that is not full
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 40, 1, 64, 0), (1, 64, 8193, 64, 0), (2, 512, 33000, 64, 0), (1, 530, 66000, 64, 1),
-                                             (1, 20, 131072, 64, 0), (1, 96, 40000, 128, 0)])
+                                             (1, 20, 131072, 64, 0), (1, 96, 40000, 128, 0), (1, 192, 33000, 128, 0), (1, 193, 20, 128, 0),
+                                             (2, 500, 20000, 128, 0), (1, 257, 40000, 128, 0), (1, 700, 131072, 128, 0), (1, 449, 66000, 128, 1)])
 def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
     say(f"score B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
     rng = np.random.default_rng(n + l_c)
