@@ -148,7 +148,7 @@ template <int D> __device__ __forceinline__ uint32_t v_swizzle(uint32_t row) { r
 // Head size 64 keeps what it computes in fp32: a probability goes into the second product as three bf16 terms, which
 // together are its fp32 value, and the results of a slice are stored as they were accumulated.  (One term and fp16 slices,
 // as for head size 128, put the outputs 2.3e-3 from the 64-bit result where rounding them to bf16 alone makes 1.66e-3; a
-// step of 512 tokens at 32k takes 81 us for it, 63 with the narrow formats.)
+// step of 512 tokens at 32k takes 80 us for it, 63 with the narrow formats.)
 template <int D> constexpr bool kFp32Probs = D == 64;
 // Natural-log normaliser from a reference in the log2 domain and the sum of exponentials relative to it.  The fp32 form
 // adds the logarithm in its own domain, one rounding of the sum instead of two.
