@@ -423,9 +423,9 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
     const float cand = halves_max(mx) * a.c2, m_old = m_run;
     const bool moved = cand > m_run + (kFp32Probs<D> ? 0.f : kLazy);
     m_run = moved ? cand : m_run;
+    float corr = 1.f;
     if (__ballot(moved) != 0ull) {
-      const float corr = __builtin_amdgcn_exp2f(m_old - m_run);
-      l_run *= corr;
+      corr = __builtin_amdgcn_exp2f(m_old - m_run);
 #pragma unroll
       for (int md = 0; md < kMD; ++md)
 #pragma unroll
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
           if (kp + 1 < 4 && at * kMat / 8 == j) piece(kp + 1, at);
         __builtin_amdgcn_sched_barrier(0);
       }
-    l_run += psum;
+    l_run = __builtin_fmaf(l_run, corr, psum);          // rounded once
   };
 
   // Turn t: tile t, requested two turns before (a turn takes 2 us, a tile that comes from HBM sometimes longer).  Its own requests

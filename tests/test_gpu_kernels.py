@@ -98,6 +98,43 @@ def test_attention_outputs_are_the_exact_ones_rounded(esa, H, H_kv, d, l_C):
     assert elsewhere <= 1.5e-3
 
 
+# Two tiles of one slice, the second with the larger logit (head size 64, where the reference follows the maximum at once): the
+# sum of exponentials moves to the new reference and takes the new tile's 1 with one rounding.  (Rounded twice, a fifth of these
+# sums are another number.)  The logits are products of two bf16 numbers, so everything up to the sum is known exactly but for
+# the exponentials, which torch takes from the same instruction.
+def test_sum_of_exponentials_is_rounded_once_when_its_reference_moves(esa):
+    say("attend, one slice of two tiles")
+    B, H, d, l_C, t0 = 32, 8, 64, 16, 128
+    rng = np.random.default_rng(d)
+    bf = lambda x: torch.from_numpy(np.asarray(x, np.float32)).bfloat16()
+    a = bf(1.0 + rng.random((B, l_C, H)))                       # the only component of a query
+    b = bf(-rng.random((2, B, H)) * 0.6 - 0.05)                 # ... of keys 0 and 1; key 64 has logit 0, all others vanish
+    q = torch.zeros((B, l_C, H, d), dtype=torch.bfloat16)
+    K = torch.zeros((B, t0 + l_C, H, d), dtype=torch.bfloat16)
+    q[..., 0] = a
+    K[..., 0] = -1024.0
+    K[:, 0, :, 0], K[:, 1, :, 0], K[:, 64, :, 0] = b[0], b[1], 0.0
+    V = torch.zeros_like(K)
+    _, lse = esa.esa_attend(q.cuda(), K.cuda(), V.cuda(), t0, 64, 64, None, None, scale=1.0, return_lse=True)
+
+    f32 = lambda x: x.to(torch.float32)
+    c2 = float(np.float32(1.4426950408889634))
+    s = a.double()[None] * b.double()[:, :, None, :]             # exact, as are the differences below in float64
+    m = f32(s.max(0)[0] * c2)
+    p = torch.exp2(f32(s * c2 - m.double()).cuda()).cpu()
+    first = p[0] + p[1]
+    corr = torch.exp2(m.cuda()).cpu()
+    total = f32(first.double() * corr.double() + 1.0)
+    twice = first * corr + 1.0
+    want, other = torch.log(total.cuda()).double(), torch.log(twice.cuda()).double()
+    # one place of the sum apart, 1 to 1.2e-7 / sum: at most two places of the logarithm, which itself errs by up to one: it cannot
+    # hide the difference in more than half of the rows, and a sum that is rounded twice is nearer in none but those
+    told = want != other
+    near = float(((lse - want).abs() < (lse - other).abs())[told].double().mean())
+    print(f"{float(told.double().mean()):.2f} of the rows tell, {near:.3f} of these are nearer to one rounding", flush=True)
+    assert told.sum() > 400 and near > 0.5
+
+
 # the shortest shares, shares with every number of load groups in flight, two blocks of queries; the first block through LDS
 # (more than 192 queries): behind a short share, in the place of the last tiles of a long one, a block that is not full
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 40, 1, 64, 0), (1, 64, 8193, 64, 0), (2, 512, 33000, 64, 0), (1, 530, 66000, 64, 1),
