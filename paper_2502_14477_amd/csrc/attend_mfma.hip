@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   // front of every LDS read.  (They have no result registers that it could reuse under way.)  Every wave issues the same
   // number per turn and waits by count.
   auto dma16 = [&](const char* src, uint32_t dst) __attribute__((always_inline)) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
   };
   // Which row a virtual key is.  Index-driven selected rows (the gather folded into this kernel): the entries of a tile's
   // selected keys go to LDS a turn ahead of the tile's keys, lane l's being that of key l.  No branch on where in the
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   auto idx_load = [&](uint32_t t, int stage) __attribute__((always_inline)) {
     const int32_t js = (int32_t)(t * kKT + lane - V.i_end);
     const uint32_t at = js < 0 ? 0u : (uint32_t)js < list_last ? (uint32_t)js : list_last;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(idx_lds + stage * (kWaves * kKT * 4)), "v"(list + at) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(idx_lds + stage * (kWaves * kKT * 4)), "v"(list + at) : "memory", "m0");
   };
   // The rows of a tile that this lane fetches a piece of: numbers in the cache, or complements of numbers in the gathered buffers.
   struct Rows {
