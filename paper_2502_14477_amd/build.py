@@ -23,7 +23,7 @@ FLAGS = [
     "-mllvm", "-amdgpu-kernarg-preload-count=14",
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-function",
+    "-Wall", "-Werror=unused-function",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 

@@ -120,26 +120,6 @@ __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
   return *(uint32_t*)&h;
 }
 
-// Row of virtual key j: which buffer, and its number there (branch-free).
-struct RowRef {
-  bool in_sel;
-  uint32_t row;
-};
-__device__ __forceinline__ uint32_t clamped_index(const KeyView& V, const int32_t* sidx, uint32_t pos) {
-  const int32_t v = sidx[pos];      // a middle token's position; clamped so that a bad index cannot leave the cache
-  return v < 0 ? 0u : ((uint32_t)v < V.idx_limit ? (uint32_t)v : V.idx_limit - 1);
-}
-// sidx: this batch element's index list, or null when the selected rows come from the gathered buffer
-__device__ __forceinline__ RowRef row_ref(const KeyView& V, const int32_t* sidx, uint32_t j) {
-  const bool in_i = j < V.i_end;
-  const bool in_s = !in_i && (j < V.i_end + V.n_sel);
-  RowRef r;
-  r.row = in_i ? j : (in_s ? j - V.i_end : j - V.i_end - V.n_sel + V.l_start);
-  r.in_sel = in_s && !sidx;
-  if (in_s && sidx) r.row = clamped_index(V, sidx, r.row);
-  return r;
-}
-
 // Swizzles of the LDS tiles: the 16-byte slot of piece p of K row R is p ^ k_swizzle(R), the 64-byte slot of chunk c
 // of V row R is c ^ v_swizzle(R).
 template <int D> __device__ __forceinline__ uint32_t k_swizzle(uint32_t row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
@@ -299,6 +279,9 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   // Loads into LDS are written out: the compiler, which cannot tell the stages apart, would put a wait for all of them in
   // front of every LDS read.  (They have no result registers that it could reuse under way.)  Every wave issues the same
   // number per turn and waits by count.
+  // (The compiler warns that it does not keep m0's value across them: it has none there.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
   auto dma16 = [&](const char* src, uint32_t dst) __attribute__((always_inline)) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
   };
@@ -314,6 +297,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
     const uint32_t at = js < 0 ? 0u : (uint32_t)js < list_last ? (uint32_t)js : list_last;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(idx_lds + stage * (kWaves * kKT * 4)), "v"(list + at) : "memory", "m0");
   };
+#pragma clang diagnostic pop
   // The rows of a tile that this lane fetches a piece of: numbers in the cache, or complements of numbers in the gathered buffers.
   struct Rows {
     int32_t at[kMyRows];
@@ -651,7 +635,7 @@ void esa_attend_merge(const void* __restrict__ part_o, const float* __restrict__
     ml[i] = *(const float2*)(part_ml + prow * 2);
     po[i] = *(const uint4*)((const char*)part_o + (prow * D + dim) * (16 / kPer));
   }
-  float M = -INFINITY;
+  float M = kNoKey;
 #pragma unroll
   for (int i = 0; i < NS; ++i) M = fmaxf(M, ml[i].x);
   float L = 0.f;
@@ -660,7 +644,7 @@ void esa_attend_merge(const void* __restrict__ part_o, const float* __restrict__
   for (int i = 0; i < kPer; ++i) acc[i] = 0.f;
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
-    const float w = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - M);
+    const float w = __builtin_amdgcn_exp2f(ml[i].x - M);
     const uint32_t u[4] = {po[i].x, po[i].y, po[i].z, po[i].w};
     L += w * ml[i].y;
 #pragma unroll
@@ -820,25 +804,24 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   }
   a.n_slot = n_slot;
   const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
-  a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0, 0, 0);   // unused
+  a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0);   // unused
   auto launch = [&](int n_split, int slot0) { launch_tiles(a, d, n_split, slot0, st); };
   auto merge = [&](int ns_a, int slot_b, int ns_b) {
     if (d == 128) launch_merge<128>(a, ns_a, slot_b, ns_b, st);
     else launch_merge<64>(a, ns_a, slot_b, ns_b, st);
   };
   if (part == kAttendAll) {
-    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, 0, 0, sel_idx, idx_bs,
-                          l_start);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, sel_idx, idx_bs, l_start);
     a.to_slots = 0;
     launch(ns_all, 0);
     if (ns_all > 1) merge(ns_all, 0, 0);
   } else if (part == kAttendLocal) {
-    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1, 0, 0);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1);
     a.to_slots = 1;
     launch(ns_local, 0);
   } else {
     if (ns_sel > 0) {
-      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, 0, 0, sel_idx, idx_bs, l_start);
+      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, sel_idx, idx_bs, l_start);
       a.to_slots = 1;
       launch(ns_sel, plan.local);
     }
@@ -892,8 +875,8 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   }
   a.n_slot = n_slot;
   a.to_slots = 0;
-  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1, 0, 0);
-  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0, 0, 0);
+  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1);
+  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0);
   launch_tiles(a, d, n_slot, 0, st);
   if (n_slot > 1) {
     if (d == 128) launch_merge<128>(a, n_slot, 0, 0, st);

@@ -34,7 +34,7 @@ __device__ __forceinline__ const char* key_row(const KeySpace& ks, int64_t j, bo
   return (values ? ks.v_cache : ks.k_cache) + (ks.l_start + j) * ks.tok_bytes;
 }
 
-// What a slice of a launch of the tiled kernels attends to: a query tensor and a virtual key sequence.  A launch
+// What the workgroups of a launch of the tiled kernels attend to: a query tensor and a virtual key sequence.  A launch
 // carries two views; the usual one uses view 0 only, the re-encoded attention of Section 3.2 gives the local keys
 // (their own encoding of queries and keys, causal) to view 0 and the initial and selected keys (queries at the fixed
 // position, every key visible) to view 1, so that both parts run in one launch.  Keys and values have strides of
@@ -51,18 +51,10 @@ struct KeyView {
   int64_t idx_bs;                         // batch stride of the index list
   uint32_t idx_limit;                     // indices are clamped into [0, idx_limit)
   int with_chunk;                         // 1: the virtual sequence ends with the current chunk (causal); 0: every key is visible to every row
-  int n_split;                            // slices of this view (view 0's slices come first)
-  uint32_t split_step;                    // 2^32 / n_split, rounded up
-  int slot0;                              // partial results of slice s go to slot slot0 + s
 };
 
-static inline uint32_t split_step(int n_split) {
+static inline uint32_t split_step(int n_split) {                // 2^32 / n_split, rounded up: for slice_tile
   return n_split > 1 ? (uint32_t)((((uint64_t)1 << 32) + n_split - 1) / n_split) : 0u;
-}
-static inline void set_splits(KeyView* v, int n_split, int slot0) {
-  v->n_split = n_split;
-  v->split_step = split_step(n_split);
-  v->slot0 = slot0;
 }
 // First of n_tiles tiles of slice s (s = n_split: behind the last): n_tiles s / n_split without a division, which as a 64-bit
 // one was a third of the instructions in front of a kernel's first load.
@@ -98,7 +90,7 @@ struct CacheRef {               // cache rows as a launch function gets them (st
   int64_t k_stride, v_stride, k_bs, v_bs;
 };
 static inline KeyView make_view(const void* q, int64_t q_bs, const CacheRef& c, int64_t esz, int64_t i_end, int64_t n_sel,
-                                int64_t l_start, int64_t n_fixed, int with_chunk, int n_split, int slot0,
+                                int64_t l_start, int64_t n_fixed, int with_chunk,
                                 const int32_t* sel_idx = nullptr, int64_t idx_bs = 0, int64_t idx_limit = 1) {
   KeyView v;
   v.q = (const char*)q;
@@ -117,7 +109,6 @@ static inline KeyView make_view(const void* q, int64_t q_bs, const CacheRef& c, 
   v.idx_bs = idx_bs;
   v.idx_limit = (uint32_t)(idx_limit > 0 ? idx_limit : 1);
   v.with_chunk = with_chunk;
-  set_splits(&v, n_split, slot0);
   return v;
 }
 // Field-wise select of the view a workgroup works on (not an indexed load): every kernel argument is then fetched in
@@ -141,9 +132,6 @@ __device__ __forceinline__ KeyView pick_view(const KeyView (&view)[2], bool seco
   V.idx_bs = second ? v1.idx_bs : v0.idx_bs;
   V.idx_limit = second ? v1.idx_limit : v0.idx_limit;
   V.with_chunk = second ? v1.with_chunk : v0.with_chunk;
-  V.n_split = second ? v1.n_split : v0.n_split;
-  V.split_step = second ? v1.split_step : v0.split_step;
-  V.slot0 = second ? v1.slot0 : v0.slot0;
   return V;
 }
 
