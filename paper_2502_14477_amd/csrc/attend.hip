@@ -192,11 +192,11 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
     const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
     const int64_t n_local = t0 - sg.l_start, n_global = sg.i_end + n_sel;
     if (!two_parts)
-      return launch_attend_split(call, make_view(q, q_bs, cache, esz, sg.i_end, n_sel, sg.l_start, n_fixed, 1, sel_idx,
+      return launch_attend_split(call, make_view(q, q_bs, cache, esz, sg.i_end, n_sel, sg.l_start, n_fixed, 1, 0, 0, sel_idx,
                                                  idx_bs, sg.l_start), nullptr, st);
     if (part == kAttendLocal)
-      return launch_attend_split_early(call, make_view(q, q_bs, cache, esz, 0, 0, sg.l_start, n_local, 1), n_local + l_c, st);
-    return launch_attend_split_late(call, make_view(q, q_bs, cache, esz, sg.i_end, n_sel, sg.l_start, n_global, 0, sel_idx,
+      return launch_attend_split_early(call, make_view(q, q_bs, cache, esz, 0, 0, sg.l_start, n_local, 1, 0, 0), n_local + l_c, st);
+    return launch_attend_split_late(call, make_view(q, q_bs, cache, esz, sg.i_end, n_sel, sg.l_start, n_global, 0, 0, 0, sel_idx,
                                                     idx_bs, sg.l_start), n_global, n_local + l_c, st);
   }
   KeySpace ks;
@@ -318,8 +318,8 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
                                         sel_bs, scale, out, lse, batch, out_bs, ws, own, st);
   if (split) {
     const SplitCall call = {l_c, h, h_kv, d, dtype, batch, scale, k_sel, v_sel, sel_bs, out, out_bs, lse, ws, own};
-    const KeyView a = make_view(q_loc, qw_bs, local, (int64_t)esz, 0, 0, 0, n_loc, 1);
-    const KeyView b = make_view(q_glob, qw_bs, cache, (int64_t)esz, sg.i_end, n_sel, 0, sg.i_end + n_sel, 0);
+    const KeyView a = make_view(q_loc, qw_bs, local, (int64_t)esz, 0, 0, 0, n_loc, 1, 0, 0);
+    const KeyView b = make_view(q_glob, qw_bs, cache, (int64_t)esz, sg.i_end, n_sel, 0, sg.i_end + n_sel, 0, 0, 0);
     return launch_attend_split(call, a, &b, st);
   }
   rc = launch_attend(kAttendLocal, ESA_SPLIT_ALGORITHM1, q_loc, l_c, h, h_kv, d, k_loc, v_loc, kv_row, n_loc, 0, n_loc,

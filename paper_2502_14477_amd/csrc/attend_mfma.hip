@@ -804,24 +804,25 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   }
   a.n_slot = n_slot;
   const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
-  a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0);   // unused
+  a.view[1] = make_view(q, q_bs, cache, 2, 0, 0, 0, 0, 0, 0, 0);   // unused
   auto launch = [&](int n_split, int slot0) { launch_tiles(a, d, n_split, slot0, st); };
   auto merge = [&](int ns_a, int slot_b, int ns_b) {
     if (d == 128) launch_merge<128>(a, ns_a, slot_b, ns_b, st);
     else launch_merge<64>(a, ns_a, slot_b, ns_b, st);
   };
   if (part == kAttendAll) {
-    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, sel_idx, idx_bs, l_start);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_end, n_sel, l_start, i_end + n_sel + (t0 - l_start), 1, 0, 0, sel_idx, idx_bs,
+                          l_start);
     a.to_slots = 0;
     launch(ns_all, 0);
     if (ns_all > 1) merge(ns_all, 0, 0);
   } else if (part == kAttendLocal) {
-    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1);
+    a.view[0] = make_view(q, q_bs, cache, 2, i_early, 0, l_start, i_early + (t0 - l_start), 1, 0, 0);
     a.to_slots = 1;
     launch(ns_local, 0);
   } else {
     if (ns_sel > 0) {
-      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, sel_idx, idx_bs, l_start);
+      a.view[0] = make_view(q, q_bs, cache, 2, i_late, n_sel, 0, i_late + n_sel, 0, 0, 0, sel_idx, idx_bs, l_start);
       a.to_slots = 1;
       launch(ns_sel, plan.local);
     }
@@ -875,8 +876,8 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   }
   a.n_slot = n_slot;
   a.to_slots = 0;
-  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1);
-  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0);
+  a.view[0] = make_view(q_loc, qw_bs, local, 2, 0, 0, 0, n_loc, 1, 0, 0);
+  a.view[1] = make_view(q_glob, qw_bs, cache, 2, i_end, n_sel, 0, keys_b, 0, 0, 0);
   launch_tiles(a, d, n_slot, 0, st);
   if (n_slot > 1) {
     if (d == 128) launch_merge<128>(a, n_slot, 0, 0, st);

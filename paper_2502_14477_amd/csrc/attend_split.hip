@@ -63,14 +63,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return *(uint32_t*)&b;
 }
 
-struct Slices {       // of a view: slices, 2^32 over their number, the slot that the first one's partial results go to
-  int n;
-  uint32_t step;
-  int slot0;
-};
 struct SplitArgs {
   KeyView view[2];
-  Slices slices[2];   // view 0's come first
   void* out;
   float* lse;
   float* part_o;      // [batch][l_c][h][n_slot][D] un-normalised
@@ -134,14 +128,12 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // ---- which (batch element, KV head, row tile, slice)
-  const int n_slices = a.slices[0].n + a.slices[1].n;
+  const int n_slices = a.view[0].n_split + a.view[1].n_split;
   const Placed at = place_in(a.grid);
   const int b = at.pair / a.h_kv, g = at.pair - b * a.h_kv, rt = at.row_tile, slice = at.slice;
-  const bool second = slice >= a.slices[0].n;
+  const bool second = slice >= a.view[0].n_split;
   const KeyView V = pick_view(a.view, second);
-  const int split = slice - (second ? a.slices[0].n : 0);
-  const int n_split = second ? a.slices[1].n : a.slices[0].n, slot0 = second ? a.slices[1].slot0 : a.slices[0].slot0;
-  const uint32_t step = second ? a.slices[1].step : a.slices[0].step;
+  const int split = slice - (second ? a.view[0].n_split : 0);
   const char* kc = V.k_cache + (int64_t)b * V.k_bs_bytes + (int64_t)g * kRowBytes;
   const char* vc = V.v_cache + (int64_t)b * V.v_bs_bytes + (int64_t)g * kRowBytes;
   const bool gathered = V.n_sel && !V.sel_idx;
@@ -156,8 +148,8 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   const int row_last = rt * kRows + kRows - 1 < n_rows ? rt * kRows + kRows - 1 : n_rows - 1;
   const uint32_t n_vis = V.n_fixed + (V.with_chunk ? (a.group_log2 >= 0 ? row_last >> a.group_log2 : row_last / a.group) + 1 : 0);     // keys the tile's last row sees
   const uint32_t n_tiles = (n_vis + kKT - 1) / kKT;
-  const uint32_t tile_begin = slice_tile(n_tiles, split, n_split, step);
-  const uint32_t tile_end = slice_tile(n_tiles, split + 1, n_split, step);
+  const uint32_t tile_begin = slice_tile(n_tiles, split, V.n_split, V.split_step);
+  const uint32_t tile_end = slice_tile(n_tiles, split + 1, V.n_split, V.split_step);
   const uint32_t k_end = tile_end * kKT < n_vis ? tile_end * kKT : n_vis;
   const uint32_t vis = V.n_fixed + (V.with_chunk ? c + 1 : 0);
   const uint32_t lim = vis < k_end ? vis : k_end;                           // first virtual key this lane's row may NOT see
@@ -431,7 +423,7 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
       }
       if (a.lse && p == 0) a.lse[prow] = lse_of<T>(M, L);
     } else {
-      const int64_t slot = prow * a.n_slot + slot0 + split;
+      const int64_t slot = prow * a.n_slot + V.slot0 + split;
       *(f32x4*)(a.part_o + slot * D + p * 4) = sum;
       if (p == 0) *(float2*)(a.part_ml + slot * 2) = make_float2(M, L);
     }
@@ -557,12 +549,10 @@ int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
   return ESA_OK;
 }
 
-Slices make_slices(int n, int slot0) { return {n, split_step(n), slot0}; }
-
 template <typename T, int D>
 void run(const SplitCall& c, const SplitArgs& args, hipStream_t st) {
   SplitArgs a = args;
-  for_pair_grids((int64_t)c.batch * c.h_kv, a.n_rt, a.slices[0].n + a.slices[1].n, [&](dim3 grid, PairGrid placed) {
+  for_pair_grids((int64_t)c.batch * c.h_kv, a.n_rt, a.view[0].n_split + a.view[1].n_split, [&](dim3 grid, PairGrid placed) {
     a.grid = placed;
     attend_split<T, D><<<grid, 64 * kWaves, 0, st>>>(a);
   });
@@ -632,9 +622,9 @@ int launch_attend_split(const SplitCall& c, KeyView v0, const KeyView* v1, hipSt
   }
   n0 = split_count(n0, k0);
   a.view[0] = v0;
-  a.slices[0] = make_slices(n0, 0);
+  set_splits(&a.view[0], n0, 0);
   a.view[1] = k1 > 0 ? *v1 : v0;
-  a.slices[1] = make_slices(n1, n0);
+  set_splits(&a.view[1], n1, n0);
   if (n0 + n1 > 1) {
     const int rc = with_slots(&a, c, n0 + n1);
     if (rc != ESA_OK) return rc;
@@ -652,9 +642,9 @@ int launch_attend_split_early(const SplitCall& c, KeyView early, int64_t early_k
   if (rc != ESA_OK) return rc;
   a.to_slots = 1;
   a.view[0] = early;
-  a.slices[0] = make_slices(split_count(limit, early_keys), 0);
+  set_splits(&a.view[0], split_count(limit, early_keys), 0);
   a.view[1] = early;
-  a.slices[1] = make_slices(0, 0);
+  set_splits(&a.view[1], 0, 0);
   dispatch(c, RunIt{c, a, st});
   ESA_LAUNCH_CHECK("attend_split (early part)");
   return ESA_OK;
@@ -667,11 +657,11 @@ int launch_attend_split_late(const SplitCall& c, KeyView late, int64_t late_keys
   if (rc != ESA_OK) return rc;
   a.to_slots = 1;
   a.view[0] = late;
-  a.slices[0] = make_slices(late_keys > 0 ? split_count(limit, late_keys) : 0, n_early);
+  set_splits(&a.view[0], late_keys > 0 ? split_count(limit, late_keys) : 0, n_early);
   a.view[1] = late;
-  a.slices[1] = make_slices(0, 0);
+  set_splits(&a.view[1], 0, 0);
   if (late_keys > 0) dispatch(c, RunIt{c, a, st});
-  dispatch(c, MergeIt{c, a, n_early + a.slices[0].n, st});
+  dispatch(c, MergeIt{c, a, n_early + a.view[0].n_split, st});
   ESA_LAUNCH_CHECK("attend_split (late part)");
   return ESA_OK;
 }

@@ -51,10 +51,20 @@ struct KeyView {
   int64_t idx_bs;                         // batch stride of the index list
   uint32_t idx_limit;                     // indices are clamped into [0, idx_limit)
   int with_chunk;                         // 1: the virtual sequence ends with the current chunk (causal); 0: every key is visible to every row
+  // The split-key kernel's, whose views have slices of their own (beside the views, in arguments of their own, they cost each of its launches
+  // 0.2 us: one token 8.06 -> 8.28 us); the matrix-core kernel lays its views' tiles end to end.
+  int n_split;                            // slices of this view (view 0's slices come first)
+  uint32_t split_step;                    // 2^32 / n_split, rounded up
+  int slot0;                              // partial results of slice s go to slot slot0 + s
 };
 
-static inline uint32_t split_step(int n_split) {                // 2^32 / n_split, rounded up: for slice_tile
+static inline uint32_t split_step(int n_split) {
   return n_split > 1 ? (uint32_t)((((uint64_t)1 << 32) + n_split - 1) / n_split) : 0u;
+}
+static inline void set_splits(KeyView* v, int n_split, int slot0) {
+  v->n_split = n_split;
+  v->split_step = split_step(n_split);
+  v->slot0 = slot0;
 }
 // First of n_tiles tiles of slice s (s = n_split: behind the last): n_tiles s / n_split without a division, which as a 64-bit
 // one was a third of the instructions in front of a kernel's first load.
@@ -63,7 +73,7 @@ __device__ __forceinline__ uint32_t slice_tile(uint32_t n_tiles, uint32_t s, int
 }
 
 // The grid of the tiled kernels: workgroups of one (batch entry, KV head) pair on one XCD (workgroup w runs on XCD w % 8) where
-// the pairs are a multiple of eight, decoded without a division.  x: 8 row tiles' worth of XCDs, or the row tiles; y: slices;
+// the pairs are a multiple of eight, decoded without a division (what is left is that of a pair into entry and head).  x: 8 row tiles' worth of XCDs, or the row tiles; y: slices;
 // z: pairs / 8, or the pairs.
 struct PairGrid {
   int xcd_log2;                           // 3, or 0
@@ -90,7 +100,7 @@ struct CacheRef {               // cache rows as a launch function gets them (st
   int64_t k_stride, v_stride, k_bs, v_bs;
 };
 static inline KeyView make_view(const void* q, int64_t q_bs, const CacheRef& c, int64_t esz, int64_t i_end, int64_t n_sel,
-                                int64_t l_start, int64_t n_fixed, int with_chunk,
+                                int64_t l_start, int64_t n_fixed, int with_chunk, int n_split, int slot0,
                                 const int32_t* sel_idx = nullptr, int64_t idx_bs = 0, int64_t idx_limit = 1) {
   KeyView v;
   v.q = (const char*)q;
@@ -109,6 +119,7 @@ static inline KeyView make_view(const void* q, int64_t q_bs, const CacheRef& c, 
   v.idx_bs = idx_bs;
   v.idx_limit = (uint32_t)(idx_limit > 0 ? idx_limit : 1);
   v.with_chunk = with_chunk;
+  set_splits(&v, n_split, slot0);
   return v;
 }
 // Field-wise select of the view a workgroup works on (not an indexed load): every kernel argument is then fetched in
@@ -132,6 +143,9 @@ __device__ __forceinline__ KeyView pick_view(const KeyView (&view)[2], bool seco
   V.idx_bs = second ? v1.idx_bs : v0.idx_bs;
   V.idx_limit = second ? v1.idx_limit : v0.idx_limit;
   V.with_chunk = second ? v1.with_chunk : v0.with_chunk;
+  V.n_split = second ? v1.n_split : v0.n_split;
+  V.split_step = second ? v1.split_step : v0.split_step;
+  V.slot0 = second ? v1.slot0 : v0.slot0;
   return V;
 }
 
