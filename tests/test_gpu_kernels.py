@@ -267,6 +267,38 @@ def test_reencoded_attention_over_slices_of_both_parts(esa, B, H, H_kv, d, t0, l
         assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
 
 
+# Gathered rows: segment boundaries at a tile's edge, one key beside it, two of them inside one tile, no boundary but the sequence's
+# end; slices that end between.  The index-driven form takes the same keys in the same order.
+@pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
+    (1, 8, 8, 128, 900, 16, 64, 64, 64), (2, 8, 2, 128, 901, 33, 63, 65, 129), (1, 8, 2, 64, 800, 70, 1, 63, 62), (1, 16, 2, 64, 1500, 257, 0, 700, 640),
+    (3, 8, 8, 128, 700, 40, 20, 30, 10), (1, 32, 8, 128, 3000, 512, 128, 1000, 1), (1, 32, 8, 128, 600, 48, 0, 0, 500)])
+def test_attention_over_gathered_rows_is_the_index_driven_one(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
+    say(f"attend gathered B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16"), torch.from_numpy(sel).cuda()
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx)
+    O, lse = esa.esa_attend(qd, Kd, Vd, t0, l_I, l_L, ks, vs, return_lse=True)
+    O_idx, lse_idx = esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx, return_lse=True)
+    assert torch.equal(O, O_idx) and torch.equal(lse, lse_idx)
+    for b in range(B):
+        want, _ = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
+
+
+# 1.000 measured; 1.034 to 1.036 where one kernel served both forms and chose base and stride for each row
+def test_attention_over_gathered_rows_is_no_slower_than_the_index_driven_one(esa):
+    say("attend, 1024 queries, 8192 gathered rows")
+    l_C, t0, n_sel = 1024, 24000, 8192
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, K, V = (torch.randn((n, h, 128), generator=g, device="cuda").to(torch.bfloat16) for n, h in ((l_C, 32), (t0 + l_C, 8), (t0 + l_C, 8)))
+    idx = 128 + torch.randperm(t0 - 8192 - 128, generator=g, device="cuda")[:n_sel].sort()[0].to(torch.int32)
+    ks, vs = esa.esa_gather_kv(K, V, idx)
+    ratios = sorted(_time_us(lambda: esa.esa_attend(q, K, V, t0, 128, 8192, ks, vs), 40) /
+                    _time_us(lambda: esa.esa_attend_indexed(q, K, V, t0, 128, 8192, idx), 40) for _ in range(15))
+    print("gathered / indexed: " + " ".join(f"{r:.3f}" for r in ratios), flush=True)
+    assert ratios[7] <= 1.02
+
+
 # more pairs of batch entry and KV head than a grid takes in z (65535): few tokens and a chunk
 @pytest.mark.parametrize("l_C", [1, 16])
 def test_attention_over_more_pairs_than_one_grid(esa, l_C):
