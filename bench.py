@@ -38,7 +38,7 @@ VARIANT_CALLS = ("score_select_gather", "attend_indexed", "attend_local", "atten
 # WRITE_SIZE per dispatch, each scaled by what the same counter reads for a plain 256 MiB device copy:
 # x2.0 for FETCH_SIZE, x1.0 for WRITE_SIZE), summed over the kernels of the call.  Counters cannot be
 # read from inside this script, so a figure is attached only to the workload it was measured on and only
-# while the kernel sources are the ones it was measured on (TRAFFIC_TREE, see csrc_tree_hash).
+# while kernel sources and compiler flags are the ones it was measured on (TRAFFIC_TREE, see csrc_tree_hash).
 TRAFFIC_TREE = "aad80e20f7df12af"
 MEASURED_TRAFFIC_BYTES = {
     ("C3", 131072, "score"): 73538784,
@@ -65,7 +65,9 @@ MEASURED_TRAFFIC_BYTES = {
 
 
 def csrc_tree_hash():
-    """Fingerprint of the kernel sources: the stored traffic figures belong to exactly one such tree."""
+    """Fingerprint of the kernels as they are compiled, sources and flags: the stored traffic figures belong to exactly one
+    such tree.  (Paths are left out: the same tree elsewhere is the same.)"""
+    from paper_2502_14477_amd import build
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2502_14477_amd", "csrc")
     for name in sorted(os.listdir(csrc)):
@@ -73,6 +75,8 @@ def csrc_tree_hash():
             h.update(name.encode())
             with open(os.path.join(csrc, name), "rb") as f:
                 h.update(f.read())
+    flags = [f for f in build.FLAGS if f != "-I" and not os.path.isabs(f)]
+    h.update(json.dumps([flags, build.EXTRA_FLAGS], sort_keys=True).encode())
     return h.hexdigest()[:16]
 
 

@@ -1,4 +1,4 @@
-"""Rules of the kernel sources that a compiler does not check."""
+"""Rules of the kernel sources and of figures tied to them that a compiler does not check."""
 import glob
 import os
 import re
@@ -19,3 +19,18 @@ def test_inline_assembly_that_writes_m0_says_so():
     for f, s in writers:
         clobbers = s.rsplit(":", 1)[-1]
         assert '"m0"' in clobbers, (f, s)
+
+
+def test_measured_traffic_is_tied_to_the_compiler_flags(monkeypatch):
+    """A flag changes the code of every kernel as a change to its source does; where the tree lies does not."""
+    import bench
+    from paper_2502_14477_amd import build
+    here = bench.csrc_tree_hash()
+    at = build.FLAGS.index("-I") + 1
+    monkeypatch.setattr(build, "FLAGS", build.FLAGS[:at] + ["/elsewhere/include"] + build.FLAGS[at + 1:])
+    assert bench.csrc_tree_hash() == here
+    monkeypatch.setattr(build, "FLAGS", ["-O2" if f == "-O3" else f for f in build.FLAGS])
+    other = bench.csrc_tree_hash()
+    assert other != here
+    monkeypatch.setattr(build, "EXTRA_FLAGS", {})
+    assert bench.csrc_tree_hash() not in (here, other)
