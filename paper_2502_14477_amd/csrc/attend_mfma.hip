@@ -32,13 +32,12 @@
 // at a 4-key x 16-dim block receive one dimension each, four consecutive keys of it.
 // One barrier per tile; the next two tiles' loads are in flight during the current tile's math, counted by hand.
 //
-// What bounds it: with all compute units busy the clock falls (matrix instructions alone go from 1.00 to 1.30 us per tile and
-// workgroup between one and 256 workgroups, a synthetic loop with the kernel's mix of matrix, vector and LDS instructions on
-// random data from 1.05 to 1.59), so the loop's instructions count more than their order: 1.58 us a tile on 16 workgroups,
-// 2.02 to 2.06 on 256, where working out each tile's segment, base and stride between two tiles took 1.68 and 2.10.  Beside the loop
-// (17 to 19 tiles, 31 to 38 us, for 512 tokens at 128k): 2.7 us from entry to the first tile, 2.6 from the last tile to the
-// stores.  Chunk of 512 at 128k 109.9 -> 108.1 us a step, 1024 at 256k 456 -> 436, 20k prompt 2918 -> 2862, tail of 77 51.9 -> 50.9,
-// head size 64 at 32k 82.6 -> 81.1.
+// What bounds it: with all compute units busy the clock falls, on random operands further than on constant ones (a matrix
+// instruction takes a SIMD 13.4 ns on one workgroup, 13.7 to 15.2 on 256 with constant operands, 18.9 to 20.0 with N(0,1)
+// ones, that is 1.28 us for the 64 of a tile's two waves), so the loop's instructions count more than their order.  Time of a call against
+// its number of tiles, merge included: 1.51 us a tile + 9.5 on 16 workgroups, 1.78 + 22 on 256 (512 tokens, 8 KV heads, 17 to 57
+// tiles a slice; 1.93 for the first of them, 1.63 for the last); head size 64 1.95 + 18.5.  With two stages and a row lookup
+// behind branches, on the same card: 1.64 + 10.5, 1.80 + 25, 2.01 + 20.
 #include "attend_mfma.h"
 #include "keyspace.h"
 
@@ -627,8 +626,8 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
 // The slots in use are [0, ns_a) and [slot_b, slot_b + ns_b) of n_slot.  Sixteen lanes per row (16 bytes of partials
 // each: eight head-dims in fp16, four in fp32), sixteen rows per workgroup.
 // NS: slots in use, a constant: with a run-time number every slot's loads stood behind a branch, which made each a round
-// trip of its own, and vector instructions were issued for sixteen slots whatever their number.  Steps with
-// four slices (16.9 MB of partials for 512 tokens): 128k chunk 105.0 -> 103.75 us, 20k prompt 2885 -> 2848, outputs the same.
+// trip of its own, and vector instructions were issued for sixteen slots whatever their number (1.2 % of a step with
+// four slices, 16.9 MB of partials for 512 tokens).
 template <int D, int NS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NS > 8 ? 4 : 8)))   // registers for all loads
 void esa_attend_merge(const void* __restrict__ part_o, const float* __restrict__ part_ml, int n_slot, int ns_a,

@@ -1024,7 +1024,9 @@ __host__ inline bool stores_scores(int l_c, int64_t n, int batch) {
   return l_c <= kFewQueries || (l_c <= kFinishMaxQueries && (int64_t)l_c * n * batch * 4 <= ((int64_t)16 << 20));
 }
 __host__ inline int64_t stored_ld(int64_t n) { return (n + 63) / 64 * 64; }
-__host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {        // one current token: S is kept where F goes
+// One current token: S is kept where F goes.  (The workspace is asked for without type and d_c: it holds the S of fp32 queries, which
+// bf16 ones with d_c 64 or 128, swept twice, leave unused.)
+__host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {
   return l_c > 1 && stores_scores(l_c, n, batch) ? (size_t)l_c * stored_ld(n) * 4 * batch : 0;
 }
 
