@@ -35,9 +35,11 @@
 // What bounds it: with all compute units busy the clock falls, on random operands further than on constant ones (a matrix
 // instruction takes a SIMD 13.4 ns on one workgroup, 13.7 to 15.2 on 256 with constant operands, 18.9 to 20.0 with N(0,1)
 // ones, that is 1.28 us for the 64 of a tile's two waves), so the loop's instructions count more than their order.  Time of a call against
-// its number of tiles, merge included: 1.51 us a tile + 9.5 on 16 workgroups, 1.78 + 22 on 256 (512 tokens, 8 KV heads, 17 to 57
-// tiles a slice; 1.93 for the first of them, 1.63 for the last); head size 64 1.95 + 18.5.  With two stages and a row lookup
-// behind branches, on the same card: 1.64 + 10.5, 1.80 + 25, 2.01 + 20.
+// its number of tiles, merge included: 1.35 us a tile + 10 on 16 workgroups, 1.74 + 21.5 on 256 (512 tokens, 8 KV heads, 17 to 57
+// tiles a slice); with a maximum taken from every tile and every row's address computed by every lane, 180 vector instructions a
+// tile and wave where 130 stand now, 1.52 + 9.5 and 1.78 + 23 on the same card (1024 tokens with 8192 selected and 8192 local ones: 431 -> 410 us a
+// step).  A tile takes 3250 cycles (2048 of them matrix instructions) at 1.8 GHz.  Steps of half a tile that carry the first product of
+// the next half, the exponentials of their own and the second product of the last take 3050, but the clock falls to 1.7 GHz: the same time.
 #include "attend_mfma.h"
 #include "keyspace.h"
 
@@ -71,7 +73,9 @@ constexpr int kMaxSelSplits = 8;        // two-call form: at most half as many l
 constexpr int kStages = 3;
 constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLazy = 8.f;        // the softmax reference lags the running maximum by at most 2^8
+// A lane's sixteen exponentials of half a tile add up to at most this, or the softmax reference moves to the running maximum: it lags
+// by at most 2^8, harmless in bf16 and fp32, and the accumulators are rescaled once or twice per row instead of per tile.
+constexpr float kMostSum = 256.f;
 constexpr float kNoKey = -FLT_MAX;  // reference of a row that has seen no key: finite, so that differences stay numbers
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   // Three stages of a K tile, then three of a V tile, then room for the query rows, which come in through the last V stage and
   // what is behind it.  Three stages of each wave's copy of a tile's index entries.
   __shared__ __attribute__((aligned(1024))) bf16_t st[(2 * kStages + 3) * kTileElems];
-  __shared__ __attribute__((aligned(1024))) int32_t idx_st[LISTED ? kStages : 1][LISTED ? kWaves : 1][kKT];
+  __shared__ __attribute__((aligned(1024))) int32_t idx_st[2][LISTED ? kWaves : 1][64];
   constexpr int kQPlace = (2 * kStages - 1) * kTileElems * 2;       // byte offset of the query rows
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
@@ -287,75 +291,79 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   auto dma16 = [&](const char* src, uint32_t dst) __attribute__((always_inline)) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
   };
-  // Index-driven selected rows (the gather folded into this kernel): the entries of a tile's selected keys go to LDS a turn
-  // ahead of the tile's keys, lane l's being that of key l.  A list without entries: the cache's first word.
+  // The rows that this lane fetches pieces of, eight tiles at a time: the lanes of a row's group (sixteen of them with two rows each,
+  // or eight with one) hold the offsets of one row of one tile each, and a tile's offsets are broadcast to the group when its turn
+  // comes: 14 vector instructions a tile and wave, where every lane of a group finding every tile's rows took 40 (a chunk of 1024
+  // with 8192 selected and 8192 local tokens: 1.04 of the step's time).
+  // Index-driven selected rows (the gather folded into this kernel): the entries for eight tiles go to LDS eight tiles ahead.  A
+  // list without entries: the cache's first word.
   const bool entries = LISTED && V.n_sel;
   const int32_t* list = entries ? V.sel_idx + (int64_t)b * V.idx_bs : (const int32_t*)kc;
   const uint32_t list_last = entries ? V.n_sel - 1 : 0;
-  auto idx_load = [&](uint32_t t, int stage) __attribute__((always_inline)) {
+  const uint32_t row_of_lane = st_row + kRowStep * (kMyRows == 2 ? lane & 1 : 0);
+  const uint32_t key_of_lane = (tile_begin + (kMyRows == 2 ? (lane & 15) >> 1 : lane & 7)) * kKT + row_of_lane;
+  auto idx_load = [&](uint32_t eight) __attribute__((always_inline)) {
     if constexpr (LISTED) {
-      const int32_t js = (int32_t)(t * kKT + lane - V.i_end);
+      const int32_t js = (int32_t)(eight * (8 * kKT) + key_of_lane - V.i_end);
       const uint32_t at = js < 0 ? 0u : (uint32_t)js < list_last ? (uint32_t)js : list_last;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(idx_lds + stage * (kWaves * kKT * 4)), "v"(list + at) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(idx_lds + (eight & 1) * (kWaves * 256)), "v"(list + at) : "memory", "m0");
     }
   };
 #pragma clang diagnostic pop
-  // The rows of a tile that this lane fetches a piece of.  LISTED: numbers in the cache, without a branch on where in the virtual
-  // sequence the tile lies, as this code stands between two tiles' matrix instructions, where nothing hides it.  Otherwise the keys'
-  // numbers: the tile's segment gives all its rows one base and stride, in scalar registers, but where a boundary crosses it.
-  struct Rows {
-    uint32_t at[kMyRows];
-  };
   const uint32_t past_sel = V.l_start - V.i_end - V.n_sel;                // from a virtual key behind the selected ones to its row
-  auto rows_of = [&](uint32_t t, int stage) __attribute__((always_inline)) {
-    Rows p;
-#pragma unroll
-    for (int u = 0; u < kMyRows; ++u) {
-      uint32_t j = t * kKT + st_row + kRowStep * u;
-      j = j < k_end ? j : k_end - 1;                                      // the tail repeats a key; masked below
-      p.at[u] = j;
-      if constexpr (LISTED) {
-        // a middle token's position, clamped so that a bad index cannot leave the cache
-        const int32_t entry = idx_st[stage][wave][st_row + kRowStep * u], most = (int32_t)V.idx_limit - 1;
-        const uint32_t selected = entry < 0 ? 0 : entry < most ? entry : most;
-        p.at[u] = j - V.i_end < V.n_sel ? selected : j < V.i_end ? j : j + past_sel;
-      }
-    }
-    return p;
-  };
-  // tile t, keys and values
-  auto tile_load = [&](uint32_t t, const Rows& rows, int stage) __attribute__((always_inline)) {
-    const uint32_t k_dst = st_lds + stage * (kTileElems * 2), v_dst = k_dst + kStages * (kTileElems * 2);
-    auto fetch = [&](const char* k_base, uint32_t k_stride, const char* v_base, uint32_t v_stride, uint32_t shift) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(k_base + kcol + (uint64_t)(rows.at[u] + shift) * k_stride, k_dst + kWaves * 1024 * u);
-#pragma unroll
-      for (int u = 0; u < kMyRows; ++u) dma16(v_base + vcol + (uint64_t)(rows.at[u] + shift) * v_stride, v_dst + kWaves * 1024 * u);
-    };
+  int64_t k_row = 0, v_row = 0;       // byte offsets from kc and vc (LISTED: the same)
+  auto find_rows = [&](uint32_t eight) __attribute__((always_inline)) {
+    uint32_t j = eight * (8 * kKT) + key_of_lane;
+    j = j < k_end ? j : k_end - 1;                                        // the tail repeats a key; masked below
     if constexpr (LISTED) {
-      fetch(kc, V.k_bytes, vc, V.v_bytes, 0u);
+      // a middle token's position, clamped so that a bad index cannot leave the cache
+      const int32_t entry = idx_st[eight & 1][wave][lane], most = (int32_t)V.idx_limit - 1;
+      const uint32_t selected = entry < 0 ? 0 : entry < most ? entry : most;
+      const uint32_t row = j - V.i_end < V.n_sel ? selected : j < V.i_end ? j : j + past_sel;
+      k_row = (int64_t)((uint64_t)row * V.k_bytes);
     } else {
-      const uint32_t sel_end = V.i_end + V.n_sel, last = k_end - 1;
-      const uint32_t j_first = t * kKT < last ? t * kKT : last, j_last = t * kKT + kKT - 1 < last ? t * kKT + kKT - 1 : last;
-      auto segment = [&](uint32_t j) { return j < V.i_end ? 0 : j < sel_end ? 1 : 2; };
-      const int seg = segment(j_first);
-      if (seg == segment(j_last)) {
-        const uint32_t shift = seg == 0 ? 0u : seg == 1 ? 0u - V.i_end : past_sel;
-        fetch(seg == 1 ? ksl : kc, seg == 1 ? a.sel_bytes : V.k_bytes, seg == 1 ? vsl : vc, seg == 1 ? a.sel_bytes : V.v_bytes, shift);
-      } else {
-#pragma unroll
-        for (int u = 0; u < 2 * kMyRows; ++u) {
-          const bool values = u >= kMyRows;
-          const uint32_t j = rows.at[u % kMyRows];
-          const int s = segment(j);
-          const uint32_t row = s == 0 ? j : s == 1 ? j - V.i_end : j + past_sel;
-          const char* base = values ? (s == 1 ? vsl : vc) + vcol : (s == 1 ? ksl : kc) + kcol;
-          dma16(base + (uint64_t)row * (s == 1 ? a.sel_bytes : values ? V.v_bytes : V.k_bytes), (values ? v_dst : k_dst) + kWaves * 1024 * (u % kMyRows));
-        }
-      }
+      const bool sel = j - V.i_end < V.n_sel;
+      const uint64_t row = sel ? j - V.i_end : j < V.i_end ? j : j + past_sel;
+      k_row = sel ? (ksl - kc) + (int64_t)(row * a.sel_bytes) : (int64_t)(row * V.k_bytes);
+      v_row = sel ? (vsl - vc) + (int64_t)(row * a.sel_bytes) : (int64_t)(row * V.v_bytes);
     }
   };
-  // ---- one tile: S^T = K Q^T, online softmax, O^T += V^T P^T
+  auto of_lane = [&](int64_t x, auto control) __attribute__((always_inline)) {       // every lane reads another of its sixteen
+    constexpr int kControl = decltype(control)::value;
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, kControl, 0xF, 0xF, true);
+    const uint32_t hi32 = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)x >> 32), kControl, 0xF, 0xF, true);
+    return (int64_t)((uint64_t)hi32 << 32 | lo);
+  };
+  auto of_group = [&](int64_t x, auto first) __attribute__((always_inline)) {        // row `first` of the group's next tile
+    constexpr int kFirst = decltype(first)::value;
+    if constexpr (kMyRows == 2) return of_lane(x, std::integral_constant<int, 0x150 + kFirst>());    // row_newbcast
+    const int64_t low = of_lane(x, std::integral_constant<int, 0x150>()), up = of_lane(x, std::integral_constant<int, 0x158>());
+    return lane & 8 ? up : low;
+  };
+  uint32_t fetched = 0;
+  // the next tile, keys and values
+  auto tile_load = [&](int stage) __attribute__((always_inline)) {
+    const uint32_t k_dst = st_lds + stage * (kTileElems * 2), v_dst = k_dst + kStages * (kTileElems * 2);
+    if ((fetched & 7) == 0) {
+      find_rows(fetched >> 3);
+      idx_load((fetched >> 3) + 1);
+    }
+    ++fetched;
+    const int64_t k0 = of_group(k_row, std::integral_constant<int, 0>()), v0 = LISTED ? k0 : of_group(v_row, std::integral_constant<int, 0>());
+    if constexpr (kMyRows == 2) {
+      const int64_t k1 = of_group(k_row, std::integral_constant<int, 1>()), v1 = LISTED ? k1 : of_group(v_row, std::integral_constant<int, 1>());
+      dma16(kc + kcol + k0, k_dst);
+      dma16(kc + kcol + k1, k_dst + kWaves * 1024);
+      dma16(vc + vcol + v0, v_dst);
+      dma16(vc + vcol + v1, v_dst + kWaves * 1024);
+    } else {
+      dma16(kc + kcol + k0, k_dst);
+      dma16(vc + vcol + v0, v_dst);
+    }
+    k_row = of_lane(k_row, std::integral_constant<int, 0x100 + kMyRows>());         // row_shl: the tile after it comes to the front
+    if constexpr (!LISTED) v_row = of_lane(v_row, std::integral_constant<int, 0x100 + kMyRows>());
+  };
+  // ---- one tile: S^T = K Q^T, online softmax, O^T += V^T P^T, the probabilities in fp32 (head size 64)
   auto tile_math = [&](uint32_t t, int stage) __attribute__((always_inline)) {
     const uint32_t j0 = t * kKT;
     if (j0 >= lim_hi) return;           // no row of this wave sees any of the tile's keys
@@ -416,12 +424,10 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[mt][v]);
-    // The reference m_run of the exponentials follows the running maximum lazily: it moves only when
-    // a tile's maximum exceeds it by more than 2^kLazy, so probabilities stay below 2^kLazy (harmless
-    // in bf16 and fp32) and the accumulators are rescaled once or twice per row instead of per tile.  (Head size 64
-    // follows it at once: the sum stays small, and its logarithm as exact as the normaliser can hold.)
+    // The reference m_run of the exponentials follows the running maximum at once: the sum stays small, and its logarithm
+    // as exact as the normaliser can hold.
     const float cand = halves_max(mx) * a.c2, m_old = m_run;
-    const bool moved = cand > m_run + (kFp32Probs<D> ? 0.f : kLazy);
+    const bool moved = cand > m_run;
     m_run = moved ? cand : m_run;
     float corr = 1.f;
     if (__ballot(moved) != 0ull) {
@@ -485,11 +491,127 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
     l_run = __builtin_fmaf(l_run, corr, psum);          // rounded once
   };
 
-  // Turn t: tile t, requested two turns before (a turn takes 2 us, a tile that comes from HBM sometimes longer).  Its own requests
-  // are tile t + 2 and the index entries of tile t + 3; tile n is in stage (n - tile_begin) % 3.  At its barrier every wave is
-  // done with the stage that these overwrite.
+  // ---- the same with probabilities in one bf16 term (head size 128), in two halves of 32 keys, so that the exponentials of one half
+  // stand beside the matrix instructions of the other.  No maximum is looked for: the exponentials are taken against the
+  // reference as it is, and where a lane's sum over a half exceeds kMostSum (infinite where the row has no reference yet) the half is
+  // done again against its maximum, with what has been summed so far rescaled.  (The 27 instructions of the maximum stood between
+  // the products, where nothing hid them: 1.53 -> 1.48 us a tile on 16 workgroups.)
+  auto half_tiles = [&](uint32_t t, int stage, auto&& loads) __attribute__((always_inline)) {
+    const uint32_t j0 = t * kKT;
+    const char* kt = (const char*)st + stage * kKT * D * 2;
+    bf16x8 kf[2][kKS];
+    auto request_keys = [&](int mt, int ks16) __attribute__((always_inline)) {
+      kf[mt][ks16] = *(const bf16x8*)(kt + k_at[ks16] + 32 * mt * D * 2);
+    };
 #pragma unroll
-  for (int i = 0; i < kStages; ++i) idx_load(tile_begin + i, i);
+    for (int ks16 = 0; ks16 < kKS; ++ks16) request_keys(0, ks16);
+    __builtin_amdgcn_sched_barrier(0);
+    loads();
+    if (j0 >= lim_hi) return;           // no row of this wave sees any of the tile's keys
+    f32x16 s[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s[mt][v] = 0.f;
+    bf16x8 vf[4][kMD];
+    auto request_values = [&](int kp, int md) __attribute__((always_inline)) {
+      const char* vp = (const char*)st + v_at[md] + (stage * kKT + 16 * kp) * D * 2;
+      const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);
+      const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 8 * D * 2));
+      vf[kp][md] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto mask = [&](int mt) __attribute__((always_inline)) {
+      if (j0 + 32 * mt + 32 > lim_lo) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (j0 + 32 * mt + 8 * (v / 4) + 4 * hi + (v % 4) >= lim) s[mt][v] = -INFINITY;
+      }
+    };
+    float psum[2] = {0.f, 0.f};
+    uint32_t pf[4][4];
+    float p[2][16];
+    auto piece = [&](int mt, int at) __attribute__((always_inline)) {    // at: 0 .. 15
+      const int kp = at / 8, a8 = at % 8;
+      const bool exps = a8 == 0 || a8 == 1 || a8 == 3 || a8 == 5;
+      const int e = a8 < 2 ? a8 : a8 == 7 ? 3 : a8 / 2 + (exps ? 1 : -1);
+      const int v = kp * 8 + 2 * e;
+      if (exps) {
+        p[mt][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mt][v], a.c2, -m_run));
+        p[mt][v + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mt][v + 1], a.c2, -m_run));
+      } else {
+        psum[mt] += p[mt][v];
+        psum[mt] += p[mt][v + 1];
+        pf[2 * mt + kp][e] = pack_bf16x2(p[mt][v], p[mt][v + 1]);
+      }
+    };
+    // (A sum that is no number does not exceed it: the row's output is none either way.)
+    auto settle = [&](int mt) __attribute__((always_inline)) {
+      if (__builtin_expect(__ballot(psum[mt] > kMostSum) != 0ull, 0)) {
+        float mx = s[mt][0];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[mt][v]);
+        const float m_old = m_run;
+        m_run = fmaxf(m_run, halves_max(mx) * a.c2);
+        const float corr = __builtin_amdgcn_exp2f(m_old - m_run);
+#pragma unroll
+        for (int md = 0; md < kMD; ++md)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[md][v] *= corr;
+        l_run *= corr;
+        if (mt) psum[0] *= corr;
+        psum[mt] = 0.f;
+#pragma unroll
+        for (int at = 0; at < 16; ++at) piece(mt, at);
+      }
+    };
+    auto second = [&](int kp, int md) __attribute__((always_inline)) {
+      const uint4 w = make_uint4(pf[kp][0], pf[kp][1], pf[kp][2], pf[kp][3]);
+      o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kp][md], *(const bf16x8*)&w, o[md], 0, 0, 0);
+    };
+    // (The order is pinned: left to itself the scheduler puts the fragment reads next to their use.)
+    // keys 0 ... 31: first product
+#pragma unroll
+    for (int i = 0; i < kKS; ++i) {
+      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][i], qf[i], s[0], 0, 0, 0);
+      request_keys(1, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    mask(0);
+    // keys 32 ... 63; beside it the exponentials of the first half
+#pragma unroll
+    for (int i = 0; i < kKS; ++i) {
+      s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][i], qf[i], s[1], 0, 0, 0);
+      request_values(i / kMD, i % kMD);
+#pragma unroll
+      for (int at = 0; at < 16; ++at)
+        if (1 + at * (kKS - 1) / 16 == i) piece(0, at);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    settle(0);
+    mask(1);
+    // second product of the first half; beside it the exponentials of the second
+#pragma unroll
+    for (int i = 0; i < 2 * kMD; ++i) {
+      second(i / kMD, i % kMD);
+      request_values(2 + i / kMD, i % kMD);
+#pragma unroll
+      for (int at = 0; at < 16; ++at)
+        if (1 + at * (2 * kMD - 1) / 16 == i) piece(1, at);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    settle(1);
+#pragma unroll
+    for (int i = 0; i < 2 * kMD; ++i) {
+      second(2 + i / kMD, i % kMD);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    l_run += psum[0] + psum[1];         // rounded once
+  };
+
+  // Turn t: tile t, requested two turns before (a turn takes 2 us, a tile that comes from HBM sometimes longer).  Its own requests
+  // are tile t + 2 and, every eighth turn, index entries; tile n is in stage (n - tile_begin) % 3.  At its barrier every wave is
+  // done with the stage that these overwrite.
+  idx_load(0);
   // The wave's 32 query rows, through LDS like a K tile: whole rows, four or eight to an instruction.  (Fetched as
   // fragments, 16 bytes of 32 rows to an instruction, they were 32 cache lines each.)
   constexpr int kQLoads = 32 / kLoadRows;
@@ -503,11 +625,8 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
     dma16(V.q + (at + ((lane_now % kPieces) ^ k_swizzle<D>(qr)) * 8) * 2, st_lds - wave * 1024 + kQPlace + wave * (32 * D * 2) + 1024 * i);
   }
   if constexpr (LISTED) loads_landed(std::integral_constant<int, kQLoads>());
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const Rows rows = rows_of(tile_begin + i, i);
-    tile_load(tile_begin + i, rows, i);
-  }
+  tile_load(0);
+  tile_load(1);
   loads_landed(std::integral_constant<int, 4 * kMyRows>());
 #pragma unroll
   for (int ks16 = 0; ks16 < kKS; ++ks16) qf[ks16] = *(const bf16x8*)((const char*)st + kQPlace + wave * (32 * D * 2) + k_at[ks16]);
@@ -516,12 +635,15 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   for (int ks16 = 0; ks16 < kKS; ++ks16) asm volatile("" : "+v"(qf[ks16]));
   auto turn = [&](uint32_t t, int s0, int s2) __attribute__((always_inline)) {        // stages of tiles t and t + 2
     loads_landed(std::integral_constant<int, 2 * kMyRows>());
-    const Rows rows = rows_of(t + 2, s2);
     all_waves();
-    idx_load(t + 3, s0);
-    tile_load(t + 2, rows, s2);
-    pin_offsets();
-    tile_math(t, s0);
+    if constexpr (kFp32Probs<D>) {
+      tile_load(s2);
+      pin_offsets();
+      tile_math(t, s0);
+    } else {
+      pin_offsets();
+      half_tiles(t, s0, [&]() __attribute__((always_inline)) { tile_load(s2); });
+    }
   };
   for (uint32_t t = tile_begin; t < tile_end; t += 3) {
     turn(t, 0, 2);

@@ -267,6 +267,34 @@ def test_reencoded_attention_over_slices_of_both_parts(esa, B, H, H_kv, d, t0, l
         assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
 
 
+# The softmax reference moves (head size 128: when half a tile's exponentials add up to too much): `rises` are virtual keys from which
+# on all logits are larger by 10.  In either half of the first tile, of a later one, of the last that every row sees, of the causal
+# one; several in a row; a first half far below the rest; slices of nine to twenty tiles, whose rows are found eight tiles at a time.
+@pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel,rises", [
+    (1, 8, 8, 128, 400, 16, 64, 128, 90, (5,)), (1, 8, 8, 128, 400, 16, 64, 128, 90, (40, 70, 100, 130, 161)), (2, 8, 2, 128, 500, 40, 10, 300, 64, (32, 64, 352)),
+    (1, 8, 2, 128, 500, 70, 10, 300, 64, (374, 400, 410)), (1, 32, 8, 128, 300, 65, 10, 200, 64, (276, 300, 338)), (1, 8, 2, 64, 500, 70, 10, 300, 64, (40, 374, 400)),
+    (4, 8, 8, 128, 9000, 16, 100, 2000, 3000, (2000,)), (1, 64, 64, 128, 9000, 17, 100, 2000, 3001, ()), (4, 8, 8, 64, 9000, 16, 100, 2000, 3000, (30,))])
+def test_attention_where_the_reference_moves_and_over_long_slices(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel, rises):
+    say(f"attend, moving reference B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel} rises={rises}")
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    i_end, l_start = segment_bounds(t0, l_I, l_L)
+    q[..., 0] = 8.0
+    for b in range(B):
+        rows = np.concatenate([np.arange(i_end), sel[b], np.arange(l_start, t0 + l_C)])       # the virtual keys' rows
+        level = sum((np.arange(rows.size) >= r).astype(float) for r in rises) if rises else np.zeros(rows.size)
+        K[b, rows, :, 0] = orc.round_to_storage(10.0 * np.sqrt(d) / 8.0 * level, "bf16")[:, None]
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16"), torch.from_numpy(sel).cuda()
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx)
+    O, lse = esa.esa_attend(qd, Kd, Vd, t0, l_I, l_L, ks, vs, return_lse=True)
+    O_idx, lse_idx = esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx, return_lse=True)
+    assert torch.equal(O, O_idx) and torch.equal(lse, lse_idx)
+    for b in range(B):
+        want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        # an output is a mean of bf16 values near 1 with weights in 8 bits: half a place of either, with the largest value 4
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3, b
+
+
 # Gathered rows: segment boundaries at a tile's edge, one key beside it, two of them inside one tile, no boundary but the sequence's
 # end; slices that end between.  The index-driven form takes the same keys in the same order.
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
