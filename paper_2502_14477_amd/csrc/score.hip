@@ -140,14 +140,19 @@ constexpr int kQPerWave = 32 * kMT;
 constexpr int kQPerBlock = kWaves * kQPerWave;
 constexpr int kMaxTilesPerBlock = 16;    // 512 tokens: 128 KB of LDS (d_c = 128); one load instruction per thread and 8 KB
 
-__host__ __device__ inline int64_t mfma_tiles_per_block(int64_t n) {
-  const int64_t n_tiles = (n + 31) / 32;
-  const int64_t per = ((n_tiles + 255) / 256 + 1) / 2 * 2;   // about one workgroup per compute unit; even
+// eps > 0: the second sweep pools over +-eps (Eq. 8, at most kTailMaxEps).  Shares then lap over their neighbours' by eps tokens
+// on either side, so that a workgroup has the scores of every window it writes; the first sweep's are the same ones, because a share
+// that the same L2 has seen is read in half the time (the second sweep took 21.1 us instead of 18.5 over other shares, 126 thousand
+// tokens).  With a pooling kernel of its own, which read the scores back and built the selection's histogram (4.9 us), a re-encoded step
+// took 63.3 us instead of 61.0 (40 tokens at 50 thousand), 80.1 / 77.0 (128 at 100), 62.4 / 59.9 (60 at 12), 77.6 / 75.8 (256 at 30) and,
+// bound by power, the same 134 (512 at 130).
+__host__ __device__ inline int64_t mfma_tiles_per_block(int64_t n, int eps) {
+  const int64_t per = ((n + 255) / 256 + 2 * eps + 63) / 64 * 2;   // about one workgroup per compute unit; even
   return per < 2 ? 2 : (per > kMaxTilesPerBlock ? kMaxTilesPerBlock : per);
 }
-__host__ __device__ inline int64_t mfma_blocks(int64_t n) {
-  const int64_t per = mfma_tiles_per_block(n);
-  return ((n + 31) / 32 + per - 1) / per;
+__host__ __device__ inline int64_t mfma_blocks(int64_t n, int eps) {
+  const int64_t own = 32 * mfma_tiles_per_block(n, eps) - 2 * eps;
+  return (n + own - 1) / own;
 }
 // K' share, column maxima, digit histogram
 __host__ __device__ inline size_t mfma_lds_bytes(int64_t per, int d_c) {
@@ -189,7 +194,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
                                                             float* __restrict__ score, int64_t q_bs, int64_t kc_bs,
                                                             int64_t score_bs, int tiles_per_block,
                                                             uint32_t* __restrict__ first_hist, int64_t first_hist_bs,
-                                                            bf16_t* __restrict__ qfrag, int64_t qfrag_bs, int n_wg) {
+                                                            bf16_t* __restrict__ qfrag, int64_t qfrag_bs, int n_wg, int eps) {
   static_assert(DC == 64 || DC == 128, "swizzle and load pattern");
   constexpr int kDc = DC;
   constexpr int kKSteps = kDc / 16;        // MFMA reduction steps per tile
@@ -209,8 +214,9 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   const int tid = __builtin_amdgcn_workitem_id_x(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // uniform: lives in a scalar register
   const int r = lane & 31, hi = lane >> 5;
-  const int64_t tok_base = (int64_t)__builtin_amdgcn_workgroup_id_x() * span;
+  const int64_t tok_base = (int64_t)__builtin_amdgcn_workgroup_id_x() * (span - 2 * eps) - eps;
   const char* kshare = (const char*)(kc + (int64_t)b * kc_bs + (m_lo + tok_base) * (int64_t)kDc);
+  const uint32_t first_row = tok_base < 0 ? (uint32_t)-tok_base : 0u;   // rows outside the middle segment repeat its first or last token
   const uint32_t last_row = (uint32_t)(n - tok_base - 1 < span - 1 ? n - tok_base - 1 : span - 1);
   const uint32_t lds_tiles = (uint32_t)(uintptr_t)(lds_byte*)lds_raw;  // LDS byte address of the share
   const uint32_t lds_colmax = lds_tiles + (uint32_t)tpb * kTileBytes;
@@ -449,7 +455,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   // ---- requests, in the order their results are needed (loads complete in order): query fragments and row
   // maxima, then the K' share.  Instruction i of wave w fills row group 8*i + w (four or eight rows, 1 KB of
   // LDS); a lane fetches, for its slot of its row of the group, the piece that undoes the swizzle.
-  // Rows past the end of the middle segment repeat its last token (no maximum changes, nothing of theirs
+  // Rows past an end of the middle segment repeat its last (first) token (no maximum changes, nothing of theirs
   // is stored); shares shorter than sixteen tiles repeat their last instruction, identical data to an
   // identical place, so that the count of outstanding loads means the same in every workgroup.
   if (PASS == 1) {
@@ -466,6 +472,7 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
       const int t = i < n_loads ? i : n_loads - 1;
       uint32_t row = 32 * kTilesPerLoad * t + row_in_load;
       row = row < last_row ? row : last_row;
+      row = row > first_row ? row : first_row;
       __builtin_amdgcn_global_load_lds((global_void*)(kshare + (size_t)row * (kDc * sizeof(bf16_t)) + piece * 16),
                                        (lds_void*)(lds_raw + (size_t)(8 * t + wave) * 1024), 16, 0, 0);
     }
@@ -569,8 +576,14 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     for (int i0 = 0; i0 < span; i0 += kThreads) {          // whole waves stay in step for hist_add
       const int i = i0 + tid;
       const int64_t m = tok_base + i;
-      const bool ok = i < span && m < n;
-      const uint32_t key = ok ? colmax[32 + i] : 0u;
+      const bool ok = i >= eps && i < span - eps && m < n;
+      uint32_t key = ok ? colmax[32 + i] : 0u;
+      if (ok)                              // (a repeated token only meets windows that hold it)
+        for (int d = 1; d <= eps; ++d) {
+          const uint32_t left = colmax[32 + i - d], right = colmax[32 + i + d];
+          key = key > left ? key : left;
+          key = key > right ? key : right;
+        }
       if (ok) score[(int64_t)b * score_bs + m] = ordered_key_to_f32(key);
       if (first_hist) hist_add(digit_hist, ok, score_digit(key));
     }
@@ -1030,8 +1043,8 @@ __host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {
   return l_c > 1 && stores_scores(l_c, n, batch) ? (size_t)l_c * stored_ld(n) * 4 * batch : 0;
 }
 
-__host__ inline size_t part_bytes(int l_c, int64_t n_mid, int batch) {
-  size_t blocks = (size_t)mfma_blocks(n_mid) * l_c;
+__host__ inline size_t part_bytes(int l_c, int64_t n_mid, int eps, int batch) {
+  size_t blocks = (size_t)mfma_blocks(n_mid, eps <= kTailMaxEps ? eps : 0) * l_c;
   if (stores_scores(l_c, n_mid, batch)) {   // a partial maximum per query and workgroup of at least 64 tokens
     const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c;
     blocks = stored > blocks ? stored : blocks;
@@ -1048,8 +1061,8 @@ __host__ inline size_t qfrag_bytes_per_batch(int l_c) {
 template <int DC>
 int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int64_t n, float* part, float* mu, float* score,
                   int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, uint32_t* hists, bool fill_first, int64_t hists_bs,
-                  bf16_t* qfrag, int64_t qfrag_bs, hipStream_t st) {
-  const int per = (int)mfma_tiles_per_block(n), nblk = (int)mfma_blocks(n);
+                  bf16_t* qfrag, int64_t qfrag_bs, int eps, hipStream_t st) {
+  const int per = (int)mfma_tiles_per_block(n, eps), nblk = (int)mfma_blocks(n, eps);
   const dim3 grid(nblk, batch);
   const size_t lds = mfma_lds_bytes(per, DC), most = mfma_lds_bytes(kMaxTilesPerBlock, DC);
   const size_t most0 = mfma_sweep0_lds_bytes(DC == 64 ? kMaxTilesPerBlock : 4, DC, kQPerBlock);          // 128 and 160 KB
@@ -1059,16 +1072,16 @@ int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int
                                  most > most0 ? most : most0, "score_mfma_bf16");
   if (rc != ESA_OK) return rc;
   score_mfma_bf16<0, DC><<<grid, kThreads, mfma_sweep0_lds_bytes(per, DC, l_c), st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per, nullptr,
-                                                      0, qfrag, qfrag_bs, nblk);
+                                                      0, qfrag, qfrag_bs, nblk, eps);
   score_rowmax_reduce<<<dim3((l_c + 3) / 4, batch), 256, 0, st>>>(part, nblk, l_c, mu, mfma_mu_stride(l_c), hists, hists_bs);
   score_mfma_bf16<1, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per,
-                                                      fill_first ? hists : nullptr, hists_bs, qfrag, qfrag_bs, nblk);
+                                                      fill_first ? hists : nullptr, hists_bs, qfrag, qfrag_bs, nblk, eps);
   return ESA_OK;
 }
 
 size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
   if (l_c <= 0 || batch <= 0 || n_mid < 0) return 256;
-  size_t b = mu_bytes(l_c, batch) + part_bytes(l_c, n_mid, batch);
+  size_t b = mu_bytes(l_c, batch) + part_bytes(l_c, n_mid, eps, batch);
   if (eps > 0) b += align_up((size_t)n_mid * 4, 256) * (size_t)batch;
   b += qfrag_bytes_per_batch(l_c) * (size_t)batch;
   b += stored_bytes(l_c, n_mid, batch);
@@ -1080,13 +1093,13 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                  size_t ws_bytes, hipStream_t st, uint32_t* first_hist, int64_t first_hist_bs, bool* first_hist_done,
                  ScoreTail* tail) {
   const int64_t n = m_hi - m_lo;
-  // eps > 0: windows of up to kTailMaxEps on either side are pooled by whatever finishes the scores (score_finish, or
-  // the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
+  // eps > 0: windows of up to kTailMaxEps on either side are pooled by whatever finishes the scores (score_finish, the second
+  // sweep, or the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
   const bool narrow = eps <= kTailMaxEps;
   bool zeroed = false;                  // the selection's histograms have been zeroed ...
   if (first_hist_done) *first_hist_done = false;        // ... and the first one filled
   float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
-  char* at = (char*)part + part_bytes(l_c, n, batch);
+  char* at = (char*)part + part_bytes(l_c, n, eps, batch);
   float* raw = score;
   int64_t raw_bs = score_bs;
   if (eps > 0) {
@@ -1141,15 +1154,12 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
   } else if (vec_ok && (d_c == 128 || d_c == 64)) {
     const int64_t qfrag_bs = (int64_t)(qfrag_bytes_per_batch(l_c) / sizeof(bf16_t));
     const auto sweeps = d_c == 128 ? launch_sweeps<128> : launch_sweeps<64>;
-    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, raw, batch, q_bs, kc_bs,
-                          raw_bs, first_hist, eps == 0, first_hist_bs, qfrag, qfrag_bs, st);
+    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, narrow ? score : raw, batch, q_bs,
+                          kc_bs, narrow ? score_bs : raw_bs, first_hist, narrow, first_hist_bs, qfrag, qfrag_bs, narrow ? eps : 0, st);
     if (rc != ESA_OK) return rc;
     zeroed = first_hist != nullptr;
-    if (first_hist && eps == 0 && first_hist_done) *first_hist_done = true;
-    if (tail && narrow && eps > 0) {
-      *tail = ScoreTail{raw, raw_bs, nullptr, 0, eps};
-      pool_left = false;
-    }
+    if (first_hist && narrow && first_hist_done) *first_hist_done = true;
+    if (narrow) pool_left = false;
   } else if (stores_scores(l_c, n, batch)) {
     const int nblk = (int)((n + kGTok - 1) / kGTok);
     const dim3 grid((unsigned)nblk, (unsigned)((l_c + kStoreQ - 1) / kStoreQ), batch);

@@ -153,6 +153,28 @@ def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
         assert got[b].max() == 0.0
 
 
+# Pooling by the second sweep: one workgroup's tokens, one more, one less; a single token; the widest window it takes in the shortest
+# share and in long ones, the narrowest, one that keeps its own pass; windows across every workgroup's edge hold the row's largest scores
+@pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 17, 1, 128, 1), (2, 40, 62, 128, 1), (1, 40, 63, 128, 1), (1, 20, 61, 64, 1), (1, 33, 32, 64, 16),
+                                             (1, 33, 4097, 64, 16), (1, 600, 33000, 128, 16), (1, 70, 131077, 128, 2), (3, 40, 9000, 128, 3),
+                                             (1, 33, 500, 128, 17)])
+def test_pooling_in_the_second_sweep(esa, B, l_c, n, d_c, eps):
+    say(f"score B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
+    rng = np.random.default_rng(n + l_c)
+    qc = orc.round_to_storage(rng.standard_normal((B, l_c, d_c)) * 1.5, "bf16")
+    kc = orc.round_to_storage(rng.standard_normal((B, n + 8, d_c)), "bf16")
+    qd, kd, k = f64_to_dev(qc, "bf16"), f64_to_dev(kc, "bf16"), max(n // 3, 1)
+    score = esa.esa_score(qd, kd, 3, n + 3, eps=eps)
+    fused, idx, _, _ = esa.esa_score_select_gather(qd, kd, 3, n + 3, k, eps=eps)
+    assert n <= k or torch.equal(fused, score)
+    assert torch.equal(idx, esa.esa_select_topk(score, k, base=3))
+    raw = to_f64(esa.esa_score(qd, kd, 3, n + 3))
+    for b in range(B):
+        want = orc.proximity(orc.importance(qc[b], kc[b, 3:n + 3]), eps)
+        assert np.max(np.abs(to_f64(score[b]) - want)) <= F_TOL["bf16"]
+        assert np.array_equal(to_f64(score[b]), orc.proximity(raw[b], eps))         # the same scores, pooled
+
+
 def _bin_crowd(rng, n, crowd, kind):
     """Scores of which `crowd` lie so close below -1 that they share a bin of a short row's histogram and the first digits of a long row's."""
     s = (-2.0 - rng.random(n) * 60.0).astype(np.float32)
