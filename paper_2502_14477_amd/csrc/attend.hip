@@ -259,12 +259,18 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
   return ESA_OK;
 }
 
+// The re-encoded copies of the local keys and values, or the table that stands for them.
+static size_t local_bytes(size_t kv_bytes, int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t n_loc) {
+  const size_t table = h % h_kv == 0 && attend_split_turns_keys(l_c, h, h_kv, d, dtype, batch) ? align_up(rope_turns_bytes(n_loc + l_c, d), 256) : 0;
+  return table > 2 * kv_bytes ? table : 2 * kv_bytes;
+}
+
 size_t attend_reencoded_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t l_l) {
   if (l_c <= 0 || h <= 0 || h_kv <= 0 || d <= 0 || batch <= 0 || l_l < 0) return 256;
   const size_t esz = (dtype == ESA_F32) ? 4 : 2;
   const size_t q_bytes = align_up((size_t)batch * l_c * h * d * esz, 256);
   const size_t kv_bytes = align_up((size_t)batch * (size_t)(l_l + l_c) * h_kv * d * esz, 256);
-  return align_up(attend_workspace_bytes(l_c, h, h_kv, d, dtype, batch), 256) + 2 * q_bytes + 2 * kv_bytes;
+  return align_up(attend_workspace_bytes(l_c, h, h_kv, d, dtype, batch), 256) + 2 * q_bytes + local_bytes(kv_bytes, l_c, h, h_kv, d, dtype, batch, l_l);
 }
 
 // Section 3.2 on un-encoded queries and keys.  The workspace holds, behind the attention workspace
@@ -285,8 +291,8 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   const size_t own = align_up(attend_workspace_bytes(l_c, h, h_kv, d, dtype, batch), 256);
   const size_t q_bytes = align_up((size_t)batch * l_c * h * d * esz, 256);
   const size_t kv_bytes = align_up((size_t)batch * (size_t)rows * h_kv * d * esz, 256);
-  if (!ws || ws_bytes < own + 2 * q_bytes + 2 * kv_bytes)
-    ESA_FAIL(ESA_EWORKSPACE, "esa_attend_reencoded: workspace needs %zu bytes", own + 2 * q_bytes + 2 * kv_bytes);
+  const size_t need = own + 2 * q_bytes + local_bytes(kv_bytes, l_c, h, h_kv, d, dtype, batch, n_loc);
+  if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend_reencoded: workspace needs %zu bytes", need);
   char* q_loc = (char*)ws + own;
   char* q_glob = q_loc + q_bytes;
   char* k_loc = q_glob + q_bytes;
@@ -309,15 +315,20 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   jobs[2] = RopeJob{k_rows, k_loc, rows, tok_stride, kv_row, cache_bs, kvw_bs, 0.0, 1.0, h_kv, 1};   // local keys from 0
   jobs[3] = RopeJob{v_rows, v_loc, rows, tok_stride, kv_row, cache_bs, kvw_bs, 0.0, 0.0, h_kv, 0};   // their values
   const bool tiled = mfma || split;
+  // A few tokens: the attention kernel turns the local keys itself, by a table.
+  const bool turned = split && attend_split_turns_keys(l_c, h, h_kv, d, dtype, batch);
+  if (turned) jobs[2] = RopeJob{nullptr, k_loc, 32 + (rows + 31) / 32, 0, 0, 0, 0, 0.0, 0.0, 1, kRopeTurns};
   int rc = launch_rope_jobs(jobs, tiled ? 3 : 4, d, base, dtype, batch, st);
   if (rc != ESA_OK) return rc;
-  const CacheRef local = {k_loc, v_rows, kv_row, tok_stride, kvw_bs, cache_bs};
+  const CacheRef local = turned ? CacheRef{k_rows, v_rows, tok_stride, tok_stride, cache_bs, cache_bs}
+                                : CacheRef{k_loc, v_rows, kv_row, tok_stride, kvw_bs, cache_bs};
   const CacheRef cache = {k_cache, v_cache, tok_stride, tok_stride, cache_bs, cache_bs};
   if (mfma)
     return launch_attend_mfma_two_views(q_loc, q_glob, qw_bs, l_c, h, h_kv, d, local, n_loc, cache, sg.i_end, k_sel, v_sel, n_sel,
                                         sel_bs, scale, out, lse, batch, out_bs, ws, own, st);
   if (split) {
-    const SplitCall call = {l_c, h, h_kv, d, dtype, batch, scale, k_sel, v_sel, sel_bs, out, out_bs, lse, ws, own};
+    SplitCall call = {l_c, h, h_kv, d, dtype, batch, scale, k_sel, v_sel, sel_bs, out, out_bs, lse, ws, own};
+    call.turns = turned ? k_loc : nullptr;
     const KeyView a = make_view(q_loc, qw_bs, local, (int64_t)esz, 0, 0, 0, n_loc, 1, 0, 0);
     const KeyView b = make_view(q_glob, qw_bs, cache, (int64_t)esz, sg.i_end, n_sel, 0, sg.i_end + n_sel, 0, 0, 0);
     return launch_attend_split(call, a, &b, st);

@@ -78,6 +78,7 @@ struct SplitArgs {
   PairGrid grid;
   float scale;                        // includes log2(e) for bf16
   int64_t out_bs, sel_bs_bytes;
+  const float* turns;                 // TURNED
 };
 
 // Wait until at most N vector-memory operations are outstanding (the other counters are left alone).  The builtin, not
@@ -111,8 +112,32 @@ template <int N, typename X> __device__ __forceinline__ void arrived4(X& a, X& b
   asm volatile("s_waitcnt lgkmcnt(%c4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
 
-template <typename T, int D>
+// Two pairs (of `a` and `b`, two bf16 numbers each) turned by the sum of two angles: cosine and sine of either pair in x and in y.
+__device__ __forceinline__ void turn_pairs(uint32_t& a, uint32_t& b, const f32x4 x, const f32x4 y) {
+  float ra[2], rb[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const float c = __builtin_fmaf(x[2 * e], y[2 * e], -(x[2 * e + 1] * y[2 * e + 1]));
+    const float s = __builtin_fmaf(x[2 * e + 1], y[2 * e], x[2 * e] * y[2 * e + 1]);
+    const float av = __uint_as_float(e ? a & 0xFFFF0000u : a << 16), bv = __uint_as_float(e ? b & 0xFFFF0000u : b << 16);
+    ra[e] = __builtin_fmaf(av, c, -(bv * s));
+    rb[e] = __builtin_fmaf(bv, c, av * s);
+  }
+  a = pack_bf16x2(ra[0], ra[1]);
+  b = pack_bf16x2(rb[0], rb[1]);
+}
+
+// TURNED: the first view's keys are un-encoded; key j of it is turned by j positions in registers, between its fragments' arrival
+// and the first product, and rounded to bf16 as an encoded row is.  A key and its half's partner are in one lane (fragments ks and
+// ks + kKS / 2), whose turn by the key's number in its tile stays in registers, and the tile's own turn comes with the tile.
+// The queries' fragments, which have no registers left, are read from LDS for every tile.
+// (A re-encoded copy of the local keys is a read, a write and another read of them, 67 MB more for eight sequences behind a window of
+// 2048.  Step, us, copied and turned here: that one at 64 thousand tokens 121.1 / 107.2, one sequence 45.4 / 43.5, eight of eight KV
+// heads at 30 thousand 85 / 73, four of five drafted tokens 75 / 70.  Distance from the 64-bit result, six shapes of six seeds: 2.8103 /
+// 2.8102e-3.)
+template <typename T, int D, bool TURNED = false>
 __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void attend_split(SplitArgs a) {
+  static_assert(!TURNED || sizeof(T) == 2, "the table's order");
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int kRowBytes = D * (int)sizeof(T);
   constexpr int kPieces = kRowBytes / 16;          // 16-byte pieces of a row
@@ -124,6 +149,9 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   __shared__ __attribute__((aligned(1024))) unsigned char k_st[kWaves][kTileBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char v_st[kWaves][kTileBytes];
   __shared__ float ml[kWaves][kRows][2];
+  constexpr int kTurnBytes = D / 2 * 8;            // a tile's turns
+  __shared__ __attribute__((aligned(1024))) unsigned char turn_st[TURNED ? kWaves : 1][TURNED ? 1024 : 1];     // (repeated up to 1 KB)
+  __shared__ __attribute__((aligned(1024))) unsigned char q_st[TURNED ? kTileBytes : 1];                      // laid out as a tile of keys
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -136,10 +164,10 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   const int split = slice - (second ? a.view[0].n_split : 0);
   const char* kc = V.k_cache + (int64_t)b * V.k_bs_bytes + (int64_t)g * kRowBytes;
   const char* vc = V.v_cache + (int64_t)b * V.v_bs_bytes + (int64_t)g * kRowBytes;
-  const bool gathered = V.n_sel && !V.sel_idx;
+  const bool gathered = V.n_sel && (TURNED || !V.sel_idx);      // (Section 3.2's selected rows are always gathered ones)
   const char* ksl = a.k_sel + (gathered ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * kRowBytes : 0);
   const char* vsl = a.v_sel + (gathered ? (int64_t)b * a.sel_bs_bytes + (int64_t)g * kRowBytes : 0);
-  const int32_t* sidx = V.sel_idx ? V.sel_idx + (int64_t)b * V.idx_bs : nullptr;
+  const int32_t* sidx = !TURNED && V.sel_idx ? V.sel_idx + (int64_t)b * V.idx_bs : nullptr;
 
   // ---- rows: one per lane (both half-waves)
   const int n_rows = a.l_c * a.group;
@@ -182,9 +210,16 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   };
   // The places of the rows this lane fetches a piece of, from the lanes that stand for their keys.
   auto spread = [&](int32_t place, int32_t (&mine)[kLoads]) {
+    int from = (int)st_row;
+    if constexpr (TURNED) asm volatile("" : "+v"(from));                    // (the lanes' numbers would be kept, and others spilled)
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) mine[i] = __shfl(place, kLoadRows * i + (int)st_row, 64);
+    for (int i = 0; i < kLoads; ++i) mine[i] = __shfl(place, kLoadRows * i + from, 64);
     __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_turn = [&](uint32_t tile) {            // one instruction; the second view's tiles have none of their own and take the first
+    if constexpr (TURNED)
+      __builtin_amdgcn_global_load_lds((global_void*)((const char*)a.turns + (32 + (second ? 0 : tile)) * (uint32_t)kTurnBytes + (uint32_t)(lane * 16 % kTurnBytes)),
+                                       (lds_void*)turn_st[wave], 16, 0, 0);
   };
   auto load_tile = [&](const int32_t (&mine)[kLoads], bool values) {
     unsigned char* dst = values ? v_st[wave] : k_st[wave];
@@ -204,17 +239,40 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   const bool has_tile = t < tile_end;
   int32_t next = 0;                                                         // index entry of the wave's next tile
   int32_t mine[kLoads];
-  u32x4 qf[kKS];
+  u32x4 qf[TURNED ? 1 : kKS];
+  f32x4 within[TURNED ? 2 * kKS : 1];              // cosine, sine of two pairs each: the turn by this lane's key's number in the tile
+  if constexpr (TURNED) {                          // eight rows from each wave
+#pragma unroll
+    for (int i = 0; i < 8 / kLoadRows; ++i) {
+      const int q_row = 8 * wave + kLoadRows * i + (int)st_row, of_tile = rt * kRows + q_row < n_rows ? rt * kRows + q_row : n_rows - 1;
+      const int q_tok = a.group_log2 >= 0 ? of_tile >> a.group_log2 : of_tile / a.group;
+      const char* src = V.q + ((int64_t)b * V.q_bs + ((int64_t)q_tok * a.h + g * a.group + of_tile - q_tok * a.group) * D) * (int64_t)sizeof(T);
+      __builtin_amdgcn_global_load_lds((global_void*)(src + (st_slot ^ k_swizzle(q_row)) * 16), (lds_void*)(q_st + (8 * wave + kLoadRows * i) * kRowBytes), 16, 0, 0);
+    }
+  }
   if (has_tile) {
     const int32_t first = lookup(t);
-    const char* qp = V.q + ((int64_t)b * V.q_bs + ((int64_t)c * a.h + head) * D) * (int64_t)sizeof(T) + hi * 16;
+    if constexpr (!TURNED) {
+      const char* qp = V.q + ((int64_t)b * V.q_bs + ((int64_t)c * a.h + head) * D) * (int64_t)sizeof(T) + hi * 16;
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) qf[ks] = *(const u32x4*)(qp + ks * 32);
+      for (int ks = 0; ks < kKS; ++ks) qf[ks] = *(const u32x4*)(qp + ks * 32);
+    }
     if (t + kWaves < tile_end) next = lookup(t + kWaves);
+    if constexpr (TURNED) {
+#pragma unroll
+      for (int i = 0; i < 2 * kKS; ++i) within[i] = *(const f32x4*)(a.turns + (i * 64 + lane) * 4);
+    }
     __builtin_amdgcn_sched_barrier(0);
     spread(place_of(t, first), mine);
+    load_turn(t);
     load_tile(mine, false);
     load_tile(mine, true);
+  }
+  if constexpr (TURNED) {                          // the queries, of all waves; the tile may still be on its way
+    if (has_tile) wait_loads<2 * kLoads + 1>();
+    else wait_loads<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   }
   f32x16 o[kMD];
 #pragma unroll
@@ -241,6 +299,35 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
       f32x16 s, s_odd;
 #pragma unroll
       for (int v = 0; v < 16; ++v) s[v] = s_odd[v] = 0.f;
+      if constexpr (TURNED) {
+        // two fragments (a pair's halves) at a time, all that a step reads in flight together: there are no registers for more
+        const uint32_t turn_at = (uint32_t)(uintptr_t)(lds_byte*)turn_st[wave] + hi * 64;
+        const uint32_t q_at = (uint32_t)(uintptr_t)(lds_byte*)q_st + r * kRowBytes + ((hi ^ k_swizzle(r)) << 4);
+#pragma unroll
+        for (int ks = 0; ks < kKS / 2; ++ks) {
+          u32x4 x[4], q[2], kf[2];
+          kf[0] = lds_read16(k_at ^ (ks << 5));
+          kf[1] = lds_read16(k_at ^ ((ks + kKS / 2) << 5));
+#pragma unroll
+          for (int w = 0; w < 4; ++w) x[w] = lds_read16(turn_at + ks * 128 + w * 16);
+          q[0] = lds_read16(q_at ^ (ks << 5));
+          q[1] = lds_read16(q_at ^ ((ks + kKS / 2) << 5));
+          arrived4<0>(x[0], x[1], x[2], x[3]);
+          arrived4<0>(kf[0], kf[1], q[0], q[1]);
+          if (!second) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+              uint32_t ka = kf[0][w], kb = kf[1][w];
+              turn_pairs(ka, kb, __builtin_bit_cast(f32x4, x[w]), within[4 * ks + w]);
+              kf[0][w] = ka;
+              kf[1][w] = kb;
+            }
+          }
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[0]), __builtin_bit_cast(bf16x8, q[0]), s, 0, 0, 0);
+          s_odd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[1]), __builtin_bit_cast(bf16x8, q[1]), s_odd, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
       u32x4 kf[kKS];
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) kf[ks] = lds_read16(k_at ^ (ks << 5));
@@ -265,10 +352,12 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
           }
         }
       }
+      }
       if constexpr (kBf16) s += s_odd;
       __builtin_amdgcn_sched_barrier(0);
       if (more) {
         spread(place_of(t + kWaves, next), mine);
+        load_turn(t + kWaves);
         load_tile(mine, false);                                             // over the keys just consumed
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -298,21 +387,24 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
           for (int v = 0; v < 16; ++v) o[md][v] *= corr;
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (more) wait_loads<kLoads>();                                       // the values; the next keys may be on their way
+      if (more) wait_loads<kLoads + (TURNED ? 1 : 0)>();                    // the values; the next keys may be on their way
       else wait_loads<0>();
       if constexpr (kBf16) {
         i16x4 vf[2][kMD][2];
+        uint32_t v_first = v_at[0];
+        if constexpr (TURNED) asm volatile("" : "+v"(v_first));             // the other dims' addresses would be kept, and spilled
         auto request = [&](auto kp_c) {
           constexpr int kp = decltype(kp_c)::value;
 #pragma unroll
           for (int md = 0; md < kMD; ++md) {
-            vf[kp][md][0] = lds_read_tr<kp * 16 * D * 2>(v_at[md]);               // keys 16kp + 4hi + 0..3
-            vf[kp][md][1] = lds_read_tr<(kp * 16 + 8) * D * 2>(v_at[md]);         // keys 16kp + 8 + 4hi + 0..3
+            const uint32_t at = TURNED ? v_first ^ (md << 6) : v_at[md];           // (the same: the chunk's number is two bits of its own)
+            vf[kp][md][0] = lds_read_tr<kp * 16 * D * 2>(at);                     // keys 16kp + 4hi + 0..3
+            vf[kp][md][1] = lds_read_tr<(kp * 16 + 8) * D * 2>(at);               // keys 16kp + 8 + 4hi + 0..3
           }
         };
         auto multiply = [&](auto kp_c) {
           constexpr int kp = decltype(kp_c)::value;
-          constexpr int kNewer = kp == 0 ? 2 * kMD : 0;
+          constexpr int kNewer = kp == 0 && !TURNED ? 2 * kMD : 0;
 #pragma unroll
           for (int md = 0; md < kMD; md += 2) arrived4<kNewer>(vf[kp][md][0], vf[kp][md][1], vf[kp][md + 1][0], vf[kp][md + 1][1]);
           // A probability goes in as three bf16 terms, each the rounded value of what the ones before it leave: together
@@ -336,8 +428,12 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
           }
         };
         request(std::integral_constant<int, 0>());
-        request(std::integral_constant<int, 1>());
+        if constexpr (!TURNED) request(std::integral_constant<int, 1>());
         multiply(std::integral_constant<int, 0>());
+        if constexpr (TURNED) {                                             // (no registers for both groups of keys at once)
+          __builtin_amdgcn_sched_barrier(0);
+          request(std::integral_constant<int, 1>());
+        }
         multiply(std::integral_constant<int, 1>());
       } else {
         // step v multiplies keys 8*(v/4) + v%4 (lower half-wave) and + 4 (upper): the keys of S^T's register v
@@ -538,6 +634,7 @@ SplitArgs make_args(const SplitCall& c) {
   a.scale = c.dtype == ESA_F32 ? c.scale : c.scale * kLog2e;
   a.out_bs = c.out_bs;
   a.sel_bs_bytes = c.sel_bs * esz;
+  a.turns = (const float*)c.turns;
   return a;
 }
 int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
@@ -554,6 +651,12 @@ void run(const SplitCall& c, const SplitArgs& args, hipStream_t st) {
   SplitArgs a = args;
   for_pair_grids((int64_t)c.batch * c.h_kv, a.n_rt, a.view[0].n_split + a.view[1].n_split, [&](dim3 grid, PairGrid placed) {
     a.grid = placed;
+    if constexpr (sizeof(T) == 2) {
+      if (a.turns) {
+        attend_split<T, D, true><<<grid, 64 * kWaves, 0, st>>>(a);
+        return;
+      }
+    }
     attend_split<T, D><<<grid, 64 * kWaves, 0, st>>>(a);
   });
 }
@@ -602,6 +705,10 @@ bool attend_split_supported(int l_c, int h, int h_kv, int d, int dtype, int batc
   if (dtype == ESA_BF16 ? (l_c >= 16 || (d != 64 && d != 128)) : (d != 32 && d != 64 && d != 128)) return false;
   return (int64_t)l_c * (h / h_kv) < (1 << 30) &&
          (int64_t)row_tiles(l_c, h, h_kv) * h_kv * batch * 2 * split_limit(l_c, h, h_kv, batch) < ((int64_t)1 << 31);
+}
+
+bool attend_split_turns_keys(int l_c, int h, int h_kv, int d, int dtype, int batch) {
+  return dtype == ESA_BF16 && attend_split_supported(l_c, h, h_kv, d, dtype, batch) && row_tiles(l_c, h, h_kv) == 1;
 }
 
 size_t attend_split_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int batch) {

@@ -162,8 +162,11 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
                   hipStream_t st, bool plain = false);
 
 // Section 3.2: rotary re-encoding.  One launch serves up to four row sets ("jobs"); row i of a job
-// is rotated to position pos0 + i * pos_step, or copied unchanged when rotate == 0.
+// is rotated to position pos0 + i * pos_step (rotate == 1), or copied unchanged (0); kRopeTurns: a table of n_tok = 32 + tiles rows of
+// fp32 cosines and sines, from which attend_split turns keys by itself (head sizes 64 and 128).
 constexpr int kMaxRopeJobs = 4;
+constexpr int kRopeTurns = 2;
+static inline size_t rope_turns_bytes(int64_t n_keys, int d) { return (size_t)(32 + (n_keys + 31) / 32) * d / 2 * 8; }
 struct RopeJob {
   const void* x;
   void* out;

@@ -66,6 +66,17 @@ __host__ __device__ inline int rows_of(int heads, int budget) {
   return r;
 }
 
+// A table of turns instead of rows: cosine and sine of 0 ... 31 positions, in the order in which the lanes of a wave that each stand
+// for a key read them as a matrix fragment, then of every multiple of 32, in the frequencies' order.  A key's angle is the sum of two
+// of them.  Row r < 32: pair i = 16 ks + 8 hi + e stands at [ks][e / 2][32 hi + r][e % 2].
+__device__ __forceinline__ void write_turns(float2* out, int64_t row, int i, int half, double freq) {
+  const double pos = row < 32 ? (double)row : 32.0 * (double)(row - 32);
+  double c = 1.0, s = 0.0;
+  if (pos != 0.0) sincos(pos * freq, &s, &c);
+  const int64_t at = row < 32 ? ((int64_t)(i / 16 * 4 + i % 8 / 2) * 64 + i / 8 % 2 * 32 + row) * 2 + i % 2 : row * half + i;
+  out[at] = make_float2((float)c, (float)s);
+}
+
 // grid (groups of rows, jobs, batch); 256 threads.  The rows' angles go through LDS once; then a thread owns VEC
 // consecutive pairs of a row (VEC elements = 16 bytes per access when VEC > 1; VEC == 1 serves unaligned rows) for all of
 // the row's heads, or for every hs-th of them where there are too few rows to go round.
@@ -73,11 +84,16 @@ template <typename T, int VEC>
 __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int d, int budget) {
   extern __shared__ double cs[];                       // [kRopeRows][d/2] cosines, then sines
   const RopeJob jb = jobs.j[blockIdx.y];
-  const int wg_rows = rows_of(jb.heads, budget);
+  const int wg_rows = jb.rotate == kRopeTurns ? 512 / d : rows_of(jb.heads, budget);
   const int64_t row0 = (int64_t)blockIdx.x * wg_rows;
   if (row0 >= jb.n_tok) return;
   const int n_rows = jb.n_tok - row0 < wg_rows ? (int)(jb.n_tok - row0) : wg_rows;
   const int half = d >> 1, tid = threadIdx.x;
+  if (jb.rotate == kRopeTurns) {          // one table for all batch entries, a sine and a cosine to a thread
+    const int g = tid / half;
+    if (blockIdx.z == 0 && g < n_rows) write_turns((float2*)jb.out, row0 + g, tid % half, half, turns.freq[tid % half]);
+    return;
+  }
   const T* x = (const T*)jb.x + (int64_t)blockIdx.z * jb.x_bs + row0 * jb.ldx;
   T* o = (T*)jb.out + (int64_t)blockIdx.z * jb.out_bs + row0 * jb.ldo;
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
@@ -187,7 +203,7 @@ int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dt
     js.j[k] = jobs[k < n_jobs ? k : 0];
     if (k >= n_jobs) js.j[k].n_tok = 0;
     if (js.j[k].n_tok > rows) rows = js.j[k].n_tok;
-    if (k < n_jobs && js.j[k].rotate && js.j[k].pos_step != 0.0) {
+    if (k < n_jobs && js.j[k].rotate == 1 && js.j[k].pos_step != 0.0) {
       if (step != 0.0 && step != js.j[k].pos_step) ESA_FAIL(ESA_EINVAL, "rope: jobs of one launch share their step");
       step = js.j[k].pos_step;
     }
@@ -201,7 +217,7 @@ int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dt
   auto groups_of = [&](int budget) {
     Groups g = {0, 0};
     for (int k = 0; k < n_jobs; ++k) {
-      const int r = rows_of(jobs[k].heads, budget);
+      const int r = jobs[k].rotate == kRopeTurns ? 512 / d : rows_of(jobs[k].heads, budget);
       const int64_t n = (jobs[k].n_tok + r - 1) / r;
       g.most = n > g.most ? n : g.most;
       g.all += n;
@@ -222,6 +238,7 @@ int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dt
   bool wide = (d / 2) % vec == 0;
   for (int k = 0; k < n_jobs; ++k) {
     const RopeJob& j = jobs[k];
+    if (j.rotate == kRopeTurns) continue;
     wide = wide && ((uintptr_t)j.x % 16 == 0) && ((uintptr_t)j.out % 16 == 0) && j.ldx % vec == 0 && j.ldo % vec == 0 &&
            j.x_bs % vec == 0 && j.out_bs % vec == 0;
   }

@@ -317,6 +317,33 @@ def test_attention_where_the_reference_moves_and_over_long_slices(esa, B, H, H_k
         assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3, b
 
 
+# Few tokens that turn the local keys as they read them: no local key but the tokens' own, a tile of keys, one less and one more, windows
+# whose slices end inside; 32 rows to a KV head (the most), one more (an encoded copy); head sizes, group sizes, a padded cache
+@pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel,pad", [
+    (1, 8, 2, 128, 300, 1, 16, 0, 40, 0), (1, 8, 2, 128, 300, 1, 16, 31, 40, 0), (2, 8, 8, 128, 300, 2, 16, 31, 0, 64), (1, 32, 8, 128, 3000, 1, 128, 2048, 500, 0),
+    (2, 32, 8, 128, 900, 8, 16, 333, 64, 8), (2, 32, 8, 128, 900, 9, 16, 333, 64, 0), (3, 16, 2, 128, 900, 4, 0, 400, 65, 0), (1, 6, 2, 128, 500, 10, 16, 100, 33, 0),
+    (1, 8, 2, 64, 300, 1, 16, 32, 40, 0), (2, 16, 2, 64, 2500, 4, 16, 2000, 100, 8), (4, 8, 8, 64, 700, 15, 16, 200, 31, 0), (1, 8, 4, 64, 0, 7, 16, 32, 0, 0)])
+def test_reencoded_attention_of_few_tokens_turns_the_local_keys(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel, pad):
+    say(f"re-encoded, few tokens B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel} pad={pad}")
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+
+    def rows(x):                    # token rows `pad` elements apart
+        x = f64_to_dev(x, "bf16")
+        buf = torch.zeros((B, t0 + l_C, H_kv * d + pad), dtype=x.dtype, device="cuda")
+        view = buf.as_strided((B, t0 + l_C, H_kv, d), ((t0 + l_C) * (H_kv * d + pad), H_kv * d + pad, d, 1))
+        view.copy_(x)
+        return view
+
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), rows(K), rows(V), torch.from_numpy(sel).cuda()
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx) if n_sel else (None, None)
+    O, lse = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5, return_lse=True)
+    for b in range(B):
+        want, want_lse = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
+        # a logit of unit scale errs by 2^-9 / sqrt(d) per element of the rounded rows: as with encoded copies
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 2e-2, b
+
+
 # Gathered rows: segment boundaries at a tile's edge, one key beside it, two of them inside one tile, no boundary but the sequence's
 # end; slices that end between.  The index-driven form takes the same keys in the same order.
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
