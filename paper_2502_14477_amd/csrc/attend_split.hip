@@ -4,7 +4,7 @@
 // A decode step reads every attended key and value once (17 MB per sequence at the Llama shape) for a few hundred
 // floating-point operations per byte less than the matrix cores need, so what counts is that many independent
 // requests are in flight and that the current tokens share them.  A workgroup owns 32 "rows" = (current tokens x query
-// heads of one KV head, numbered token by token) and a slice of the virtual key sequence [I | M_k | L | C]; its four
+// heads of one KV head, numbered token by token) and a slice of the virtual key sequence [I | M_k | L | C]; its four or five
 // waves take the slice's 32-key tiles in turn, each with staging space of its own, so that no barrier stands in the
 // tile loop: a wave waits for its own keys, and while its values are still arriving requests the next tile's keys.
 // The waves' results meet in LDS, the slices' in a second small kernel (Algorithm 1's log-sum-exp rule).
@@ -36,7 +36,8 @@ typedef __attribute__((address_space(1))) const void global_void;
 
 constexpr int kKT = 32;             // keys per tile
 constexpr int kRows = 32;           // rows per workgroup
-constexpr int kWaves = 4;
+constexpr int kWavesOfTwo = 4;      // waves of a workgroup of which a compute unit holds two ...
+constexpr int kWavesOfOne = 5;      // ... and of one that has it to itself (see waves_of)
 constexpr int kMaxSplits = 64;
 constexpr int kTargetWorkgroups = 512;   // two per compute unit: 64 KB of staging each at 256-byte rows
 constexpr float kLog2e = 1.4426950408889634f;
@@ -135,8 +136,9 @@ __device__ __forceinline__ void turn_pairs(uint32_t& a, uint32_t& b, const f32x4
 // 2048.  Step, us, copied and turned here: that one at 64 thousand tokens 121.1 / 107.2, one sequence 45.4 / 43.5, eight of eight KV
 // heads at 30 thousand 85 / 73, four of five drafted tokens 75 / 70.  Distance from the 64-bit result, six shapes of six seeds: 2.8103 /
 // 2.8102e-3.)
-template <typename T, int D, bool TURNED = false>
-__global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void attend_split(SplitArgs a) {
+template <typename T, int D, int kWaves, bool TURNED = false>
+__global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 || kWaves > kWavesOfTwo ? 1 : 2) __attribute__((amdgpu_waves_per_eu(D * sizeof(T) > 256 ? 1 : 2)))
+void attend_split(SplitArgs a) {
   static_assert(!TURNED || sizeof(T) == 2, "the table's order");
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int kRowBytes = D * (int)sizeof(T);
@@ -241,13 +243,13 @@ __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 ? 1 : 2) void atte
   int32_t mine[kLoads];
   u32x4 qf[TURNED ? 1 : kKS];
   f32x4 within[TURNED ? 2 * kKS : 1];              // cosine, sine of two pairs each: the turn by this lane's key's number in the tile
-  if constexpr (TURNED) {                          // eight rows from each wave
+  if constexpr (TURNED) {                          // eight rows from each wave, which need four
 #pragma unroll
     for (int i = 0; i < 8 / kLoadRows; ++i) {
-      const int q_row = 8 * wave + kLoadRows * i + (int)st_row, of_tile = rt * kRows + q_row < n_rows ? rt * kRows + q_row : n_rows - 1;
+      const int wave_rows = 8 * (wave & 3), q_row = wave_rows + kLoadRows * i + (int)st_row, of_tile = rt * kRows + q_row < n_rows ? rt * kRows + q_row : n_rows - 1;
       const int q_tok = a.group_log2 >= 0 ? of_tile >> a.group_log2 : of_tile / a.group;
       const char* src = V.q + ((int64_t)b * V.q_bs + ((int64_t)q_tok * a.h + g * a.group + of_tile - q_tok * a.group) * D) * (int64_t)sizeof(T);
-      __builtin_amdgcn_global_load_lds((global_void*)(src + (st_slot ^ k_swizzle(q_row)) * 16), (lds_void*)(q_st + (8 * wave + kLoadRows * i) * kRowBytes), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_void*)(src + (st_slot ^ k_swizzle(q_row)) * 16), (lds_void*)(q_st + (wave_rows + kLoadRows * i) * kRowBytes), 16, 0, 0);
     }
   }
   if (has_tile) {
@@ -607,9 +609,17 @@ int split_limit(int l_c, int h, int h_kv, int batch) {
   return (int)(ns < 1 ? 1 : (ns > kMaxSplits ? kMaxSplits : ns));
 }
 // Slices of n_keys keys: a tile per wave at least.
-int split_count(int limit, int64_t n_keys) {
-  const int64_t most = (n_keys + kKT * kWaves - 1) / (kKT * kWaves);
+int split_count(int limit, int64_t n_keys, int waves = kWavesOfTwo) {
+  const int64_t most = (n_keys + kKT * waves - 1) / (kKT * waves);
   return (int)(most < 1 ? 1 : (most < limit ? most : limit));
+}
+// Waves of a workgroup: five where workgroups of four with a tile per wave are a few more than the compute units and those of five are not.
+// A compute unit takes 64 KB of tiles in 0.9 us and 128 KB in 2.3 (a row at a time into LDS), so that the sixteen that got two workgroups
+// of 272 kept the others waiting: one token over 4225 keys of 8 KV heads 7.35 -> 6.6 us from first entry to last store (8.3 -> 7.4 on a
+// long document), a step 41.5 -> 40.35, re-encoded 46.9 -> 45.6.
+int waves_of(int64_t groups, int64_t n_keys0, int64_t n_keys1) {
+  auto workgroups = [&](int w) { return groups * ((n_keys0 + kKT * w - 1) / (kKT * w) + (n_keys1 + kKT * w - 1) / (kKT * w)); };
+  return workgroups(kWavesOfTwo) > 256 && workgroups(kWavesOfOne) <= (256 < groups * kMaxSplits ? 256 : groups * kMaxSplits) ? kWavesOfOne : kWavesOfTwo;
 }
 
 size_t ml_offset(int64_t rows, int n_slot, int d) { return align_up((size_t)rows * n_slot * d * sizeof(float), 256); }
@@ -647,17 +657,16 @@ int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
 }
 
 template <typename T, int D>
-void run(const SplitCall& c, const SplitArgs& args, hipStream_t st) {
+void run(const SplitCall& c, const SplitArgs& args, int waves, hipStream_t st) {
   SplitArgs a = args;
+  auto kernel = attend_split<T, D, kWavesOfTwo>;
+  if constexpr (sizeof(T) == 2) {
+    if (waves == kWavesOfOne) kernel = a.turns ? attend_split<T, D, kWavesOfOne, true> : attend_split<T, D, kWavesOfOne>;
+    else if (a.turns) kernel = attend_split<T, D, kWavesOfTwo, true>;
+  }
   for_pair_grids((int64_t)c.batch * c.h_kv, a.n_rt, a.view[0].n_split + a.view[1].n_split, [&](dim3 grid, PairGrid placed) {
     a.grid = placed;
-    if constexpr (sizeof(T) == 2) {
-      if (a.turns) {
-        attend_split<T, D, true><<<grid, 64 * kWaves, 0, st>>>(a);
-        return;
-      }
-    }
-    attend_split<T, D><<<grid, 64 * kWaves, 0, st>>>(a);
+    kernel<<<grid, 64 * waves, 0, st>>>(a);
   });
 }
 template <typename T, int D>
@@ -685,7 +694,8 @@ struct RunIt {
   const SplitCall& c;
   const SplitArgs& a;
   hipStream_t st;
-  template <typename T, int D> void operator()() { run<T, D>(c, a, st); }
+  int waves = kWavesOfTwo;
+  template <typename T, int D> void operator()() { run<T, D>(c, a, waves, st); }
 };
 struct MergeIt {
   const SplitCall& c;
@@ -720,14 +730,17 @@ int launch_attend_split(const SplitCall& c, KeyView v0, const KeyView* v1, hipSt
   SplitArgs a = make_args(c);
   const int limit = split_limit(c.l_c, c.h, c.h_kv, c.batch);
   const int64_t k0 = keys_of(v0, c.l_c), k1 = v1 ? keys_of(*v1, c.l_c) : 0;
+  const int waves = c.dtype == ESA_BF16 ? waves_of((int64_t)a.n_rt * c.h_kv * c.batch, k0, k1) : kWavesOfTwo;
   int n0 = limit, n1 = 0;
-  if (k1 > 0) {            // the slices are shared out in proportion to the two parts' lengths, at least one each
+  if (waves == kWavesOfOne) {
+    n1 = k1 > 0 ? split_count(limit, k1, waves) : 0;
+  } else if (k1 > 0) {            // the slices are shared out in proportion to the two parts' lengths, at least one each
     n1 = (int)((limit * k1 + (k0 + k1) / 2) / (k0 + k1));
     n1 = n1 < 1 ? 1 : n1;
     n0 = limit - n1 < 1 ? 1 : limit - n1;
     n1 = split_count(n1, k1);
   }
-  n0 = split_count(n0, k0);
+  n0 = split_count(n0, k0, waves);
   a.view[0] = v0;
   set_splits(&a.view[0], n0, 0);
   a.view[1] = k1 > 0 ? *v1 : v0;
@@ -736,7 +749,7 @@ int launch_attend_split(const SplitCall& c, KeyView v0, const KeyView* v1, hipSt
     const int rc = with_slots(&a, c, n0 + n1);
     if (rc != ESA_OK) return rc;
   }
-  dispatch(c, RunIt{c, a, st});
+  dispatch(c, RunIt{c, a, st, waves});
   if (n0 + n1 > 1) dispatch(c, MergeIt{c, a, n0 + n1, st});
   ESA_LAUNCH_CHECK("attend_split");
   return ESA_OK;

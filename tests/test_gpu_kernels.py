@@ -317,6 +317,28 @@ def test_attention_where_the_reference_moves_and_over_long_slices(esa, B, H, H_k
         assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3, b
 
 
+# Workgroups of five waves (bf16): the fewest and the most keys they take for 8, 16 and 64 pairs of sequence and KV head, one key less and
+# one more, a last tile of one key; in one part and in Section 3.2's two
+@pytest.mark.parametrize("B,H,H_kv,d,l_C,keys", [(1, 16, 8, 128, 1, 4096), (1, 16, 8, 128, 1, 4097), (1, 16, 8, 64, 1, 5120), (1, 16, 8, 128, 1, 5121), (1, 16, 8, 128, 5, 4300),
+                                                 (2, 8, 8, 64, 1, 2049), (2, 8, 8, 128, 1, 2560), (8, 8, 8, 128, 1, 513), (8, 8, 8, 64, 3, 640), (1, 8, 1, 128, 15, 9000)])
+def test_split_key_attention_in_workgroups_of_five_waves(esa, B, H, H_kv, d, l_C, keys):
+    say(f"attend, five waves B={B} H={H} H_kv={H_kv} d={d} l_C={l_C} keys={keys}")
+    l_I, n_sel = 64, keys // 3
+    l_L = keys - l_C - l_I - n_sel
+    t0 = l_I + 2 * n_sel + l_L
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16"), torch.from_numpy(sel).cuda()
+    O, lse = esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx, return_lse=True)
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx)
+    O_re = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5)
+    for b in range(B):
+        want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"]
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3
+        want, _ = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
+        assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL["bf16"]
+
+
 # Few tokens that turn the local keys as they read them: no local key but the tokens' own, a tile of keys, one less and one more, windows
 # whose slices end inside; 32 rows to a KV head (the most), one more (an encoded copy); head sizes, group sizes, a padded cache
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel,pad", [
