@@ -65,10 +65,8 @@ constexpr int kKT = 64;             // virtual keys per tile
 constexpr int kRows = 256;          // query rows per workgroup
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kMaxSlots = 16;           // partial results per row
-// Slices of the key sequence, one-call form.  Short chunks need sixteen to fill the chip (77 tokens at 50k: 61 -> 55.6 us a
-// step against eight); their fp16 results err independently (outputs 2.27e-3 from the 64-bit result, 2.31e-3 with eight).
-constexpr int kMaxSplits = 16;
+constexpr int kMaxSlots = 32;           // partial results per row
+constexpr int kMaxSplits = 16;          // slices of the key sequence, two-call form
 constexpr int kMaxSelSplits = 8;        // two-call form: at most half as many local slices, then the selected ones
 constexpr int kStages = 3;
 constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
@@ -544,19 +542,24 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
         pf[2 * mt + kp][e] = pack_bf16x2(p[mt][v], p[mt][v + 1]);
       }
     };
-    // (A sum that is no number does not exceed it: the row's output is none either way.)
+    // (A sum that is no number does not exceed it: the row's output is none either way.)  In the first two tiles the reference moves to
+    // the largest logit in any case: the key that it stands at has an exact probability, and a slice's largest of 128 keys weighs more
+    // than its largest of 32.  Distance from the 64-bit result, mean over eleven calls of 20 to 700 tokens, four seeds: 2.295e-3, 2.330 without
+    // (2.308 with the maximum of every tile and up to sixteen slices); steps 0 to 1.5 % longer.
     auto settle = [&](int mt) __attribute__((always_inline)) {
-      if (__builtin_expect(__ballot(psum[mt] > kMostSum) != 0ull, 0)) {
+      if (__builtin_expect(__ballot(psum[mt] > kMostSum) != 0ull || (mt == 1 && t < tile_begin + 2), 0)) {
         float mx = s[mt][0];
 #pragma unroll
         for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[mt][v]);
         const float m_old = m_run;
         m_run = fmaxf(m_run, halves_max(mx) * a.c2);
         const float corr = __builtin_amdgcn_exp2f(m_old - m_run);
+        if (mt || t != tile_begin || part) {              // (nothing has been summed yet)
 #pragma unroll
-        for (int md = 0; md < kMD; ++md)
+          for (int md = 0; md < kMD; ++md)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) o[md][v] *= corr;
+            for (int v = 0; v < 16; ++v) o[md][v] *= corr;
+        }
         l_run *= corr;
         if (mt) psum[0] *= corr;
         psum[mt] = 0.f;
@@ -751,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
 // trip of its own, and vector instructions were issued for sixteen slots whatever their number (1.2 % of a step with
 // four slices, 16.9 MB of partials for 512 tokens).
 template <int D, int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NS > 8 ? 4 : 8)))   // registers for all loads
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NS > 16 ? 2 : NS > 8 ? 4 : 8)))   // registers for all loads
 void esa_attend_merge(const void* __restrict__ part_o, const float* __restrict__ part_ml, int n_slot, int ns_a,
                       int slot_b, int64_t rows, bf16_t* __restrict__ out, float* __restrict__ lse, int64_t out_bs,
                       int64_t lse_bs) {
@@ -804,12 +807,12 @@ void esa_attend_merge(const void* __restrict__ part_o, const float* __restrict__
   if (lse && dim == 0) lse[(int64_t)b * lse_bs + row] = lse_of<D>(M, L);
 }
 
-// Row tiles: as few as hold the chunk at 256 rows each, the tokens shared out evenly in units of a wave's 32 rows.
+// Row tiles: as few as hold the chunk at most_rows rows each, the tokens shared out evenly in units of a wave's 32 rows.
 struct RowTiles {
   int n_qt, qpt;
 };
-RowTiles row_tiles(int l_c, int group) {
-  const int most = kRows / group, unit = 32 / group;
+RowTiles row_tiles(int l_c, int group, int most_rows = kRows) {
+  const int most = most_rows / group, unit = 32 / group;
   RowTiles t;
   t.n_qt = (l_c + most - 1) / most;
   t.qpt = ((l_c + t.n_qt - 1) / t.n_qt + unit - 1) / unit * unit;
@@ -818,8 +821,48 @@ RowTiles row_tiles(int l_c, int group) {
 
 int choose_splits(int l_c, int group, int h_kv, int batch) {
   const int64_t tiles = (int64_t)row_tiles(l_c, group).n_qt * h_kv * batch;
-  int64_t ns = (256 + tiles - 1) / tiles;
+  const int64_t ns = (256 + tiles - 1) / tiles;
   return (int)(ns < 1 ? 1 : (ns > kMaxSplits ? kMaxSplits : ns));
+}
+
+// ---- one-call form: row tiles of 256 or of 128 rows, and the number of slices.  A compute unit holds one workgroup, so a workgroup
+// more than 256 costs another round of them (160 tokens of eight KV heads in eleven slices of three row tiles, 264 workgroups: 38.5 us a
+// call, 23.6 as chosen here), and a number far below leaves compute units idle.  With 128 rows a SIMD has one wave instead of
+// two: a tile takes 1.0 us instead of 1.6, start, end and merge 12.4 instead of 17 (calls of 64 to 512 tokens of eight KV heads over 4
+// thousand keys fit these to 0.3 us), so half the rows are the better choice up to some 11 tiles a slice.  A merge of more than sixteen
+// slots has few rows and waits for its loads.  Calls of l_c tokens of eight KV heads, us, with 256 rows and 256 / tiles slices rounded up, at
+// most sixteen, and as chosen here, 4 thousand keys: 48 19.3 / 16.7, 77 21.5 / 18.4, 128 24.6 / 21.3, 256 31.0 / 29.6, 300 49.3 / 34.8,
+// 384 54 / 39.7, 700 91 / 67, 512 and 1000 the same; 16 thousand: 20 24.8 / 21.0, 64 35.0 / 27.7, 300 130 / 84, 700 290 / 190.
+// Slices that a launch over this many (row tile, pair)s may have: one round of workgroups where that fills nine tenths of the compute
+// units, three otherwise.  (Known without the number of keys, so that the workspace is.)
+int most_slices(int64_t base) {
+  const int64_t one = 256 / base, ns = one * base >= 230 ? one : 768 / base;
+  return (int)(ns < 1 ? 1 : ns > kMaxSlots ? kMaxSlots : ns);
+}
+struct Plan {
+  RowTiles rows;
+  int n_split;
+};
+Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t n_keys, int64_t keys_of_first_row) {
+  const int group = h / h_kv;
+  const int64_t tiles = (n_keys + kKT - 1) / kKT, first = (keys_of_first_row + kKT - 1) / kKT;
+  Plan best = {row_tiles(l_c, group), 1};
+  float least = FLT_MAX;
+  for (int most_rows = kRows; most_rows >= kRows / 2; most_rows /= 2) {
+    const RowTiles r = row_tiles(l_c, group, most_rows);
+    const int64_t base = (int64_t)r.n_qt * h_kv * batch;
+    const bool one_wave = r.qpt * group <= kRows / 2;                    // a SIMD's waves with rows
+    const int most = (int)(most_slices(base) < first ? most_slices(base) : first);
+    for (int ns = 1; ns <= most || ns == 1; ++ns) {
+      const float per_round = (one_wave ? 5.3f + 1.0f * (tiles + ns - 1) / ns : 8.0f + 1.6f * (tiles + ns - 1) / ns);
+      const float t = (float)((base * ns + 255) / 256) * per_round + (ns > 1 ? 3.f + 6.4e-5f * (float)l_c * h * batch * ns : 0.f) + (ns > 16 ? 0.2f * (ns - 16) : 0.f);
+      if (t < least) {
+        least = t;
+        best = {r, ns};
+      }
+    }
+  }
+  return best;
 }
 
 void launch_tiles(AttendArgs& a, int d, int n_split, int slot0, hipStream_t st) {
@@ -856,16 +899,15 @@ bool attend_mfma_supported(int l_c, int h, int h_kv, int d, int dtype) {
 
 namespace {
 
-// Planned slice counts.  One call: `all` slices of the whole virtual sequence.  Two calls: the local
-// part [ I | L | C ] runs beside other work, so it gets fewer, longer slices than the selected part,
-// which is on the critical path and should cover the chip by itself.
+// Planned slice counts of the two-call form: the local part [ I | L | C ] runs beside other work, so it gets fewer, longer slices than
+// the selected part, which is on the critical path and should cover the chip by itself.
 struct SplitPlan {
-  int all, local, sel;
+  int local, sel;
 };
 SplitPlan plan_splits(int l_c, int group, int h_kv, int batch) {
   SplitPlan p;
-  p.all = choose_splits(l_c, group, h_kv, batch);
-  p.sel = p.all < kMaxSelSplits ? p.all : kMaxSelSplits;
+  const int all = choose_splits(l_c, group, h_kv, batch);
+  p.sel = all < kMaxSelSplits ? all : kMaxSelSplits;
   p.local = p.sel > 1 ? p.sel / 2 : 1;
   return p;
 }
@@ -880,7 +922,11 @@ size_t slots_bytes(int n_slot, int l_c, int h, int d, int batch) {
 
 size_t attend_mfma_workspace_bytes(int l_c, int h, int h_kv, int d, int batch) {
   const SplitPlan p = plan_splits(l_c, h / h_kv, h_kv, batch);
-  const int n_slot = p.local + p.sel > p.all ? p.local + p.sel : p.all;
+  int n_slot = p.local + p.sel;
+  for (int most_rows = kRows; most_rows >= kRows / 2; most_rows /= 2) {
+    const int ns = most_slices((int64_t)row_tiles(l_c, h / h_kv, most_rows).n_qt * h_kv * batch);
+    n_slot = ns > n_slot ? ns : n_slot;
+  }
   return slots_bytes(n_slot, l_c, h, d, batch);
 }
 
@@ -912,7 +958,9 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.h_kv = h_kv;
   a.group = h / h_kv;
   a.group_log2 = __builtin_ctz(a.group);
-  const RowTiles tiles = row_tiles(l_c, a.group);
+  const int64_t n_fixed = i_end + n_sel + (t0 - l_start);
+  const Plan one = plan_one_call(l_c, h, h_kv, batch, n_fixed + l_c, n_fixed + 1);
+  const RowTiles tiles = part == kAttendAll ? one.rows : row_tiles(l_c, a.group);
   a.qpt = tiles.qpt;
   a.n_qt = tiles.n_qt;
   a.batch = batch;
@@ -922,8 +970,8 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
 
   const SplitPlan plan = plan_splits(l_c, a.group, h_kv, batch);
   const int first_rows = l_c < a.qpt ? l_c : a.qpt;
-  // slices in use: one call -> `all`; two calls -> local in slots [0, ns_local), selected in [plan.local, +ns_sel)
-  const int ns_all = clamp_splits(plan.all, i_end + n_sel + (t0 - l_start) + first_rows);
+  // slices in use: one call -> ns_all; two calls -> local in slots [0, ns_local), selected in [plan.local, +ns_sel)
+  const int ns_all = one.n_split;
   // split == ESA_SPLIT_ALGORITHM1 moves the initial tokens from the early part to the late one
   const int64_t i_early = split == ESA_SPLIT_ALGORITHM1 ? 0 : i_end, i_late = i_end - i_early;
   const int ns_local = clamp_splits(plan.local, i_early + (t0 - l_start) + first_rows);
@@ -990,18 +1038,16 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.h_kv = h_kv;
   a.group = h / h_kv;
   a.group_log2 = __builtin_ctz(a.group);
-  const RowTiles tiles = row_tiles(l_c, a.group);
-  a.qpt = tiles.qpt;
-  a.n_qt = tiles.n_qt;
+  // slices of the two parts' tiles laid end to end
+  const int64_t keys_b = i_end + n_sel;
+  const Plan plan = plan_one_call(l_c, h, h_kv, batch, align_up(n_loc + l_c, kKT) + keys_b, align_up(n_loc + 1, kKT) + keys_b);
+  a.qpt = plan.rows.qpt;
+  a.n_qt = plan.rows.n_qt;
   a.batch = batch;
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
   a.sel_bs_bytes = sel_bs * 2;
-  // the planned slices of the two parts' tiles laid end to end
-  const SplitPlan plan = plan_splits(l_c, a.group, h_kv, batch);
-  const int first_rows = l_c < a.qpt ? l_c : a.qpt;
-  const int64_t keys_b = i_end + n_sel;
-  const int n_slot = clamp_splits(plan.all, align_up(n_loc + first_rows, kKT) + keys_b);
+  const int n_slot = plan.n_split;
   const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
   a.part_o = nullptr;
   a.part_ml = nullptr;

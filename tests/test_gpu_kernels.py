@@ -339,6 +339,27 @@ def test_split_key_attention_in_workgroups_of_five_waves(esa, B, H, H_kv, d, l_C
         assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL["bf16"]
 
 
+# Plans of the one-call form: row tiles of 128 and of 256 rows, one slice and 32, more workgroups than one round of compute units, fewer
+# keys than slices would take, group sizes; Section 3.2's two parts with the same plans
+@pytest.mark.parametrize("B,H,H_kv,d,l_C,l_I,l_L,n_sel", [
+    (1, 32, 8, 128, 33, 64, 500, 400), (1, 32, 8, 128, 64, 64, 3000, 1000), (1, 32, 8, 128, 65, 64, 500, 400), (1, 32, 8, 128, 160, 64, 500, 400), (1, 16, 4, 128, 352, 64, 900, 700),
+    (1, 4, 4, 128, 20, 128, 9000, 7200), (1, 16, 2, 64, 17, 64, 500, 400), (2, 8, 8, 64, 130, 64, 500, 400), (33, 8, 8, 128, 16, 16, 40, 20), (3, 8, 1, 128, 700, 0, 30, 1), (40, 8, 8, 64, 257, 0, 0, 0)])
+def test_matrix_core_attention_plans(esa, B, H, H_kv, d, l_C, l_I, l_L, n_sel):
+    t0 = l_I + n_sel + n_sel // 2 + l_L
+    say(f"attend plan B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16"), torch.from_numpy(sel).cuda()
+    O, lse = esa.esa_attend_indexed(qd, Kd, Vd, t0, l_I, l_L, idx, return_lse=True)
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx) if n_sel else (None, None)
+    O_re = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5)
+    for b in range(0, B, max(1, B // 3)):
+        want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"]
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3
+        want, _ = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
+        assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL["bf16"]
+
+
 # Few tokens that turn the local keys as they read them: no local key but the tokens' own, a tile of keys, one less and one more, windows
 # whose slices end inside; 32 rows to a KV head (the most), one more (an encoded copy); head sizes, group sizes, a padded cache
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel,pad", [
