@@ -153,6 +153,22 @@ def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
         assert got[b].max() == 0.0
 
 
+# Shares of whole rounds of workgroups: the longest row of one round and one token more, rows of two rounds and of three, several
+# sequences whose shares together make a round, one more than that
+@pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 17, 131072, 64, 0), (1, 17, 131073, 64, 0), (1, 33, 140000, 128, 0), (1, 20, 263000, 64, 1), (4, 64, 20000, 128, 0),
+                                             (2, 70, 65536, 64, 0), (2, 70, 65537, 64, 2), (300, 20, 70, 64, 0)])
+def test_score_sweeps_in_whole_rounds(esa, B, l_c, n, d_c, eps):
+    say(f"score rounds B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
+    g = torch.Generator(device="cuda").manual_seed(n + l_c)
+    qc, kc = (torch.randn((B, m, d_c), generator=g, device="cuda").bfloat16() for m in (l_c, n + 8))
+    got = esa.esa_score(qc, kc, 3, n + 3, eps=eps)
+    for b in range(0, B, max(1, B // 2)):
+        want = orc.importance(to_f64(qc[b]), to_f64(kc[b, 3:n + 3]))
+        want = orc.proximity(want, eps) if eps else want
+        assert np.max(np.abs(to_f64(got[b]) - want)) <= F_TOL["bf16"], b
+        assert got[b].max() == 0.0
+
+
 # Pooling by the second sweep: one workgroup's tokens, one more, one less; a single token; the widest window it takes in the shortest
 # share and in long ones, the narrowest, one that keeps its own pass; windows across every workgroup's edge hold the row's largest scores
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 17, 1, 128, 1), (2, 40, 62, 128, 1), (1, 40, 63, 128, 1), (1, 20, 61, 64, 1), (1, 33, 32, 64, 16),
