@@ -1,8 +1,8 @@
 // Selected attention (Eq. 1) on the matrix cores: bf16 storage, head sizes 128 and 64.
 //
 // Work decomposition.  The query heads of one KV group share keys and values, so a workgroup
-// owns up to 256 "rows" = (up to 256/G consecutive current tokens) x (heads of one KV group), numbered
-// token by token, and one slice of the virtual key sequence [I | M_k | L | C]; slices of one row tile
+// owns up to 256 "rows" (128 where plan_one_call finds that quicker) = (up to 256/G consecutive current tokens) x (heads of one KV
+// group), numbered token by token, and one slice of the virtual key sequence [I | M_k | L | C]; slices of one row tile
 // are merged afterwards with the log-sum-exp rule of Algorithm 1 (esa_attend_merge).  The chunk's tokens are
 // shared out evenly over the row tiles, in units of a wave's 32 rows, and a wave without rows, or whose rows see
 // no key of a tile, leaves the tile's arithmetic out.  Eight waves of 32 rows each, two waves

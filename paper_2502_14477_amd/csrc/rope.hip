@@ -4,8 +4,8 @@
 // element i of its second half turn by the angle pos * base^(-2i/d).
 //
 // The angles are fp64.  esa_rope's products are, too, and round once into the storage type, so a row encoded there
-// equals the fp64 definition rounded to storage; bf16 rows for the attention kernels alone take fp32 products.  What bounds it is that arithmetic as much as the memory traffic
-// (re-encoded decode, batch 8: 16392 key rows of 2 KB, 67 MB): with a power, a sine and a cosine per row and frequency,
+// equals the fp64 definition rounded to storage; bf16 rows for the attention kernels alone take fp32 products.
+// What bounds it is that arithmetic as much as the memory traffic (re-encoded decode, batch 8: 16392 key rows of 2 KB, 67 MB): with a power, a sine and a cosine per row and frequency,
 // their table read again for every head, and a rounding from fp64 to bf16 in 64-bit integer steps it took 31.5 us.  Now
 // the frequencies and the turn from one row to the next come from the host (fp64 too, kept per thread for a base and
 // head size), a thread evaluates sine and cosine for the first of its few consecutive rows and turns the others by complex

@@ -1,6 +1,6 @@
 // Importance of every middle token (Eq. 6 inside Eq. 4):
 //   S[c,m] = q'_c . k'_m,  mu[c] = max_m S[c,m],  F[m] = max_c (S[c,m] - mu[c]),
-// optionally followed by the proximity max-pool of Eq. 8.
+// optionally with the proximity max-pool of Eq. 8: narrow windows in the kernel that writes the scores, wider ones behind it.
 //
 // F needs every row maximum before any column maximum.  A chunk of more than a few queries sweeps K' twice and
 // recomputes S instead of storing it (S would be l_C x N fp32; K' is only N x d_c storage elements).  Both sweeps compute
@@ -25,7 +25,7 @@ namespace {
 // floating-point mode attributes differ from the kernels'), and every use would be a function call.
 
 // Workspace: [batch][l_c] row maxima (uint32 keys or fp32), [batch][blocks][l_c] fp32 partial row maxima of the
-// matrix-core kernel, then (eps > 0) [batch][n] fp32 unpooled scores.
+// matrix-core kernel, then (windows that no score kernel pools) [batch][n] fp32 unpooled scores.
 __host__ __device__ inline size_t mu_bytes(int l_c, int batch) {      // rows padded to whole groups of 64
   return align_up((size_t)((l_c + 63) / 64 * 64) * batch * 4, 256);
 }
