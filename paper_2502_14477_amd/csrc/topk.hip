@@ -31,7 +31,7 @@ namespace esa {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kItems = 2;                       // consecutive scores per thread
+constexpr int kItems = 2;                       // scores per thread and tile
 constexpr int kTile = kThreads * kItems;        // scores per block
 constexpr int kBins = kRadixBins;
 constexpr int kBinsPerThread = kBins / kThreads;
@@ -70,37 +70,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
-// Exclusive prefix sums of two values per thread over a block of NT threads (one pair of barriers for both);
-// *total_a and *total_b get the block sums.  wave_sums: 2 * NT / 64 words.
-template <int NT>
-__device__ __forceinline__ void block_excl_scan2(uint32_t a, uint32_t b, uint32_t* before_a, uint32_t* before_b,
-                                                 uint32_t* total_a, uint32_t* total_b, uint32_t* wave_sums) {
-  constexpr int kWavesPerBlock = NT / 64;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
-  __syncthreads();                       // wave_sums may still be read from a previous call
-  if (lane == 63) {
-    wave_sums[w] = ia;
-    wave_sums[kWavesPerBlock + w] = ib;
-  }
-  __syncthreads();
-  uint32_t base_a = 0, tot_a = 0, base_b = 0, tot_b = 0;
-#pragma unroll
-  for (int i = 0; i < kWavesPerBlock; ++i) {
-    const uint32_t sa = wave_sums[i], sb = wave_sums[kWavesPerBlock + i];
-    if (i < w) {
-      base_a += sa;
-      base_b += sb;
-    }
-    tot_a += sa;
-    tot_b += sb;
-  }
-  *total_a = tot_a;
-  *total_b = tot_b;
-  *before_a = base_a + ia - a;
-  *before_b = base_b + ib - b;
-}
-
 // Exclusive prefix sum of one value per thread over the block.
 template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_sums) {
@@ -115,19 +84,11 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_s
   return base + incl - v;
 }
 
-__device__ __forceinline__ void load_keys(const float* row, int64_t n, int64_t first, uint32_t (&key)[kItems],
-                                          bool (&ok)[kItems]) {
-  // unconditional loads (a position past the end reads score 0 instead): both are in flight together, and with
+__device__ __forceinline__ void load_scores(const float* row, int64_t n, int64_t first, float (&v)[kItems]) {
+  // unconditional loads (a position past the end reads score 0 instead): all are in flight together, and with
   // the histogram loads that follow, rather than one round trip each behind a branch
-  float v[kItems];
 #pragma unroll
-  for (int e = 0; e < kItems; ++e) {
-    const int64_t i = first + e;
-    ok[e] = i < n;
-    v[e] = row[ok[e] ? i : 0];
-  }
-#pragma unroll
-  for (int e = 0; e < kItems; ++e) key[e] = ok[e] ? ordered_key(v[e]) : 0u;
+  for (int e = 0; e < kItems; ++e) v[e] = row[first + e * kThreads < n ? first + e * kThreads : 0];
 }
 
 // Where rank k_rem falls in a histogram of 2048 bins, walking from the top bin down: the bin, its population, and
@@ -257,10 +218,9 @@ __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ 
   __shared__ uint32_t n_above, n_cand;             // PASS 2: this workgroup's scores above / sharing the prefix
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
-  const int64_t first = (int64_t)blockIdx.x * kTile * sub + (int64_t)threadIdx.x * kItems;
-  uint32_t key[kItems];
-  bool ok[kItems];
-  load_keys(row, n, first, key, ok);
+  const int64_t first0 = (int64_t)blockIdx.x * kTile * sub + threadIdx.x;
+  float v[kItems];
+  load_scores(row, n, first0, v);
   for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
   if (threadIdx.x == 0) {
     n_above = 0u;
@@ -272,7 +232,15 @@ __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ 
   uint16_t* cand = (uint16_t*)(w + TopkLayout::blk + 2 * nblk) + (int64_t)blockIdx.x * kTile * sub;
   uint32_t above = 0;
   for (int st = 0; st < sub; ++st) {               // `sub` tiles of kTile scores, one histogram
-    if (st > 0) load_keys(row, n, first + (int64_t)st * kTile, key, ok);
+    const int64_t first = first0 + (int64_t)st * kTile;
+    uint32_t key[kItems];
+    bool ok[kItems];
+#pragma unroll
+    for (int e = 0; e < kItems; ++e) {
+      ok[e] = first + e * kThreads < n;
+      key[e] = ok[e] ? ordered_key(v[e]) : 0u;
+    }
+    if (st + 1 < sub) load_scores(row, n, first + kTile, v);    // the next tile's, during this one's histogram
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
       if (PASS == 0) {
@@ -299,24 +267,39 @@ __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ 
   }
 }
 
+// A wave owns consecutive scores, a lane every 64th of them, so that two ballots per 64 scores give every selected one its place
+// and the waves meet once, whatever SUB (the tiles of a workgroup) is.  What bounds it: two round trips, the prefix resolution, a barrier.
+// With a block scan per tile and consecutive scores to a lane it took 11.9 us for sixteen rows of 260k scores (SUB 6), 9.1 now, and
+// 4.2 / 4.2 for one row; a call 34.9 -> 31.6 (the histogram passes, a lane every 512th score and the next tile requested
+// early, give 1.0 of it), 64 rows of 100k 49.9 -> 45.7.
+template <int SUB>
 __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__ score, int64_t n, int64_t score_bs,
                                                        uint32_t* __restrict__ ws, int64_t row_words, int nblk,
                                                        int64_t base, int32_t* __restrict__ idx, int64_t idx_bs,
-                                                       uint32_t k, int sub) {
-  __shared__ uint32_t wave_sums[2 * kThreads / 64];
+                                                       uint32_t k) {
+  constexpr int kW = kThreads / 64, kMine = kItems * SUB;
+  __shared__ uint32_t wave_sums[kW];
   __shared__ uint32_t result[3];
+  __shared__ uint32_t before[2][kW], mine[2][kW];        // selected / equal to T: in earlier workgroups, in this one's waves
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
   int32_t* out = idx + (int64_t)blockIdx.y * idx_bs;
-  const int64_t first0 = (int64_t)blockIdx.x * kTile * sub + (int64_t)threadIdx.x * kItems;
-  uint32_t key[kItems];
-  bool ok[kItems];
-  load_keys(row, n, first0, key, ok);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t first = (int64_t)blockIdx.x * kTile * SUB + wave * (64 * kMine) + lane;
+  const int left = (int)(n - first < 64 * kMine ? n - first : 64 * kMine);   // 64 * e < left: the lane has an e-th score
+  uint32_t key[kMine];
+  {
+    float v[kMine];                                      // unconditional loads: a position past the end reads score 0 instead
+#pragma unroll
+    for (int e = 0; e < kMine; ++e) v[e] = row[64 * e < left ? first + 64 * e : 0];
+#pragma unroll
+    for (int e = 0; e < kMine; ++e) key[e] = ordered_key(v[e]);
+  }
   // What the third histogram pass left about the first workgroup this thread looks at: requested
   // before T is resolved, so that the two round trips overlap.
   constexpr int kPeek = 4;
   const uint16_t* cand_all = (const uint16_t*)(w + TopkLayout::blk + 2 * nblk);
-  const int64_t cap = (int64_t)kTile * sub;
+  constexpr int64_t cap = (int64_t)kTile * SUB;
   uint32_t c0 = 0, above0 = 0, peek[kPeek];
 #pragma unroll
   for (int j = 0; j < kPeek; ++j) peek[j] = 0u;
@@ -355,34 +338,42 @@ __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__
       my_eq += dgt == t_digit ? 1u : 0u;
     }
   }
-  uint32_t off_gt, off_eq, unused_a, unused_b;
-  block_excl_scan2<kThreads>(my_gt, my_eq, &unused_a, &unused_b, &off_gt, &off_eq, wave_sums);
-  for (int st = 0; st < sub; ++st) {                     // tiles in position order; the offsets run on
-    const int64_t first = first0 + (int64_t)st * kTile;
-    if (st > 0) load_keys(row, n, first, key, ok);
-    uint32_t gt = 0, eq = 0;
+  my_gt = wave_incl_scan(my_gt);                         // lane 63 holds the wave's total
+  my_eq = wave_incl_scan(my_eq);
+  uint32_t gt = 0, eq = 0;                               // of the wave
 #pragma unroll
-    for (int e = 0; e < kItems; ++e) {
-      gt += (ok[e] && key[e] > T) ? 1u : 0u;
-      eq += (ok[e] && key[e] == T) ? 1u : 0u;
-    }
-    uint32_t tot_g, tot_e, g_before, e_before;
-    block_excl_scan2<kThreads>(gt, eq, &g_before, &e_before, &tot_g, &tot_e, wave_sums);
-    g_before += off_gt;
-    e_before += off_eq;
+  for (int e = 0; e < kMine; ++e) {
+    const bool ok = 64 * e < left;
+    gt += (uint32_t)__popcll(__ballot(ok && key[e] > T));
+    eq += (uint32_t)__popcll(__ballot(ok && key[e] == T));
+  }
+  if (lane == 63) {
+    before[0][wave] = my_gt;
+    before[1][wave] = my_eq;
+    mine[0][wave] = gt;
+    mine[1][wave] = eq;
+  }
+  __syncthreads();
+  uint32_t g0 = 0, e0 = 0;
 #pragma unroll
-    for (int e = 0; e < kItems; ++e) {
-      if (!ok[e]) continue;
-      const bool is_gt = key[e] > T, is_eq = key[e] == T;
-      if (is_gt || (is_eq && e_before < need)) {
-        const uint32_t slot = g_before + (e_before < need ? e_before : need);
-        if (slot < k) out[slot] = (int32_t)(base + first + e);
-      }
-      g_before += is_gt ? 1u : 0u;
-      e_before += is_eq ? 1u : 0u;
+  for (int i = 0; i < kW; ++i) {
+    g0 += before[0][i] + (i < wave ? mine[0][i] : 0u);
+    e0 += before[1][i] + (i < wave ? mine[1][i] : 0u);
+  }
+  if (gt + eq == 0u) return;                             // the same in every lane
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int e = 0; e < kMine; ++e) {
+    const bool ok = 64 * e < left;
+    const bool is_gt = ok && key[e] > T, is_eq = ok && key[e] == T;
+    const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
+    const uint32_t gb = g0 + (uint32_t)__popcll(mg & below), eb = e0 + (uint32_t)__popcll(me & below);
+    if (is_gt || (is_eq && eb < need)) {
+      const uint32_t slot = gb + (eb < need ? eb : need);
+      if (slot < k) out[slot] = (int32_t)(base + first + 64 * e);
     }
-    off_gt += tot_g;
-    off_eq += tot_e;
+    g0 += (uint32_t)__popcll(mg);
+    e0 += (uint32_t)__popcll(me);
   }
 }
 
@@ -591,7 +582,15 @@ int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx
   }
   topk_hist<1><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
   topk_hist<2><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
-  topk_write<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, base, idx, idx_bs, (uint32_t)k, sub);
+  const auto write = sub == 1   ? topk_write<1>
+                     : sub == 2 ? topk_write<2>
+                     : sub == 3 ? topk_write<3>
+                     : sub == 4 ? topk_write<4>
+                     : sub == 5 ? topk_write<5>
+                     : sub == 6 ? topk_write<6>
+                     : sub == 7 ? topk_write<7>
+                                : topk_write<8>;
+  write<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, base, idx, idx_bs, (uint32_t)k);
   ESA_LAUNCH_CHECK("topk");
   return ESA_OK;
 }

@@ -92,6 +92,23 @@ def test_select_topk_many_rows_several_tiles_per_workgroup(esa, B, n, k):
         assert np.array_equal(got[b], orc.select_topk(s[b].astype(np.float64), k, base=11)), b
 
 
+@pytest.mark.parametrize("sub", [1, 2, 3, 4, 5, 6, 7, 8, 10])
+def test_select_topk_for_every_number_of_tiles_per_workgroup(esa, sub):
+    """Nine to ten tiles of 1024 scores in rows of a ragged length; 768 workgroups in all decide on the tiles of each (at most 8).
+    Exact: ties by position, also across waves and workgroups."""
+    n = 9 * 1024 + (1 if sub % 2 else 1023)
+    B = 768 * sub // 10
+    say(f"topk tiles per workgroup {sub}: batch={B} n={n}")
+    rng = np.random.default_rng(sub)
+    kinds = ("normal", "ties", "importance", "constant")
+    few = [_scores(rng, n, kd) for kd in kinds]
+    s = np.stack([np.roll(few[b % 4], 37 * b) for b in range(B)])
+    for k in (1, 700, n - 1):
+        got = esa.esa_select_topk(torch.from_numpy(s).cuda(), k, base=5).cpu().numpy()
+        for b in range(0, B, 1 if k == 700 else 17):
+            assert np.array_equal(got[b], orc.select_topk(s[b].astype(np.float64), k, base=5)), (b, k)
+
+
 # ------------------------------------------------------------------------------------------ gather
 @pytest.mark.parametrize("dtype,h_kv,d,pad", [("f32", 2, 64, 0), ("bf16", 8, 128, 0), ("bf16", 2, 64, 24),
                                               ("f32", 1, 32, 5), ("bf16", 3, 32, 1)])
