@@ -72,6 +72,26 @@ __device__ __forceinline__ void bin_add(uint32_t* h, bool active, uint32_t bin) 
   if (active) atomicAdd(&h[bin], 1u);
 }
 
+// A first histogram in LDS of which every fourth lane has a copy of its own, [kRadixBins][kLaneCopies], 16-byte aligned: the scores of
+// a row crowd into some five bins, and lanes of one instruction that add to one address are served one after the other.  A
+// sixteenth of a wave in turn costs less than two ballots and what folding the leader's bin leaves: score_finish of sixteen rows of 260k
+// scores 13.8 -> 10.8 us (13.0 with both), of four rows of 100k 6.1 -> 5.6, of one row the same (four times the words to clear).
+constexpr int kLaneCopies = 4;
+__device__ __forceinline__ void lane_copies_clear(uint32_t* h, int tid, int n_threads) {
+  for (int i = tid; i < kRadixBins; i += n_threads) ((uint4*)h)[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+__device__ __forceinline__ void lane_copies_add(uint32_t* h, bool active, uint32_t bin, int lane) {
+  if (active) atomicAdd(&h[bin * kLaneCopies + (lane & (kLaneCopies - 1))], 1u);
+}
+__device__ __forceinline__ void lane_copies_flush(uint32_t* __restrict__ gh, const uint32_t* h, int wg, int tid, int n_threads) {
+  uint32_t* g = gh + (wg % kHistReplicas) * kRadixBins;
+  for (int i = tid; i < kRadixBins; i += n_threads) {
+    const uint4 c = ((const uint4*)h)[i];
+    const uint32_t sum = c.x + c.y + c.z + c.w;
+    if (sum) atomicAdd(&g[i], sum);
+  }
+}
+
 // A workgroup's finished LDS histogram h, added to its copy of one pass's global histogram gh ([kHistReplicas][kRadixBins]).
 __device__ __forceinline__ void hist_flush(uint32_t* __restrict__ gh, const uint32_t* h, int wg, int tid, int n_threads) {
   uint32_t* g = gh + (wg % kHistReplicas) * kRadixBins;

@@ -856,7 +856,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
   __shared__ float mu[SPLIT == 1 ? kFewQueries : kFinishMaxQueries];
   __shared__ float red[256];
   __shared__ float tile[SPLIT == 1 ? kTok + 2 * kTailMaxEps : kTok];
-  __shared__ uint32_t digit_hist[kRadixBins];
+  __shared__ __attribute__((aligned(16))) uint32_t digit_hist[(SPLIT == 1 ? kLaneCopies : 1) * kRadixBins];
   const int b = __builtin_amdgcn_workgroup_id_y(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
   const int lane = tid & 63, wave = tid >> 6;
   const float* s = S + (int64_t)b * s_bs;
@@ -887,8 +887,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
       for (int u = 0; u < 4; ++u) v[u] = pt[j0 + u * 256 < n_part ? j0 + u * 256 : j0];
       m = fmaxf(fmaxf(m, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
     }
-    if (first_hist)
-      for (int i = tid; i < kRadixBins; i += 256) digit_hist[i] = 0u;
+    if (first_hist) lane_copies_clear(digit_hist, tid, 256);
     m = wave_max(m);
     if (lane == 0) red[wave] = m;
     __syncthreads();
@@ -906,8 +905,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
     }
     m = lanes_max16(m);
     if ((tid & 15) == 0) red[tid >> 4] = m;
-    if (first_hist)
-      for (int i = tid; i < kRadixBins; i += 256) digit_hist[i] = 0u;
+    if (first_hist) lane_copies_clear(digit_hist, tid, 256);
     __syncthreads();
     if (tid < l_c) {
       const int rows = 16 / lc2;
@@ -976,7 +974,7 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
         float v = f[u];
         if (POOL) v = m < n ? pooled(m, 256 * u + tid + eps, tile[256 * u + tid + eps]) : 0.f;
         if (m < n) score[(int64_t)b * score_bs + m] = v;
-        if (first_hist) hist_add(digit_hist, m < n, score_digit(ordered_key(v)));
+        if (first_hist) lane_copies_add(digit_hist, m < n, score_digit(ordered_key(v)), lane);
       }
     }
   } else {
@@ -1001,7 +999,11 @@ __global__ __launch_bounds__(256) void score_finish(const float* __restrict__ S,
   }
   if (first_hist) {
     __syncthreads();
-    hist_flush(first_hist + (int64_t)b * first_hist_bs, digit_hist, blk, tid, 256);
+    uint32_t* gh = first_hist + (int64_t)b * first_hist_bs;
+    if (SPLIT == 1)
+      lane_copies_flush(gh, digit_hist, blk, tid, 256);
+    else
+      hist_flush(gh, digit_hist, blk, tid, 256);
   }
 }
 

@@ -109,6 +109,25 @@ def test_select_topk_for_every_number_of_tiles_per_workgroup(esa, sub):
             assert np.array_equal(got[b], orc.select_topk(s[b].astype(np.float64), k, base=5)), (b, k)
 
 
+@pytest.mark.parametrize("B,l_c,eps", [(1, 1, 0), (200, 1, 0), (200, 3, 2), (420, 1, 5)])
+def test_first_histogram_of_crowded_scores(esa, B, l_c, eps):
+    """Scores of two values, or all equal, in the call whose score kernel builds the first histogram: as many lanes of a wave
+    in one bin as there are.  Exact, against the selection from the scores that the call returns."""
+    n = 9 * 1024 + 77
+    say(f"first histogram of crowded scores: batch={B} l_c={l_c} eps={eps}")
+    g = torch.Generator(device="cuda").manual_seed(B + l_c)
+    kc = torch.zeros((B, n, 64), dtype=torch.bfloat16, device="cuda")
+    kc[..., 0] = torch.where(torch.rand((B, n), generator=g, device="cuda") < 0.01, 2.0, 1.0).to(torch.bfloat16)
+    for scale in (0.0, 1.0):
+        q = torch.full((B, l_c, 64), scale, dtype=torch.bfloat16, device="cuda")
+        score, idx, _, _ = esa.esa_score_select_gather(q, kc, 0, n, 1500, eps=eps)
+        s = score.cpu().numpy()
+        F = scale * (kc[..., 0].double().cpu().numpy() - 2.0)
+        for b in range(0, B, 13):
+            assert np.array_equal(s[b], orc.proximity(F[b], eps) if eps else F[b]), b       # small integers: exact
+            assert np.array_equal(idx[b].cpu().numpy(), orc.select_topk(s[b].astype(np.float64), 1500, base=0)), b
+
+
 # ------------------------------------------------------------------------------------------ gather
 @pytest.mark.parametrize("dtype,h_kv,d,pad", [("f32", 2, 64, 0), ("bf16", 8, 128, 0), ("bf16", 2, 64, 24),
                                               ("f32", 1, 32, 5), ("bf16", 3, 32, 1)])
