@@ -84,13 +84,6 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_s
   return base + incl - v;
 }
 
-__device__ __forceinline__ void load_scores(const float* row, int64_t n, int64_t first, float (&v)[kItems]) {
-  // unconditional loads (a position past the end reads score 0 instead): all are in flight together, and with
-  // the histogram loads that follow, rather than one round trip each behind a branch
-#pragma unroll
-  for (int e = 0; e < kItems; ++e) v[e] = row[first + e * kThreads < n ? first + e * kThreads : 0];
-}
-
 // Where rank k_rem falls in a histogram of 2048 bins, walking from the top bin down: the bin, its population, and
 // the rank inside it.  Thread t owns bins kBins - 1 - t * PER .. downwards, c[0] the highest.  Every thread of the
 // block gets the result.
@@ -207,20 +200,23 @@ __global__ void topk_init(uint32_t* ws, int64_t row_words) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kHistWords; i += gridDim.x * blockDim.x) w[i] = 0u;
 }
 
-// PASS 0: bits 31..21, PASS 1: bits 20..10, PASS 2: bits 9..0.
-template <int PASS>
+// PASS 0: bits 31..21, PASS 1: bits 20..10, PASS 2: bits 9..0.  SUB: tiles of a workgroup, all of whose scores are requested in front
+// of the prefix resolution (sixteen rows of 260k: 7.3 and 7.7 us a pass with a tile requested at a time, 6.6 and 7.6 now).
+template <int PASS, int SUB>
 __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ score, int64_t n, int64_t score_bs,
                                                       uint32_t* __restrict__ ws, int64_t row_words, int nblk,
-                                                      uint32_t k, int sub) {
+                                                      uint32_t k) {
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t wave_sums[kThreads / 64];
   __shared__ uint32_t result[3];
   __shared__ uint32_t n_above, n_cand;             // PASS 2: this workgroup's scores above / sharing the prefix
   const float* row = score + (int64_t)blockIdx.y * score_bs;
   uint32_t* w = ws + (int64_t)blockIdx.y * row_words;
-  const int64_t first0 = (int64_t)blockIdx.x * kTile * sub + threadIdx.x;
-  float v[kItems];
-  load_scores(row, n, first0, v);
+  constexpr int kMine = kItems * SUB;
+  const int64_t first = (int64_t)blockIdx.x * kTile * SUB + threadIdx.x;
+  float v[kMine];                                  // unconditional loads: a position past the end reads score 0 instead
+#pragma unroll
+  for (int e = 0; e < kMine; ++e) v[e] = row[first + e * kThreads < n ? first + e * kThreads : 0];
   for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0u;
   if (threadIdx.x == 0) {
     n_above = 0u;
@@ -229,30 +225,21 @@ __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ 
   uint32_t prefix, k_rem;
   resolve_prefix<PASS>(w, k, wave_sums, result, &prefix, &k_rem);
   __syncthreads();
-  uint16_t* cand = (uint16_t*)(w + TopkLayout::blk + 2 * nblk) + (int64_t)blockIdx.x * kTile * sub;
+  uint16_t* cand = (uint16_t*)(w + TopkLayout::blk + 2 * nblk) + (int64_t)blockIdx.x * kTile * SUB;
   uint32_t above = 0;
-  for (int st = 0; st < sub; ++st) {               // `sub` tiles of kTile scores, one histogram
-    const int64_t first = first0 + (int64_t)st * kTile;
-    uint32_t key[kItems];
-    bool ok[kItems];
 #pragma unroll
-    for (int e = 0; e < kItems; ++e) {
-      ok[e] = first + e * kThreads < n;
-      key[e] = ok[e] ? ordered_key(v[e]) : 0u;
-    }
-    if (st + 1 < sub) load_scores(row, n, first + kTile, v);    // the next tile's, during this one's histogram
-#pragma unroll
-    for (int e = 0; e < kItems; ++e) {
-      if (PASS == 0) {
-        hist_add(h, ok[e], score_digit(key[e]));
-      } else if (PASS == 1) {
-        hist_add(h, ok[e] && (key[e] >> 21) == (prefix >> 21), (key[e] >> 10) & 2047u);
-      } else {
-        const bool shares = ok[e] && (key[e] >> 10) == (prefix >> 10);
-        hist_add(h, shares, key[e] & 1023u);
-        above += (ok[e] && (key[e] >> 10) > (prefix >> 10)) ? 1u : 0u;
-        if (shares) cand[atomicAdd(&n_cand, 1u)] = (uint16_t)(key[e] & 1023u);   // order does not matter: they are counted
-      }
+  for (int e = 0; e < kMine; ++e) {
+    const bool ok = first + e * kThreads < n;
+    const uint32_t key = ordered_key(v[e]);
+    if (PASS == 0) {
+      hist_add(h, ok, score_digit(key));
+    } else if (PASS == 1) {
+      hist_add(h, ok && (key >> 21) == (prefix >> 21), (key >> 10) & 2047u);
+    } else {
+      const bool shares = ok && (key >> 10) == (prefix >> 10);
+      hist_add(h, shares, key & 1023u);
+      above += (ok && (key >> 10) > (prefix >> 10)) ? 1u : 0u;
+      if (shares) cand[atomicAdd(&n_cand, 1u)] = (uint16_t)(key & 1023u);   // order does not matter: they are counted
     }
   }
   if (PASS == 2) {
@@ -270,8 +257,7 @@ __global__ __launch_bounds__(kThreads) void topk_hist(const float* __restrict__ 
 // A wave owns consecutive scores, a lane every 64th of them, so that two ballots per 64 scores give every selected one its place
 // and the waves meet once, whatever SUB (the tiles of a workgroup) is.  What bounds it: two round trips, the prefix resolution, a barrier.
 // With a block scan per tile and consecutive scores to a lane it took 11.9 us for sixteen rows of 260k scores (SUB 6), 9.1 now, and
-// 4.2 / 4.2 for one row; a call 34.9 -> 31.6 (the histogram passes, a lane every 512th score and the next tile requested
-// early, give 1.0 of it), 64 rows of 100k 49.9 -> 45.7.
+// 4.2 / 4.2 for one row; with the histogram passes as they are now a call 34.9 -> 30.2, 64 rows of 100k 49.9 -> 45.0.
 template <int SUB>
 __global__ __launch_bounds__(kThreads) void topk_write(const float* __restrict__ score, int64_t n, int64_t score_bs,
                                                        uint32_t* __restrict__ ws, int64_t row_words, int nblk,
@@ -486,6 +472,17 @@ __global__ void topk_all(int64_t n, int64_t base, int32_t* idx, int64_t idx_bs) 
     out[i] = (int32_t)(base + i);
 }
 
+// The passes of long rows, with SUB tiles to a workgroup.
+template <int SUB>
+void launch_passes(const float* score, int64_t n, int64_t score_bs, uint32_t* w, int64_t row_words, dim3 grid, int64_t base,
+                   int32_t* idx, int64_t idx_bs, uint32_t k, bool first_hist_ready, hipStream_t st) {
+  const int nblk = (int)grid.x;
+  if (!first_hist_ready) topk_hist<0, SUB><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, k);
+  topk_hist<1, SUB><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, k);
+  topk_hist<2, SUB><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, k);
+  topk_write<SUB><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, base, idx, idx_bs, k);
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- library-owned scratch (no caller workspace)
@@ -576,21 +573,17 @@ int launch_topk(const float* score, int64_t n, int k, int64_t base, int32_t* idx
   const int64_t row_words = topk_row_stride_words(n, batch);
   uint32_t* w = (uint32_t*)ws;
   const dim3 grid(nblk, batch);
-  if (!first_hist_ready) {     // otherwise the score call has zeroed the histograms and filled the first one
-    topk_init<<<dim3(3 * kHistReplicas, batch), 1024, 0, st>>>(w, row_words);
-    topk_hist<0><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
-  }
-  topk_hist<1><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
-  topk_hist<2><<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, (uint32_t)k, sub);
-  const auto write = sub == 1   ? topk_write<1>
-                     : sub == 2 ? topk_write<2>
-                     : sub == 3 ? topk_write<3>
-                     : sub == 4 ? topk_write<4>
-                     : sub == 5 ? topk_write<5>
-                     : sub == 6 ? topk_write<6>
-                     : sub == 7 ? topk_write<7>
-                                : topk_write<8>;
-  write<<<grid, kThreads, 0, st>>>(score, n, score_bs, w, row_words, nblk, base, idx, idx_bs, (uint32_t)k);
+  // otherwise the score call has zeroed the histograms and filled the first one
+  if (!first_hist_ready) topk_init<<<dim3(3 * kHistReplicas, batch), 1024, 0, st>>>(w, row_words);
+  const auto passes = sub == 1   ? launch_passes<1>
+                      : sub == 2 ? launch_passes<2>
+                      : sub == 3 ? launch_passes<3>
+                      : sub == 4 ? launch_passes<4>
+                      : sub == 5 ? launch_passes<5>
+                      : sub == 6 ? launch_passes<6>
+                      : sub == 7 ? launch_passes<7>
+                                 : launch_passes<8>;
+  passes(score, n, score_bs, w, row_words, grid, base, idx, idx_bs, (uint32_t)k, first_hist_ready, st);
   ESA_LAUNCH_CHECK("topk");
   return ESA_OK;
 }
