@@ -128,6 +128,10 @@ __device__ __forceinline__ void turn_pairs(uint32_t& a, uint32_t& b, const f32x4
   b = pack_bf16x2(rb[0], rb[1]);
 }
 
+// Where a tile's turns begin in the table.  64 bits: a window of 2^28 keys of head size 128 has a table of 4 GB.
+constexpr uint64_t turn_offset(uint32_t tile, int turn_bytes) { return (uint64_t)(32 + (uint64_t)tile) * turn_bytes; }
+static_assert(turn_offset((1u << 31) / kKT, 512) == (((1ull << 31) / kKT) + 32) * 512, "the last tile of the longest window");
+
 // TURNED: the first view's keys are un-encoded; key j of it is turned by j positions in registers, between its fragments' arrival
 // and the first product, and rounded to bf16 as an encoded row is.  A key and its half's partner are in one lane (fragments ks and
 // ks + kKS / 2), whose turn by the key's number in its tile stays in registers, and the tile's own turn comes with the tile.
@@ -220,7 +224,7 @@ void attend_split(SplitArgs a) {
   };
   auto load_turn = [&](uint32_t tile) {            // one instruction; the second view's tiles have none of their own and take the first
     if constexpr (TURNED)
-      __builtin_amdgcn_global_load_lds((global_void*)((const char*)a.turns + (32 + (second ? 0 : tile)) * (uint32_t)kTurnBytes + (uint32_t)(lane * 16 % kTurnBytes)),
+      __builtin_amdgcn_global_load_lds((global_void*)((const char*)a.turns + turn_offset(second ? 0 : tile, kTurnBytes) + lane * 16 % kTurnBytes),
                                        (lds_void*)turn_st[wave], 16, 0, 0);
   };
   auto load_tile = [&](const int32_t (&mine)[kLoads], bool values) {
