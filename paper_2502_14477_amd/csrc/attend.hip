@@ -318,7 +318,7 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   // A few tokens: the attention kernel turns the local keys itself, by a table.
   const bool turned = split && attend_split_turns_keys(l_c, h, h_kv, d, dtype, batch);
   if (turned) jobs[2] = RopeJob{nullptr, k_loc, 32 + (rows + 31) / 32, 0, 0, 0, 0, 0.0, 0.0, 1, kRopeTurns};
-  int rc = launch_rope_jobs(jobs, tiled ? 3 : 4, d, base, dtype, batch, st, tiled);
+  int rc = launch_rope_jobs(jobs, tiled ? 3 : 4, d, base, dtype, batch, st);
   if (rc != ESA_OK) return rc;
   const CacheRef local = turned ? CacheRef{k_rows, v_rows, tok_stride, tok_stride, cache_bs, cache_bs}
                                 : CacheRef{k_loc, v_rows, kv_row, tok_stride, kvw_bs, cache_bs};

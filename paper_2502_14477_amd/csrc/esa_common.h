@@ -175,8 +175,7 @@ struct RopeJob {
   int heads, rotate;
 };
 bool rope_head_size_ok(int d);
-// fp32_products: bf16 rows that nobody but the attention kernels reads (fp64 otherwise: an encoded row is the exact one rounded).
-int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dtype, int batch, hipStream_t st, bool fp32_products = false);
+int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dtype, int batch, hipStream_t st);
 
 size_t attend_reencoded_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t l_l);
 int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, const void* k_cache, const void* v_cache,

@@ -3,13 +3,16 @@
 // position 0, which is the identity).  Rotate-half pairing: element i of a head's first half and
 // element i of its second half turn by the angle pos * base^(-2i/d).
 //
-// The angles are fp64.  esa_rope's products are, too, and round once into the storage type, so a row encoded there
-// equals the fp64 definition rounded to storage; bf16 rows for the attention kernels alone take fp32 products.
-// What bounds it is that arithmetic as much as the memory traffic (re-encoded decode, batch 8: 16392 key rows of 2 KB, 67 MB): with a power, a sine and a cosine per row and frequency,
+// The arithmetic is fp64 end to end and rounds once into the storage type, so a row encoded here
+// equals the fp64 definition rounded to storage.  What bounds it is that arithmetic as much as the memory traffic
+// (re-encoded decode, batch 8: 16392 key rows of 2 KB, 67 MB): with a power, a sine and a cosine per row and frequency,
 // their table read again for every head, and a rounding from fp64 to bf16 in 64-bit integer steps it took 31.5 us.  Now
 // the frequencies and the turn from one row to the next come from the host (fp64 too, kept per thread for a base and
 // head size), a thread evaluates sine and cosine for the first of its few consecutive rows and turns the others by complex
 // multiplication (a handful of errors of 2^-53), and the heads of a row share the pairs held in registers.
+// fp32 products of the same angles take 9.2 us instead of 13.6 (512 queries twice and 4608 keys, 31 MB), but put an element of every
+// hundredth row on the other side of a rounding.  Checked against their error bound and done again in fp64 where it leaves the rounding
+// open (one element in a thousand, so two instructions of a wave in three), they take what fp64 takes.
 #include <cmath>
 
 #include "esa_common.h"
@@ -41,22 +44,20 @@ __device__ __forceinline__ float narrow_for_bf16(double v) {
   return f;
 }
 
-template <typename R> __device__ __forceinline__ R load_as(float v) { return (R)v; }
-template <typename R> __device__ __forceinline__ R load_as(bf16_t v) { return (R)bf16_to_f32(v); }
+template <typename T> __device__ __forceinline__ double load_f64(T v);
+template <> __device__ __forceinline__ double load_f64<float>(float v) { return (double)v; }
+template <> __device__ __forceinline__ double load_f64<bf16_t>(bf16_t v) { return (double)bf16_to_f32(v); }
 
 // Two results rounded into storage.
-__device__ __forceinline__ void store_two(float* p, double a, double b) {
+template <typename T> __device__ __forceinline__ void store_f64(T* p, double a, double b);
+template <> __device__ __forceinline__ void store_f64<float>(float* p, double a, double b) {
   p[0] = (float)a;
   p[1] = (float)b;
 }
-__device__ __forceinline__ void store_two(bf16_t* p, float a, float b) {
-  const f32x2 f = {a, b};
+template <> __device__ __forceinline__ void store_f64<bf16_t>(bf16_t* p, double a, double b) {
+  const f32x2 f = {narrow_for_bf16(a), narrow_for_bf16(b)};
   *(uint32_t*)p = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
 }
-__device__ __forceinline__ void store_two(bf16_t* p, double a, double b) { store_two(p, narrow_for_bf16(a), narrow_for_bf16(b)); }
-// a x - b y, the product b y rounded on the way
-__device__ __forceinline__ double turned(double a, double x, double b, double y) { return a * x - b * y; }
-__device__ __forceinline__ float turned(float a, float x, float b, float y) { return __builtin_fmaf(a, x, -(b * y)); }
 
 constexpr int kRopeRows = 16;     // most rows of a workgroup
 constexpr int kAhead = 4;         // heads whose loads a thread has in flight
@@ -82,14 +83,9 @@ __device__ __forceinline__ void write_turns(float2* out, int64_t row, int i, int
 // grid (groups of rows, jobs, batch); 256 threads.  The rows' angles go through LDS once; then a thread owns VEC
 // consecutive pairs of a row (VEC elements = 16 bytes per access when VEC > 1; VEC == 1 serves unaligned rows) for all of
 // the row's heads, or for every hs-th of them where there are too few rows to go round.
-// R: the products' type.  fp32 (bf16 rows that only the attention kernels read): cosine and sine are rounded once from fp64 and an
-// element once more before it goes into storage, by 2^-24 of its size each, where storage rounds by 2^-9.  512 queries twice and 4608 keys,
-// 31 MB: 13.6 -> 9.2 us; re-encoded steps of 40 to 512 tokens 60.7 -> 57.6, 78.0 -> 74.1, 76.3 -> 72.7, 139.5 -> 134.5.  Outputs' distance from
-// the 64-bit result, six shapes of six seeds: 3.12316 / 3.12315e-3.
-template <typename T, int VEC, typename R = double>
+template <typename T, int VEC>
 __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int d, int budget) {
-  extern __shared__ double cs_lds[];
-  R* cs = (R*)cs_lds;                                  // [kRopeRows][d/2] cosines, then sines
+  extern __shared__ double cs[];                       // [kRopeRows][d/2] cosines, then sines
   const RopeJob jb = jobs.j[blockIdx.y];
   const int wg_rows = jb.rotate == kRopeTurns ? 512 / d : rows_of(jb.heads, budget);
   const int64_t row0 = (int64_t)blockIdx.x * wg_rows;
@@ -110,7 +106,7 @@ __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int
       *(vec_t*)(o + (int64_t)(e / n) * jb.ldo + e % n * VEC) = *(const vec_t*)(x + (int64_t)(e / n) * jb.ldx + e % n * VEC);
     return;
   }
-  R* sn = cs + kRopeRows * half;
+  double* sn = cs + kRopeRows * half;
   {
     const int groups = 256 / half, i = tid % half, g = tid / half;        // half is a power of two, at most kMaxHalf
     const int per = groups < wg_rows ? wg_rows / groups : 1;              // consecutive rows of a thread
@@ -122,8 +118,8 @@ __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int
       const bool turning = jb.pos_step != 0.0;
       const double dc = turning ? turns.c[i] : 1.0, ds = turning ? turns.s[i] : 0.0;
       for (int r = first; r < first + per && r < n_rows; ++r) {
-        cs[r * half + i] = (R)c;
-        sn[r * half + i] = (R)s;
+        cs[r * half + i] = c;
+        sn[r * half + i] = s;
         const double c2 = c * dc - s * ds;
         s = s * dc + c * ds;
         c = c2;
@@ -136,7 +132,7 @@ __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int
   while (hs < jb.heads && n_rows * n_vecs * hs < 256) hs *= 2;
   for (int e = tid; e < n_rows * n_vecs * hs; e += 256) {
     const int i = e % n_vecs * VEC, r = e / n_vecs % n_rows, h0 = e / (n_vecs * n_rows);
-    R c[VEC], s[VEC];
+    double c[VEC], s[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
       c[k] = cs[r * half + i + k];
@@ -160,16 +156,16 @@ __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int
           vec_t ra, rb;
 #pragma unroll
           for (int k = 0; k < VEC; k += 2) {
-            const R a0 = load_as<R>((T)a[u][k]), a1 = load_as<R>((T)a[u][k + 1]), b0 = load_as<R>((T)b[u][k]), b1 = load_as<R>((T)b[u][k + 1]);
-            store_two((T*)&ra + k, turned(a0, c[k], b0, s[k]), turned(a1, c[k + 1], b1, s[k + 1]));
-            store_two((T*)&rb + k, turned(b0, c[k], -a0, s[k]), turned(b1, c[k + 1], -a1, s[k + 1]));
+            const double a0 = load_f64<T>(a[u][k]), a1 = load_f64<T>(a[u][k + 1]), b0 = load_f64<T>(b[u][k]), b1 = load_f64<T>(b[u][k + 1]);
+            store_f64<T>((T*)&ra + k, a0 * c[k] - b0 * s[k], a1 * c[k + 1] - b1 * s[k + 1]);
+            store_f64<T>((T*)&rb + k, b0 * c[k] + a0 * s[k], b1 * c[k + 1] + a1 * s[k + 1]);
           }
           *(vec_t*)(orow + h * d) = ra;
           *(vec_t*)(orow + h * d + half) = rb;
         } else {
-          const R a0 = load_as<R>((T)a[u][0]), b0 = load_as<R>((T)b[u][0]);
+          const double a0 = load_f64<T>(a[u][0]), b0 = load_f64<T>(b[u][0]);
           __attribute__((aligned(8))) T both[2];
-          store_two(both, turned(a0, c[0], b0, s[0]), turned(b0, c[0], -a0, s[0]));
+          store_f64<T>(both, a0 * c[0] - b0 * s[0], b0 * c[0] + a0 * s[0]);
           orow[h * d] = both[0];
           orow[h * d + half] = both[1];
         }
@@ -202,7 +198,7 @@ const Turns& turns_for(double base, int d, double step) {
 
 bool rope_head_size_ok(int d) { return d >= 2 && d <= 256 && (d & (d - 1)) == 0; }
 
-int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dtype, int batch, hipStream_t st, bool fp32_products) {
+int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dtype, int batch, hipStream_t st) {
   RopeJobs js;
   double step = 0.0;      // the jobs' common step (a job may also stand still)
   int64_t rows = 0;
@@ -250,9 +246,7 @@ int launch_rope_jobs(const RopeJob* jobs, int n_jobs, int d, double base, int dt
            j.x_bs % vec == 0 && j.out_bs % vec == 0;
   }
   if (dtype == ESA_BF16) {
-    if (wide && fp32_products)
-      rope_rows<bf16_t, 8, float><<<grid, 256, lds / 2, st>>>(js, turns, d, budget);
-    else if (wide)
+    if (wide)
       rope_rows<bf16_t, 8><<<grid, 256, lds, st>>>(js, turns, d, budget);
     else
       rope_rows<bf16_t, 1><<<grid, 256, lds, st>>>(js, turns, d, budget);

@@ -403,6 +403,41 @@ def test_reencoded_attention_of_few_tokens_turns_the_local_keys(esa, B, H, H_kv,
         assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 2e-2, b
 
 
+# Section 3.2's rows are encoded in 64 bits and rounded once.  Every row of queries is made from one local key, each tile of the window
+# having its turn, and that key takes the whole softmax: lse is its logit, so a single element of it or of the query that is rounded to the
+# other bf16 number shows (7e-4 in the median; products and sums of fp32 err by 1e-5), and a tile encoded with another one's positions gives
+# another key's value.
+@pytest.mark.parametrize("B,H,H_kv,d,l_C,l_L", [(1, 32, 8, 128, 64, 2048), (1, 16, 8, 64, 100, 1000), (2, 8, 8, 128, 130, 1500)])
+def test_reencoded_rows_are_the_exact_ones_rounded_once(esa, B, H, H_kv, d, l_C, l_L):
+    say(f"re-encoded rows rounded once B={B} H={H} H_kv={H_kv} d={d} l_C={l_C} l_L={l_L}")
+    base, w, l_I, n_sel = 5e5, 4096.0, 64, 256
+    t0, scale, gain = l_I + 300 + l_L, 1.0 / np.sqrt(d), 24.0 / np.sqrt(d)
+    rng = np.random.default_rng(d + l_C)
+    bf16 = lambda x: orc.round_to_storage(x, "bf16")
+    K, V = (bf16(rng.standard_normal((B, t0 + l_C, H_kv, d))) for _ in range(2))
+    sel = (l_I + np.sort(rng.permutation(300)[:n_sel])).astype(np.int32)
+    n_tiles, group = -(-l_L // 32), H // H_kv
+    q = np.zeros((B, l_C, H, d))
+    for b in range(B):
+        for c in range(l_C):
+            for h in range(H):
+                tile = (2 * (c * group + h % group) + b * H_kv + h // group) % n_tiles
+                j = min(32 * tile + int(rng.integers(32)), l_L - 1)
+                q[b, c, h] = gain * orc.rope(K[b, t0 - l_L + j, h // group][None, None], [j - (l_L + c)], base)[0, 0]
+    q = bf16(q)
+    qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), f64_to_dev(K, "bf16"), f64_to_dev(V, "bf16"), torch.from_numpy(np.tile(sel, (B, 1))).cuda()
+    ks, vs = esa.esa_gather_kv(Kd, Vd, idx)
+    O, lse = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, w, base, return_lse=True)
+    for b in range(B):
+        K_l = np.zeros_like(K[b])
+        K_l[t0 - l_L:] = bf16(orc.rope(K[b, t0 - l_L:], np.arange(l_L + l_C), base))
+        q_l, q_g = bf16(orc.rope(q[b], l_L + np.arange(l_C), base)), bf16(orc.rope(q[b], np.full(l_C, w), base))
+        want, want_lse = orc.attend_two_encodings(q_l, q_g, K_l, K[b], V[b], t0, l_I, l_L, sel, scale)
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 5e-5, b
+        # half a unit in the last place from the rounding of the output, half from that of a probability
+        assert np.all(np.abs(to_f64(O[b]) - want) <= bf16_ulp(want) + 1e-4), b
+
+
 # Gathered rows: segment boundaries at a tile's edge, one key beside it, two of them inside one tile, no boundary but the sequence's
 # end; slices that end between.  The index-driven form takes the same keys in the same order.
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
