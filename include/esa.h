@@ -302,8 +302,8 @@ ESA_API int esa_rope(const void* x, int64_t n_tok, int heads, int d, int64_t ldx
  * position 0; the two groups of logits share one softmax (Algorithm 1's merge of the two partial
  * attentions).  The library encodes the chunk's queries twice and the local rows of the key cache
  * once into its workspace (esa_rope's arithmetic), then runs the local and the global part; a few
- * tokens' local keys are turned as they are read instead (bf16, at most 32 rows of queries to a KV
- * head: fp32 turns, rounded once as an encoded row is).
+ * tokens' local keys are turned as they are read instead where they are many (bf16, at most 32 rows of
+ * queries to a KV head, 8192 keys of all batch entries and KV heads or more: the same encoded rows).
  *   q, k_cache, k_sel   un-encoded; v_cache, v_sel, out, lse, sizes and strides as esa_attend
  *   w, rope_base        the global queries' position and the encoding's base
  *   workspace           esa_attend_reencoded_workspace_bytes(..., l_l) bytes, 256-byte aligned

@@ -259,18 +259,12 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
   return ESA_OK;
 }
 
-// The re-encoded copies of the local keys and values, or the table that stands for them.
-static size_t local_bytes(size_t kv_bytes, int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t n_loc) {
-  const size_t table = h % h_kv == 0 && attend_split_turns_keys(l_c, h, h_kv, d, dtype, batch) ? align_up(rope_turns_bytes(n_loc + l_c, d), 256) : 0;
-  return table > 2 * kv_bytes ? table : 2 * kv_bytes;
-}
-
 size_t attend_reencoded_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t l_l) {
   if (l_c <= 0 || h <= 0 || h_kv <= 0 || d <= 0 || batch <= 0 || l_l < 0) return 256;
   const size_t esz = (dtype == ESA_F32) ? 4 : 2;
   const size_t q_bytes = align_up((size_t)batch * l_c * h * d * esz, 256);
   const size_t kv_bytes = align_up((size_t)batch * (size_t)(l_l + l_c) * h_kv * d * esz, 256);
-  return align_up(attend_workspace_bytes(l_c, h, h_kv, d, dtype, batch), 256) + 2 * q_bytes + local_bytes(kv_bytes, l_c, h, h_kv, d, dtype, batch, l_l);
+  return align_up(attend_workspace_bytes(l_c, h, h_kv, d, dtype, batch), 256) + 2 * q_bytes + 2 * kv_bytes;
 }
 
 // Section 3.2 on un-encoded queries and keys.  The workspace holds, behind the attention workspace
@@ -291,7 +285,7 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   const size_t own = align_up(attend_workspace_bytes(l_c, h, h_kv, d, dtype, batch), 256);
   const size_t q_bytes = align_up((size_t)batch * l_c * h * d * esz, 256);
   const size_t kv_bytes = align_up((size_t)batch * (size_t)rows * h_kv * d * esz, 256);
-  const size_t need = own + 2 * q_bytes + local_bytes(kv_bytes, l_c, h, h_kv, d, dtype, batch, n_loc);
+  const size_t need = own + 2 * q_bytes + 2 * kv_bytes;      // (a table of turns is smaller than the rows that it stands for)
   if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend_reencoded: workspace needs %zu bytes", need);
   char* q_loc = (char*)ws + own;
   char* q_glob = q_loc + q_bytes;
@@ -316,8 +310,8 @@ int launch_attend_reencoded(const void* q, int l_c, int h, int h_kv, int d, cons
   jobs[3] = RopeJob{v_rows, v_loc, rows, tok_stride, kv_row, cache_bs, kvw_bs, 0.0, 0.0, h_kv, 0};   // their values
   const bool tiled = mfma || split;
   // A few tokens: the attention kernel turns the local keys itself, by a table.
-  const bool turned = split && attend_split_turns_keys(l_c, h, h_kv, d, dtype, batch);
-  if (turned) jobs[2] = RopeJob{nullptr, k_loc, 32 + (rows + 31) / 32, 0, 0, 0, 0, 0.0, 0.0, 1, kRopeTurns};
+  const bool turned = split && attend_split_turns_keys(l_c, h, h_kv, d, dtype, batch, rows);
+  if (turned) jobs[2] = RopeJob{nullptr, k_loc, rope_turn_rows(rows, d), 0, 0, 0, 0, 0.0, 0.0, 1, kRopeTurns};
   int rc = launch_rope_jobs(jobs, tiled ? 3 : 4, d, base, dtype, batch, st);
   if (rc != ESA_OK) return rc;
   const CacheRef local = turned ? CacheRef{k_rows, v_rows, tok_stride, tok_stride, cache_bs, cache_bs}

@@ -21,8 +21,8 @@ struct SplitCall {
   size_t ws_bytes;
   const void* turns = nullptr;    // not null: view a's keys are un-encoded and turned from position 0 on, by this table (kRopeTurns)
 };
-// Whether the kernel can turn the local keys itself: bf16, all rows in one workgroup, which then reads each key once.
-bool attend_split_turns_keys(int l_c, int h, int h_kv, int d, int dtype, int batch);
+// Whether the kernel turns the n_keys local keys itself: bf16, all rows in one workgroup, which then reads each key once.
+bool attend_split_turns_keys(int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t n_keys);
 // The slice counts and slots of the views are filled in by the launch.
 // One call over the whole key sequence (one view), or over Section 3.2's two parts (view a: the local keys, b: the
 // initial and selected ones; b may have no keys).

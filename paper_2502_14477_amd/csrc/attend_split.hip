@@ -25,6 +25,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) double f64x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -79,7 +80,7 @@ struct SplitArgs {
   PairGrid grid;
   float scale;                        // includes log2(e) for bf16
   int64_t out_bs, sel_bs_bytes;
-  const float* turns;                 // TURNED
+  const double* turns;                // TURNED
 };
 
 // Wait until at most N vector-memory operations are outstanding (the other counters are left alone).  The builtin, not
@@ -113,33 +114,21 @@ template <int N, typename X> __device__ __forceinline__ void arrived4(X& a, X& b
   asm volatile("s_waitcnt lgkmcnt(%c4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
 
-// Two pairs (of `a` and `b`, two bf16 numbers each) turned by the sum of two angles: cosine and sine of either pair in x and in y.
-__device__ __forceinline__ void turn_pairs(uint32_t& a, uint32_t& b, const f32x4 x, const f32x4 y) {
-  float ra[2], rb[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const float c = __builtin_fmaf(x[2 * e], y[2 * e], -(x[2 * e + 1] * y[2 * e + 1]));
-    const float s = __builtin_fmaf(x[2 * e + 1], y[2 * e], x[2 * e] * y[2 * e + 1]);
-    const float av = __uint_as_float(e ? a & 0xFFFF0000u : a << 16), bv = __uint_as_float(e ? b & 0xFFFF0000u : b << 16);
-    ra[e] = __builtin_fmaf(av, c, -(bv * s));
-    rb[e] = __builtin_fmaf(bv, c, av * s);
-  }
-  a = pack_bf16x2(ra[0], ra[1]);
-  b = pack_bf16x2(rb[0], rb[1]);
-}
+__device__ __forceinline__ void lds_write4(uint32_t at, uint32_t x) { asm volatile("ds_write_b32 %0, %1" : : "v"(at), "v"(x)); }
 
-// Where a tile's turns begin in the table.  64 bits: a window of 2^28 keys of head size 128 has a table of 4 GB.
-constexpr uint64_t turn_offset(uint32_t tile, int turn_bytes) { return (uint64_t)(32 + (uint64_t)tile) * turn_bytes; }
-static_assert(turn_offset((1u << 31) / kKT, 512) == (((1ull << 31) / kKT) + 32) * 512, "the last tile of the longest window");
+// TURNED: the first view's keys are un-encoded.  When a tile of them has arrived its wave turns it where it lies in LDS, key j by j
+// positions, in fp64 and rounded once: the keys are then those that esa_rope writes.  A lane has two neighbouring pairs of D / 8
+// consecutive keys (half a tile, a quarter with head size 64): it takes their first turn from the table, and the next key's from the
+// last two (cos(a + x) = 2 cos x cos a - cos(a - x)), whose error grows to some 2^-46 over sixteen keys.
+// Where a tile's turns begin in the table, which starts with the turn by one position.
+constexpr int kTurnBytes = 2048;                   // of a tile: 256 / D rows of D / 2 pairs of fp64 cosine and sine
+constexpr uint64_t turn_offset(uint32_t tile, int d) { return 8u * d + (uint64_t)tile * kTurnBytes; }
+static_assert(turn_offset((1u << 31) / kKT, 128) == 1024 + (((1ull << 31) / kKT) << 11), "the last tile of the longest window, beyond 32 bits");
 
-// TURNED: the first view's keys are un-encoded; key j of it is turned by j positions in registers, between its fragments' arrival
-// and the first product, and rounded to bf16 as an encoded row is.  A key and its half's partner are in one lane (fragments ks and
-// ks + kKS / 2), whose turn by the key's number in its tile stays in registers, and the tile's own turn comes with the tile.
-// The queries' fragments, which have no registers left, are read from LDS for every tile.
 // (A re-encoded copy of the local keys is a read, a write and another read of them, 67 MB more for eight sequences behind a window of
-// 2048.  Step, us, copied and turned here: that one at 64 thousand tokens 121.1 / 107.2, one sequence 45.4 / 43.5, eight of eight KV
-// heads at 30 thousand 85 / 73, four of five drafted tokens 75 / 70.  Distance from the 64-bit result, six shapes of six seeds: 2.8103 /
-// 2.8102e-3.)
+// 2048: step at 64 thousand tokens 129.4 us copied, 121.2 turned here.  What turning costs is 25 vector instructions a pair, 0.8 us a tile
+// and SIMD with the SIMDs busy, 1.5 us of a call that has a tile a wave.  In fp32, by products of two turns in registers, it cost
+// half of that (117.1), but put an element of every hundredth key on the other side of its rounding.)
 template <typename T, int D, int kWaves, bool TURNED = false>
 __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 || kWaves > kWavesOfTwo ? 1 : 2) __attribute__((amdgpu_waves_per_eu(D * sizeof(T) > 256 ? 1 : 2)))
 void attend_split(SplitArgs a) {
@@ -155,9 +144,7 @@ void attend_split(SplitArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char k_st[kWaves][kTileBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char v_st[kWaves][kTileBytes];
   __shared__ float ml[kWaves][kRows][2];
-  constexpr int kTurnBytes = D / 2 * 8;            // a tile's turns
-  __shared__ __attribute__((aligned(1024))) unsigned char turn_st[TURNED ? kWaves : 1][TURNED ? 1024 : 1];     // (repeated up to 1 KB)
-  __shared__ __attribute__((aligned(1024))) unsigned char q_st[TURNED ? kTileBytes : 1];                      // laid out as a tile of keys
+  __shared__ __attribute__((aligned(1024))) unsigned char turn_st[TURNED ? kWaves : 1][TURNED ? kTurnBytes : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -216,16 +203,18 @@ void attend_split(SplitArgs a) {
   };
   // The places of the rows this lane fetches a piece of, from the lanes that stand for their keys.
   auto spread = [&](int32_t place, int32_t (&mine)[kLoads]) {
-    int from = (int)st_row;
-    if constexpr (TURNED) asm volatile("" : "+v"(from));                    // (the lanes' numbers would be kept, and others spilled)
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) mine[i] = __shfl(place, kLoadRows * i + from, 64);
+    for (int i = 0; i < kLoads; ++i) mine[i] = __shfl(place, kLoadRows * i + (int)st_row, 64);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto load_turn = [&](uint32_t tile) {            // one instruction; the second view's tiles have none of their own and take the first
-    if constexpr (TURNED)
-      __builtin_amdgcn_global_load_lds((global_void*)((const char*)a.turns + turn_offset(second ? 0 : tile, kTurnBytes) + lane * 16 % kTurnBytes),
-                                       (lds_void*)turn_st[wave], 16, 0, 0);
+  constexpr int kTurnLoads = TURNED ? kTurnBytes / 1024 : 0;
+  auto load_turn = [&](uint32_t tile) {            // the second view's tiles have none of their own and take the first
+    if constexpr (TURNED) {
+      const char* src = (const char*)a.turns + turn_offset(second ? 0 : tile, D) + lane * 16;
+#pragma unroll
+      for (int i = 0; i < kTurnLoads; ++i)
+        __builtin_amdgcn_global_load_lds((global_void*)(src + i * 1024), (lds_void*)(turn_st[wave] + i * 1024), 16, 0, 0);
+    }
   };
   auto load_tile = [&](const int32_t (&mine)[kLoads], bool values) {
     unsigned char* dst = values ? v_st[wave] : k_st[wave];
@@ -245,40 +234,28 @@ void attend_split(SplitArgs a) {
   const bool has_tile = t < tile_end;
   int32_t next = 0;                                                         // index entry of the wave's next tile
   int32_t mine[kLoads];
-  u32x4 qf[TURNED ? 1 : kKS];
-  f32x4 within[TURNED ? 2 * kKS : 1];              // cosine, sine of two pairs each: the turn by this lane's key's number in the tile
-  if constexpr (TURNED) {                          // eight rows from each wave, which need four
-#pragma unroll
-    for (int i = 0; i < 8 / kLoadRows; ++i) {
-      const int wave_rows = 8 * (wave & 3), q_row = wave_rows + kLoadRows * i + (int)st_row, of_tile = rt * kRows + q_row < n_rows ? rt * kRows + q_row : n_rows - 1;
-      const int q_tok = a.group_log2 >= 0 ? of_tile >> a.group_log2 : of_tile / a.group;
-      const char* src = V.q + ((int64_t)b * V.q_bs + ((int64_t)q_tok * a.h + g * a.group + of_tile - q_tok * a.group) * D) * (int64_t)sizeof(T);
-      __builtin_amdgcn_global_load_lds((global_void*)(src + (st_slot ^ k_swizzle(q_row)) * 16), (lds_void*)(q_st + (wave_rows + kLoadRows * i) * kRowBytes), 16, 0, 0);
-    }
-  }
+  u32x4 qf[kKS];
+  double step[TURNED ? 4 : 1];                     // cosine and sine of the lane's two pairs' turn by one position
   if (has_tile) {
     const int32_t first = lookup(t);
-    if constexpr (!TURNED) {
-      const char* qp = V.q + ((int64_t)b * V.q_bs + ((int64_t)c * a.h + head) * D) * (int64_t)sizeof(T) + hi * 16;
+    const char* qp = V.q + ((int64_t)b * V.q_bs + ((int64_t)c * a.h + head) * D) * (int64_t)sizeof(T) + hi * 16;
 #pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) qf[ks] = *(const u32x4*)(qp + ks * 32);
-    }
+    for (int ks = 0; ks < kKS; ++ks) qf[ks] = *(const u32x4*)(qp + ks * 32);
     if (t + kWaves < tile_end) next = lookup(t + kWaves);
     if constexpr (TURNED) {
 #pragma unroll
-      for (int i = 0; i < 2 * kKS; ++i) within[i] = *(const f32x4*)(a.turns + (i * 64 + lane) * 4);
+      for (int i = 0; i < 4; ++i) step[i] = a.turns[lane % (D / 4) * 4 + i];
     }
     __builtin_amdgcn_sched_barrier(0);
     spread(place_of(t, first), mine);
     load_turn(t);
     load_tile(mine, false);
     load_tile(mine, true);
-  }
-  if constexpr (TURNED) {                          // the queries, of all waves; the tile may still be on its way
-    if (has_tile) wait_loads<2 * kLoads + 1>();
-    else wait_loads<0>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    if constexpr (TURNED) {                        // (a use that the compiler saw first in the loop it would put behind all loads)
+      wait_loads<kTurnLoads + 2 * kLoads>();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(step[i]));
+    }
   }
   f32x16 o[kMD];
 #pragma unroll
@@ -297,6 +274,54 @@ void attend_split(SplitArgs a) {
         v_at[md] = kBf16 ? v0 + ((4 * hi + tr_key) * D + ((md ^ v_swizzle(tr_key)) << 5) + tr_dim) * 2
                          : v0 + 4 * hi * kRowBytes + (32 * md + r) * 4;
     }
+    auto turn_keys = [&]() __attribute__((always_inline)) {
+      constexpr int kMine = D / 8;                                          // keys of a lane
+      const uint32_t block = lane / (D / 4), dword = lane % (D / 4);
+      const uint32_t first = (uint32_t)(uintptr_t)(lds_byte*)k_st[wave] + block * (kMine * kRowBytes) +
+                             (((dword >> 2) ^ (D == 64 ? (block & 1) << 2 : 0)) << 4) + (dword & 3) * 4;
+      auto place = [&](uint32_t key) { return (first ^ ((D == 128 ? key : key >> 1) << 4)) + key * kRowBytes; };   // upper half: ^ D
+      const uint32_t turn_at = (uint32_t)(uintptr_t)(lds_byte*)turn_st[wave] + lane * 32;
+      u32x4 turn[2];
+      asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(turn[0]), "=&v"(turn[1]) : "v"(turn_at));
+      double c[2], sn[2], c_before[2], sn_before[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        c[e] = __builtin_bit_cast(f64x2, turn[e])[0];
+        sn[e] = __builtin_bit_cast(f64x2, turn[e])[1];
+        c_before[e] = c[e] * step[2 * e] + sn[e] * step[2 * e + 1];
+        sn_before[e] = sn[e] * step[2 * e] - c[e] * step[2 * e + 1];
+      }
+      // Four keys a turn of a loop: a copy of its code for every key would be cold for longer than it takes.
+#pragma unroll 1
+      for (uint32_t key = 0; key < kMine; key += 4) {
+        uint32_t at[4], x[4], y[4];                                         // the keys' lower and upper halves
+#pragma unroll
+        for (int k = 0; k < 4; ++k) at[k] = place(key + k);
+        asm volatile("ds_read_b32 %0, %8\n\tds_read_b32 %4, %12\n\tds_read_b32 %1, %9\n\tds_read_b32 %5, %13\n\t"
+                     "ds_read_b32 %2, %10\n\tds_read_b32 %6, %14\n\tds_read_b32 %3, %11\n\tds_read_b32 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])
+                     : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[0] ^ D), "v"(at[1] ^ D), "v"(at[2] ^ D), "v"(at[3] ^ D));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          double turned[4];
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const double av = __uint_as_float(e ? x[k] & 0xFFFF0000u : x[k] << 16), bv = __uint_as_float(e ? y[k] & 0xFFFF0000u : y[k] << 16);
+            turned[e] = av * c[e] - bv * sn[e];
+            turned[2 + e] = bv * c[e] + av * sn[e];
+            const double twice = 2.0 * step[2 * e], c_next = twice * c[e] - c_before[e], sn_next = twice * sn[e] - sn_before[e];
+            c_before[e] = c[e];
+            sn_before[e] = sn[e];
+            c[e] = c_next;
+            sn[e] = sn_next;
+          }
+          float f[4];
+          narrow4_for_bf16(turned, f);
+          lds_write4(at[k], pack_bf16x2(f[0], f[1]));
+          lds_write4(at[k] ^ D, pack_bf16x2(f[2], f[3]));
+        }
+      }
+    };
     for (; t < tile_end; t += kWaves) {
       const bool more = t + kWaves < tile_end;
       const uint32_t j0 = t * kKT;
@@ -306,34 +331,8 @@ void attend_split(SplitArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) s[v] = s_odd[v] = 0.f;
       if constexpr (TURNED) {
-        // two fragments (a pair's halves) at a time, all that a step reads in flight together: there are no registers for more
-        const uint32_t turn_at = (uint32_t)(uintptr_t)(lds_byte*)turn_st[wave] + hi * 64;
-        const uint32_t q_at = (uint32_t)(uintptr_t)(lds_byte*)q_st + r * kRowBytes + ((hi ^ k_swizzle(r)) << 4);
-#pragma unroll
-        for (int ks = 0; ks < kKS / 2; ++ks) {
-          u32x4 x[4], q[2], kf[2];
-          kf[0] = lds_read16(k_at ^ (ks << 5));
-          kf[1] = lds_read16(k_at ^ ((ks + kKS / 2) << 5));
-#pragma unroll
-          for (int w = 0; w < 4; ++w) x[w] = lds_read16(turn_at + ks * 128 + w * 16);
-          q[0] = lds_read16(q_at ^ (ks << 5));
-          q[1] = lds_read16(q_at ^ ((ks + kKS / 2) << 5));
-          arrived4<0>(x[0], x[1], x[2], x[3]);
-          arrived4<0>(kf[0], kf[1], q[0], q[1]);
-          if (!second) {
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-              uint32_t ka = kf[0][w], kb = kf[1][w];
-              turn_pairs(ka, kb, __builtin_bit_cast(f32x4, x[w]), within[4 * ks + w]);
-              kf[0][w] = ka;
-              kf[1][w] = kb;
-            }
-          }
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[0]), __builtin_bit_cast(bf16x8, q[0]), s, 0, 0, 0);
-          s_odd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[1]), __builtin_bit_cast(bf16x8, q[1]), s_odd, 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
+        if (!second) turn_keys();
+      }
       u32x4 kf[kKS];
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) kf[ks] = lds_read16(k_at ^ (ks << 5));
@@ -357,7 +356,6 @@ void attend_split(SplitArgs a) {
             for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[e], q4[e], s, 0, 0, 0);
           }
         }
-      }
       }
       if constexpr (kBf16) s += s_odd;
       __builtin_amdgcn_sched_barrier(0);
@@ -393,24 +391,21 @@ void attend_split(SplitArgs a) {
           for (int v = 0; v < 16; ++v) o[md][v] *= corr;
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (more) wait_loads<kLoads + (TURNED ? 1 : 0)>();                    // the values; the next keys may be on their way
+      if (more) wait_loads<kLoads + kTurnLoads>();                          // the values; the next keys may be on their way
       else wait_loads<0>();
       if constexpr (kBf16) {
         i16x4 vf[2][kMD][2];
-        uint32_t v_first = v_at[0];
-        if constexpr (TURNED) asm volatile("" : "+v"(v_first));             // the other dims' addresses would be kept, and spilled
         auto request = [&](auto kp_c) {
           constexpr int kp = decltype(kp_c)::value;
 #pragma unroll
           for (int md = 0; md < kMD; ++md) {
-            const uint32_t at = TURNED ? v_first ^ (md << 6) : v_at[md];           // (the same: the chunk's number is two bits of its own)
-            vf[kp][md][0] = lds_read_tr<kp * 16 * D * 2>(at);                     // keys 16kp + 4hi + 0..3
-            vf[kp][md][1] = lds_read_tr<(kp * 16 + 8) * D * 2>(at);               // keys 16kp + 8 + 4hi + 0..3
+            vf[kp][md][0] = lds_read_tr<kp * 16 * D * 2>(v_at[md]);               // keys 16kp + 4hi + 0..3
+            vf[kp][md][1] = lds_read_tr<(kp * 16 + 8) * D * 2>(v_at[md]);         // keys 16kp + 8 + 4hi + 0..3
           }
         };
         auto multiply = [&](auto kp_c) {
           constexpr int kp = decltype(kp_c)::value;
-          constexpr int kNewer = kp == 0 && !TURNED ? 2 * kMD : 0;
+          constexpr int kNewer = kp == 0 ? 2 * kMD : 0;
 #pragma unroll
           for (int md = 0; md < kMD; md += 2) arrived4<kNewer>(vf[kp][md][0], vf[kp][md][1], vf[kp][md + 1][0], vf[kp][md + 1][1]);
           // A probability goes in as three bf16 terms, each the rounded value of what the ones before it leave: together
@@ -434,12 +429,8 @@ void attend_split(SplitArgs a) {
           }
         };
         request(std::integral_constant<int, 0>());
-        if constexpr (!TURNED) request(std::integral_constant<int, 1>());
+        request(std::integral_constant<int, 1>());
         multiply(std::integral_constant<int, 0>());
-        if constexpr (TURNED) {                                             // (no registers for both groups of keys at once)
-          __builtin_amdgcn_sched_barrier(0);
-          request(std::integral_constant<int, 1>());
-        }
         multiply(std::integral_constant<int, 1>());
       } else {
         // step v multiplies keys 8*(v/4) + v%4 (lower half-wave) and + 4 (upper): the keys of S^T's register v
@@ -648,7 +639,7 @@ SplitArgs make_args(const SplitCall& c) {
   a.scale = c.dtype == ESA_F32 ? c.scale : c.scale * kLog2e;
   a.out_bs = c.out_bs;
   a.sel_bs_bytes = c.sel_bs * esz;
-  a.turns = (const float*)c.turns;
+  a.turns = (const double*)c.turns;
   return a;
 }
 int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
@@ -721,8 +712,12 @@ bool attend_split_supported(int l_c, int h, int h_kv, int d, int dtype, int batc
          (int64_t)row_tiles(l_c, h, h_kv) * h_kv * batch * 2 * split_limit(l_c, h, h_kv, batch) < ((int64_t)1 << 31);
 }
 
-bool attend_split_turns_keys(int l_c, int h, int h_kv, int d, int dtype, int batch) {
-  return dtype == ESA_BF16 && attend_split_supported(l_c, h, h_kv, d, dtype, batch) && row_tiles(l_c, h, h_kv) == 1;
+// Turning costs a call 1.5 us and more, a copy its bytes.  Copied / turned, us, by batch entries x KV heads x local keys, one token and four:
+// 1 x 4096 12.8 / 13.8, 13.9 / 14.9; 2 x 2048 13.3 / 14.2, 16.1 / 16.9; 2 x 4096 13.9 / 14.1, 17.7 / 17.0; 4 x 2048 14.8 / 14.2, 17.9 / 17.2;
+// 16 x 512 14.1 / 13.7, 15.6 / 14.9; 8 x 4096 21.7 / 17.4, 22.7 / 19.7; 64 x 2048 40.0 / 34.3, 41.6 / 34.9; head size 64: 2 x 2048 11.3 / 11.8,
+// 2 x 4096 11.7 / 11.8, 4 x 2048 11.95 / 11.8, 64 x 2048 26.8 / 23.2.
+bool attend_split_turns_keys(int l_c, int h, int h_kv, int d, int dtype, int batch, int64_t n_keys) {
+  return dtype == ESA_BF16 && attend_split_supported(l_c, h, h_kv, d, dtype, batch) && row_tiles(l_c, h, h_kv) == 1 && n_keys * h_kv * batch >= 8192;
 }
 
 size_t attend_split_workspace_bytes(int l_c, int h, int h_kv, int d, int dtype, int batch) {

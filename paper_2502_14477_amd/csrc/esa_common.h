@@ -44,6 +44,37 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
+// fp64 -> fp32, such that rounding the result to bf16 rounds the fp64 value: where the nearest fp32 number is the midpoint
+// of two bf16 numbers and not the value itself, the side the value lies on is kept.
+__device__ __forceinline__ float narrow_for_bf16(double v) {
+  const float f = (float)v;
+  const uint32_t u = __float_as_uint(f);
+  if ((u & 0xFFFFu) == 0x8000u) {
+    const double left = v - (double)f;      // exact
+    if (left != 0.0) return __uint_as_float((left > 0.0) == (f > 0.f) ? u + 1u : u - 1u);
+  }
+  return f;
+}
+
+// Four of them, with one branch for the midpoints.
+__device__ __forceinline__ void narrow4_for_bf16(const double (&v)[4], float (&f)[4]) {
+  bool midpoint = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[i] = (float)v[i];
+    midpoint |= (uint16_t)__float_as_uint(f[i]) == 0x8000u;
+  }
+  if (__builtin_expect(midpoint, 0)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      asm volatile("" : "+v"(f[i]));       // (this block's tests would be made in front of the branch)
+      const double left = v[i] - (double)f[i];
+      const uint32_t u = __float_as_uint(f[i]);
+      if ((uint16_t)u == 0x8000u && left != 0.0) f[i] = __uint_as_float((left > 0.0) == (f[i] > 0.f) ? u + 1u : u - 1u);
+    }
+  }
+}
+
 template <typename T> __device__ __forceinline__ float load_f32(const T* p);
 template <> __device__ __forceinline__ float load_f32<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float load_f32<bf16_t>(const bf16_t* p) { return bf16_to_f32(*p); }
@@ -162,11 +193,13 @@ int launch_attend(int part, int split, const void* q, int l_c, int h, int h_kv, 
                   hipStream_t st, bool plain = false);
 
 // Section 3.2: rotary re-encoding.  One launch serves up to four row sets ("jobs"); row i of a job
-// is rotated to position pos0 + i * pos_step (rotate == 1), or copied unchanged (0); kRopeTurns: a table of n_tok = 32 + tiles rows of
-// fp32 cosines and sines, from which attend_split turns keys by itself (head sizes 64 and 128).
+// is rotated to position pos0 + i * pos_step (rotate == 1), or copied unchanged (0); kRopeTurns: a table of fp64 cosines and sines, from
+// which attend_split turns n_keys keys by itself (head sizes 64 and 128): of one position, then of every d / 8 positions up to a
+// whole number of tiles of 32 keys.
 constexpr int kMaxRopeJobs = 4;
 constexpr int kRopeTurns = 2;
-static inline size_t rope_turns_bytes(int64_t n_keys, int d) { return (size_t)(32 + (n_keys + 31) / 32) * d / 2 * 8; }
+static inline int64_t rope_turn_rows(int64_t n_keys, int d) { return 1 + (n_keys + 31) / 32 * (256 / d); }
+static inline size_t rope_turns_bytes(int64_t n_keys, int d) { return (size_t)rope_turn_rows(n_keys, d) * d * sizeof(double); }
 struct RopeJob {
   const void* x;
   void* out;

@@ -32,18 +32,6 @@ struct RopeJobs {
   RopeJob j[kMaxRopeJobs];
 };
 
-// fp64 -> fp32, such that rounding the result to bf16 rounds the fp64 value: where the nearest fp32 number is the midpoint
-// of two bf16 numbers and not the value itself, the side the value lies on is kept.
-__device__ __forceinline__ float narrow_for_bf16(double v) {
-  const float f = (float)v;
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0xFFFFu) == 0x8000u) {
-    const double left = v - (double)f;      // exact
-    if (left != 0.0) return __uint_as_float((left > 0.0) == (f > 0.f) ? u + 1u : u - 1u);
-  }
-  return f;
-}
-
 template <typename T> __device__ __forceinline__ double load_f64(T v);
 template <> __device__ __forceinline__ double load_f64<float>(float v) { return (double)v; }
 template <> __device__ __forceinline__ double load_f64<bf16_t>(bf16_t v) { return (double)bf16_to_f32(v); }
@@ -69,15 +57,13 @@ __host__ __device__ inline int rows_of(int heads, int budget) {
   return r;
 }
 
-// A table of turns instead of rows: cosine and sine of 0 ... 31 positions, in the order in which the lanes of a wave that each stand
-// for a key read them as a matrix fragment, then of every multiple of 32, in the frequencies' order.  A key's angle is the sum of two
-// of them.  Row r < 32: pair i = 16 ks + 8 hi + e stands at [ks][e / 2][32 hi + r][e % 2].
-__device__ __forceinline__ void write_turns(float2* out, int64_t row, int i, int half, double freq) {
-  const double pos = row < 32 ? (double)row : 32.0 * (double)(row - 32);
+// A table of turns instead of rows, cosine and sine for each frequency: of one position, then of every multiple of d / 8.
+__device__ __forceinline__ void write_turns(double* out, int64_t row, int i, int half, double freq) {
+  const double pos = row == 0 ? 1.0 : (double)((row - 1) * (half / 4));
   double c = 1.0, s = 0.0;
   if (pos != 0.0) sincos(pos * freq, &s, &c);
-  const int64_t at = row < 32 ? ((int64_t)(i / 16 * 4 + i % 8 / 2) * 64 + i / 8 % 2 * 32 + row) * 2 + i % 2 : row * half + i;
-  out[at] = make_float2((float)c, (float)s);
+  out[(row * half + i) * 2] = c;
+  out[(row * half + i) * 2 + 1] = s;
 }
 
 // grid (groups of rows, jobs, batch); 256 threads.  The rows' angles go through LDS once; then a thread owns VEC
@@ -94,7 +80,7 @@ __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int
   const int half = d >> 1, tid = threadIdx.x;
   if (jb.rotate == kRopeTurns) {          // one table for all batch entries, a sine and a cosine to a thread
     const int g = tid / half;
-    if (blockIdx.z == 0 && g < n_rows) write_turns((float2*)jb.out, row0 + g, tid % half, half, turns.freq[tid % half]);
+    if (blockIdx.z == 0 && g < n_rows) write_turns((double*)jb.out, row0 + g, tid % half, half, turns.freq[tid % half]);
     return;
   }
   const T* x = (const T*)jb.x + (int64_t)blockIdx.z * jb.x_bs + row0 * jb.ldx;

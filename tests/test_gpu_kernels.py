@@ -30,6 +30,16 @@ def attend_inputs(seed, dtype, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
     return q, K, V, sel
 
 
+def attend_reencoded_rounded(q, K, V, t0, l_I, l_L, sel, w, base):
+    """The oracle's Section 3.2 over bf16 rows: each encoded query and key is rounded once."""
+    l_C, l_start = q.shape[0], segment_bounds(t0, l_I, l_L)[1]
+    K_l = np.zeros_like(K)
+    K_l[l_start:t0 + l_C] = orc.rope(K[l_start:t0 + l_C], np.arange(t0 + l_C - l_start), base)
+    q_l, q_g = orc.rope(q, t0 - l_start + np.arange(l_C), base), orc.rope(q, np.full(l_C, w), base)
+    q_l, q_g, K_l = (orc.round_to_storage(x, "bf16") for x in (q_l, q_g, K_l))
+    return orc.attend_two_encodings(q_l, q_g, K_l, K, V, t0, l_I, l_L, sel, 1.0 / np.sqrt(q.shape[2]))
+
+
 # one token of a 32-row wave tile more or less, row tiles of unequal filling, one slice and many, every group size
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
     (1, 4, 4, 64, 900, 16, 8, 64, 31), (1, 8, 4, 64, 700, 17, 8, 100, 64), (2, 8, 2, 64, 1000, 65, 0, 130, 129),
@@ -376,12 +386,16 @@ def test_matrix_core_attention_plans(esa, B, H, H_kv, d, l_C, l_I, l_L, n_sel):
         assert np.max(np.abs(to_f64(O_re[b]) - want)) <= O_TOL["bf16"]
 
 
-# Few tokens that turn the local keys as they read them: no local key but the tokens' own, a tile of keys, one less and one more, windows
-# whose slices end inside; 32 rows to a KV head (the most), one more (an encoded copy); head sizes, group sizes, a padded cache
+# Few tokens: an encoded copy of the local keys below 8192 of them in all (batch entries x KV heads x keys), turned as they are read from there
+# on.  No local key but the tokens' own, a tile of keys, one less and one more, windows whose slices end inside; 32 rows to a KV head (the
+# most), one more (an encoded copy); head sizes, group sizes, a padded cache
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel,pad", [
     (1, 8, 2, 128, 300, 1, 16, 0, 40, 0), (1, 8, 2, 128, 300, 1, 16, 31, 40, 0), (2, 8, 8, 128, 300, 2, 16, 31, 0, 64), (1, 32, 8, 128, 3000, 1, 128, 2048, 500, 0),
     (2, 32, 8, 128, 900, 8, 16, 333, 64, 8), (2, 32, 8, 128, 900, 9, 16, 333, 64, 0), (3, 16, 2, 128, 900, 4, 0, 400, 65, 0), (1, 6, 2, 128, 500, 10, 16, 100, 33, 0),
-    (1, 8, 2, 64, 300, 1, 16, 32, 40, 0), (2, 16, 2, 64, 2500, 4, 16, 2000, 100, 8), (4, 8, 8, 64, 700, 15, 16, 200, 31, 0), (1, 8, 4, 64, 0, 7, 16, 32, 0, 0)])
+    (1, 8, 2, 64, 300, 1, 16, 32, 40, 0), (2, 16, 2, 64, 2500, 4, 16, 2000, 100, 8), (4, 8, 8, 64, 700, 15, 16, 200, 31, 0), (1, 8, 4, 64, 0, 7, 16, 32, 0, 0),
+    (32, 8, 8, 128, 80, 1, 16, 30, 20, 0), (32, 8, 8, 128, 80, 1, 16, 31, 20, 0), (32, 8, 8, 128, 80, 1, 16, 32, 0, 0), (33, 32, 8, 128, 90, 4, 16, 30, 20, 8),
+    (16, 32, 8, 128, 300, 8, 16, 64, 100, 0), (1, 8, 8, 128, 1200, 1, 0, 1100, 0, 0), (256, 3, 1, 64, 60, 10, 4, 22, 9, 8), (32, 16, 2, 64, 300, 4, 16, 130, 31, 0),
+    (32, 8, 8, 64, 90, 15, 0, 17, 31, 0), (4, 32, 8, 64, 700, 8, 16, 300, 64, 0)])
 def test_reencoded_attention_of_few_tokens_turns_the_local_keys(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel, pad):
     say(f"re-encoded, few tokens B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel} pad={pad}")
     q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
@@ -396,22 +410,23 @@ def test_reencoded_attention_of_few_tokens_turns_the_local_keys(esa, B, H, H_kv,
     qd, Kd, Vd, idx = f64_to_dev(q, "bf16"), rows(K), rows(V), torch.from_numpy(sel).cuda()
     ks, vs = esa.esa_gather_kv(Kd, Vd, idx) if n_sel else (None, None)
     O, lse = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, 4096.0, 5e5, return_lse=True)
-    for b in range(B):
-        want, want_lse = orc.attend_reencoded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d), 4096.0, 5e5)
-        # a logit of unit scale errs by 2^-9 / sqrt(d) per element of the rounded rows: as with encoded copies
-        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"], b
-        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 2e-2, b
+    for b in range(0, B, max(1, B // 4)):
+        want, want_lse = attend_reencoded_rounded(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 4096.0, 5e5)
+        # fp32 arithmetic on the rows that the oracle has too, and one rounding (a tile of 2048 keys turned by its neighbour's angle: O 2.0e-3, lse 7.5e-4)
+        assert np.all(np.abs(to_f64(O[b]) - want) <= 0.502 * bf16_ulp(want) + 5e-5), b
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 5e-5, b
 
 
 # Section 3.2's rows are encoded in 64 bits and rounded once.  Every row of queries is made from one local key, each tile of the window
 # having its turn, and that key takes the whole softmax: lse is its logit, so a single element of it or of the query that is rounded to the
 # other bf16 number shows (7e-4 in the median; products and sums of fp32 err by 1e-5), and a tile encoded with another one's positions gives
 # another key's value.
-@pytest.mark.parametrize("B,H,H_kv,d,l_C,l_L", [(1, 32, 8, 128, 64, 2048), (1, 16, 8, 64, 100, 1000), (2, 8, 8, 128, 130, 1500)])
+@pytest.mark.parametrize("B,H,H_kv,d,l_C,l_L", [(8, 32, 8, 128, 8, 2048), (1, 8, 8, 128, 1, 2048), (4, 16, 8, 64, 15, 2000), (2, 16, 2, 128, 3, 4096),
+                                                (1, 32, 8, 128, 64, 2048), (1, 16, 8, 64, 100, 1000), (2, 8, 8, 128, 130, 1500)])
 def test_reencoded_rows_are_the_exact_ones_rounded_once(esa, B, H, H_kv, d, l_C, l_L):
     say(f"re-encoded rows rounded once B={B} H={H} H_kv={H_kv} d={d} l_C={l_C} l_L={l_L}")
     base, w, l_I, n_sel = 5e5, 4096.0, 64, 256
-    t0, scale, gain = l_I + 300 + l_L, 1.0 / np.sqrt(d), 24.0 / np.sqrt(d)
+    t0, gain = l_I + 300 + l_L, 24.0 / np.sqrt(d)
     rng = np.random.default_rng(d + l_C)
     bf16 = lambda x: orc.round_to_storage(x, "bf16")
     K, V = (bf16(rng.standard_normal((B, t0 + l_C, H_kv, d))) for _ in range(2))
@@ -429,10 +444,7 @@ def test_reencoded_rows_are_the_exact_ones_rounded_once(esa, B, H, H_kv, d, l_C,
     ks, vs = esa.esa_gather_kv(Kd, Vd, idx)
     O, lse = esa.esa_attend_reencoded(qd, Kd, Vd, t0, l_I, l_L, ks, vs, w, base, return_lse=True)
     for b in range(B):
-        K_l = np.zeros_like(K[b])
-        K_l[t0 - l_L:] = bf16(orc.rope(K[b, t0 - l_L:], np.arange(l_L + l_C), base))
-        q_l, q_g = bf16(orc.rope(q[b], l_L + np.arange(l_C), base)), bf16(orc.rope(q[b], np.full(l_C, w), base))
-        want, want_lse = orc.attend_two_encodings(q_l, q_g, K_l, K[b], V[b], t0, l_I, l_L, sel, scale)
+        want, want_lse = attend_reencoded_rounded(q[b], K[b], V[b], t0, l_I, l_L, sel, w, base)
         assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 5e-5, b
         # half a unit in the last place from the rounding of the output, half from that of a probability
         assert np.all(np.abs(to_f64(O[b]) - want) <= bf16_ulp(want) + 1e-4), b
