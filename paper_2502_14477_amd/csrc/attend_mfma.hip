@@ -74,6 +74,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // A lane's sixteen exponentials of half a tile add up to at most this, or the softmax reference moves to the running maximum: it lags
 // by at most 2^8, harmless in bf16 and fp32, and the accumulators are rescaled once or twice per row instead of per tile.
 constexpr float kMostSum = 256.f;
+constexpr uint32_t kFollow = 2;
 constexpr float kNoKey = -FLT_MAX;  // reference of a row that has seen no key: finite, so that differences stay numbers
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -94,6 +95,7 @@ struct AttendArgs {
   uint32_t split_step;
   int slot0;          // slice s leaves its partial results in slot slot0 + s ...
   int n_slot;         // ... of so many per row
+  uint32_t follow;    // tiles of a slice at whose end the softmax reference moves to the running maximum (head size 128)
   int to_slots;       // 1: write partial results even when the launch has a single slice
   float c2;           // scale * log2(e)
   int64_t out_bs, sel_bs_bytes;
@@ -542,12 +544,12 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
         pf[2 * mt + kp][e] = pack_bf16x2(p[mt][v], p[mt][v + 1]);
       }
     };
-    // (A sum that is no number does not exceed it: the row's output is none either way.)  In the first two tiles the reference moves to
-    // the largest logit in any case: the key that it stands at has an exact probability, and a slice's largest of 128 keys weighs more
-    // than its largest of 32.  Distance from the 64-bit result, mean over eleven calls of 20 to 700 tokens, four seeds: 2.295e-3, 2.330 without
-    // (2.308 with the maximum of every tile and up to sixteen slices); steps 0 to 1.5 % longer.
+    // (A sum that is no number does not exceed it: the row's output is none either way.)  In the first tiles, two of a slice or `follow` of
+    // them, the reference moves to the largest logit in any case: the keys that it has stood at have exact probabilities, and a slice's largest of
+    // 128 keys weighs more than its largest of 32.  Distance from the 64-bit result, mean over eleven calls of 20 to 700 tokens, four
+    // seeds: 2.295e-3, 2.330 without (2.308 with the maximum of every tile and up to sixteen slices); steps 0 to 1.5 % longer.
     auto settle = [&](int mt) __attribute__((always_inline)) {
-      if (__builtin_expect(__ballot(psum[mt] > kMostSum) != 0ull || (mt == 1 && t < tile_begin + 2), 0)) {
+      if (__builtin_expect(__ballot(psum[mt] > kMostSum) != 0ull || (mt == 1 && t < tile_begin + a.follow), 0)) {
         float mx = s[mt][0];
 #pragma unroll
         for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[mt][v]);
@@ -842,11 +844,12 @@ int most_slices(int64_t base) {
 struct Plan {
   RowTiles rows;
   int n_split;
+  uint32_t follow;
 };
 Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t n_keys, int64_t keys_of_first_row) {
   const int group = h / h_kv;
   const int64_t tiles = (n_keys + kKT - 1) / kKT, first = (keys_of_first_row + kKT - 1) / kKT;
-  Plan best = {row_tiles(l_c, group), 1};
+  Plan best = {row_tiles(l_c, group), 1, kFollow};
   float least = FLT_MAX;
   for (int most_rows = kRows; most_rows >= kRows / 2; most_rows /= 2) {
     const RowTiles r = row_tiles(l_c, group, most_rows);
@@ -858,10 +861,17 @@ Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t n_keys, int64_t 
       const float t = (float)((base * ns + 255) / 256) * per_round + (ns > 1 ? 3.f + 6.4e-5f * (float)l_c * h * batch * ns : 0.f) + (ns > 16 ? 0.2f * (ns - 16) : 0.f);
       if (t < least) {
         least = t;
-        best = {r, ns};
+        best = {r, ns, kFollow};
       }
     }
   }
+  // Every slice has its own reference, so a row has the fewer exact probabilities the fewer slices it is cut into.  Where they are fewer than
+  // one round of workgroups of 256 rows would take, the reference follows the maximum for more tiles, the same number in all.  Distance from
+  // the 64-bit result, 1e-3, with that many slices, with fewer and two tiles, and so: 300 tokens of 16 heads of two 2.290 / 2.308 / 2.276, 128 tokens of 32 heads of eight
+  // 2.294 / 2.305 / 2.283, 512 of eight of eight 2.299 / 2.311 / 2.291; none of 80 calls of 17 to 1024 tokens is further from it than with that
+  // many slices.  The calls concerned take 1 to 3 % longer.
+  const int round = choose_splits(l_c, group, h_kv, batch), whole = round < tiles ? round : (int)tiles;
+  if (best.n_split < whole) best.follow = (uint32_t)(kFollow * whole + best.n_split - 1) / best.n_split;
   return best;
 }
 
@@ -959,8 +969,9 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.group = h / h_kv;
   a.group_log2 = __builtin_ctz(a.group);
   const int64_t n_fixed = i_end + n_sel + (t0 - l_start);
-  const Plan one = plan_one_call(l_c, h, h_kv, batch, n_fixed + l_c, n_fixed + 1);
-  const RowTiles tiles = part == kAttendAll ? one.rows : row_tiles(l_c, a.group);
+  const Plan one = part == kAttendAll ? plan_one_call(l_c, h, h_kv, batch, n_fixed + l_c, n_fixed + 1) : Plan{row_tiles(l_c, a.group), 0, kFollow};
+  const RowTiles tiles = one.rows;
+  a.follow = one.follow;
   a.qpt = tiles.qpt;
   a.n_qt = tiles.n_qt;
   a.batch = batch;
@@ -1043,6 +1054,7 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   const Plan plan = plan_one_call(l_c, h, h_kv, batch, align_up(n_loc + l_c, kKT) + keys_b, align_up(n_loc + 1, kKT) + keys_b);
   a.qpt = plan.rows.qpt;
   a.n_qt = plan.rows.n_qt;
+  a.follow = plan.follow;
   a.batch = batch;
   a.c2 = scale * kLog2e;
   a.out_bs = out_bs;
