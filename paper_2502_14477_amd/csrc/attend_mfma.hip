@@ -830,11 +830,15 @@ int choose_splits(int l_c, int group, int h_kv, int batch) {
 // ---- one-call form: row tiles of 256 or of 128 rows, and the number of slices.  A compute unit holds one workgroup, so a workgroup
 // more than 256 costs another round of them (160 tokens of eight KV heads in eleven slices of three row tiles, 264 workgroups: 38.5 us a
 // call, 23.6 as chosen here), and a number far below leaves compute units idle.  With 128 rows a SIMD has one wave instead of
-// two: a tile takes 1.0 us instead of 1.6, start, end and merge 12.4 instead of 17 (calls of 64 to 512 tokens of eight KV heads over 4
-// thousand keys fit these to 0.3 us), so half the rows are the better choice up to some 11 tiles a slice.  A merge of more than sixteen
-// slots has few rows and waits for its loads.  Calls of l_c tokens of eight KV heads, us, with 256 rows and 256 / tiles slices rounded up, at
-// most sixteen, and as chosen here, 4 thousand keys: 48 19.3 / 16.7, 77 21.5 / 18.4, 128 24.6 / 21.3, 256 31.0 / 29.6, 300 49.3 / 34.8,
-// 384 54 / 39.7, 700 91 / 67, 512 and 1000 the same; 16 thousand: 20 24.8 / 21.0, 64 35.0 / 27.7, 300 130 / 84, 700 290 / 190.
+// two, which takes 0.6 of the time a tile.  A merge of more than sixteen slots has few rows and waits for its loads; a slice that
+// holds the end of Section 3.2's first part and the start of its second has the queries to fetch again, about a tile's time.
+// The constants of the cost are a fit to 375 calls, every number of slices of each (17 to 1000 tokens; 32 heads of 8, 16 of 2 and 8 of 8;
+// head sizes 128 and 64; 3 to 16 thousand keys; one to four sequences; one view and two): the plan takes 1.004 of the best one's time
+// in the mean, 1.065 at most.  (Fitted on one view of one sequence of eight KV heads, without the second part's start: 1.016 and 1.13.)
+// Calls, us, with 256 rows and 256 / tiles slices rounded up, at most sixteen (and the kernel of whole tiles), and as chosen here: 4 thousand
+// keys of eight KV heads, 17 tokens 14.9 / 14.4, 48 19.7 / 16.5, 77 21.8 / 18.7, 128 25.1 / 22.2, 200 28.8 / 28.5, 300 50.4 / 34.2, 384
+// 55.5 / 39.3, 512 48.1 / 46.8, 700 95.5 / 68.5; 16 thousand, 17 27.4 / 21.6, 77 38.3 / 34.8, 300 137 / 84.7, 700 305 / 190; three sequences of 4
+// thousand, 48 36.5 / 23.6, 256 93.5 / 68.8; Section 3.2, 6 thousand, 48 33.1 / 29.9, 200 44.3 / 44.9, 300 73.5 / 52.4.
 // Slices that a launch over this many (row tile, pair)s may have: one round of workgroups where that fills nine tenths of the compute
 // units, three otherwise.  (Known without the number of keys, so that the workspace is.)
 int most_slices(int64_t base) {
@@ -846,23 +850,45 @@ struct Plan {
   int n_split;
   uint32_t follow;
 };
-Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t n_keys, int64_t keys_of_first_row) {
+// keys: in front of the chunk's own; second_keys: of Section 3.2's second part, -1 where there is one view only.
+Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t keys, int64_t second_keys) {
   const int group = h / h_kv;
-  const int64_t tiles = (n_keys + kKT - 1) / kKT, first = (keys_of_first_row + kKT - 1) / kKT;
+  auto tiles_of = [](int64_t n) { return (uint32_t)((n + kKT - 1) / kKT); };
+  const uint32_t second = second_keys > 0 ? tiles_of(second_keys) : 0;
+  const uint32_t tiles = tiles_of(keys + l_c) + second, first = tiles_of(keys + 1) + second;
   Plan best = {row_tiles(l_c, group), 1, kFollow};
   float least = FLT_MAX;
   for (int most_rows = kRows; most_rows >= kRows / 2; most_rows /= 2) {
     const RowTiles r = row_tiles(l_c, group, most_rows);
     const int64_t base = (int64_t)r.n_qt * h_kv * batch;
     const bool one_wave = r.qpt * group <= kRows / 2;                    // a SIMD's waves with rows
-    const int most = (int)(most_slices(base) < first ? most_slices(base) : first);
-    for (int ns = 1; ns <= most || ns == 1; ++ns) {
-      const float per_round = (one_wave ? 5.3f + 1.0f * (tiles + ns - 1) / ns : 8.0f + 1.6f * (tiles + ns - 1) / ns);
-      const float t = (float)((base * ns + 255) / 256) * per_round + (ns > 1 ? 3.f + 6.4e-5f * (float)l_c * h * batch * ns : 0.f) + (ns > 16 ? 0.2f * (ns - 16) : 0.f);
+    const uint32_t most = (uint32_t)most_slices(base) < first ? most_slices(base) : first;
+    // The longest slice, of the first row tile or the last.
+    auto longest = [&](uint32_t ns) {
+      uint32_t most_tiles = 0;
+      for (int64_t seen : {keys + (r.qpt < l_c ? r.qpt : l_c), keys + l_c}) {
+        const uint32_t end = tiles_of(seen), all = end + second;
+        uint32_t n = (all + ns - 1) / ns;
+        if (second) {
+          const uint32_t s = ((end + 1) * ns - 1) / all, lo = all * s / ns, hi = all * (s + 1) / ns;     // the slice of the second part's first tile
+          if (lo < end && hi - lo + 1 > n) n = hi - lo + 1;
+        }
+        most_tiles = n > most_tiles ? n : most_tiles;
+      }
+      return most_tiles;
+    };
+    for (uint32_t ns = 1;;) {
+      const float n = (float)longest(ns);
+      float t = (float)((base * ns + 255) / 256) * (one_wave ? 0.8f + 1.f * n : 2.f + 1.4f * n);
+      if (ns > 1) t += 4.f + 9.8e-5f * (float)l_c * h * batch * ns + (ns > 16 ? 0.08f * (ns - 16) : 0.f);
+      if (one_wave && second_keys >= 0) t *= 1.05f;
       if (t < least) {
         least = t;
-        best = {r, ns, kFollow};
+        best = {r, (int)ns, kFollow};
       }
+      if (ns >= most) break;
+      ns += ns < 16 ? 1 : 4;
+      ns = ns < most ? ns : most;
     }
   }
   // Every slice has its own reference, so a row has the fewer exact probabilities the fewer slices it is cut into.  Where they are fewer than
@@ -870,8 +896,8 @@ Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t n_keys, int64_t 
   // the 64-bit result, 1e-3, with that many slices, with fewer and two tiles, and so: 300 tokens of 16 heads of two 2.290 / 2.308 / 2.276, 128 tokens of 32 heads of eight
   // 2.294 / 2.305 / 2.283, 512 of eight of eight 2.299 / 2.311 / 2.291; none of 80 calls of 17 to 1024 tokens is further from it than with that
   // many slices.  The calls concerned take 1 to 3 % longer.
-  const int round = choose_splits(l_c, group, h_kv, batch), whole = round < tiles ? round : (int)tiles;
-  if (best.n_split < whole) best.follow = (uint32_t)(kFollow * whole + best.n_split - 1) / best.n_split;
+  const int round = choose_splits(l_c, group, h_kv, batch), whole = (uint32_t)round < tiles ? round : (int)tiles;
+  if (best.n_split < whole) best.follow = (uint32_t)(kFollow * whole + best.n_split / 2) / best.n_split;
   return best;
 }
 
@@ -969,7 +995,7 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.group = h / h_kv;
   a.group_log2 = __builtin_ctz(a.group);
   const int64_t n_fixed = i_end + n_sel + (t0 - l_start);
-  const Plan one = part == kAttendAll ? plan_one_call(l_c, h, h_kv, batch, n_fixed + l_c, n_fixed + 1) : Plan{row_tiles(l_c, a.group), 0, kFollow};
+  const Plan one = part == kAttendAll ? plan_one_call(l_c, h, h_kv, batch, n_fixed, -1) : Plan{row_tiles(l_c, a.group), 0, kFollow};
   const RowTiles tiles = one.rows;
   a.follow = one.follow;
   a.qpt = tiles.qpt;
@@ -1051,7 +1077,7 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.group_log2 = __builtin_ctz(a.group);
   // slices of the two parts' tiles laid end to end
   const int64_t keys_b = i_end + n_sel;
-  const Plan plan = plan_one_call(l_c, h, h_kv, batch, align_up(n_loc + l_c, kKT) + keys_b, align_up(n_loc + 1, kKT) + keys_b);
+  const Plan plan = plan_one_call(l_c, h, h_kv, batch, n_loc, keys_b);
   a.qpt = plan.rows.qpt;
   a.n_qt = plan.rows.n_qt;
   a.follow = plan.follow;
