@@ -16,6 +16,7 @@
 #include "esa_common.h"
 #include <type_traits>
 #include "radix_hist.h"
+#include "score_shares.h"
 
 namespace esa {
 namespace {
@@ -138,7 +139,6 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kMT = 2;                   // 32-query tiles per wave
 constexpr int kQPerWave = 32 * kMT;
 constexpr int kQPerBlock = kWaves * kQPerWave;
-constexpr int kMaxTilesPerBlock = 16;    // 512 tokens: 128 KB of LDS (d_c = 128); one load instruction per thread and 8 KB
 
 // eps > 0: the second sweep pools over +-eps (Eq. 8, at most kTailMaxEps).  Shares then lap over their neighbours' by eps tokens
 // on either side, so that a workgroup has the scores of every window it writes; the first sweep's are the same ones, because a share
@@ -146,20 +146,7 @@ constexpr int kMaxTilesPerBlock = 16;    // 512 tokens: 128 KB of LDS (d_c = 128
 // tokens).  With a pooling kernel of its own, which read the scores back and built the selection's histogram (4.9 us), a re-encoded step
 // took 63.3 us instead of 61.0 (40 tokens at 50 thousand), 80.1 / 77.0 (128 at 100), 62.4 / 59.9 (60 at 12), 77.6 / 75.8 (256 at 30) and,
 // bound by power, the same 134 (512 at 130).
-// Whole rounds of workgroups, one per compute unit: as few as hold all rows, all shares of one length.  (Full shares of 512 tokens for all
-// but the last were 274 workgroups for 140 thousand tokens, a second round for eighteen of them: steps of 512 and 128 tokens there 124.3 ->
-// 111.3 us and 76.2 -> 68.9, 300 at 190 thousand 109.1 -> 102.4.  Shares by a row's length alone gave two sequences of 33 thousand tokens 344
-// workgroups, four of 20 thousand 628: score of 512 and 64 tokens 36.0 -> 26.9 us, 26.7 -> 16.1.)
-__host__ __device__ inline int64_t mfma_tiles_per_block(int64_t n, int eps, int batch) {
-  const int64_t most = 256 * (32 * kMaxTilesPerBlock - 2 * eps), total = n * batch, rounds = total > most ? (total + most - 1) / most : 1;
-  const int64_t per = ((total + 256 * rounds - 1) / (256 * rounds) + 2 * eps + 63) / 64 * 2;      // even, at least 2, at most kMaxTilesPerBlock
-  const int64_t row = (n + 2 * eps + 63) / 64 * 2;
-  return per < row ? per : row;
-}
-__host__ __device__ inline int64_t mfma_blocks(int64_t n, int eps, int batch) {
-  const int64_t own = 32 * mfma_tiles_per_block(n, eps, batch) - 2 * eps;
-  return (n + own - 1) / own;
-}
+// (score_shares.h: how long a share is, and when.)
 // K' share, column maxima, digit histogram
 __host__ __device__ inline size_t mfma_lds_bytes(int64_t per, int d_c) {
   return (size_t)per * 32 * d_c * sizeof(bf16_t) + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t);
@@ -1052,12 +1039,12 @@ __host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {
 }
 
 __host__ inline size_t part_bytes(int l_c, int64_t n_mid, int eps, int batch) {
-  size_t blocks = (size_t)mfma_blocks(n_mid, eps <= kTailMaxEps ? eps : 0, batch) * l_c;
+  size_t blocks = (size_t)share_count(n_mid, eps <= kTailMaxEps ? eps : 0, batch) * l_c * batch;
   if (stores_scores(l_c, n_mid, batch)) {   // a partial maximum per query and workgroup of at least 64 tokens
-    const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c;
+    const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c * batch;
     blocks = stored > blocks ? stored : blocks;
   }
-  return align_up(blocks * batch * 4, 256);
+  return align_up(blocks * 4, 256);
 }
 
 // fragment-ordered copy of Q' (matrix-core path): whole blocks of 512 queries, 256 bytes each
@@ -1070,7 +1057,7 @@ template <int DC>
 int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int64_t n, float* part, float* mu, float* score,
                   int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, uint32_t* hists, bool fill_first, int64_t hists_bs,
                   bf16_t* qfrag, int64_t qfrag_bs, int eps, hipStream_t st) {
-  const int per = (int)mfma_tiles_per_block(n, eps, batch), nblk = (int)mfma_blocks(n, eps, batch);
+  const int per = (int)share_tiles(n, eps, batch), nblk = (int)share_count(n, eps, batch);
   const dim3 grid(nblk, batch);
   const size_t lds = mfma_lds_bytes(per, DC), most = mfma_lds_bytes(kMaxTilesPerBlock, DC);
   const size_t most0 = mfma_sweep0_lds_bytes(DC == 64 ? kMaxTilesPerBlock : 4, DC, kQPerBlock);          // 128 and 160 KB

@@ -164,9 +164,11 @@ def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
 
 
 # Shares of whole rounds of workgroups: the longest row of one round and one token more, rows of two rounds and of three, several
-# sequences whose shares together make a round, one more than that
+# sequences whose shares together make a round, one more than that; rows that each round up to a share too many; the longest row that the second
+# sweep pools in one round, one that it does not
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 17, 131072, 64, 0), (1, 17, 131073, 64, 0), (1, 33, 140000, 128, 0), (1, 20, 263000, 64, 1), (4, 64, 20000, 128, 0),
-                                             (2, 70, 65536, 64, 0), (2, 70, 65537, 64, 2), (300, 20, 70, 64, 0)])
+                                             (2, 70, 65536, 64, 0), (2, 70, 65537, 64, 2), (300, 20, 70, 64, 0), (3, 20, 10894, 64, 0), (7, 40, 4661, 128, 1), (24, 17, 18849, 64, 0),
+                                             (1, 33, 130560, 64, 1), (1, 33, 130561, 64, 1), (1, 300, 131072, 128, 16)])
 def test_score_sweeps_in_whole_rounds(esa, B, l_c, n, d_c, eps):
     say(f"score rounds B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
     g = torch.Generator(device="cuda").manual_seed(n + l_c)
@@ -182,7 +184,7 @@ def test_score_sweeps_in_whole_rounds(esa, B, l_c, n, d_c, eps):
 # Pooling by the second sweep: one workgroup's tokens, one more, one less; a single token; the widest window it takes in the shortest
 # share and in long ones, the narrowest, one that keeps its own pass; windows across every workgroup's edge hold the row's largest scores
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 17, 1, 128, 1), (2, 40, 62, 128, 1), (1, 40, 63, 128, 1), (1, 20, 61, 64, 1), (1, 33, 32, 64, 16),
-                                             (1, 33, 4097, 64, 16), (1, 600, 33000, 128, 16), (1, 70, 131077, 128, 2), (3, 40, 9000, 128, 3),
+                                             (1, 33, 4097, 64, 16), (1, 600, 33000, 128, 16), (1, 70, 131077, 128, 2), (3, 40, 9000, 128, 3), (1, 70, 131000, 128, 2),
                                              (1, 33, 500, 128, 17)])
 def test_pooling_in_the_second_sweep(esa, B, l_c, n, d_c, eps):
     say(f"score B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")

@@ -1,0 +1,40 @@
+"""How the score sweeps share out the middle tokens (host arithmetic): rounds of workgroups."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LENGTHS = sorted({1, 2, 63, 64, 65, 4661, 5400, 6500, 9300, 10894, 10900, 14500, 16384, 16385, 18500, 18849, 20000, 33000, 60000, 65536, 65537, 130560,
+                  130561, 131072, 131073, 140000, 160000, 163841, 190000, 196608, 250000, 262144, 400000, 1000003} | {97 * i for i in range(1, 400)})
+BATCHES = [1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 24, 255, 256, 257, 300]
+PROGRAM = r"""
+#include <cstdio>
+#include "score_shares.h"
+int main() {
+  long long n; int eps, batch;
+  while (scanf("%lld %d %d", &n, &eps, &batch) == 3)
+    printf("%lld %lld %lld\n", (long long)esa::share_tiles(n, eps, batch), (long long)esa::share_count(n, eps, batch),
+           (long long)esa::share_rounds(n, eps, batch));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shares(tmp_path_factory):
+    """{(n, eps, batch): (tiles, shares of a row, rounds)}"""
+    path = tmp_path_factory.mktemp("shares")
+    (path / "main.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2502_14477_amd", "csrc"), str(path / "main.cpp"), "-o", str(path / "main")], check=True)
+    asked = [(n, eps, batch) for n in LENGTHS for eps in (0, 1, 16) for batch in BATCHES]
+    out = subprocess.run([str(path / "main")], input="".join("%d %d %d\n" % a for a in asked), capture_output=True, text=True, check=True).stdout
+    return dict(zip(asked, (tuple(map(int, line.split())) for line in out.splitlines())))
+
+
+def test_shares_cover_every_row_in_the_fewest_rounds(shares):
+    for (n, eps, batch), (tiles, count, rounds) in shares.items():
+        row = lambda t: -(-n // (32 * t - 2 * eps))
+        assert tiles % 2 == 0 and 2 <= tiles <= 16 and count == row(tiles)
+        assert rounds == -(-batch * row(16) // 256)                              # what the longest shares need
+        assert batch * count <= 256 * rounds                                     # and no workgroup more
+        assert tiles == 2 or batch * row(tiles - 2) > 256 * rounds               # in shares no longer than that takes
