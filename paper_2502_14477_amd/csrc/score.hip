@@ -1039,7 +1039,7 @@ __host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {
 }
 
 __host__ inline size_t part_bytes(int l_c, int64_t n_mid, int eps, int batch) {
-  size_t blocks = (size_t)share_count(n_mid, eps <= kTailMaxEps ? eps : 0, batch) * l_c * batch;
+  size_t blocks = (size_t)share_count(n_mid, sweep_pools(n_mid, eps, batch, kTailMaxEps) ? eps : 0, batch) * l_c * batch;
   if (stores_scores(l_c, n_mid, batch)) {   // a partial maximum per query and workgroup of at least 64 tokens
     const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c * batch;
     blocks = stored > blocks ? stored : blocks;
@@ -1149,12 +1149,13 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
   } else if (vec_ok && (d_c == 128 || d_c == 64)) {
     const int64_t qfrag_bs = (int64_t)(qfrag_bytes_per_batch(l_c) / sizeof(bf16_t));
     const auto sweeps = d_c == 128 ? launch_sweeps<128> : launch_sweeps<64>;
-    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, narrow ? score : raw, batch, q_bs,
-                          kc_bs, narrow ? score_bs : raw_bs, first_hist, narrow, first_hist_bs, qfrag, qfrag_bs, narrow ? eps : 0, st);
+    const bool pools = sweep_pools(n, eps, batch, kTailMaxEps);
+    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, pools ? score : raw, batch, q_bs,
+                          kc_bs, pools ? score_bs : raw_bs, first_hist, pools, first_hist_bs, qfrag, qfrag_bs, pools ? eps : 0, st);
     if (rc != ESA_OK) return rc;
     zeroed = first_hist != nullptr;
-    if (first_hist && narrow && first_hist_done) *first_hist_done = true;
-    if (narrow) pool_left = false;
+    if (first_hist && pools && first_hist_done) *first_hist_done = true;
+    if (pools) pool_left = false;
   } else if (stores_scores(l_c, n, batch)) {
     const int nblk = (int)((n + kGTok - 1) / kGTok);
     const dim3 grid((unsigned)nblk, (unsigned)((l_c + kStoreQ - 1) / kStoreQ), batch);

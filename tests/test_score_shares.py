@@ -14,15 +14,15 @@ PROGRAM = r"""
 int main() {
   long long n; int eps, batch;
   while (scanf("%lld %d %d", &n, &eps, &batch) == 3)
-    printf("%lld %lld %lld\n", (long long)esa::share_tiles(n, eps, batch), (long long)esa::share_count(n, eps, batch),
-           (long long)esa::share_rounds(n, eps, batch));
+    printf("%lld %lld %lld %d\n", (long long)esa::share_tiles(n, eps, batch), (long long)esa::share_count(n, eps, batch),
+           (long long)esa::share_rounds(n, eps, batch), (int)esa::sweep_pools(n, eps, batch, 16));
 }
 """
 
 
 @pytest.fixture(scope="module")
 def shares(tmp_path_factory):
-    """{(n, eps, batch): (tiles, shares of a row, rounds)}"""
+    """{(n, eps, batch): (tiles, shares of a row, rounds, pooled by the sweep)}"""
     path = tmp_path_factory.mktemp("shares")
     (path / "main.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2502_14477_amd", "csrc"), str(path / "main.cpp"), "-o", str(path / "main")], check=True)
@@ -32,9 +32,15 @@ def shares(tmp_path_factory):
 
 
 def test_shares_cover_every_row_in_the_fewest_rounds(shares):
-    for (n, eps, batch), (tiles, count, rounds) in shares.items():
+    for (n, eps, batch), (tiles, count, rounds, _) in shares.items():
         row = lambda t: -(-n // (32 * t - 2 * eps))
         assert tiles % 2 == 0 and 2 <= tiles <= 16 and count == row(tiles)
         assert rounds == -(-batch * row(16) // 256)                              # what the longest shares need
         assert batch * count <= 256 * rounds                                     # and no workgroup more
         assert tiles == 2 or batch * row(tiles - 2) > 256 * rounds               # in shares no longer than that takes
+
+
+def test_pooling_in_the_sweep_takes_no_round_more(shares):
+    for (n, eps, batch), s in shares.items():
+        assert s[3] == (s[2] == shares[n, 0, batch][2])
+    assert not shares[131072, 1, 1][3] and shares[130560, 1, 1][3]
