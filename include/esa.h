@@ -103,7 +103,8 @@ ESA_API int esa_compress_qk(const void* xq, int64_t d_in_q, int64_t ldxq, const 
  *   qc        [batch][l_c, d_c]  contiguous rows, batch stride q_bs
  *   kc_cache  [batch][>= m_hi, d_c] contiguous rows, batch stride kc_bs
  *   score     [batch][m_hi-m_lo] fp32, batch stride score_bs
- *   workspace esa_score_workspace_bytes(l_c, m_hi-m_lo, eps, batch) bytes, 256-byte aligned
+ *   workspace esa_score_workspace_bytes(l_c, m_hi-m_lo, eps, batch) bytes, 256-byte aligned (beyond 16 MiB of
+ *             scores, l_c * (m_hi-m_lo) * batch * 4, the size does not fall with a longer row or more rows)
  * m_hi == m_lo is a no-op.
  */
 ESA_API size_t esa_score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch);

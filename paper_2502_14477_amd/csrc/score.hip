@@ -1039,7 +1039,7 @@ __host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {
 }
 
 __host__ inline size_t part_bytes(int l_c, int64_t n_mid, int eps, int batch) {
-  size_t blocks = (size_t)share_count(n_mid, sweep_pools(n_mid, eps, batch, kTailMaxEps) ? eps : 0, batch) * l_c * batch;
+  size_t blocks = (size_t)most_shares(n_mid, eps <= kTailMaxEps ? eps : 0, batch) * l_c;       // of all rows
   if (stores_scores(l_c, n_mid, batch)) {   // a partial maximum per query and workgroup of at least 64 tokens
     const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c * batch;
     blocks = stored > blocks ? stored : blocks;

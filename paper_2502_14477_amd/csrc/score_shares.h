@@ -30,6 +30,12 @@ constexpr int64_t share_tiles(int64_t n, int eps, int batch) {
   return tiles;
 }
 constexpr int64_t share_count(int64_t n, int eps, int batch) { return shares_of(n, eps, share_tiles(n, eps, batch)); }
+// Workgroups of all rows: at least batch * share_count of these sizes and of any fewer tokens and rows, so that a workspace for the longest
+// context serves the shorter ones.
+constexpr int64_t most_shares(int64_t n, int eps, int batch) {
+  const int64_t rounds = share_rounds(n, eps, batch) * kComputeUnits, shortest = batch * shares_of(n, eps, 2);
+  return rounds < shortest ? rounds : shortest;
+}
 // Whether the second sweep pools over +-eps: the shares then lap over their neighbours', and where that would take another round
 // a kernel of its own pools.  (512 tokens over 131072, eps 1: score
 // 48.7 us pooled by the sweep, 40.0 so; five rows of 13000, 300 tokens, 35.6 / 22.9.)

@@ -1,8 +1,10 @@
-"""How the score sweeps share out the middle tokens (host arithmetic): rounds of workgroups."""
+"""How the score sweeps share out the middle tokens (host arithmetic): rounds of workgroups, and the workspace that covers them."""
 import os
 import subprocess
 
 import pytest
+
+import paper_2502_14477_amd as esa
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LENGTHS = sorted({1, 2, 63, 64, 65, 4661, 5400, 6500, 9300, 10894, 10900, 14500, 16384, 16385, 18500, 18849, 20000, 33000, 60000, 65536, 65537, 130560,
@@ -14,15 +16,15 @@ PROGRAM = r"""
 int main() {
   long long n; int eps, batch;
   while (scanf("%lld %d %d", &n, &eps, &batch) == 3)
-    printf("%lld %lld %lld %d\n", (long long)esa::share_tiles(n, eps, batch), (long long)esa::share_count(n, eps, batch),
-           (long long)esa::share_rounds(n, eps, batch), (int)esa::sweep_pools(n, eps, batch, 16));
+    printf("%lld %lld %lld %lld %d\n", (long long)esa::share_tiles(n, eps, batch), (long long)esa::share_count(n, eps, batch),
+           (long long)esa::share_rounds(n, eps, batch), (long long)esa::most_shares(n, eps, batch), (int)esa::sweep_pools(n, eps, batch, 16));
 }
 """
 
 
 @pytest.fixture(scope="module")
 def shares(tmp_path_factory):
-    """{(n, eps, batch): (tiles, shares of a row, rounds, pooled by the sweep)}"""
+    """{(n, eps, batch): (tiles, shares of a row, rounds, bound of all shares, pooled by the sweep)}"""
     path = tmp_path_factory.mktemp("shares")
     (path / "main.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2502_14477_amd", "csrc"), str(path / "main.cpp"), "-o", str(path / "main")], check=True)
@@ -32,7 +34,7 @@ def shares(tmp_path_factory):
 
 
 def test_shares_cover_every_row_in_the_fewest_rounds(shares):
-    for (n, eps, batch), (tiles, count, rounds, _) in shares.items():
+    for (n, eps, batch), (tiles, count, rounds, _, _) in shares.items():
         row = lambda t: -(-n // (32 * t - 2 * eps))
         assert tiles % 2 == 0 and 2 <= tiles <= 16 and count == row(tiles)
         assert rounds == -(-batch * row(16) // 256)                              # what the longest shares need
@@ -42,5 +44,25 @@ def test_shares_cover_every_row_in_the_fewest_rounds(shares):
 
 def test_pooling_in_the_sweep_takes_no_round_more(shares):
     for (n, eps, batch), s in shares.items():
-        assert s[3] == (s[2] == shares[n, 0, batch][2])
-    assert not shares[131072, 1, 1][3] and shares[130560, 1, 1][3]
+        assert s[4] == (s[2] == shares[n, 0, batch][2])
+    assert not shares[131072, 1, 1][4] and shares[130560, 1, 1][4]
+
+
+def test_bound_of_the_shares_covers_shorter_rows_and_fewer_of_them(shares):
+    for eps in (0, 1, 16):
+        for i, batch in enumerate(BATCHES):
+            most = [shares[n, eps, batch][3] for n in LENGTHS]
+            assert most == sorted(most)
+            for n in LENGTHS:
+                assert shares[n, eps, batch][3] >= batch * shares[n, eps, batch][1]
+                assert shares[n, eps, batch][3] >= batch * shares[n, 0, batch][1]          # where a kernel of its own pools
+                assert i == 0 or shares[n, eps, batch][3] >= shares[n, eps, BATCHES[i - 1]][3]
+
+
+def test_score_workspace_for_the_longest_context_covers_shorter_ones():
+    # 512 and 77 queries; rows beyond the size at which S is stored
+    for l_c in (512, 77):
+        for eps in (0, 1, 16, 40):
+            for batch in (1, 3, 7):
+                sizes = [esa.lib.esa_score_workspace_bytes(l_c, n, eps, batch) for n in LENGTHS if l_c * n * 4 > 16 << 20]
+                assert sizes == sorted(sizes)
