@@ -203,7 +203,8 @@ ESA_API int esa_gather_kv(const void* k_cache, const void* v_cache, int64_t tok_
  *   k_cache, v_cache as in esa_gather_kv;  k_sel, v_sel [batch][n_sel, h_kv, d] (may be NULL if n_sel == 0)
  *   out  [batch][l_c, h, d] contiguous, batch stride out_bs
  *   lse  [batch][l_c, h] fp32 natural-log normaliser, batch stride l_c*h; NULL to skip
- *   workspace esa_attend_workspace_bytes(...) bytes, 256-byte aligned
+ *   workspace esa_attend_workspace_bytes(...) bytes, 256-byte aligned (bf16, head sizes 64 and 128, 16 tokens or
+ *             more: the size does not fall with more tokens or sequences)
  * Values may use the whole finite range of the storage type as long as the products and sums of Eq. 1
  * stay finite in fp32; intermediate results that pass through the workspace carry their own scale.
  */

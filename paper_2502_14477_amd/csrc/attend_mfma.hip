@@ -949,21 +949,20 @@ SplitPlan plan_splits(int l_c, int group, int h_kv, int batch) {
 }
 
 size_t part_o_bytes(size_t rows, int d) { return align_up(rows * d * (d == 64 ? sizeof(float) : sizeof(uint16_t)), 256); }
-size_t slots_bytes(int n_slot, int l_c, int h, int d, int batch) {
-  const size_t rows = (size_t)batch * n_slot * l_c * h;
+size_t slots_bytes(int64_t slots, int h, int d) {          // slots: of a token's h rows
+  const size_t rows = (size_t)slots * h;
   return part_o_bytes(rows, d) + align_up(rows * 2 * sizeof(float), 256);
 }
 
 }  // namespace
 
+// Covers every shorter chunk (of kMinLc tokens or more) and fewer sequences too, so that a workspace for the longest chunk serves the last one: more than one
+// slice are at most 768 workgroups (most_slices; the two-call form's slots are at most one and a half times ceil(256 / base)) of
+// at most kRows rows, and at most kMaxSlots of them; one slice of the two-call form's parts each are two slots.
 size_t attend_mfma_workspace_bytes(int l_c, int h, int h_kv, int d, int batch) {
-  const SplitPlan p = plan_splits(l_c, h / h_kv, h_kv, batch);
-  int n_slot = p.local + p.sel;
-  for (int most_rows = kRows; most_rows >= kRows / 2; most_rows /= 2) {
-    const int ns = most_slices((int64_t)row_tiles(l_c, h / h_kv, most_rows).n_qt * h_kv * batch);
-    n_slot = ns > n_slot ? ns : n_slot;
-  }
-  return slots_bytes(n_slot, l_c, h, d, batch);
+  const int64_t tokens = (int64_t)l_c * batch, round = (int64_t)768 * kRows / h, all = tokens * kMaxSlots;
+  const int64_t split = round < all ? round : all;
+  return slots_bytes(split > 2 * tokens ? split : 2 * tokens, h, d);
 }
 
 namespace {
@@ -1018,7 +1017,7 @@ int launch_attend_mfma(int part, int split, const void* q, int l_c, int h, int h
   a.part_o = nullptr;
   a.part_ml = nullptr;
   if (part != kAttendAll || ns_all > 1) {
-    const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
+    const size_t need = slots_bytes((int64_t)batch * n_slot * l_c, h, d);
     if (!ws || ws_bytes < need) ESA_FAIL(ESA_EWORKSPACE, "esa_attend: workspace needs %zu bytes", need);
     const size_t rows = (size_t)batch * n_slot * l_c * h;
     a.part_o = ws;
@@ -1086,7 +1085,7 @@ int launch_attend_mfma_two_views(const void* q_loc, const void* q_glob, int64_t 
   a.out_bs = out_bs;
   a.sel_bs_bytes = sel_bs * 2;
   const int n_slot = plan.n_split;
-  const size_t need = slots_bytes(n_slot, l_c, h, d, batch);
+  const size_t need = slots_bytes((int64_t)batch * n_slot * l_c, h, d);
   a.part_o = nullptr;
   a.part_ml = nullptr;
   if (n_slot > 1) {

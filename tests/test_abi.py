@@ -176,3 +176,14 @@ def test_what_is_done_once_is_done_once_on_every_device(tmp_path):
     assert subprocess.run([str(exe)], timeout=60).returncode == 0
     for name in os.listdir(csrc):          # no launch keeps a flag of its own for all devices
         assert not re.search(r"static bool \w+ *=", open(os.path.join(csrc, name)).read()), name
+
+
+def test_attention_workspace_for_the_longest_chunk_covers_shorter_ones():
+    size = esa.lib.esa_attend_workspace_bytes
+    for h, h_kv, d in ((32, 8, 128), (16, 2, 128), (8, 8, 128), (32, 8, 64)):
+        for batch in (1, 2, 3, 8):
+            sizes = [size(l_c, h, h_kv, d, 1, batch) for l_c in range(16, 1100)]
+            assert sizes == sorted(sizes)
+        for l_c in (16, 77, 300, 512):
+            sizes = [size(l_c, h, h_kv, d, 1, batch) for batch in range(1, 40)]
+            assert sizes == sorted(sizes)
