@@ -130,8 +130,8 @@ ESA_API int esa_select_topk(const float* score, int64_t n, int k, int64_t base,
 
 /*
  * esa_score, esa_select_topk (base = m_lo) and, if wanted, esa_gather_kv in one call, with two
- * kernels fewer than the three calls: the kernel that writes the scores (Eq. 4, or Eq. 8's pooling
- * pass when eps > 0) also leaves the first digit histogram of the radix selection (Eq. 2) while the
+ * kernels fewer than the three calls: the kernel that writes the scores (where Eq. 8's pooling is a pass
+ * of its own, that pass) also leaves the first digit histogram of the radix selection (Eq. 2) while the
  * scores are still on chip, and the zero-fill of the histograms rides on an earlier kernel of the
  * score call.  Up to 8192 middle tokens are selected from by one kernel, which also finishes the scores
  * where the score call would need a kernel of its own for that.
@@ -264,8 +264,8 @@ ESA_API int esa_attend_finish(const void* q, int l_c, int h, int h_kv, int d,
  * caches through the index list (ascending absolute positions, as esa_select_topk writes them), so
  * no gathered copy is written and read back: only the selected rows are read, once (Appendix B's
  * per-step loading of the selected keys and values).  Computes exactly what esa_gather_kv followed by esa_attend computes.  Every
- * kernel follows the indices itself; the matrix-core prefill kernel looks the rows of a tile up one
- * tile ahead of the tile's loads.
+ * kernel follows the indices itself; the matrix-core prefill kernel looks up the rows of eight tiles
+ * at a time.
  *   idx  [batch][n_sel] int32, batch stride idx_bs; entries are positions of middle tokens (an entry
  *        outside [0, l_start) is clamped into it rather than followed)
  *   workspace esa_attend_indexed_workspace_bytes(...) bytes, 256-byte aligned

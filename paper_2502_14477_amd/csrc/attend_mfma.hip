@@ -72,7 +72,7 @@ constexpr int kStages = 3;
 constexpr int kMinLc = 16;          // shorter chunks go to the split-key kernel (attend_split.hip)
 constexpr float kLog2e = 1.4426950408889634f;
 // A lane's sixteen exponentials of half a tile add up to at most this, or the softmax reference moves to the running maximum: it lags
-// by at most 2^8, harmless in bf16 and fp32, and the accumulators are rescaled once or twice per row instead of per tile.
+// by at most 2^8, harmless in bf16 and fp32, and the accumulators are rescaled in the first tiles of a slice and rarely after them.
 constexpr float kMostSum = 256.f;
 constexpr uint32_t kFollow = 2;
 constexpr float kNoKey = -FLT_MAX;  // reference of a row that has seen no key: finite, so that differences stay numbers
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   constexpr int kKS = D / 16;             // reduction steps of the first product
   constexpr int kMD = D / 32;             // 32-dim tiles of the second product
   // Three stages of a K tile, then three of a V tile, then room for the query rows, which come in through the last V stage and
-  // what is behind it.  Three stages of each wave's copy of a tile's index entries.
+  // what is behind it.  Two buffers of each wave's index entries, for eight tiles each.
   __shared__ __attribute__((aligned(1024))) bf16_t st[(2 * kStages + 3) * kTileElems];
   __shared__ __attribute__((aligned(1024))) int32_t idx_st[2][LISTED ? kWaves : 1][64];
   constexpr int kQPlace = (2 * kStages - 1) * kTileElems * 2;       // byte offset of the query rows
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
       second(2 + i / kMD, i % kMD);
       __builtin_amdgcn_sched_barrier(0);
     }
-    l_run += psum[0] + psum[1];         // rounded once
+    l_run += psum[0] + psum[1];
   };
 
   // Turn t: tile t, requested two turns before (a turn takes 2 us, a tile that comes from HBM sometimes longer).  Its own requests

@@ -1,6 +1,7 @@
 // Importance of every middle token (Eq. 6 inside Eq. 4):
 //   S[c,m] = q'_c . k'_m,  mu[c] = max_m S[c,m],  F[m] = max_c (S[c,m] - mu[c]),
-// optionally with the proximity max-pool of Eq. 8: narrow windows in the kernel that writes the scores, wider ones behind it.
+// optionally with the proximity max-pool of Eq. 8: narrow windows in the kernel that writes the scores, wider ones (and those whose lap
+// would take the sweeps another round of workgroups) behind it.
 //
 // F needs every row maximum before any column maximum.  A chunk of more than a few queries sweeps K' twice and
 // recomputes S instead of storing it (S would be l_C x N fp32; K' is only N x d_c storage elements).  Both sweeps compute
@@ -144,8 +145,8 @@ constexpr int kQPerBlock = kWaves * kQPerWave;
 // on either side, so that a workgroup has the scores of every window it writes; the first sweep's are the same ones, because a share
 // that the same L2 has seen is read in half the time (the second sweep took 21.1 us instead of 18.5 over other shares, 126 thousand
 // tokens).  With a pooling kernel of its own, which read the scores back and built the selection's histogram (4.9 us), a re-encoded step
-// took 63.3 us instead of 61.0 (40 tokens at 50 thousand), 80.1 / 77.0 (128 at 100), 62.4 / 59.9 (60 at 12), 77.6 / 75.8 (256 at 30) and,
-// bound by power, the same 134 (512 at 130).
+// took 63.3 us instead of 61.0 (40 tokens at 50 thousand), 80.1 / 77.0 (128 at 100), 62.4 / 59.9 (60 at 12), 77.6 / 75.8 (256 at 30) and the same
+// 134 (512 at 130).
 // (score_shares.h: how long a share is, and when.)
 // K' share, column maxima, digit histogram
 __host__ __device__ inline size_t mfma_lds_bytes(int64_t per, int d_c) {
@@ -1089,7 +1090,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                  ScoreTail* tail) {
   const int64_t n = m_hi - m_lo;
   // eps > 0: windows of up to kTailMaxEps on either side are pooled by whatever finishes the scores (score_finish, the second
-  // sweep, or the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
+  // sweep where sweep_pools, or the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
   const bool narrow = eps <= kTailMaxEps;
   bool zeroed = false;                  // the selection's histograms have been zeroed ...
   if (first_hist_done) *first_hist_done = false;        // ... and the first one filled
