@@ -452,6 +452,7 @@ def test_reencoded_attention_of_few_tokens_turns_the_local_keys(esa, B, H, H_kv,
 # other bf16 number shows (7e-4 in the median; products and sums of fp32 err by 1e-5), and a tile encoded with another one's positions gives
 # another key's value.
 @pytest.mark.parametrize("B,H,H_kv,d,l_C,l_L", [(8, 32, 8, 128, 8, 2048), (1, 8, 8, 128, 1, 2048), (4, 16, 8, 64, 15, 2000), (2, 16, 2, 128, 3, 4096),
+                                                (1, 32, 8, 128, 4, 4096), (1, 8, 8, 64, 2, 4096),     # (workgroups of five waves)
                                                 (1, 32, 8, 128, 64, 2048), (1, 16, 8, 64, 100, 1000), (2, 8, 8, 128, 130, 1500)])
 def test_reencoded_rows_are_the_exact_ones_rounded_once(esa, B, H, H_kv, d, l_C, l_L):
     say(f"re-encoded rows rounded once B={B} H={H} H_kv={H_kv} d={d} l_C={l_C} l_L={l_L}")
