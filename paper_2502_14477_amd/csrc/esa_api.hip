@@ -114,9 +114,10 @@ size_t esa_score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
   return score_workspace_bytes(l_c, n_mid, eps, batch);
 }
 
-int esa_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
-              float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* workspace,
-              size_t ws_bytes, void* stream) {
+// patience: see launch_score; 0 but for a test's call.
+static int score_call(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
+                      float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* workspace,
+                      size_t ws_bytes, uint32_t patience, void* stream) {
   if (!dtype_ok(dtype)) ESA_FAIL(ESA_EUNSUPPORTED, "esa_score: dtype %d", dtype);
   if (l_c <= 0 || d_c <= 0 || batch <= 0 || batch > kMaxBatch || eps < 0 || m_lo < 0 || m_hi < m_lo)
     ESA_FAIL(ESA_EINVAL, "esa_score: bad size (l_c=%d d_c=%d batch=%d eps=%d m=[%lld,%lld))", l_c, d_c, batch, eps,
@@ -132,7 +133,20 @@ int esa_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64
     ESA_FAIL(ESA_EWORKSPACE, "esa_score: workspace needs %zu bytes, 256-byte aligned",
              score_workspace_bytes(l_c, m_hi - m_lo, eps, batch));
   return launch_score(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace,
-                      ws_bytes, (hipStream_t)stream);
+                      ws_bytes, (hipStream_t)stream, nullptr, 0, nullptr, nullptr, patience);
+}
+
+int esa_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
+              float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* workspace,
+              size_t ws_bytes, void* stream) {
+  return score_call(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, ws_bytes, 0, stream);
+}
+
+// Not part of the boundary: esa_score whose workgroups wait at most ticks * 10 ns for one another, for the tests.
+ESA_API int esa_internal_score_waiting(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
+                                       float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* workspace,
+                                       size_t ws_bytes, uint32_t ticks, void* stream) {
+  return score_call(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, ws_bytes, ticks + 1, stream);
 }
 
 size_t esa_select_topk_workspace_bytes(int64_t n, int k, int batch) { return topk_workspace_bytes(n, k, batch); }

@@ -112,7 +112,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // instruction t, or t/2, of every wave) is usable once every wave has waited for its own instruction and
 // a barrier has passed; the tiles are consumed as they land, two per barrier.  Queries are the
 // register-resident operand (64 per wave as A fragments for the whole d_c; chunks longer than
-// 512 loop over query blocks against the same LDS tile), so K' is read from memory once per sweep.
+// 512 loop over query blocks against the same LDS tile).  Share and queries stay where they are for the second sweep, so K' is read
+// from memory once, or, where the shares are more than a round of workgroups, once and again all but the last share of each.
+// Up to 256 queries do not give every wave 64 of its own: the waves that hold the same ones share out the tiles.
 //
 // Inside a wave the tiles are software-pipelined: right after the matrix instructions of reduction
 // step ks of tile t have issued, fragment ks of tile t+1 is read from LDS into the registers they
@@ -121,8 +123,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // pipe fed.  With a token per lane, the column maximum of Eq. 4 is an in-lane reduction over the
 // accumulator registers plus one exchange between the two half-waves, folded across waves with an
 // LDS integer maximum on order-preserving keys; the row maximum is kept per register across all
-// tiles and reduced across lanes once, then written as this workgroup's partial row maxima (no
-// atomics across workgroups) for score_rowmax_reduce.
+// tiles and reduced across lanes once.
 //
 // While the share is landing, every LDS access of the tile loop is written as an instruction of its
 // own with its own counter waits: an LDS access the compiler generates is preceded by a wait for ALL
@@ -142,28 +143,31 @@ constexpr int kQPerWave = 32 * kMT;
 constexpr int kQPerBlock = kWaves * kQPerWave;
 
 // eps > 0: the second sweep pools over +-eps (Eq. 8, at most kTailMaxEps).  Shares then lap over their neighbours' by eps tokens
-// on either side, so that a workgroup has the scores of every window it writes; the first sweep's are the same ones, because a share
-// that the same L2 has seen is read in half the time (the second sweep took 21.1 us instead of 18.5 over other shares, 126 thousand
-// tokens).  With a pooling kernel of its own, which read the scores back and built the selection's histogram (4.9 us), a re-encoded step
+// on either side, so that a workgroup has the scores of every window it writes; the first sweep's are the same ones.  With a pooling kernel of its own, which read the scores back and built the selection's histogram (4.9 us), a re-encoded step
 // took 63.3 us instead of 61.0 (40 tokens at 50 thousand), 80.1 / 77.0 (128 at 100), 62.4 / 59.9 (60 at 12), 77.6 / 75.8 (256 at 30) and the same
 // 134 (512 at 130).
 // (score_shares.h: how long a share is, and when.)
-// K' share, column maxima, digit histogram
-__host__ __device__ inline size_t mfma_lds_bytes(int64_t per, int d_c) {
-  return (size_t)per * 32 * d_c * sizeof(bf16_t) + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t);
+// Waves of a workgroup that hold different queries (64 each), a power of two; the others take other tiles for the same ones.
+__host__ inline int query_waves_log2(int l_c) { return l_c > 256 ? 3 : l_c > 128 ? 2 : l_c > 64 ? 1 : 0; }
+__host__ inline int query_waves(int l_c) { return 1 << query_waves_log2(l_c); }
+// The first block of queries comes in through LDS behind the share's first tiles, in the place of those that are requested when it
+// is in registers: as many as leave room, or, where all eight waves hold queries and consume the tiles as they land, four.
+__host__ inline int tiles_before_queries(int per, int d_c, int l_c) {
+  const int room = (160 * 1024) / (64 * d_c) - 2 * query_waves(l_c), first = query_waves(l_c) == kWaves ? 4 : room;
+  return per < first ? per : first;
 }
-// Sweep 0 of a chunk of more than kStageFrom queries brings the first block of them in through LDS, behind the share where
-// they fit beside it.  Fewer waves with queries hold the address unit for less time than the further trip takes.  The score
-// call, us, fragments from memory against LDS: 512 queries 37.3 / 34.8 (128 thousand tokens), 22.7 / 20.8 (48), 17.4 / 15.5 (12);
-// 256 24.3 / 24.1, 16.6 / 16.2, 13.6 / 13.3; 192 22.3 / 22.6, 15.6 / 15.7, 12.8 / 13.0; 77 20.7 / 21.5, 14.2 / 15.0, 11.7 / 12.6.
-constexpr int kStageFrom = 192;
-__host__ __device__ inline bool query_stage_fits(int64_t per, int d_c) { return d_c == 64 || per <= 4; }
-__host__ __device__ inline size_t mfma_sweep0_lds_bytes(int64_t per, int d_c, int l_c) {
-  if (l_c <= kStageFrom) return mfma_lds_bytes(per, d_c);
-  const size_t tile = 32 * d_c * sizeof(bf16_t), share = per * tile, rows = 16 * tile;
-  if (query_stage_fits(per, d_c)) return share + rows;
-  return share + tile > rows ? share + tile : rows;         // (the last tile's step fetches one tile more)
+// That, or the share and behind it the second sweep's column maxima, digit histogram and row maxima.
+__host__ inline size_t sweeps_lds_bytes(int per, int d_c, int l_c) {
+  const size_t tile = 32 * d_c * sizeof(bf16_t), share = per * tile;
+  const size_t staged = (tiles_before_queries(per, d_c, l_c) + 2 * query_waves(l_c)) * tile;
+  const size_t second = share + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t) + (size_t)(kQPerBlock + 4) * sizeof(float);
+  return staged > second ? staged : second;
 }
+// Marks of the shares that are done: sixteen to a word, a word to 256 bytes, and kMuCopies copies of them all, one for the readers on each XCD:
+// whatever reaches one cache line from several XCDs is served one at a time (250 workgroups behind the last one's mark: 7 us with all
+// words in one line, 3.2 with 64 bytes for each, 2.2 with 256).
+constexpr int kMuCopies = 8, kMarksPerWord = 16, kMarkStride = 64;
+__host__ __device__ constexpr int64_t mark_words(int64_t shares) { return (shares + kMarksPerWord - 1) / kMarksPerWord * kMarkStride; }   // of a copy
 // Row maxima of the matrix-core path: one row of mfma_mu_stride(l_c) floats per batch entry, so that groups
 // of four are 16-byte aligned and in bounds for every query tile that holds a query.
 __host__ __device__ inline int mfma_mu_stride(int l_c) { return (l_c + 63) / 64 * 64; }
@@ -177,18 +181,30 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
   else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LEFT) : "memory");
 }
 
-// PASS 0: partial row maxima into part_max[l_c][blocks].  PASS 1: F into score, using mu; with
-// first_hist given, also the histogram of the scores' first digits (radix_hist.h; the scores are in LDS here, so the
-// selection need not read them for it).
-template <int PASS, int DC>
-__global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __restrict__ qc, int l_c,
-                                                            const bf16_t* __restrict__ kc, int64_t m_lo, int64_t n,
-                                                            float* __restrict__ part_max,
-                                                            const float* __restrict__ mu_all,
-                                                            float* __restrict__ score, int64_t q_bs, int64_t kc_bs,
-                                                            int64_t score_bs, int tiles_per_block,
-                                                            uint32_t* __restrict__ first_hist, int64_t first_hist_bs,
-                                                            bf16_t* __restrict__ qfrag, int64_t qfrag_bs, int n_wg, int eps) {
+// The kernel.  Workgroup g owns shares g, g + grid, ... of all rows together (one, where a round of workgroups takes them all).  It
+// finds its shares' row maxima, folds them into mu_keys with atomic maxima, marks the share as done, waits until every share is
+// done, and computes the scores of its shares, the last one of which is still in LDS and its queries still in registers.
+// What bounds it: the matrix instructions of the two tile loops where queries are many (in-kernel stamps, 512 queries over 128 thousand tokens: 3.9 us until
+// the first, 11 + 10.7 of tile loops, 1.5 of waiting for the slowest workgroup's mark, 0.9 for the row maxima, 1.2 of epilogue); the round trips in
+// front of, between and behind them where they are few (77 over 48 thousand: 11.7 in all, 3.3 until the first instruction).
+// As two launches with a kernel between them that reduced partial row maxima, a call paid for that kernel, a second start of all
+// workgroups, a second fetch of the share and of the queries: 20.7 + 4.9 + 19.2 us against 4.9 + 35.5 with score_sweeps_clear (512 queries, 128 thousand
+// tokens), 7.4 + 2.3 + 7.6 against 2.1 + 13.7 (77, 48).  Steps: 101.3 -> 97.2 us, 49.6 -> 46.7; 1024 at 256k 417 -> 407, re-encoded 512 140.5 -> 133.6.
+//
+// The wait needs no other workgroup to be resident: it is bounded by the time the workgroup has been running itself, and a
+// workgroup that has waited so long does the missing shares' row maxima itself, one after the other (the maxima are
+// idempotent; whoever finishes a share marks it), so that every workgroup gets to its end whatever else holds the other compute units.
+//
+// What crosses workgroups inside the launch goes through device-scope atomics only (maxima, marks, and the loads that read them), each
+// wave's maxima complete (vmcnt) before its workgroup's marks: no fence, which would write back an L2 (5 to 10 us).  One copy of
+// the maxima per XCD: maxima on one address are served one at a time, 17 to 30 ns each.
+template <int DC>
+__global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __restrict__ qc, const bf16_t* __restrict__ kc, int n, int l_c_arg,
+                                                              int tiles_per_block, int before_queries, int member_bits, int n_row,
+                                                              int n_shares, int n_wg, int eps, uint32_t* mu_keys, uint32_t* marks,
+                                                              float* __restrict__ score, int64_t q_bs, int64_t kc_bs, int64_t score_bs,
+                                                              uint32_t* __restrict__ first_hist, int64_t first_hist_bs,
+                                                              uint32_t patience) {     // kc: the first middle token's row
   static_assert(DC == 64 || DC == 128, "swizzle and load pattern");
   constexpr int kDc = DC;
   constexpr int kKSteps = kDc / 16;        // MFMA reduction steps per tile
@@ -196,171 +212,134 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
   constexpr int kPieces = kDc / 8;         // 16-byte pieces of a row
   constexpr int kTilesPerLoad = kWaves * 1024 / kTileBytes;           // tiles that one load instruction per wave brings
   constexpr int kLoads = kMaxTilesPerBlock / kTilesPerLoad;           // load instructions of a full share
-  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];   // n_wg: workgroups per batch entry
-  const int tpb = tiles_per_block;
-  const int span = tpb * 32;                                           // tokens of this workgroup
-  uint32_t* colmax = (uint32_t*)(lds_raw + (size_t)tpb * kTileBytes);  // PASS 1: [32 spare + span] keys
-  uint32_t* digit_hist = colmax + 32 + span;                           // PASS 1: [kRadixBins]
-  const int b = __builtin_amdgcn_workgroup_id_y();
-  const bf16_t* q = qc + (int64_t)b * q_bs;
-  const int mu_stride = mfma_mu_stride(l_c);
-  const float* mu = mu_all + (int64_t)b * mu_stride;
-  const int tid = __builtin_amdgcn_workitem_id_x(), lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // uniform: lives in a scalar register
-  const int r = lane & 31, hi = lane >> 5;
-  const int64_t tok_base = (int64_t)__builtin_amdgcn_workgroup_id_x() * (span - 2 * eps) - eps;
-  const char* kshare = (const char*)(kc + (int64_t)b * kc_bs + (m_lo + tok_base) * (int64_t)kDc);
-  const uint32_t first_row = tok_base < 0 ? (uint32_t)-tok_base : 0u;   // rows outside the middle segment repeat its first or last token
-  const uint32_t last_row = (uint32_t)(n - tok_base - 1 < span - 1 ? n - tok_base - 1 : span - 1);
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+  const uint64_t started = __builtin_amdgcn_s_memrealtime();
+  int tpb = tiles_per_block, l_c = l_c_arg;
+  const int span = tpb * 32;                                           // tokens of a share
+  uint32_t* colmax = (uint32_t*)(lds_raw + (size_t)tpb * kTileBytes);  // second sweep: [32 spare + span] keys
+  uint32_t* digit_hist = colmax + 32 + span;                           // [kRadixBins]
+  float* mu_rows = (float*)(digit_hist + kRadixBins);                  // [kWaves][kQPerWave]
+  int* todo = (int*)(mu_rows + kQPerBlock);                            // the share that nobody has done, or -1
+  int wave = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_workitem_id_x() >> 6);      // uniform: lives in a scalar register
+  int n_groups = kWaves >> member_bits, member = wave & ((1 << member_bits) - 1), group = wave >> member_bits;
+  const int wg = __builtin_amdgcn_workgroup_id_x();
+  // The lane's number, taken afresh wherever it is needed outside the tile loop, whose registers are all spoken for: what is
+  // computed from a value that the compiler knows to stay the same it would keep (or spill) through the loop.
+  auto lane_now = [&]() -> int {
+    uint32_t l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return (int)l;
+  };
+  // The same for the scalars that most addresses and conditions follow from: new values, as far as the compiler knows, once per share
+  // (it put 200 instructions in front of the first request).
+  auto scalars_afresh = [&]() { asm volatile("" : "+s"(tpb), "+s"(l_c), "+s"(wave), "+s"(n_groups), "+s"(member), "+s"(group)); };
   const uint32_t lds_tiles = (uint32_t)(uintptr_t)(lds_byte*)lds_raw;  // LDS byte address of the share
   const uint32_t lds_colmax = lds_tiles + (uint32_t)tpb * kTileBytes;
 
+  // the share at hand
+  int b = 0, blk = 0;
+  int tok_base = 0;
+  const char* kshare = nullptr;
+  uint32_t first_row = 0, last_row = 0;                           // rows outside the middle segment repeat its first or last token
+  auto set_share = [&](int s) {
+    b = 0;
+    while (s >= n_row) {
+      s -= n_row;
+      ++b;
+    }
+    blk = s;
+    tok_base = s * (span - 2 * eps) - eps;
+    kshare = (const char*)(kc + (int64_t)tok_base * kDc);
+    if (b > 0) kshare += (int64_t)b * kc_bs * (int64_t)sizeof(bf16_t);
+    first_row = tok_base < 0 ? (uint32_t)-tok_base : 0u;
+    last_row = (uint32_t)(n - 1) - (uint32_t)tok_base;            // below 2^31 + 16
+    last_row = last_row < (uint32_t)(span - 1) ? last_row : (uint32_t)(span - 1);
+  };
+
   bf16x8 a[kMT][kKSteps];
-  float aux[kMT][16];                    // PASS 0: running row maxima.  PASS 1: mu of the lane's rows.
+  float aux[kMT][16];                    // first sweep: running row maxima.  Second: mu of the lane's rows.
   // Rows past the chunk repeat its last query: a repeated row changes no maximum, and its own results
-  // are never written (PASS 0) or are pushed to -inf by mu = +inf (PASS 1).  Register v of tile mt
+  // are never written (first sweep) or are pushed to -inf by mu = +inf (second).  Register v of tile mt
   // belongs to row 8*(v/4) + 4*hi + v%4 of the tile.
   //
-  // The requests for the fragments and (PASS 1) the row maxima are instructions written out here, and so
+  // The requests for the fragments are instructions written out here, and so
   // is the wait that ends them (queries_arrived): had the compiler generated the loads, its own wait for them
   // would be a wait for everything once loads into LDS are outstanding behind them (it does not count on
   // those completing in order with ordinary loads), which would put a round trip in front of the share's
   // requests.  Between request and wait the registers are only named by that wait.
-  f32x4 mu4[kMT][4];
-  int qb_now = 0;
-  auto wave_has_queries = [&](int qb) { return qb * kQPerBlock + wave * kQPerWave < l_c; };
-  // Fragment-ordered copy of Q' in the workspace, [block][wave][tile][step][lane] x 16 bytes: written by the
-  // first workgroups of sweep 0 from their registers (every workgroup holds the same fragments), read by
-  // every workgroup of sweep 1.
-  auto qfrag_of = [&](int qb, int mt) -> bf16_t* {
-    return qfrag + (int64_t)b * qfrag_bs + ((((int64_t)qb * kWaves + wave) * kMT + mt) * kKSteps * 64 + lane) * 8;
-  };
+  auto wave_has_queries = [&](int qb) { return qb * kQPerBlock + member * kQPerWave < l_c; };
   auto request_query_block = [&](int qb) {
-    const int q0 = qb * kQPerBlock + wave * kQPerWave;
-    if (!wave_has_queries(qb)) {          // a wave without queries only takes part in the loads and barriers
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) {
-#pragma unroll
-        for (int ks = 0; ks < kKSteps; ++ks) a[mt][ks] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) mu4[mt][g4] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      }
-      return;
-    }
+    if (!wave_has_queries(qb)) return;    // a wave without queries only takes part in the share's loads and the barriers
+    const bf16_t* q = qc + (int64_t)b * q_bs;
+    const int lane = lane_now(), r = lane & 31, hi = lane >> 5;
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt) {
-      if (PASS == 1) {
-        // the copy of the fragments in register order that sweep 0 left: a wave instruction reads 1 KB in one
-        // piece (eight cache lines) instead of 16 bytes of 32 rows (32 lines), a quarter of the address work
-        const bf16_t* p = qfrag_of(qb, mt);
+      int row = qb * kQPerBlock + member * kQPerWave + 32 * mt + r;
+      row = row < l_c ? row : l_c - 1;
+      const bf16_t* p = q + (int64_t)row * kDc + hi * 8;
 #pragma unroll
-        for (int ks = 0; ks < kKSteps; ++ks) {
-          if (ks < 4) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p), "n"(ks * 1024));
-          else asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p + 2048), "n"((ks & 3) * 1024));
-        }
-      } else {
-        int row = q0 + 32 * mt + r;
-        row = row < l_c ? row : l_c - 1;
-        const bf16_t* p = q + (int64_t)row * kDc + hi * 8;
-#pragma unroll
-        for (int ks = 0; ks < kKSteps; ++ks)
-          asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p), "n"(ks * 32));
-      }
-      if (PASS == 1) {
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int qrow = q0 + 32 * mt + 8 * g4 + 4 * hi;
-          const float* mp = mu + (qrow < mu_stride - 4 ? qrow : mu_stride - 4);
-          asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(mu4[mt][g4]) : "v"(mp));
-        }
-      }
+      for (int ks = 0; ks < kKSteps; ++ks)
+        asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p), "n"(ks * 32));
     }
   };
 #define ESA_QUERY_REGS(mt)                                                                                     \
   "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3]), "+v"(a[mt][kKSteps - 4]), "+v"(a[mt][kKSteps - 3]), \
       "+v"(a[mt][kKSteps - 2]), "+v"(a[mt][kKSteps - 1])
 #define ESA_QUERY_REGS_SHORT(mt) "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3])
-#define ESA_MU_REGS(mt) "+v"(mu4[mt][0]), "+v"(mu4[mt][1]), "+v"(mu4[mt][2]), "+v"(mu4[mt][3])
   // Everything requested before the share has arrived once at most all but (16 / d_c-dependent) two tiles' worth of
   // the share's requests are outstanding (first block; tiles 0 and 1 are in LDS then as well), or nothing at all
   // (later blocks).
   constexpr int kLeftFirst = kLoads - 2 / kTilesPerLoad;
   auto queries_arrived = [&](bool first) {
     if constexpr (kKSteps == 8) {
-      if (PASS == 0) {
-        if (first) asm volatile("s_waitcnt vmcnt(%c16)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1) : "n"(kLeftFirst));
-        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1));
-      } else {
-        if (first) asm volatile("s_waitcnt vmcnt(%c24)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1), ESA_MU_REGS(0), ESA_MU_REGS(1) : "n"(kLeftFirst));
-        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1), ESA_MU_REGS(0), ESA_MU_REGS(1));
-      }
+      if (first) asm volatile("s_waitcnt vmcnt(%c16)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1) : "n"(kLeftFirst));
+      else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1));
     } else {
-      if (PASS == 0) {
-        if (first) asm volatile("s_waitcnt vmcnt(%c8)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1) : "n"(kLeftFirst));
-        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1));
-      } else {
-        if (first) asm volatile("s_waitcnt vmcnt(%c16)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1), ESA_MU_REGS(0), ESA_MU_REGS(1) : "n"(kLeftFirst));
-        else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1), ESA_MU_REGS(0), ESA_MU_REGS(1));
-      }
+      if (first) asm volatile("s_waitcnt vmcnt(%c8)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1) : "n"(kLeftFirst));
+      else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1));
     }
-#pragma unroll
-    for (int mt = 0; mt < kMT; ++mt)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        if (PASS == 0) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) aux[mt][4 * g4 + e] = -INFINITY;
-        } else {
-          const int qrow = (qb_now * kQPerBlock + wave * kQPerWave) + 32 * mt + 8 * g4 + 4 * hi;
-          const f32x4 m4 = mu4[mt][g4];
-          aux[mt][4 * g4 + 0] = qrow + 0 < l_c ? m4.x : INFINITY;
-          aux[mt][4 * g4 + 1] = qrow + 1 < l_c ? m4.y : INFINITY;
-          aux[mt][4 * g4 + 2] = qrow + 2 < l_c ? m4.z : INFINITY;
-          aux[mt][4 * g4 + 3] = qrow + 3 < l_c ? m4.w : INFINITY;
-        }
-      }
   };
 #undef ESA_QUERY_REGS
 #undef ESA_QUERY_REGS_SHORT
-#undef ESA_MU_REGS
 
-  // ---- the pipeline over this workgroup's tiles
+  // ---- the pipeline over a share's tiles
   bf16x8 bfr[kKSteps];
   f32x16 acc0[kMT], acc1[kMT];
   // LDS byte address of this lane's fragment ks of tile nt: row r, slot (2 ks + hi) ^ swizzle(r).  The share
   // starts at a multiple of 256 bytes, so the slot's ks bits can be XORed into the address of fragment 0.
   auto swizzle = [](uint32_t row) { return kDc == 128 ? row & 15 : (row >> 1) & 7; };
-  const uint32_t frag0_at = lds_tiles + (uint32_t)r * (kDc * 2) + (uint32_t)((hi ^ swizzle(r)) * 16);
+  const uint32_t first_lane = __builtin_amdgcn_workitem_id_x() & 63, frag_row = first_lane & 31;
+  const uint32_t frag0_at = lds_tiles + frag_row * (kDc * 2) + ((first_lane >> 5) ^ swizzle(frag_row)) * 16;
+  const uint32_t colmax_at = lds_colmax + frag_row * 4;
   auto read_fragment = [&](int nt, int ks) {
     asm volatile("ds_read_b128 %0, %1" : "=v"(bfr[ks]) : "v"((frag0_at ^ (uint32_t)(ks * 32)) + (uint32_t)nt * kTileBytes));
   };
   float best = -INFINITY;
   // One reduction step's share of the maximum / subtract work on a finished tile's accumulators.
-  auto epilogue_part = [&](f32x16 (&P)[kMT], int part) {
+  auto epilogue_part = [&](auto sweep, f32x16 (&P)[kMT], int part) {
     constexpr int kShare = 16 * kMT / kKSteps;
 #pragma unroll
     for (int e = kShare * part; e < kShare * (part + 1); ++e) {
       const int mt = e / 16, v = e % 16;
-      if (PASS == 0) aux[mt][v] = fmaxf(aux[mt][v], P[mt][v]);
+      if (decltype(sweep)::value == 0) aux[mt][v] = fmaxf(aux[mt][v], P[mt][v]);
       else best = fmaxf(best, P[mt][v] - aux[mt][v]);
     }
   };
-  auto epilogue_end = [&](int nt) {
-    if (PASS == 1) {
+  auto epilogue_end = [&](auto sweep, int nt) {
+    if (decltype(sweep)::value == 1) {
       // The other half-wave's maximum for the same token: a lane swap in the vector unit (an LDS-routed
       // shuffle would put a wait for every outstanding fragment read into each tile).  Both halves then hold
       // the column maximum and both fold it into LDS: an integer maximum, exact and order-free.
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
       best = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      asm volatile("ds_max_u32 %0, %1" ::"v"(lds_colmax + (uint32_t)(32 * (nt + 1) + r) * 4), "v"(ordered_key(best)) : "memory");
+      asm volatile("ds_max_u32 %0, %1" ::"v"(colmax_at + (uint32_t)(nt + 1) * 128), "v"(ordered_key(best)) : "memory");
       best = -INFINITY;
     }
   };
-  // Tile nt into C; meanwhile the fragments of tile nt+1 are fetched and the epilogue of tile nt-1, held in
-  // P, is done.  The first tile's "previous tile" is a set of -inf (its column maxima go to the spare slots in
-  // front of colmax); behind the last tile the fetch reads what follows the share in LDS and nothing uses it:
-  // every step is the same code.
-  auto step = [&](int nt, f32x16 (&C)[kMT], f32x16 (&P)[kMT]) {
+  // The tile whose fragments have been read into C; meanwhile the fragments of tile `next` are fetched and the epilogue of tile
+  // `prev`, held in P, is done.  The first tile's "previous tile" is a set of -inf (its column maxima go to the spare slots in
+  // front of colmax); behind the last tile it is fetched again and nothing uses it: every step is the same code.
+  auto step = [&](auto sweep, int next, int prev, f32x16 (&C)[kMT], f32x16 (&P)[kMT]) {
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < kKSteps; ++ks) {
@@ -368,10 +347,10 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
 #pragma unroll
       for (int mt = 0; mt < kMT; ++mt)
         C[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][ks], bfr[ks], ks == 0 ? zero : C[mt], 0, 0, 0);
-      read_fragment(nt + 1, ks);
-      epilogue_part(P, ks);
+      read_fragment(next, ks);
+      epilogue_part(sweep, P, ks);
     }
-    epilogue_end(nt - 1);
+    epilogue_end(sweep, prev);
     __builtin_amdgcn_sched_barrier(0);                       // a tile's work stays inside its step
   };
   // streaming: the share is still landing.  Tiles become usable in growing groups: 0-1 behind the barrier in
@@ -385,37 +364,48 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     else if (nt == 2) wait_loads_then_barrier<kLoads - 8 / kTilesPerLoad>();
     else wait_loads_then_barrier<0>();
   };
-  auto run_tiles = [&](bool streaming, bool active) {
+  auto run_tiles = [&](auto sweep, bool streaming, bool active) {
     if (!active) {
       if (streaming)
         for (int nt = 0; nt + 2 < tpb && nt <= 6; nt += nt + 2) next_group(nt);
       return;
     }
+    // Group g takes tiles g, g + n_groups, ..., an even number of them, where need be the last tile again (no maximum changes).
+    const int last = tpb - 1, steps = (((tpb + n_groups - 1) >> (3 - member_bits)) + 1) & ~1;
+    auto tile_of = [&](int i) { return group + i * n_groups < last ? group + i * n_groups : last; };
+    const int first = tile_of(0);
 #pragma unroll
-    for (int ks = 0; ks < kKSteps; ++ks) read_fragment(0, ks);
+    for (int ks = 0; ks < kKSteps; ++ks) read_fragment(first, ks);
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc1[mt][v] = -INFINITY;
     __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0), where the compiler sees it: not inside the loop
-    for (int nt = 0; nt < tpb; nt += 2) {
-      step(nt, acc0, acc1);
+    int prev = -1, even = first;
+    for (int nt = 0; nt < steps; nt += 2) {
+      const int odd = tile_of(nt + 1);
+      step(sweep, odd, prev, acc0, acc1);
       if (streaming && nt + 2 < tpb && (nt == 0 || nt == 2 || nt == 6))
         next_group(nt);
-      step(nt + 1, acc1, acc0);
+      const int next = tile_of(nt + 2);
+      step(sweep, next, even, acc1, acc0);
+      prev = odd;
+      even = next;
     }
 #pragma unroll
-    for (int ks = 0; ks < kKSteps; ++ks) epilogue_part(acc1, ks);
-    epilogue_end(tpb - 1);
+    for (int ks = 0; ks < kKSteps; ++ks) epilogue_part(sweep, acc1, ks);
+    epilogue_end(sweep, prev);
   };
 
-  // PASS 0: 32 running maxima per lane, each to be reduced over the 32 lanes of a half-wave: a butterfly
+  // First sweep: 32 running maxima per lane, each to be reduced over the 32 lanes of a half-wave: a butterfly
   // that halves the number of values per step (31 exchanges instead of 160).  Every exchange is a vector-unit
   // move: the two 16-lane rows of the half-wave swap (v_permlane16_swap hands both directions over at once),
   // then inside a row lane i pairs with i ^ 8 (row rotation by 8), with 7 - i inside its group of eight
   // (half-row mirror), with i ^ 1 and with i ^ 2 (quad permutations).  The side a lane keeps is decided by its
   // bits 4, 3, 2, 0, 1 in that order, so lane r ends up with value (r & 28) | (r & 1) << 1 | (r >> 1) & 1.
-  auto flush_row_maxima = [&](int q0) {
+  // A wave without queries only takes part in the barrier.
+  auto flush_row_maxima = [&](int q0, bool active) {
+    const int lane = lane_now(), r = lane & 31, hi = lane >> 5;
     float red[32];
 #pragma unroll
     for (int i = 0; i < 32; ++i) red[i] = aux[i / 16][i % 16];
@@ -440,136 +430,232 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
 #undef ESA_EXCHANGE_STEP
     const int held = (r & 28) | ((r & 1) << 1) | ((r >> 1) & 1);
     const int mt = held / 16, v = held % 16;
-    const int qrow = q0 + 32 * mt + 8 * (v / 4) + 4 * hi + (v % 4);
-    // 32-bit index (batch x l_c x workgroups stays far below 2^32): scalar base + lane offset, no 64-bit address
-    // to carry through the tile loop
-    if (qrow < l_c) part_max[((uint32_t)b * (uint32_t)l_c + (uint32_t)qrow) * (uint32_t)n_wg + __builtin_amdgcn_workgroup_id_x()] = red[0];
+    const int in_wave = 32 * mt + 8 * (v / 4) + 4 * hi + (v % 4), qrow = q0 + in_wave;
+    uint32_t key = ordered_key(red[0]);
+    if (n_groups > 1) {                // the groups' maxima meet in LDS: one operation per row and workgroup
+      uint32_t* rows = (uint32_t*)mu_rows + member * kQPerWave + in_wave;
+      rows[group * (kQPerWave << member_bits)] = key;
+      __syncthreads();
+      if (group > 0) return;
+      for (int g = 1; g < n_groups; ++g) {
+        const uint32_t other = rows[g * (kQPerWave << member_bits)];
+        key = key > other ? key : other;
+      }
+    }
+    if (!active) return;
+    if (qrow < l_c)
+      __hip_atomic_fetch_max(&mu_keys[((int64_t)b * kMuCopies + wg % kMuCopies) * mfma_mu_stride(l_c) + qrow], key, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
   };
 
-  // ---- requests, in the order their results are needed (loads complete in order): query fragments and row
-  // maxima, then the K' share.  Instruction i of wave w fills row group 8*i + w (four or eight rows, 1 KB of
+  // ---- requests, in the order their results are needed (loads complete in order): query fragments, then the
+  // K' share.  Instruction i of wave w fills row group 8*i + w (four or eight rows, 1 KB of
   // LDS); a lane fetches, for its slot of its row of the group, the piece that undoes the swizzle.
   // Rows past an end of the middle segment repeat its last (first) token (no maximum changes, nothing of theirs
   // is stored); shares shorter than sixteen tiles repeat their last instruction, identical data to an
   // identical place, so that the count of outstanding loads means the same in every workgroup.
-  if (PASS == 1) {
-    for (int i = tid; i < span + 32; i += kThreads) colmax[i] = kOrderedKeyOfMinusInf;
-    if (first_hist)
-      for (int i = tid; i < kRadixBins; i += kThreads) digit_hist[i] = 0u;
-  }
-  const uint32_t row_in_load = (64 / kPieces) * wave + lane / kPieces;
-  const uint32_t piece = (lane % kPieces) ^ swizzle(row_in_load);
   auto request_share = [&](int from, int to) {
+    const int lane = lane_now();
+    const uint32_t row_in_load = (64 / kPieces) * wave + lane / kPieces;
+    const uint32_t piece = (lane % kPieces) ^ swizzle(row_in_load);
     const int n_loads = tpb / kTilesPerLoad;                 // tpb is even
-#pragma unroll
+#pragma unroll 1
     for (int i = from; i < to; ++i) {
       const int t = i < n_loads ? i : n_loads - 1;
       uint32_t row = 32 * kTilesPerLoad * t + row_in_load;
       row = row < last_row ? row : last_row;
       row = row > first_row ? row : first_row;
-      __builtin_amdgcn_global_load_lds((global_void*)(kshare + (size_t)row * (kDc * sizeof(bf16_t)) + piece * 16),
+      __builtin_amdgcn_global_load_lds((global_void*)(kshare + (row * (uint32_t)(kDc * sizeof(bf16_t)) + piece * 16)),
                                        (lds_void*)(lds_raw + (size_t)(8 * t + wave) * 1024), 16, 0, 0);
     }
   };
-  const bool room = query_stage_fits(tpb, kDc);
-  if (PASS == 0 && l_c > kStageFrom) {
-    // The first query block comes in through LDS, whole rows of 256 (128) bytes, four (eight) to an instruction, into a place
-    // of each wave's own; read as fragments, 16 bytes of 32 rows to an instruction, it held the address unit for 2 us before
-    // the share's first request got through.  Behind a short share there is room for all of it; beside a long one half the
-    // rows at a time take the place of tiles 8 to 15, which are requested when every wave is done with it.
-    constexpr int kRowsPerLoad = 64 / kPieces, kTileLoads = 32 / kRowsPerLoad;
-    const uint32_t stage = room ? (uint32_t)(tpb * kTileBytes + wave * kMT * kTileBytes) : (uint32_t)(kWaves * kTileBytes + wave * kTileBytes);
-    auto request_rows = [&](int mt, uint32_t to) {
-#pragma unroll
-      for (int i = 0; i < kTileLoads; ++i) {
-        const uint32_t in_tile = kRowsPerLoad * i + lane / kPieces;
-        int row = wave * kQPerWave + 32 * mt + (int)in_tile;
-        row = row < l_c ? row : l_c - 1;
-        __builtin_amdgcn_global_load_lds((global_void*)(q + (int64_t)row * kDc + ((lane % kPieces) ^ swizzle(in_tile)) * 8),
-                                         (lds_void*)(lds_raw + to + 1024 * i), 16, 0, 0);
+  // Brings in the share at hand and, where `queries`, the first block of them.  When it returns the queries are in registers and, with one
+  // group, tiles 0 and 1 in LDS; with several all tiles.
+  // The queries come through LDS, whole rows of 256 (128) bytes, four (eight) to an instruction: read as fragments, 16 bytes
+  // of 32 rows to an instruction, 512 of them held the address unit for 2 us before the share's first request got through.
+  auto begin = [&](bool queries) {
+    constexpr int kRowsPerLoad = 64 / kPieces, kRowLoads = kQPerWave / kRowsPerLoad;
+    const int before = queries ? before_queries : kMaxTilesPerBlock;
+    const uint32_t stage = (uint32_t)((before + member * kMT) * kTileBytes);
+    if (queries) {
+      const int lane = lane_now();
+      const char* q = (const char*)(qc + (int64_t)b * q_bs);
+#pragma unroll 1
+      for (int i = group; i < kRowLoads; i += n_groups) {
+        const uint32_t mine = kRowsPerLoad * i + lane / kPieces;
+        uint32_t row = member * kQPerWave + mine;
+        row = row < (uint32_t)l_c ? row : (uint32_t)l_c - 1;
+        __builtin_amdgcn_global_load_lds((global_void*)(q + (row * (uint32_t)(kDc * sizeof(bf16_t)) + ((lane % kPieces) ^ swizzle(mine)) * 16)),
+                                         (lds_void*)(lds_raw + stage + 1024 * i), 16, 0, 0);
       }
-    };
-    auto read_rows = [&](int mt, uint32_t from) {             // requests and wait in one block: the registers are complete behind it
-      const uint32_t at = frag0_at + from;
-      if constexpr (kKSteps == 8)
-        asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-                     "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3]), "=&v"(a[mt][kKSteps - 4]),
-                       "=&v"(a[mt][kKSteps - 3]), "=&v"(a[mt][kKSteps - 2]), "=&v"(a[mt][kKSteps - 1])
-                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u), "v"(at ^ 224u)
-                     : "memory");
-      else
-        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3])
-                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u)
-                     : "memory");
-    };
-    auto landed = [&](auto left) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(left)::value) : "memory"); };
-    static_assert(kMT == 2, "two tiles of queries");
-    if (room) {
-      request_rows(0, stage);
-      request_rows(1, stage + kTileBytes);
-      request_share(0, kLoads);
-      landed(std::integral_constant<int, kLoads>());
-      read_rows(0, stage);
-      read_rows(1, stage + kTileBytes);
-      wait_loads_then_barrier<kLeftFirst>();                 // tiles 0 and 1
+    }
+    const int first_loads = queries && before < tpb ? before / kTilesPerLoad : kLoads;
+    request_share(0, first_loads);
+    if (queries) {
+      if (n_groups == 1) {                                     // a wave reads what it has requested itself
+        if (first_loads == kLoads) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 / kTilesPerLoad) : "memory");
+      } else {
+        wait_loads_then_barrier<0>();
+      }
+#pragma unroll
+      for (int mt = 0; mt < kMT; ++mt) {                       // requests and wait in one block: the registers are complete behind it
+        const uint32_t at = frag0_at + stage + mt * kTileBytes;
+        if constexpr (kKSteps == 8)
+          asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                       "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                       : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3]), "=&v"(a[mt][kKSteps - 4]),
+                         "=&v"(a[mt][kKSteps - 3]), "=&v"(a[mt][kKSteps - 2]), "=&v"(a[mt][kKSteps - 1])
+                       : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u), "v"(at ^ 224u)
+                       : "memory");
+        else
+          asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                       : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3])
+                       : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u)
+                       : "memory");
+      }
+    }
+    if (first_loads < kLoads) {
+      wait_loads_then_barrier<2 / kTilesPerLoad>();            // tiles 0 and 1 of four; every wave has its queries
+      request_share(first_loads, kLoads);
+      if (n_groups > 1) wait_loads_then_barrier<0>();
+    } else if (n_groups == 1) {
+      wait_loads_then_barrier<kLeftFirst>();                   // tiles 0 and 1
     } else {
-      request_rows(0, stage);
-      request_share(0, kLoads / 2);
-      landed(std::integral_constant<int, kLoads / 2>());
-      read_rows(0, stage);
-      request_rows(1, stage);
-      landed(std::integral_constant<int, 0>());              // the first half of the share, too
-      read_rows(1, stage);
-      wait_loads_then_barrier<0>();
-      request_share(kLoads / 2, kLoads);
+      wait_loads_then_barrier<0>();                            // all tiles; every wave has its queries
     }
+  };
+
+  int in_regs = 0, in_regs_row = -1;     // the query block in registers, and whose
+  // One sweep over the share at hand, all query blocks (chunks longer than 512 tokens have several): first the one in registers.
+  auto sweep_share = [&](auto sweep, bool streaming) {
+    const int n_blocks = (l_c + kQPerBlock - 1) / kQPerBlock;
+    for (int i = 0; i < n_blocks; ++i) {
+      if (i > 0) {
+        in_regs = in_regs + 1 < n_blocks ? in_regs + 1 : 0;
+        request_query_block(in_regs);
+        queries_arrived(false);
+      }
+      const bool active = wave_has_queries(in_regs);
+      if (decltype(sweep)::value == 0) {
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt)
+        for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) aux[mt][v] = -INFINITY;
-  } else {
-    request_query_block(0);
-    __builtin_amdgcn_sched_barrier(0);
-    request_share(0, kLoads);
-    __builtin_amdgcn_sched_barrier(0);
-    queries_arrived(true);
-    wait_loads_then_barrier<kLeftFirst, true>();               // tiles 0 and 1 (and this wave's LDS writes above)
+          for (int v = 0; v < 16; ++v) aux[mt][v] = -INFINITY;
+      } else if (active) {
+        const int lane = lane_now(), hi = lane >> 5, row = in_regs * kQPerBlock + member * kQPerWave + lane;      // < mu_stride
+        const int mu_stride = mfma_mu_stride(l_c);
+        uint32_t* p = mu_keys + (int64_t)b * kMuCopies * mu_stride + row;
+        uint32_t key[kMuCopies];
+#pragma unroll
+        for (int c = 0; c < kMuCopies; ++c) key[c] = __hip_atomic_load(p + c * mu_stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int c = 1; c < kMuCopies; ++c) key[0] = key[0] > key[c] ? key[0] : key[c];
+        float* mine = mu_rows + wave * kQPerWave;
+        mine[lane] = row < l_c ? ordered_key_to_f32(key[0]) : INFINITY;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            const f32x4 m4 = *(const f32x4*)(mine + 32 * mt + 8 * g4 + 4 * hi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) aux[mt][4 * g4 + e] = m4[e];
+          }
+      }
+      run_tiles(sweep, streaming && i == 0 && n_groups == 1, active);
+      if (decltype(sweep)::value == 0 && (active || n_groups > 1)) flush_row_maxima(in_regs * kQPerBlock + member * kQPerWave, active);
+    }
+  };
+
+  // ---- first sweep, and the wait
+  int share = wg, own = wg, at_hand;
+  bool waiting = false;
+  uint64_t give_up = 0;
+  for (;;) {
+    scalars_afresh();
+    set_share(share);
+    at_hand = share;
+    const bool queries = in_regs_row != b;
+    begin(queries);
+    if (queries) in_regs = 0;
+    in_regs_row = b;
+    sweep_share(std::integral_constant<int, 0>(), true);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // this wave's maxima are in mu_keys
+    __syncthreads();
+    const int lane = lane_now(), tid = 64 * wave + lane;
+    uint32_t* my_marks = marks + wg % kMuCopies * mark_words(n_shares);
+    if (tid < kMuCopies)
+      __hip_atomic_fetch_or(&marks[tid * mark_words(n_shares) + share / kMarksPerWord * kMarkStride], 1u << (share % kMarksPerWord), __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
+    if (!waiting && share + n_wg < n_shares) {
+      own = share += n_wg;
+      continue;
+    }
+    for (int i = tid; i < span + 32; i += kThreads) colmax[i] = kOrderedKeyOfMinusInf;
+    for (int i = tid; i < kRadixBins; i += kThreads) digit_hist[i] = 0u;
+    if (wave == 0) {
+      if (!waiting) {
+        const uint64_t now = __builtin_amdgcn_s_memrealtime();     // 10 ns
+        give_up = now + (patience ? patience - 1 : (now - started) + 500);
+      }
+      int missing = -1;
+      auto marks_from = [&](int c) {                              // the lane's word: the bits of shares
+        const int here = n_shares - c - lane * kMarksPerWord;
+        return here >= kMarksPerWord ? (1u << kMarksPerWord) - 1u : here > 0 ? (1u << here) - 1u : 0u;
+      };
+      uint32_t open = marks_from(0);
+      for (int c = 0; c < n_shares;) {                            // 64 words of marks at a time; a word that is complete is not read again
+        const int of = c + lane * kMarksPerWord;
+        if (open != 0u) open &= ~__hip_atomic_load(&my_marks[of / kMarksPerWord * kMarkStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t lanes = __ballot(open != 0u);
+        if (lanes == 0) {
+          c += 64 * kMarksPerWord;
+          open = marks_from(c);
+        } else if (__builtin_amdgcn_s_memrealtime() >= give_up) {
+          // lanes in turn from one of the workgroup's own: those that give up together take different shares
+          const int turn = (wg * 29) & 63;
+          const uint64_t turned = (lanes >> turn) | (turn ? lanes << (64 - turn) : 0);
+          const int l = (__ffsll((long long)turned) - 1 + turn) & 63;
+          missing = __builtin_amdgcn_readlane(of + __ffs((int)open) - 1, l);
+          break;
+        } else {
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+      if (lane == 0) *todo = missing;
+    }
+    __syncthreads();
+    const int missing = __builtin_amdgcn_readfirstlane(*todo);
+    if (missing < 0) break;
+    waiting = true;
+    share = missing;
+    __syncthreads();                                              // *todo is read
   }
 
-  // ---- query blocks (chunks longer than 512 tokens take several); from the second on, the share is in LDS
-  for (int qb = 0; qb * kQPerBlock < l_c; ++qb) {
-    if (qb > 0) {
-      qb_now = qb;
-      request_query_block(qb);
-      queries_arrived(false);
+  // ---- second sweep: own shares, the last one first
+  for (;; own -= n_wg) {
+    scalars_afresh();
+    if (own != at_hand) {
+      set_share(own);
+      const bool queries = in_regs_row != b;
+      begin(queries);
+      if (queries) in_regs = 0;
+      in_regs_row = b;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      const int tid = 64 * wave + lane_now();
+      for (int i = tid; i < span + 32; i += kThreads) colmax[i] = kOrderedKeyOfMinusInf;
+      for (int i = tid; i < kRadixBins; i += kThreads) digit_hist[i] = 0u;
+      __syncthreads();
     }
-    run_tiles(qb == 0, wave_has_queries(qb));
-    if (PASS == 0 && wave_has_queries(qb)) {      // the sixteen fragments are shared out over the first workgroups
-      // The lane number is taken afresh here: an address computed at the top of the kernel would be one more
-      // value to keep (or spill) through the tile loop, whose registers are all spoken for.
-      // fragment i goes out from workgroup i (from workgroup 0 on a tiny grid)
-      uint32_t lane_now;
-      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane_now));
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt)
-#pragma unroll
-        for (int ks = 0; ks < kKSteps; ++ks)
-          if (mt * kKSteps + ks == (int)__builtin_amdgcn_workgroup_id_x() || (__builtin_amdgcn_workgroup_id_x() == 0 && mt * kKSteps + ks >= n_wg))
-            *(bf16x8*)(qfrag + (int64_t)b * qfrag_bs + ((((int64_t)qb * kWaves + wave) * kMT + mt) * kKSteps + ks) * 512 +
-                       lane_now * 8) = a[mt][ks];
-    }
-    if (PASS == 0 && wave_has_queries(qb)) flush_row_maxima(qb * kQPerBlock + wave * kQPerWave);
-    if (qb == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // repeated instructions of a short share
-  }
-
-  if (PASS == 1) {
+    sweep_share(std::integral_constant<int, 1>(), false);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // this wave's column maxima are in LDS
     __syncthreads();
+    const int tid = 64 * wave + lane_now();
     for (int i0 = 0; i0 < span; i0 += kThreads) {          // whole waves stay in step for hist_add
       const int i = i0 + tid;
-      const int64_t m = tok_base + i;
+      const int64_t m = (int64_t)tok_base + i;
       const bool ok = i >= eps && i < span - eps && m < n;
       uint32_t key = ok ? colmax[32 + i] : 0u;
       if (ok)                              // (a repeated token only meets windows that hold it)
@@ -583,38 +669,27 @@ __global__ __launch_bounds__(kThreads) void score_mfma_bf16(const bf16_t* __rest
     }
     if (first_hist) {
       __syncthreads();
-      uint32_t* gh = first_hist + (int64_t)b * first_hist_bs;
-      hist_flush(gh, digit_hist, __builtin_amdgcn_workgroup_id_x(), tid, kThreads);
+      hist_flush(first_hist + (int64_t)b * first_hist_bs, digit_hist, blk, tid, kThreads);
     }
+    if (own < n_wg) break;
+    at_hand = -1;
+    __syncthreads();                                       // the LDS is free for the next share
   }
 }
 
-// mu[c] = max over workgroups of their partial row maxima ([l_c][blocks] layout): one wave per query.
-// Running between the two sweeps, it also zeroes the selection's histograms when given them.
-__global__ __launch_bounds__(256) void score_rowmax_reduce(const float* __restrict__ part_max, int nblk, int l_c,
-                                                           float* __restrict__ mu, int mu_stride,
-                                                           uint32_t* __restrict__ hists, int64_t hists_bs) {
-  const int lane = __builtin_amdgcn_workitem_id_x() & 63;
-  const int c = __builtin_amdgcn_workgroup_id_x() * 4 + (__builtin_amdgcn_workitem_id_x() >> 6);
-  const int b = __builtin_amdgcn_workgroup_id_y();
-  if (hists)
-    for (int i = __builtin_amdgcn_workgroup_id_x() * 256 + __builtin_amdgcn_workitem_id_x(); i < kHistWords; i += (l_c + 3) / 4 * 256)
-      hists[(int64_t)b * hists_bs + i] = 0u;                 // (l_c + 3) / 4 workgroups of 256 threads
-  if (c >= l_c) return;
-  const float* p = part_max + ((int64_t)b * l_c + c) * nblk;
-  float m = -INFINITY;
-  for (int i0 = lane; i0 < nblk; i0 += 4 * 64) {      // four loads in flight per lane (256 workgroups per trip)
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + 64 * u;
-      v[u] = p[i < nblk ? i : lane];
-      if (i >= nblk) v[u] = -INFINITY;
-    }
-    m = fmaxf(fmaxf(m, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
+// In front of the sweeps: mu_keys and the marks, and the selection's histograms, cleared.  (A kernel of its own, 2 us: nothing that a call finds in its
+// workspace says whether another workgroup has cleared it already.)
+__global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ own, int64_t n_own, uint32_t* __restrict__ hists,
+                                                          int64_t hists_bs, int batch) {
+  const int64_t i = (int64_t)__builtin_amdgcn_workgroup_id_x() * 256 + __builtin_amdgcn_workitem_id_x();
+  const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+  if (i < n_own) {
+    own[i] = zero;
+    return;
   }
-  m = wave_max(m);
-  if (lane == 0) mu[(int64_t)b * mu_stride + c] = m;
+  constexpr int kRow = kHistWords / 4;
+  const int64_t j = i - n_own;
+  if (hists && j < (int64_t)kRow * batch) *(uint4*)(hists + j / kRow * hists_bs + j % kRow * 4) = zero;
 }
 
 // ------------------------------------------------------------------------------------------ decode (l_c = 1)
@@ -1039,47 +1114,41 @@ __host__ inline size_t stored_bytes(int l_c, int64_t n, int batch) {
   return l_c > 1 && stores_scores(l_c, n, batch) ? (size_t)l_c * stored_ld(n) * 4 * batch : 0;
 }
 
-__host__ inline size_t part_bytes(int l_c, int64_t n_mid, int eps, int batch) {
-  size_t blocks = (size_t)most_shares(n_mid, eps <= kTailMaxEps ? eps : 0, batch) * l_c;       // of all rows
-  if (stores_scores(l_c, n_mid, batch)) {   // a partial maximum per query and workgroup of at least 64 tokens
-    const size_t stored = (size_t)((n_mid + kGTok - 1) / kGTok) * l_c * batch;
-    blocks = stored > blocks ? stored : blocks;
-  }
-  return align_up(blocks * 4, 256);
+// partial row maxima of the kernels that store S: one per query and workgroup of at least 64 tokens
+__host__ inline size_t part_bytes(int l_c, int64_t n_mid, int batch) {
+  return stores_scores(l_c, n_mid, batch) ? align_up((size_t)((n_mid + kGTok - 1) / kGTok) * l_c * batch * 4, 256) : 0;
+}
+// what the sweeps need cleared: the copies of the row maxima, a mark for every share
+__host__ inline size_t mu_copies_bytes(int l_c, int batch) { return mu_bytes(l_c, batch) * kMuCopies; }
+__host__ inline size_t sweeps_bytes(int l_c, int64_t n_mid, int eps, int batch) {
+  return mu_copies_bytes(l_c, batch) + (size_t)mark_words(most_shares(n_mid, eps <= kTailMaxEps ? eps : 0, batch)) * kMuCopies * 4;
 }
 
-// fragment-ordered copy of Q' (matrix-core path): whole blocks of 512 queries, 256 bytes each
-__host__ inline size_t qfrag_bytes_per_batch(int l_c) {
-  return l_c > 1 ? (size_t)((l_c + kQPerBlock - 1) / kQPerBlock) * kQPerBlock * 128 * sizeof(bf16_t) : 0;
-}
-
-// The two sweeps of the matrix-core path and the reduction between them.
+// The two sweeps of the matrix-core path.  patience: 0, or 1 + how long (10 ns) a workgroup waits for the others.
 template <int DC>
-int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int64_t n, float* part, float* mu, float* score,
-                  int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, uint32_t* hists, bool fill_first, int64_t hists_bs,
-                  bf16_t* qfrag, int64_t qfrag_bs, int eps, hipStream_t st) {
-  const int per = (int)share_tiles(n, eps, batch), nblk = (int)share_count(n, eps, batch);
-  const dim3 grid(nblk, batch);
-  const size_t lds = mfma_lds_bytes(per, DC), most = mfma_lds_bytes(kMaxTilesPerBlock, DC);
-  const size_t most0 = mfma_sweep0_lds_bytes(DC == 64 ? kMaxTilesPerBlock : 4, DC, kQPerBlock);          // 128 and 160 KB
-  static_assert(kQPerBlock == 512, "mfma_sweep0_lds_bytes");
+int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int64_t n, void* ws, float* score, int batch, int64_t q_bs,
+                  int64_t kc_bs, int64_t score_bs, uint32_t* hists, bool fill_first, int64_t hists_bs, int eps, uint32_t patience, hipStream_t st) {
+  const int per = (int)share_tiles(n, eps, batch), n_row = (int)share_count(n, eps, batch);
+  const int64_t n_shares = (int64_t)n_row * batch;
+  const int n_wg = (int)(n_shares < kComputeUnits ? n_shares : kComputeUnits);
   static OncePerDevice raised;
-  const int rc = raise_lds_limit(raised, {(const void*)score_mfma_bf16<0, DC>, (const void*)score_mfma_bf16<1, DC>},
-                                 most > most0 ? most : most0, "score_mfma_bf16");
+  const int rc = raise_lds_limit(raised, {(const void*)score_sweeps_bf16<DC>}, 160 * 1024, "score_sweeps_bf16");
   if (rc != ESA_OK) return rc;
-  score_mfma_bf16<0, DC><<<grid, kThreads, mfma_sweep0_lds_bytes(per, DC, l_c), st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per, nullptr,
-                                                      0, qfrag, qfrag_bs, nblk, eps);
-  score_rowmax_reduce<<<dim3((l_c + 3) / 4, batch), 256, 0, st>>>(part, nblk, l_c, mu, mfma_mu_stride(l_c), hists, hists_bs);
-  score_mfma_bf16<1, DC><<<grid, kThreads, lds, st>>>(qc, l_c, kc, m_lo, n, part, mu, score, q_bs, kc_bs, score_bs, per,
-                                                      fill_first ? hists : nullptr, hists_bs, qfrag, qfrag_bs, nblk, eps);
+  uint32_t* mu_keys = (uint32_t*)ws;
+  uint32_t* marks = (uint32_t*)((char*)ws + mu_copies_bytes(l_c, batch));
+  const int64_t n_own = (int64_t)(mu_copies_bytes(l_c, batch) + mark_words(n_shares) * kMuCopies * 4) / 16;
+  const int64_t n_clear = n_own + (hists ? (int64_t)batch * (kHistWords / 4) : 0);
+  score_sweeps_clear<<<(unsigned)((n_clear + 255) / 256), 256, 0, st>>>((uint4*)ws, n_own, hists, hists_bs, batch);
+  score_sweeps_bf16<DC><<<n_wg, kThreads, sweeps_lds_bytes(per, DC, l_c), st>>>(
+      qc, kc + m_lo * DC, (int)n, l_c, per, tiles_before_queries(per, DC, l_c), query_waves_log2(l_c), n_row, (int)n_shares, n_wg, eps, mu_keys, marks, score,
+      q_bs, kc_bs, score_bs, fill_first ? hists : nullptr, hists_bs, patience);
   return ESA_OK;
 }
 
 size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
   if (l_c <= 0 || batch <= 0 || n_mid < 0) return 256;
-  size_t b = mu_bytes(l_c, batch) + part_bytes(l_c, n_mid, eps, batch);
+  size_t b = sweeps_bytes(l_c, n_mid, eps, batch) + part_bytes(l_c, n_mid, batch);
   if (eps > 0) b += align_up((size_t)n_mid * 4, 256) * (size_t)batch;
-  b += qfrag_bytes_per_batch(l_c) * (size_t)batch;
   b += stored_bytes(l_c, n_mid, batch);
   return b;
 }
@@ -1087,15 +1156,15 @@ size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
 int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
                  float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* ws,
                  size_t ws_bytes, hipStream_t st, uint32_t* first_hist, int64_t first_hist_bs, bool* first_hist_done,
-                 ScoreTail* tail) {
+                 ScoreTail* tail, uint32_t patience) {
   const int64_t n = m_hi - m_lo;
   // eps > 0: windows of up to kTailMaxEps on either side are pooled by whatever finishes the scores (score_finish, the second
   // sweep where sweep_pools, or the selection through *tail); the unpooled scores of the other cases go to `raw` and proximity_maxpool reads them.
   const bool narrow = eps <= kTailMaxEps;
   bool zeroed = false;                  // the selection's histograms have been zeroed ...
   if (first_hist_done) *first_hist_done = false;        // ... and the first one filled
-  float* part = (float*)((char*)ws + mu_bytes(l_c, batch));
-  char* at = (char*)part + part_bytes(l_c, n, eps, batch);
+  float* part = (float*)((char*)ws + sweeps_bytes(l_c, n, eps, batch));
+  char* at = (char*)part + part_bytes(l_c, n, batch);
   float* raw = score;
   int64_t raw_bs = score_bs;
   if (eps > 0) {
@@ -1103,8 +1172,6 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     raw_bs = (int64_t)(align_up((size_t)n * 4, 256) / 4);
     at += align_up((size_t)n * 4, 256) * (size_t)batch;
   }
-  bf16_t* qfrag = (bf16_t*)at;
-  at += qfrag_bytes_per_batch(l_c) * (size_t)batch;
   if (tail) *tail = ScoreTail{score, score_bs, nullptr, 0, 0};
   bool pool_left = eps > 0;
   const bool vec_ok = dtype == ESA_BF16 && (((uintptr_t)qc | (uintptr_t)kc_cache) % 16 == 0) && q_bs % 8 == 0 &&
@@ -1148,11 +1215,10 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
                                                      kc_bs, nblk, first_hist, first_hist_bs);
     finish(nblk);
   } else if (vec_ok && (d_c == 128 || d_c == 64)) {
-    const int64_t qfrag_bs = (int64_t)(qfrag_bytes_per_batch(l_c) / sizeof(bf16_t));
     const auto sweeps = d_c == 128 ? launch_sweeps<128> : launch_sweeps<64>;
     const bool pools = sweep_pools(n, eps, batch, kTailMaxEps);
-    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, (float*)ws, pools ? score : raw, batch, q_bs,
-                          kc_bs, pools ? score_bs : raw_bs, first_hist, pools, first_hist_bs, qfrag, qfrag_bs, pools ? eps : 0, st);
+    const int rc = sweeps((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, ws, pools ? score : raw, batch, q_bs, kc_bs,
+                          pools ? score_bs : raw_bs, first_hist, pools, first_hist_bs, pools ? eps : 0, patience, st);
     if (rc != ESA_OK) return rc;
     zeroed = first_hist != nullptr;
     if (first_hist && pools && first_hist_done) *first_hist_done = true;

@@ -181,6 +181,46 @@ def test_score_sweeps_in_whole_rounds(esa, B, l_c, n, d_c, eps):
         assert got[b].max() == 0.0
 
 
+# No workgroup of the sweeps depends on another one's being resident: told to wait for 0 or 2 us only, they do each other's row maxima,
+# and the scores have the same bits.  One share, a few, a round of them, two rounds, several rows; both query paths, several blocks of queries
+@pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 20, 30, 128, 0), (1, 40, 20000, 64, 1), (1, 77, 48000, 128, 0), (1, 530, 130000, 128, 0),
+                                             (1, 300, 140000, 128, 3), (3, 40, 70000, 128, 0), (2, 512, 33000, 128, 0)])
+def test_score_sweeps_that_do_not_wait_for_each_other(esa, B, l_c, n, d_c, eps):
+    import ctypes
+    say(f"score without waiting B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
+    g = torch.Generator(device="cuda").manual_seed(n + l_c)
+    qc, kc = (torch.randn((B, m, d_c), generator=g, device="cuda").bfloat16() for m in (l_c, n + 8))
+    want = esa.esa_score(qc, kc, 3, n + 3, eps=eps)
+    call = ctypes.CDLL(esa.lib_path()).esa_internal_score_waiting
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    i64 = ctypes.c_int64
+    size = esa.lib.esa_score_workspace_bytes(l_c, n, eps, B)
+    for ticks in (0, 200):
+        got, ws = torch.full_like(want, 7.0), torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+        rc = call(ptr(qc), l_c, ptr(kc), i64(3), i64(n + 3), d_c, eps, ptr(got), esa.ESA_BF16, B, i64(l_c * d_c), i64((n + 8) * d_c), i64(n),
+                  ptr(ws), ctypes.c_size_t(size), ticks, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0 and torch.equal(got, want), ticks
+
+
+def test_score_sweeps_on_several_streams_at_once(esa):
+    """Calls that compete for the compute units, each workgroup of which waits for the others of its call: the same bits, and an end."""
+    say("score on four streams")
+    g = torch.Generator(device="cuda").manual_seed(8)
+    shapes = [(77, 48000), (512, 130000), (300, 60000), (20, 128000)]
+    data = [tuple(torch.randn((m, 128), generator=g, device="cuda").bfloat16() for m in (l_c, n)) for l_c, n in shapes]
+    want = [esa.esa_score(q, k, 0, k.shape[0]) for q, k in data]
+    streams = [torch.cuda.Stream() for _ in data]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        got = []
+        for s, (q, k) in zip(streams, data):
+            with torch.cuda.stream(s):
+                got += [esa.esa_score(q, k, 0, k.shape[0]) for _ in range(4)]
+        torch.cuda.synchronize()
+        for i, g_ in enumerate(got):
+            assert torch.equal(g_, want[i // 4]), i
+
+
 # Pooling by the second sweep: one workgroup's tokens, one more, one less; a single token; the widest window it takes in the shortest
 # share and in long ones, the narrowest, one that keeps its own pass; windows across every workgroup's edge hold the row's largest scores
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 17, 1, 128, 1), (2, 40, 62, 128, 1), (1, 40, 63, 128, 1), (1, 20, 61, 64, 1), (1, 33, 32, 64, 16),
