@@ -30,7 +30,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 typedef __attribute__((address_space(1))) const void global_void;
@@ -129,7 +129,8 @@ static_assert(turn_offset((1u << 31) / kKT, 128) == 1024 + (((1ull << 31) / kKT)
 // 2048: step at 64 thousand tokens 129.4 us copied, 121.2 turned here.  What turning costs is 25 vector instructions a pair, 0.8 us a tile
 // and SIMD with the SIMDs busy, 1.5 us of a call that has a tile a wave.  In fp32, by products of two turns in registers, it cost
 // half of that (117.1), but put an element of every hundredth key on the other side of its rounding.)
-template <typename T, int D, int kWaves, bool TURNED = false>
+// STREAM: keys and values are fetched non-temporally (see streams).
+template <typename T, int D, int kWaves, bool TURNED = false, bool STREAM = false>
 __global__ __launch_bounds__(64 * kWaves, D * sizeof(T) > 256 || kWaves > kWavesOfTwo ? 1 : 2) __attribute__((amdgpu_waves_per_eu(D * sizeof(T) > 256 ? 1 : 2)))
 void attend_split(SplitArgs a) {
   static_assert(!TURNED || sizeof(T) == 2, "the table's order");
@@ -225,7 +226,7 @@ void attend_split(SplitArgs a) {
       const uint32_t piece = values ? ((((st_slot >> 2) ^ v_swizzle(key)) << 2) | (st_slot & 3)) : st_slot ^ k_swizzle(key);
       const char* src = p < 0 ? (values ? vsl : ksl) + (uint64_t)(uint32_t)~p * a.sel_bytes
                               : (values ? vc : kc) + (uint64_t)(uint32_t)p * (values ? V.v_bytes : V.k_bytes);
-      __builtin_amdgcn_global_load_lds((global_void*)(src + piece * 16), (lds_void*)(dst + i * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_void*)(src + piece * 16), (lds_void*)(dst + i * 1024), 16, 0, STREAM ? kNonTemporal : 0);
     }
   };
 
@@ -651,12 +652,21 @@ int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
   return ESA_OK;
 }
 
+// Whether each row of keys and values is fetched by one workgroup and they are together more than the last-level cache keeps from
+// one layer's step to the next beside what else passes through it.  One token, 16 x 4225 keys of 8 KV heads (277 MB), us, three inputs in turn:
+// 54.7 -> 50.2 (55.2 -> 50.4 on long documents); 8 sequences (138 MB) 31.1 -> 28.9, 4 (69 MB) 19.3 -> 18.3.  Less is often there still:
+// 3 sequences (52 MB) 14.6 / 14.7, five tokens of 2 (35 MB) 14.4 -> 15.3.  (One input again and again: 8 sequences 26.6 -> 29.1.)  Row tiles that share
+// keys want them kept (fp32, sixteen row tiles: a step 52.2 -> 53.9); so do gathered rows, which have just been written (8 re-encoded sequences 34.5 -> 35.4).
+bool streams(const SplitCall& c, const SplitArgs& a, int64_t n_keys) {
+  return c.dtype == ESA_BF16 && a.n_rt == 1 && !c.turns && !c.k_sel && 2 * n_keys * c.h_kv * c.batch * c.d * 2 >= ((int64_t)64 << 20);
+}
 template <typename T, int D>
-void run(const SplitCall& c, const SplitArgs& args, int waves, hipStream_t st) {
+void run(const SplitCall& c, const SplitArgs& args, int waves, bool stream, hipStream_t st) {
   SplitArgs a = args;
   auto kernel = attend_split<T, D, kWavesOfTwo>;
   if constexpr (sizeof(T) == 2) {
-    if (waves == kWavesOfOne) kernel = a.turns ? attend_split<T, D, kWavesOfOne, true> : attend_split<T, D, kWavesOfOne>;
+    if (stream) kernel = attend_split<T, D, kWavesOfTwo, false, true>;
+    else if (waves == kWavesOfOne) kernel = a.turns ? attend_split<T, D, kWavesOfOne, true> : attend_split<T, D, kWavesOfOne>;
     else if (a.turns) kernel = attend_split<T, D, kWavesOfTwo, true>;
   }
   for_pair_grids((int64_t)c.batch * c.h_kv, a.n_rt, a.view[0].n_split + a.view[1].n_split, [&](dim3 grid, PairGrid placed) {
@@ -690,7 +700,8 @@ struct RunIt {
   const SplitArgs& a;
   hipStream_t st;
   int waves = kWavesOfTwo;
-  template <typename T, int D> void operator()() { run<T, D>(c, a, waves, st); }
+  bool stream = false;
+  template <typename T, int D> void operator()() { run<T, D>(c, a, waves, stream, st); }
 };
 struct MergeIt {
   const SplitCall& c;
@@ -748,7 +759,7 @@ int launch_attend_split(const SplitCall& c, KeyView v0, const KeyView* v1, hipSt
     const int rc = with_slots(&a, c, n0 + n1);
     if (rc != ESA_OK) return rc;
   }
-  dispatch(c, RunIt{c, a, st, waves});
+  dispatch(c, RunIt{c, a, st, waves, waves == kWavesOfTwo && streams(c, a, k0 + k1)});
   if (n0 + n1 > 1) dispatch(c, MergeIt{c, a, n0 + n1, st});
   ESA_LAUNCH_CHECK("attend_split");
   return ESA_OK;

@@ -698,12 +698,14 @@ __global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ ow
 // step; a workgroup covers 64 or 256 rows.  Writes S and the workgroup's maximum of it (no atomics: thousands of
 // workgroups folding into one word serialise in L2); score_finish then reduces those maxima to mu,
 // every workgroup for itself, and forms F = S - mu.
-// ROWS per workgroup.  256: the loads stand behind their bounds checks, each step a round trip of its own, which the
-// sixteen waves of a compute unit hide from one another.  Few rows in all do not give a compute unit so many waves: 64,
-// all requested before the first use.  Score and selection of one token, us, 256 against 64 rows: 3 thousand rows 11.2
-// against 8.3, 12 thousand 19.5 / 16.6, 100 thousand 22.2 / 18.6, 4 x 20 thousand 22.1 / 18.4; 200 thousand 25.1 / 25.4,
-// 8 x 63 thousand 37.4 / 37.1, where the longer list of partial maxima takes back what is left to gain.
-constexpr int64_t kGemvFewRows = 131072;
+// What bounds it is HBM.  Workgroups of 512 rows, eight requests a lane in flight, non-temporal (see streams), each row whole cache lines of one
+// instruction; the scores leave by way of LDS, 256 bytes a wave and non-temporally too (four lanes' words at a time cost 18 of 172 us, 10
+// now).  Sixteen rows of 260 thousand (1.07 GB) 201.5 -> 169.6 us, 6.3 TB/s (with the loads behind their bounds checks and stores as they came
+// 256 rows a workgroup had 5.3); one row out of HBM 17.9 -> 13.1, of 180 thousand 15.4 -> 10.2.
+// Few rows in all give a compute unit too few requests that way, and the last-level cache often has them still: 64 rows a workgroup, ordinary
+// loads.  64 / 512 rows, us, three inputs in turn and twelve: 150 thousand 8.3 / 11.5, 9.9 / 11.2; 180 9.6 / 11.6, 10.2 / 11.6; 210 10.4 / 12.1, 11.8 / 12.0;
+// 262 12.9 / 13.5, 13.7 / 13.7, but then score_finish has a list of partial maxima to go through that is eight times as long (4.2 -> 4.6).
+constexpr int64_t kGemvFewRows = 196608;
 // grids of the passes over the scores (host and device agree on them; the kernels do not ask the dispatch packet)
 __host__ __device__ inline int maxpool_blocks(int64_t n) { return (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096); }
 
@@ -726,22 +728,26 @@ __device__ __forceinline__ float lanes_max16(float v) {
   return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true)));
 }
 
-template <int LPR, int ROWS>
-__global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict__ qc, const bf16_t* __restrict__ kc,
-                                                       int64_t m_lo, int64_t n, float* __restrict__ part,
-                                                       float* __restrict__ raw, int64_t q_bs, int64_t kc_bs,
-                                                       int64_t raw_bs, uint32_t* __restrict__ hists, int64_t hists_bs) {
+// THREADS, and STEPS rows to each LPR of them.
+template <int LPR, int THREADS, int STEPS>
+__global__ __launch_bounds__(THREADS) void score_gemv_bf16(const bf16_t* __restrict__ qc, const bf16_t* __restrict__ kc,
+                                                           int64_t m_lo, int64_t n, float* __restrict__ part,
+                                                           float* __restrict__ raw, int64_t q_bs, int64_t kc_bs,
+                                                           int64_t raw_bs, uint32_t* __restrict__ hists, int64_t hists_bs) {
   constexpr int kDcv = LPR * 8;
-  constexpr int kRowsPerStep = 256 / LPR;
-  constexpr int kSteps = ROWS / kRowsPerStep;
-  const int n_wg = (int)((n + ROWS - 1) / ROWS);           // workgroups per batch entry (the launch's grid)
-  __shared__ float red[4];
-  const int b = __builtin_amdgcn_workgroup_id_y();
+  constexpr int kRowsPerStep = THREADS / LPR;
+  constexpr int kRows = kRowsPerStep * STEPS;
+  constexpr int kAhead = STEPS < 8 ? STEPS : 8;            // rows of a lane in flight
+  constexpr bool kStream = THREADS == 512;
+  const int n_wg = (int)((n + kRows - 1) / kRows);         // workgroups per batch entry (the launch's grid)
+  __shared__ float red[THREADS / 64];
+  __shared__ float staged[kRows];
+  const int b = __builtin_amdgcn_workgroup_id_y(), tid = __builtin_amdgcn_workitem_id_x();
   if (hists)       // the selection's histograms, zeroed here for the pass that follows
-    for (int i = __builtin_amdgcn_workgroup_id_x() * 256 + __builtin_amdgcn_workitem_id_x(); i < kHistWords; i += n_wg * 256)
+    for (int i = __builtin_amdgcn_workgroup_id_x() * THREADS + tid; i < kHistWords; i += n_wg * THREADS)
       hists[(int64_t)b * hists_bs + i] = 0u;
   const bf16_t* kmid = kc + (int64_t)b * kc_bs + m_lo * (int64_t)kDcv;
-  const int sub = __builtin_amdgcn_workitem_id_x() % LPR, grp = __builtin_amdgcn_workitem_id_x() / LPR;
+  const int sub = tid % LPR, grp = tid / LPR;
   float qv[8];
   {
     const uint4 u = *(const uint4*)(qc + (int64_t)b * q_bs + sub * 8);
@@ -751,87 +757,106 @@ __global__ __launch_bounds__(256) void score_gemv_bf16(const bf16_t* __restrict_
     qv[6] = __uint_as_float(u.w << 16); qv[7] = __uint_as_float(u.w & 0xFFFF0000u);
   }
   float best = -INFINITY;
-  const int64_t row0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * ROWS + grp;
-  auto finish = [&](const uint4& u, int64_t row) {
-    float s = qv[0] * __uint_as_float(u.x << 16);
-    s = __fmaf_rn(qv[1], __uint_as_float(u.x & 0xFFFF0000u), s);
-    s = __fmaf_rn(qv[2], __uint_as_float(u.y << 16), s);
-    s = __fmaf_rn(qv[3], __uint_as_float(u.y & 0xFFFF0000u), s);
-    s = __fmaf_rn(qv[4], __uint_as_float(u.z << 16), s);
-    s = __fmaf_rn(qv[5], __uint_as_float(u.z & 0xFFFF0000u), s);
-    s = __fmaf_rn(qv[6], __uint_as_float(u.w << 16), s);
-    s = __fmaf_rn(qv[7], __uint_as_float(u.w & 0xFFFF0000u), s);
-    s = lanes_sum<LPR>(s);
-    if (row < n) {
-      if (sub == 0) raw[(int64_t)b * raw_bs + row] = s;
+  const int64_t row0 = (int64_t)__builtin_amdgcn_workgroup_id_x() * kRows;
+#pragma unroll
+  for (int it0 = 0; it0 < STEPS; it0 += kAhead) {
+    uint4 u[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {                     // rows past the end repeat the last one: no maximum changes
+      const int64_t row = row0 + (it0 + i) * kRowsPerStep + grp;
+      u[i] = load16<kStream>(kmid + (row < n ? row : n - 1) * kDcv + sub * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      float s = qv[0] * __uint_as_float(u[i].x << 16);
+      s = __fmaf_rn(qv[1], __uint_as_float(u[i].x & 0xFFFF0000u), s);
+      s = __fmaf_rn(qv[2], __uint_as_float(u[i].y << 16), s);
+      s = __fmaf_rn(qv[3], __uint_as_float(u[i].y & 0xFFFF0000u), s);
+      s = __fmaf_rn(qv[4], __uint_as_float(u[i].z << 16), s);
+      s = __fmaf_rn(qv[5], __uint_as_float(u[i].z & 0xFFFF0000u), s);
+      s = __fmaf_rn(qv[6], __uint_as_float(u[i].w << 16), s);
+      s = __fmaf_rn(qv[7], __uint_as_float(u[i].w & 0xFFFF0000u), s);
+      s = lanes_sum<LPR>(s);
+      if (sub == 0) staged[(it0 + i) * kRowsPerStep + grp] = s;
       best = fmaxf(best, s);
-    }
-  };
-  if constexpr (ROWS == 64) {              // every row requested before the first is used: with few workgroups nothing else hides a round trip
-    uint4 u[kSteps];
-#pragma unroll
-    for (int it = 0; it < kSteps; ++it) {
-      const int64_t row = row0 + it * kRowsPerStep;
-      u[it] = *(const uint4*)(kmid + (row < n ? row : n - 1) * kDcv + sub * 8);
-    }
-#pragma unroll
-    for (int it = 0; it < kSteps; ++it) finish(u[it], row0 + it * kRowsPerStep);
-  } else {
-#pragma unroll
-    for (int it = 0; it < kSteps; ++it) {
-      const int64_t row = row0 + it * kRowsPerStep;
-      uint4 u = make_uint4(0u, 0u, 0u, 0u);
-      if (row < n) u = *(const uint4*)(kmid + row * kDcv + sub * 8);
-      finish(u, row);
     }
   }
   best = wave_max(best);
-  if ((__builtin_amdgcn_workitem_id_x() & 63) == 0) red[__builtin_amdgcn_workitem_id_x() >> 6] = best;
+  if ((tid & 63) == 0) red[tid >> 6] = best;
   __syncthreads();
-  if (__builtin_amdgcn_workitem_id_x() == 0)
-    part[(int64_t)b * n_wg + __builtin_amdgcn_workgroup_id_x()] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  for (int i = tid; i < kRows; i += THREADS)
+    if (row0 + i < n) {
+      float* to = &raw[(int64_t)b * raw_bs + row0 + i];
+      if (kStream) __builtin_nontemporal_store(staged[i], to);
+      else *to = staged[i];
+    }
+  if (tid == 0) {
+#pragma unroll
+    for (int w = 1; w < THREADS / 64; ++w) best = fmaxf(best, red[w]);
+    part[(int64_t)b * n_wg + __builtin_amdgcn_workgroup_id_x()] = best;
+  }
 }
 
 // Two to sixteen current tokens: one pass over K' on the matrix cores, S stored.  v_mfma_f32_16x16x32_bf16, A rows are
 // tokens, B columns queries (rows past the chunk repeat its last one): a lane owns four consecutive tokens of one query,
-// a 16-byte store.  K' is the stream to keep moving: a wave has its 64 tokens' fragments in flight at once (16 or 8
-// loads of 16 bytes per lane, sixteen rows of 64 bytes per instruction).  Four sequences of 100k tokens, five queries:
-// 102 MB, where each of the two sweeps took 35 us.
+// a 16-byte store.  K' is the stream to keep moving, in whole cache lines: a wave requests its 64 tokens' rows at once, a lane 16 bytes of
+// each, and passes them through 4 KB of LDS of its own, sixteen rows at a time, into fragments.  Read as fragments, half a line to an instruction, the rows could
+// not be fetched non-temporally (17.8 -> 24.9 us).  From kFewStreamBytes on they are: four sequences of 100k tokens (102 MB), five queries,
+// out of HBM 22.2 -> 21.0 us; less is often still in the last-level cache (eight of 30k, 61 MB, ordinary loads 12.0 / 14.4, non-temporal 14.7 / 14.0 with three inputs
+// in turn / eight; two of 60k 7.7 / 8.5, 8.1 / 8.1).  Each of the two sweeps took 35 us for the 102 MB.
 constexpr int kFewQueries = 16;
 constexpr int kFewTok = 256;             // tokens per workgroup
-template <int DC>
+constexpr int64_t kFewStreamBytes = (int64_t)64 << 20;
+template <int DC, bool STREAM>
 __global__ __launch_bounds__(256) void score_few_bf16(const bf16_t* __restrict__ qc, int l_c, const bf16_t* __restrict__ kc,
                                                       int64_t m_lo, int64_t n, float* __restrict__ part, float* __restrict__ S,
                                                       int64_t s_ld, int64_t s_bs, int64_t q_bs, int64_t kc_bs, int n_wg,
                                                       uint32_t* __restrict__ hists, int64_t hists_bs) {
   constexpr int kKS = DC / 32, kTiles = kFewTok / 64;
+  constexpr int kPieces = DC / 8, kLoadRows = 64 / kPieces;                  // 16-byte pieces of a row, rows of a load instruction
+  constexpr int kTileLoads = 16 / kLoadRows;
+  __shared__ __attribute__((aligned(256))) unsigned char staged[4][16 * DC * 2];
   __shared__ float red[4][kFewQueries];
   const int b = __builtin_amdgcn_workgroup_id_y(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
-  const int lane = tid & 63, wave = tid >> 6, r = lane & 15, q4 = lane >> 4;
-  const bf16_t* k = kc + (int64_t)b * kc_bs + m_lo * (int64_t)DC + q4 * 8;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, q4 = lane >> 4;
+  const bf16_t* k = kc + (int64_t)b * kc_bs + m_lo * (int64_t)DC + lane % kPieces * 8;
   const bf16_t* qp = qc + (int64_t)b * q_bs + (int64_t)(r < l_c ? r : l_c - 1) * DC + q4 * 8;
-  bf16x8 kf[kTiles][kKS], qf[kKS];
+  bf16x8 qf[kKS];
 #pragma unroll
   for (int ks = 0; ks < kKS; ++ks) qf[ks] = *(const bf16x8*)(qp + 32 * ks);
   const int64_t tok0 = (int64_t)blk * kFewTok + wave * (16 * kTiles);
+  uint4 kv[kTiles][kTileLoads];
 #pragma unroll
-  for (int t = 0; t < kTiles; ++t) {
-    int64_t tok = tok0 + 16 * t + r;
-    tok = tok < n ? tok : n - 1;                            // repeats the last token: no maximum changes
+  for (int t = 0; t < kTiles; ++t)
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) kf[t][ks] = *(const bf16x8*)(k + tok * DC + 32 * ks);
-  }
+    for (int i = 0; i < kTileLoads; ++i) {
+      const int64_t tok = tok0 + 16 * t + kLoadRows * i + lane / kPieces;
+      kv[t][i] = load16<STREAM>(k + (tok < n ? tok : n - 1) * DC);                // repeats the last token: no maximum changes
+    }
   if (hists)       // the selection's histograms, zeroed here for the pass that follows
     for (int i = blk * 256 + tid; i < kHistWords; i += n_wg * 256) hists[(int64_t)b * hists_bs + i] = 0u;
+  // rows land in LDS with their pieces swizzled, so that neither the writes nor the fragment reads meet in a bank
+  auto slot = [&](uint32_t row, uint32_t piece) { return staged[wave] + row * (DC * 2) + ((piece ^ (DC == 128 ? row & 15 : (row >> 1) & 7)) << 4); };
   float best = -INFINITY;
+  f32x4 acc[kTiles];
 #pragma unroll
   for (int t = 0; t < kTiles; ++t) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qf[ks], acc, 0, 0, 0);
-    best = fmaxf(fmaxf(best, acc[0]), fmaxf(fmaxf(acc[1], acc[2]), acc[3]));
+    for (int i = 0; i < kTileLoads; ++i) *(uint4*)slot(kLoadRows * i + lane / kPieces, lane % kPieces) = kv[t][i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                   // (a wave's LDS operations complete in order)
+    bf16x8 kf[kKS];
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) kf[ks] = *(const bf16x8*)slot(r, 4 * ks + q4);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    acc[t] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[ks], acc[t], 0, 0, 0);
+    best = fmaxf(fmaxf(best, acc[t][0]), fmaxf(fmaxf(acc[t][1], acc[t][2]), acc[t][3]));
+  }
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t) {
     const int64_t tok = tok0 + 16 * t + 4 * q4;
-    if (r < l_c && tok < s_ld) *(f32x4*)(S + (int64_t)b * s_bs + (int64_t)r * s_ld + tok) = acc;      // s_ld: n rounded up to whole tiles
+    if (r < l_c && tok < s_ld) *(f32x4*)(S + (int64_t)b * s_bs + (int64_t)r * s_ld + tok) = acc[t];      // s_ld: n rounded up to whole tiles
   }
   best = fmaxf(best, __shfl_xor(best, 16, 64));
   best = fmaxf(best, __shfl_xor(best, 32, 64));
@@ -1197,10 +1222,10 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
   };
   if (vec_ok && l_c == 1 && (d_c == 64 || d_c == 128 || d_c == 256)) {
     const bool few_rows = n * batch <= kGemvFewRows;
-    const int rows = few_rows ? 64 : 256, nblk = (int)((n + rows - 1) / rows);
-    const auto gemv = few_rows ? (d_c == 64 ? score_gemv_bf16<8, 64> : d_c == 128 ? score_gemv_bf16<16, 64> : score_gemv_bf16<32, 64>)
-                               : (d_c == 64 ? score_gemv_bf16<8, 256> : d_c == 128 ? score_gemv_bf16<16, 256> : score_gemv_bf16<32, 256>);
-    gemv<<<dim3((unsigned)nblk, batch), 256, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
+    const int rows = few_rows ? 64 : 512, threads = few_rows ? 256 : 512, nblk = (int)((n + rows - 1) / rows);
+    const auto gemv = few_rows ? (d_c == 64 ? score_gemv_bf16<8, 256, 2> : d_c == 128 ? score_gemv_bf16<16, 256, 4> : score_gemv_bf16<32, 256, 8>)
+                               : (d_c == 64 ? score_gemv_bf16<8, 512, 8> : d_c == 128 ? score_gemv_bf16<16, 512, 16> : score_gemv_bf16<32, 512, 32>);
+    gemv<<<dim3((unsigned)nblk, batch), threads, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
                                                       first_hist, first_hist_bs);
     if (tail && narrow) {
       *tail = ScoreTail{raw, raw_bs, part, nblk, eps};
@@ -1210,7 +1235,9 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     }
   } else if (vec_ok && l_c <= kFewQueries && (d_c == 128 || d_c == 64)) {
     const int nblk = (int)((n + kFewTok - 1) / kFewTok);
-    const auto few = d_c == 128 ? score_few_bf16<128> : score_few_bf16<64>;
+    const bool stream = n * batch * d_c * (int64_t)sizeof(bf16_t) >= kFewStreamBytes;
+    const auto few = d_c == 128 ? (stream ? score_few_bf16<128, true> : score_few_bf16<128, false>)
+                                : (stream ? score_few_bf16<64, true> : score_few_bf16<64, false>);
     few<<<dim3((unsigned)nblk, batch), 256, 0, st>>>((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, S, s_ld, s_bs, q_bs,
                                                      kc_bs, nblk, first_hist, first_hist_bs);
     finish(nblk);

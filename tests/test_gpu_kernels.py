@@ -747,3 +747,35 @@ def test_calls_on_two_streams_and_threads_do_not_share_scratch(esa):
         for results in got[i]:
             for a, b in zip(results, want[i]):
                 assert torch.equal(a, b)
+
+
+# K' as a stream: one token with the fewest rows in all and one less, a workgroup's 512 rows and one more in the last one; a few queries with the fewest bytes
+# and one row less, batches, both row lengths
+@pytest.mark.parametrize("B,l_c,n,d_c", [(1, 1, 196608, 128), (1, 1, 196609, 128), (3, 1, 65537, 256), (2, 1, 131072, 64), (24, 1, 8705, 128), (1, 2, 262143, 128),
+                                         (1, 2, 262144, 128), (3, 16, 200001, 64)])
+def test_score_of_streamed_compressed_keys(esa, B, l_c, n, d_c):
+    say(f"score, K' streamed B={B} l_c={l_c} n={n} d_c={d_c}")
+    rng = np.random.default_rng(n + d_c)
+    qc = orc.round_to_storage(rng.standard_normal((B, l_c, d_c)), "bf16")
+    kd = torch.randn((B, n + 3, d_c), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").bfloat16()
+    got = esa.esa_score(f64_to_dev(qc, "bf16"), kd, 2, 2 + n)
+    for b in range(B):
+        s = torch.from_numpy(qc[b]).cuda() @ kd[b, 2:2 + n].double().T
+        want = (s - s.max(1, keepdim=True).values).max(0).values
+        assert float((got[b].double() - want).abs().max()) <= F_TOL["bf16"], b
+        assert float(got[b].max()) == 0.0
+
+
+# Keys and values as a stream (64 MB together and more, one row tile): the fewest keys and one less, rows that fill the tile, both head sizes
+@pytest.mark.parametrize("B,H,H_kv,d,l_C,keys", [(4, 32, 8, 128, 1, 4096), (4, 32, 8, 128, 1, 4095), (8, 32, 8, 64, 8, 4097), (2, 16, 16, 128, 5, 4100)])
+def test_split_key_attention_over_streamed_rows(esa, B, H, H_kv, d, l_C, keys):
+    say(f"attend, streamed B={B} H={H} H_kv={H_kv} d={d} l_C={l_C} keys={keys}")
+    l_I, n_sel = 64, keys // 3
+    l_L = keys - l_C - l_I - n_sel
+    t0 = l_I + n_sel + 200 + l_L
+    q, K, V, sel = attend_inputs(d + l_C, "bf16", B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel)
+    O, lse = esa.esa_attend_indexed(*(f64_to_dev(x, "bf16") for x in (q, K, V)), t0, l_I, l_L, torch.from_numpy(sel).cuda(), return_lse=True)
+    for b in range(B):
+        want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
+        assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"]
+        assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3
