@@ -317,7 +317,7 @@ void attend_split(SplitArgs a) {
             sn[e] = sn_next;
           }
           float f[4];
-          narrow4_for_bf16(turned, f);
+          narrow_for_bf16(turned, f);
           lds_write4(at[k], pack_bf16x2(f[0], f[1]));
           lds_write4(at[k] ^ D, pack_bf16x2(f[2], f[3]));
         }

@@ -56,17 +56,18 @@ __device__ __forceinline__ float narrow_for_bf16(double v) {
   return f;
 }
 
-// Four of them, with one branch for the midpoints.
-__device__ __forceinline__ void narrow4_for_bf16(const double (&v)[4], float (&f)[4]) {
+// N of them, with one branch for the midpoints.
+template <int N>
+__device__ __forceinline__ void narrow_for_bf16(const double (&v)[N], float (&f)[N]) {
   bool midpoint = false;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < N; ++i) {
     f[i] = (float)v[i];
     midpoint |= (uint16_t)__float_as_uint(f[i]) == 0x8000u;
   }
   if (__builtin_expect(midpoint, 0)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
       asm volatile("" : "+v"(f[i]));       // (this block's tests would be made in front of the branch)
       const double left = v[i] - (double)f[i];
       const uint32_t u = __float_as_uint(f[i]);

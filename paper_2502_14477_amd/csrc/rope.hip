@@ -10,7 +10,7 @@
 // the frequencies and the turn from one row to the next come from the host (fp64 too, kept per thread for a base and
 // head size), a thread evaluates sine and cosine for the first of its few consecutive rows and turns the others by complex
 // multiplication (a handful of errors of 2^-53), and the heads of a row share the pairs held in registers.
-// fp32 products of the same angles take 9.2 us instead of 13.6 (512 queries twice and 4608 keys, 31 MB), but put an element of every
+// fp32 products of the same angles take 9.2 us (512 queries twice and 4608 keys, 31 MB; fp64 12.4), but put an element of every
 // hundredth row on the other side of a rounding.  Checked against their error bound and done again in fp64 where it leaves the rounding
 // open (one element in a thousand, so two instructions of a wave in three), they take what fp64 takes.
 #include <cmath>
@@ -36,19 +36,22 @@ template <typename T> __device__ __forceinline__ double load_f64(T v);
 template <> __device__ __forceinline__ double load_f64<float>(float v) { return (double)v; }
 template <> __device__ __forceinline__ double load_f64<bf16_t>(bf16_t v) { return (double)bf16_to_f32(v); }
 
-// Two results rounded into storage.
-template <typename T> __device__ __forceinline__ void store_f64(T* p, double a, double b);
-template <> __device__ __forceinline__ void store_f64<float>(float* p, double a, double b) {
-  p[0] = (float)a;
-  p[1] = (float)b;
+// Results rounded into storage.
+template <int N> __device__ __forceinline__ void store_f64(float* p, const double (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) p[i] = (float)v[i];
 }
-template <> __device__ __forceinline__ void store_f64<bf16_t>(bf16_t* p, double a, double b) {
-  const f32x2 f = {narrow_for_bf16(a), narrow_for_bf16(b)};
-  *(uint32_t*)p = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+template <int N> __device__ __forceinline__ void store_f64(bf16_t* p, const double (&v)[N]) {
+  float f[N];
+  narrow_for_bf16(v, f);
+#pragma unroll
+  for (int i = 0; i < N; i += 2) *(uint32_t*)(p + i) = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{f[i], f[i + 1]}), bf16x2));
 }
 
 constexpr int kRopeRows = 16;     // most rows of a workgroup
 constexpr int kAhead = 4;         // heads whose loads a thread has in flight
+// Pairs whose roundings share a branch: with one for every element, 512 queries twice and 4608 keys took 13.5 us; four pairs 12.4, eight 12.6.
+constexpr int kTogether = 4;
 // Rows of a workgroup, of at most `budget` rows x heads: fewer of the wide ones, so that a thread has one or two rounds
 // of kAhead heads to turn (every round is a round trip to memory, and a chunk's queries are few rows of many heads).
 __host__ __device__ inline int rows_of(int heads, int budget) {
@@ -139,19 +142,31 @@ __global__ __launch_bounds__(256) void rope_rows(RopeJobs jobs, Turns turns, int
         const int h = hb + u * hs;
         if (h >= jb.heads) break;
         if constexpr (VEC > 1) {
-          vec_t ra, rb;
+          vec_t r2[2];                                 // the turned pairs' first and second halves
 #pragma unroll
-          for (int k = 0; k < VEC; k += 2) {
-            const double a0 = load_f64<T>(a[u][k]), a1 = load_f64<T>(a[u][k + 1]), b0 = load_f64<T>(b[u][k]), b1 = load_f64<T>(b[u][k + 1]);
-            store_f64<T>((T*)&ra + k, a0 * c[k] - b0 * s[k], a1 * c[k + 1] - b1 * s[k + 1]);
-            store_f64<T>((T*)&rb + k, b0 * c[k] + a0 * s[k], b1 * c[k + 1] + a1 * s[k + 1]);
+          for (int k = 0; k < VEC; k += kTogether) {
+            double v[2 * kTogether];
+#pragma unroll
+            for (int j = 0; j < kTogether; ++j) {
+              const double a0 = load_f64<T>(a[u][k + j]), b0 = load_f64<T>(b[u][k + j]);
+              v[j] = a0 * c[k + j] - b0 * s[k + j];
+              v[kTogether + j] = b0 * c[k + j] + a0 * s[k + j];
+            }
+            T out[2 * kTogether] __attribute__((aligned(16)));
+            store_f64(out, v);
+#pragma unroll
+            for (int j = 0; j < kTogether; ++j) {
+              r2[0][k + j] = out[j];
+              r2[1][k + j] = out[kTogether + j];
+            }
           }
-          *(vec_t*)(orow + h * d) = ra;
-          *(vec_t*)(orow + h * d + half) = rb;
+          *(vec_t*)(orow + h * d) = r2[0];
+          *(vec_t*)(orow + h * d + half) = r2[1];
         } else {
           const double a0 = load_f64<T>(a[u][0]), b0 = load_f64<T>(b[u][0]);
           __attribute__((aligned(8))) T both[2];
-          store_f64<T>(both, a0 * c[0] - b0 * s[0], b0 * c[0] + a0 * s[0]);
+          const double v[2] = {a0 * c[0] - b0 * s[0], b0 * c[0] + a0 * s[0]};
+          store_f64(both, v);
           orow[h * d] = both[0];
           orow[h * d + half] = both[1];
         }
