@@ -865,9 +865,10 @@ __global__ __launch_bounds__(256) void score_few_bf16(const bf16_t* __restrict__
   if (tid < l_c) part[((int64_t)b * n_wg + blk) * l_c + tid] = fmaxf(fmaxf(red[0][tid], red[1][tid]), fmaxf(red[2][tid], red[3][tid]));
 }
 
-// The same for every storage type and d_c: a workgroup computes S for 64 tokens (one per lane) and 32 queries (eight per
+// The same for every storage type, d_c and alignment: a workgroup computes S for 64 tokens (one per lane) and 32 queries (eight per
 // wave), both in LDS as fp32 rows (the queries' reads are broadcasts), fp32 FMAs in ascending order.
 constexpr int kStoreQ = 32;
+constexpr int kTileQ = 64;
 __host__ __device__ inline int store_ld(int d_c) { return d_c + 4; }       // d_c is a multiple of 16: rows 16-byte aligned, spread over the banks
 template <typename T>
 __global__ __launch_bounds__(256) void score_store_fma(const T* __restrict__ qc, int l_c, const T* __restrict__ kc, int64_t m_lo,
@@ -923,6 +924,65 @@ __global__ __launch_bounds__(256) void score_store_fma(const T* __restrict__ qc,
     const float mx = wave_max(acc[j]);
     if (lane == 0) part[((int64_t)b * n_wg + blk) * l_c + c0 + j] = mx;
   }
+}
+
+// The same for fp32 rows that are 16-byte aligned, on the matrix cores: v_mfma_f32_32x32x2_f32, exact products and fp32 sums, A rows are
+// tokens, B columns queries; a lane's sixteen bytes of a row feed four instructions (lanes 32 apart hold neighbouring pieces).  A wave owns
+// 32 tokens x 32 queries and takes its fragments straight from memory: a small layer's call is round trips, and staging through LDS with
+// its index arithmetic, 72 LDS reads a wave and a butterfly per query made it 6.8 us for 128 queries over 1632 tokens of d_c 32, 4.2 now (five
+// queries over 940: 6.4 -> 3.8; the layer's step 28.8 -> 27.6).  Two chains of half the sum are nearer to the 64-bit result than one: scores 1.83e-7 ->
+// 1.35e-7 at d_c 32, 3.99e-7 -> 2.29e-7 at 128.
+__global__ __launch_bounds__(256) void score_store_f32(const float* __restrict__ qc, int l_c, const float* __restrict__ kc, int64_t m_lo,
+                                                       int64_t n, int d_c, float* __restrict__ part, float* __restrict__ S,
+                                                       int64_t s_ld, int64_t s_bs, int64_t q_bs, int64_t kc_bs, int n_wg,
+                                                       uint32_t* __restrict__ hists, int64_t hists_bs) {
+  __shared__ float red[2][kTileQ];
+  const int b = __builtin_amdgcn_workgroup_id_z(), blk = __builtin_amdgcn_workgroup_id_x(), tid = __builtin_amdgcn_workitem_id_x();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 31, hi = lane >> 5;
+  const int64_t tok0 = (int64_t)blk * kGTok + (wave & 1) * 32;
+  const int c0 = (int)__builtin_amdgcn_workgroup_id_y() * kTileQ + (wave >> 1) * 32, c = c0 + r;
+  // past the end: the last token, the last query again
+  const float* kp = kc + (int64_t)b * kc_bs + (m_lo + (tok0 + r < n ? tok0 + r : n - 1)) * (int64_t)d_c + 4 * hi;
+  const float* qp = qc + (int64_t)b * q_bs + (int64_t)(c < l_c ? c : l_c - 1) * d_c + 4 * hi;
+  f32x16 even, odd;                                        // two chains, each of half the sum
+#pragma unroll
+  for (int v = 0; v < 16; ++v) even[v] = odd[v] = 0.f;
+  constexpr int kAhead = 4;                                // steps of eight dimensions in flight: all of them at d_c = 32
+  const int steps = d_c / 8;                               // even
+  for (int j0 = 0; j0 < steps; j0 += kAhead) {
+    f32x4 k4[kAhead], q4[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int at = 8 * (j0 + j < steps ? j0 + j : j0);
+      k4[j] = *(const f32x4*)(kp + at);
+      q4[j] = *(const f32x4*)(qp + at);
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; j += 2) {
+      if (j0 + j >= steps) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        even = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[j][e], q4[j][e], even, 0, 0, 0);
+        odd = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[j + 1][e], q4[j + 1][e], odd, 0, 0, 0);
+      }
+    }
+  }
+  if (hists && __builtin_amdgcn_workgroup_id_y() == 0)
+    for (int i = blk * 256 + tid; i < kHistWords; i += n_wg * 256) hists[(int64_t)b * hists_bs + i] = 0u;
+  even += odd;
+  float best = -INFINITY;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 s4 = {even[4 * g], even[4 * g + 1], even[4 * g + 2], even[4 * g + 3]};
+    best = fmaxf(best, fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3])));
+    if (c < l_c) *(f32x4*)(S + (int64_t)b * s_bs + (int64_t)c * s_ld + tok0 + 8 * g + 4 * hi) = s4;      // s_ld: whole blocks of 64 tokens
+  }
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
+  best = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  if (hi == 0) red[wave & 1][(wave >> 1) * 32 + r] = best;
+  __syncthreads();
+  const int cc = (int)__builtin_amdgcn_workgroup_id_y() * kTileQ + tid;
+  if (tid < kTileQ && cc < l_c) part[((int64_t)b * n_wg + blk) * l_c + cc] = fmaxf(red[0][tid], red[1][tid]);
 }
 
 // F[m] = max_c (S[c][m] - mu_c), mu_c = the largest of the n_part partial maxima of query c ([n_part][l_c]), found by
@@ -1262,9 +1322,15 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
       kernel<<<grid, 256, smem, st>>>(q, l_c, k, m_lo, n, d_c, part, S, s_ld, s_bs, q_bs, kc_bs, nblk, first_hist, first_hist_bs);
       return ESA_OK;
     };
-    const int rc = dtype == ESA_BF16 ? go(score_store_fma<bf16_t>, (const bf16_t*)qc, (const bf16_t*)kc_cache)
-                                     : go(score_store_fma<float>, (const float*)qc, (const float*)kc_cache);
-    if (rc != ESA_OK) return rc;
+    // (one query's S lies where F goes, in rows of any length)
+    if (dtype == ESA_F32 && l_c > 1 && (((uintptr_t)qc | (uintptr_t)kc_cache) % 16 == 0) && q_bs % 4 == 0 && kc_bs % 4 == 0) {
+      score_store_f32<<<dim3((unsigned)nblk, (unsigned)((l_c + kTileQ - 1) / kTileQ), batch), 256, 0, st>>>(
+          (const float*)qc, l_c, (const float*)kc_cache, m_lo, n, d_c, part, S, s_ld, s_bs, q_bs, kc_bs, nblk, first_hist, first_hist_bs);
+    } else {
+      const int rc = dtype == ESA_BF16 ? go(score_store_fma<bf16_t>, (const bf16_t*)qc, (const bf16_t*)kc_cache)
+                                       : go(score_store_fma<float>, (const float*)qc, (const float*)kc_cache);
+      if (rc != ESA_OK) return rc;
+    }
     finish(nblk);
   } else {
     uint32_t* mu = (uint32_t*)ws;

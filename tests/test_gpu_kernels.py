@@ -779,3 +779,21 @@ def test_split_key_attention_over_streamed_rows(esa, B, H, H_kv, d, l_C, keys):
         want, want_lse = orc.attend(q[b], K[b], V[b], t0, l_I, l_L, sel[b], 1.0 / np.sqrt(d))
         assert np.max(np.abs(to_f64(O[b]) - want)) <= O_TOL["bf16"]
         assert np.max(np.abs(to_f64(lse[b]) - want_lse)) <= 1e-3
+
+
+# fp32 scores on the matrix cores: one token and one more than a block, tiles of queries and one more, every number of steps in flight; rows that
+# are not 16-byte aligned take plain FMAs
+@pytest.mark.parametrize("B,l_c,n,d_c,eps,shift", [(1, 2, 1, 16, 0, 0), (2, 65, 63, 48, 1, 0), (3, 33, 65, 32, 0, 0), (1, 64, 4097, 256, 17, 0), (2, 100, 3000, 112, 2, 0),
+                                                   (1, 33, 500, 32, 0, 1), (2, 5, 700, 64, 1, 2)])
+def test_fp32_scores_of_several_queries(esa, B, l_c, n, d_c, eps, shift):
+    say(f"score fp32 B={B} l_c={l_c} n={n} d_c={d_c} eps={eps} shift={shift}")
+    rng = np.random.default_rng(n + l_c)
+    qc, kc = (orc.round_to_storage(rng.standard_normal((B, m, d_c)), "f32") for m in (l_c, n + 5))
+    kd = torch.zeros(B * (n + 5) * d_c + shift, device="cuda")[shift:].view(B, n + 5, d_c)
+    kd.copy_(f64_to_dev(kc, "f32"))
+    got = to_f64(esa.esa_score(f64_to_dev(qc, "f32"), kd, 3, n + 3, eps=eps))
+    for b in range(B):
+        want = orc.importance(qc[b], kc[b, 3:n + 3])
+        want = orc.proximity(want, eps) if eps else want
+        assert np.max(np.abs(got[b] - want)) <= F_TOL["f32"]
+        assert got[b].max() == 0.0
