@@ -173,35 +173,36 @@ __global__ __launch_bounds__(256) void compress_mfma_bf16(const bf16_t* __restri
 // C[4*(l/16) .. +3][l%16].  A rows are tokens (of all batch entries, numbered through), B columns are outputs.
 //
 // A workgroup owns TT x 16 rows x 16 outputs of both inputs, its eight waves take every eighth piece of 64 reduction
-// elements.  What bounds it is the rate at which a compute unit takes rows in (75 GB/s from L2): each reads (16 TT + 16)
+// elements.  What bounds it is the rate at which the L2s hand rows out (512 tokens: 80 MB in the 3.4 us of the loop, 24 TB/s of some 31): each reads (16 TT + 16)
 // rows of d_in.  Read as fragments, sixteen half cache lines per instruction, a line's second half had left the first-
 // level cache before it was asked for and the 80 MB of a chunk of 512 tokens became 160 MB of L2 traffic: 11.1 us
-// (7.3 now; 1024 tokens 22.4 -> 11.0, 77 tokens 9.8 -> 6.4).  So whole lines go to LDS without passing through registers, eight 128-byte rows per instruction, RING
-// pieces ahead in a ring of the wave's own: no barrier until the waves' sums meet, in a fixed order (deterministic).
+// (7.0 now; 1024 tokens 22.4 -> 10.9, 77 tokens 9.8 -> 6.0).  So whole lines go to LDS without passing through registers, eight 128-byte rows per instruction, two
+// pieces at a time in a ring of the wave's own: no barrier until the waves' sums meet, in a fixed order (deterministic).  (More pieces in flight are
+// no quicker: 512 tokens with two, three, four, five 7.0, 7.4, 7.4, 8.0 us; 16 rows 5.6, 6.0, 6.2, 6.4.)
 // 16-byte slots of a row are swizzled by row / 2 (two rows share the 256 bytes that the banks cover), which keeps the
 // fragment reads free of conflicts.
 constexpr int kPWaves = 8;
 constexpr int kPiece = 64;                       // reduction elements of a piece: a cache line per row
 constexpr int kPieceRows = 16 * kPiece * 2;      // bytes of sixteen rows of a piece
+constexpr int kRing = 2;                         // pieces of a wave in LDS
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void global_void;
 
-template <int TT, int RING>
-constexpr int packed_lds_bytes() { return kPWaves * RING * (TT + 1) * kPieceRows; }
+template <int TT>
+constexpr int packed_lds_bytes() { return kPWaves * kRing * (TT + 1) * kPieceRows; }
 
 // Every load but the LEFT newest of this wave is in LDS.
 template <int LEFT>
 __device__ __forceinline__ void loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory"); }
 
 // split_jobs: a workgroup takes one of the two inputs (column tiles numbered job by job) instead of both.
-template <int TT, int RING>
+template <int TT>
 __global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(CompressJob<bf16_t> j0, CompressJob<bf16_t> j1, int n_jobs,
                                                                           int split_jobs, uint32_t n_tok, uint32_t n_rows,
                                                                           int row_tiles, int col_tiles) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char ring_lds[];
   constexpr int kLoads = 2 * TT + 2;             // load instructions of a piece
   constexpr int kBytes = (TT + 1) * kPieceRows;  // a piece in LDS: the token rows, then the weight rows
-  static_assert((RING - 1) * kLoads < 64 && RING >= 2 && RING <= 4, "wait counter, waits below");
   // Column tiles of one row tile on one XCD where there are enough row tiles (workgroup w runs on XCD w % 8): its rows
   // are then fetched into one L2.  Fewer row tiles spread over the XCDs.
   const int n_col = split_jobs ? n_jobs * col_tiles : col_tiles;
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(Compre
     for (int i = 0; i < 2; ++i)
       pw[i] = (const char*)(j.Wt + (int64_t)(col0 + 8 * i + lr) * j.d_in + wave * kPiece + (slot ^ (((8 * i + lr) >> 1) & 7)) * 8);
   };
-  unsigned char* mine = ring_lds + wave * (RING * kBytes);
+  unsigned char* mine = ring_lds + wave * (kRing * kBytes);
   int issued = 0, in_slot = 0;
   auto issue = [&]() {                           // the next piece into the next slot of the ring
     if (issued == 0 || issued == c0) point_at(issued >= c0);
@@ -265,10 +266,10 @@ __global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(Compre
       pw[i] += kPWaves * kPiece * 2;
     }
     ++issued;
-    in_slot = in_slot + 1 == RING ? 0 : in_slot + 1;
+    in_slot = in_slot ^ 1;
   };
 #pragma unroll
-  for (int i = 0; i < RING; ++i)
+  for (int i = 0; i < kRing; ++i)
     if (i < count) issue();
 
   // Two chains per tile (even and odd halves of the pieces) for each input.
@@ -282,10 +283,7 @@ __global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(Compre
   const uint32_t frag = (uint32_t)(uintptr_t)(lds_void*)mine + r * 128 + ((q ^ ((r >> 1) & 7)) << 4);
   int out_slot = 0;
   for (int i = 0; i < count; ++i) {
-    const int behind = issued - i - 1;           // pieces requested after this one
-    if (behind >= 3) loads_but<RING >= 4 ? 3 * kLoads : 0>();
-    else if (behind == 2) loads_but<RING >= 3 ? 2 * kLoads : 0>();
-    else if (behind == 1) loads_but<kLoads>();
+    if (issued - i == kRing) loads_but<kLoads>();  // a piece has been requested after this one
     else loads_but<0>();
     // The fragment reads and their wait are one block: reads that the compiler sees would wait for every load in flight.
     const uint32_t at0 = frag + (uint32_t)(out_slot * kBytes), at1 = at0 ^ 64u;
@@ -306,7 +304,7 @@ __global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(Compre
           : "memory");
     }
     if (issued < count) issue();                 // the slot is free: its fragments are in registers
-    out_slot = out_slot + 1 == RING ? 0 : out_slot + 1;
+    out_slot = out_slot ^ 1;
     auto multiply = [&](f32x4 (&c)[TT][2]) {
 #pragma unroll
       for (int t = 0; t < TT; ++t) {
@@ -322,7 +320,7 @@ __global__ __launch_bounds__(64 * kPWaves) void compress_mfma_packed_bf16(Compre
   __syncthreads();
   float* red = (float*)ring_lds;
   constexpr int kTile = TT * 256;
-  static_assert(2 * kPWaves * kTile * 4 <= packed_lds_bytes<TT, RING>(), "the sums of both inputs fit the ring");
+  static_assert(2 * kPWaves * kTile * 4 <= packed_lds_bytes<TT>(), "the sums of both inputs fit the ring");
 #pragma unroll
   for (int j = 0; j < 2; ++j)
     if (j >= job_first && j <= job_last)
@@ -437,17 +435,17 @@ bool packed_ok(const void* x, int64_t d_in, int64_t ldx, const void* W, int64_t 
   return d_in % kPiece == 0 && ldx % 8 == 0 && x_bs % 8 == 0 && (((uintptr_t)x | (uintptr_t)W) % 16 == 0);
 }
 
-template <int TT, int RING>
+template <int TT>
 int run_packed_tiles(const CompressJob<bf16_t>& j0, const CompressJob<bf16_t>& j1, int n_jobs, int split_jobs, uint32_t n_tok,
                      uint32_t n_rows, int d_c, hipStream_t st) {
-  constexpr int kLds = packed_lds_bytes<TT, RING>();
+  constexpr int kLds = packed_lds_bytes<TT>();
   static OncePerDevice raised;
-  const int rc = raise_lds_limit(raised, {(const void*)compress_mfma_packed_bf16<TT, RING>}, kLds, "esa_compress");
+  const int rc = raise_lds_limit(raised, {(const void*)compress_mfma_packed_bf16<TT>}, kLds, "esa_compress");
   if (rc != ESA_OK) return rc;
   const int row_tiles = (int)((n_rows + 16 * TT - 1) / (16 * TT)), col_tiles = d_c / 16;
   const int64_t padded = row_tiles >= 8 ? (row_tiles + 7) / 8 * 8 : row_tiles;
   const int64_t n_wg = padded * col_tiles * (split_jobs ? n_jobs : 1);
-  compress_mfma_packed_bf16<TT, RING><<<dim3((unsigned)n_wg), 64 * kPWaves, kLds, st>>>(j0, j1, n_jobs, split_jobs, n_tok, n_rows,
+  compress_mfma_packed_bf16<TT><<<dim3((unsigned)n_wg), 64 * kPWaves, kLds, st>>>(j0, j1, n_jobs, split_jobs, n_tok, n_rows,
                                                                                       row_tiles, col_tiles);
   ESA_LAUNCH_CHECK("compress");
   return ESA_OK;
@@ -465,8 +463,8 @@ int run_packed(const CompressJob<bf16_t>& j0, const CompressJob<bf16_t>& j1, int
   // Sixteen rows per workgroup while those fit the chip at one workgroup per compute unit (each brings 32 rows of d_in
   // in); beyond, thirty-two rows (48 rows for twice the work).  Both inputs in one workgroup, unless compute units
   // would stay idle.
-  if (tiles > 256) return run_packed_tiles<2, 3>(j0, j1, n_jobs, 0, (uint32_t)n_tok, n_rows, d_c, st);
-  return run_packed_tiles<1, 4>(j0, j1, n_jobs, n_jobs == 2 && 2 * tiles <= 256, (uint32_t)n_tok, n_rows, d_c, st);
+  if (tiles > 256) return run_packed_tiles<2>(j0, j1, n_jobs, 0, (uint32_t)n_tok, n_rows, d_c, st);
+  return run_packed_tiles<1>(j0, j1, n_jobs, n_jobs == 2 && 2 * tiles <= 256, (uint32_t)n_tok, n_rows, d_c, st);
 }
 
 // The kernel for every storage type, shape and alignment; job 1 may repeat job 0 (n_jobs = 1).
