@@ -261,46 +261,41 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
   // Rows past the chunk repeat its last query: a repeated row changes no maximum, and its own results
   // are never written (first sweep) or are pushed to -inf by mu = +inf (second).  Register v of tile mt
   // belongs to row 8*(v/4) + 4*hi + v%4 of the tile.
-  //
-  // The requests for the fragments are instructions written out here, and so
-  // is the wait that ends them (queries_arrived): had the compiler generated the loads, its own wait for them
-  // would be a wait for everything once loads into LDS are outstanding behind them (it does not count on
-  // those completing in order with ordinary loads), which would put a round trip in front of the share's
-  // requests.  Between request and wait the registers are only named by that wait.
+  // Later blocks of a chunk of more than 512 queries come straight from memory.  Requests and wait are one block of instructions, whose
+  // registers are complete behind it; a load of the compiler's would put its wait into the tile loop, which the first block
+  // runs with the share still landing.
   auto wave_has_queries = [&](int qb) { return qb * kQPerBlock + member * kQPerWave < l_c; };
-  auto request_query_block = [&](int qb) {
+  auto load_query_block = [&](int qb) {
     if (!wave_has_queries(qb)) return;    // a wave without queries only takes part in the share's loads and the barriers
     const bf16_t* q = qc + (int64_t)b * q_bs;
     const int lane = lane_now(), r = lane & 31, hi = lane >> 5;
+    const bf16_t* p[kMT];
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt) {
       int row = qb * kQPerBlock + member * kQPerWave + 32 * mt + r;
       row = row < l_c ? row : l_c - 1;
-      const bf16_t* p = q + (int64_t)row * kDc + hi * 8;
-#pragma unroll
-      for (int ks = 0; ks < kKSteps; ++ks)
-        asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(a[mt][ks]) : "v"(p), "n"(ks * 32));
+      p[mt] = q + (int64_t)row * kDc + hi * 8;
     }
+#define ESA_LOAD4(r0, r1, r2, r3, p, at)                                                                                   \
+  "global_load_dwordx4 %" r0 ", %" p ", off offset:" at "\n\tglobal_load_dwordx4 %" r1 ", %" p ", off offset:" at "+32\n\t" \
+  "global_load_dwordx4 %" r2 ", %" p ", off offset:" at "+64\n\tglobal_load_dwordx4 %" r3 ", %" p ", off offset:" at "+96\n\t"
+#define ESA_REGS4(mt, ks) "=&v"(a[mt][ks]), "=&v"(a[mt][(ks) + 1]), "=&v"(a[mt][(ks) + 2]), "=&v"(a[mt][(ks) + 3])
+    if constexpr (kKSteps == 8)
+      asm volatile(ESA_LOAD4("0", "1", "2", "3", "16", "0") ESA_LOAD4("4", "5", "6", "7", "16", "128")
+                   ESA_LOAD4("8", "9", "10", "11", "17", "0") ESA_LOAD4("12", "13", "14", "15", "17", "128") "s_waitcnt vmcnt(0)"
+                   : ESA_REGS4(0, 0), ESA_REGS4(0, kKSteps - 4), ESA_REGS4(1, 0), ESA_REGS4(1, kKSteps - 4)
+                   : "v"(p[0]), "v"(p[1])
+                   : "memory");
+    else
+      asm volatile(ESA_LOAD4("0", "1", "2", "3", "8", "0") ESA_LOAD4("4", "5", "6", "7", "9", "0") "s_waitcnt vmcnt(0)"
+                   : ESA_REGS4(0, 0), ESA_REGS4(1, 0)
+                   : "v"(p[0]), "v"(p[1])
+                   : "memory");
+#undef ESA_LOAD4
+#undef ESA_REGS4
   };
-#define ESA_QUERY_REGS(mt)                                                                                     \
-  "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3]), "+v"(a[mt][kKSteps - 4]), "+v"(a[mt][kKSteps - 3]), \
-      "+v"(a[mt][kKSteps - 2]), "+v"(a[mt][kKSteps - 1])
-#define ESA_QUERY_REGS_SHORT(mt) "+v"(a[mt][0]), "+v"(a[mt][1]), "+v"(a[mt][2]), "+v"(a[mt][3])
-  // Everything requested before the share has arrived once at most all but (16 / d_c-dependent) two tiles' worth of
-  // the share's requests are outstanding (first block; tiles 0 and 1 are in LDS then as well), or nothing at all
-  // (later blocks).
+  // Tiles 0 and 1 are in LDS once at most so many of the share's requests are outstanding.
   constexpr int kLeftFirst = kLoads - 2 / kTilesPerLoad;
-  auto queries_arrived = [&](bool first) {
-    if constexpr (kKSteps == 8) {
-      if (first) asm volatile("s_waitcnt vmcnt(%c16)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1) : "n"(kLeftFirst));
-      else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS(0), ESA_QUERY_REGS(1));
-    } else {
-      if (first) asm volatile("s_waitcnt vmcnt(%c8)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1) : "n"(kLeftFirst));
-      else asm volatile("s_waitcnt vmcnt(0)" : ESA_QUERY_REGS_SHORT(0), ESA_QUERY_REGS_SHORT(1));
-    }
-  };
-#undef ESA_QUERY_REGS
-#undef ESA_QUERY_REGS_SHORT
 
   // ---- the pipeline over a share's tiles
   bf16x8 bfr[kKSteps];
@@ -533,8 +528,7 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
     for (int i = 0; i < n_blocks; ++i) {
       if (i > 0) {
         in_regs = in_regs + 1 < n_blocks ? in_regs + 1 : 0;
-        request_query_block(in_regs);
-        queries_arrived(false);
+        load_query_block(in_regs);
       }
       const bool active = wave_has_queries(in_regs);
       if (decltype(sweep)::value == 0) {
