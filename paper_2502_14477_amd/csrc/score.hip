@@ -26,8 +26,9 @@ namespace {
 // off (see build.py) the device library's accessors behind threadIdx / blockIdx / gridDim are not inlined (their
 // floating-point mode attributes differ from the kernels'), and every use would be a function call.
 
-// Workspace: [batch][l_c] row maxima (uint32 keys or fp32), [batch][blocks][l_c] fp32 partial row maxima of the
-// matrix-core kernel, then (windows that no score kernel pools) [batch][n] fp32 unpooled scores.
+// Workspace: the row maxima (uint32 keys or fp32; eight copies of them and the shares' marks for the matrix-core sweeps, or
+// [batch][blocks][l_c] fp32 partial maxima of the kernels that store S), then (windows that no score kernel pools)
+// [batch][n] fp32 unpooled scores, then S where it is stored.
 __host__ __device__ inline size_t mu_bytes(int l_c, int batch) {      // rows padded to whole groups of 64
   return align_up((size_t)((l_c + 63) / 64 * 64) * batch * 4, 256);
 }
