@@ -307,8 +307,17 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
   const uint32_t first_lane = __builtin_amdgcn_workitem_id_x() & 63, frag_row = first_lane & 31;
   const uint32_t frag0_at = lds_tiles + frag_row * (kDc * 2) + ((first_lane >> 5) ^ swizzle(frag_row)) * 16;
   const uint32_t colmax_at = lds_colmax + frag_row * 4;
+  // A request only: its registers are the compiler's to use again from here on, as far as it knows, until a wait names them.  So every
+  // request is followed, on every path, by a wait with its fragment as an operand; those of the last step by fragments_arrived.
   auto read_fragment = [&](int nt, int ks) {
     asm volatile("ds_read_b128 %0, %1" : "=v"(bfr[ks]) : "v"((frag0_at ^ (uint32_t)(ks * 32)) + (uint32_t)nt * kTileBytes));
+  };
+  auto fragments_arrived = [&]() {
+    if constexpr (kKSteps == 8)
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bfr[0]), "+v"(bfr[1]), "+v"(bfr[2]), "+v"(bfr[3]), "+v"(bfr[kKSteps - 4]), "+v"(bfr[kKSteps - 3]),
+                   "+v"(bfr[kKSteps - 2]), "+v"(bfr[kKSteps - 1]) : : "memory");
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bfr[0]), "+v"(bfr[1]), "+v"(bfr[2]), "+v"(bfr[3]) : : "memory");
   };
   float best = -INFINITY;
   // One reduction step's share of the maximum / subtract work on a finished tile's accumulators.
@@ -390,6 +399,7 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
     }
 #pragma unroll
     for (int ks = 0; ks < kKSteps; ++ks) epilogue_part(sweep, acc1, ks);
+    fragments_arrived();
     epilogue_end(sweep, prev);
   };
 
