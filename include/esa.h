@@ -104,7 +104,8 @@ ESA_API int esa_compress_qk(const void* xq, int64_t d_in_q, int64_t ldxq, const 
  *   kc_cache  [batch][>= m_hi, d_c] contiguous rows, batch stride kc_bs
  *   score     [batch][m_hi-m_lo] fp32, batch stride score_bs
  *   workspace esa_score_workspace_bytes(l_c, m_hi-m_lo, eps, batch) bytes, 256-byte aligned (beyond 16 MiB of
- *             scores, l_c * (m_hi-m_lo) * batch * 4, the size does not fall with a longer row or more rows)
+ *             scores, l_c * (m_hi-m_lo) * batch * 4, the size of more than 16 tokens does not fall with a longer row,
+ *             more rows or more tokens, and is enough for one token over the same rows)
  * m_hi == m_lo is a no-op.
  */
 ESA_API size_t esa_score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch);

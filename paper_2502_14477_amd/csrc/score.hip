@@ -1235,9 +1235,24 @@ int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int
   return ESA_OK;
 }
 
+// What lies in front of the partial maxima: the sweeps', or the row maxima alone.
+__host__ inline size_t front_bytes(int l_c, int64_t n_mid, int eps, int batch) {
+  return l_c > kFewQueries ? sweeps_bytes(l_c, n_mid, eps, batch) : mu_bytes(l_c, batch);
+}
+
+// Callers size one workspace by their chunks and use it for the few tokens behind them, too, which store S and so need more than a chunk does.
+// A chunk's size is therefore not what the sweeps need but 4 bytes a query and share and 256 bytes a query (whole blocks): it covers any shorter
+// chunk that is swept, one token and, as far as it goes, up to sixteen (512 tokens over 20000: eight).
 size_t score_workspace_bytes(int l_c, int64_t n_mid, int eps, int batch) {
   if (l_c <= 0 || batch <= 0 || n_mid < 0) return 256;
-  size_t b = sweeps_bytes(l_c, n_mid, eps, batch) + part_bytes(l_c, n_mid, batch);
+  size_t b = front_bytes(l_c, n_mid, eps, batch) + part_bytes(l_c, n_mid, batch);
+  if (l_c > kFewQueries) {
+    const size_t shares = (size_t)most_shares(n_mid, eps <= kTailMaxEps ? eps : 0, batch), blocks = (l_c + kQPerBlock - 1) / kQPerBlock;
+    size_t rows = align_up(shares * l_c * 4, 256);
+    rows = rows > part_bytes(l_c, n_mid, batch) ? rows : part_bytes(l_c, n_mid, batch);
+    const size_t chunk = mu_bytes(l_c, batch) + rows + blocks * kQPerBlock * 256 * batch;
+    b = b > chunk ? b : chunk;
+  }
   if (eps > 0) b += align_up((size_t)n_mid * 4, 256) * (size_t)batch;
   b += stored_bytes(l_c, n_mid, batch);
   return b;
@@ -1253,7 +1268,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
   const bool narrow = eps <= kTailMaxEps;
   bool zeroed = false;                  // the selection's histograms have been zeroed ...
   if (first_hist_done) *first_hist_done = false;        // ... and the first one filled
-  float* part = (float*)((char*)ws + sweeps_bytes(l_c, n, eps, batch));
+  float* part = (float*)((char*)ws + front_bytes(l_c, n, eps, batch));
   char* at = (char*)part + part_bytes(l_c, n, batch);
   float* raw = score;
   int64_t raw_bs = score_bs;

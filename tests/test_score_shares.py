@@ -66,3 +66,17 @@ def test_score_workspace_for_the_longest_context_covers_shorter_ones():
             for batch in (1, 3, 7):
                 sizes = [esa.lib.esa_score_workspace_bytes(l_c, n, eps, batch) for n in LENGTHS if l_c * n * 4 > 16 << 20]
                 assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("eps", [0, 1, 16, 40])
+def test_score_workspace_for_a_chunk_covers_what_follows_it(eps):
+    """Shorter chunks, and one token, for any row."""
+    for n in LENGTHS:
+        for batch in (1, 3, 16):
+            for size in (lambda l_c: esa.lib.esa_score_workspace_bytes(l_c, n, eps, batch),
+                         lambda l_c: esa.lib.esa_score_select_gather_workspace_bytes(l_c, n, eps, 2048, batch)):
+                swept = [l_c for l_c in (17, 20, 32, 77, 300, 512, 513, 1024) if l_c * n * batch * 4 > 16 << 20]
+                sizes = [size(l_c) for l_c in swept]
+                assert sizes == sorted(sizes)
+                assert all(s >= size(1) for s in sizes), (n, batch)
+    assert esa.lib.esa_score_workspace_bytes(512, 20000, eps, 1) >= esa.lib.esa_score_workspace_bytes(8, 20000, eps, 1)      # whose scores are stored
