@@ -36,6 +36,8 @@ constexpr int64_t most_shares(int64_t n, int eps, int batch) {
   const int64_t rounds = share_rounds(n, eps, batch) * kComputeUnits, shortest = batch * shares_of(n, eps, 2);
   return rounds < shortest ? rounds : shortest;
 }
+// s / n is the upper half of s * inverse_of(n), or one more: s (2^32 - n * inverse) / (n 2^32) <= s / 2^32 < 1 is missing from the quotient.
+constexpr uint32_t inverse_of(uint32_t n) { return 0xFFFFFFFFu / n; }
 // Whether the second sweep pools over +-eps: the shares then lap over their neighbours', and where that would take another round
 // a kernel of its own pools.  (512 tokens over 131072, eps 1: score
 // 48.7 us pooled by the sweep, 40.0 so; five rows of 13000, 300 tokens, 35.6 / 22.9.)

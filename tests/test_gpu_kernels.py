@@ -202,6 +202,30 @@ def test_score_sweeps_that_do_not_wait_for_each_other(esa, B, l_c, n, d_c, eps):
         assert rc == 0 and torch.equal(got, want), ticks
 
 
+def test_score_of_many_rows_costs_what_its_rows_cost(esa):
+    """A workgroup finds a share's row in a time that does not grow with the number of rows: four times as many rows take about four times
+    as long, and below eight times (looked for row by row they took 11.1 times as long; 4.0 now)."""
+    say("score of 1024 and 4096 rows")
+    g = torch.Generator(device="cuda").manual_seed(11)
+    qc, kc = (torch.randn((4096, m, 128), generator=g, device="cuda").bfloat16() for m in (17, 600))
+    took = {}
+    for B in (1024, 4096):
+        best = None
+        for _ in range(5):                             # the first one warms up
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                got = esa.esa_score(qc[:B], kc[:B], 0, 600)
+            b.record()
+            b.synchronize()
+            best = a.elapsed_time(b) if best is None else min(best, a.elapsed_time(b))
+        took[B] = best
+        for row in (0, 511, B - 1):
+            want = orc.importance(to_f64(qc[row]), to_f64(kc[row]))
+            assert np.max(np.abs(to_f64(got[row]) - want)) <= F_TOL["bf16"], row
+    assert took[4096] < 8 * took[1024], took
+
+
 def test_score_sweeps_on_several_streams_at_once(esa):
     """Calls that compete for the compute units, each workgroup of which waits for the others of its call: the same bits, and an end."""
     say("score on four streams")

@@ -59,6 +59,16 @@ def test_bound_of_the_shares_covers_shorter_rows_and_fewer_of_them(shares):
                 assert i == 0 or shares[n, eps, batch][3] >= shares[n, eps, BATCHES[i - 1]][3]
 
 
+def test_row_of_a_share():
+    """The quotient as the sweeps find it: exact for shares up to 2^31 - 1, of rows of any length."""
+    for n in [1, 2, 3, 5, 7, 255, 256, 257, 1023, 1024, 65537, 10 ** 6, 2 ** 30, 2 ** 31 - 1] + list(range(1, 300, 11)):
+        inverse = 0xFFFFFFFF // n                                                 # inverse_of
+        top = 2 ** 31 - 1
+        for s in sorted({x for q in (0, 1, 2, 1000, 65534, top // n - 1, top // n) for x in (q * n - 1, q * n, q * n + 1, q * n + n - 1, top) if 0 <= x <= top}):
+            b = s * inverse >> 32
+            assert b + (s - b * n >= n) == s // n, (s, n)
+
+
 def test_score_workspace_for_the_longest_context_covers_shorter_ones():
     # 512 and 77 queries; rows beyond the size at which S is stored
     for l_c in (512, 77):
