@@ -705,7 +705,7 @@ __global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ ow
 // ------------------------------------------------------------------------------------------ decode (l_c = 1)
 // One current token: S is a matrix-vector product over the whole compressed-key cache, pure HBM
 // streaming.  LPR lanes share a K' row (16 bytes each), so a wave reads 64*16 contiguous bytes per
-// step; a workgroup covers 64 or 256 rows.  Writes S and the workgroup's maximum of it (no atomics: thousands of
+// step; a workgroup covers 64 or 512 rows.  Writes S and the workgroup's maximum of it (no atomics: thousands of
 // workgroups folding into one word serialise in L2); score_finish then reduces those maxima to mu,
 // every workgroup for itself, and forms F = S - mu.
 // What bounds it is HBM.  Workgroups of 512 rows, eight requests a lane in flight, non-temporal (see streams), each row whole cache lines of one
@@ -713,9 +713,25 @@ __global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ ow
 // now).  Sixteen rows of 260 thousand (1.07 GB) 201.5 -> 169.6 us, 6.3 TB/s (with the loads behind their bounds checks and stores as they came
 // 256 rows a workgroup had 5.3); one row out of HBM 17.9 -> 13.1, of 180 thousand 15.4 -> 10.2.
 // Few rows in all give a compute unit too few requests that way, and the last-level cache often has them still: 64 rows a workgroup, ordinary
-// loads.  64 / 512 rows, us, three inputs in turn and twelve: 150 thousand 8.3 / 11.5, 9.9 / 11.2; 180 9.6 / 11.6, 10.2 / 11.6; 210 10.4 / 12.1, 11.8 / 12.0;
-// 262 12.9 / 13.5, 13.7 / 13.7, but then score_finish has a list of partial maxima to go through that is eight times as long (4.2 -> 4.6).
-constexpr int64_t kGemvFewRows = 196608;
+// loads.  512 for one row of more than 196608, whose list of partial maxima each of score_finish's workgroups goes through (4.6 us with 64-row
+// workgroups, 4.2), and for more rows than that in all from 72 MB on, where at most an eighth of the work is padding.  64 / 512 rows, us:
+//                           score and selection, one input again and again, three in turn, twelve      the step, attention between two scores
+//    1 x 165 thousand, d' 128   42 MB   22.1 / 22.9   22.3 / 24.2   23.4 / 24.0
+//    1 x 262           d'  64   34 MB   20.9 / 20.6   22.2 / 21.1   23.5 / 22.0
+//    1 x 262           d' 128   67 MB   26.2 / 25.8   26.2 / 25.8   28.2 / 26.9
+//    1 x 262           d' 256  134 MB   36.0 / 36.8   39.5 / 38.0   39.8 / 38.9
+//    8 x  30           d' 128   61 MB   25.3 / 25.9   24.8 / 26.5   27.3 / 27.1                           58.4 / 60.7
+//   16 x  32           d'  64   66 MB   27.3 / 29.0   27.4 / 29.7   29.2 / 29.7                           62.3 / 65.2
+//    4 x 150           d'  64   77 MB                                                                     48.4 / 47.1
+//    2 x 190           d' 128   97 MB                                                                     51.3 / 49.0
+//    8 x  60           d' 128  123 MB   35.2 / 37.4   38.7 / 38.2   39.3 / 38.8                           73.6 / 71.8
+//    2 x 150           d' 256  154 MB                                                                     60.8 / 62.7
+//   12 x 100           d' 128  307 MB                                                                    121.6 / 115.5
+// (A single layer whose K' a cache keeps from one call to the next would rather have 64 up to 270 MB: 16 x 60 thousand 54.5 / 61.7.)
+__host__ inline bool gemv_streams(int64_t n, int batch, int d_c) {
+  const int64_t rows = n * batch;
+  return n > 196608 || (rows > 196608 && rows * d_c * (int64_t)sizeof(bf16_t) >= ((int64_t)72 << 20) && (n + 511) / 512 * 512 * 8 <= n * 9);
+}
 // grids of the passes over the scores (host and device agree on them; the kernels do not ask the dispatch packet)
 __host__ __device__ inline int maxpool_blocks(int64_t n) { return (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096); }
 
@@ -1306,10 +1322,10 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     pool_left = eps > 0 && !narrow;
   };
   if (vec_ok && l_c == 1 && (d_c == 64 || d_c == 128 || d_c == 256)) {
-    const bool few_rows = n * batch <= kGemvFewRows;
-    const int rows = few_rows ? 64 : 512, threads = few_rows ? 256 : 512, nblk = (int)((n + rows - 1) / rows);
-    const auto gemv = few_rows ? (d_c == 64 ? score_gemv_bf16<8, 256, 2> : d_c == 128 ? score_gemv_bf16<16, 256, 4> : score_gemv_bf16<32, 256, 8>)
-                               : (d_c == 64 ? score_gemv_bf16<8, 512, 8> : d_c == 128 ? score_gemv_bf16<16, 512, 16> : score_gemv_bf16<32, 512, 32>);
+    const bool stream = gemv_streams(n, batch, d_c);
+    const int rows = stream ? 512 : 64, threads = stream ? 512 : 256, nblk = (int)((n + rows - 1) / rows);
+    const auto gemv = stream ? (d_c == 64 ? score_gemv_bf16<8, 512, 8> : d_c == 128 ? score_gemv_bf16<16, 512, 16> : score_gemv_bf16<32, 512, 32>)
+                             : (d_c == 64 ? score_gemv_bf16<8, 256, 2> : d_c == 128 ? score_gemv_bf16<16, 256, 4> : score_gemv_bf16<32, 256, 8>);
     gemv<<<dim3((unsigned)nblk, batch), threads, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
                                                       first_hist, first_hist_bs);
     if (tail && narrow) {
