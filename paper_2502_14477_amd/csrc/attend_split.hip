@@ -666,8 +666,11 @@ int with_slots(SplitArgs* a, const SplitCall& c, int n_slot) {
 // one layer's step to the next beside what else passes through it.  One token, 16 x 4225 keys of 8 KV heads (277 MB), us, three inputs in turn:
 // 54.7 -> 50.2 (55.2 -> 50.4 on long documents); 8 sequences (138 MB) 31.1 -> 28.9, 4 (69 MB) 19.3 -> 18.3.  Less is often there still:
 // 3 sequences (52 MB) 14.6 / 14.7, five tokens of 2 (35 MB) 14.4 -> 15.3.  (One input again and again: 8 sequences 26.6 -> 29.1.)  Row tiles that share
-// keys want them kept (fp32, sixteen row tiles: a step 52.2 -> 53.9); so do gathered rows, which have just been written (8 re-encoded sequences 34.5 -> 35.4).
+// keys want them kept (fp32, sixteen row tiles: a step 52.2 -> 53.9); so do gathered rows, which have just been written (8 re-encoded sequences 34.5 -> 35.4),
+// and sequences that share one cache (16 of them 28.9 / 30.6).
 bool streams(const SplitCall& c, const SplitArgs& a, int64_t n_keys) {
+  const KeyView& v = a.view[0];
+  if (c.batch > 1 && (v.k_bs_bytes == 0 || v.v_bs_bytes == 0)) return false;
   return c.dtype == ESA_BF16 && a.n_rt == 1 && !c.turns && !c.k_sel && 2 * n_keys * c.h_kv * c.batch * c.d * 2 >= ((int64_t)64 << 20);
 }
 template <typename T, int D>

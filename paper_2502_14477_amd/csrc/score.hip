@@ -728,8 +728,11 @@ __global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ ow
 //    2 x 150           d' 256  154 MB                                                                     60.8 / 62.7
 //   12 x 100           d' 128  307 MB                                                                    121.6 / 115.5
 // (A single layer whose K' a cache keeps from one call to the next would rather have 64 up to 270 MB: 16 x 60 thousand 54.5 / 61.7.)
-__host__ inline bool gemv_streams(int64_t n, int batch, int d_c) {
+// Sequences that share one K' read it from a cache all but once: 8 x 130 thousand 22.0 / 46.5, five queries each of 4 x 130 27.4 / 30.9.
+__host__ inline bool shared_keys(int batch, int64_t kc_bs) { return batch > 1 && kc_bs == 0; }
+__host__ inline bool gemv_streams(int64_t n, int batch, int d_c, int64_t kc_bs) {
   const int64_t rows = n * batch;
+  if (shared_keys(batch, kc_bs)) return false;
   return n > 196608 || (rows > 196608 && rows * d_c * (int64_t)sizeof(bf16_t) >= ((int64_t)72 << 20) && (n + 511) / 512 * 512 * 8 <= n * 9);
 }
 // grids of the passes over the scores (host and device agree on them; the kernels do not ask the dispatch packet)
@@ -765,7 +768,8 @@ __global__ __launch_bounds__(THREADS) void score_gemv_bf16(const bf16_t* __restr
   constexpr int kRows = kRowsPerStep * STEPS;
   constexpr int kAhead = STEPS < 8 ? STEPS : 8;            // rows of a lane in flight
   constexpr bool kStream = THREADS == 512;
-  const int n_wg = (int)((n + kRows - 1) / kRows);         // workgroups per batch entry (the launch's grid)
+  const int n_wg = (int)((n + kRows - 1) / kRows);         // workgroups per batch entry
+  if ((int)__builtin_amdgcn_workgroup_id_x() >= n_wg) return;      // (the launch's grid is rounded up for shared_keys)
   __shared__ float red[THREADS / 64];
   __shared__ float staged[kRows];
   const int b = __builtin_amdgcn_workgroup_id_y(), tid = __builtin_amdgcn_workitem_id_x();
@@ -1322,11 +1326,13 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     pool_left = eps > 0 && !narrow;
   };
   if (vec_ok && l_c == 1 && (d_c == 64 || d_c == 128 || d_c == 256)) {
-    const bool stream = gemv_streams(n, batch, d_c);
+    const bool stream = gemv_streams(n, batch, d_c, kc_bs);
     const int rows = stream ? 512 : 64, threads = stream ? 512 : 256, nblk = (int)((n + rows - 1) / rows);
     const auto gemv = stream ? (d_c == 64 ? score_gemv_bf16<8, 512, 8> : d_c == 128 ? score_gemv_bf16<16, 512, 16> : score_gemv_bf16<32, 512, 32>)
                              : (d_c == 64 ? score_gemv_bf16<8, 256, 2> : d_c == 128 ? score_gemv_bf16<16, 256, 4> : score_gemv_bf16<32, 256, 8>);
-    gemv<<<dim3((unsigned)nblk, batch), threads, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
+    // workgroup w runs on XCD w % 8: in rows of a multiple of eight, all sequences that share a part of K' fetch it into one L2
+    const unsigned grid = shared_keys(batch, kc_bs) ? (unsigned)((nblk + 7) / 8 * 8) : (unsigned)nblk;
+    gemv<<<dim3(grid, batch), threads, 0, st>>>((const bf16_t*)qc, (const bf16_t*)kc_cache, m_lo, n, part, raw, q_bs, kc_bs, raw_bs,
                                                       first_hist, first_hist_bs);
     if (tail && narrow) {
       *tail = ScoreTail{raw, raw_bs, part, nblk, eps};
@@ -1336,7 +1342,7 @@ int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, in
     }
   } else if (vec_ok && l_c <= kFewQueries && (d_c == 128 || d_c == 64)) {
     const int nblk = (int)((n + kFewTok - 1) / kFewTok);
-    const bool stream = n * batch * d_c * (int64_t)sizeof(bf16_t) >= kFewStreamBytes;
+    const bool stream = !shared_keys(batch, kc_bs) && n * batch * d_c * (int64_t)sizeof(bf16_t) >= kFewStreamBytes;
     const auto few = d_c == 128 ? (stream ? score_few_bf16<128, true> : score_few_bf16<128, false>)
                                 : (stream ? score_few_bf16<64, true> : score_few_bf16<64, false>);
     few<<<dim3((unsigned)nblk, batch), 256, 0, st>>>((const bf16_t*)qc, l_c, (const bf16_t*)kc_cache, m_lo, n, part, S, s_ld, s_bs, q_bs,
