@@ -97,6 +97,7 @@ struct AttendArgs {
   int n_slot;         // ... of so many per row
   uint32_t follow;    // tiles of a slice at whose end the softmax reference moves to the running maximum (head size 128)
   int to_slots;       // 1: write partial results even when the launch has a single slice
+  int stream_slices;  // head size 64: slices leave non-temporally, as whole rows (see kStreamSlices)
   float c2;           // scale * log2(e)
   int64_t out_bs, sel_bs_bytes;
 };
@@ -668,9 +669,8 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
   // scale 2^-E that brings the row's largest magnitude to about 2^13 (fp16's 11-bit significand keeps the
   // rounding well below that of the bf16 output, and any magnitude bf16 inputs can produce fits); beside
   // them go m + E and l * 2^-E, so that the merge's sums of 2^(m+E-M) * (O 2^-E) and 2^(m+E-M) * (l 2^-E)
-  // are the plain log-sum-exp combination of Algorithm 1 with no trace of E.  Head size 64 stores its slices in fp32, as whole rows too
-  // and non-temporally: 512 tokens behind 32k (16.8 MB of slices) 50.1 -> 47.5 us, 100 tokens 19.2 -> 17.9; by ordinary stores whole rows
-  // or a lane's own pieces take the same.  (The fp16 slices of head size 128, the same bytes: 45.8 / 45.7 us, a step 0.994 to 1.006.)
+  // are the plain log-sum-exp combination of Algorithm 1 with no trace of E.  Head size 64 stores its slices in fp32: many bytes as whole
+  // rows too and non-temporally, few as each lane holds them.
   const float l_tot = halves_sum(l_run);
   const bool final_out = a.n_split == 1 && !a.to_slots;
   float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -679,6 +679,19 @@ __global__ __launch_bounds__(kThreads) void attend_mfma_bf16(AttendArgs a) {    
     if (!final_out) {
       const int64_t prow0 = ((int64_t)(b * a.n_slot + a.slot0 + split) * a.l_c) * a.h;
       if (hi == 0 && c_ok) *(float2*)(a.part_ml + (prow0 + (int64_t)c * a.h + head) * 2) = make_float2(m_run, l_tot);
+      if (!a.stream_slices) {
+        if (c_ok) {
+          float* dst = (float*)a.part_o + (prow0 + (int64_t)c * a.h + head) * D + 4 * hi;
+#pragma unroll
+          for (int md = 0; md < kMD; ++md)
+#pragma unroll
+            for (int vg = 0; vg < 4; ++vg) {
+              const f32x4 w = {o[md][4 * vg], o[md][4 * vg + 1], o[md][4 * vg + 2], o[md][4 * vg + 3]};
+              *(f32x4*)(dst + 32 * md + 8 * vg) = w;
+            }
+        }
+        return;
+      }
       __syncthreads();                   // every wave is done with the last tile
       float* mine = (float*)st + wave * 32 * D;
 #pragma unroll
@@ -910,8 +923,15 @@ Plan plan_one_call(int l_c, int h, int h_kv, int batch, int64_t keys, int64_t se
   return best;
 }
 
+// Head size 64: bytes of a launch's slices (256 a row) from which on they leave as whole rows and non-temporally.  As each lane holds them / so, us: 0.8 MB
+// (17 tokens, 8 heads) 9.5 / 11.0, 2.1 (17, 32) 11.1 / 12.2, 3.1 (100, 8) 11.7 / 12.3, 3.9 (64, 16) 12.46 / 12.40, 4.6 (40, 32) 14.69 / 14.69, 5.2 (2 x 40, 32)
+// 19.3 / 18.6, 5.7 (400, 8) 18.0 / 16.7, 6.3 (64, 16) 14.25 / 14.26, 6.6 (100, 32) 17.0 / 15.6, 13.1 (200, 32) 29.3 / 27.3, 16.8 (512, 32) 50.1 / 47.5.  Whole
+// rows by ordinary stores take what a lane's own pieces take, or 0.5 more.  (The fp16 slices of head size 128, 16.8 MB: 45.8 / 45.7, a step 0.994 to 1.006.)
+constexpr int64_t kStreamSlices = 5000000;
+
 void launch_tiles(AttendArgs& a, int d, int n_split, int slot0, hipStream_t st) {
   a.n_split = n_split;
+  a.stream_slices = (int64_t)n_split * a.batch * a.l_c * a.h * 256 >= kStreamSlices;
   a.split_step = split_step(n_split);
   a.slot0 = slot0;
   for_pair_grids((int64_t)a.batch * a.h_kv, a.n_qt, n_split, [&](dim3 grid, PairGrid placed) {

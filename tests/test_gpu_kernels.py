@@ -44,6 +44,7 @@ def attend_reencoded_rounded(q, K, V, t0, l_I, l_L, sel, w, base):
 @pytest.mark.parametrize("B,H,H_kv,d,t0,l_C,l_I,l_L,n_sel", [
     (1, 4, 4, 64, 900, 16, 8, 64, 31), (1, 8, 4, 64, 700, 17, 8, 100, 64), (2, 8, 2, 64, 1000, 65, 0, 130, 129),
     (1, 16, 2, 64, 1100, 33, 16, 64, 200), (1, 8, 2, 64, 0, 63, 16, 64, 0), (1, 32, 8, 64, 3000, 257, 128, 512, 700),
+    (1, 32, 8, 64, 3000, 41, 128, 1000, 1500), (2, 32, 8, 64, 3000, 41, 128, 1000, 1500), (1, 8, 8, 64, 3000, 399, 16, 1000, 700),      # few bytes of slices, many
     (1, 16, 2, 128, 1100, 33, 16, 64, 200), (2, 8, 2, 128, 1000, 65, 0, 130, 129), (1, 8, 8, 128, 700, 259, 8, 100, 64)])
 def test_matrix_core_attention_head_sizes_and_row_tiles(esa, B, H, H_kv, d, t0, l_C, l_I, l_L, n_sel):
     say(f"attend B={B} H={H} H_kv={H_kv} d={d} t0={t0} l_C={l_C} l_I={l_I} l_L={l_L} n_sel={n_sel}")
