@@ -157,11 +157,26 @@ __host__ inline int tiles_before_queries(int per, int d_c, int l_c) {
   const int room = (160 * 1024) / (64 * d_c) - 2 * query_waves(l_c), first = query_waves(l_c) == kWaves ? 4 : room;
   return per < first ? per : first;
 }
-// That, or the share and behind it the second sweep's column maxima, digit histogram and row maxima.
+// The share and behind it the second sweep's column maxima, digit histogram and row maxima.
+__host__ inline size_t second_sweep_lds_bytes(int per, int d_c) {
+  return (size_t)per * 32 * d_c * sizeof(bf16_t) + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t) + (size_t)(kQPerBlock + 4) * sizeof(float);
+}
+// Later blocks of a chunk of more than 512 queries come in through LDS too, behind all of that, while the block before is at work: whole (1), where there is
+// no room for it half of each wave's queries at a time (2); or, where a block is few queries or there is no room, straight from memory (0).  d_c = 128, score,
+// us, from memory / so: shares of two tiles (whole): 600 queries over 8 thousand tokens 17.4 / 15.7, 1024 21.4 / 17.7, 2048 36.5 / 28.7, 4096 67.4 / 49.0 (61.3 as two
+// launches), 8192 129.1 / 91.2 (109.0); of four (halves): 600 over 30 20.3 / 19.5, 1000 25.7 / 23.9, 4096 85.0 / 77.0; of eight: 600 over 60 26.6 / 27.7, 832
+// 33.5 / 33.4, 1000 35.6 / 34.0, 4096 126.3 / 117.7; of ten: 900 over 80 41.7 / 41.4, 1000 42.7 / 41.3.
+__host__ inline int later_queries_parts(int per, int d_c, int l_c) {
+  const size_t at = align_up(second_sweep_lds_bytes(per, d_c), 1024), block = (size_t)kQPerBlock * d_c * sizeof(bf16_t);
+  if (l_c <= kQPerBlock) return 0;
+  if (at + block <= 160 * 1024) return 1;
+  return at + block / 2 <= 160 * 1024 && (per <= 4 || l_c >= 896) ? 2 : 0;
+}
+__host__ inline int later_queries_at(int per, int d_c) { return (int)align_up(second_sweep_lds_bytes(per, d_c), 1024); }
 __host__ inline size_t sweeps_lds_bytes(int per, int d_c, int l_c) {
-  const size_t tile = 32 * d_c * sizeof(bf16_t), share = per * tile;
-  const size_t staged = (tiles_before_queries(per, d_c, l_c) + 2 * query_waves(l_c)) * tile;
-  const size_t second = share + (size_t)(per + 1) * 32 * sizeof(uint32_t) + (size_t)kRadixBins * sizeof(uint32_t) + (size_t)(kQPerBlock + 4) * sizeof(float);
+  const size_t tile = 32 * d_c * sizeof(bf16_t), staged = (tiles_before_queries(per, d_c, l_c) + 2 * query_waves(l_c)) * tile;
+  const int parts = later_queries_parts(per, d_c, l_c);
+  const size_t second = parts ? later_queries_at(per, d_c) + (size_t)kQPerBlock * d_c * sizeof(bf16_t) / parts : second_sweep_lds_bytes(per, d_c);
   return staged > second ? staged : second;
 }
 // Marks of the shares that are done: sixteen to a word, a word to 256 bytes, and kMuCopies copies of them all, one for the readers on each XCD:
@@ -199,13 +214,14 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 // What crosses workgroups inside the launch goes through device-scope atomics only (maxima, marks, and the loads that read them), each
 // wave's maxima complete (vmcnt) before its workgroup's marks: no fence, which would write back an L2 (5 to 10 us).  One copy of
 // the maxima per XCD: maxima on one address are served one at a time, 17 to 30 ns each.
-template <int DC>
+// LATER: how the blocks of queries behind the first come in (see later_queries_parts).
+template <int DC, int LATER>
 __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __restrict__ qc, const bf16_t* __restrict__ kc, int n, int l_c_arg,
                                                               int tiles_per_block, int before_queries, int member_bits, int n_row,
                                                               int n_shares, int n_wg, int eps, uint32_t row_inverse, uint32_t* mu_keys, uint32_t* marks,
                                                               float* __restrict__ score, int64_t q_bs, int64_t kc_bs, int64_t score_bs,
                                                               uint32_t* __restrict__ first_hist, int64_t first_hist_bs,
-                                                              uint32_t patience) {     // kc: the first middle token's row
+                                                              uint32_t patience, int later_at) {     // kc: the first middle token's row
   static_assert(DC == 64 || DC == 128, "swizzle and load pattern");
   constexpr int kDc = DC;
   constexpr int kKSteps = kDc / 16;        // MFMA reduction steps per tile
@@ -267,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
   // Rows past the chunk repeat its last query: a repeated row changes no maximum, and its own results
   // are never written (first sweep) or are pushed to -inf by mu = +inf (second).  Register v of tile mt
   // belongs to row 8*(v/4) + 4*hi + v%4 of the tile.
-  // Later blocks of a chunk of more than 512 queries come straight from memory.  Requests and wait are one block of instructions, whose
+  // Later blocks of a chunk of more than 512 queries, straight from memory (LATER == 0).  Requests and wait are one block of instructions, whose
   // registers are complete behind it; a load of the compiler's would put its wait into the tile loop, which the first block
   // runs with the share still landing.
   auto wave_has_queries = [&](int qb) { return qb * kQPerBlock + member * kQPerWave < l_c; };
@@ -480,26 +496,64 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
                                        (lds_void*)(lds_raw + (size_t)(8 * t + wave) * 1024), 16, 0, 0);
     }
   };
+  // Queries come through LDS, whole rows of 256 (128) bytes, four (eight) to an instruction, into a place of each wave's own: read as fragments, 16 bytes
+  // of 32 rows to an instruction, 512 of them held the address unit for 2 us before the share's first request got through.
+  constexpr int kRowsPerLoad = 64 / kPieces, kRowLoads = kQPerWave / kRowsPerLoad;
+  auto request_queries = [&](int qb, uint32_t stage, int from, int to) {          // loads [from, to) of the wave's
+    const int lane = lane_now();
+    const char* q = (const char*)(qc + (int64_t)b * q_bs);
+#pragma unroll 1
+    for (int i = from; i < to; i += n_groups) {
+      const uint32_t mine = kRowsPerLoad * i + lane / kPieces;
+      uint32_t row = qb * kQPerBlock + member * kQPerWave + mine;
+      row = row < (uint32_t)l_c ? row : (uint32_t)l_c - 1;
+      __builtin_amdgcn_global_load_lds((global_void*)(q + (row * (uint32_t)(kDc * sizeof(bf16_t)) + ((lane % kPieces) ^ swizzle(mine)) * 16)),
+                                       (lds_void*)(lds_raw + stage + 1024 * i), 16, 0, 0);
+    }
+  };
+  auto read_tile = [&](bf16x8 (&f)[kKSteps], uint32_t at) {    // requests and wait in one block: the registers are complete behind it
+    at += frag0_at;
+    if constexpr (kKSteps == 8)
+      asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                   "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[kKSteps - 4]),
+                     "=&v"(f[kKSteps - 3]), "=&v"(f[kKSteps - 2]), "=&v"(f[kKSteps - 1])
+                   : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u), "v"(at ^ 224u)
+                   : "memory");
+    else
+      asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
+                   : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u)
+                   : "memory");
+  };
+  static_assert(kMT == 2, "two tiles of queries");
+  auto read_queries = [&](uint32_t stage) {
+    asm volatile("" : "+s"(stage));                            // (its sixteen addresses would be kept from block to block)
+    read_tile(a[0], stage);
+    read_tile(a[1], stage + kTileBytes);
+  };
+  // A block of queries behind the first: requested (by halves the first one) while the block before is at work, and taken in.
+  auto later_stage = [&]() { return (uint32_t)(later_at + member * (kMT * kTileBytes / (LATER == 0 ? 1 : LATER))); };
+  auto request_later = [&](int qb) { request_queries(qb, later_stage(), 0, kRowLoads / (LATER == 0 ? 1 : LATER)); };
+  auto take_later = [&](int qb) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // a wave reads what it has requested itself
+    if constexpr (LATER == 1) {
+      read_queries(later_stage());
+    } else {
+      uint32_t stage = later_stage();
+      asm volatile("" : "+s"(stage));
+      read_tile(a[0], stage);
+      request_queries(qb, stage - 1024 * (kRowLoads / 2), kRowLoads / 2, kRowLoads);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      read_tile(a[1], stage);
+    }
+  };
   // Brings in the share at hand and, where `queries`, the first block of them.  When it returns the queries are in registers and, with one
   // group, tiles 0 and 1 in LDS; with several all tiles.
-  // The queries come through LDS, whole rows of 256 (128) bytes, four (eight) to an instruction: read as fragments, 16 bytes
-  // of 32 rows to an instruction, 512 of them held the address unit for 2 us before the share's first request got through.
   auto begin = [&](bool queries) {
-    constexpr int kRowsPerLoad = 64 / kPieces, kRowLoads = kQPerWave / kRowsPerLoad;
     const int before = queries ? before_queries : kMaxTilesPerBlock;
     const uint32_t stage = (uint32_t)((before + member * kMT) * kTileBytes);
-    if (queries) {
-      const int lane = lane_now();
-      const char* q = (const char*)(qc + (int64_t)b * q_bs);
-#pragma unroll 1
-      for (int i = group; i < kRowLoads; i += n_groups) {
-        const uint32_t mine = kRowsPerLoad * i + lane / kPieces;
-        uint32_t row = member * kQPerWave + mine;
-        row = row < (uint32_t)l_c ? row : (uint32_t)l_c - 1;
-        __builtin_amdgcn_global_load_lds((global_void*)(q + (row * (uint32_t)(kDc * sizeof(bf16_t)) + ((lane % kPieces) ^ swizzle(mine)) * 16)),
-                                         (lds_void*)(lds_raw + stage + 1024 * i), 16, 0, 0);
-      }
-    }
+    if (queries) request_queries(0, stage, group, kRowLoads);
     const int first_loads = queries && before < tpb ? before / kTilesPerLoad : kLoads;
     request_share(0, first_loads);
     if (queries) {
@@ -509,22 +563,7 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
       } else {
         wait_loads_then_barrier<0>();
       }
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) {                       // requests and wait in one block: the registers are complete behind it
-        const uint32_t at = frag0_at + stage + mt * kTileBytes;
-        if constexpr (kKSteps == 8)
-          asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-                       "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
-                       : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3]), "=&v"(a[mt][kKSteps - 4]),
-                         "=&v"(a[mt][kKSteps - 3]), "=&v"(a[mt][kKSteps - 2]), "=&v"(a[mt][kKSteps - 1])
-                       : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u), "v"(at ^ 224u)
-                       : "memory");
-        else
-          asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
-                       : "=&v"(a[mt][0]), "=&v"(a[mt][1]), "=&v"(a[mt][2]), "=&v"(a[mt][3])
-                       : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u)
-                       : "memory");
-      }
+      read_queries(stage);
     }
     if (first_loads < kLoads) {
       wait_loads_then_barrier<2 / kTilesPerLoad>();            // tiles 0 and 1 of four; every wave has its queries
@@ -541,11 +580,16 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
   // One sweep over the share at hand, all query blocks (chunks longer than 512 tokens have several): first the one in registers.
   auto sweep_share = [&](auto sweep, bool streaming) {
     const int n_blocks = (l_c + kQPerBlock - 1) / kQPerBlock;
+    auto next_block = [&]() { return in_regs + 1 < n_blocks ? in_regs + 1 : 0; };
     for (int i = 0; i < n_blocks; ++i) {
       if (i > 0) {
-        in_regs = in_regs + 1 < n_blocks ? in_regs + 1 : 0;
-        load_query_block(in_regs);
+        in_regs = next_block();
+        if constexpr (LATER == 0) load_query_block(in_regs);
+        else if (wave_has_queries(in_regs)) take_later(in_regs);
       }
+      // (behind a landing share: its waits count loads, and would wait for the share's last ones as well)
+      const bool landing = streaming && i == 0, more = LATER != 0 && i + 1 < n_blocks && wave_has_queries(next_block());
+      if (more && !landing) request_later(next_block());
       const bool active = wave_has_queries(in_regs);
       if (decltype(sweep)::value == 0) {
 #pragma unroll
@@ -573,7 +617,8 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
             for (int e = 0; e < 4; ++e) aux[mt][4 * g4 + e] = m4[e];
           }
       }
-      run_tiles(sweep, streaming && i == 0 && n_groups == 1, active);
+      run_tiles(sweep, landing && n_groups == 1, active);
+      if (more && landing) request_later(next_block());
       if (decltype(sweep)::value == 0 && (active || n_groups > 1)) flush_row_maxima(in_regs * kQPerBlock + member * kQPerWave, active);
     }
   };
@@ -1247,16 +1292,20 @@ int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int
   const int64_t n_shares = (int64_t)n_row * batch;
   const int n_wg = (int)(n_shares < kComputeUnits ? n_shares : kComputeUnits);
   static OncePerDevice raised;
-  const int rc = raise_lds_limit(raised, {(const void*)score_sweeps_bf16<DC>}, 160 * 1024, "score_sweeps_bf16");
+  constexpr int kHalves = DC == 128 ? 2 : 1;               // d_c = 64: there is always room for whole blocks
+  const int rc = raise_lds_limit(raised, {(const void*)score_sweeps_bf16<DC, 0>, (const void*)score_sweeps_bf16<DC, 1>, (const void*)score_sweeps_bf16<DC, kHalves>},
+                                 160 * 1024, "score_sweeps_bf16");
   if (rc != ESA_OK) return rc;
   uint32_t* mu_keys = (uint32_t*)ws;
   uint32_t* marks = (uint32_t*)((char*)ws + mu_copies_bytes(l_c, batch));
   const int64_t n_own = (int64_t)(mu_copies_bytes(l_c, batch) + mark_words(n_shares) * kMuCopies * 4) / 16;
+  const int parts = later_queries_parts(per, DC, l_c);
+  const auto sweeps = parts == 0 ? score_sweeps_bf16<DC, 0> : parts == 1 ? score_sweeps_bf16<DC, 1> : score_sweeps_bf16<DC, kHalves>;
   const int64_t n_clear = n_own + (hists ? (int64_t)batch * (kHistWords / 4) : 0);
   score_sweeps_clear<<<(unsigned)((n_clear + 255) / 256), 256, 0, st>>>((uint4*)ws, n_own, hists, hists_bs, batch);
-  score_sweeps_bf16<DC><<<n_wg, kThreads, sweeps_lds_bytes(per, DC, l_c), st>>>(
+  sweeps<<<n_wg, kThreads, sweeps_lds_bytes(per, DC, l_c), st>>>(
       qc, kc + m_lo * DC, (int)n, l_c, per, tiles_before_queries(per, DC, l_c), query_waves_log2(l_c), n_row, (int)n_shares, n_wg, eps, inverse_of((uint32_t)n_row),
-      mu_keys, marks, score, q_bs, kc_bs, score_bs, fill_first ? hists : nullptr, hists_bs, patience);
+      mu_keys, marks, score, q_bs, kc_bs, score_bs, fill_first ? hists : nullptr, hists_bs, patience, later_queries_at(per, DC));
   return ESA_OK;
 }
 

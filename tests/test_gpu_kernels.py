@@ -150,7 +150,10 @@ def test_sum_of_exponentials_is_rounded_once_when_its_reference_moves(esa):
 # (more than 192 queries): behind a short share, in the place of the last tiles of a long one, a block that is not full
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 40, 1, 64, 0), (1, 64, 8193, 64, 0), (2, 512, 33000, 64, 0), (1, 530, 66000, 64, 1),
                                              (1, 20, 131072, 64, 0), (1, 96, 40000, 128, 0), (1, 192, 33000, 128, 0), (1, 193, 20, 128, 0),
-                                             (2, 500, 20000, 128, 0), (1, 257, 40000, 128, 0), (1, 700, 131072, 128, 0), (1, 449, 66000, 128, 1)])
+                                             (2, 500, 20000, 128, 0), (1, 257, 40000, 128, 0), (1, 700, 131072, 128, 0), (1, 449, 66000, 128, 1),
+                                             # later blocks through LDS, whole, by halves and not: the longest shares that leave room and one token more, last
+                                             # blocks of few and all waves
+                                             (1, 513, 16384, 128, 0), (1, 1537, 16385, 128, 0), (1, 1025, 81920, 128, 0), (1, 1025, 81921, 128, 0), (1, 600, 32768, 128, 0), (1, 600, 32769, 128, 0), (1, 2049, 700, 128, 2), (3, 1024, 5000, 128, 0), (1, 1100, 131072, 64, 0), (2, 1500, 131072, 64, 0)])
 def test_matrix_core_score_sweeps(esa, B, l_c, n, d_c, eps):
     say(f"score B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
     rng = np.random.default_rng(n + l_c)
@@ -185,7 +188,7 @@ def test_score_sweeps_in_whole_rounds(esa, B, l_c, n, d_c, eps):
 # No workgroup of the sweeps depends on another one's being resident: told to wait for 0 or 2 us only, they do each other's row maxima,
 # and the scores have the same bits.  One share, a few, a round of them, two rounds, several rows; both query paths, several blocks of queries
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 20, 30, 128, 0), (1, 40, 20000, 64, 1), (1, 77, 48000, 128, 0), (1, 530, 130000, 128, 0),
-                                             (1, 300, 140000, 128, 3), (3, 40, 70000, 128, 0), (2, 512, 33000, 128, 0)])
+                                             (1, 300, 140000, 128, 3), (3, 40, 70000, 128, 0), (2, 512, 33000, 128, 0), (1, 1300, 9000, 128, 0), (3, 600, 70000, 64, 0)])
 def test_score_sweeps_that_do_not_wait_for_each_other(esa, B, l_c, n, d_c, eps):
     import ctypes
     say(f"score without waiting B={B} l_c={l_c} n={n} d_c={d_c} eps={eps}")
