@@ -188,13 +188,11 @@ __host__ __device__ constexpr int64_t mark_words(int64_t shares) { return (share
 // of four are 16-byte aligned and in bounds for every query tile that holds a query.
 __host__ __device__ inline int mfma_mu_stride(int l_c) { return (l_c + 63) / 64 * 64; }
 
-// Wait until at most LEFT vector-memory loads of this wave are outstanding, then the workgroup barrier.  Only the
-// first one also waits for the LDS operations issued before it, the initialising writes; in the tile loop the
-// fragment reads in flight stay in flight across the barrier.
-template <int LEFT, bool LDS_TOO = false>
+// Wait until at most LEFT vector-memory loads of this wave are outstanding, then the workgroup barrier.  It waits for no LDS operation: fragment reads
+// in flight stay in flight across it, and what the waves write to LDS for one another takes a __syncthreads.
+template <int LEFT>
 __device__ __forceinline__ void wait_loads_then_barrier() {
-  if (LDS_TOO) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
-  else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LEFT) : "memory");
 }
 
 // The kernel.  Workgroup g owns shares g, g + grid, ... of all rows together (one, where a round of workgroups takes them all).  It
