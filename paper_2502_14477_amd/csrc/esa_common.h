@@ -171,7 +171,7 @@ constexpr int kTailMaxEps = 16;     // wider windows keep their own pass
 // and *first_hist_done is set.
 // tail: null, or the selection that follows is launch_select_small: the scores are left as *tail says.
 // patience: how long the matrix-core sweeps' workgroups wait for one another before they do the missing work themselves: 0 (as long as
-// they have been running), or 1 + the time in units of 10 ns.
+// they have been running and 5 us), or 1 + the time in units of 10 ns.
 int launch_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
                  float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs,
                  void* ws, size_t ws_bytes, hipStream_t st, uint32_t* first_hist = nullptr, int64_t first_hist_bs = 0,

@@ -205,13 +205,16 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 // workgroups, a second fetch of the share and of the queries: 20.7 + 4.9 + 19.2 us against 4.9 + 35.5 with score_sweeps_clear (512 queries, 128 thousand
 // tokens), 7.4 + 2.3 + 7.6 against 2.1 + 13.7 (77, 48).  Steps: 101.3 -> 97.2 us, 49.6 -> 46.7; 1024 at 256k 417 -> 407, re-encoded 512 140.5 -> 133.6.
 //
-// The wait needs no other workgroup to be resident: it is bounded by the time the workgroup has been running itself, and a
+// The wait needs no other workgroup to be resident: it is bounded by the time the workgroup has been running itself plus kPatience, and a
 // workgroup that has waited so long does the missing shares' row maxima itself, one after the other (the maxima are
 // idempotent; whoever finishes a share marks it), so that every workgroup gets to its end whatever else holds the other compute units.
 //
 // What crosses workgroups inside the launch goes through device-scope atomics only (maxima, marks, and the loads that read them), each
 // wave's maxima complete (vmcnt) before its workgroup's marks: no fence, which would write back an L2 (5 to 10 us).  One copy of
 // the maxima per XCD: maxima on one address are served one at a time, 17 to 30 ns each.
+// What a workgroup waits beyond the time it has been running: those of a short call start up to 2 us apart, and redoing a share costs more than that.
+constexpr uint64_t kPatience = 500;              // 5 us in ticks of 10 ns (s_memrealtime)
+
 // LATER: how the blocks of queries behind the first come in (see later_queries_parts).
 template <int DC, int LATER>
 __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __restrict__ qc, const bf16_t* __restrict__ kc, int n, int l_c_arg,
@@ -650,7 +653,7 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
     if (wave == 0) {
       if (!waiting) {
         const uint64_t now = __builtin_amdgcn_s_memrealtime();     // 10 ns
-        give_up = now + (patience ? patience - 1 : (now - started) + 500);
+        give_up = now + (patience ? patience - 1 : (now - started) + kPatience);
       }
       int missing = -1;
       auto marks_from = [&](int c) {                              // the lane's word: the bits of shares
