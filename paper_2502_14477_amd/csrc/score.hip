@@ -115,7 +115,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // register-resident operand (64 per wave as A fragments for the whole d_c; chunks longer than
 // 512 loop over query blocks against the same LDS tile).  Share and queries stay where they are for the second sweep, so K' is read
 // from memory once, or, where the shares are more than a round of workgroups, once and again all but the last share of each.
-// Up to 256 queries do not give every wave 64 of its own: the waves that hold the same ones share out the tiles.
+// Up to 256 queries do not give every wave 64 of its own: where it pays, the waves that hold the same ones share out the tiles (query_waves_log2).
 //
 // Inside a wave the tiles are software-pipelined: right after the matrix instructions of reduction
 // step ks of tile t have issued, fragment ks of tile t+1 is read from LDS into the registers they
@@ -148,13 +148,20 @@ constexpr int kQPerBlock = kWaves * kQPerWave;
 // took 63.3 us instead of 61.0 (40 tokens at 50 thousand), 80.1 / 77.0 (128 at 100), 62.4 / 59.9 (60 at 12), 77.6 / 75.8 (256 at 30) and the same
 // 134 (512 at 130).
 // (score_shares.h: how long a share is, and when.)
-// Waves of a workgroup that hold different queries (64 each), a power of two; the others take other tiles for the same ones.
-__host__ inline int query_waves_log2(int l_c) { return l_c > 256 ? 3 : l_c > 128 ? 2 : l_c > 64 ? 1 : 0; }
-__host__ inline int query_waves(int l_c) { return 1 << query_waves_log2(l_c); }
+// Waves of a workgroup that hold different queries (64 each), a power of two; the others take other tiles for the same ones, which takes all tiles in LDS and a
+// barrier more for the row maxima.  A share of up to four tiles, or of d_c = 128 and more than 128 queries (whose waves are on all SIMDs as they are), is quicker
+// without: eight.  Score, us, shared out / eight waves: 48 queries over 8 thousand tokens (two tiles) 12.2 / 11.0, 17 over 15 12.6 / 11.2 (two launches of all
+// eight waves 11.4), 128 over 30 (four) 12.8 / 12.8, 45 (six) 13.4 / 14.4; 129 over 45 15.6 / 14.4, 200 39.3 / 36.4, 256 over 60 17.1 / 16.3, over 8 rows of 50 92.0 /
+// 81.2; d_c = 64, 256 queries, 60 thousand 12.5 / 12.9, 12 rows of 120 161 / 170.
+__host__ inline int query_waves_log2(int l_c, int per, int d_c) {
+  if (per <= 4 || (d_c == 128 && l_c > 128)) return 3;
+  return l_c > 256 ? 3 : l_c > 128 ? 2 : l_c > 64 ? 1 : 0;
+}
+__host__ inline int query_waves(int l_c, int per, int d_c) { return 1 << query_waves_log2(l_c, per, d_c); }
 // The first block of queries comes in through LDS behind the share's first tiles, in the place of those that are requested when it
 // is in registers: as many as leave room, or, where all eight waves hold queries and consume the tiles as they land, four.
 __host__ inline int tiles_before_queries(int per, int d_c, int l_c) {
-  const int room = (160 * 1024) / (64 * d_c) - 2 * query_waves(l_c), first = query_waves(l_c) == kWaves ? 4 : room;
+  const int waves = query_waves(l_c, per, d_c), room = (160 * 1024) / (64 * d_c) - 2 * waves, first = waves == kWaves ? 4 : room;
   return per < first ? per : first;
 }
 // The share and behind it the second sweep's column maxima, digit histogram and row maxima.
@@ -174,7 +181,7 @@ __host__ inline int later_queries_parts(int per, int d_c, int l_c) {
 }
 __host__ inline int later_queries_at(int per, int d_c) { return (int)align_up(second_sweep_lds_bytes(per, d_c), 1024); }
 __host__ inline size_t sweeps_lds_bytes(int per, int d_c, int l_c) {
-  const size_t tile = 32 * d_c * sizeof(bf16_t), staged = (tiles_before_queries(per, d_c, l_c) + 2 * query_waves(l_c)) * tile;
+  const size_t tile = 32 * d_c * sizeof(bf16_t), staged = (tiles_before_queries(per, d_c, l_c) + 2 * query_waves(l_c, per, d_c)) * tile;
   const int parts = later_queries_parts(per, d_c, l_c);
   const size_t second = parts ? later_queries_at(per, d_c) + (size_t)kQPerBlock * d_c * sizeof(bf16_t) / parts : second_sweep_lds_bytes(per, d_c);
   return staged > second ? staged : second;
@@ -1305,7 +1312,7 @@ int launch_sweeps(const bf16_t* qc, int l_c, const bf16_t* kc, int64_t m_lo, int
   const int64_t n_clear = n_own + (hists ? (int64_t)batch * (kHistWords / 4) : 0);
   score_sweeps_clear<<<(unsigned)((n_clear + 255) / 256), 256, 0, st>>>((uint4*)ws, n_own, hists, hists_bs, batch);
   sweeps<<<n_wg, kThreads, sweeps_lds_bytes(per, DC, l_c), st>>>(
-      qc, kc + m_lo * DC, (int)n, l_c, per, tiles_before_queries(per, DC, l_c), query_waves_log2(l_c), n_row, (int)n_shares, n_wg, eps, inverse_of((uint32_t)n_row),
+      qc, kc + m_lo * DC, (int)n, l_c, per, tiles_before_queries(per, DC, l_c), query_waves_log2(l_c, per, DC), n_row, (int)n_shares, n_wg, eps, inverse_of((uint32_t)n_row),
       mu_keys, marks, score, q_bs, kc_bs, score_bs, fill_first ? hists : nullptr, hists_bs, patience, later_queries_at(per, DC));
   return ESA_OK;
 }

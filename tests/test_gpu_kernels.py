@@ -185,6 +185,23 @@ def test_score_sweeps_in_whole_rounds(esa, B, l_c, n, d_c, eps):
         assert got[b].max() == 0.0
 
 
+# How a workgroup's waves share out queries and tiles changes no bit: the same queries once, in few waves, and again and again, in all eight.
+# Shares of two, four and six tiles, of sixteen, two to a workgroup; up to 64, 128 and 256 queries and one more
+@pytest.mark.parametrize("d_c", [64, 128])
+@pytest.mark.parametrize("n", [16384, 16385, 32768, 32769, 131072, 140000])
+@pytest.mark.parametrize("l_c", [17, 64, 65, 128, 129, 256])
+def test_waves_that_share_queries_find_the_same_scores(esa, l_c, n, d_c):
+    say(f"score by shared waves l_c={l_c} n={n} d_c={d_c}")
+    g = torch.Generator(device="cuda").manual_seed(n + l_c)
+    qc, kc = (torch.randn((m, d_c), generator=g, device="cuda").bfloat16() for m in (l_c, n))
+    got = esa.esa_score(qc, kc, 0, n)
+    assert torch.equal(got, esa.esa_score(qc.repeat(512 // l_c + 1, 1)[:512], kc, 0, n))
+    some = torch.randperm(n, generator=g, device="cuda")[:64]
+    S = qc.double() @ kc.double().T
+    want = (S - S.max(dim=1, keepdim=True).values).max(dim=0).values[some]
+    assert (got[some].double() - want).abs().max().item() <= F_TOL["bf16"]
+
+
 # No workgroup of the sweeps depends on another one's being resident: told to wait for 0 or 2 us only, they do each other's row maxima,
 # and the scores have the same bits.  One share, a few, a round of them, two rounds, several rows; both query paths, several blocks of queries
 @pytest.mark.parametrize("B,l_c,n,d_c,eps", [(1, 20, 30, 128, 0), (1, 40, 20000, 64, 1), (1, 77, 48000, 128, 0), (1, 530, 130000, 128, 0),
