@@ -41,12 +41,26 @@ __global__ void fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 // ------------------------------------------------------------------------------------------ generic
 constexpr int kGTok = 64;      // middle tokens per block (one per lane)
 
-// One fixed-order fp32 dot product, shared by both sweeps.
+// One fixed-order dot product in fp32, shared by both sweeps.  Of fp32 rows, in the order of the matrix instructions of score_store_f32, so that a token's
+// score does not depend on the call: two chains, of every other eight dimensions, each taking dimensions 0, 4, 1, 5, 2, 6, 3, 7 of its eight.  (One ascending chain:
+// scores 1.83e-7 from the 64-bit result at d_c 32, so 1.35e-7; 3.99e-7 and 2.29e-7 at 128.)  d_c is a multiple of 16.
 template <typename T>
 __device__ __forceinline__ float dot_fixed(const T* __restrict__ q, const float* __restrict__ krow, int d_c) {
-  float s = 0.f;
-  for (int i = 0; i < d_c; ++i) s = __fmaf_rn(load_f32(q + i), krow[i], s);
-  return s;
+  if constexpr (sizeof(T) == 4) {
+    float even = 0.f, odd = 0.f;
+    for (int i = 0; i < d_c; i += 16)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int at = i + e / 2 + e % 2 * 4;
+        even = __fmaf_rn(q[at], krow[at], even);
+        odd = __fmaf_rn(q[at + 8], krow[at + 8], odd);
+      }
+    return even + odd;
+  } else {
+    float s = 0.f;
+    for (int i = 0; i < d_c; ++i) s = __fmaf_rn(load_f32(q + i), krow[i], s);
+    return s;
+  }
 }
 
 // SWEEP 0: row maxima into mu_keys.  SWEEP 1: F into score.
@@ -949,7 +963,7 @@ __global__ __launch_bounds__(256) void score_few_bf16(const bf16_t* __restrict__
 }
 
 // The same for every storage type, d_c and alignment: a workgroup computes S for 64 tokens (one per lane) and 32 queries (eight per
-// wave), both in LDS as fp32 rows (the queries' reads are broadcasts), fp32 FMAs in ascending order.
+// wave), both in LDS as fp32 rows (the queries' reads are broadcasts), fp32 FMAs in ascending order (of fp32 rows in dot_fixed's).
 constexpr int kStoreQ = 32;
 constexpr int kTileQ = 64;
 __host__ __device__ inline int store_ld(int d_c) { return d_c + 4; }       // d_c is a multiple of 16: rows 16-byte aligned, spread over the banks
@@ -989,15 +1003,38 @@ __global__ __launch_bounds__(256) void score_store_fma(const T* __restrict__ qc,
   __syncthreads();
   float acc[kStoreQ / 4] = {};
   const float* qrow = qs + wave * (kStoreQ / 4) * ld;
-  for (int i = 0; i < d_c; i += 4) {
-    const float4 kv = *(const float4*)&smem[lane * ld + i];
+  if constexpr (sizeof(T) == 4) {                      // the order of dot_fixed
+    float odd[kStoreQ / 4] = {};
+    for (int i = 0; i < d_c; i += 16) {
+      float4 kv[4];
 #pragma unroll
-    for (int j = 0; j < kStoreQ / 4; ++j) {
-      const float4 qv = *(const float4*)&qrow[j * ld + i];
-      acc[j] = __fmaf_rn(qv.x, kv.x, acc[j]);
-      acc[j] = __fmaf_rn(qv.y, kv.y, acc[j]);
-      acc[j] = __fmaf_rn(qv.z, kv.z, acc[j]);
-      acc[j] = __fmaf_rn(qv.w, kv.w, acc[j]);
+      for (int p = 0; p < 4; ++p) kv[p] = *(const float4*)&smem[lane * ld + i + 4 * p];
+      auto eight = [](const float4& q0, const float4& q1, const float4& k0, const float4& k1, float s) {
+        s = __fmaf_rn(q1.x, k1.x, __fmaf_rn(q0.x, k0.x, s));
+        s = __fmaf_rn(q1.y, k1.y, __fmaf_rn(q0.y, k0.y, s));
+        s = __fmaf_rn(q1.z, k1.z, __fmaf_rn(q0.z, k0.z, s));
+        return __fmaf_rn(q1.w, k1.w, __fmaf_rn(q0.w, k0.w, s));
+      };
+#pragma unroll
+      for (int j = 0; j < kStoreQ / 4; ++j) {
+        const float4* qv = (const float4*)&qrow[j * ld + i];
+        acc[j] = eight(qv[0], qv[1], kv[0], kv[1], acc[j]);
+        odd[j] = eight(qv[2], qv[3], kv[2], kv[3], odd[j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kStoreQ / 4; ++j) acc[j] += odd[j];
+  } else {
+    for (int i = 0; i < d_c; i += 4) {
+      const float4 kv = *(const float4*)&smem[lane * ld + i];
+#pragma unroll
+      for (int j = 0; j < kStoreQ / 4; ++j) {
+        const float4 qv = *(const float4*)&qrow[j * ld + i];
+        acc[j] = __fmaf_rn(qv.x, kv.x, acc[j]);
+        acc[j] = __fmaf_rn(qv.y, kv.y, acc[j]);
+        acc[j] = __fmaf_rn(qv.z, kv.z, acc[j]);
+        acc[j] = __fmaf_rn(qv.w, kv.w, acc[j]);
+      }
     }
   }
 #pragma unroll
@@ -1013,8 +1050,7 @@ __global__ __launch_bounds__(256) void score_store_fma(const T* __restrict__ qc,
 // tokens, B columns queries; a lane's sixteen bytes of a row feed four instructions (lanes 32 apart hold neighbouring pieces).  A wave owns
 // 32 tokens x 32 queries and takes its fragments straight from memory: a small layer's call is round trips, and staging through LDS with
 // its index arithmetic, 72 LDS reads a wave and a butterfly per query made it 6.8 us for 128 queries over 1632 tokens of d_c 32, 4.2 now (five
-// queries over 940: 6.4 -> 3.8; the layer's step 28.8 -> 27.6).  Two chains of half the sum are nearer to the 64-bit result than one: scores 1.83e-7 ->
-// 1.35e-7 at d_c 32, 3.99e-7 -> 2.29e-7 at 128.
+// queries over 940: 6.4 -> 3.8).  dot_fixed's order.
 __global__ __launch_bounds__(256) void score_store_f32(const float* __restrict__ qc, int l_c, const float* __restrict__ kc, int64_t m_lo,
                                                        int64_t n, int d_c, float* __restrict__ part, float* __restrict__ S,
                                                        int64_t s_ld, int64_t s_bs, int64_t q_bs, int64_t kc_bs, int n_wg,

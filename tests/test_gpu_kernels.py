@@ -870,3 +870,23 @@ def test_fp32_scores_of_several_queries(esa, B, l_c, n, d_c, eps, shift):
         want = orc.proximity(want, eps) if eps else want
         assert np.max(np.abs(got[b] - want)) <= F_TOL["f32"]
         assert got[b].max() == 0.0
+
+
+# fp32: a token's score has the same bits whatever the call's other sizes and alignment.  One query, several on the matrix cores, several whose
+# rows are not 16-byte aligned, and more scores than are stored
+@pytest.mark.parametrize("n,d_c", [(15000, 16), (14337, 32), (14500, 48), (15000, 128), (14400, 256)])
+def test_fp32_scores_do_not_depend_on_the_call(esa, n, d_c):
+    say(f"score fp32 n={n} d_c={d_c}")
+    g = torch.Generator(device="cuda").manual_seed(n + d_c)
+    q, kc = torch.randn((1, d_c), generator=g, device="cuda"), torch.randn((n, d_c), generator=g, device="cuda")
+
+    def shifted(t):                        # the same rows, 4 bytes further
+        room = torch.empty(t.numel() + 1, device="cuda")
+        room[1:] = t.reshape(-1)
+        return room[1:].view(t.shape)
+
+    one = esa.esa_score(q, kc, 0, n)
+    for name, other in (("three", (q.repeat(3, 1), kc)), ("three, shifted", (shifted(q.repeat(3, 1)), kc)), ("one, shifted", (q, shifted(kc))),
+                        ("three hundred", (q.repeat(300, 1), kc)), ("three hundred, shifted", (q.repeat(300, 1), shifted(kc)))):
+        assert torch.equal(one, esa.esa_score(*other, 0, n)), name
+
