@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include "esa_common.h"
+#include "esa_internal.h"
 #include "attend_mfma.h"
 #include "radix_hist.h"
 
@@ -142,11 +143,11 @@ int esa_score(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64
   return score_call(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, ws_bytes, 0, stream);
 }
 
-// Not part of the boundary: esa_score whose workgroups wait at most ticks * 10 ns for one another, for the tests.
-ESA_API int esa_internal_score_waiting(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
-                                       float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* workspace,
-                                       size_t ws_bytes, uint32_t ticks, void* stream) {
-  return score_call(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, ws_bytes, ticks + 1, stream);
+int esa_internal_score_waiting(const void* qc, int l_c, const void* kc_cache, int64_t m_lo, int64_t m_hi, int d_c, int eps,
+                               float* score, int dtype, int batch, int64_t q_bs, int64_t kc_bs, int64_t score_bs, void* workspace,
+                               size_t ws_bytes, uint32_t ticks, void* stream) {
+  const uint32_t patience = ticks < UINT32_MAX ? ticks + 1 : UINT32_MAX;
+  return score_call(qc, l_c, kc_cache, m_lo, m_hi, d_c, eps, score, dtype, batch, q_bs, kc_bs, score_bs, workspace, ws_bytes, patience, stream);
 }
 
 size_t esa_select_topk_workspace_bytes(int64_t n, int k, int batch) { return topk_workspace_bytes(n, k, batch); }

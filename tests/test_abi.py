@@ -187,3 +187,18 @@ def test_attention_workspace_for_the_longest_chunk_covers_shorter_ones():
         for l_c in (16, 77, 300, 512):
             sizes = [size(l_c, h, h_kv, d, 1, batch) for batch in range(1, 40)]
             assert sizes == sorted(sizes)
+
+
+def _parameter_types(header, name):
+    text = open(os.path.join(ROOT, *header)).read()
+    listed = re.search(r"ESA_API\s+int\s+%s\s*\(([^)]*)\)" % name, text).group(1)
+    return [re.sub(r"\s*\w+$", "", p.strip()) for p in listed.split(",")]
+
+
+def test_entry_points_for_tests_are_declared():
+    """esa_score's parameters, and how long the workgroups wait in front of the stream: what the tests' call passes."""
+    boundary = _parameter_types(("include", "esa.h"), "esa_score")
+    internal = _parameter_types(("paper_2502_14477_amd", "csrc", "esa_internal.h"), "esa_internal_score_waiting")
+    assert internal == boundary[:-1] + ["uint32_t"] + boundary[-1:]
+    exported = subprocess.run(["nm", "-D", "--defined-only", esa.lib_path()], capture_output=True, text=True, check=True).stdout
+    assert set(re.findall(r"\besa_internal_\w+", exported)) == {"esa_internal_score_waiting"}
