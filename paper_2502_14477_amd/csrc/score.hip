@@ -229,6 +229,8 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 // The wait needs no other workgroup to be resident: it is bounded by the time the workgroup has been running itself plus kPatience, and a
 // workgroup that has waited so long does the missing shares' row maxima itself, one after the other (the maxima are
 // idempotent; whoever finishes a share marks it), so that every workgroup gets to its end whatever else holds the other compute units.
+// What a waiting workgroup holds meanwhile another stream's kernels do not get, and the other way round: a step of 512 tokens at 128 thousand whose local attention
+// starts on a second stream in front of the sweeps takes 148.5 us where the two launches took 137.5 (behind them 126.4 and 132.3; on one stream 104 and 109.5).
 //
 // What crosses workgroups inside the launch goes through device-scope atomics only (maxima, marks, and the loads that read them), each
 // wave's maxima complete (vmcnt) before its workgroup's marks: no fence, which would write back an L2 (5 to 10 us).  One copy of
@@ -754,8 +756,8 @@ __global__ __launch_bounds__(kThreads) void score_sweeps_bf16(const bf16_t* __re
   }
 }
 
-// In front of the sweeps: mu_keys and the marks, and the selection's histograms, cleared.  (A kernel of its own, 2 us: nothing that a call finds in its
-// workspace says whether another workgroup has cleared it already.)
+// In front of the sweeps: mu_keys and the marks, and the selection's histograms, cleared.  (A kernel of its own, 2 us for 77 tokens, 4 to 5 for 512 and 1024: nothing
+// that a call finds in its workspace says whether another workgroup has cleared it already.)
 __global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ own, int64_t n_own, uint32_t* __restrict__ hists,
                                                           int64_t hists_bs, int batch) {
   const int64_t i = (int64_t)__builtin_amdgcn_workgroup_id_x() * 256 + __builtin_amdgcn_workitem_id_x();
@@ -794,7 +796,8 @@ __global__ __launch_bounds__(256) void score_sweeps_clear(uint4* __restrict__ ow
 //    8 x  60           d' 128  123 MB   35.2 / 37.4   38.7 / 38.2   39.3 / 38.8                           73.6 / 71.8
 //    2 x 150           d' 256  154 MB                                                                     60.8 / 62.7
 //   12 x 100           d' 128  307 MB                                                                    121.6 / 115.5
-// (A single layer whose K' a cache keeps from one call to the next would rather have 64 up to 270 MB: 16 x 60 thousand 54.5 / 61.7.)
+// (A single layer whose K' a cache keeps from one call to the next would rather have 64 up to 270 MB: 16 x 60 thousand 54.5 / 61.7, 1 x 290 of d' 256, 148 MB, score
+// and selection 38.5 / 43.6; the same with eight inputs in turn 50.8 / 45.1.)
 // Sequences that share one K' read it from a cache all but once: 8 x 130 thousand 22.0 / 46.5, five queries each of 4 x 130 27.4 / 30.9.
 __host__ inline bool shared_keys(int batch, int64_t kc_bs) { return batch > 1 && kc_bs == 0; }
 __host__ inline bool gemv_streams(int64_t n, int batch, int d_c, int64_t kc_bs) {
